@@ -29,17 +29,9 @@ hipError_t launch_bwd_fused_64_64(const float *g_rows, const float *own_rows, co
                                   float *grad_feat, float *partials, int *control, int B, int N, int K, int out_bcn,
                                   int *n_wg, hipStream_t s);
 hipError_t launch_bwd_fused_late_64_64(const float *g_rows, const float *own_rows, const float *pos,
-                                       const int32_t *nbr, float *partials, const int *control, int B, int N, int K,
-                                       hipStream_t s);
-
-// 128 -> 128 layers as passes over 64-channel blocks (flex_tiled_inst.hip, shapes 64x128 and 64x64)
-bool split_ok_128_128(int N, int K, int csr);
-hipError_t launch_gc_split_128_128(const float *rows_half, const float *pos, const int32_t *nbr, const int32_t *off,
-                                   const int32_t *src, const int32_t *order, const void *thetaP, float *out, int B,
-                                   int N, int K, int csr, int accumulate, hipStream_t s);
-hipError_t launch_gt_split_128_128(const float *rows_half, const float *pos, const int32_t *nbr,
-                                   const float *g_half, float *partials, int B, int N, int K, int *n_wg,
-                                   hipStream_t s);
+                                       const int32_t *nbr, const void *thetaP, const float *grad_theta,
+                                       const float *grad_bias, int Din, int Dout, float *partials, int *control, int B,
+                                       int N, int K, hipStream_t s);
 
 // layers with both widths multiples of 128 as passes over column blocks (same file, same two shapes)
 bool split_wide_ok(int N, int K, int max_width);
@@ -50,10 +42,7 @@ hipError_t launch_gt_split_wide(const float *rows, int rs, const float *pos, con
                                 int gst, float *partials, int n_hi, int n_ho, int chunks, int B, int N, int K,
                                 hipStream_t s);
 int split_wide_gt_chunks(int B, int N, int blocks);
-hipError_t launch_reduce_partials_blocks(const float *partials, int n_wg, int first, int count, int n_ho, int Din,
-                                         int Dout, float *grad_theta, float *grad_bias, hipStream_t s);
-
-hipError_t launch_reduce_partials(const float *partials, int n_wg, int DIP, int DOP, int Din,
+hipError_t launch_reduce_partials(const float *partials, int n_wg, int DIP, int DOP, int n_blocks, int n_ho, int Din,
                                   int Dout, float *grad_theta, float *grad_bias, hipStream_t s);
 
 bool gather_contract_supported(int DI, int DO)
@@ -138,65 +127,11 @@ int lean_producer_mode()
     return mode;
 }
 
-// 128 -> 128 point-major layers run as passes of the 64-wide lean kernels over channel blocks
-// (FLEX_SPLIT=0 in the environment keeps them on the single-pass fp32 kernels, for comparisons)
-static bool use_split_128(int Din, int Dout, int layout, int N, int K, int csr)
-{
-    static const bool off = [] { const char *v = getenv("FLEX_SPLIT"); return v != nullptr && v[0] == '0'; }();
-    return !off && Din == 128 && Dout == 128 && layout == FLEX_LAYOUT_BNC && split_ok_128_128(N, K, csr);
-}
-
-// Forward (transpose == 0: passes over the input-channel halves) or feature gradient (transpose == 1: passes over
-// the halves of the upstream gradient's channels) of a 128 -> 128 layer.  scratch: theta_ws_bytes(128, 128).
-static hipError_t split_gather_contract_128(const float *rows, const float *pos, const int32_t *nbr,
-                                            const int32_t *off, const int32_t *src, const int32_t *order,
-                                            const float *theta,
-                                            const float *bias, void *scratch, float *out, int B, int N, int K,
-                                            int transpose, hipStream_t s)
-{
-    float *blk_theta = (float *)scratch, *blk_bias = blk_theta + 3 * 64 * 128;
-    void *packed = (char *)scratch + sizeof(float) * 4 * 64 * 128;
-    for (int h = 0; h < 2; ++h) {
-        hipError_t e;
-        if (!transpose) {
-            e = launch_param_block((float *)theta, (float *)bias, blk_theta, blk_bias, 128, 128, 64 * h, 0, 64, 128, 0, s);
-            if (e != hipSuccess) return e;
-            e = launch_pack_theta_f16(blk_theta, blk_bias, packed, 64, 128, 64, 128, 0, s);
-        } else {
-            e = launch_param_block((float *)theta, (float *)bias, blk_theta, blk_bias, 128, 128, 0, 64 * h, 128, 64, 0, s);
-            if (e != hipSuccess) return e;
-            e = launch_pack_theta_f16(blk_theta, blk_bias, packed, 128, 64, 64, 128, 1, s);
-        }
-        if (e != hipSuccess) return e;
-        e = launch_gc_split_128_128(rows + 64 * h, pos, nbr, off, src, order, packed, out, B, N, K, transpose, h, s);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-// Parameter gradients of a 128 -> 128 layer: four [4*64 x 64] blocks.  scratch: room for one block.
-static hipError_t split_grad_theta_128(const float *rows, const float *pos, const int32_t *nbr, const float *g_rows,
-                                       float *partials, void *scratch, float *grad_theta, float *grad_bias, int B,
-                                       int N, int K, hipStream_t s)
-{
-    float *blk_theta = (float *)scratch, *blk_bias = blk_theta + 3 * 64 * 64;
-    for (int hi = 0; hi < 2; ++hi)
-        for (int ho = 0; ho < 2; ++ho) {
-            int n_wg = 0;
-            hipError_t e = launch_gt_split_128_128(rows + 64 * hi, pos, nbr, g_rows + 64 * ho, partials, B, N, K, &n_wg, s);
-            if (e != hipSuccess) return e;
-            e = launch_reduce_partials(partials, n_wg, 64, 64, 64, 64, blk_theta, blk_bias, s);
-            if (e != hipSuccess) return e;
-            e = launch_param_block(grad_theta, grad_bias, blk_theta, blk_bias, 128, 128, 64 * hi, 64 * ho, 64, 64, 1, s);
-            if (e != hipSuccess) return e;
-        }
-    return hipSuccess;
-}
-
-// Wide layers (both widths multiples of 128, not 128 -> 128 itself): the paper's network doubles the feature
-// length at every resolution stage (Sec. 4.3), so its deeper stages are of this kind.  They run as passes of the
-// 64 -> 128 (forward, feature gradient) and 64 -> 64 (parameter gradients) lean kernels over column blocks of the
-// point-major tensors.
+// Wide layers (both widths multiples of 128): the paper's network doubles the feature length at every resolution
+// stage while the point count drops by four (Sec. 4.3), so its deeper stages are of this kind.  They run as passes of
+// the 64 -> 128 (forward, feature gradient) and 64 -> 64 (parameter gradients) lean kernels over column blocks of the
+// point-major tensors (FLEX_SPLIT=0 in the environment keeps 128 -> 128 on the single-pass fp32 kernels and the wider
+// ones on the direct form, for comparisons).
 static bool split_disabled()
 {
     static const bool off = [] { const char *v = getenv("FLEX_SPLIT"); return v != nullptr && v[0] == '0'; }();
@@ -204,36 +139,22 @@ static bool split_disabled()
 }
 static bool wide_shape(int Din, int Dout)
 {
-    return !split_disabled() && Din % 128 == 0 && Dout % 128 == 0 && (Din > 128 || Dout > 128) &&
+    return !split_disabled() && Din % 128 == 0 && Dout % 128 == 0 &&
            (int64_t)(Din / 64) * (Dout / 64) <= 65535;      // one grid row of the reduction per block
 }
 // packed parameter blocks of the whole layer (forward / feature gradient)
-// channel-major 128 -> 128: transposed copies and the block passes beat the single-pass fp32 kernels that take
-// channel-major tensors directly (1M points: forward 1.9 -> 1.2 ms)
-static bool wide_route_128(int Din, int Dout, int layout)
-{
-    return Din == 128 && Dout == 128 && layout == FLEX_LAYOUT_BCN && !split_disabled();
-}
-
 static size_t wide_param_scratch_bytes(int Din, int Dout)
 {
     const size_t blocks = (size_t)(Din / 64) * (Dout / 64) / 2;     // 64 x 128 each, either way round
     return blocks * theta_f16_bytes(64, 128);
 }
 
-// Forward (transpose == 0: rows = features [.., Din], out [.., Dout]) or feature gradient (transpose == 1:
-// rows = upstream gradient [.., Dout], out = grad_feat [.., Din]; in-edge lists) of a wide layer: two launches.
-static hipError_t wide_gather_contract(const float *rows, const float *pos, const int32_t *nbr, const int32_t *off,
-                                       const int32_t *src, const int32_t *order, const float *theta,
-                                       const float *bias, void *scratch,
-                                       float *out, int B, int N, int K, int Din, int Dout, int transpose,
-                                       hipStream_t s)
+// The packing of a wide layer's parameters for launch_gc_split_wide: 64 gathered channels x 128 written ones per block.
+static void pack_wide(PrepList &prep, const float *theta, const float *bias, void *thetaF, int Din, int Dout, int Dki,
+                      int Dko, int transpose)
 {
-    const int w_in = transpose ? Dout : Din, w_out = transpose ? Din : Dout;   // gathered / written widths
-    const int n_in = w_in / 64, n_out = w_out / 128;
-    hipError_t e = launch_pack_theta_f16_blocks(theta, bias, scratch, Din, Dout, 64, 128, n_in, n_out, transpose, s);
-    if (e != hipSuccess) return e;
-    return launch_gc_split_wide(rows, w_in, pos, nbr, off, src, order, scratch, out, w_out, n_in, n_out, B, N, K, transpose, s);
+    const int w_in = transpose ? Dko : Dki, w_out = transpose ? Dki : Dko;     // gathered / written widths
+    prep.pack_theta(theta, bias, thetaF, Din, Dout, 64, 128, w_in / 64, w_out / 128, transpose);
 }
 
 // Parameter gradients of a wide layer: (Din/64) x (Dout/64) independent blocks of [4*64 x 64], two launches
@@ -244,24 +165,15 @@ static size_t wide_partial_bytes(int B, int N, int Din, int Dout)
     return align256(sizeof(float) * (size_t)blocks * split_wide_gt_chunks(B, N, blocks) * 4 * 64 * 64);
 }
 
+// (Dki, Dko): the widths of the rows, which may be padded; (Din, Dout): the parameters'.
 static hipError_t wide_grad_theta(const float *rows, const float *pos, const int32_t *nbr, const float *g_rows,
-                                  float *partials, float *grad_theta, float *grad_bias, int B, int N, int K, int Din,
-                                  int Dout, hipStream_t s)
+                                  float *partials, float *grad_theta, float *grad_bias, int B, int N, int K, int Dki,
+                                  int Dko, int Din, int Dout, hipStream_t s)
 {
-    const int n_hi = Din / 64, n_ho = Dout / 64, chunks = split_wide_gt_chunks(B, N, n_hi * n_ho);
-    hipError_t e = launch_gt_split_wide(rows, Din, pos, nbr, g_rows, Dout, partials, n_hi, n_ho, chunks, B, N, K, s);
+    const int n_hi = Dki / 64, n_ho = Dko / 64, chunks = split_wide_gt_chunks(B, N, n_hi * n_ho);
+    hipError_t e = launch_gt_split_wide(rows, Dki, pos, nbr, g_rows, Dko, partials, n_hi, n_ho, chunks, B, N, K, s);
     if (e != hipSuccess) return e;
-    return launch_reduce_partials_blocks(partials, chunks, 0, n_hi * n_ho, n_ho, Din, Dout, grad_theta, grad_bias, s);
-}
-
-// Packs (theta, bias) for launch_gather_contract in the format that kernel wants.
-static hipError_t pack_for_contract(const float *theta, const float *bias, void *thetaP, int Din,
-                                    int Dout, int transpose, int fmt, hipStream_t s)
-{
-    const int RP = transpose ? (Dout + 3) / 4 * 4 : (Din + 3) / 4 * 4;
-    const int CP = transpose ? (Din + 15) / 16 * 16 : (Dout + 15) / 16 * 16;
-    if (fmt) return launch_pack_theta_f16(theta, bias, thetaP, Din, Dout, RP, CP, transpose, s);
-    return launch_pack_theta(theta, bias, (float *)thetaP, Din, Dout, RP, CP, transpose, s);
+    return launch_reduce_partials(partials, chunks, 64, 64, n_hi * n_ho, n_ho, Din, Dout, grad_theta, grad_bias, s);
 }
 
 // Workspace bytes of the packed parameters in either format (rows padded to 4, columns to 16).
@@ -303,20 +215,20 @@ size_t grad_theta_partial_bytes(int64_t B, int64_t N, int Din, int Dout)
     return align256(sizeof(float) * (size_t)grid * 4 * pad4(Din) * pad16(Dout));
 }
 
-hipError_t launch_grad_theta(const float *rows, const float *pos, const int32_t *nbr,
-                             const float *g_rows, float *partials, float *grad_theta,
-                             float *grad_bias, int B, int N, int K, int Din, int Dout, hipStream_t s)
+// (Dki, Dko): the widths of the rows, which may be padded; (Din, Dout): the parameters'.
+static hipError_t launch_grad_theta(const float *rows, const float *pos, const int32_t *nbr, const float *g_rows,
+                                    float *partials, float *grad_theta, float *grad_bias, int B, int N, int K, int Dki,
+                                    int Dko, int Din, int Dout, hipStream_t s)
 {
     int n_wg = 0;
     hipError_t e = hipErrorNotSupported;
 #define FLEX_SHAPE(DI_, DO_, W, T, OCC, WS)                                                    \
-    if (Din == DI_ && Dout == DO_)                                                         \
+    if (Dki == DI_ && Dko == DO_)                                                         \
         e = launch_gt_##DI_##_##DO_(rows, pos, nbr, g_rows, partials, B, N, K, &n_wg, s);
 #include "flex_shapes.def"
 #undef FLEX_SHAPE
     if (e != hipSuccess) return e;
-    return launch_reduce_partials(partials, n_wg, pad4(Din), pad16(Dout), Din, Dout, grad_theta,
-                                  grad_bias, s);
+    return launch_reduce_partials(partials, n_wg, pad4(Dki), pad16(Dko), 1, 1, Din, Dout, grad_theta, grad_bias, s);
 }
 
 // ---- workspace plans -----------------------------------------------------------
@@ -337,8 +249,7 @@ static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
 {
     FwdPlan p{};
     p.tiled = gather_contract_supported(Din, Dout);
-    p.wide = ((!p.tiled && wide_shape(Din, Dout)) || wide_route_128(Din, Dout, layout)) &&
-             split_wide_ok((int)N, K, Din > Dout ? Din : Dout);
+    p.wide = wide_shape(Din, Dout) && split_wide_ok((int)N, K, Din > Dout ? Din : Dout);
     size_t at = 0;
     if (p.tiled || p.wide) {
         p.thetaP = at; at += p.wide ? wide_param_scratch_bytes(Din, Dout) : theta_ws_bytes(Din, Dout);
@@ -353,8 +264,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
 {
     BwdPlan p{};
     p.tiled = gather_contract_supported(Din, Dout) && gather_contract_supported(Dout, Din);
-    p.wide = ((!p.tiled && wide_shape(Din, Dout)) || wide_route_128(Din, Dout, layout)) &&
-             split_wide_ok((int)N, K, Din > Dout ? Din : Dout);
+    p.wide = wide_shape(Din, Dout) && split_wide_ok((int)N, K, Din > Dout ? Din : Dout);
     size_t at = 0;
     if (p.tiled || p.wide) {
         p.thetaP = at; at += p.wide ? wide_param_scratch_bytes(Din, Dout) : theta_ws_bytes(Dout, Din);
@@ -540,6 +450,12 @@ int flexconv_has_fast_path(int Din, int Dout)
     return padded_shape(Din, Dout, &a, &b) ? 2 : 0;
 }
 
+// the block passes' name in the route query: 128 -> 128 point-major has one of its own
+static int wide_route(int Din, int Dout, int layout)
+{
+    return Din == 128 && Dout == 128 && layout == FLEX_LAYOUT_BNC ? FLEX_ROUTE_SPLIT128 : FLEX_ROUTE_WIDE;
+}
+
 int flexconv_kernel_route(int op, int B, int N, int K, int Din, int Dout, int layout)
 {
     if (layout != FLEX_LAYOUT_BCN && layout != FLEX_LAYOUT_BNC) return -1;
@@ -549,15 +465,13 @@ int flexconv_kernel_route(int op, int B, int N, int K, int Din, int Dout, int la
     if (padded_shape(Din, Dout, &DIp, &DOp)) return FLEX_ROUTE_PADDED;
     if (op == FLEX_OP_CONV_FWD) {
         const FwdPlan p = plan_fwd(B, N, K, Din, Dout, layout);
-        if (p.wide) return FLEX_ROUTE_WIDE;
+        if (p.wide) return wide_route(Din, Dout, layout);
         if (!p.tiled) return FLEX_ROUTE_DIRECT;
-        if (use_split_128(Din, Dout, layout, N, K, 0)) return FLEX_ROUTE_SPLIT128;
         return gather_contract_route(Din, Dout, N, K, 0);
     }
     const BwdPlan p = plan_bwd(B, N, K, Din, Dout, layout, false);
-    if (p.wide) return FLEX_ROUTE_WIDE;
+    if (p.wide) return wide_route(Din, Dout, layout);
     if (!p.tiled) return FLEX_ROUTE_DIRECT;
-    if (use_split_128(Din, Dout, layout, N, K, 1)) return FLEX_ROUTE_SPLIT128;
     if (p.fused) return FLEX_ROUTE_LEAN_FUSED;
     return gather_contract_route(Dout, Din, N, K, 1);
 }
@@ -596,56 +510,40 @@ int flexconv_fwd(const float *feat, const float *pos, const int32_t *nbr, const 
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
     const int bcn = (layout == FLEX_LAYOUT_BCN);
-    int DIp, DOp;
-    if (padded_shape(Din, Dout, &DIp, &DOp)) {
-        const PadPlan pp = plan_pad(B, N, K, DIp, DOp, false, false);
-        if (!ws_ok(workspace, workspace_bytes, pp.total)) return FLEX_ERR_WORKSPACE;
-        float *featP = (float *)(ws + pp.featP), *thetaP = (float *)(ws + pp.thetaP), *biasP = thetaP + 3 * DIp * DOp;
-        float *outP = (float *)(ws + pp.outP);
-        FLEX_HIP(launch_copy_rows(feat, featP, B, N, Din, DIp, bcn, 0, s));
-        FLEX_HIP(launch_fill_zero(thetaP, sizeof(float) * (size_t)4 * DIp * DOp, s));
-        FLEX_HIP(launch_param_block(thetaP, biasP, (float *)theta, (float *)bias, DIp, DOp, 0, 0, Din, Dout, 1, s));
-        const int st = flexconv_fwd(featP, pos, nbr, thetaP, biasP, outP, B, N, K, DIp, DOp, FLEX_LAYOUT_BNC,
-                                    ws + pp.sub, pp.sub_bytes, stream);
-        if (st != FLEX_OK) return st;
-        FLEX_HIP(launch_copy_rows(outP, out, B, N, DOp, Dout, 0, bcn, s));
-        return FLEX_OK;
-    }
-    const FwdPlan p = plan_fwd(B, N, K, Din, Dout, layout);
-    if (!ws_ok(workspace, workspace_bytes, p.total)) return FLEX_ERR_WORKSPACE;
-    if (p.wide) {
-        const float *rows = feat;
-        float *dst = out;
-        if (bcn) {
-            FLEX_HIP(launch_bcn_to_bnc(feat, (float *)(ws + p.featT), B, Din, N, s));
-            rows = (float *)(ws + p.featT);
-            dst = (float *)(ws + p.outT);
-        }
-        FLEX_HIP(wide_gather_contract(rows, pos, nbr, nullptr, nullptr, nullptr, theta, bias, ws + p.thetaP, dst, B, N, K,
-                                      Din, Dout, 0, s));
-        if (bcn) FLEX_HIP(launch_bnc_to_bcn(dst, out, B, Dout, N, s));
-        return FLEX_OK;
-    }
-    if (!p.tiled) {
+    int Dki = Din, Dko = Dout;               // the widths the kernels run at
+    const bool padded = padded_shape(Din, Dout, &Dki, &Dko);
+    PadPlan pp{};
+    if (padded) pp = plan_pad(B, N, K, Dki, Dko, false, false);
+    const FwdPlan p = plan_fwd(B, N, K, Dki, Dko, padded ? FLEX_LAYOUT_BNC : layout);
+    if (!ws_ok(workspace, workspace_bytes, padded ? pp.total : p.total)) return FLEX_ERR_WORKSPACE;
+    if (!p.tiled && !p.wide) {
         FLEX_HIP(launch_generic_fwd(feat, pos, nbr, theta, bias, out, B, N, K, Din, Dout, !bcn, s));
         return FLEX_OK;
     }
-    void *thetaP = ws + p.thetaP;
-    if (use_split_128(Din, Dout, layout, N, K, 0)) {
-        FLEX_HIP(split_gather_contract_128(feat, pos, nbr, nullptr, nullptr, nullptr, theta, bias, thetaP, out, B, N, K, 0,
-                                           s));
-        return FLEX_OK;
-    }
-    const int fmt = gather_contract_theta_format(Din, Dout, N, K, 0);
-    FLEX_HIP(pack_for_contract(theta, bias, thetaP, Din, Dout, 0, fmt, s));
+    char *sub = ws + pp.sub;
+    void *thetaP = sub + p.thetaP;
+    PrepList prep;
     const float *rows = feat;
-    if (bcn) {
-        float *featT = (float *)(ws + p.featT);
-        FLEX_HIP(launch_bcn_to_bnc(feat, featT, B, Din, N, s));
-        rows = featT;
+    if (padded || bcn) {
+        float *copy = (float *)(padded ? ws + pp.featP : sub + p.featT);
+        prep.copy(feat, copy, B, N, Din, Dki, bcn, 0);
+        rows = copy;
     }
-    FLEX_HIP(launch_gather_contract(rows, pos, nbr, nullptr, nullptr, nullptr, thetaP, fmt, out, B, N, K, Din,
-                                    Dout, 0, bcn, s));
+    float *dst = padded ? (float *)(ws + pp.outP) : (bcn && p.wide) ? (float *)(sub + p.outT) : out;
+    if (p.wide) {
+        pack_wide(prep, theta, bias, thetaP, Din, Dout, Dki, Dko, 0);
+        FLEX_HIP(prep.launch(s));
+        FLEX_HIP(launch_gc_split_wide(rows, Dki, pos, nbr, nullptr, nullptr, nullptr, thetaP, dst, Dko, Dki / 64, Dko / 128,
+                                      B, N, K, 0, s));
+    } else {
+        const int fmt = gather_contract_theta_format(Dki, Dko, N, K, 0);
+        if (fmt) prep.pack_theta(theta, bias, thetaP, Din, Dout, pad4(Dki), pad16(Dko), 1, 1, 0);
+        else FLEX_HIP(launch_pack_theta(theta, bias, (float *)thetaP, Din, Dout, pad4(Dki), pad16(Dko), 0, s));
+        FLEX_HIP(prep.launch(s));
+        FLEX_HIP(launch_gather_contract(rows, pos, nbr, nullptr, nullptr, nullptr, thetaP, fmt, dst, B, N, K, Dki, Dko, 0,
+                                        bcn && !padded, s));
+    }
+    if (dst != out) FLEX_HIP(launch_copy_rows(dst, out, B, N, Dko, Dout, 0, bcn, s));
     return FLEX_OK;
 }
 
@@ -723,128 +621,74 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
     const int bcn = (layout == FLEX_LAYOUT_BCN);
-    int DIp, DOp;
-    if (padded_shape(Din, Dout, &DIp, &DOp)) {
-        const PadPlan pp = plan_pad(B, N, K, DIp, DOp, true, build);
-        if (!ws_ok(workspace, workspace_bytes, pp.total)) return FLEX_ERR_WORKSPACE;
-        float *featP = (float *)(ws + pp.featP), *gP = (float *)(ws + pp.gP), *gfP = (float *)(ws + pp.gfP);
-        float *thetaP = (float *)(ws + pp.thetaP), *biasP = thetaP + 3 * DIp * DOp;
-        float *gtP = (float *)(ws + pp.gtP), *gbP = gtP + 3 * DIp * DOp;
-        FLEX_HIP(launch_copy_rows(feat, featP, B, N, Din, DIp, bcn, 0, s));
-        FLEX_HIP(launch_copy_rows(grad_out, gP, B, N, Dout, DOp, bcn, 0, s));
-        FLEX_HIP(launch_fill_zero(thetaP, sizeof(float) * (size_t)4 * DIp * DOp, s));
-        FLEX_HIP(launch_param_block(thetaP, biasP, (float *)theta, (float *)bias, DIp, DOp, 0, 0, Din, Dout, 1, s));
-        const int st = flexconv_bwd(featP, pos, nbr, thetaP, biasP, gP, grad_feat ? gfP : nullptr,
-                                    grad_theta ? gtP : nullptr, grad_theta ? gbP : nullptr, in_off, in_src, B, N, K,
-                                    DIp, DOp, FLEX_LAYOUT_BNC, ws + pp.sub, pp.sub_bytes, stream);
-        if (st != FLEX_OK) return st;
-        if (grad_feat) FLEX_HIP(launch_copy_rows(gfP, grad_feat, B, N, DIp, Din, 0, bcn, s));
-        if (grad_theta) FLEX_HIP(launch_param_block(gtP, gbP, grad_theta, grad_bias, DIp, DOp, 0, 0, Din, Dout, 0, s));
-        return FLEX_OK;
-    }
-    const BwdPlan p = plan_bwd(B, N, K, Din, Dout, layout, build);
-    if (!ws_ok(workspace, workspace_bytes, p.total)) return FLEX_ERR_WORKSPACE;
-    if (p.wide) {
-        const float *rows = feat, *g_rows = grad_out;
-        if (bcn) {
-            FLEX_HIP(launch_bcn_to_bnc(grad_out, (float *)(ws + p.gT), B, Dout, N, s));
-            g_rows = (float *)(ws + p.gT);
-            if (grad_theta) {
-                FLEX_HIP(launch_bcn_to_bnc(feat, (float *)(ws + p.featT), B, Din, N, s));
-                rows = (float *)(ws + p.featT);
-            }
-        }
-        if (grad_theta)
-            FLEX_HIP(wide_grad_theta(rows, pos, nbr, g_rows, (float *)(ws + p.partials), grad_theta, grad_bias, B, N,
-                                     K, Din, Dout, s));
-        if (grad_feat) {
-            if (build) {
-                int32_t *off = (int32_t *)(ws + p.in_off), *src = (int32_t *)(ws + p.in_src);
-                FLEX_HIP(launch_inedges_build(nbr, B, N, K, off, src, ws + p.inedge_ws, s));
-                in_off = off;
-                in_src = src;
-            }
-            float *dst = bcn ? (float *)(ws + p.gfT) : grad_feat;
-            int32_t *order = (int32_t *)(ws + p.order);
-            FLEX_HIP(launch_inedges_order(in_off, B, N, order, s));
-            FLEX_HIP(wide_gather_contract(g_rows, pos, nullptr, in_off, in_src, order, theta, bias, ws + p.thetaP, dst,
-                                          B, N, K, Din, Dout, 1, s));
-            if (bcn) FLEX_HIP(launch_bnc_to_bcn(dst, grad_feat, B, Din, N, s));
-        }
-        return FLEX_OK;
-    }
-    if (!p.tiled) {
+    int Dki = Din, Dko = Dout;               // the widths the kernels run at
+    const bool padded = padded_shape(Din, Dout, &Dki, &Dko);
+    PadPlan pp{};
+    if (padded) pp = plan_pad(B, N, K, Dki, Dko, true, build);
+    const BwdPlan p = plan_bwd(B, N, K, Dki, Dko, padded ? FLEX_LAYOUT_BNC : layout, build);
+    if (!ws_ok(workspace, workspace_bytes, padded ? pp.total : p.total)) return FLEX_ERR_WORKSPACE;
+    if (!p.tiled && !p.wide) {
         FLEX_HIP(launch_generic_bwd(feat, pos, nbr, theta, bias, grad_out, grad_feat, grad_theta,
                                     grad_bias, B, N, K, Din, Dout, !bcn, s));
         return FLEX_OK;
     }
+    char *sub = ws + pp.sub;
+    if (build) {
+        int32_t *off = (int32_t *)(sub + p.in_off), *src = (int32_t *)(sub + p.in_src);
+        FLEX_HIP(launch_inedges_build(nbr, B, N, K, off, src, sub + p.inedge_ws, s));
+        in_off = off;
+        in_src = src;
+    }
+    void *thetaP = sub + p.thetaP;
+    float *partials = (float *)(sub + p.partials);
+    int32_t *order = (int32_t *)(sub + p.order);
+    int *control = (int *)(sub + p.flag);
+    const bool fused = p.fused && grad_theta && grad_feat;
+    const int fmt = p.wide ? 1 : gather_contract_theta_format(Dko, Dki, N, K, 1);
+    PrepList prep;
     const float *rows = feat, *g_rows = grad_out;
-    if (bcn) {
-        float *gT = (float *)(ws + p.gT);
-        FLEX_HIP(launch_bcn_to_bnc(grad_out, gT, B, Dout, N, s));
-        g_rows = gT;
-        if (grad_theta) {
-            float *featT = (float *)(ws + p.featT);
-            FLEX_HIP(launch_bcn_to_bnc(feat, featT, B, Din, N, s));
-            rows = featT;
-        }
-    }
-    if (p.fused && grad_theta && grad_feat) {
-        if (build) {
-            int32_t *off = (int32_t *)(ws + p.in_off), *src = (int32_t *)(ws + p.in_src);
-            FLEX_HIP(launch_inedges_build(nbr, B, N, K, off, src, ws + p.inedge_ws, s));
-            in_off = off;
-            in_src = src;
-        }
-        void *thetaP = ws + p.thetaP;
-        int32_t *order = (int32_t *)(ws + p.order);
-        int *flag = (int *)(ws + p.flag);
-        float *partials = (float *)(ws + p.partials);
-        FLEX_HIP(launch_inedges_order(in_off, B, N, order, s));
-        FLEX_HIP(launch_fill_zero(flag, sizeof(int) * FUSED_FLAG_INTS, s));
-        FLEX_HIP(pack_for_contract(theta, bias, thetaP, Din, Dout, 1, 1, s));
-        int n_wg = 0;
-        FLEX_HIP(launch_bwd_fused_64_64(g_rows, rows, pos, nbr, in_off, in_src, order, thetaP, grad_feat, partials,
-                                        flag, B, N, K, bcn, &n_wg, s));
-        FLEX_HIP(launch_reduce_partials(partials, n_wg, pad4(Din), pad16(Dout), Din, Dout, grad_theta, grad_bias, s));
-        // is the result resolved by the f16 halves?  if not (decided on the device), the stand-alone kernel and a
-        // second reduction run; both return at once otherwise
-        const float *rscale = reinterpret_cast<const float *>(reinterpret_cast<const char *>(thetaP) +
-                                                              theta_f16_rscale_offset(pad4(Dout), pad16(Din)));
-        FLEX_HIP(launch_fused_bwd_check(flag, n_wg, rscale, grad_theta, grad_bias, s));
-        FLEX_HIP(launch_bwd_fused_late_64_64(g_rows, rows, pos, nbr, partials, flag, B, N, K, s));
-        FLEX_HIP(launch_reduce_partials_if(flag, FUSED_UNRESOLVED, partials, n_wg, pad4(Din), pad16(Dout), Din, Dout,
-                                           grad_theta, grad_bias, s));
-        return FLEX_OK;
-    }
-    if (grad_theta) {
-        if (use_split_128(Din, Dout, layout, N, K, 0))
-            FLEX_HIP(split_grad_theta_128(rows, pos, nbr, g_rows, (float *)(ws + p.partials), ws + p.thetaP,
-                                          grad_theta, grad_bias, B, N, K, s));
-        else
-            FLEX_HIP(launch_grad_theta(rows, pos, nbr, g_rows, (float *)(ws + p.partials), grad_theta,
-                                       grad_bias, B, N, K, Din, Dout, s));
+    if (padded || bcn) {
+        float *g_copy = (float *)(padded ? ws + pp.gP : sub + p.gT), *f_copy = (float *)(padded ? ws + pp.featP : sub + p.featT);
+        prep.copy(grad_out, g_copy, B, N, Dout, Dko, bcn, 0);
+        if (grad_theta) prep.copy(feat, f_copy, B, N, Din, Dki, bcn, 0);
+        g_rows = g_copy;
+        rows = f_copy;
     }
     if (grad_feat) {
-        if (build) {
-            int32_t *off = (int32_t *)(ws + p.in_off), *src = (int32_t *)(ws + p.in_src);
-            FLEX_HIP(launch_inedges_build(nbr, B, N, K, off, src, ws + p.inedge_ws, s));
-            in_off = off;
-            in_src = src;
-        }
-        void *thetaP = ws + p.thetaP;
-        int32_t *order = (int32_t *)(ws + p.order);
-        FLEX_HIP(launch_inedges_order(in_off, B, N, order, s));
-        if (use_split_128(Din, Dout, layout, N, K, 1)) {
-            FLEX_HIP(split_gather_contract_128(g_rows, pos, nullptr, in_off, in_src, order, theta, bias, thetaP,
-                                               grad_feat, B, N, K, 1, s));
-            return FLEX_OK;
-        }
-        const int fmt = gather_contract_theta_format(Dout, Din, N, K, 1);
-        FLEX_HIP(pack_for_contract(theta, bias, thetaP, Din, Dout, 1, fmt, s));
-        FLEX_HIP(launch_gather_contract(g_rows, pos, nullptr, in_off, in_src, order, thetaP, fmt, grad_feat, B, N,
-                                        K, Dout, Din, 1, bcn, s));
+        if (p.wide) pack_wide(prep, theta, bias, thetaP, Din, Dout, Dki, Dko, 1);
+        else if (fmt) prep.pack_theta(theta, bias, thetaP, Din, Dout, pad4(Dko), pad16(Dki), 1, 1, 1);
+        else FLEX_HIP(launch_pack_theta(theta, bias, (float *)thetaP, Din, Dout, pad4(Dko), pad16(Dki), 1, s));
+        prep.order(in_off, B, N, order);
     }
+    if (fused) prep.clear(control, FUSED_FLAG_INTS);
+    FLEX_HIP(prep.launch(s));
+    float *dst = padded ? (float *)(ws + pp.gfP) : (bcn && p.wide) ? (float *)(sub + p.gfT) : grad_feat;
+    const int out_bcn = bcn && !padded;
+    if (fused) {
+        int n_wg = 0;
+        FLEX_HIP(launch_bwd_fused_64_64(g_rows, rows, pos, nbr, in_off, in_src, order, thetaP, dst, partials, control, B,
+                                        N, K, out_bcn, &n_wg, s));
+        FLEX_HIP(launch_reduce_partials_fused(partials, n_wg, control, Din, Dout, grad_theta, grad_bias, s));
+        // is the result resolved by the f16 halves, and did no row overflow them?  if not (decided on the device), the
+        // stand-alone kernel and a second reduction run; both return at once otherwise
+        FLEX_HIP(launch_bwd_fused_late_64_64(g_rows, rows, pos, nbr, thetaP, grad_theta, grad_bias, Din, Dout, partials,
+                                             control, B, N, K, s));
+        FLEX_HIP(launch_reduce_partials_if(control, partials, n_wg, 64, 64, Din, Dout, grad_theta, grad_bias, s));
+    } else {
+        if (grad_theta && p.wide)
+            FLEX_HIP(wide_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, Dki, Dko, Din, Dout,
+                                     s));
+        else if (grad_theta)
+            FLEX_HIP(launch_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, Dki, Dko, Din,
+                                       Dout, s));
+        if (grad_feat && p.wide)
+            FLEX_HIP(launch_gc_split_wide(g_rows, Dko, pos, nullptr, in_off, in_src, order, thetaP, dst, Dki, Dko / 64,
+                                          Dki / 128, B, N, K, 1, s));
+        else if (grad_feat)
+            FLEX_HIP(launch_gather_contract(g_rows, pos, nullptr, in_off, in_src, order, thetaP, fmt, dst, B, N, K, Dko,
+                                            Dki, 1, out_bcn, s));
+    }
+    if (grad_feat && dst != grad_feat) FLEX_HIP(launch_copy_rows(dst, grad_feat, B, N, Dki, Din, 0, bcn, s));
     return FLEX_OK;
 }
 
@@ -1064,10 +908,13 @@ int flexconv_bwd_pos(const float *feat, const int32_t *nbr, const float *theta, 
     if (p.blocked) {
         const int n_hi = (Din + 63) / 64, n_ho = (Dout + 63) / 64;
         const size_t blk_bytes = align256(sizeof(float) * (size_t)B * N * 64);
-        for (int hi = 0; hi < n_hi; ++hi)
-            FLEX_HIP(launch_copy_rows(feat, (float *)(ws + p.featT + hi * blk_bytes), B, N, Din, 64, bcn, 0, s, 64 * hi));
-        for (int ho = 0; ho < n_ho; ++ho)
-            FLEX_HIP(launch_copy_rows(grad_out, (float *)(ws + p.gT + ho * blk_bytes), B, N, Dout, 64, bcn, 0, s, 64 * ho));
+        PrepList prep;
+        for (int i = 0; i < n_hi + n_ho; ++i) {
+            if (prep.n == PREP_MAX_JOBS) FLEX_HIP(prep.launch(s));
+            if (i < n_hi) prep.copy(feat, (float *)(ws + p.featT + i * blk_bytes), B, N, Din, 64, bcn, 0, 64 * i);
+            else prep.copy(grad_out, (float *)(ws + p.gT + (i - n_hi) * blk_bytes), B, N, Dout, 64, bcn, 0, 64 * (i - n_hi));
+        }
+        FLEX_HIP(prep.launch(s));
         if (build) {
             int32_t *off = (int32_t *)(ws + p.in_off), *src = (int32_t *)(ws + p.in_src);
             FLEX_HIP(launch_inedges_build(nbr, B, N, K, off, src, ws + p.inedge_ws, s));
@@ -1075,14 +922,13 @@ int flexconv_bwd_pos(const float *feat, const int32_t *nbr, const float *theta, 
             in_src = src;
         }
         void *thC = ws + p.thetaC, *thN = ws + p.thetaN;
-        float *thB = (float *)(ws + p.thB);
         for (int hi = 0; hi < n_hi; ++hi)
             for (int ho = 0; ho < n_ho; ++ho) {
                 const float *f_blk = (const float *)(ws + p.featT + hi * blk_bytes);
                 const float *g_blk = (const float *)(ws + p.gT + ho * blk_bytes);
-                FLEX_HIP(launch_theta_block_padded(theta, thB, Din, Dout, 64 * hi, 64 * ho, 64, 64, s));
-                FLEX_HIP(launch_pack_theta_pos(thB, thC, 64, 64, 64, 64, 0, s));
-                FLEX_HIP(launch_pack_theta_pos(thB, thN, 64, 64, 64, 64, 1, s));
+                prep.pack_theta_pos(theta, thC, Din, Dout, 64 * hi, 64 * ho, 64, 64, 0);
+                prep.pack_theta_pos(theta, thN, Din, Dout, 64 * hi, 64 * ho, 64, 64, 1);
+                FLEX_HIP(prep.launch(s));
                 FLEX_HIP(launch_grad_pos_term(f_blk, nbr, nullptr, nullptr, thC, g_blk, grad_pos, -1.f,
                                               (hi | ho) != 0, B, N, K, 64, 64, 0, s));
                 FLEX_HIP(launch_grad_pos_term(g_blk, nullptr, in_off, in_src, thN, f_blk, grad_pos, 1.f, 1, B, N, K, 64,
@@ -1095,9 +941,10 @@ int flexconv_bwd_pos(const float *feat, const int32_t *nbr, const float *theta, 
         return FLEX_OK;
     }
     const float *rows = feat, *g_rows = grad_out;
+    PrepList prep;
     if (bcn) {
-        FLEX_HIP(launch_bcn_to_bnc(feat, (float *)(ws + p.featT), B, Din, N, s));
-        FLEX_HIP(launch_bcn_to_bnc(grad_out, (float *)(ws + p.gT), B, Dout, N, s));
+        prep.copy(feat, (float *)(ws + p.featT), B, N, Din, Din, 1, 0);
+        prep.copy(grad_out, (float *)(ws + p.gT), B, N, Dout, Dout, 1, 0);
         rows = (const float *)(ws + p.featT);
         g_rows = (const float *)(ws + p.gT);
     }
@@ -1108,8 +955,9 @@ int flexconv_bwd_pos(const float *feat, const int32_t *nbr, const float *theta, 
         in_src = src;
     }
     void *thC = ws + p.thetaC, *thN = ws + p.thetaN;
-    FLEX_HIP(launch_pack_theta_pos(theta, thC, Din, Dout, pad32(pad4(Din)), pad16(Dout), 0, s));
-    FLEX_HIP(launch_pack_theta_pos(theta, thN, Din, Dout, pad32(pad4(Dout)), pad16(Din), 1, s));
+    prep.pack_theta_pos(theta, thC, Din, Dout, 0, 0, pad32(pad4(Din)), pad16(Dout), 0);
+    prep.pack_theta_pos(theta, thN, Din, Dout, 0, 0, pad32(pad4(Dout)), pad16(Din), 1);
+    FLEX_HIP(prep.launch(s));
     // centre term: -<(sum_k feat[n_k(x)])^T theta_d, grad_out[x]>, then neighbour term added on top
     FLEX_HIP(launch_grad_pos_term(rows, nbr, nullptr, nullptr, thC, g_rows, grad_pos, -1.f, 0, B, N, K, Din, Dout, 0, s));
     FLEX_HIP(launch_grad_pos_term(g_rows, nullptr, in_off, in_src, thN, rows, grad_pos, 1.f, 1, B, N, K, Dout, Din, 1, s));

@@ -32,11 +32,32 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 hipError_t launch_pack_theta(const float *theta, const float *bias, float *thetaP,
                              int Din, int Dout, int RP, int CP, int transpose, hipStream_t s);
 
-// Split-half (f16 hi/lo) fragment form of the same matrix for the wave-specialised
-// kernels; layout documented at pack_theta_f16_kernel.  RP = padded rows per j, CP =
-// padded columns (multiple of 16).
-hipError_t launch_pack_theta_f16(const float *theta, const float *bias, void *thetaF, int Din,
-                                 int Dout, int RP, int CP, int transpose, hipStream_t s);
+// The steps in front of a call's main kernels as jobs of one launch (flex_prep.hip): collect, then launch once.
+// None of a list's jobs may read what another one writes.
+constexpr int PACK_MAX_KD = 512, PREP_MAX_JOBS = 6, PREP_JOB_BYTES = 80;
+struct PrepList {
+    int n = 0;
+    bool bad = false;
+    alignas(8) char storage[PREP_MAX_JOBS * PREP_JOB_BYTES];
+    // Split-half (f16 hi/lo) fragment form of the parameters for the wave-specialised kernels (layout: flex_prep.hip).
+    // RP = rows per component (4 * RP <= PACK_MAX_KD), CP = columns (a multiple of 16) of a block; block (i, j) of
+    // n_i x n_j (rows RP * i.., columns CP * j..) lands theta_f16_bytes(RP, CP) * (j * n_i + i) bytes into thetaF.
+    // transpose == 0: rows = input channels, columns = output channels; 1: the other way round.  Din, Dout: the real
+    // tensor's widths; what a block reaches beyond them is zero.
+    void pack_theta(const float *theta, const float *bias, void *thetaF, int Din, int Dout, int RP, int CP, int n_i,
+                    int n_j, int transpose);
+    // The location gradient's form of theta's block of input channels ci0.. and output channels co0.. (KDP deep, CP
+    // columns; zero outside theta).
+    void pack_theta_pos(const float *theta, void *thetaF, int Din, int Dout, int ci0, int co0, int KDP, int CP,
+                        int transpose);
+    // order[b*N + p] = point at position p: the cloud's points sorted by in-edge list length inside windows of nearby
+    // points (the walking order of the gather kernels over in-edge lists); inedges_order_bytes(B * N)
+    void order(const int32_t *in_off, int B, int N, int32_t *order);
+    // dst[b, n, c] = src[b, n, c_off + c] where that channel exists, else 0 (c < Cd); *_bcn: that tensor is channel-major
+    void copy(const float *src, float *dst, int B, int N, int Cs, int Cd, int src_bcn, int dst_bcn, int c_off = 0);
+    void clear(void *dst, int words);
+    hipError_t launch(hipStream_t s);
+};
 size_t theta_f16_exp_offset(int RP, int CP);
 size_t theta_f16_rscale_offset(int RP, int CP);
 size_t theta_f16_bytes(int RP, int CP);
@@ -49,17 +70,14 @@ size_t theta_f16_bytes(int RP, int CP);
 constexpr int FUSED_FLAG_INTS = 64, FUSED_RECORD_INTS = 128, FUSED_MAX_WG = 1024;
 constexpr int FUSED_OVERFLOW = 1, FUSED_UNRESOLVED = 2;
 constexpr size_t fused_control_bytes() { return sizeof(int) * (size_t)(FUSED_FLAG_INTS + FUSED_RECORD_INTS * FUSED_MAX_WG); }
-hipError_t launch_fused_bwd_check(int *control, int n_wg, const float *rscale, const float *grad_theta,
-                                  const float *grad_bias, hipStream_t s);
-hipError_t launch_reduce_partials_if(const int *flag, int want, const float *partials, int n_wg, int DIP, int DOP,
-                                     int Din, int Dout, float *grad_theta, float *grad_bias, hipStream_t s);
-hipError_t launch_pack_theta_f16_blocks(const float *theta, const float *bias, void *thetaF_all, int Din, int Dout,
-                                        int r_blk, int c_blk, int n_i, int n_j, int transpose, hipStream_t s);
+constexpr int FUSED_Q_INT = 96;      // record c, words 96 and 97: Q_c (reduce_partials_fused_kernel)
+hipError_t launch_reduce_partials_fused(const float *partials, int n_wg, int *control, int Din, int Dout,
+                                        float *grad_theta, float *grad_bias, hipStream_t s);
+hipError_t launch_reduce_partials_if(const int *flag, const float *partials, int n_wg, int DIP, int DOP, int Din,
+                                     int Dout, float *grad_theta, float *grad_bias, hipStream_t s);
 
 // Location gradient (flex_ws.hpp grad_pos_kernel): Theta_d fragments and one term of the gradient.
 // launch_grad_pos_term returns hipErrorNotSupported when (DI, DO, N, K) has no lean kernel.
-hipError_t launch_pack_theta_pos(const float *theta, void *thetaF, int Din, int Dout, int KDP, int CP,
-                                 int transpose, hipStream_t s);
 size_t theta_pos_exp_offset(int KDP, int CP);
 size_t theta_pos_bytes(int KDP, int CP);
 hipError_t launch_grad_pos_term(const float *rows, const int32_t *nbr, const int32_t *off, const int32_t *src,
@@ -71,13 +89,9 @@ hipError_t launch_generic_bwd_pos(const float *feat, const int32_t *nbr, const f
                                   const float *grad_out, float *grad_pos, int B, int N, int K, int Din,
                                   int Dout, int bnc, hipStream_t s);
 
-// [B,C,N] -> [B,N,C] and back.
+// A PrepList of one copy.
 hipError_t launch_copy_rows(const float *src, float *dst, int B, int N, int Cs, int Cd, int src_bcn, int dst_bcn,
                             hipStream_t s, int c_off = 0);
-hipError_t launch_theta_block_padded(const float *theta, float *blk, int Din, int Dout, int r0, int c0, int nr, int nc,
-                                     hipStream_t s);
-hipError_t launch_bcn_to_bnc(const float *src, float *dst, int B, int C, int N, hipStream_t s);
-hipError_t launch_bnc_to_bcn(const float *src, float *dst, int B, int C, int N, hipStream_t s);
 
 // Tiled matrix-core path.  `rows` is point-major [B*N, DI].  Returns
 // hipErrorNotSupported when (DI,DO) has no instantiation.
@@ -85,8 +99,8 @@ hipError_t launch_bnc_to_bcn(const float *src, float *dst, int B, int C, int N, 
 //   csr == 1: in-edge lists (off,src), dp = pos[centre]-pos[src]
 //   theta_fmt: what thetaP holds, as answered by gather_contract_theta_format for the same
 //   (DI, DO, N, K, csr): 0 = fp32 ThetaP (launch_pack_theta), 1 = split-half fragments
-//   (launch_pack_theta_f16).
-//   order (csr == 1 only): the walking order from launch_inedges_order for these lists
+//   (PrepList::pack_theta).
+//   order (csr == 1 only): the walking order of these lists (PrepList::order)
 hipError_t launch_gather_contract(const float *rows, const float *pos, const int32_t *nbr,
                                   const int32_t *off, const int32_t *src, const int32_t *order,
                                   const void *thetaP, int theta_fmt, float *out, int B, int N, int K, int DI,
@@ -101,12 +115,7 @@ bool contract_in_fp32();
 // 2 (default) = lean producers, three per consumer wave where the shape allows.
 int lean_producer_mode();
 
-// grad_theta / grad_bias: per-workgroup partial sums into `partials`
-// ([n_wg, KD, DOP] floats), then a reduction into the two outputs.
-hipError_t launch_grad_theta(const float *rows, const float *pos, const int32_t *nbr,
-                             const float *g_rows, float *partials, float *grad_theta,
-                             float *grad_bias, int B, int N, int K, int Din, int Dout,
-                             hipStream_t s);
+// Workspace of the per-workgroup partial sums of grad_theta / grad_bias ([n_wg, KD, DOP] floats).
 size_t grad_theta_partial_bytes(int64_t B, int64_t N, int Din, int Dout);
 
 // Generic (any Din/Dout) direct-form kernels; strides select the layout.
@@ -124,10 +133,7 @@ hipError_t launch_inedges_build(const int32_t *nbr, int B, int N, int K, int32_t
 hipError_t launch_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int B, int N, int Ns, int K,
                                     int32_t *in_off, int32_t *in_src, void *ws, hipStream_t s);
 size_t inedges_ws_bytes(int64_t BN);
-// order[b*N + p] = point at position p: the cloud's points sorted by in-edge list length inside windows of nearby
-// points (the walking order of the gather kernels over in-edge lists)
 size_t inedges_order_bytes(int64_t BN);
-hipError_t launch_inedges_order(const int32_t *in_off, int B, int N, int32_t *order, hipStream_t s);
 size_t exclusive_scan_ws_bytes(int64_t n);
 hipError_t launch_exclusive_scan_i32(const int32_t *cnt, int32_t *off, int64_t n, void *ws, hipStream_t s);
 size_t knn_ws_bytes(int B, int N);
@@ -173,8 +179,6 @@ hipError_t launch_upsample_check_sel(const int32_t *sel, const int32_t *inv, int
 
 hipError_t launch_count_bad(const int32_t *nbr, int64_t count, int N, int32_t *bad, hipStream_t s);
 hipError_t launch_fill_zero(void *ptr, size_t bytes, hipStream_t s);
-hipError_t launch_param_block(float *theta, float *bias, float *blk_theta, float *blk_bias, int R, int C, int r0,
-                              int c0, int nr, int nc, int insert, hipStream_t s);
 size_t idiss_ws_bytes(int B, int N);
 size_t distinct_ws_bytes(int B, int Ns);
 hipError_t launch_selection_make_distinct(int32_t *sel, int B, int N, int Ns, void *ws, hipStream_t s);

@@ -18,7 +18,7 @@ using S = TileShape<FLEX_DI, FLEX_DO, FLEX_W, FLEX_T, FLEX_OCC>;
 static constexpr int WG_PER_CU = (FLEX_OCC * 4) / FLEX_W > 0 ? (FLEX_OCC * 4) / FLEX_W : 1;
 
 // 1 if this (shape, K, list form) runs the wave-specialised kernel with the split-half
-// contraction, i.e. wants the parameters from launch_pack_theta_f16; 0: fp32 ThetaP.
+// contraction, i.e. wants the parameters from PrepList::pack_theta; 0: fp32 ThetaP.
 // the lean fixed-K producers take this neighbour tensor: 32-bit byte offsets in a cloud (any K: batches of 8
 // slots, the last one of a tile masked past K)
 static bool lean_fixed_ok(int N, int K)
@@ -220,25 +220,9 @@ bool bwd_fused_ok_64_64(int N, int K)
     return !off && !contract_in_fp32() && lean_fixed_ok(N, K) && gc_route(N, K, 1, 1) == 3;
 }
 
-// The stand-alone parameter-gradient kernel over the same grid, run on the device only if *control == want.
-static hipError_t launch_gt_if(const int *control, int want, const float *own_rows, const float *pos,
-                               const int32_t *nbr, const float *g_rows, float *partials, int N, int K, int tpc, int tot,
-                               int n_wg, hipStream_t s)
-{
-    using WL = WsGeom<S, 2, 2>;
-    if (K % 8 == 0)
-        hipLaunchKernelGGL((grad_theta_lean_if_kernel<S, false>), dim3(n_wg), dim3(WL::NT), 0, s, control, want,
-                           own_rows, pos, nbr, g_rows, partials, N, K, tpc, tot);
-    else
-        hipLaunchKernelGGL((grad_theta_lean_if_kernel<S, true>), dim3(n_wg), dim3(WL::NT), 0, s, control, want,
-                           own_rows, pos, nbr, g_rows, partials, N, K, tpc, tot);
-    return hipGetLastError();
-}
-
 // g_rows / own_rows: upstream gradient and features, point-major; partials: *n_wg blocks of [4*64 x 64];
 // control: fused_control_bytes() whose flag word the caller has zeroed on the stream.  Leaves the partials of the
-// parameter gradients (the one-pass kernel's, or the stand-alone kernel's if a row overflowed) and the workgroups'
-// records for the check after the reduction.
+// parameter gradients and the workgroups' records for the check after the reduction.
 hipError_t launch_bwd_fused_64_64(const float *g_rows, const float *own_rows, const float *pos, const int32_t *nbr,
                                   const int32_t *off, const int32_t *src, const int32_t *order, const void *thetaP,
                                   float *grad_feat, float *partials, int *control, int B, int N, int K, int out_bcn,
@@ -260,54 +244,25 @@ hipError_t launch_bwd_fused_64_64(const float *g_rows, const float *own_rows, co
     if (out_bcn) hipLaunchKernelGGL((bwd_fused_lean_kernel<S, true>), g, dim3(F::NT), 0, s, FLEX_FUSED_ARGS);
     else hipLaunchKernelGGL((bwd_fused_lean_kernel<S, false>), g, dim3(F::NT), 0, s, FLEX_FUSED_ARGS);
 #undef FLEX_FUSED_ARGS
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_gt_if(control, FUSED_OVERFLOW, own_rows, pos, nbr, g_rows, partials, N, K, tpc, tot, *n_wg, s);
+    return hipGetLastError();
 }
 
-// The hand-over after the check: the stand-alone kernel again, run only if the check set FUSED_UNRESOLVED.
+// The hand-over after the first reduction (grad_theta / grad_bias: its result): the stand-alone kernel over the same
+// grid, which decides on the device whether it runs.
 hipError_t launch_bwd_fused_late_64_64(const float *g_rows, const float *own_rows, const float *pos,
-                                       const int32_t *nbr, float *partials, const int *control, int B, int N, int K,
-                                       hipStream_t s)
+                                       const int32_t *nbr, const void *thetaP, const float *grad_theta,
+                                       const float *grad_bias, int Din, int Dout, float *partials, int *control, int B,
+                                       int N, int K, hipStream_t s)
 {
-    using F = FusedGeom<S>;
-    const int tpc = (N + F::G::T - 1) / F::G::T;
-    const int tot = B * tpc;
-    return launch_gt_if(control, FUSED_UNRESOLVED, own_rows, pos, nbr, g_rows, partials, N, K, tpc, tot,
-                        persistent_grid(tot, 1), s);
-}
-#endif
-
-#if FLEX_WS && FLEX_DI == 64 && FLEX_DO == 128
-// 128 -> 128 layers as two passes of this shape's lean kernels: each gathers one 64-channel half of the
-// 128-wide rows (row stride 128) and contracts it with its [4*64 x 128] block of the parameters; the second
-// pass adds to the first one's output.  Point-major tensors only.
-bool split_ok_128_128(int N, int K, int csr)
-{
-    if (contract_in_fp32() || lean_producer_mode() == 0) return false;
-    if ((int64_t)N * 128 * 4 >= (1ll << 32) || (int64_t)N * 12 >= (1ll << 32)) return false;
-    return csr || ((K % 8 == 0) && (int64_t)K * N * 4 < (1ll << 32));
-}
-
-hipError_t launch_gc_split_128_128(const float *rows_half, const float *pos, const int32_t *nbr, const int32_t *off,
-                                   const int32_t *src, const int32_t *order, const void *thetaP, float *out, int B,
-                                   int N, int K, int csr, int accumulate, hipStream_t s)
-{
-    using W = WsGeom<S, 1>;
-    const int tpc = (N + W::T - 1) / W::T;
-    const int64_t tot64 = (int64_t)B * tpc;
-    if (tot64 > 0x7fffffff) return hipErrorInvalidValue;
-    const int tot = (int)tot64;
-    const dim3 g(persistent_grid(tot, W::WG_PER_CU)), blk(W::NT);
-    const int exp_off = (int)theta_f16_exp_offset(S::DIP, S::DOP);
-    if (csr && order == nullptr) return hipErrorInvalidValue;
-    if (!csr) {
-        if (accumulate) hipLaunchKernelGGL((gather_contract_lean_kernel<S, false, 1, 128, 128, true>), g, blk, 0, s, rows_half, pos, nbr, thetaP, exp_off, out, N, K, tpc, tot);
-        else hipLaunchKernelGGL((gather_contract_lean_kernel<S, false, 1, 128, 128, false>), g, blk, 0, s, rows_half, pos, nbr, thetaP, exp_off, out, N, K, tpc, tot);
-    } else {
-        if (accumulate) hipLaunchKernelGGL((grad_feat_lean_kernel<S, false, 1, 128, 128, true>), g, blk, 0, s, rows_half, pos, off, src, order, thetaP, exp_off, out, N, tpc, tot);
-        else hipLaunchKernelGGL((grad_feat_lean_kernel<S, false, 1, 128, 128, false>), g, blk, 0, s, rows_half, pos, off, src, order, thetaP, exp_off, out, N, tpc, tot);
-    }
+    using WL = WsGeom<S, 2, 2>;
+    const int tpc = (N + WL::T - 1) / WL::T, tot = B * tpc;
+    const dim3 g(persistent_grid(tot, 1));
+    const float *rscale = reinterpret_cast<const float *>(reinterpret_cast<const char *>(thetaP) +
+                                                          theta_f16_rscale_offset(S::DIP, S::DOP));
+#define FLEX_LATE_ARGS control, rscale, grad_theta, grad_bias, Din, Dout, own_rows, pos, nbr, g_rows, partials, N, K, tpc, tot
+    if (K % 8 == 0) hipLaunchKernelGGL((grad_theta_lean_late_kernel<S, false>), g, dim3(WL::NT), 0, s, FLEX_LATE_ARGS);
+    else hipLaunchKernelGGL((grad_theta_lean_late_kernel<S, true>), g, dim3(WL::NT), 0, s, FLEX_LATE_ARGS);
+#undef FLEX_LATE_ARGS
     return hipGetLastError();
 }
 #endif
@@ -381,23 +336,6 @@ hipError_t launch_gt_split_wide(const float *rows, int rs, const float *pos, con
     else
         hipLaunchKernelGGL((grad_theta_lean_blocks_kernel<S, true>), dim3((unsigned)grid), dim3(WL::NT), 0, s, rows,
                            pos, nbr, g_rows, partials, N, K, tpc, tot, rs, gst, chunks, n_ho);
-    return hipGetLastError();
-}
-
-// One [4*64 x 64] block of the parameter gradient of a 128 -> 128 layer: the aggregate of a 64-channel half of
-// the 128-wide feature rows against a 64-channel half of the 128-wide upstream gradient rows.
-hipError_t launch_gt_split_128_128(const float *rows_half, const float *pos, const int32_t *nbr,
-                                   const float *g_half, float *partials, int B, int N, int K, int *n_wg,
-                                   hipStream_t s)
-{
-    using WL = WsGeom<S, 2, 2>;
-    const int tpc = (N + WL::T - 1) / WL::T;
-    const int64_t tot64 = (int64_t)B * tpc;
-    if (tot64 > 0x7fffffff) return hipErrorInvalidValue;
-    const int tot = (int)tot64;
-    *n_wg = persistent_grid(tot, 1);
-    hipLaunchKernelGGL((grad_theta_lean_kernel<S, 128, 128>), dim3(*n_wg), dim3(WL::NT), 0, s, rows_half, pos, nbr,
-                       g_half, partials, N, K, tpc, tot);
     return hipGetLastError();
 }
 #endif

@@ -1974,7 +1974,7 @@ void grad_theta_lean_blocks_kernel(const float *__restrict__ rows, const float *
 // kernel, launched behind it in its run-if-flagged form, recomputes the partials (results stay correct, that call is
 // slower).  What the halves cannot RESOLVE -- a result far below the product of the largest aggregate and the largest
 // feature -- is judged after the reduction, on the whole result, from the records the workgroups leave
-// (fused_bwd_check_kernel).
+// (fused_result_resolved).
 // Pipeline: producers fill tile k+1 while the Theta^T waves contract tile k and fetch, scale and split the own rows
 // of tile k (ids and exponents are known only once the tile is complete) and the T waves contract tile k-1; hence
 // three tile buffers and one trailing barrier.  The matrix op accumulates with round-toward-zero, so the T waves add their
@@ -2272,7 +2272,7 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
     }
     if (!fresh || !have_prev) flush();    // a workgroup without tiles still writes its (zero) partial
 
-    // ---- what the check after the reduction needs from this workgroup (fused_bwd_check_kernel) ----
+    // ---- what the check after the reduction needs from this workgroup (fused_result_resolved) ----
     // its last running exponent, its number of terms and its channel exponents: words 0, 1 and 2 .. 2 + DO of its
     // record, FUSED_RECORD_INTS apart, behind the flag
     if (j == 0) {
@@ -2282,15 +2282,95 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
     }
 }
 
-// The stand-alone parameter-gradient kernel as the fused kernel's fall-back: runs only if *overflow == want.
+// Do the one-pass backward kernel's parameter gradients (grad_theta [3,Din,Dout], grad_bias [Din,Dout], at most 64
+// wide, already reduced) stand clear of what its f16 halves can resolve?  A term of its sum over points -- tile entry times own'
+// element -- is off by at most 2^-25 (half the smallest f16 step) times the tile entry (< 2^15), i.e. 2^-10 in the
+// units of the workgroup's accumulators, which are 2^-(E + cs_c) / rs_(j,o) true units (E: the workgroup's last
+// running exponent, the smallest it had; cs_c: its channel exponent; rs: the row scale of the packed parameters).
+// Errors of random sign add in quadrature: err^2[(j,c),o] = Q_c / rs_(j,o)^2 with
+// Q_c = sum over workgroups of n_wg * 2^(-20 - 2 (E_wg + cs_wg,c)), summed by reduce_partials_fused_kernel.  Every row
+// (j,c) over o and every column (j,o) over c of the result must have a sum of squares at least 2^32 times that of its
+// error bound (RMS 2^16 times: a relative error of 1.5e-5, where ordinary data stands some 2^8 clear of the bar); rows
+// and columns that are exactly zero -- a dead channel, a channel without gradient -- are exact and exempt.
+// Called by all 1024 threads of a workgroup; the same answer in every workgroup.  Sums in double (the exponents span
+// more than fp32 holds).
+__device__ __forceinline__ bool fused_result_resolved(const int *__restrict__ control, const float *__restrict__ rscale,
+                                                      const float *__restrict__ grad_theta,
+                                                      const float *__restrict__ grad_bias, int Din, int Dout,
+                                                      double (*s_col)[64])
+{
+    constexpr int C = 64;
+    constexpr double BAR = 4294967296.0;
+    const int t = threadIdx.x, lane = t & 63, quad = t & 15, c = t >> 4, wave = t >> 6;
+    auto q_of = [&](int ch) {
+        return *reinterpret_cast<const double *>(control + FUSED_FLAG_INTS + ch * FUSED_RECORD_INTS + FUSED_Q_INT);
+    };
+    auto irs2 = [&](float rs) { return __builtin_ldexp(1.0, -2 * (__builtin_amdgcn_frexp_expf(rs) - 1)); };   // rs = 2^k exactly
+    const double Qc = q_of(c);
+    double Qsum = q_of(lane);
+    float x[4][4], rs[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int o = 4 * quad + i;
+            x[j][i] = (c < Din && o < Dout) ? (j < 3 ? grad_theta + j * Din * Dout : grad_bias)[c * Dout + o] : 0.f;
+            rs[j][i] = rscale[j * C + 4 * quad + i];
+        }
+    float rs_col[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) rs_col[j] = rscale[j * C + lane];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) Qsum += __shfl_xor(Qsum, d, 64);
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        double sq = 0.0, bound = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double v = (double)x[j][i] * (double)x[j][i];
+            sq += v;
+            bound += irs2(rs[j][i]);
+            v += __shfl_xor(v, 16, 64);
+            v += __shfl_xor(v, 32, 64);
+            if (lane < 16) s_col[wave][4 * quad + i] = v;
+        }
+#pragma unroll
+        for (int d = 1; d < 16; d <<= 1) { sq += __shfl_xor(sq, d, 64); bound += __shfl_xor(bound, d, 64); }
+        bad |= !(sq == 0.0 || sq >= BAR * bound * Qc);
+        __syncthreads();
+        if (t < C) {
+            double col = 0.0;
+            for (int w = 0; w < 16; ++w) col += s_col[w][t];
+            bad |= !(col == 0.0 || col >= BAR * irs2(rs_col[j]) * Qsum);
+        }
+        __syncthreads();
+    }
+    return !__syncthreads_or(bad);
+}
+
+// The stand-alone parameter-gradient kernel as the fused kernel's fall-back, behind the first reduction: it runs if a
+// feature row overflowed (*control set by the fused kernel) or if the reduced result does not stand clear of what the
+// halves resolve, which every workgroup finds out for itself (72 KB read from L2: cheaper than a launch of its own for
+// one workgroup to do it); else it returns at once.  The flag it leaves tells the second reduction.
 template <class S, bool TAIL>
 __global__ __launch_bounds__((WsGeom<S, 2, 2>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void grad_theta_lean_if_kernel(const int *__restrict__ overflow, int want, const float *__restrict__ rows,
-                               const float *__restrict__ pos, const int32_t *__restrict__ nbr,
-                               const float *__restrict__ g_rows, float *__restrict__ partials, int N, int K,
-                               int tiles_per_cloud, int total_tiles)
+void grad_theta_lean_late_kernel(int *__restrict__ control, const float *__restrict__ rscale,
+                                 const float *__restrict__ grad_theta, const float *__restrict__ grad_bias, int Din, int Dout,
+                                 const float *__restrict__ rows, const float *__restrict__ pos,
+                                 const int32_t *__restrict__ nbr, const float *__restrict__ g_rows,
+                                 float *__restrict__ partials, int N, int K, int tiles_per_cloud, int total_tiles)
 {
-    if (*overflow != want) return;
+    static_assert(WsGeom<S, 2, 2>::NT == 1024, "the check's threads");
+    __shared__ double s_col[16][64];
+    __shared__ int s_flag;
+    // one read for the whole workgroup: another one may be setting the flag meanwhile (to the answer found here too)
+    if (threadIdx.x == 0) s_flag = *control;
+    __syncthreads();
+    if (s_flag == 0) {
+        if (fused_result_resolved(control, rscale, grad_theta, grad_bias, Din, Dout, s_col)) return;
+        if (threadIdx.x == 0) *control = FUSED_UNRESOLVED;
+    }
     grad_theta_lean_body<S, S::DI, S::DO, TAIL>(rows, pos, nbr, g_rows, partials + (int64_t)blockIdx.x * S::KD * S::DOP,
                                                 N, K, tiles_per_cloud, TileSchedule(total_tiles), 0, 0);
 }
