@@ -70,7 +70,9 @@ size_t theta_f16_bytes(int RP, int CP);
 constexpr int FUSED_FLAG_INTS = 64, FUSED_RECORD_INTS = 128, FUSED_MAX_WG = 1024;
 constexpr int FUSED_OVERFLOW = 1, FUSED_UNRESOLVED = 2;
 constexpr size_t fused_control_bytes() { return sizeof(int) * (size_t)(FUSED_FLAG_INTS + FUSED_RECORD_INTS * FUSED_MAX_WG); }
-constexpr int FUSED_Q_INT = 96;      // record c, words 96 and 97: Q_c (reduce_partials_fused_kernel)
+// what reduce_partials_fused_kernel leaves in the records' spare words, as doubles
+constexpr int FUSED_Q_INT = 96;      // record c: Q_c
+constexpr int FUSED_ROW_INT = 98;    // record kd: the sum of squares of the result's row kd
 hipError_t launch_reduce_partials_fused(const float *partials, int n_wg, int *control, int Din, int Dout,
                                         float *grad_theta, float *grad_bias, hipStream_t s);
 hipError_t launch_reduce_partials_if(const int *flag, const float *partials, int n_wg, int DIP, int DOP, int Din,

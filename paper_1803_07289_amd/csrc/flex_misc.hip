@@ -68,9 +68,20 @@ struct ReduceArgs {
     int n_ho;                    // blocks of the result per row of blocks (blocks of DIP x DOP channels)
 };
 
-__device__ __forceinline__ void reduce_segment(const float *__restrict__ partials, const ReduceArgs &p, int block,
-                                               int segment, float *__restrict__ grad_theta,
-                                               float *__restrict__ grad_bias, double (*s_sum)[64])
+__device__ __forceinline__ void reduce_store(const ReduceArgs &p, int block, int e, double v,
+                                             float *__restrict__ grad_theta, float *__restrict__ grad_bias)
+{
+    const int kd = e / p.DOP, o0 = e - kd * p.DOP;
+    const int j = kd / p.DIP, bi = block / p.n_ho, bo = block - bi * p.n_ho;
+    const int c = bi * p.DIP + kd - j * p.DIP, o = bo * p.DOP + o0;
+    if (c >= p.Din || o >= p.Dout) return;
+    (j < 3 ? grad_theta + (int64_t)j * p.Din * p.Dout : grad_bias)[(int64_t)c * p.Dout + o] = (float)v;
+}
+
+// Returns the sum that thread t < 64 stored (element 64 * segment + t).
+__device__ __forceinline__ double reduce_segment(const float *__restrict__ partials, const ReduceArgs &p, int block,
+                                                 int segment, float *__restrict__ grad_theta,
+                                                 float *__restrict__ grad_bias, double (*s_sum)[64])
 {
     const int64_t E = (int64_t)4 * p.DIP * p.DOP;
     const int tid = threadIdx.x, q = tid & 15, grp = tid >> 4, wave = tid >> 6;
@@ -95,15 +106,38 @@ __device__ __forceinline__ void reduce_segment(const float *__restrict__ partial
         if ((tid & 63) < 16) s_sum[wave][4 * q + i] = sum[i];
     }
     __syncthreads();
-    if (tid >= 64) return;
+    if (tid >= 64) return 0.0;
     double v = 0.0;
 #pragma unroll
     for (int w = 0; w < 16; ++w) v += s_sum[w][tid];
-    const int e = 64 * segment + tid, kd = e / p.DOP, o0 = e - kd * p.DOP;
-    const int j = kd / p.DIP, bi = block / p.n_ho, bo = block - bi * p.n_ho;
-    const int c = bi * p.DIP + kd - j * p.DIP, o = bo * p.DOP + o0;
-    if (c >= p.Din || o >= p.Dout) return;
-    (j < 3 ? grad_theta + (int64_t)j * p.Din * p.Dout : grad_bias)[(int64_t)c * p.Dout + o] = (float)v;
+    reduce_store(p, block, 64 * segment + tid, v, grad_theta, grad_bias);
+    return v;
+}
+
+// Few partials per block (a deep, wide layer has many blocks of the result and few workgroups on each): a thread per
+// four elements reads them all.  512 x 512 channels, four partials per block: 9 us (61 in the form above, most of whose
+// threads would have nothing to read).
+constexpr int REDUCE_FEW = 16;
+__global__ __launch_bounds__(256) void reduce_partials_few_kernel(const float *__restrict__ partials, const ReduceArgs p,
+                                                                  float *__restrict__ grad_theta,
+                                                                  float *__restrict__ grad_bias)
+{
+    const int E = 4 * p.DIP * p.DOP, e = 4 * (blockIdx.x * 256 + threadIdx.x);
+    if (e >= E) return;
+    const float *src = partials + (int64_t)blockIdx.y * p.n_wg * E + e;
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int g0 = 0; g0 < p.n_wg; g0 += 4) {
+        v4f x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const v4f *>(src + (int64_t)min(g0 + u, p.n_wg - 1) * E);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (g0 + u < p.n_wg)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum[i] += (double)x[u][i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) reduce_store(p, blockIdx.y, e + i, sum[i], grad_theta, grad_bias);
 }
 
 // grid: (64-element segments of a partial, blocks of the result)
@@ -130,8 +164,13 @@ __global__ __launch_bounds__(1024) void reduce_partials_if_kernel(const int *__r
 hipError_t launch_reduce_partials(const float *partials, int n_wg, int DIP, int DOP, int n_blocks, int n_ho, int Din,
                                   int Dout, float *grad_theta, float *grad_bias, hipStream_t s)
 {
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3(4 * DIP * DOP / 64, (unsigned)n_blocks), dim3(1024), 0, s, partials,
-                       ReduceArgs{n_wg, DIP, DOP, Din, Dout, n_ho}, grad_theta, grad_bias);
+    const ReduceArgs a{n_wg, DIP, DOP, Din, Dout, n_ho};
+    if (n_wg <= REDUCE_FEW)
+        hipLaunchKernelGGL(reduce_partials_few_kernel, dim3((4 * DIP * DOP + 1023) / 1024, (unsigned)n_blocks), dim3(256), 0,
+                           s, partials, a, grad_theta, grad_bias);
+    else
+        hipLaunchKernelGGL(reduce_partials_kernel, dim3(4 * DIP * DOP / 64, (unsigned)n_blocks), dim3(1024), 0, s, partials,
+                           a, grad_theta, grad_bias);
     return hipGetLastError();
 }
 
@@ -143,8 +182,9 @@ hipError_t launch_reduce_partials_if(const int *flag, const float *partials, int
     return hipGetLastError();
 }
 
-// The first reduction of the one-pass backward (64 -> 64), with one more workgroup that sums what the check of the
-// result needs from the workgroups' records: Q_c (see fused_bwd_check), left as a double at FUSED_Q_INT of record c.
+// The first reduction of the one-pass backward (64 -> 64).  It leaves what the check of the result needs
+// (fused_result_resolved): every workgroup its row's sum of squares, and one more workgroup Q_c from the workgroups'
+// records; as doubles at FUSED_ROW_INT of record kd and FUSED_Q_INT of record c.
 __global__ __launch_bounds__(1024) void reduce_partials_fused_kernel(const float *__restrict__ partials,
                                                                      const ReduceArgs p, int *__restrict__ control,
                                                                      float *__restrict__ grad_theta,
@@ -152,7 +192,15 @@ __global__ __launch_bounds__(1024) void reduce_partials_fused_kernel(const float
 {
     __shared__ double s_sum[16][64];
     if (blockIdx.x + 1 < gridDim.x) {
-        reduce_segment(partials, p, 0, blockIdx.x, grad_theta, grad_bias, s_sum);
+        double v = reduce_segment(partials, p, 0, blockIdx.x, grad_theta, grad_bias, s_sum);    // row kd = blockIdx.x
+        if (threadIdx.x < 64) {
+            v = (double)(float)v;
+            v *= v;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d, 64);
+            if (threadIdx.x == 0)
+                *reinterpret_cast<double *>(control + FUSED_FLAG_INTS + (int64_t)blockIdx.x * FUSED_RECORD_INTS + FUSED_ROW_INT) = v;
+        }
         return;
     }
     const int c = threadIdx.x & 63, part = threadIdx.x >> 6;

@@ -7,7 +7,10 @@
 
 namespace flex {
 
-static constexpr int PREP_NT = 256;
+// 512 threads and loops that are unrolled no further than the loads in flight ask for: a launch of a few workgroups is
+// over in the time its instructions take to arrive, so the code executed in a straight line counts (256 threads with
+// everything unrolled twice as far: 9 us for the packing at 64 x 64).
+static constexpr int PREP_NT = 512, PREP_WAVES = PREP_NT / 64;
 
 // ---- parameter packing for the split-half contraction ------------------------------
 // The wave-specialised kernels contract on the f16 matrix cores with every fp32
@@ -49,7 +52,6 @@ struct PackArgs {
 struct PackBlock {
     const float *theta, *bias;
     int Din, Dout, r0, c0, transpose;
-    __device__ __forceinline__ const float *comp(int j) const { return j < 3 ? theta + (int64_t)j * Din * Dout : bias; }
     __device__ __forceinline__ int rows() const { return (transpose ? Dout : Din) - r0; }
     __device__ __forceinline__ int cols() const { return (transpose ? Din : Dout) - c0; }
     // channels (input, output) of (row, column)
@@ -72,6 +74,55 @@ __device__ __forceinline__ float dpp_max(float m)
     return fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), CTRL, 0xf, 0xf, true)));
 }
 
+// Row maxima of a block into s_er.  The tensor's contiguous index (output channel) runs over the lanes of a 16-lane
+// group, four channels each; a group takes one component and every eighth input channel, UN rows requested together
+// (addresses clamped instead of branches, so that nothing stands between the requests; a repeat changes no maximum).
+// VEC: 16-byte reads.
+template <bool VEC, bool TR>
+__device__ __forceinline__ void pack_row_maxima(const PackBlock &v, int RP, int nr, int nc, int *s_er)
+{
+    constexpr int UN = VEC ? 8 : 4, STEP = PREP_NT / 64;
+    const int l16 = threadIdx.x & 15, j = (threadIdx.x >> 4) & 3;
+    const int ni = TR ? nc : nr, no = TR ? nr : nc;                     // input / output channels of the block
+    const float *base = (j < 3 ? v.theta + (int64_t)j * v.Din * v.Dout : v.bias) +
+                        (int64_t)(TR ? v.c0 : v.r0) * v.Dout + (TR ? v.r0 : v.c0);
+#pragma unroll 1
+    for (int o = 4 * l16; o - 4 * l16 < no; o += 64) {
+        float mt[4] = {0.f, 0.f, 0.f, 0.f};             // TR: the maxima of rows (j, o .. o+3)
+#pragma unroll 1
+        for (int r0 = threadIdx.x >> 6; r0 < ni; r0 += STEP * UN) {
+            v4f x[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const float *src = base + (int64_t)min(r0 + STEP * u, ni - 1) * v.Dout;
+                if constexpr (VEC) x[u] = *reinterpret_cast<const v4f *>(src + min(o, no - 4));
+                else x[u] = v4f{src[min(o, no - 1)], src[min(o + 1, no - 1)], src[min(o + 2, no - 1)], src[min(o + 3, no - 1)]};
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                if constexpr (TR) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) mt[i] = max_finite(mt[i], x[u][i]);
+                } else {
+                    float m = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) m = max_finite(m, x[u][i]);
+                    m = dpp_max<0xB1>(m); m = dpp_max<0x4E>(m); m = dpp_max<0x141>(m); m = dpp_max<0x140>(m);
+                    if (l16 == 0) atomicMax(&s_er[j * RP + min(r0 + STEP * u, ni - 1)], __float_as_int(m));
+                }
+            }
+        }
+        if constexpr (TR) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (o + i < no) atomicMax(&s_er[j * RP + o + i], __float_as_int(mt[i]));
+        }
+    }
+}
+
+// exponent e with |m| * 2^-e in [1/2, 1); 0 for m == 0
+__device__ __forceinline__ int frexp_exp(float m) { return __builtin_amdgcn_frexp_expf(m); }
+
 __device__ void pack_slice(const float *theta, const float *bias, char *thetaF_all, const PackArgs &p, int block,
                            char *lds)
 {
@@ -81,88 +132,28 @@ __device__ void pack_slice(const float *theta, const float *bias, char *thetaF_a
     const int j_blk = blk / p.n_i, i_blk = blk - j_blk * p.n_i;
     const PackBlock v{theta, bias, p.Din, p.Dout, p.RP * i_blk, p.CP * j_blk, p.transpose};
     const int KD = 4 * p.RP, KDP = (KD + 31) / 32 * 32, KS = KDP / 32;
-    const int tid = threadIdx.x, l16 = tid & 15, g16 = tid >> 4;
-    const int nr = min(p.RP, v.rows()), nc = min(p.CP, v.cols());       // what exists of the block
+    const int tid = threadIdx.x, l16 = tid & 15;
+    const int nr = min(p.RP, v.rows()), nc = min(p.CP, v.cols());       // what exists of the block (may be nothing)
     for (int i = tid; i < PACK_MAX_KD; i += PREP_NT) s_er[i] = 0;
     if (tid < 16) s_ec[tid] = 0;
     __syncthreads();
-    // row maxima.  The tensor's contiguous index (output channel) runs over the lanes of a 16-lane group, four
-    // channels each; the group walks (component, input channel) rows of memory, eight in flight.
-    constexpr int UN = 8, GROUPS = PREP_NT / 16;
-    const int ni = p.transpose ? nc : nr, no = p.transpose ? nr : nc;   // input / output channels of the block
-    const int ci0 = p.transpose ? v.c0 : v.r0, co0 = p.transpose ? v.r0 : v.c0;
-    const bool vec = ((p.Dout | co0) & 3) == 0 && ((reinterpret_cast<uintptr_t>(theta) | reinterpret_cast<uintptr_t>(bias)) & 15) == 0;
-    for (int o = 4 * l16; o - 4 * l16 < no; o += 64) {
-        float mt[4][4] = {};                            // transposed: the maxima of rows (j, o .. o+3) so far
-        for (int row0 = g16; row0 < 4 * ni; row0 += GROUPS * UN) {
-            v4f x[UN];
-            int jj[UN], rr[UN];
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const int row = row0 + GROUPS * u;
-                jj[u] = (row >= ni) + (row >= 2 * ni) + (row >= 3 * ni);
-                rr[u] = row - jj[u] * ni;
-                x[u] = v4f{0.f, 0.f, 0.f, 0.f};
-                if (row < 4 * ni && o < no) {
-                    const float *src = v.comp(jj[u]) + (int64_t)(ci0 + rr[u]) * p.Dout + co0 + o;
-                    if (vec && o + 3 < no) x[u] = *reinterpret_cast<const v4f *>(src);
-                    else {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (o + i < no) x[u][i] = src[i];
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                if (p.transpose) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (jj[u] == j)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) mt[j][i] = max_finite(mt[j][i], x[u][i]);
-                } else {
-                    float m = 0.f;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) m = max_finite(m, x[u][i]);
-                    m = dpp_max<0xB1>(m); m = dpp_max<0x4E>(m); m = dpp_max<0x141>(m); m = dpp_max<0x140>(m);
-                    // the row belongs to this lane group alone (other column chunks: the same group, later)
-                    if (l16 == 0 && row0 + GROUPS * u < 4 * ni) {
-                        int *e = &s_er[jj[u] * p.RP + rr[u]];
-                        *e = max(*e, __float_as_int(m));
-                    }
-                }
-            }
-        }
+    if (nr > 0 && nc > 0) {
+        const int no = p.transpose ? nr : nc, co0 = p.transpose ? v.r0 : v.c0;
+        const bool vec = ((p.Dout | co0 | no) & 3) == 0 &&
+                         ((reinterpret_cast<uintptr_t>(theta) | reinterpret_cast<uintptr_t>(bias)) & 15) == 0;
         if (p.transpose) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float m = mt[j][i];
-                    m = fmaxf(m, __shfl_xor(m, 16, 64));
-                    m = fmaxf(m, __shfl_xor(m, 32, 64));
-                    if ((tid & 63) < 16 && o + i < no) atomicMax(&s_er[j * p.RP + o + i], __float_as_int(m));
-                }
+            if (vec) pack_row_maxima<true, true>(v, p.RP, nr, nc, s_er);
+            else pack_row_maxima<false, true>(v, p.RP, nr, nc, s_er);
+        } else {
+            if (vec) pack_row_maxima<true, false>(v, p.RP, nr, nc, s_er);
+            else pack_row_maxima<false, false>(v, p.RP, nr, nc, s_er);
         }
     }
-    __syncthreads();
-    _Float16 *thetaF = reinterpret_cast<_Float16 *>(thetaF_all + (size_t)blk * p.block_bytes);
-    for (int kd = tid; kd < KDP; kd += PREP_NT) {
-        const float m = __int_as_float(s_er[kd]);
-        int er = 0;
-        if (m > 0.f) { (void)frexpf(m, &er); er = -er; }
-        er = er < -60 ? -60 : (er > 60 ? 60 : er);
-        s_er[kd] = er;
-        if (slice == 0)
-            reinterpret_cast<float *>(reinterpret_cast<char *>(thetaF) + p.rs_off)[kd] = ldexpf(1.f, -er);
-    }
-    __syncthreads();
-    // this slice's fragments: item = (step, lane), eight depth rows of one column
+    // this slice's elements: item = (step, lane), eight depth rows of one column
     constexpr int ITEMS = PACK_MAX_KD / 32 * 64 / PREP_NT;
     float y[ITEMS][8];
     const int col = 16 * slice + l16;
-    float mc = 0.f;
+    const int64_t slab = (int64_t)p.Din * p.Dout;
 #pragma unroll
     for (int t = 0; t < ITEMS; ++t) {
         const int item = tid + PREP_NT * t;
@@ -171,10 +162,25 @@ __device__ void pack_slice(const float *theta, const float *bias, char *thetaF_a
         int j = kd0 / p.RP, r = kd0 - j * p.RP;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            y[t][e] = (j < 4 && r < nr && col < nc) ? v.comp(j)[v.at(r, col)] : 0.f;
+            const bool on = j < 4 && r < nr && col < nc;
+            const float *src = (j < 3 ? theta + min(j, 2) * slab : bias) + (on ? v.at(r, col) : 0);
+            const float x = *src;
+            y[t][e] = on ? x : 0.f;
             if (++r == p.RP) { r = 0; ++j; }
         }
     }
+    __syncthreads();
+    _Float16 *thetaF = reinterpret_cast<_Float16 *>(thetaF_all + (size_t)blk * p.block_bytes);
+    for (int kd = tid; kd < KDP; kd += PREP_NT) {
+        const float m = __int_as_float(s_er[kd]);
+        int er = m > 0.f ? -frexp_exp(m) : 0;
+        er = er < -60 ? -60 : (er > 60 ? 60 : er);
+        s_er[kd] = er;
+        if (slice == 0)
+            reinterpret_cast<float *>(reinterpret_cast<char *>(thetaF) + p.rs_off)[kd] = __builtin_ldexpf(1.f, -er);
+    }
+    __syncthreads();
+    float mc = 0.f;
 #pragma unroll
     for (int t = 0; t < ITEMS; ++t) {
         const int item = tid + PREP_NT * t;
@@ -182,7 +188,7 @@ __device__ void pack_slice(const float *theta, const float *bias, char *thetaF_a
         const int kd0 = 32 * (item >> 6) + 8 * ((item >> 4) & 3);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            y[t][e] = ldexpf(y[t][e], s_er[kd0 + e]);
+            y[t][e] = __builtin_ldexpf(y[t][e], s_er[kd0 + e]);
             mc = max_finite(mc, y[t][e]);
         }
     }
@@ -190,12 +196,9 @@ __device__ void pack_slice(const float *theta, const float *bias, char *thetaF_a
     mc = fmaxf(mc, __shfl_xor(mc, 32, 64));
     if ((tid & 63) < 16) atomicMax(&s_ec[l16], __float_as_int(mc));
     __syncthreads();
-    int ec = 0;
-    {
-        const float m = __int_as_float(s_ec[l16]);
-        if (m > 0.f) { (void)frexpf(m, &ec); ec = 15 - ec; }
-        if (tid < 16) reinterpret_cast<int *>(reinterpret_cast<char *>(thetaF) + p.exp_off)[col] = ec;
-    }
+    const float m = __int_as_float(s_ec[l16]);
+    const int ec = m > 0.f ? 15 - frexp_exp(m) : 0;
+    if (tid < 16) reinterpret_cast<int *>(reinterpret_cast<char *>(thetaF) + p.exp_off)[col] = ec;
     const int per_part = NS * KS * 64 * 8;
 #pragma unroll
     for (int t = 0; t < ITEMS; ++t) {
@@ -204,7 +207,7 @@ __device__ void pack_slice(const float *theta, const float *bias, char *thetaF_a
         h8 hi, lo;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float vs = ldexpf(y[t][e], ec);
+            const float vs = __builtin_ldexpf(y[t][e], ec);
             hi[e] = (_Float16)vs;
             lo[e] = (_Float16)(vs - (float)hi[e]);
         }
@@ -248,23 +251,23 @@ __device__ void pack_pos_slice(const float *theta, _Float16 *thetaF, const PackP
     const int tid = threadIdx.x;
     float m = 0.f;
     for (int o = tid & 63; o < no; o += 64)
-        for (int r0 = tid >> 6; r0 < 3 * ni; r0 += 4 * 16) {
-            float x[16];
+        for (int r0 = tid >> 6; r0 < 3 * ni; r0 += PREP_WAVES * 8) {
+            float x[8];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int row = r0 + 4 * u, j = (row >= ni) + (row >= 2 * ni);
-                x[u] = row < 3 * ni ? theta[((int64_t)j * p.Din + p.ci0 + row - j * ni) * p.Dout + p.co0 + o] : 0.f;
+            for (int u = 0; u < 8; ++u) {
+                const int row = min(r0 + PREP_WAVES * u, 3 * ni - 1), j = (row >= ni) + (row >= 2 * ni);   // repeats change no maximum
+                x[u] = theta[((int64_t)j * p.Din + p.ci0 + row - j * ni) * p.Dout + p.co0 + o];
             }
 #pragma unroll
-            for (int u = 0; u < 16; ++u) m = fmaxf(m, fabsf(x[u]));
+            for (int u = 0; u < 8; ++u) m = fmaxf(m, fabsf(x[u]));
         }
 #pragma unroll
     for (int w = 1; w < 64; w <<= 1) m = fmaxf(m, __shfl_xor(m, w, 64));
     if ((tid & 63) == 0) s_max[tid >> 6] = m;
     __syncthreads();
-    m = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+    for (int w = 0; w < PREP_WAVES; ++w) m = fmaxf(m, s_max[w]);
     int ex = 0;
-    if (m > 0.f && m < __builtin_inff()) { (void)frexpf(m, &ex); ex = 15 - ex; }
+    if (m > 0.f && m < __builtin_inff()) ex = 15 - frexp_exp(m);
     if (block == 0 && tid == 0) *reinterpret_cast<int *>(reinterpret_cast<char *>(thetaF) + p.exp_off) = ex;
     const int per_part = NS * KS * 64 * 8;
     for (int item = tid; item < KS * 64; item += PREP_NT) {
@@ -273,9 +276,9 @@ __device__ void pack_pos_slice(const float *theta, _Float16 *thetaF, const PackP
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int kd = kd0 + e, ci = p.ci0 + (p.transpose ? col : kd), co = p.co0 + (p.transpose ? kd : col);
-            float x = 0.f;
-            if (ci < p.Din && co < p.Dout) x = theta[((int64_t)d * p.Din + ci) * p.Dout + co];
-            const float vs = ldexpf(x, ex);
+            const bool on = ci < p.Din && co < p.Dout;
+            const float x = theta[on ? ((int64_t)d * p.Din + ci) * p.Dout + co : 0];
+            const float vs = __builtin_ldexpf(on ? x : 0.f, ex);
             hi[e] = (_Float16)vs;
             lo[e] = (_Float16)(vs - (float)hi[e]);
         }
@@ -294,30 +297,34 @@ size_t theta_pos_bytes(int KDP, int CP) { return theta_pos_exp_offset(KDP, CP) +
 // of equal length in index order.  A wave of the gather kernels takes four consecutive positions and a tile a few
 // dozen, so their lists have (nearly) one length: no slot of a batch stays empty and no wave waits for a longer
 // list at the tile's barrier, while a window is small enough for its gathered rows to stay in the caches.
-// One workgroup per window: lengths -> per (length, 64-point chunk) counts by ballots -> running sum in
+// Four waves per window: lengths -> per (length, 64-point chunk) counts by ballots -> running sum in
 // (length, chunk) order -> every point's place.
 // The window is 13 tiles of 48 points: the persistent kernels deal tiles to workgroups with a stride that is a
 // power of two, and a window of a power-of-two number of tiles would hand a workgroup the same place in every
 // window, i.e. always the short or always the long lists.
 static constexpr int ORDER_WINDOW = 624;
 static constexpr int ORDER_CHUNKS = (ORDER_WINDOW + 63) / 64;  // 64-point chunks of a window
-static constexpr int ORDER_ROUNDS = (ORDER_CHUNKS + 3) / 4;    // chunks per wave (4 waves)
+static constexpr int ORDER_NT = 256, ORDER_WAVES = ORDER_NT / 64;       // threads per window
+static constexpr int ORDER_PER_BLOCK = PREP_NT / ORDER_NT;              // windows per workgroup
+static constexpr int ORDER_ROUNDS = (ORDER_CHUNKS + ORDER_WAVES - 1) / ORDER_WAVES;    // chunks per wave
 static constexpr int ORDER_BUCKETS = 32;
 static_assert((ORDER_BUCKETS * ORDER_CHUNKS) % 64 == 0, "order: whole entries per lane in the running sum");
 
 __device__ void order_window(const int32_t *__restrict__ off, int32_t *__restrict__ order, int N, int windows_per_cloud,
-                             int block, char *lds)
+                             int windows, int block, char *lds)
 {
-    int *s_cnt = reinterpret_cast<int *>(lds);                 // [length][chunk], then its exclusive running sum
-    int *s_ord = s_cnt + ORDER_BUCKETS * ORDER_CHUNKS;         // [ORDER_WINDOW]
-    const int b = block / windows_per_cloud, w = block - b * windows_per_cloud;
-    const int p0 = w * ORDER_WINDOW, n = min(ORDER_WINDOW, N - p0);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int part = threadIdx.x / ORDER_NT, tid = threadIdx.x % ORDER_NT;      // window of the workgroup, thread in it
+    int *s_cnt = reinterpret_cast<int *>(lds) + part * (ORDER_BUCKETS * ORDER_CHUNKS + ORDER_WINDOW);
+    int *s_ord = s_cnt + ORDER_BUCKETS * ORDER_CHUNKS;         // [ORDER_WINDOW]; s_cnt: [length][chunk], then its exclusive running sum
+    const int win = block * ORDER_PER_BLOCK + part;
+    const int b = win / windows_per_cloud, w = win - b * windows_per_cloud;
+    const int p0 = w * ORDER_WINDOW, n = win < windows ? min(ORDER_WINDOW, N - p0) : 0;
+    const int lane = tid & 63, wave = tid >> 6;
     const uint64_t lt = (1ull << lane) - 1ull;
     int len[ORDER_ROUNDS], rank[ORDER_ROUNDS];
 #pragma unroll
     for (int r = 0; r < ORDER_ROUNDS; ++r) {
-        const int chunk = r * 4 + wave, i = chunk * 64 + lane;
+        const int chunk = r * ORDER_WAVES + wave, i = chunk * 64 + lane;
         len[r] = -1;
         if (i < n) {
             const int64_t g = (int64_t)b * N + p0 + i;
@@ -325,11 +332,11 @@ __device__ void order_window(const int32_t *__restrict__ off, int32_t *__restric
         }
         rank[r] = 0;
     }
-    for (int i = threadIdx.x; i < ORDER_BUCKETS * ORDER_CHUNKS; i += PREP_NT) s_cnt[i] = 0;
+    for (int i = tid; i < ORDER_BUCKETS * ORDER_CHUNKS; i += ORDER_NT) s_cnt[i] = 0;
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < ORDER_ROUNDS; ++r) {
-        const int chunk = r * 4 + wave;
+        const int chunk = r * ORDER_WAVES + wave;
         // one round per length that occurs in the chunk (about ten of the 32)
         uint64_t todo = __ballot(len[r] >= 0);
         while (todo) {
@@ -361,11 +368,11 @@ __device__ void order_window(const int32_t *__restrict__ off, int32_t *__restric
     // every point's place, through LDS so that the window leaves as one contiguous write
 #pragma unroll
     for (int r = 0; r < ORDER_ROUNDS; ++r) {
-        const int chunk = r * 4 + wave, i = chunk * 64 + lane;
+        const int chunk = r * ORDER_WAVES + wave, i = chunk * 64 + lane;
         if (i < n) s_ord[s_cnt[len[r] * ORDER_CHUNKS + chunk] + rank[r]] = p0 + i;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < n; i += PREP_NT) order[(int64_t)b * N + p0 + i] = s_ord[i];
+    for (int i = tid; i < n; i += ORDER_NT) order[(int64_t)b * N + p0 + i] = s_ord[i];
 }
 
 size_t inedges_order_bytes(int64_t BN) { return align256(sizeof(int32_t) * (size_t)BN); }
@@ -393,10 +400,10 @@ __device__ void copy_tile(const float *__restrict__ src, float *__restrict__ dst
     float *d = dst + b * (int64_t)p.N * p.Cd;
     if (p.vec) {
         const int x = 4 * (threadIdx.x & 15), y = threadIdx.x >> 4;
-        v4f v[4];
+        v4f v[2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int yy = y + 16 * i;
+        for (int i = 0; i < 2; ++i) {
+            const int yy = y + 32 * i;
             v[i] = v4f{0.f, 0.f, 0.f, 0.f};
             if (p.src_bcn) {
                 const int c = p.c_off + c0 + yy;
@@ -407,16 +414,16 @@ __device__ void copy_tile(const float *__restrict__ src, float *__restrict__ dst
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (p.src_bcn) tile[y + 16 * i][x + e] = v[i][e];
-                else tile[x + e][y + 16 * i] = v[i][e];
+                if (p.src_bcn) tile[y + 32 * i][x + e] = v[i][e];
+                else tile[x + e][y + 32 * i] = v[i][e];
             }
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int yy = y + 16 * i;
+        for (int i = 0; i < 2; ++i) {
+            const int yy = y + 32 * i;
             if (p.dst_bcn) {
                 if (c0 + yy < p.Cd && n0 + x < p.N)
                     *reinterpret_cast<v4f *>(d + (int64_t)(c0 + yy) * p.N + n0 + x) =
@@ -430,22 +437,22 @@ __device__ void copy_tile(const float *__restrict__ src, float *__restrict__ dst
         return;
     }
     const int x = threadIdx.x & 63, y = threadIdx.x >> 6;
-    float v[16];
+    float v[8];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int yy = y + 4 * i;
+    for (int i = 0; i < 8; ++i) {
+        const int yy = y + 8 * i;
         const int c = p.c_off + c0 + (p.src_bcn ? yy : x), n = n0 + (p.src_bcn ? x : yy);
         v[i] = (c < p.Cs && n < p.N) ? __builtin_nontemporal_load(p.src_bcn ? s + (int64_t)c * p.N + n : s + (int64_t)n * p.Cs + c) : 0.f;
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        if (p.src_bcn) tile[y + 4 * i][x] = v[i];
-        else tile[x][y + 4 * i] = v[i];
+    for (int i = 0; i < 8; ++i) {
+        if (p.src_bcn) tile[y + 8 * i][x] = v[i];
+        else tile[x][y + 8 * i] = v[i];
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int yy = y + 4 * i;
+    for (int i = 0; i < 8; ++i) {
+        const int yy = y + 8 * i;
         if (p.dst_bcn) {
             if (c0 + yy < p.Cd && n0 + x < p.N) d[(int64_t)(c0 + yy) * p.N + n0 + x] = tile[yy][x];
         } else {
@@ -463,7 +470,7 @@ struct PrepJob {
         PackArgs pack;
         PackPosArgs pos;
         CopyArgs copy;
-        struct { int N, wpc; } order;
+        struct { int N, wpc, windows; } order;
         struct { int words; } clear;
     };
 };
@@ -473,11 +480,11 @@ struct PrepJobs {
     PrepJob job[PREP_MAX_JOBS];
 };
 
-__global__ __launch_bounds__(PREP_NT) void prep_kernel(const PrepJobs jobs)
+__global__ __launch_bounds__(PREP_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void prep_kernel(const PrepJobs jobs)
 {
     __shared__ __attribute__((aligned(16))) char lds[64 * 65 * sizeof(float)];
     static_assert(sizeof(lds) >= sizeof(int) * (PACK_MAX_KD + 16) &&
-                  sizeof(lds) >= sizeof(int) * (ORDER_BUCKETS * ORDER_CHUNKS + ORDER_WINDOW), "LDS of every job");
+                  sizeof(lds) >= sizeof(int) * ORDER_PER_BLOCK * (ORDER_BUCKETS * ORDER_CHUNKS + ORDER_WINDOW), "LDS of every job");
     int block = blockIdx.x, i = 0;
     while (block >= jobs.job[i].blocks) { block -= jobs.job[i].blocks; ++i; }     // the grid is the sum of the blocks
     const PrepJob &j = jobs.job[i];
@@ -489,7 +496,7 @@ __global__ __launch_bounds__(PREP_NT) void prep_kernel(const PrepJobs jobs)
         pack_pos_slice((const float *)j.a, (_Float16 *)j.dst, j.pos, block, lds);
         break;
     case PREP_ORDER:
-        order_window((const int32_t *)j.a, (int32_t *)j.dst, j.order.N, j.order.wpc, block, lds);
+        order_window((const int32_t *)j.a, (int32_t *)j.dst, j.order.N, j.order.wpc, j.order.windows, block, lds);
         break;
     case PREP_COPY:
         copy_tile((const float *)j.a, (float *)j.dst, j.copy, block, lds);
@@ -527,8 +534,9 @@ void PrepList::pack_theta_pos(const float *theta, void *thetaF, int Din, int Dou
 void PrepList::order(const int32_t *in_off, int B, int N, int32_t *order)
 {
     const int wpc = (N + ORDER_WINDOW - 1) / ORDER_WINDOW;
-    if (PrepJob *j = next_job(*this, PREP_ORDER, (int64_t)B * wpc, in_off, nullptr, order)) {
-        j->order.N = N; j->order.wpc = wpc;
+    const int64_t windows = (int64_t)B * wpc;
+    if (PrepJob *j = next_job(*this, PREP_ORDER, (windows + ORDER_PER_BLOCK - 1) / ORDER_PER_BLOCK, in_off, nullptr, order)) {
+        j->order.N = N; j->order.wpc = wpc; j->order.windows = (int)windows;
     }
 }
 

@@ -2293,58 +2293,45 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
 // error bound (RMS 2^16 times: a relative error of 1.5e-5, where ordinary data stands some 2^8 clear of the bar); rows
 // and columns that are exactly zero -- a dead channel, a channel without gradient -- are exact and exempt.
 // Called by all 1024 threads of a workgroup; the same answer in every workgroup.  Sums in double (the exponents span
-// more than fp32 holds).
+// more than fp32 holds).  The rows' sums come from the reduction; columns are summed here, a quarter of the channels c
+// per thread.
 __device__ __forceinline__ bool fused_result_resolved(const int *__restrict__ control, const float *__restrict__ rscale,
                                                       const float *__restrict__ grad_theta,
                                                       const float *__restrict__ grad_bias, int Din, int Dout,
-                                                      double (*s_col)[64])
+                                                      double (*s_col)[256])
 {
     constexpr int C = 64;
     constexpr double BAR = 4294967296.0;
-    const int t = threadIdx.x, lane = t & 63, quad = t & 15, c = t >> 4, wave = t >> 6;
-    auto q_of = [&](int ch) {
-        return *reinterpret_cast<const double *>(control + FUSED_FLAG_INTS + ch * FUSED_RECORD_INTS + FUSED_Q_INT);
+    const int t = threadIdx.x, lane = t & 63, r = t & 255, j = r >> 6, quarter = t >> 8;
+    auto record = [&](int i, int word) {
+        return *reinterpret_cast<const double *>(control + FUSED_FLAG_INTS + i * FUSED_RECORD_INTS + word);
     };
-    auto irs2 = [&](float rs) { return __builtin_ldexp(1.0, -2 * (__builtin_amdgcn_frexp_expf(rs) - 1)); };   // rs = 2^k exactly
-    const double Qc = q_of(c);
-    double Qsum = q_of(lane);
-    float x[4][4], rs[4][4];
+    float x[16];
+    {
+        const float *src = j < 3 ? grad_theta + j * Din * Dout : grad_bias;      // column o = lane
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int o = 4 * quad + i;
-            x[j][i] = (c < Din && o < Dout) ? (j < 3 ? grad_theta + j * Din * Dout : grad_bias)[c * Dout + o] : 0.f;
-            rs[j][i] = rscale[j * C + 4 * quad + i];
+        for (int i = 0; i < 16; ++i) {
+            const int c = 16 * quarter + i;
+            const bool on = c < Din && lane < Dout;
+            const float v = src[on ? c * Dout + lane : 0];
+            x[i] = on ? v : 0.f;
         }
-    float rs_col[4];
+    }
+    const double row = record(r, FUSED_ROW_INT), q = record(lane, FUSED_Q_INT);   // row (j, c = lane)
+    const float rs = rscale[r];                                                   // of (j, o = lane)
+    double sq = 0.0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) rs_col[j] = rscale[j * C + lane];
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) Qsum += __shfl_xor(Qsum, d, 64);
+    for (int i = 0; i < 16; ++i) sq += (double)x[i] * (double)x[i];
+    s_col[quarter][r] = sq;
+    __syncthreads();
     bool bad = false;
+    if (quarter == 0) {
+        const double irs2 = __builtin_ldexp(1.0, -2 * (__builtin_amdgcn_frexp_expf(rs) - 1));     // rs = 2^k exactly
+        double irs2_sum = irs2, q_sum = q;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        double sq = 0.0, bound = 0.0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            double v = (double)x[j][i] * (double)x[j][i];
-            sq += v;
-            bound += irs2(rs[j][i]);
-            v += __shfl_xor(v, 16, 64);
-            v += __shfl_xor(v, 32, 64);
-            if (lane < 16) s_col[wave][4 * quad + i] = v;
-        }
-#pragma unroll
-        for (int d = 1; d < 16; d <<= 1) { sq += __shfl_xor(sq, d, 64); bound += __shfl_xor(bound, d, 64); }
-        bad |= !(sq == 0.0 || sq >= BAR * bound * Qc);
-        __syncthreads();
-        if (t < C) {
-            double col = 0.0;
-            for (int w = 0; w < 16; ++w) col += s_col[w][t];
-            bad |= !(col == 0.0 || col >= BAR * irs2(rs_col[j]) * Qsum);
-        }
-        __syncthreads();
+        for (int d = 1; d < C; d <<= 1) { irs2_sum += __shfl_xor(irs2_sum, d, 64); q_sum += __shfl_xor(q_sum, d, 64); }
+        const double col = (s_col[0][r] + s_col[1][r]) + (s_col[2][r] + s_col[3][r]);
+        bad = !(row == 0.0 || row >= BAR * irs2_sum * q) || !(col == 0.0 || col >= BAR * irs2 * q_sum);
     }
     return !__syncthreads_or(bad);
 }
@@ -2362,7 +2349,7 @@ void grad_theta_lean_late_kernel(int *__restrict__ control, const float *__restr
                                  float *__restrict__ partials, int N, int K, int tiles_per_cloud, int total_tiles)
 {
     static_assert(WsGeom<S, 2, 2>::NT == 1024, "the check's threads");
-    __shared__ double s_col[16][64];
+    __shared__ double s_col[4][256];
     __shared__ int s_flag;
     // one read for the whole workgroup: another one may be setting the flag meanwhile (to the answer found here too)
     if (threadIdx.x == 0) s_flag = *control;
