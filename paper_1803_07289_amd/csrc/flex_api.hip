@@ -281,7 +281,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
         if (build) {
             p.in_off = at;    at += align256(sizeof(int32_t) * (size_t)(B * N + 1));
             p.in_src = at;    at += align256(sizeof(int32_t) * (size_t)(B * N) * K);
-            p.inedge_ws = at; at += inedges_ws_bytes(B * N);
+            p.inedge_ws = at; at += inedges_ws_bytes(B * N, K);
         }
     }
     p.total = at > 0 ? at : 256;
@@ -314,7 +314,7 @@ static PosPlan plan_pos(int64_t B, int64_t N, int K, int Din, int Dout, int layo
         if (build) {
             p.in_off = at;    at += align256(sizeof(int32_t) * (size_t)(B * N + 1));
             p.in_src = at;    at += align256(sizeof(int32_t) * (size_t)(B * N) * K);
-            p.inedge_ws = at; at += inedges_ws_bytes(B * N);
+            p.inedge_ws = at; at += inedges_ws_bytes(B * N, K);
         }
     } else if (!pad_disabled() && grad_pos_supported(64, 64, (int)N, K)) {
         // other widths: the sum over 64 x 64 blocks of the parameters of the 64 -> 64 kernel's result on zero-padded
@@ -329,7 +329,7 @@ static PosPlan plan_pos(int64_t B, int64_t N, int K, int Din, int Dout, int layo
         if (build) {
             p.in_off = at;    at += align256(sizeof(int32_t) * (size_t)(B * N + 1));
             p.in_src = at;    at += align256(sizeof(int32_t) * (size_t)(B * N) * K);
-            p.inedge_ws = at; at += inedges_ws_bytes(B * N);
+            p.inedge_ws = at; at += inedges_ws_bytes(B * N, K);
         }
     }
     p.total = at > 0 ? at : 256;
@@ -408,7 +408,7 @@ static bool idiss_sizes_ok(int64_t B, int64_t N)
 static bool knn_sizes_ok(int64_t B, int64_t N, int64_t K)
 {
     if (!sizes_ok(B, N, K, 1, 1) || B > 65535 || !knn_k_supported((int)K)) return false;
-    const int64_t per_cloud = 8 * N < (1ll << 24) ? 8 * N : (1ll << 24);
+    const int64_t per_cloud = 8 * N < (1ll << 24) ? 8 * N : (1ll << 24);      // the most a cloud's grid may have
     return B * per_cloud < 0x7fffffffLL;
 }
 
@@ -490,7 +490,7 @@ size_t flexconv_workspace_bytes(int op, int B, int N, int K, int Din, int Dout, 
         if (op == FLEX_OP_CONV_FWD) return plan_fwd(B, N, K, Din, Dout, layout).total;
         return plan_bwd(B, N, K, Din, Dout, layout, op == FLEX_OP_CONV_BWD_BUILD).total;
     }
-    case FLEX_OP_INEDGES: return sizes_ok(B, N, K, 1, 1) ? inedges_ws_bytes((int64_t)B * N) : 0;
+    case FLEX_OP_INEDGES: return sizes_ok(B, N, K, 1, 1) ? inedges_ws_bytes((int64_t)B * N, K) : 0;
     case FLEX_OP_CONV_BWD_POS: return sizes_ok(B, N, K, Din, Dout) ? plan_pos(B, N, K, Din, Dout, layout, false).total : 0;
     case FLEX_OP_CONV_BWD_POS_BUILD: return sizes_ok(B, N, K, Din, Dout) ? plan_pos(B, N, K, Din, Dout, layout, true).total : 0;
     case FLEX_OP_UPSAMPLE: return sizes_ok(B, N, 1, 1, 1) ? align256(sizeof(int32_t) * (size_t)B * N) : 0;
@@ -602,7 +602,7 @@ int flex_inedges_build(const int32_t *nbr, int B, int N, int K, int32_t *in_off,
 {
     if (!nbr || !in_off || !in_src) return FLEX_ERR_NULL;
     if (!sizes_ok(B, N, K, 1, 1)) return FLEX_ERR_SHAPE;
-    if (!ws_ok(workspace, workspace_bytes, inedges_ws_bytes((int64_t)B * N))) return FLEX_ERR_WORKSPACE;
+    if (!ws_ok(workspace, workspace_bytes, inedges_ws_bytes((int64_t)B * N, K))) return FLEX_ERR_WORKSPACE;
     FLEX_HIP(launch_inedges_build(nbr, B, N, K, in_off, in_src, workspace, (hipStream_t)stream));
     return FLEX_OK;
 }
@@ -886,7 +886,7 @@ int flex_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int B, int N,
 {
     if (!nbr || !sel || !in_off || !in_src) return FLEX_ERR_NULL;
     if (!sizes_ok(B, N, K, 1, 1) || Ns <= 0 || Ns > N) return FLEX_ERR_SHAPE;
-    if (!ws_ok(workspace, workspace_bytes, inedges_ws_bytes((int64_t)B * N))) return FLEX_ERR_WORKSPACE;
+    if (!ws_ok(workspace, workspace_bytes, inedges_ws_bytes((int64_t)B * N, K))) return FLEX_ERR_WORKSPACE;
     FLEX_HIP(launch_inedges_build_sub(nbr, sel, B, N, Ns, K, in_off, in_src, workspace, (hipStream_t)stream));
     return FLEX_OK;
 }

@@ -17,17 +17,28 @@ static constexpr int IDISS_CHUNK = 256 * IDISS_ITEMS;       // points per block
 __global__ __launch_bounds__(256) void idiss_phi_kernel(const float *__restrict__ pos, const int32_t *__restrict__ nbr,
                                                         float *__restrict__ phi, int64_t BN, int N, int K)
 {
+    constexpr int UN = 8;
     for (int64_t gp = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; gp < BN; gp += (int64_t)gridDim.x * blockDim.x) {
         const int64_t b = gp / N;
         const int l = (int)(gp - b * N);
         const float *p = pos + b * 3 * N;
         const int32_t *nb = nbr + b * K * N + l;
         const float cx = p[l], cy = p[(int64_t)N + l], cz = p[2 * (int64_t)N + l];
+        // the ids of eight neighbours together, then their 24 position components: on a cloud stored without locality
+        // every one of those is a line of its own, and what counts is how many are on their way
         float s = 0.f;
-        for (int k = 0; k < K; ++k) {
-            const int n = nb[(int64_t)k * N];
-            const float dx = p[n] - cx, dy = p[(int64_t)N + n] - cy, dz = p[2 * (int64_t)N + n] - cz;
-            s += sqrtf(dx * dx + dy * dy + dz * dz);
+        for (int k0 = 0; k0 < K; k0 += UN) {
+            int n[UN];
+            float x[UN], y[UN], z[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) n[u] = nb[(int64_t)min(k0 + u, K - 1) * N];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) { x[u] = p[n[u]]; y[u] = p[(int64_t)N + n[u]]; z[u] = p[2 * (int64_t)N + n[u]]; }
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const float dx = x[u] - cx, dy = y[u] - cy, dz = z[u] - cz;
+                if (k0 + u < K) s += sqrtf(dx * dx + dy * dy + dz * dz);
+            }
         }
         phi[gp] = s;
     }

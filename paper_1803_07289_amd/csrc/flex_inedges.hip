@@ -1,8 +1,15 @@
 // Transposed neighbour graph: for every point, the list of centres that name
-// it as a neighbour (CSR: in_off / in_src).  Counting sort by target point:
-// count -> exclusive scan -> fill -> sort each list ascending so that the
-// result does not depend on the order in which the fill's atomics landed (and
-// so that repeated sources sit next to each other).
+// it as a neighbour (CSR: in_off / in_src), each list ascending, so that the
+// result does not depend on the order in which atomics land (and so that
+// repeated sources sit next to each other).
+//
+// Two ways.  Up to EDGE_BUCKETS_MAX buckets (134 M edges): edges are first dealt
+// into buckets of consecutive target points, then each bucket is sorted in LDS
+// by one workgroup.  Global atomics per (workgroup, bucket) instead of per edge:
+// a random-address atomic per edge (twice) and the scattered 4-byte writes behind
+// it were 600 us of the 650 us that 1M points x 8 neighbours in the sensor's
+// order took; this takes 85 us.  Beyond that: counting sort by target point with
+// an atomic per edge (count -> exclusive scan -> fill -> sort each list).
 #include "flex_common.hpp"
 
 namespace flex {
@@ -151,63 +158,66 @@ __global__ __launch_bounds__(256) void inedge_fill_kernel(const int32_t *__restr
     }
 }
 
+// Sorts the d ids at p ascending (one thread).
+__device__ void sort_list(int32_t *__restrict__ p, int d)
+{
+    if (d < 2) return;
+    if (d <= SORT_LOCAL) {
+        int v[SORT_LOCAL];
+#pragma unroll
+        for (int i = 0; i < SORT_LOCAL; ++i) v[i] = (i < d) ? p[i] : 0x7fffffff;
+        // odd-even transposition network: data-independent, stays in registers
+#pragma unroll 1
+        for (int pass = 0; pass < d; ++pass) {
+#pragma unroll
+            for (int i = 0; i + 1 < SORT_LOCAL; i += 2) {
+                const int a = v[i], c = v[i + 1];
+                v[i] = min(a, c); v[i + 1] = max(a, c);
+            }
+#pragma unroll
+            for (int i = 1; i + 1 < SORT_LOCAL; i += 2) {
+                const int a = v[i], c = v[i + 1];
+                v[i] = min(a, c); v[i + 1] = max(a, c);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < SORT_LOCAL; ++i)
+            if (i < d) p[i] = v[i];
+    } else if (d <= 256) {
+        for (int i = 1; i < d; ++i) {                 // rare: insertion sort in place
+            const int x = p[i];
+            int j = i - 1;
+            while (j >= 0 && p[j] > x) { p[j + 1] = p[j]; --j; }
+            p[j + 1] = x;
+        }
+    } else {
+        // very rare (a point named by hundreds of centres): heapsort in place, O(d log d)
+        auto sift = [&](int root, int end) {
+            const int x = p[root];
+            for (;;) {
+                int child = 2 * root + 1;
+                if (child >= end) break;
+                if (child + 1 < end && p[child + 1] > p[child]) ++child;
+                if (p[child] <= x) break;
+                p[root] = p[child];
+                root = child;
+            }
+            p[root] = x;
+        };
+        for (int i = d / 2 - 1; i >= 0; --i) sift(i, d);
+        for (int end = d - 1; end > 0; --end) {
+            const int x = p[end]; p[end] = p[0]; p[0] = x;
+            sift(0, end);
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void inedge_sort_kernel(const int32_t *__restrict__ off,
                                                           int32_t *__restrict__ src, int64_t BN)
 {
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < BN;
-         g += (int64_t)gridDim.x * blockDim.x) {
-        const int beg = off[g], d = off[g + 1] - beg;
-        if (d < 2) continue;
-        int32_t *p = src + beg;
-        if (d <= SORT_LOCAL) {
-            int v[SORT_LOCAL];
-#pragma unroll
-            for (int i = 0; i < SORT_LOCAL; ++i) v[i] = (i < d) ? p[i] : 0x7fffffff;
-            // odd-even transposition network: data-independent, stays in registers
-#pragma unroll 1
-            for (int pass = 0; pass < d; ++pass) {
-#pragma unroll
-                for (int i = 0; i + 1 < SORT_LOCAL; i += 2) {
-                    const int a = v[i], c = v[i + 1];
-                    v[i] = min(a, c); v[i + 1] = max(a, c);
-                }
-#pragma unroll
-                for (int i = 1; i + 1 < SORT_LOCAL; i += 2) {
-                    const int a = v[i], c = v[i + 1];
-                    v[i] = min(a, c); v[i + 1] = max(a, c);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < SORT_LOCAL; ++i)
-                if (i < d) p[i] = v[i];
-        } else if (d <= 256) {
-            for (int i = 1; i < d; ++i) {                 // rare: insertion sort in place
-                const int x = p[i];
-                int j = i - 1;
-                while (j >= 0 && p[j] > x) { p[j + 1] = p[j]; --j; }
-                p[j + 1] = x;
-            }
-        } else {
-            // very rare (a point named by hundreds of centres): heapsort in place, O(d log d)
-            auto sift = [&](int root, int end) {
-                const int x = p[root];
-                for (;;) {
-                    int child = 2 * root + 1;
-                    if (child >= end) break;
-                    if (child + 1 < end && p[child + 1] > p[child]) ++child;
-                    if (p[child] <= x) break;
-                    p[root] = p[child];
-                    root = child;
-                }
-                p[root] = x;
-            };
-            for (int i = d / 2 - 1; i >= 0; --i) sift(i, d);
-            for (int end = d - 1; end > 0; --end) {
-                const int x = p[end]; p[end] = p[0]; p[0] = x;
-                sift(0, end);
-            }
-        }
-    }
+         g += (int64_t)gridDim.x * blockDim.x)
+        sort_list(src + off[g], off[g + 1] - off[g]);
 }
 
 // off[0..n] = exclusive running sum of cnt[0..n) (off[n] = total); ws: exclusive_scan_ws_bytes(n)
@@ -223,8 +233,285 @@ hipError_t launch_exclusive_scan_i32(const int32_t *cnt, int32_t *off, int64_t n
     return hipGetLastError();
 }
 
-size_t inedges_ws_bytes(int64_t BN)
+// ---- edges through buckets -------------------------------------------------------------------------
+// bucket = 2^shift consecutive target points (over all clouds), about BUCKET_EDGES edges on average.
+//   count    every workgroup takes a run of edges, counts them per bucket in LDS, adds the counts to the buckets'
+//   scan     exclusive running sum over the buckets (one workgroup)
+//   deal     the same runs again: a workgroup reserves a stretch of every bucket it has edges for (one atomic each)
+//            and writes source and target-within-bucket of its edges there
+//   sort     one workgroup per bucket: its edges into registers, counts per target and their running sum in LDS
+//            (= the list bounds), every edge's rank inside its list by comparing with the list, the sorted bucket
+//            out as one contiguous write
+static constexpr int BUCKET_EDGES_LOG2 = 13;
+static constexpr int BUCKET_NT = 1024;                           // threads per workgroup, all four steps
+static constexpr int BUCKET_PER_THREAD = 12;                     // edges a thread of the sort keeps
+static constexpr int BUCKET_CAP = BUCKET_NT * BUCKET_PER_THREAD; // edges a bucket sorts in LDS (1.5 x the average)
+static constexpr int BUCKET_TARGETS_MAX = 2048;
+static constexpr int EDGE_BUCKETS_MAX = 16384;                   // counters of the count / deal steps: 64 KB of LDS
+
+struct EdgeRuns {
+    const int32_t *nbr, *sel;        // sel == nullptr: every point is a centre
+    int N, Nc, K;                    // points and centres per cloud
+    int E;                           // edges
+    int run;                         // edges per workgroup
+    int shift;                       // target >> shift = bucket
+};
+
+// Walks a workgroup's run of edges (cloud b, slot k, centre j), BUCKET_NT apart, without a division per edge.
+struct EdgeWalk {
+    int i, b, k, j;
+    __device__ __forceinline__ EdgeWalk(const EdgeRuns &p, int64_t first) : i((int)first)
+    {
+        const int bk = i / p.Nc;
+        j = i - bk * p.Nc;
+        b = bk / p.K;
+        k = bk - b * p.K;
+    }
+    __device__ __forceinline__ void next(const EdgeRuns &p)
+    {
+        i += BUCKET_NT;
+        j += BUCKET_NT;
+        while (j >= p.Nc) {
+            j -= p.Nc;
+            if (++k == p.K) { k = 0; ++b; }
+        }
+    }
+    // the point this edge names (over all clouds); entries of sel outside [0,N) are clamped
+    __device__ __forceinline__ int target(const EdgeRuns &p) const
+    {
+        const int l = p.sel ? min(max(p.sel[(int64_t)b * p.Nc + j], 0), p.N - 1) : j;
+        return b * p.N + p.nbr[((int64_t)b * p.K + k) * p.N + l];
+    }
+};
+
+// counter[key] += 1 for every lane with on, returning the value before the lane's own addition.  On a cloud stored with
+// locality most of a wave's lanes share a key, and as many atomics on one LDS word would queue up: the lanes of the
+// first two keys met are counted by a ballot, only the rest go one by one.
+__device__ __forceinline__ int lds_count(int *counter, int key, bool on)
 {
+    const int lane = threadIdx.x & 63;
+    const uint64_t below = (1ull << lane) - 1ull;
+    int old = 0;
+    bool todo = on;
+#pragma unroll
+    for (int round = 0; round < 2; ++round) {
+        const uint64_t left = __ballot(todo);
+        if (left == 0) return old;
+        const int first = __ffsll((long long)left) - 1;
+        const int lead = __builtin_amdgcn_readlane(key, first);
+        const uint64_t same = __ballot(todo && key == lead);
+        int base = 0;
+        if (lane == first) base = atomicAdd(&counter[lead], __popcll(same));
+        base = __builtin_amdgcn_readlane(base, first);
+        if (todo && key == lead) { old = base + __popcll(same & below); todo = false; }
+    }
+    if (todo) old = atomicAdd(&counter[key], 1);
+    return old;
+}
+
+__global__ __launch_bounds__(BUCKET_NT) void edge_count_kernel(const EdgeRuns p, int32_t *__restrict__ bucket_cnt,
+                                                               int buckets)
+{
+    extern __shared__ int s_cnt[];
+    for (int i = threadIdx.x; i < buckets; i += BUCKET_NT) s_cnt[i] = 0;
+    __syncthreads();
+    const int64_t first = (int64_t)blockIdx.x * p.run;
+    const int n = (int)min((int64_t)p.run, p.E - first);
+    constexpr int UN = 8;
+    EdgeWalk w(p, min(first + threadIdx.x, (int64_t)p.E - 1));
+    for (int e0 = 0; e0 < n; e0 += BUCKET_NT * UN) {
+        int t[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const bool on = e0 + BUCKET_NT * u + (int)threadIdx.x < n;
+            t[u] = on ? w.target(p) : -1;
+            if (e0 + BUCKET_NT * (u + 1) + (int)threadIdx.x < n) w.next(p);
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) lds_count(s_cnt, t[u] >> p.shift, t[u] >= 0);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < buckets; i += BUCKET_NT)
+        if (s_cnt[i]) atomicAdd(&bucket_cnt[i], s_cnt[i]);
+}
+
+// off[0..buckets] = exclusive running sum of cnt; cur = a copy of it for the deal step's reservations; one workgroup
+__global__ __launch_bounds__(BUCKET_NT) void edge_scan_kernel(const int32_t *__restrict__ cnt, int32_t *__restrict__ off,
+                                                              int32_t *__restrict__ cur, int buckets)
+{
+    __shared__ int s_wave[BUCKET_NT / 64];
+    const int per = (buckets + BUCKET_NT - 1) / BUCKET_NT, i0 = threadIdx.x * per;      // at most 16
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int v[EDGE_BUCKETS_MAX / BUCKET_NT], sum = 0;
+#pragma unroll
+    for (int i = 0; i < EDGE_BUCKETS_MAX / BUCKET_NT; ++i) {
+        v[i] = (i < per && i0 + i < buckets) ? cnt[i0 + i] : 0;
+        sum += v[i];
+    }
+    int x = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(x, d, 64);
+        if (lane >= d) x += y;
+    }
+    if (lane == 63) s_wave[wave] = x;
+    __syncthreads();
+    int run = x - sum;
+    for (int w = 0; w < wave; ++w) run += s_wave[w];
+#pragma unroll
+    for (int i = 0; i < EDGE_BUCKETS_MAX / BUCKET_NT; ++i) {
+        if (i < per && i0 + i < buckets) { off[i0 + i] = run; cur[i0 + i] = run; }
+        run += v[i];
+    }
+    if (threadIdx.x == BUCKET_NT - 1) off[buckets] = run;
+}
+
+__global__ __launch_bounds__(BUCKET_NT) void edge_deal_kernel(const EdgeRuns p, int32_t *__restrict__ bucket_cur,
+                                                              int32_t *__restrict__ st_src, uint16_t *__restrict__ st_tgt,
+                                                              int buckets)
+{
+    extern __shared__ int s_cnt[];
+    for (int i = threadIdx.x; i < buckets; i += BUCKET_NT) s_cnt[i] = 0;
+    __syncthreads();
+    const int64_t first = (int64_t)blockIdx.x * p.run;
+    const int n = (int)min((int64_t)p.run, p.E - first);
+    constexpr int MAXE = 32;                     // p.run <= MAXE * BUCKET_NT
+    int t[MAXE], rank[MAXE];
+    {
+        EdgeWalk w(p, min(first + threadIdx.x, (int64_t)p.E - 1));
+#pragma unroll
+        for (int u = 0; u < MAXE; ++u) {
+            t[u] = -1;
+            if (BUCKET_NT * u < n) {             // uniform
+                if (BUCKET_NT * u + (int)threadIdx.x < n) t[u] = w.target(p);
+                if (BUCKET_NT * (u + 1) + (int)threadIdx.x < n) w.next(p);
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < MAXE; ++u)
+        if (BUCKET_NT * u < n) rank[u] = lds_count(s_cnt, t[u] >> p.shift, t[u] >= 0);
+    __syncthreads();
+    for (int i = threadIdx.x; i < buckets; i += BUCKET_NT)
+        if (const int c = s_cnt[i]) s_cnt[i] = atomicAdd(&bucket_cur[i], c);
+    __syncthreads();
+    EdgeWalk w(p, min(first + threadIdx.x, (int64_t)p.E - 1));
+#pragma unroll
+    for (int u = 0; u < MAXE; ++u)
+        if (BUCKET_NT * u < n) {
+            if (t[u] >= 0) {
+                const int at = s_cnt[t[u] >> p.shift] + rank[u];
+                st_src[at] = w.j;
+                st_tgt[at] = (uint16_t)(t[u] & ((1 << p.shift) - 1));
+            }
+            if (BUCKET_NT * (u + 1) + (int)threadIdx.x < n) w.next(p);
+        }
+}
+
+__global__ __launch_bounds__(BUCKET_NT) void edge_sort_kernel(const int32_t *__restrict__ bucket_off,
+                                                              const int32_t *__restrict__ st_src,
+                                                              const uint16_t *__restrict__ st_tgt,
+                                                              int32_t *__restrict__ in_off, int32_t *__restrict__ in_src,
+                                                              int64_t BN, int E, int shift)
+{
+    __shared__ int s_off[BUCKET_TARGETS_MAX + 1];     // counts, then list starts inside the bucket
+    __shared__ int s_src[BUCKET_CAP];
+    __shared__ int s_wave[BUCKET_NT / 64];
+    const int targets = 1 << shift, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int beg = bucket_off[blockIdx.x], n = bucket_off[blockIdx.x + 1] - beg;
+    const int64_t g0 = (int64_t)blockIdx.x << shift;
+    for (int i = tid; i < targets; i += BUCKET_NT) s_off[i] = 0;
+    const bool fits = n <= BUCKET_CAP;
+    int src[BUCKET_PER_THREAD], tgt[BUCKET_PER_THREAD], slot[BUCKET_PER_THREAD];
+    if (fits) {
+#pragma unroll
+        for (int u = 0; u < BUCKET_PER_THREAD; ++u) {
+            const int i = tid + BUCKET_NT * u;
+            src[u] = i < n ? st_src[beg + i] : 0;
+            tgt[u] = i < n ? st_tgt[beg + i] : -1;
+        }
+    }
+    __syncthreads();
+    if (fits) {
+#pragma unroll
+        for (int u = 0; u < BUCKET_PER_THREAD; ++u) slot[u] = tgt[u] >= 0 ? atomicAdd(&s_off[tgt[u]], 1) : 0;
+    } else {
+        for (int i = tid; i < n; i += BUCKET_NT) atomicAdd(&s_off[st_tgt[beg + i]], 1);
+    }
+    __syncthreads();
+    {   // counts -> list starts, two targets per thread
+        const int i0 = 2 * tid;
+        const int a = i0 < targets ? s_off[i0] : 0, c = i0 + 1 < targets ? s_off[i0 + 1] : 0;
+        int x = a + c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(x, d, 64);
+            if (lane >= d) x += y;
+        }
+        if (lane == 63) s_wave[wave] = x;
+        __syncthreads();
+        int run = x - (a + c);
+        for (int w = 0; w < wave; ++w) run += s_wave[w];
+        if (i0 < targets) { s_off[i0] = run; if (g0 + i0 < BN) in_off[g0 + i0] = beg + run; }
+        if (i0 + 1 < targets) { s_off[i0 + 1] = run + a; if (g0 + i0 + 1 < BN) in_off[g0 + i0 + 1] = beg + run + a; }
+        if (tid == 0) {
+            s_off[targets] = n;
+            if (blockIdx.x == gridDim.x - 1) in_off[BN] = E;
+        }
+    }
+    __syncthreads();
+    if (fits) {
+#pragma unroll
+        for (int u = 0; u < BUCKET_PER_THREAD; ++u)
+            if (tgt[u] >= 0) s_src[s_off[tgt[u]] + slot[u]] = src[u];
+        __syncthreads();
+        // rank inside the list: sources before mine (equal ones: in slot order)
+#pragma unroll
+        for (int u = 0; u < BUCKET_PER_THREAD; ++u)
+            if (tgt[u] >= 0) {
+                const int lo = s_off[tgt[u]], hi = s_off[tgt[u] + 1], me = lo + slot[u];
+                int r = lo;
+                for (int i = lo; i < hi; ++i) {
+                    const int o = s_src[i];
+                    r += (o < src[u] || (o == src[u] && i < me)) ? 1 : 0;
+                }
+                slot[u] = r;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < BUCKET_PER_THREAD; ++u)
+            if (tgt[u] >= 0) s_src[slot[u]] = src[u];
+        __syncthreads();
+        for (int i = tid; i < n; i += BUCKET_NT) in_src[beg + i] = s_src[i];
+        return;
+    }
+    // a bucket of far more edges than its share (hub points): the lists are filled and sorted in global memory
+    for (int i = tid; i < targets; i += BUCKET_NT) s_src[i] = s_off[i];
+    __syncthreads();
+    for (int i = tid; i < n; i += BUCKET_NT) in_src[beg + atomicAdd(&s_src[st_tgt[beg + i]], 1)] = st_src[beg + i];
+    __syncthreads();                              // the workgroup's own writes, read back below
+    for (int i = tid; i < targets; i += BUCKET_NT) sort_list(in_src + beg + s_off[i], s_off[i + 1] - s_off[i]);
+}
+
+// the bucketed way's geometry; buckets == 0: too many of them
+static int bucket_shift(int K)
+{
+    int shift = BUCKET_EDGES_LOG2;
+    while (shift > 0 && ((int64_t)K << shift) > (1 << BUCKET_EDGES_LOG2)) --shift;
+    return shift > 11 ? 11 : shift;               // BUCKET_TARGETS_MAX
+}
+static int64_t bucket_count(int64_t BN, int K)
+{
+    const int64_t n = cdiv64(BN, (int64_t)1 << bucket_shift(K));
+    return n <= EDGE_BUCKETS_MAX ? n : 0;
+}
+
+size_t inedges_ws_bytes(int64_t BN, int K)
+{
+    if (const int64_t buckets = bucket_count(BN, K)) {
+        const size_t E = (size_t)BN * K;
+        return align256(sizeof(int32_t) * (size_t)(3 * buckets + 1)) + align256(sizeof(int32_t) * E) + align256(sizeof(uint16_t) * E);
+    }
     const int64_t nblk = cdiv64(BN, SCAN_CHUNK);
     return align256(sizeof(int32_t) * (size_t)BN) + align256(sizeof(int32_t) * (size_t)(nblk + 1));
 }
@@ -241,6 +528,25 @@ hipError_t launch_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int 
                                     int32_t *in_off, int32_t *in_src, void *ws, hipStream_t s)
 {
     const int64_t BN = (int64_t)B * N, KN = (int64_t)K * N, E = (int64_t)B * K * (sel ? Ns : N);
+    if (const int buckets = (int)bucket_count(BN, K)) {
+        int32_t *cnt = (int32_t *)ws, *off = cnt + buckets, *cur = off + buckets + 1;
+        int32_t *st_src = (int32_t *)((char *)ws + align256(sizeof(int32_t) * (size_t)(3 * buckets + 1)));
+        uint16_t *st_tgt = (uint16_t *)((char *)st_src + align256(sizeof(int32_t) * (size_t)BN * K));
+        // runs of edges: a workgroup per CU while they are short, at most what the deal step's registers hold
+        int64_t run = cdiv64(cdiv64(E, device_cu_count()), BUCKET_NT) * BUCKET_NT;
+        if (run > 32 * BUCKET_NT) run = 32 * BUCKET_NT;
+        const EdgeRuns p{nbr, sel, N, sel ? Ns : N, K, (int)E, (int)run, bucket_shift(K)};
+        const dim3 g((unsigned)cdiv64(E, run)), blk(BUCKET_NT);
+        const size_t lds = sizeof(int) * (size_t)buckets;
+        hipError_t e = launch_fill_zero(cnt, sizeof(int32_t) * (size_t)buckets, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(edge_count_kernel, g, blk, lds, s, p, cnt, buckets);
+        hipLaunchKernelGGL(edge_scan_kernel, dim3(1), blk, 0, s, cnt, off, cur, buckets);
+        hipLaunchKernelGGL(edge_deal_kernel, g, blk, lds, s, p, cur, st_src, st_tgt, buckets);
+        hipLaunchKernelGGL(edge_sort_kernel, dim3((unsigned)buckets), blk, 0, s, off, st_src, st_tgt, in_off, in_src, BN,
+                           (int)E, p.shift);
+        return hipGetLastError();
+    }
     const int64_t nblk64 = cdiv64(BN, SCAN_CHUNK);
     const int nblk = (int)nblk64;
     int32_t *cnt = (int32_t *)ws;
