@@ -495,7 +495,7 @@ size_t flexconv_workspace_bytes(int op, int B, int N, int K, int Din, int Dout, 
     case FLEX_OP_CONV_BWD_POS_BUILD: return sizes_ok(B, N, K, Din, Dout) ? plan_pos(B, N, K, Din, Dout, layout, true).total : 0;
     case FLEX_OP_UPSAMPLE: return sizes_ok(B, N, 1, 1, 1) ? align256(sizeof(int32_t) * (size_t)B * N) : 0;
     case FLEX_OP_IDISS: return idiss_sizes_ok(B, N) ? idiss_ws_bytes(B, N) : 0;
-    case FLEX_OP_KNN: return knn_sizes_ok(B, N, K) ? knn_ws_bytes(B, N) : 0;
+    case FLEX_OP_KNN: return knn_sizes_ok(B, N, K) ? knn_ws_bytes(B, N, K) : 0;
     default: return 0;
     }
 }
@@ -847,7 +847,7 @@ int flex_knn(const float *pos, int32_t *nbr, int B, int N, int K, void *workspac
 {
     if (!pos || !nbr) return FLEX_ERR_NULL;
     if (!knn_sizes_ok(B, N, K)) return FLEX_ERR_SHAPE;
-    if (!ws_ok(workspace, workspace_bytes, knn_ws_bytes(B, N))) return FLEX_ERR_WORKSPACE;
+    if (!ws_ok(workspace, workspace_bytes, knn_ws_bytes(B, N, K))) return FLEX_ERR_WORKSPACE;
     FLEX_HIP(launch_knn(pos, nbr, B, N, K, workspace, (hipStream_t)stream));
     return FLEX_OK;
 }

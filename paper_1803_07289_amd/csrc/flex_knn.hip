@@ -4,21 +4,26 @@
 // ((dx*dx + dy*dy) + dz*dz) with every operation rounded on its own, the form the CPU check uses, so
 // that the ranking (an integer-valued decision) comes out identical.
 //
-// Steps per call: bounding box of each cloud -> grid of cubic cells (at most 2^24 cells, about
-// eight cells per point) -> counting sort of the points by cell (count, scan, fill of (x,y,z,id)
-// records) -> one thread per point walks the shells of cells around its own cell, keeps the K best
-// in registers and stops once the K-th distance is inside the block of cells already searched.
+// Steps per call: bounding box of each cloud -> grid of cubic cells (at most 2^24) -> counting sort
+// of the points by cell (count, scan, fill of (x,y,z,id) records) -> one thread per point, in cell
+// order, searches the 27 cells around its own, then shell by shell, keeps the K best in registers
+// and stops once the K-th distance is inside the block of cells already searched -> the lists, so
+// far in cell order, go to their places.
 #include "flex_common.hpp"
 
 namespace flex {
 
 static constexpr int KNN_MAX_CELLS_LOG2 = 24;
 
-// cells a cloud's grid may have: about eight per point
-__host__ __device__ inline int64_t knn_cell_cap(int64_t N)
+// cells a cloud's grid may have: 16 / K per point (at most 8).  On scanned surfaces, whose points fill few of the box's cells, the
+// block of 27 cells then holds some 50 points at K = 8 and nearly always the K nearest; in a filled volume it takes the
+// second shell, 62 points.  Eight per point, whatever K, made four searches of five go on to the second or third shell
+// (125 or 343 cells, most of them empty) and cost a 32 MB table for 1M points: 64 us of running sums instead of 20.
+__host__ __device__ inline int64_t knn_cell_cap(int64_t N, int K)
 {
-    const int64_t want = 8 * N;
-    return want < ((int64_t)1 << KNN_MAX_CELLS_LOG2) ? want : ((int64_t)1 << KNN_MAX_CELLS_LOG2);
+    const int64_t share = 16 * N / K > 1 ? 16 * N / K : 1, eight = 8 * N, most = (int64_t)1 << KNN_MAX_CELLS_LOG2;
+    const int64_t want = share < eight ? share : eight;
+    return want < most ? want : most;
 }
 
 struct KnnGrid {
@@ -37,11 +42,14 @@ __device__ __forceinline__ float from_ordered_bits(unsigned u)
     return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
 }
 
-// bbox[b][0..2] = min, [3..5] = max, as order-preserving unsigned keys (min starts at ~0, max at 0)
-__global__ __launch_bounds__(256) void knn_bbox_init_kernel(unsigned *__restrict__ bbox, int B)
+// bbox[b][0..2] = min, [3..5] = max, as order-preserving unsigned keys (min starts at ~0, max at 0); the cells' counters
+// start at zero
+__global__ __launch_bounds__(256) void knn_init_kernel(unsigned *__restrict__ bbox, int B, int32_t *__restrict__ cnt,
+                                                       int64_t cells)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < 6 * B) bbox[i] = (i % 6 < 3) ? 0xffffffffu : 0u;
+    for (int64_t c = i; c < cells; c += (int64_t)gridDim.x * blockDim.x) cnt[c] = 0;
 }
 
 __global__ __launch_bounds__(256) void knn_bbox_kernel(const float *__restrict__ pos, unsigned *__restrict__ bbox, int N)
@@ -78,9 +86,9 @@ __global__ __launch_bounds__(256) void knn_bbox_kernel(const float *__restrict__
     }
 }
 
-// every thread derives the same grid from the bounding box: cubic cells, about eight per point, at
-// most 2^24 in total; a flat or degenerate box gets one layer of cells along its thin axes
-__device__ __forceinline__ KnnGrid knn_grid(const unsigned *__restrict__ bbox, int b, int N)
+// every thread derives the same grid from the bounding box: cubic cells, at most cap in total; a
+// flat or degenerate box gets one layer of cells along its thin axes
+__device__ __forceinline__ KnnGrid knn_grid(const unsigned *__restrict__ bbox, int b, int64_t cap)
 {
     KnnGrid g;
     float ext[3];
@@ -90,7 +98,6 @@ __device__ __forceinline__ KnnGrid knn_grid(const unsigned *__restrict__ bbox, i
         ext[d] = fmaxf(from_ordered_bits(bbox[6 * b + 3 + d]) - g.lo[d], 0.f);
     }
     const float longest = fmaxf(fmaxf(ext[0], ext[1]), fmaxf(ext[2], 1e-30f));
-    const int64_t cap = knn_cell_cap(N);
     float cells = (float)cap;
     float h = longest;                                   // one cell if everything else fails
     // volume / cells with thin axes counted as one cell thick; two refinements settle the estimate
@@ -130,48 +137,56 @@ __device__ __forceinline__ void knn_cell_of(const KnnGrid &g, float x, float y, 
     cz = min(g.n[2] - 1, max(0, (int)((z - g.lo[2]) * g.inv_h)));
 }
 
-// cell[b*N + l] = linear cell of the point; cnt[b*CELLS + cell] += 1
+// cell[b*N + l] = linear cell of the point, place[b*N + l] = its number among the cell's points (in no set order)
 __global__ __launch_bounds__(256) void knn_count_kernel(const float *__restrict__ pos, const unsigned *__restrict__ bbox,
-                                                        int32_t *__restrict__ cell, int32_t *__restrict__ cnt, int N,
-                                                        int64_t cells_per_cloud)
+                                                        int32_t *__restrict__ cell, int32_t *__restrict__ place,
+                                                        int32_t *__restrict__ cnt, int N, int64_t cells_per_cloud)
 {
     const int b = blockIdx.y;
-    const KnnGrid g = knn_grid(bbox, b, N);
+    const KnnGrid g = knn_grid(bbox, b, cells_per_cloud);
     const float *p = pos + (int64_t)b * 3 * N;
     for (int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; l < N; l += (int64_t)gridDim.x * blockDim.x) {
         int cx, cy, cz;
         knn_cell_of(g, p[l], p[(int64_t)N + l], p[2 * (int64_t)N + l], cx, cy, cz);
         const int c = (cz * g.n[1] + cy) * g.n[0] + cx;
         cell[(int64_t)b * N + l] = c;
-        atomicAdd(&cnt[b * cells_per_cloud + c], 1);
+        place[(int64_t)b * N + l] = atomicAdd(&cnt[b * cells_per_cloud + c], 1);
     }
 }
 
-// rec[off[cell] + slot] = (x, y, z, id); cnt runs down to zero
+// rec[off[cell] + place] = (x, y, z, id); place becomes the record's number inside the cloud
 __global__ __launch_bounds__(256) void knn_fill_kernel(const float *__restrict__ pos, const int32_t *__restrict__ cell,
-                                                       const int32_t *__restrict__ off, int32_t *__restrict__ cnt,
+                                                       const int32_t *__restrict__ off, int32_t *__restrict__ place,
                                                        float4 *__restrict__ rec, int N, int64_t cells_per_cloud)
 {
     const int b = blockIdx.y;
     const float *p = pos + (int64_t)b * 3 * N;
     for (int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; l < N; l += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t c = b * cells_per_cloud + cell[(int64_t)b * N + l];
-        const int slot = atomicSub(&cnt[c], 1) - 1;
-        rec[off[c] + slot] = make_float4(p[l], p[(int64_t)N + l], p[2 * (int64_t)N + l], __int_as_float((int)l));
+        const int at = off[b * cells_per_cloud + cell[(int64_t)b * N + l]] + place[(int64_t)b * N + l];
+        rec[at] = make_float4(p[l], p[(int64_t)N + l], p[2 * (int64_t)N + l], __int_as_float((int)l));
+        place[(int64_t)b * N + l] = at - b * N;
     }
 }
 
-// (d2, id) ascending
-__device__ __forceinline__ bool knn_before(float d, int i, float bd, int bi) { return d < bd || (d == bd && i < bi); }
+// (d2, id) as one number whose order is theirs: the bits of d2 (non-negative: they order like the value) above those
+// of id, read as a double -- positive, and finite since a float's exponent field fills only the upper bits of a
+// double's -- so that the sorted insertion is a minimum and a maximum per place.  (Double arithmetic keeps denormals
+// here, which the pairs with d2 == 0 are.)
+__device__ __forceinline__ double knn_key(float d2, int id) { return __hiloint2double(__float_as_int(d2), id); }
 
-// One thread per point, in cell order (neighbouring threads search neighbouring cells).
+// One thread per point, in cell order (neighbouring threads search neighbouring cells); lists[record][K].
+// What bounds it is the chain offsets -> records of one thread.  So the nine rows of cells of the first block (three
+// cells each, contiguous records) have all their offsets requested at once, and one loop runs over the records of all
+// nine, the next one already requested, so that a wave waits for its longest total and not for the longest of every
+// row; the rows' bounds wait in LDS.
 template <int K>
 __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict__ rec, const int32_t *__restrict__ off,
-                                                        const unsigned *__restrict__ bbox, int32_t *__restrict__ nbr,
+                                                        const unsigned *__restrict__ bbox, int32_t *__restrict__ lists,
                                                         int N, int64_t cells_per_cloud)
 {
-    const int b = blockIdx.y;
-    const KnnGrid g = knn_grid(bbox, b, N);
+    __shared__ int s_beg[9][256], s_end[9][256];
+    const int b = blockIdx.y, tid = threadIdx.x;
+    const KnnGrid g = knn_grid(bbox, b, cells_per_cloud);
     const int32_t *offb = off + b * cells_per_cloud;
     // slack for the rounding of the cell planes lo + c*h and of the cell a point was put in
     const float span = fmaxf(fmaxf(g.n[0], g.n[1]), (float)g.n[2]) * g.h;
@@ -179,47 +194,26 @@ __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict
     const float eps = 4e-6f * span + 2e-6f * far;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
         const float4 me = rec[(int64_t)b * N + i];
-        const int self = __float_as_int(me.w);
         int cx, cy, cz;
         knn_cell_of(g, me.x, me.y, me.z, cx, cy, cz);
-        float bd[K];
-        int bi[K];
+        double best[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) { bd[k] = __builtin_inff(); bi[k] = 0x7fffffff; }
-        const int rmax = max(max(g.n[0], g.n[1]), g.n[2]);
-        for (int r = 0; r <= rmax; ++r) {
-            const int z0 = max(cz - r, 0), z1 = min(cz + r, g.n[2] - 1);
-            const int y0 = max(cy - r, 0), y1 = min(cy + r, g.n[1] - 1);
-            const int x0 = max(cx - r, 0), x1 = min(cx + r, g.n[0] - 1);
-            for (int z = z0; z <= z1; ++z)
-                for (int y = y0; y <= y1; ++y) {
-                    const bool face = (abs(z - cz) == r) || (abs(y - cy) == r);
-                    // on a face row every x is on the shell; otherwise only the two ends are
-                    const int xs = face ? 1 : max(2 * r, 1);
-                    for (int x = face ? x0 : cx - r; x <= x1; x += xs) {
-                        if (x < x0) continue;
-                        const int c = (z * g.n[1] + y) * g.n[0] + x;
-                        const int e1 = offb[c + 1];
-                        for (int e = offb[c]; e < e1; ++e) {
-                            const float4 q = rec[e];
-                            const float dx = __fsub_rn(q.x, me.x), dy = __fsub_rn(q.y, me.y), dz = __fsub_rn(q.z, me.z);
-                            const float d2 = __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
-                            int id = __float_as_int(q.w);
-                            if (!knn_before(d2, id, bd[K - 1], bi[K - 1])) continue;
-                            float d = d2;
+        for (int k = 0; k < K; ++k) best[k] = knn_key(__builtin_inff(), 0x7fffffff);
+        auto offer = [&](const float4 &q) {
+            const float dx = __fsub_rn(q.x, me.x), dy = __fsub_rn(q.y, me.y), dz = __fsub_rn(q.z, me.z);
+            const float d2 = __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
+            double x = knn_key(d2, __float_as_int(q.w));
+            if (x < best[K - 1]) {
 #pragma unroll
-                            for (int k = 0; k < K; ++k) {        // sorted insertion: the candidate bubbles down the list
-                                const bool first = knn_before(d, id, bd[k], bi[k]);
-                                const float td = first ? bd[k] : d;
-                                const int ti = first ? bi[k] : id;
-                                bd[k] = first ? d : bd[k];
-                                bi[k] = first ? id : bi[k];
-                                d = td; id = ti;
-                            }
-                        }
-                    }
+                for (int k = 0; k < K; ++k) {        // sorted insertion: the candidate bubbles down the list
+                    const double worse = fmax(best[k], x);
+                    best[k] = fmin(best[k], x);
+                    x = worse;
                 }
-            // everything outside the block of cells [c-r, c+r] is at least `reach` away
+            }
+        };
+        // is everything outside the block of cells [c-r, c+r] farther away than the K-th so far?
+        auto settled = [&](int r) {
             float reach = __builtin_inff();
             if (cx - r > 0) reach = fminf(reach, me.x - (g.lo[0] + (float)(cx - r) * g.h));
             if (cx + r < g.n[0] - 1) reach = fminf(reach, (g.lo[0] + (float)(cx + r + 1) * g.h) - me.x);
@@ -228,45 +222,121 @@ __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict
             if (cz - r > 0) reach = fminf(reach, me.z - (g.lo[2] + (float)(cz - r) * g.h));
             if (cz + r < g.n[2] - 1) reach = fminf(reach, (g.lo[2] + (float)(cz + r + 1) * g.h) - me.z);
             reach -= eps;
-            if (reach == __builtin_inff()) break;                       // the block is the whole grid
-            if (reach > 0.f && bd[K - 1] < reach * reach * 0.999999f) break;
-        }
+            if (reach == __builtin_inff()) return true;                 // the block is the whole grid
+            const float kth = __int_as_float(__double2hiint(best[K - 1]));
+            return reach > 0.f && kth < reach * reach * 0.999999f;
+        };
+        {
+            // the 27 cells around: the non-empty rows' bounds to LDS, then one loop over their records
+            int b0[9], b1[9];
 #pragma unroll
-        for (int k = 0; k < K; ++k) nbr[((int64_t)b * K + k) * N + self] = bi[k];
+            for (int j = 0; j < 9; ++j) {
+                const int z = cz + j / 3 - 1, y = cy + j % 3 - 1;
+                const bool on = z >= 0 && z < g.n[2] && y >= 0 && y < g.n[1];
+                const int row = ((on ? z : cz) * g.n[1] + (on ? y : cy)) * g.n[0];
+                b0[j] = offb[row + max(cx - 1, 0)];
+                b1[j] = offb[row + min(cx + 1, g.n[0] - 1) + 1];
+                if (!on) b1[j] = b0[j];
+            }
+            int rows = 0;
+#pragma unroll
+            for (int j = 0; j < 9; ++j)
+                if (b0[j] < b1[j]) { s_beg[rows][tid] = b0[j]; s_end[rows][tid] = b1[j]; ++rows; }
+            // (the thread's own cell is never empty)
+            int j = 0, e = s_beg[0][tid], end = s_end[0][tid];
+            float4 q = rec[e];
+            for (bool more = true; more;) {
+                const float4 cur = q;
+                if (++e == end) {
+                    more = ++j < rows;
+                    if (more) { e = s_beg[j][tid]; end = s_end[j][tid]; }
+                }
+                if (more) q = rec[e];
+                offer(cur);
+            }
+        }
+        const int rmax = max(max(g.n[0], g.n[1]), g.n[2]);
+        for (int r = 2; !settled(r - 1) && r <= rmax; ++r) {
+            const int z0 = max(cz - r, 0), z1 = min(cz + r, g.n[2] - 1);
+            const int y0 = max(cy - r, 0), y1 = min(cy + r, g.n[1] - 1);
+            const int x0 = max(cx - r, 0), x1 = min(cx + r, g.n[0] - 1);
+            for (int z = z0; z <= z1; ++z)
+                for (int y = y0; y <= y1; ++y) {
+                    const int row = (z * g.n[1] + y) * g.n[0];
+                    // on a face row every x is on the shell; otherwise only the two ends are
+                    if (abs(z - cz) == r || abs(y - cy) == r) {
+                        const int e1 = offb[row + x1 + 1];
+                        for (int e = offb[row + x0]; e < e1; ++e) offer(rec[e]);
+                    } else {
+                        const int xa = cx - r, xb = cx + r;
+                        const int a0 = xa >= 0 ? offb[row + xa] : 0, a1 = xa >= 0 ? offb[row + xa + 1] : 0;
+                        const int c0 = xb < g.n[0] ? offb[row + xb] : 0, c1 = xb < g.n[0] ? offb[row + xb + 1] : 0;
+                        for (int e = a0; e < a1; ++e) offer(rec[e]);
+                        for (int e = c0; e < c1; ++e) offer(rec[e]);
+                    }
+                }
+        }
+        int32_t *dst = lists + ((int64_t)b * N + i) * K;
+#pragma unroll
+        for (int k = 0; k < K; ++k) dst[k] = __double2loint(best[k]);
     }
 }
 
-size_t knn_ws_bytes(int B, int N)
+// nbr[b][k][l] = lists[b][place of l][k]: a list is read as one stretch and the tensor written in its own order.  (The
+// search writing to the points' own columns, on a cloud in the sensor's order 4 bytes per line of memory, took 100 us
+// of the 365 that 1M points x 8 cost.)
+__global__ __launch_bounds__(256) void knn_place_kernel(const int32_t *__restrict__ lists,
+                                                        const int32_t *__restrict__ place, int32_t *__restrict__ nbr,
+                                                        int N, int K)
 {
-    const int64_t cells = (int64_t)B * knn_cell_cap(N);
-    return align256(sizeof(float4) * (size_t)B * N) + align256(sizeof(int32_t) * (size_t)B * N) +
-           align256(sizeof(int32_t) * (size_t)(cells + 1)) * 2 + exclusive_scan_ws_bytes(cells) + align256(sizeof(unsigned) * 6 * (size_t)B);
+    const int b = blockIdx.y;
+    for (int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; l < N; l += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t *src = lists + ((int64_t)b * N + place[(int64_t)b * N + l]) * K;
+        int32_t *dst = nbr + (int64_t)b * K * N + l;
+        for (int k0 = 0; k0 < K; k0 += 8) {
+            int v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = src[min(k0 + u, K - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (k0 + u < K) dst[(int64_t)(k0 + u) * N] = v[u];
+        }
+    }
+}
+
+size_t knn_ws_bytes(int B, int N, int K)
+{
+    const int64_t cells = (int64_t)B * knn_cell_cap(N, K);
+    return align256(sizeof(float4) * (size_t)B * N) + 2 * align256(sizeof(int32_t) * (size_t)B * N) +
+           align256(sizeof(int32_t) * (size_t)B * N * K) + align256(sizeof(int32_t) * (size_t)(cells + 1)) * 2 +
+           exclusive_scan_ws_bytes(cells) + align256(sizeof(unsigned) * 6 * (size_t)B);
 }
 
 hipError_t launch_knn(const float *pos, int32_t *nbr, int B, int N, int K, void *ws, hipStream_t s)
 {
-    const int64_t cpc = knn_cell_cap(N), cells = (int64_t)B * cpc;
+    const int64_t cpc = knn_cell_cap(N, K), cells = (int64_t)B * cpc;
     char *at = (char *)ws;
     float4 *rec = (float4 *)at;       at += align256(sizeof(float4) * (size_t)B * N);
     int32_t *cell = (int32_t *)at;    at += align256(sizeof(int32_t) * (size_t)B * N);
+    int32_t *place = (int32_t *)at;   at += align256(sizeof(int32_t) * (size_t)B * N);
+    int32_t *lists = (int32_t *)at;   at += align256(sizeof(int32_t) * (size_t)B * N * K);
     int32_t *cnt = (int32_t *)at;     at += align256(sizeof(int32_t) * (size_t)(cells + 1));
     int32_t *off = (int32_t *)at;     at += align256(sizeof(int32_t) * (size_t)(cells + 1));
     void *scan_ws = at;               at += exclusive_scan_ws_bytes(cells);
     unsigned *bbox = (unsigned *)at;
-    hipLaunchKernelGGL(knn_bbox_init_kernel, dim3((6 * B + 255) / 256), dim3(256), 0, s, bbox, B);
+    const int64_t ib = cdiv64(cells > 6 * (int64_t)B ? cells : 6 * (int64_t)B, 256);
+    hipLaunchKernelGGL(knn_init_kernel, dim3((unsigned)(ib < 8192 ? ib : 8192)), dim3(256), 0, s, bbox, B, cnt, cells);
     int nb = (int)((N + 255) / 256);
     if (nb > 2048) nb = 2048;
     hipLaunchKernelGGL(knn_bbox_kernel, dim3(nb < 512 ? nb : 512, B), dim3(256), 0, s, pos, bbox, N);
-    hipError_t e = launch_fill_zero(cnt, sizeof(int32_t) * (size_t)cells, s);
+    hipLaunchKernelGGL(knn_count_kernel, dim3(nb, B), dim3(256), 0, s, pos, bbox, cell, place, cnt, N, cpc);
+    hipError_t e = launch_exclusive_scan_i32(cnt, off, cells, scan_ws, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(knn_count_kernel, dim3(nb, B), dim3(256), 0, s, pos, bbox, cell, cnt, N, cpc);
-    e = launch_exclusive_scan_i32(cnt, off, cells, scan_ws, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(knn_fill_kernel, dim3(nb, B), dim3(256), 0, s, pos, cell, off, cnt, rec, N, cpc);
+    hipLaunchKernelGGL(knn_fill_kernel, dim3(nb, B), dim3(256), 0, s, pos, cell, off, place, rec, N, cpc);
     int qb = (int)((N + 255) / 256);
     if (qb > 65535) qb = 65535;
 #define FLEX_KNN_CASE(KK) \
-    case KK: hipLaunchKernelGGL(knn_query_kernel<KK>, dim3(qb, B), dim3(256), 0, s, rec, off, bbox, nbr, N, cpc); break;
+    case KK: hipLaunchKernelGGL(knn_query_kernel<KK>, dim3(qb, B), dim3(256), 0, s, rec, off, bbox, lists, N, cpc); break;
     switch (K) {
         FLEX_KNN_CASE(1) FLEX_KNN_CASE(2) FLEX_KNN_CASE(3) FLEX_KNN_CASE(4) FLEX_KNN_CASE(5) FLEX_KNN_CASE(6)
         FLEX_KNN_CASE(7) FLEX_KNN_CASE(8) FLEX_KNN_CASE(9) FLEX_KNN_CASE(10) FLEX_KNN_CASE(12) FLEX_KNN_CASE(16)
@@ -274,6 +344,7 @@ hipError_t launch_knn(const float *pos, int32_t *nbr, int B, int N, int K, void 
     default: return hipErrorInvalidValue;
     }
 #undef FLEX_KNN_CASE
+    hipLaunchKernelGGL(knn_place_kernel, dim3(qb, B), dim3(256), 0, s, lists, place, nbr, N, K);
     return hipGetLastError();
 }
 
