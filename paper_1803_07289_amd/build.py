@@ -37,6 +37,8 @@ def _jobs():
     for name in ("flex_api", "flex_prep", "flex_misc", "flex_pool", "flex_inedges", "flex_upsample", "flex_idiss", "flex_knn",
                  "flex_calibrate"):
         jobs.append((os.path.join(CSRC, name + ".hip"), os.path.join(OBJ, name + ".o"), []))
+    for csr in (0, 1):
+        jobs.append((os.path.join(CSRC, "flex_tile.hip"), os.path.join(OBJ, f"flex_tile_{csr}.o"), [f"-DFLEX_TILE_CSR={csr}"]))
     for (di, do, w, t, occ, ws) in shapes():
         jobs.append((os.path.join(CSRC, "flex_tiled_inst.hip"),
                      os.path.join(OBJ, f"flex_tiled_{di}_{do}.o"),

@@ -1,6 +1,7 @@
 // C-ABI entry points of libflexconv: validation, workspace carving, dispatch.
 #include "flex_common.hpp"
 #include <stdlib.h>
+#include <algorithm>
 #include <mutex>
 #include "../../include/flexconv.h"
 
@@ -33,17 +34,17 @@ hipError_t launch_bwd_fused_late_64_64(const float *g_rows, const float *own_row
                                        const float *grad_bias, int Din, int Dout, float *partials, int *control, int B,
                                        int N, int K, hipStream_t s);
 
-// layers with both widths multiples of 128 as passes over column blocks (same file, same two shapes)
-bool split_wide_ok(int N, int K, int max_width);
-hipError_t launch_gc_split_wide(const float *rows, int rs, const float *pos, const int32_t *nbr, const int32_t *off,
-                                const int32_t *src, const int32_t *order, const void *thetaP_all, float *out, int os,
-                                int n_in, int n_out, int B, int N, int K, int csr, hipStream_t s);
+// parameter gradients of layers with both widths multiples of 128, block by block (same file, same shape)
 hipError_t launch_gt_split_wide(const float *rows, int rs, const float *pos, const int32_t *nbr, const float *g_rows,
                                 int gst, float *partials, int n_hi, int n_ho, int chunks, int B, int N, int K,
                                 hipStream_t s);
 int split_wide_gt_chunks(int B, int N, int blocks);
 hipError_t launch_reduce_partials(const float *partials, int n_wg, int DIP, int DOP, int n_blocks, int n_ho, int Din,
                                   int Dout, float *grad_theta, float *grad_bias, hipStream_t s);
+
+// the 64-point tile kernels over fixed-K neighbour tensors / in-edge lists
+hipError_t launch_tile_0(const TileArgs &a, int outw, int grid, hipStream_t s);
+hipError_t launch_tile_1(const TileArgs &a, int outw, int grid, hipStream_t s);
 
 bool gather_contract_supported(int DI, int DO)
 {
@@ -128,33 +129,30 @@ int lean_producer_mode()
 }
 
 // Wide layers (both widths multiples of 128): the paper's network doubles the feature length at every resolution
-// stage while the point count drops by four (Sec. 4.3), so its deeper stages are of this kind.  They run as passes of
-// the 64 -> 128 (forward, feature gradient) and 64 -> 64 (parameter gradients) lean kernels over column blocks of the
-// point-major tensors (FLEX_SPLIT=0 in the environment keeps 128 -> 128 on the single-pass fp32 kernels and the wider
-// ones on the direct form, for comparisons).
+// stage while the point count drops by four (Sec. 4.3), so its deeper stages are of this kind.  They run on the 64-point
+// tile kernels (forward, feature gradient) and, for the parameter gradients, on 64 -> 64 lean kernels over column blocks
+// of the point-major tensors (FLEX_SPLIT=0 in the environment keeps 128 -> 128 on the single-pass fp32 kernels and the
+// wider ones on the direct form, for comparisons).
 static bool split_disabled()
 {
     static const bool off = [] { const char *v = getenv("FLEX_SPLIT"); return v != nullptr && v[0] == '0'; }();
     return off;
+}
+// Can the 64-point tile kernels take this gather of w_in wide rows?  32-bit byte offsets inside a cloud, and one more
+// row's worth of them for slots without an entry.
+static bool tile_ok(int64_t N, int w_in)
+{
+    return !split_disabled() && !contract_in_fp32() && lean_producer_mode() != 0 && (N + 1) * w_in * 4 <= (1ll << 32) &&
+           N * 12 < (1ll << 32);
 }
 static bool wide_shape(int Din, int Dout)
 {
     return !split_disabled() && Din % 128 == 0 && Dout % 128 == 0 &&
            (int64_t)(Din / 64) * (Dout / 64) <= 65535;      // one grid row of the reduction per block
 }
-// packed parameter blocks of the whole layer (forward / feature gradient)
-static size_t wide_param_scratch_bytes(int Din, int Dout)
+static bool wide_ok(int64_t N, int K, int Din, int Dout)
 {
-    const size_t blocks = (size_t)(Din / 64) * (Dout / 64) / 2;     // 64 x 128 each, either way round
-    return blocks * theta_f16_bytes(64, 128);
-}
-
-// The packing of a wide layer's parameters for launch_gc_split_wide: 64 gathered channels x 128 written ones per block.
-static void pack_wide(PrepList &prep, const float *theta, const float *bias, void *thetaF, int Din, int Dout, int Dki,
-                      int Dko, int transpose)
-{
-    const int w_in = transpose ? Dko : Dki, w_out = transpose ? Dki : Dko;     // gathered / written widths
-    prep.pack_theta(theta, bias, thetaF, Din, Dout, 64, 128, w_in / 64, w_out / 128, transpose);
+    return wide_shape(Din, Dout) && tile_ok(N, Din) && tile_ok(N, Dout) && (int64_t)K * N * 4 < (1ll << 32);
 }
 
 // Parameter gradients of a wide layer: (Din/64) x (Dout/64) independent blocks of [4*64 x 64], two launches
@@ -231,15 +229,74 @@ static hipError_t launch_grad_theta(const float *rows, const float *pos, const i
     return launch_reduce_partials(partials, n_wg, pad4(Dki), pad16(Dko), 1, 1, Din, Dout, grad_theta, grad_bias, s);
 }
 
+// ---- the 64-point tile kernels ------------------------------------------------------------
+// Do they?  Where the gathered rows are wider than the 64 channels that the wave-specialised kernels hold the parameters
+// of in registers (those would walk the cloud once per 64 channels: 128 -> 128, 1M points, forward 819 against 755 us,
+// feature gradient 965 against 809; 512 -> 512, 109k points, 1350 against 860 and 1580 against 860), and where those would
+// need zero-padded copies of the tensors (except rows of fewer than four channels, which have no lane to themselves).
+static bool use_tile(int64_t N, int w_in, bool padded) { return tile_ok(N, w_in) && (w_in > 64 || padded); }
+
+struct TilePlan { int outw, n_in, n_out; };
+// How a gather is cut: input blocks of 64 channels, output blocks as wide as pays.  A wider output block gathers its rows
+// for more channels; a narrower one makes more jobs for a cloud of few tiles.  The costs of a tile and input block
+// (thousands of clocks) are measured ones.
+static TilePlan tile_plan(int64_t B, int64_t N, int w_in, int w_out)
+{
+    TilePlan p{};
+    p.n_in = (w_in + 63) / 64;
+    const int64_t tiles = B * cdiv64(N, 64);
+    const int widths[3] = {64, 128, 256}, cost[3] = {50, 55, 75};
+    int64_t best = -1;
+    for (int i = 0; i < 3; ++i) {
+        if (i > 0 && widths[i] >= 2 * w_out) break;
+        const int n_out = (w_out + widths[i] - 1) / widths[i];
+        const int64_t c = cdiv64(tiles * n_out, device_cu_count()) * cost[i];
+        if (best < 0 || c < best) { best = c; p.outw = widths[i]; p.n_out = n_out; }
+    }
+    return p;
+}
+static size_t tile_bytes(const TilePlan &p) { return (size_t)p.n_in * p.n_out * theta_f16_bytes(64, p.outw); }
+
+static void tile_pack(PrepList &prep, const TilePlan &p, const float *theta, const float *bias, void *thetaF, int Din,
+                       int Dout, int transpose)
+{
+    prep.pack_theta(theta, bias, thetaF, Din, Dout, 64, p.outw, p.n_in, p.n_out, transpose);
+}
+
+// rows [B*N, rs] (w_in channels used) onto out [B, N, w_out] or, out_bcn, [B, w_out, N]
+static hipError_t tile_launch(const TilePlan &p, const float *rows, int rs, int w_in, const float *pos,
+                               const int32_t *nbr, const int32_t *off, const int32_t *src, const int32_t *order,
+                               const void *theta, float *out, int w_out, int out_bcn, int B, int N, int K, hipStream_t s)
+{
+    TileArgs a{};
+    a.rows = rows; a.pos = pos; a.nbr = nbr; a.off = off; a.src = src; a.order = order;
+    a.theta = (const char *)theta; a.out = out;
+    a.out_c = out_bcn ? N : 1; a.out_l = out_bcn ? 1 : w_out; a.out_b = (int64_t)N * w_out;
+    a.rs = rs; a.w_in = w_in; a.w_out = w_out;
+    a.blk_bytes = (int)theta_f16_bytes(64, p.outw);
+    a.exp_off = (int)theta_f16_exp_offset(64, p.outw);
+    a.rs_off = (int)theta_f16_rscale_offset(64, p.outw);
+    a.N = N; a.K = K; a.tpc = (N + 63) / 64; a.n_in = p.n_in;
+    const int64_t total = (int64_t)B * a.tpc;
+    if (total > 0x7fffffff) return hipErrorInvalidValue;
+    a.total = (int)total;
+    // workgroups per output block: whole multiples of 8 where there are that many, so that a share's number tells its XCD
+    int64_t chunks = device_cu_count() / p.n_out;
+    if (total < chunks) chunks = total;
+    a.chunks = (int)(chunks >= 8 ? (chunks + 7) / 8 * 8 : (chunks > 1 ? chunks : 1));
+    const int grid = p.n_out * a.chunks;
+    return off != nullptr ? launch_tile_1(a, p.outw, grid, s) : launch_tile_0(a, p.outw, grid, s);
+}
+
 // ---- workspace plans -----------------------------------------------------------
 struct FwdPlan {
     bool tiled, wide;
-    size_t thetaP, featT, outT, total;   // byte offsets / total
+    size_t thetaP, featT, total;         // byte offsets / total
 };
 struct BwdPlan {
     bool tiled, wide;
     bool fused;      // feature and parameter gradients, when both are asked for, come from the one-pass kernel
-    size_t thetaP, featT, gT, gfT, partials, order, flag, in_off, in_src, inedge_ws, total;
+    size_t thetaP, featT, gT, partials, order, flag, in_off, in_src, inedge_ws, total;
 };
 
 // The route (block passes of the wide path / single-pass tiled kernels / direct form) is decided here, once, from
@@ -249,12 +306,13 @@ static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
 {
     FwdPlan p{};
     p.tiled = gather_contract_supported(Din, Dout);
-    p.wide = wide_shape(Din, Dout) && split_wide_ok((int)N, K, Din > Dout ? Din : Dout);
+    p.wide = wide_ok(N, K, Din, Dout);
     size_t at = 0;
     if (p.tiled || p.wide) {
-        p.thetaP = at; at += p.wide ? wide_param_scratch_bytes(Din, Dout) : theta_ws_bytes(Din, Dout);
+        size_t packed = p.wide ? 0 : theta_ws_bytes(Din, Dout);
+        if (tile_ok(N, Din)) packed = std::max(packed, tile_bytes(tile_plan(B, N, Din, Dout)));
+        p.thetaP = at; at += packed;
         if (layout == FLEX_LAYOUT_BCN) { p.featT = at; at += align256(sizeof(float) * (size_t)(B * N) * Din); }
-        if (layout == FLEX_LAYOUT_BCN && p.wide) { p.outT = at; at += align256(sizeof(float) * (size_t)(B * N) * Dout); }
     }
     p.total = at > 0 ? at : 256;
     return p;
@@ -264,14 +322,15 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
 {
     BwdPlan p{};
     p.tiled = gather_contract_supported(Din, Dout) && gather_contract_supported(Dout, Din);
-    p.wide = wide_shape(Din, Dout) && split_wide_ok((int)N, K, Din > Dout ? Din : Dout);
+    p.wide = wide_ok(N, K, Din, Dout);
     size_t at = 0;
     if (p.tiled || p.wide) {
-        p.thetaP = at; at += p.wide ? wide_param_scratch_bytes(Din, Dout) : theta_ws_bytes(Dout, Din);
+        size_t packed = p.wide ? 0 : theta_ws_bytes(Dout, Din);
+        if (tile_ok(N, Dout)) packed = std::max(packed, tile_bytes(tile_plan(B, N, Dout, Din)));
+        p.thetaP = at; at += packed;
         if (layout == FLEX_LAYOUT_BCN) {
             p.featT = at; at += align256(sizeof(float) * (size_t)(B * N) * Din);
             p.gT = at;    at += align256(sizeof(float) * (size_t)(B * N) * Dout);
-            if (p.wide) { p.gfT = at; at += align256(sizeof(float) * (size_t)(B * N) * Din); }
         }
         p.partials = at;
         at += p.wide ? wide_partial_bytes((int)B, (int)N, Din, Dout) : grad_theta_partial_bytes(B, N, Din, Dout);
@@ -524,25 +583,32 @@ int flexconv_fwd(const float *feat, const float *pos, const int32_t *nbr, const 
     void *thetaP = sub + p.thetaP;
     PrepList prep;
     const float *rows = feat;
+    if (use_tile(N, Dki, padded)) {
+        // rows of any width as they are; only channel-major ones have to be turned round
+        const TilePlan ph = tile_plan(B, N, Dki, Dko);
+        const int w_in = std::max(Din, 4);
+        if (bcn || w_in > Din) {
+            float *copy = (float *)(padded ? ws + pp.featP : sub + p.featT);
+            prep.copy(feat, copy, B, N, Din, w_in, bcn, 0);
+            rows = copy;
+        }
+        tile_pack(prep, ph, theta, bias, thetaP, Din, Dout, 0);
+        FLEX_HIP(prep.launch(s));
+        FLEX_HIP(tile_launch(ph, rows, w_in, w_in, pos, nbr, nullptr, nullptr, nullptr, thetaP, out, Dout, bcn, B, N, K, s));
+        return FLEX_OK;
+    }
     if (padded || bcn) {
         float *copy = (float *)(padded ? ws + pp.featP : sub + p.featT);
         prep.copy(feat, copy, B, N, Din, Dki, bcn, 0);
         rows = copy;
     }
-    float *dst = padded ? (float *)(ws + pp.outP) : (bcn && p.wide) ? (float *)(sub + p.outT) : out;
-    if (p.wide) {
-        pack_wide(prep, theta, bias, thetaP, Din, Dout, Dki, Dko, 0);
-        FLEX_HIP(prep.launch(s));
-        FLEX_HIP(launch_gc_split_wide(rows, Dki, pos, nbr, nullptr, nullptr, nullptr, thetaP, dst, Dko, Dki / 64, Dko / 128,
-                                      B, N, K, 0, s));
-    } else {
-        const int fmt = gather_contract_theta_format(Dki, Dko, N, K, 0);
-        if (fmt) prep.pack_theta(theta, bias, thetaP, Din, Dout, pad4(Dki), pad16(Dko), 1, 1, 0);
-        else FLEX_HIP(launch_pack_theta(theta, bias, (float *)thetaP, Din, Dout, pad4(Dki), pad16(Dko), 0, s));
-        FLEX_HIP(prep.launch(s));
-        FLEX_HIP(launch_gather_contract(rows, pos, nbr, nullptr, nullptr, nullptr, thetaP, fmt, dst, B, N, K, Dki, Dko, 0,
-                                        bcn && !padded, s));
-    }
+    float *dst = padded ? (float *)(ws + pp.outP) : out;
+    const int fmt = gather_contract_theta_format(Dki, Dko, N, K, 0);
+    if (fmt) prep.pack_theta(theta, bias, thetaP, Din, Dout, pad4(Dki), pad16(Dko), 1, 1, 0);
+    else FLEX_HIP(launch_pack_theta(theta, bias, (float *)thetaP, Din, Dout, pad4(Dki), pad16(Dko), 0, s));
+    FLEX_HIP(prep.launch(s));
+    FLEX_HIP(launch_gather_contract(rows, pos, nbr, nullptr, nullptr, nullptr, thetaP, fmt, dst, B, N, K, Dki, Dko, 0,
+                                    bcn && !padded, s));
     if (dst != out) FLEX_HIP(launch_copy_rows(dst, out, B, N, Dko, Dout, 0, bcn, s));
     return FLEX_OK;
 }
@@ -644,7 +710,10 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
     int32_t *order = (int32_t *)(sub + p.order);
     int *control = (int *)(sub + p.flag);
     const bool fused = p.fused && grad_theta && grad_feat;
-    const int fmt = p.wide ? 1 : gather_contract_theta_format(Dko, Dki, N, K, 1);
+    const bool tile = !fused && grad_feat && use_tile(N, Dko, padded);
+    TilePlan ph{};
+    if (tile) ph = tile_plan(B, N, Dko, Dki);
+    const int fmt = tile ? 1 : gather_contract_theta_format(Dko, Dki, N, K, 1);
     PrepList prep;
     const float *rows = feat, *g_rows = grad_out;
     if (padded || bcn) {
@@ -655,14 +724,14 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
         rows = f_copy;
     }
     if (grad_feat) {
-        if (p.wide) pack_wide(prep, theta, bias, thetaP, Din, Dout, Dki, Dko, 1);
+        if (tile) tile_pack(prep, ph, theta, bias, thetaP, Din, Dout, 1);
         else if (fmt) prep.pack_theta(theta, bias, thetaP, Din, Dout, pad4(Dko), pad16(Dki), 1, 1, 1);
         else FLEX_HIP(launch_pack_theta(theta, bias, (float *)thetaP, Din, Dout, pad4(Dko), pad16(Dki), 1, s));
         prep.order(in_off, B, N, order);
     }
     if (fused) prep.clear(control, FUSED_FLAG_INTS);
     FLEX_HIP(prep.launch(s));
-    float *dst = padded ? (float *)(ws + pp.gfP) : (bcn && p.wide) ? (float *)(sub + p.gfT) : grad_feat;
+    float *dst = padded && !tile ? (float *)(ws + pp.gfP) : grad_feat;
     const int out_bcn = bcn && !padded;
     if (fused) {
         int n_wg = 0;
@@ -681,9 +750,9 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
         else if (grad_theta)
             FLEX_HIP(launch_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, Dki, Dko, Din,
                                        Dout, s));
-        if (grad_feat && p.wide)
-            FLEX_HIP(launch_gc_split_wide(g_rows, Dko, pos, nullptr, in_off, in_src, order, thetaP, dst, Dki, Dko / 64,
-                                          Dki / 128, B, N, K, 1, s));
+        if (tile)
+            FLEX_HIP(tile_launch(ph, g_rows, Dko, std::max(Dout, 4), pos, nullptr, in_off, in_src, order, thetaP,
+                                  grad_feat, Din, bcn, B, N, K, s));
         else if (grad_feat)
             FLEX_HIP(launch_gather_contract(g_rows, pos, nullptr, in_off, in_src, order, thetaP, fmt, dst, B, N, K, Dko,
                                             Dki, 1, out_bcn, s));

@@ -117,6 +117,19 @@ bool contract_in_fp32();
 // 2 (default) = lean producers, three per consumer wave where the shape allows.
 int lean_producer_mode();
 
+// The 64-point tile kernels (flex_tile.hpp): layers of any width.
+struct TileArgs {
+    const float *rows, *pos;
+    const int32_t *nbr, *off, *src, *order;
+    const char *theta;           // packed blocks [output block][input block]
+    float *out;
+    int64_t out_c, out_l, out_b; // output strides: channel, point, cloud
+    int rs, w_in, w_out;         // row stride (floats), real widths
+    int blk_bytes, exp_off, rs_off;
+    int N, K, tpc, total;        // tiles per cloud, tiles
+    int n_in, chunks;            // input blocks; workgroups per output block
+};
+
 // Workspace of the per-workgroup partial sums of grad_theta / grad_bias ([n_wg, KD, DOP] floats).
 size_t grad_theta_partial_bytes(int64_t B, int64_t N, int Din, int Dout);
 

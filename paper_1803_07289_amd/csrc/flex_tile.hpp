@@ -1,0 +1,488 @@
+// Flex-convolution on tiles of 64 points (gfx950, wave64): the forward pass (fixed-K neighbour tensor) and the feature
+// gradient (in-edge lists) of layers of any width.
+//
+// A workgroup of sixteen waves, one per CU.  Eight GATHER waves sum the rows of a tile's neighbours in registers,
+//     A[l][j*64 + c] = sum_k dp_j(l,k) row[n_k(l)][c]      (dp_3 = 1; a block of 64 input channels)
+// and park the result in LDS as split-half rows (flex_prep.hip: f16 hi + lo of the scaled value); eight CONTRACT waves
+// multiply the tile before with the packed parameters on the f16 matrix cores (hi*hi + hi*lo + lo*hi).  Two tile
+// buffers, one barrier per tile.  A layer wider than 64 input channels walks its input blocks tile by tile with the
+// sums kept in the contracting waves' registers, so a row is gathered once per OUTW output channels (up to 256) and
+// nothing but the result leaves the chip.
+//
+// The kernels of flex_ws.hpp keep their parameters in registers whatever the width and walk a wide layer in passes over
+// the whole cloud, adding to the output in memory, with 32-point tiles; their gathering waves spend some 540
+// instructions on four points.  Here parameters of more than one input block stream from L2, 64 points to a pass, and
+// what a lane needs to gather a row -- the position difference and the row's offset -- is prepared one entry per lane
+// (eight slots of the wave's eight points: a step) and a step ahead, through LDS: 300 instructions per four points.
+// Both matter because a wave issues at most one instruction per five clocks.
+#pragma once
+#include "flex_ws.hpp"
+
+namespace flex {
+
+template <int WM_, int NSW_>
+struct TileGeom {
+    static constexpr int IC = 64;                        // input channels per block
+    static constexpr int WM = WM_, WN = 8 / WM_;         // contracting waves along the points / the output channels
+    static constexpr int NSW = NSW_;                     // 16-channel slices per contracting wave
+    static constexpr int NT = 1024, T = 64;
+    static constexpr int LPR = IC / 4, G = 64 / LPR;     // lanes per row, points a wave gathers at a time
+    static constexpr int PASSES = 8 / G;
+    static constexpr int KD = 4 * IC, KS = KD / 32;      // depth, depth steps of the matrix op
+    static constexpr int ARS = 4 * KD + 16;              // tile row: [hi: KD halves][lo: KD halves][16 B], = 16 mod 128
+    static constexpr int MB = 4 / WM;                    // 16-point blocks per contracting wave
+    static constexpr int OUTW = 16 * WN * NSW;
+};
+
+// Rows are read through a buffer descriptor of the cloud's tensor: a slot without an entry carries an offset past its
+// end (the last row that 32-bit offsets reach, which the host keeps free), for which the load returns zeros without touching memory.  So every slot's load is issued unconditionally, which
+// is what keeps eight of them in flight: the compiler waits for a load by counting the younger ones, and where those
+// may or may not have been issued it has to wait for all of them (branches around them: 13 000 clocks a tile).
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(const float *rows, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(rows), 0, (int)bytes, 0x00027000);
+}
+__device__ __forceinline__ v4f load_row4(__amdgpu_buffer_rsrc_t rows, unsigned offset)
+{
+    return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)offset, 0, 0));
+}
+
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+
+// maximum over the wave, in every lane
+__device__ __forceinline__ int wave_max(int v)
+{
+    v = max(v, dpp_movi<0xB1>(v));
+    v = max(v, dpp_movi<0x4E>(v));
+    v = max(v, dpp_movi<0x141>(v));
+    v = max(v, dpp_movi<0x140>(v));
+    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// One step of a gathering wave: eight list slots of its eight points of a tile, for one input block (all wave-uniform).
+struct TileStep {
+    int b, ib;
+    int n0, n1;          // slots that some point of the first / second four has
+    bool last;           // last step of (tile, input block)
+};
+
+// Walks a gathering wave's steps.  lane = 8 * slot + point.
+template <bool CSR>
+struct StepWalk {
+    TileWalk tw;
+    int ib, c;                       // input block, step inside the lists
+    int nc;                          // steps per input block
+    // CSR: this lane's point and list in the current tile and in the next, its point in the one after
+    int pid, lo, deg, pid1, lo1, hi1, pid2;
+    TileWalk tw1, tw2;
+
+    __device__ __forceinline__ int position(const TileWalk &w, int first) const { return w.tic * 64 + first + (threadIdx.x & 7); }
+    __device__ __forceinline__ int point_at(const TileArgs &a, const TileWalk &w, int first) const
+    {
+        return a.order[(int64_t)w.b * a.N + min(position(w, first), a.N - 1)];
+    }
+    __device__ __forceinline__ void bounds(const TileArgs &a)
+    {
+        const int64_t gp = (int64_t)tw1.b * a.N + pid1;
+        lo1 = a.off[gp];
+        hi1 = a.off[gp + 1];
+    }
+    __device__ __forceinline__ void enter(const TileArgs &a, int first)
+    {
+        // the walk `tw1` stands on the tile that becomes current
+        tw = tw1;
+        pid = pid1; lo = lo1;
+        deg = position(tw, first) < a.N ? hi1 - lo1 : 0;         // positions past the cloud have no list
+        nc = max(1, (wave_max(deg) + 7) >> 3);
+        tw1.next_clamped();
+        pid1 = pid2;
+        tw2.next_clamped();
+        pid2 = point_at(a, tw2, first);
+        bounds(a);
+    }
+    // first: the wave's first point inside a tile
+    __device__ __forceinline__ StepWalk(const TileArgs &a, const TileSchedule &sc, int first)
+        : tw(sc, a.tpc), tw1(sc, a.tpc), tw2(sc, a.tpc)
+    {
+        ib = c = 0;
+        if constexpr (CSR) {
+            pid1 = point_at(a, tw1, first);
+            tw2.next_clamped();
+            pid2 = point_at(a, tw2, first);
+            bounds(a);
+            enter(a, first);
+        } else {
+            nc = (a.K + 7) >> 3;
+        }
+    }
+    // The step's descriptor and this lane's entry of it: the id and the point it belongs to, has: whether it exists.  Then
+    // moves on; past the workgroup's last tile it repeats that tile.
+    __device__ __forceinline__ TileStep fetch(const TileArgs &a, int first, int &id, int &point, bool &has)
+    {
+        TileStep d;
+        d.b = tw.b; d.ib = ib;
+        d.last = c == nc - 1;
+        const int slot = 8 * c + ((threadIdx.x >> 3) & 7);
+        if constexpr (CSR) {
+            point = pid;
+            has = slot < deg;
+            id = a.src[has ? lo + slot : 0];                     // a list entry is always there (K >= 1)
+            id = has ? id : pid;
+            auto most = [&](int l) {
+                return max(max(__builtin_amdgcn_readlane(deg, l), __builtin_amdgcn_readlane(deg, l + 1)),
+                           max(__builtin_amdgcn_readlane(deg, l + 2), __builtin_amdgcn_readlane(deg, l + 3))) - 8 * c;
+            };
+            d.n0 = most(0); d.n1 = most(4);
+        } else {
+            d.n0 = d.n1 = a.K - 8 * c;
+            point = min(position(tw, first), a.N - 1);
+            has = slot < a.K;
+            id = a.nbr[((int64_t)d.b * a.K + min(slot, a.K - 1)) * a.N + point];
+        }
+        if (++c == nc) {
+            c = 0;
+            if (++ib == a.n_in) {
+                ib = 0;
+                if constexpr (CSR) enter(a, first);
+                else tw.next_clamped();
+            }
+        }
+        return d;
+    }
+};
+
+template <int WM, int NSW, bool CSR, bool MULTI>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void tile_conv_kernel(const TileArgs a)
+{
+    using P = TileGeom<WM, NSW>;
+    constexpr int IC = P::IC;
+    __shared__ __attribute__((aligned(16))) char s_A[2][P::T * P::ARS];
+    __shared__ __attribute__((aligned(16))) float s_ent[8][2][64][4];     // per gathering wave: (dx, dy, dz, row byte offset) of entry 8 * slot + point
+    __shared__ int s_P[2][P::T];                                          // CSR: the point in every tile row
+    __shared__ int s_E[2][P::T];                                          // exponents of the tile rows
+    constexpr int RS_BLOCKS = MULTI ? 8 : 1;
+    __shared__ __attribute__((aligned(16))) float s_rs[RS_BLOCKS][4 * IC];   // depth scales of the first input blocks' parameters
+
+    const int j = blockIdx.x / a.chunks;
+    const TileSchedule sc(a.total, (int)blockIdx.x - j * a.chunks, a.chunks);
+    if (!(sc.first < sc.end)) return;
+    const int tiles = (sc.end - sc.first + sc.step - 1) / sc.step * a.n_in;   // (tile, input block) pairs of this workgroup
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const char *theta_j = a.theta + (int64_t)j * a.n_in * a.blk_bytes;
+
+    for (int i = threadIdx.x; i < min(a.n_in, RS_BLOCKS) * 4 * IC; i += P::NT)
+        s_rs[i / (4 * IC)][i % (4 * IC)] =
+            reinterpret_cast<const float *>(theta_j + (int64_t)(i / (4 * IC)) * a.blk_bytes + a.rs_off)[i % (4 * IC)];
+    __syncthreads();
+
+    if (wave < 8) {
+        // ---- gather ----
+        static_assert(P::PASSES == 2 && P::G == 4, "two passes of four points");
+        const int t = lane % P::LPR, grp = lane / P::LPR, first = 8 * wave;
+        float (*ent)[64][4] = s_ent[wave];
+        StepWalk<CSR> walk(a, sc, first);
+        struct Positions { float n[3], c[3]; };
+        auto request = [&](const TileStep &d, int id, int point, Positions &p) {
+            const char *pb = reinterpret_cast<const char *>(a.pos + (int64_t)d.b * 3 * a.N);
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                p.n[x] = *reinterpret_cast<const float *>(pb + 4u * ((unsigned)(x * a.N) + (unsigned)id));
+                p.c[x] = *reinterpret_cast<const float *>(pb + 4u * ((unsigned)(x * a.N) + (unsigned)point));
+            }
+        };
+        auto publish = [&](int buf, int id, bool has, const Positions &p) {
+            const float sg = CSR ? -1.f : 1.f;          // CSR: point - listing centre
+            *reinterpret_cast<v4f *>(ent[buf][lane]) =
+                v4f{sg * (p.n[0] - p.c[0]), sg * (p.n[1] - p.c[1]), sg * (p.n[2] - p.c[2]),
+                    __uint_as_float(has ? (unsigned)id * (4u * (unsigned)a.rs) : 0u - 4u * (unsigned)a.rs)};
+            wave_lds_sync();
+        };
+        // this lane's channels of a row: past the row's end the last four again, put right after the sums
+        auto lane_channel = [&](int ib) { return min(ib * IC + 4 * t, a.w_in - 4); };
+        auto rows_of = [&](const TileStep &d) {
+            return row_buffer(a.rows + (int64_t)d.b * a.N * a.rs, (unsigned)a.N * (unsigned)a.rs * 4u);
+        };
+        const bool ragged = a.w_in % IC != 0;
+
+        TileStep d0, d1, d2;
+        int id1, id2, pt1, pt2, pt0;                    // this lane's entries of the next two steps
+        bool has1, has2;
+        Positions p1;
+        v4f f[8];                                       // rows in flight
+        // how far ahead of its use LDS is read, as the registers allow: the differences EA slots, the offsets of four
+        // points from slot to slot over the four points before (fixed lists) or at once in front of them
+        constexpr int EA = CSR ? 2 : 4;
+        constexpr bool OFF_AHEAD = !CSR;
+        unsigned off[8];
+        {
+            int id0;
+            bool has0;
+            Positions p0;
+            d0 = walk.fetch(a, first, id0, pt0, has0);
+            d1 = walk.fetch(a, first, id1, pt1, has1);
+            request(d0, id0, pt0, p0);
+            d2 = walk.fetch(a, first, id2, pt2, has2);
+            publish(0, id0, has0, p0);
+            request(d1, id1, pt1, p1);
+            const auto rows = rows_of(d0);
+            const unsigned lane_off = 4u * (unsigned)lane_channel(d0.ib);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) f[u] = load_row4(rows, __float_as_uint(ent[0][8 * u + grp][3]) + lane_off);
+            if constexpr (OFF_AHEAD) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) off[u] = __float_as_uint(ent[0][8 * u + 4 + grp][3]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        v4f acc[2][4];                                  // [pass][channel][component]
+        auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[p][v] = v4f{0.f, 0.f, 0.f, 0.f};
+        };
+        clear();
+
+        int ex_run[2] = {0, 0};
+        int m_buf = 0;                                  // tile buffer of the tile being gathered
+        for (int s = 0, k = 0; k < tiles; ++s) {
+            const int buf = s & 1;
+            publish(buf ^ 1, id1, has1, p1);            // the next step's entries
+            request(d2, id2, pt2, p1);                  // positions of the step after it, entries of the one after that
+            int id3, pt3;
+            bool has3;
+            const TileStep d3 = walk.fetch(a, first, id3, pt3, has3);
+
+            // Eight rows are in flight at all times: the registers of a slot that has been summed take the same slot of
+            // the next four points at once, of the next step's after the second four.
+            const auto rows0 = rows_of(d0), rows1 = rows_of(d1);
+            const unsigned lane_off0 = 4u * (unsigned)lane_channel(d0.ib), lane_off1 = 4u * (unsigned)lane_channel(d1.ib);
+            v4f e[EA + 1];
+#pragma unroll
+            for (int u = 0; u < EA; ++u) e[u] = *reinterpret_cast<const v4f *>(ent[buf][8 * u + grp]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                if constexpr (!OFF_AHEAD) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) off[u] = __float_as_uint(p == 0 ? ent[buf][8 * u + 4 + grp][3] : ent[buf ^ 1][8 * u + grp][3]);
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    constexpr int R = EA + 1;
+                    const int i = 8 * p + u;
+                    if (i + EA < 16) e[(i + EA) % R] = *reinterpret_cast<const v4f *>(ent[buf][8 * ((i + EA) & 7) + 4 * ((i + EA) >> 3) + grp]);
+                    const v4f d = e[i % R];
+                    if (u < (p == 0 ? d0.n0 : d0.n1)) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            acc[p][v][0] = fmaf(d[0], f[u][v], acc[p][v][0]);
+                            acc[p][v][1] = fmaf(d[1], f[u][v], acc[p][v][1]);
+                            acc[p][v][2] = fmaf(d[2], f[u][v], acc[p][v][2]);
+                            acc[p][v][3] += f[u][v];
+                        }
+                    }
+                    f[u] = p == 0 ? load_row4(rows0, off[u] + lane_off0) : load_row4(rows1, off[u] + lane_off1);
+                    if constexpr (OFF_AHEAD) off[u] = __float_as_uint(ent[buf ^ 1][8 * u + 4 * p + grp][3]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if (d0.last) {
+                // ---- park ----
+                const int ib = MULTI ? d0.ib : 0;
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const int shift = ib * IC + 4 * t - lane_channel(ib);
+                    if (ragged && shift > 0) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            v4f x = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                            for (int w = v + 1; w < 4; ++w)
+                                if (w - v == shift) x = acc[p][w];
+                            acc[p][v] = x;
+                        }
+                    }
+                    float m = 0.f;
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) {
+                        const float *rs = ib < RS_BLOCKS ? &s_rs[ib][jj * IC + 4 * t]
+                            : reinterpret_cast<const float *>(theta_j + (int64_t)ib * a.blk_bytes + a.rs_off) + jj * IC + 4 * t;
+                        const v4f r = *reinterpret_cast<const v4f *>(rs);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            acc[p][v][jj] *= r[v];
+                            m = __builtin_amdgcn_fmed3f(m, __builtin_fabsf(acc[p][v][jj]), __builtin_inff());
+                        }
+                    }
+                    m = group_max<P::LPR>(m);
+                    int ex = 15 - __builtin_amdgcn_frexp_expf(m);
+                    if constexpr (MULTI) {     // one exponent per point over all input blocks so far, see the contraction
+                        ex = ib > 0 ? min(ex, ex_run[p]) : ex;
+                        ex_run[p] = ex;
+                    }
+                    const int pt = first + 4 * p + grp;
+                    char *row = s_A[m_buf] + pt * P::ARS + 8 * t;
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) {
+                        typedef float f2 __attribute__((ext_vector_type(2)));
+                        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+                        h2 h[2], l[2];
+#pragma unroll
+                        for (int w = 0; w < 2; ++w) {
+                            const f2 x = {__builtin_ldexpf(acc[p][2 * w][jj], ex), __builtin_ldexpf(acc[p][2 * w + 1][jj], ex)};
+                            h[w] = __builtin_convertvector(x, h2);
+                            const f2 back = __builtin_convertvector(h[w], f2);
+                            l[w] = __builtin_convertvector(x - back, h2);
+                        }
+                        *reinterpret_cast<h4 *>(row + 2 * jj * IC) = h4{h[0][0], h[0][1], h[1][0], h[1][1]};
+                        *reinterpret_cast<h4 *>(row + 2 * (P::KD + jj * IC)) = h4{l[0][0], l[0][1], l[1][0], l[1][1]};
+                    }
+                    if (t == 0) s_E[m_buf][pt] = ex;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (CSR && lane < 8) s_P[m_buf][first + lane] = pt0;
+                m_buf ^= 1;
+                ++k;
+                clear();
+                __syncthreads();               // the tile is complete
+            }
+            d0 = d1; d1 = d2; d2 = d3;
+            pt0 = pt1; pt1 = pt2; pt2 = pt3;
+            id1 = id2; id2 = id3;
+            has1 = has2; has2 = has3;
+        }
+        return;
+    }
+
+    // ---- contract ----
+    constexpr bool RESIDENT = !MULTI && NSW == 1;       // one block of parameters, 64 registers: kept
+    const int cw = wave - 8, q = lane >> 4, r16 = lane & 15;
+    const int wm = cw % WM, wn = cw / WM;
+    constexpr int PART = (P::OUTW / 16) * P::KS * 64 * 16;
+    constexpr int AHEAD = RESIDENT ? P::KS : NSW == 1 ? 4 : 2;     // depth steps whose parameters are held
+    h8 tH[AHEAD][NSW], tL[AHEAD][NSW];
+    // Sums over several input blocks stay in the accumulators.  They carry the scale 2^(e + ec) of the block being added
+    // (e: the tile row's exponent, the smallest of the point's so far, so that adding a block never pushes the sums up;
+    // ec: the column's exponent in the packed block), and are moved -- exactly -- to the next block's before it is added.
+    v4f cc[P::MB][NSW];
+    int e_now[P::MB];
+    v4i ec_now[NSW];
+    const char *blk = theta_j;
+    unsigned th_off = (unsigned)((wn * NSW) * P::KS * 64 + lane) * 16u;
+    auto load_theta = [&](int st, int n) __attribute__((always_inline)) {
+        tH[st % AHEAD][n] = *reinterpret_cast<const h8 *>(blk + (n * P::KS + st) * 1024 + th_off);
+        tL[st % AHEAD][n] = *reinterpret_cast<const h8 *>(blk + PART + (n * P::KS + st) * 1024 + th_off);
+    };
+    if constexpr (RESIDENT) {
+#pragma unroll
+        for (int st = 0; st < P::KS; ++st) load_theta(st, 0);
+    }
+    TileWalk tw(sc, a.tpc);
+    int ib = 0;
+    for (int k = 0; k < tiles; ++k) {
+        __syncthreads();                   // the tile is complete
+        const int m_buf = k & 1, b = tw.b, l0 = tw.tic * 64;
+        {
+            // (the lane's offsets are formed anew for every tile: the compiler would otherwise read the parameters once
+            // and for all before the loop, and spill them)
+            unsigned a_off = (unsigned)((wm * P::MB * 16 + r16) * P::ARS + 16 * q);
+            int o_lane = wn * NSW * 16 + 4 * q, l_lane = wm * P::MB * 16 + r16;
+            asm volatile("" : "+v"(th_off), "+v"(a_off), "+v"(o_lane), "+v"(l_lane));
+            if constexpr (!RESIDENT) {
+                blk = theta_j + (int64_t)(MULTI ? ib : 0) * a.blk_bytes;
+#pragma unroll
+                for (int st = 0; st < AHEAD; ++st)
+#pragma unroll
+                    for (int n = 0; n < NSW; ++n) load_theta(st, n);
+            }
+            const int *ecol = reinterpret_cast<const int *>(blk + a.exp_off) + o_lane;
+#pragma unroll
+            for (int n = 0; n < NSW; ++n) {
+                const v4i ec = *reinterpret_cast<const v4i *>(ecol + 16 * n);
+#pragma unroll
+                for (int m = 0; m < P::MB; ++m) {
+                    const int e = s_E[m_buf][m * 16 + l_lane];
+                    if (MULTI && ib > 0) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) cc[m][n][i] = __builtin_ldexpf(cc[m][n][i], (e - e_now[m]) + (ec[i] - ec_now[n][i]));
+                    } else {
+                        cc[m][n] = v4f{0.f, 0.f, 0.f, 0.f};
+                    }
+                    if (n == NSW - 1) e_now[m] = e;
+                }
+                ec_now[n] = ec;
+            }
+            const char *arow = s_A[m_buf] + a_off;
+            // Two point blocks at a time, a depth step after the other; the fragments of the next two are read while the
+            // matrix ops of the current ones run.
+            constexpr int MH = 2, HALVES = P::MB / MH, ITEMS = P::KS * HALVES;
+            h8 bh[2][MH], bl[2][MH];
+            auto load_b = [&](int item) __attribute__((always_inline)) {
+                const int st = item / HALVES, m0 = item % HALVES * MH;
+#pragma unroll
+                for (int m = 0; m < MH; ++m) {
+                    bh[item & 1][m] = *reinterpret_cast<const h8 *>(arow + (m0 + m) * 16 * P::ARS + 64 * st);
+                    bl[item & 1][m] = *reinterpret_cast<const h8 *>(arow + (m0 + m) * 16 * P::ARS + 64 * st + 2 * P::KD);
+                }
+            };
+            load_b(0);
+#pragma unroll
+            for (int item = 0; item < ITEMS; ++item) {
+                const int st = item / HALVES, m0 = item % HALVES * MH;
+                if (item + 1 < ITEMS) load_b(item + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int n = 0; n < NSW; ++n) {
+                    const h8 L = tL[st % AHEAD][n];
+#pragma unroll
+                    for (int m = 0; m < MH; ++m) cc[m0 + m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(L, bh[item & 1][m], cc[m0 + m][n], 0, 0, 0);
+                }
+#pragma unroll
+                for (int n = 0; n < NSW; ++n) {
+                    const h8 H = tH[st % AHEAD][n];
+#pragma unroll
+                    for (int m = 0; m < MH; ++m) cc[m0 + m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(H, bl[item & 1][m], cc[m0 + m][n], 0, 0, 0);
+                }
+#pragma unroll
+                for (int n = 0; n < NSW; ++n) {
+                    const h8 H = tH[st % AHEAD][n];
+#pragma unroll
+                    for (int m = 0; m < MH; ++m) cc[m0 + m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(H, bh[item & 1][m], cc[m0 + m][n], 0, 0, 0);
+                    if constexpr (!RESIDENT)
+                        if (m0 + MH == P::MB && st + AHEAD < P::KS) load_theta(st + AHEAD, n);     // into the registers just read
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (MULTI && ib + 1 < a.n_in) { ++ib; continue; }
+#pragma unroll
+            for (int n = 0; n < NSW; ++n) {
+                const int o = j * P::OUTW + 16 * n + o_lane;
+#pragma unroll
+                for (int m = 0; m < P::MB; ++m) {
+                    const int pt = m * 16 + l_lane;
+                    v4f d = cc[m][n];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) d[i] = __builtin_ldexpf(d[i], -(e_now[m] + ec_now[n][i]));
+                    if (l0 + pt >= a.N) continue;
+                    const int l = CSR ? s_P[m_buf][pt] : l0 + pt;
+                    float *dst = a.out + b * a.out_b + l * a.out_l + o * a.out_c;
+                    if (a.out_c == 1 && o + 3 < a.w_out) *reinterpret_cast<v4fu *>(dst) = d;
+                    else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (o + i < a.w_out) dst[i * a.out_c] = d[i];
+                    }
+                }
+            }
+        }
+        ib = 0;
+        tw.next();
+    }
+}
+
+}  // namespace flex

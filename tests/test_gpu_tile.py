@@ -1,0 +1,48 @@
+"""The 64-point tile kernels (forward pass and feature gradient of layers wider than 64 gathered channels, and of widths
+without a kernel of their own), at the sizes where they can go wrong: clouds around a tile and around one point, rows that
+end inside a lane's four channels or inside an input block, output blocks that reach past the width, list lengths around
+a step of eight slots, hub points, several clouds, both layouts."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1803_07289_amd as fx
+from gpu_util import TOL, dev, to_layout, from_layout, say
+from helpers import rel_err
+from test_gpu_parity import random_problem
+
+pytestmark = pytest.mark.gpu
+
+
+def check(seed, B, N, K, Din, Dout, layout, hub=False):
+    say(f"tile: B={B} N={N} K={K} {Din}->{Dout} layout={layout} hub={hub}")
+    pos, nbr, feat, theta, bias, g = random_problem(seed, B, N, K, Din, Dout)
+    if hub:                                  # point 3 is listed by every centre: a list of N entries, empty ones elsewhere
+        nbr[:, -1, :] = 3
+    a = (to_layout(feat, layout), dev(pos), dev(nbr), dev(theta), dev(bias))
+    edges = fx.flex_inedges_build(a[2])
+    out = fx.flexconv_fwd(*a, layout=layout)
+    gf, _, _ = fx.flexconv_bwd(*a, to_layout(g, layout), layout=layout, in_edges=edges, need_params=False)
+    torch.cuda.synchronize()
+    assert rel_err(from_layout(out, layout), oracle.flexconv_fwd(feat, pos, nbr, theta, bias)) <= TOL
+    rgf, _, _ = oracle.flexconv_bwd(feat, pos, nbr, theta, bias, g)
+    assert rel_err(from_layout(gf, layout), rgf) <= TOL
+
+
+@pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
+@pytest.mark.parametrize("B,N,K,Din,Dout", [
+    (1, 1, 1, 128, 128), (1, 63, 7, 128, 64), (1, 64, 8, 128, 128), (2, 65, 9, 128, 256), (1, 130, 16, 256, 128),
+    (3, 200, 17, 70, 90),        # ragged input block, ragged output block
+    (1, 97, 8, 66, 3),           # two channels in the second input block, a three-channel result
+    (1, 150, 5, 3, 70),          # rows of fewer than four channels
+    (2, 80, 8, 5, 7),            # one narrow block
+    (1, 300, 8, 640, 384),       # ten input blocks (scales past the table), two output blocks
+])
+def test_sizes_around_the_tile_and_its_blocks(B, N, K, Din, Dout, layout):
+    check(70 + N + K, B, N, K, Din, Dout, layout)
+
+
+def test_hub_point_and_empty_lists():
+    check(5, 1, 500, 4, 128, 128, fx.BNC, hub=True)
+    check(6, 2, 90, 8, 100, 70, fx.BNC, hub=True)
