@@ -71,3 +71,8 @@ def test_compose_kernels_on_ragged_and_multi_tile_widths(Din0, Dmid, Dout):
     assert rel_err(gt.cpu().numpy(), np.einsum("ce,deo->dco", W64, gtc64)) <= 1e-6
     assert rel_err(gb.cpu().numpy(), np.einsum("ce,eo->co", W64, gbc64)) <= 1e-6
     assert rel_err(gW.cpu().numpy(), np.einsum("dco,deo->ce", t64, gtc64) + np.einsum("co,eo->ce", b64, gbc64)) <= 1e-6
+
+
+def test_compose_kernels_at_widths_that_fill_the_device():
+    """From 256 workgroups of 64 x 64 results on, the composition and its transposes take the larger tiles."""
+    test_compose_kernels_on_ragged_and_multi_tile_widths(520, 500, 512)
