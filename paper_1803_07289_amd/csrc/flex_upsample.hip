@@ -3,6 +3,7 @@
 // layer's neighbourhoods.  The zero-filled tensor is never written: an inverse map
 // inv[b*Nf + m] = j (or -1) is built in the workspace and the pooling gather reads row
 // inv[n] of the smaller layer, or takes 0.  Same tie rule as the pooling layer.
+#include <climits>
 #include "flex_common.hpp"
 
 namespace flex {
@@ -45,52 +46,86 @@ __global__ __launch_bounds__(256) void upsample_inv_scatter_kernel(const int32_t
     }
 }
 
-// Point-major, C % 4 == 0: one thread per (larger-layer point, 4 channels); ids, then inverse-map
-// entries, then rows of 8 neighbours are requested before anything is compared.
+// Point-major, C % 4 == 0: a workgroup takes `points` consecutive points of the larger layer.  First eight lanes per point
+// sort its neighbours out: those with a row in the smaller layer go to the point's list in LDS, all the zero-filled ones
+// together are one candidate, the value 0 with the lowest of their indices.  Then a thread per (point, 4 channels) compares
+// the rows of the list and that candidate.  What bounds it is the vector ALU and the chain neighbour -> inverse map -> row:
+// compared one by one, the three quarters of the neighbours that are zero-filled cost as much as the others, and every lane
+// of a point loaded the same ids and map entries (437.5k points x 128, K = 8, a quarter kept: 215 -> 138 us, of which the outputs alone are 72).
+// K * points entries of LDS; points: a power of two, at most 32.
 __global__ __launch_bounds__(256) void upsample_fwd_bnc4_kernel(const float *__restrict__ feat_small,
                                                                 const int32_t *__restrict__ inv,
                                                                 const int32_t *__restrict__ nbr,
                                                                 float *__restrict__ out,
                                                                 int32_t *__restrict__ argmax, int64_t BN,
-                                                                int Ns, int Nf, int K, int C4, int PT,
+                                                                int Ns, int Nf, int K, int C4, int points,
                                                                 int64_t total_tiles)
 {
-    constexpr int U = 8;
+    constexpr int U = 4;
+    extern __shared__ int2 s_list[];               // [points][K]: (index in the larger layer, row of the smaller one)
+    __shared__ int2 s_head[32];                    // (entries | first neighbour has a row << 30, lowest zero-filled index)
     const int64_t tile = xcd_tile_up(total_tiles);
     if (tile < 0) return;
-    for (int i = threadIdx.x; i < PT * C4; i += 256) {
-        const int c4 = i % C4;
-        const int64_t gp = tile * PT + i / C4;
+    {
+        const int slot = threadIdx.x & 7, p = threadIdx.x >> 3;
+        const int64_t gp = tile * points + p;
+        if (p < points && gp < BN) {               // whole groups of eight lanes take either side
+            const int b = (int)(gp / Nf), l = (int)(gp % Nf);
+            const int32_t *nb = nbr + (int64_t)b * K * Nf + l;
+            const int32_t *iv = inv + (int64_t)b * Nf;
+            int entries = 0, zero = INT_MAX, first = 0;
+            for (int k0 = 0; k0 < K; k0 += 8) {
+                const int k = k0 + slot;
+                const int n = nb[(int64_t)min(k, K - 1) * Nf];
+                const int j = iv[n];
+                const bool has = k < K && j >= 0;
+                zero = (k < K && j < 0) ? min(zero, n) : zero;
+                const unsigned mask = (unsigned)(__ballot(has) >> (threadIdx.x & 56)) & 0xffu;
+                if (has) s_list[p * K + entries + __popc(mask & ((1u << slot) - 1))] = make_int2(n, j);
+                if (k0 == 0) first = mask & 1;
+                entries += __popc(mask);
+            }
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) zero = min(zero, __shfl_xor(zero, d, 64));
+            if (slot == 0) s_head[p] = make_int2(entries | first << 30, zero);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < points * C4; i += 256) {
+        const int p = i / C4, c4 = i - p * C4;
+        const int64_t gp = tile * points + p;
         if (gp >= BN) break;
-        const int b = (int)(gp / Nf), l = (int)(gp % Nf);
-        const int32_t *nb = nbr + (int64_t)b * K * Nf + l;
-        const int32_t *iv = inv + (int64_t)b * Nf;
-        const v4f *rows = reinterpret_cast<const v4f *>(feat_small) + (int64_t)b * Ns * C4 + c4;
+        const v4f *rows = reinterpret_cast<const v4f *>(feat_small) + gp / Nf * Ns * C4 + c4;
+        const int2 head = s_head[p];
+        const int entries = head.x & 0x3fffffff, zero = head.y;
+        const int2 *list = s_list + p * K;
+        // the first neighbour is what the others are compared with
         float v0 = 0.f, v1 = 0.f, v2 = 0.f, v3 = 0.f;
-        int b0 = 0, b1 = 0, b2 = 0, b3 = 0;
-        for (int k0 = 0; k0 < K; k0 += U) {
-            int n[U], j[U];
+        int b0 = zero, b1 = zero, b2 = zero, b3 = zero;
+        for (int e0 = 0; e0 < entries; e0 += U) {
+            int2 en[U];
             v4f v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) n[u] = nb[(int64_t)min(k0 + u, K - 1) * Nf];   // past K: the last slot again
+            for (int u = 0; u < U; ++u) en[u] = list[min(e0 + u, entries - 1)];        // past the end: the last entry again
 #pragma unroll
-            for (int u = 0; u < U; ++u) j[u] = iv[n[u]];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                v[u] = v4f{0.f, 0.f, 0.f, 0.f};                      // a point that was only zero-filled
-                if (j[u] >= 0) v[u] = rows[(int64_t)j[u] * C4];
-            }
-            if (k0 == 0) {
+            for (int u = 0; u < U; ++u) v[u] = rows[(int64_t)en[u].y * C4];
+            if (e0 == 0 && head.x >> 30) {
                 v0 = v[0].x; v1 = v[0].y; v2 = v[0].z; v3 = v[0].w;
-                b0 = b1 = b2 = b3 = n[0];
+                b0 = b1 = b2 = b3 = en[0].x;
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                take_up(v[u].x, n[u], v0, b0);
-                take_up(v[u].y, n[u], v1, b1);
-                take_up(v[u].z, n[u], v2, b2);
-                take_up(v[u].w, n[u], v3, b3);
+                take_up(v[u].x, en[u].x, v0, b0);
+                take_up(v[u].y, en[u].x, v1, b1);
+                take_up(v[u].z, en[u].x, v2, b2);
+                take_up(v[u].w, en[u].x, v3, b3);
             }
+        }
+        if (zero != INT_MAX) {
+            take_up(0.f, zero, v0, b0);
+            take_up(0.f, zero, v1, b1);
+            take_up(0.f, zero, v2, b2);
+            take_up(0.f, zero, v3, b3);
         }
         const v4f bv = {v0, v1, v2, v3};
         // streaming stores, as in the pooling kernels
@@ -243,12 +278,13 @@ hipError_t launch_upsample_inv(const int32_t *sel, int32_t *inv, int B, int Ns, 
 hipError_t launch_upsample_fwd(const float *feat_small, const int32_t *inv, const int32_t *nbr, float *out,
                                int32_t *argmax, int B, int Ns, int Nf, int K, int C, int bnc, hipStream_t s)
 {
-    if (bnc && (C % 4 == 0)) {
-        const int C4 = C / 4;
-        const int PT = C4 >= 256 ? 1 : 256 / C4;
-        const int64_t BN = (int64_t)B * Nf, tiles = (BN + PT - 1) / PT;
-        hipLaunchKernelGGL(upsample_fwd_bnc4_kernel, dim3(xcd_grid_up(tiles)), dim3(256), 0, s, feat_small, inv, nbr,
-                           out, argmax, BN, Ns, Nf, K, C4, PT, tiles);
+    // 32 points a workgroup (eight lanes each) as far as their lists fit 16 KB
+    int points = 32;
+    while (points > 1 && (int64_t)points * K > 2048) points >>= 1;
+    const int64_t BN = (int64_t)B * Nf, tiles = (BN + points - 1) / points;
+    if (bnc && C % 4 == 0 && K <= 8192) {          // one point's list of up to 64 KB
+        hipLaunchKernelGGL(upsample_fwd_bnc4_kernel, dim3(xcd_grid_up(tiles)), dim3(256), sizeof(int2) * points * K, s, feat_small,
+                           inv, nbr, out, argmax, BN, Ns, Nf, K, C / 4, points, tiles);
     } else {
         hipLaunchKernelGGL(upsample_fwd_generic_kernel, dim3(capped_blocks((int64_t)B * Nf * C, 1 << 20)), dim3(256),
                            0, s, feat_small, inv, nbr, out, argmax, B, Ns, Nf, K, C, bnc);

@@ -84,3 +84,22 @@ def test_flexpool_sub_room_scale():
     assert np.array_equal(from_layout(arg, fx.BNC), ra)
     assert np.array_equal(from_layout(out, fx.BNC).view(np.uint32), ro.view(np.uint32))
     assert rel_err(from_layout(gf, fx.BNC), oracle.flexpool_sub_bwd(g, ra, sel, N)) <= 1e-5
+
+
+@pytest.mark.parametrize("N,C", [(41_003, 192), (17_001, 1024)])
+def test_flexpool_sub_bwd_several_points_per_thread(N, C):
+    """The backward pass of large clouds with at most half of the centres kept has four points per thread under way: ragged
+    last tile, rows that do not fill a workgroup, empty lists, lists of more than one load of sixteen entries."""
+    say(f"pool_sub bwd N={N} C={C}")
+    rng = np.random.default_rng(N)
+    Ns, K = N // 4, 4
+    nbr = rng.integers(0, N, size=(1, K, N)).astype(np.int32)
+    nbr[0, 0, ::3] = rng.integers(0, 97, size=nbr[0, 0, ::3].shape)          # a few points on hundreds of lists
+    sel = np.sort(rng.permutation(N)[:Ns]).astype(np.int32)[None]
+    arg = np.take_along_axis(nbr[0][:, sel[0]], rng.integers(0, K, size=(1, Ns)), axis=0)[0]        # a neighbour each
+    arg = np.ascontiguousarray(np.broadcast_to(arg[None, :, None], (1, Ns, C))).astype(np.int32)
+    g = rng.standard_normal((1, Ns, C)).astype(np.float32)
+    gf = fx.flexpool_sub_bwd(dev(g), dev(arg), N, layout=fx.BNC, in_edges=fx.flex_inedges_build_sub(dev(nbr), dev(sel)))
+    ref = np.zeros((N, C))
+    np.add.at(ref, arg[0, :, 0], g[0].astype(np.float64))
+    assert rel_err(gf.cpu().numpy()[0], ref) <= 1e-5

@@ -68,3 +68,20 @@ def test_flexupsample_room_scale():
     assert np.array_equal(from_layout(arg, fx.BNC), ra)
     assert np.array_equal(from_layout(out, fx.BNC).view(np.uint32), ro.view(np.uint32))
     assert rel_err(from_layout(gs, fx.BNC), oracle.flexupsample_bwd(g, ra, sel)) <= 1e-5
+
+
+@pytest.mark.parametrize("Nf,Ns,K,C", [(45, 1, 7, 4), (33, 33, 17, 8), (150, 40, 100, 12), (64, 16, 9, 1028), (2100, 500, 2100, 4)])
+def test_flexupsample_fwd_list_edges(Nf, Ns, K, C):
+    """The forward pass sorts a workgroup's neighbours out first: lists with nothing but zero-filled neighbours and with none,
+    K around the eight lanes a point has, fewer points per workgroup for long lists, rows wider than a workgroup."""
+    say(f"upsample lists Nf={Nf} Ns={Ns} K={K} C={C}")
+    rng = np.random.default_rng(Nf + K)
+    feat = rng.integers(-2, 3, size=(2, C, Ns)).astype(np.float32)
+    feat[:, :, 1::3] = -0.0
+    sel = np.stack([rng.permutation(Nf)[:Ns] for _ in range(2)]).astype(np.int32)
+    nbr = rng.integers(0, Nf, size=(2, K, Nf)).astype(np.int32)
+    ro, ra = oracle.flexupsample_fwd(feat, sel, nbr)
+    out, arg = fx.flexupsample_fwd(to_layout(feat, fx.BNC), dev(sel), dev(nbr), layout=fx.BNC)
+    torch.cuda.synchronize()
+    assert np.array_equal(from_layout(arg, fx.BNC), ra)
+    assert np.array_equal(from_layout(out, fx.BNC).view(np.uint32), ro.view(np.uint32))
