@@ -45,7 +45,7 @@ __global__ __launch_bounds__(256) void idiss_phi_kernel(const float *__restrict_
 }
 
 // per-cloud maximum; phi >= 0, so the float order is the order of the bit patterns
-__global__ __launch_bounds__(256) void idiss_max_kernel(const float *__restrict__ phi, unsigned *__restrict__ mx, int N)
+__global__ __launch_bounds__(1024) void idiss_max_kernel(const float *__restrict__ phi, unsigned *__restrict__ mx, int N)
 {
     const int b = blockIdx.y;
     unsigned m = 0;
@@ -53,7 +53,15 @@ __global__ __launch_bounds__(256) void idiss_max_kernel(const float *__restrict_
         m = max(m, __float_as_uint(phi[(int64_t)b * N + l]));
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, d, 64));
-    if ((threadIdx.x & 63) == 0 && m) atomicMax(&mx[b], m);
+    // one atomic per workgroup: they serialise on the cloud's word (one per wave of 489 workgroups: 25 us at 1M points)
+    __shared__ unsigned s_max[16];
+    if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < 16; ++w) m = max(m, s_max[w]);
+        if (m) atomicMax(&mx[b], m);
+    }
 }
 
 __device__ __forceinline__ unsigned idiss_quantum(float x, float mx, int bits)
@@ -299,8 +307,8 @@ hipError_t launch_idiss_sample(const float *phi, const uint32_t *u, int32_t *sel
     unsigned *mx = (unsigned *)((char *)bsum + align256(sizeof(unsigned long long) * (size_t)B * (nblk + 1)));
     hipError_t e = launch_fill_zero(mx, sizeof(unsigned) * (size_t)B, s);
     if (e != hipSuccess) return e;
-    const int mb = nblk < 1024 ? nblk : 1024;
-    hipLaunchKernelGGL(idiss_max_kernel, dim3(mb, B), dim3(256), 0, s, phi, mx, N);
+    const int mb = (N + 4095) / 4096;                      // four values per thread
+    hipLaunchKernelGGL(idiss_max_kernel, dim3(mb < 256 ? mb : 256, B), dim3(1024), 0, s, phi, mx, N);
     hipLaunchKernelGGL(idiss_chunk_sums_kernel, dim3(nblk, B), dim3(256), 0, s, phi, mx, bsum, N, nblk, bits);
     hipLaunchKernelGGL(idiss_scan_sums_kernel, dim3(B), dim3(256), 0, s, bsum, nblk);
     hipLaunchKernelGGL(idiss_running_sum_kernel, dim3(nblk, B), dim3(256), 0, s, phi, mx, bsum, C, N, nblk, bits);
