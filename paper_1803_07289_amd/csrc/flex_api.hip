@@ -35,9 +35,6 @@ hipError_t launch_bwd_fused_late_64_64(const float *g_rows, const float *own_row
                                        int N, int K, hipStream_t s);
 
 // parameter gradients of layers with both widths multiples of 128, block by block (same file, same shape)
-hipError_t launch_gt_split_wide(const float *rows, int rs, const float *pos, const int32_t *nbr, const float *g_rows,
-                                int gst, float *partials, int n_hi, int n_ho, int chunks, int B, int N, int K,
-                                hipStream_t s);
 int split_wide_gt_chunks(int B, int N, int blocks);
 hipError_t launch_reduce_partials(const float *partials, int n_wg, int DIP, int DOP, int n_blocks, int n_ho, int Din,
                                   int Dout, float *grad_theta, float *grad_bias, hipStream_t s);
@@ -45,6 +42,8 @@ hipError_t launch_reduce_partials(const float *partials, int n_wg, int DIP, int 
 // the 64-point tile kernels over fixed-K neighbour tensors / in-edge lists
 hipError_t launch_tile_0(const TileArgs &a, int outw, int grid, hipStream_t s);
 hipError_t launch_tile_1(const TileArgs &a, int outw, int grid, hipStream_t s);
+hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int gst, int n_hi, int n_ho, float *partials,
+                                  hipStream_t s);
 
 bool gather_contract_supported(int DI, int DO)
 {
@@ -169,7 +168,14 @@ static hipError_t wide_grad_theta(const float *rows, const float *pos, const int
                                   int Dko, int Din, int Dout, hipStream_t s)
 {
     const int n_hi = Dki / 64, n_ho = Dko / 64, chunks = split_wide_gt_chunks(B, N, n_hi * n_ho);
-    hipError_t e = launch_gt_split_wide(rows, Dki, pos, nbr, g_rows, Dko, partials, n_hi, n_ho, chunks, B, N, K, s);
+    TileArgs a{};
+    a.rows = rows; a.pos = pos; a.nbr = nbr;
+    a.rs = Dki; a.w_in = Dki;
+    a.N = N; a.K = K; a.tpc = (N + 63) / 64; a.n_in = 1; a.chunks = chunks;
+    const int64_t total = (int64_t)B * a.tpc;
+    if (total > 0x7fffffff || (int64_t)n_hi * n_ho * chunks > 0x7fffffff) return hipErrorInvalidValue;
+    a.total = (int)total;
+    hipError_t e = launch_tile_grad_theta(a, g_rows, Dko, n_hi, n_ho, partials, s);
     if (e != hipSuccess) return e;
     return launch_reduce_partials(partials, chunks, 64, 64, n_hi * n_ho, n_ho, Din, Dout, grad_theta, grad_bias, s);
 }

@@ -153,6 +153,133 @@ struct StepWalk {
     }
 };
 
+// Lane's channels of a row in input block ib: past the row's end the last four again, put right after the sums.
+__device__ __forceinline__ int tile_lane_channel(const TileArgs &a, int ib) { return min(ib * 64 + 4 * ((int)threadIdx.x & 15), a.w_in - 4); }
+
+// What a gathering wave does: the sums of its eight points (from `first` of every tile) over input blocks ib0 .. ib0 + n_in - 1,
+// acc[pass][channel][component]; park(acc, ib, point) takes them when a (tile, input block) is complete.
+// Eight rows are in flight at all times.
+template <bool CSR, class Park>
+__device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedule &sc, int tiles, int first, int ib0,
+                                             float (*ent)[64][4], Park &&park)
+{
+    const int lane = threadIdx.x & 63, grp = lane / 16;
+    StepWalk<CSR> walk(a, sc, first);
+    struct Positions { float n[3], c[3]; };
+    auto request = [&](const TileStep &d, int id, int point, Positions &p) {
+        const char *pb = reinterpret_cast<const char *>(a.pos + (int64_t)d.b * 3 * a.N);
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            p.n[x] = *reinterpret_cast<const float *>(pb + 4u * ((unsigned)(x * a.N) + (unsigned)id));
+            p.c[x] = *reinterpret_cast<const float *>(pb + 4u * ((unsigned)(x * a.N) + (unsigned)point));
+        }
+    };
+    auto publish = [&](int buf, int id, bool has, const Positions &p) {
+        const float sg = CSR ? -1.f : 1.f;          // CSR: point - listing centre
+        *reinterpret_cast<v4f *>(ent[buf][lane]) =
+            v4f{sg * (p.n[0] - p.c[0]), sg * (p.n[1] - p.c[1]), sg * (p.n[2] - p.c[2]),
+                __uint_as_float(has ? (unsigned)id * (4u * (unsigned)a.rs) : 0u - 4u * (unsigned)a.rs)};
+        wave_lds_sync();
+    };
+    auto lane_channel = [&](int ib) { return tile_lane_channel(a, ib0 + ib); };
+    auto rows_of = [&](const TileStep &d) {
+        return row_buffer(a.rows + (int64_t)d.b * a.N * a.rs, (unsigned)a.N * (unsigned)a.rs * 4u);
+    };
+
+    TileStep d0, d1, d2;
+    int id1, id2, pt1, pt2, pt0;                    // this lane's entries of the next two steps
+    bool has1, has2;
+    Positions p1;
+    v4f f[8];                                       // rows in flight
+    // how far ahead of its use LDS is read, as the registers allow: the differences EA slots, the offsets of four
+    // points from slot to slot over the four points before (fixed lists) or at once in front of them
+    constexpr int EA = CSR ? 2 : 4;
+    constexpr bool OFF_AHEAD = !CSR;
+    unsigned off[8];
+    {
+        int id0;
+        bool has0;
+        Positions p0;
+        d0 = walk.fetch(a, first, id0, pt0, has0);
+        d1 = walk.fetch(a, first, id1, pt1, has1);
+        request(d0, id0, pt0, p0);
+        d2 = walk.fetch(a, first, id2, pt2, has2);
+        publish(0, id0, has0, p0);
+        request(d1, id1, pt1, p1);
+        const auto rows = rows_of(d0);
+        const unsigned lane_off = 4u * (unsigned)lane_channel(d0.ib);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) f[u] = load_row4(rows, __float_as_uint(ent[0][8 * u + grp][3]) + lane_off);
+        if constexpr (OFF_AHEAD) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) off[u] = __float_as_uint(ent[0][8 * u + 4 + grp][3]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    v4f acc[2][4];                                  // [pass][channel][component]
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[p][v] = v4f{0.f, 0.f, 0.f, 0.f};
+    };
+    clear();
+
+    for (int s = 0, k = 0; k < tiles; ++s) {
+        const int buf = s & 1;
+        publish(buf ^ 1, id1, has1, p1);            // the next step's entries
+        request(d2, id2, pt2, p1);                  // positions of the step after it, entries of the one after that
+        int id3, pt3;
+        bool has3;
+        const TileStep d3 = walk.fetch(a, first, id3, pt3, has3);
+
+        // Eight rows are in flight at all times: the registers of a slot that has been summed take the same slot of
+        // the next four points at once, of the next step's after the second four.
+        const auto rows0 = rows_of(d0), rows1 = rows_of(d1);
+        const unsigned lane_off0 = 4u * (unsigned)lane_channel(d0.ib), lane_off1 = 4u * (unsigned)lane_channel(d1.ib);
+        v4f e[EA + 1];
+#pragma unroll
+        for (int u = 0; u < EA; ++u) e[u] = *reinterpret_cast<const v4f *>(ent[buf][8 * u + grp]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            if constexpr (!OFF_AHEAD) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) off[u] = __float_as_uint(p == 0 ? ent[buf][8 * u + 4 + grp][3] : ent[buf ^ 1][8 * u + grp][3]);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                constexpr int R = EA + 1;
+                const int i = 8 * p + u;
+                if (i + EA < 16) e[(i + EA) % R] = *reinterpret_cast<const v4f *>(ent[buf][8 * ((i + EA) & 7) + 4 * ((i + EA) >> 3) + grp]);
+                const v4f d = e[i % R];
+                if (u < (p == 0 ? d0.n0 : d0.n1)) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        acc[p][v][0] = fmaf(d[0], f[u][v], acc[p][v][0]);
+                        acc[p][v][1] = fmaf(d[1], f[u][v], acc[p][v][1]);
+                        acc[p][v][2] = fmaf(d[2], f[u][v], acc[p][v][2]);
+                        acc[p][v][3] += f[u][v];
+                    }
+                }
+                f[u] = p == 0 ? load_row4(rows0, off[u] + lane_off0) : load_row4(rows1, off[u] + lane_off1);
+                if constexpr (OFF_AHEAD) off[u] = __float_as_uint(ent[buf ^ 1][8 * u + 4 * p + grp][3]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (d0.last) {
+            park(acc, d0.ib, pt0);
+            ++k;
+            clear();
+        }
+        d0 = d1; d1 = d2; d2 = d3;
+        pt0 = pt1; pt1 = pt2; pt2 = pt3;
+        id1 = id2; id2 = id3;
+        has1 = has2; has2 = has3;
+    }
+}
+
 template <int WM, int NSW, bool CSR, bool MULTI>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void tile_conv_kernel(const TileArgs a)
@@ -182,180 +309,67 @@ void tile_conv_kernel(const TileArgs a)
         // ---- gather ----
         static_assert(P::PASSES == 2 && P::G == 4, "two passes of four points");
         const int t = lane % P::LPR, grp = lane / P::LPR, first = 8 * wave;
-        float (*ent)[64][4] = s_ent[wave];
-        StepWalk<CSR> walk(a, sc, first);
-        struct Positions { float n[3], c[3]; };
-        auto request = [&](const TileStep &d, int id, int point, Positions &p) {
-            const char *pb = reinterpret_cast<const char *>(a.pos + (int64_t)d.b * 3 * a.N);
-#pragma unroll
-            for (int x = 0; x < 3; ++x) {
-                p.n[x] = *reinterpret_cast<const float *>(pb + 4u * ((unsigned)(x * a.N) + (unsigned)id));
-                p.c[x] = *reinterpret_cast<const float *>(pb + 4u * ((unsigned)(x * a.N) + (unsigned)point));
-            }
-        };
-        auto publish = [&](int buf, int id, bool has, const Positions &p) {
-            const float sg = CSR ? -1.f : 1.f;          // CSR: point - listing centre
-            *reinterpret_cast<v4f *>(ent[buf][lane]) =
-                v4f{sg * (p.n[0] - p.c[0]), sg * (p.n[1] - p.c[1]), sg * (p.n[2] - p.c[2]),
-                    __uint_as_float(has ? (unsigned)id * (4u * (unsigned)a.rs) : 0u - 4u * (unsigned)a.rs)};
-            wave_lds_sync();
-        };
-        // this lane's channels of a row: past the row's end the last four again, put right after the sums
-        auto lane_channel = [&](int ib) { return min(ib * IC + 4 * t, a.w_in - 4); };
-        auto rows_of = [&](const TileStep &d) {
-            return row_buffer(a.rows + (int64_t)d.b * a.N * a.rs, (unsigned)a.N * (unsigned)a.rs * 4u);
-        };
         const bool ragged = a.w_in % IC != 0;
-
-        TileStep d0, d1, d2;
-        int id1, id2, pt1, pt2, pt0;                    // this lane's entries of the next two steps
-        bool has1, has2;
-        Positions p1;
-        v4f f[8];                                       // rows in flight
-        // how far ahead of its use LDS is read, as the registers allow: the differences EA slots, the offsets of four
-        // points from slot to slot over the four points before (fixed lists) or at once in front of them
-        constexpr int EA = CSR ? 2 : 4;
-        constexpr bool OFF_AHEAD = !CSR;
-        unsigned off[8];
-        {
-            int id0;
-            bool has0;
-            Positions p0;
-            d0 = walk.fetch(a, first, id0, pt0, has0);
-            d1 = walk.fetch(a, first, id1, pt1, has1);
-            request(d0, id0, pt0, p0);
-            d2 = walk.fetch(a, first, id2, pt2, has2);
-            publish(0, id0, has0, p0);
-            request(d1, id1, pt1, p1);
-            const auto rows = rows_of(d0);
-            const unsigned lane_off = 4u * (unsigned)lane_channel(d0.ib);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) f[u] = load_row4(rows, __float_as_uint(ent[0][8 * u + grp][3]) + lane_off);
-            if constexpr (OFF_AHEAD) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) off[u] = __float_as_uint(ent[0][8 * u + 4 + grp][3]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        v4f acc[2][4];                                  // [pass][channel][component]
-        auto clear = [&]() __attribute__((always_inline)) {
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[p][v] = v4f{0.f, 0.f, 0.f, 0.f};
-        };
-        clear();
-
         int ex_run[2] = {0, 0};
         int m_buf = 0;                                  // tile buffer of the tile being gathered
-        for (int s = 0, k = 0; k < tiles; ++s) {
-            const int buf = s & 1;
-            publish(buf ^ 1, id1, has1, p1);            // the next step's entries
-            request(d2, id2, pt2, p1);                  // positions of the step after it, entries of the one after that
-            int id3, pt3;
-            bool has3;
-            const TileStep d3 = walk.fetch(a, first, id3, pt3, has3);
-
-            // Eight rows are in flight at all times: the registers of a slot that has been summed take the same slot of
-            // the next four points at once, of the next step's after the second four.
-            const auto rows0 = rows_of(d0), rows1 = rows_of(d1);
-            const unsigned lane_off0 = 4u * (unsigned)lane_channel(d0.ib), lane_off1 = 4u * (unsigned)lane_channel(d1.ib);
-            v4f e[EA + 1];
-#pragma unroll
-            for (int u = 0; u < EA; ++u) e[u] = *reinterpret_cast<const v4f *>(ent[buf][8 * u + grp]);
-            __builtin_amdgcn_sched_barrier(0);
+        gather_steps<CSR>(a, sc, tiles, first, 0, s_ent[wave], [&](v4f (&acc)[2][4], int step_ib, int point) __attribute__((always_inline)) {
+            // ---- park ----
+            const int ib = MULTI ? step_ib : 0;
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                if constexpr (!OFF_AHEAD) {
+                const int shift = ib * IC + 4 * t - tile_lane_channel(a, ib);
+                if (ragged && shift > 0) {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) off[u] = __float_as_uint(p == 0 ? ent[buf][8 * u + 4 + grp][3] : ent[buf ^ 1][8 * u + grp][3]);
-                }
+                    for (int v = 0; v < 4; ++v) {
+                        v4f x = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    constexpr int R = EA + 1;
-                    const int i = 8 * p + u;
-                    if (i + EA < 16) e[(i + EA) % R] = *reinterpret_cast<const v4f *>(ent[buf][8 * ((i + EA) & 7) + 4 * ((i + EA) >> 3) + grp]);
-                    const v4f d = e[i % R];
-                    if (u < (p == 0 ? d0.n0 : d0.n1)) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            acc[p][v][0] = fmaf(d[0], f[u][v], acc[p][v][0]);
-                            acc[p][v][1] = fmaf(d[1], f[u][v], acc[p][v][1]);
-                            acc[p][v][2] = fmaf(d[2], f[u][v], acc[p][v][2]);
-                            acc[p][v][3] += f[u][v];
-                        }
+                        for (int w = v + 1; w < 4; ++w)
+                            if (w - v == shift) x = acc[p][w];
+                        acc[p][v] = x;
                     }
-                    f[u] = p == 0 ? load_row4(rows0, off[u] + lane_off0) : load_row4(rows1, off[u] + lane_off1);
-                    if constexpr (OFF_AHEAD) off[u] = __float_as_uint(ent[buf ^ 1][8 * u + 4 * p + grp][3]);
-                    __builtin_amdgcn_sched_barrier(0);
                 }
+                float m = 0.f;
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    const float *rs = ib < RS_BLOCKS ? &s_rs[ib][jj * IC + 4 * t]
+                        : reinterpret_cast<const float *>(theta_j + (int64_t)ib * a.blk_bytes + a.rs_off) + jj * IC + 4 * t;
+                    const v4f r = *reinterpret_cast<const v4f *>(rs);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        acc[p][v][jj] *= r[v];
+                        m = __builtin_amdgcn_fmed3f(m, __builtin_fabsf(acc[p][v][jj]), __builtin_inff());
+                    }
+                }
+                m = group_max<P::LPR>(m);
+                int ex = 15 - __builtin_amdgcn_frexp_expf(m);
+                if constexpr (MULTI) {     // one exponent per point over all input blocks so far, see the contraction
+                    ex = ib > 0 ? min(ex, ex_run[p]) : ex;
+                    ex_run[p] = ex;
+                }
+                const int pt = first + 4 * p + grp;
+                char *row = s_A[m_buf] + pt * P::ARS + 8 * t;
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    typedef float f2 __attribute__((ext_vector_type(2)));
+                    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+                    h2 h[2], l[2];
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        const f2 x = {__builtin_ldexpf(acc[p][2 * w][jj], ex), __builtin_ldexpf(acc[p][2 * w + 1][jj], ex)};
+                        h[w] = __builtin_convertvector(x, h2);
+                        const f2 back = __builtin_convertvector(h[w], f2);
+                        l[w] = __builtin_convertvector(x - back, h2);
+                    }
+                    *reinterpret_cast<h4 *>(row + 2 * jj * IC) = h4{h[0][0], h[0][1], h[1][0], h[1][1]};
+                    *reinterpret_cast<h4 *>(row + 2 * (P::KD + jj * IC)) = h4{l[0][0], l[0][1], l[1][0], l[1][1]};
+                }
+                if (t == 0) s_E[m_buf][pt] = ex;
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (d0.last) {
-                // ---- park ----
-                const int ib = MULTI ? d0.ib : 0;
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    const int shift = ib * IC + 4 * t - lane_channel(ib);
-                    if (ragged && shift > 0) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            v4f x = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                            for (int w = v + 1; w < 4; ++w)
-                                if (w - v == shift) x = acc[p][w];
-                            acc[p][v] = x;
-                        }
-                    }
-                    float m = 0.f;
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        const float *rs = ib < RS_BLOCKS ? &s_rs[ib][jj * IC + 4 * t]
-                            : reinterpret_cast<const float *>(theta_j + (int64_t)ib * a.blk_bytes + a.rs_off) + jj * IC + 4 * t;
-                        const v4f r = *reinterpret_cast<const v4f *>(rs);
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            acc[p][v][jj] *= r[v];
-                            m = __builtin_amdgcn_fmed3f(m, __builtin_fabsf(acc[p][v][jj]), __builtin_inff());
-                        }
-                    }
-                    m = group_max<P::LPR>(m);
-                    int ex = 15 - __builtin_amdgcn_frexp_expf(m);
-                    if constexpr (MULTI) {     // one exponent per point over all input blocks so far, see the contraction
-                        ex = ib > 0 ? min(ex, ex_run[p]) : ex;
-                        ex_run[p] = ex;
-                    }
-                    const int pt = first + 4 * p + grp;
-                    char *row = s_A[m_buf] + pt * P::ARS + 8 * t;
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        typedef float f2 __attribute__((ext_vector_type(2)));
-                        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-                        h2 h[2], l[2];
-#pragma unroll
-                        for (int w = 0; w < 2; ++w) {
-                            const f2 x = {__builtin_ldexpf(acc[p][2 * w][jj], ex), __builtin_ldexpf(acc[p][2 * w + 1][jj], ex)};
-                            h[w] = __builtin_convertvector(x, h2);
-                            const f2 back = __builtin_convertvector(h[w], f2);
-                            l[w] = __builtin_convertvector(x - back, h2);
-                        }
-                        *reinterpret_cast<h4 *>(row + 2 * jj * IC) = h4{h[0][0], h[0][1], h[1][0], h[1][1]};
-                        *reinterpret_cast<h4 *>(row + 2 * (P::KD + jj * IC)) = h4{l[0][0], l[0][1], l[1][0], l[1][1]};
-                    }
-                    if (t == 0) s_E[m_buf][pt] = ex;
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if (CSR && lane < 8) s_P[m_buf][first + lane] = pt0;
-                m_buf ^= 1;
-                ++k;
-                clear();
-                __syncthreads();               // the tile is complete
-            }
-            d0 = d1; d1 = d2; d2 = d3;
-            pt0 = pt1; pt1 = pt2; pt2 = pt3;
-            id1 = id2; id2 = id3;
-            has1 = has2; has2 = has3;
-        }
+            if (CSR && lane < 8) s_P[m_buf][first + lane] = point;
+            m_buf ^= 1;
+            __syncthreads();               // the tile is complete
+        });
         return;
     }
 
@@ -483,6 +497,146 @@ void tile_conv_kernel(const TileArgs a)
         ib = 0;
         tw.next();
     }
+}
+
+// ---------------------------------------------------------------------------
+// Parameter gradients of wide layers on 64-point tiles: partial[kd][o] = sum over the workgroup's points of A[pt][kd] g[pt][o]
+// for one block of 64 feature channels (kd = j*64 + c) and 64 output channels.
+//
+// Workgroup x serves block p = x / chunks = (hi, ho) = (p / n_ho, p % n_ho) as share x % chunks: a deep, low-resolution
+// layer has many blocks and few points, so a workgroup walks all points for one block instead of all of them walking a few
+// tiles each for every block.
+//
+// The sums over points are those of grad_theta_lean_body: every value as three bf16 pieces, six products on the bf16
+// matrix cores, accumulators flushed into running totals every eight depth steps, operands read transposed out of
+// point-major LDS tiles.  The gathering waves are those of the convolution above, and the contracting waves fetch the
+// upstream gradient.  One tile buffer (100 KB of LDS): the gathering waves sum the next tile in registers while this one is
+// contracted, and park it between two barriers.
+// What bounds it is the vector ALU (three quarters busy, the matrix cores 39 percent): the gather alone takes 140 us of 203
+// at 128 -> 128 and 200k points, the contraction alone 143.  A block of 128 output channels would gather half as often, but
+// its accumulators and their running totals do not fit the registers.  Against lean waves on 32-point tiles with
+// run-time strides, us: 256 -> 256 100k points 411 -> 393, K = 9 33k points 200 -> 170; 512 -> 512 33k points K = 9
+// 776 -> 656.
+// ---------------------------------------------------------------------------
+static __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, int gst, int n_ho, float *__restrict__ partials)
+{
+    constexpr int IC = 64, KD = 4 * IC, OC = 64, T = 64;
+    constexpr int AS = bf3_stride(KD), GS = bf3_stride(OC);
+    __shared__ __attribute__((aligned(16))) char s_A[T * AS];
+    __shared__ __attribute__((aligned(16))) char s_G[T * GS];
+    __shared__ __attribute__((aligned(16))) float s_ent[8][2][64][4];
+
+    const int p = blockIdx.x / a.chunks, hi = p / n_ho, ho = p - hi * n_ho;
+    const TileSchedule sc(a.total, (int)blockIdx.x - p * a.chunks, a.chunks);
+    const int tiles = sc.first < sc.end ? (sc.end - sc.first + sc.step - 1) / sc.step : 0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+
+    if (wave < 8) {
+        // ---- gather ----
+        if (tiles == 0) return;
+        const int t = lane & 15, grp = lane >> 4, first = 8 * wave;
+        gather_steps<false>(a, sc, tiles, first, hi, s_ent[wave], [&](v4f (&acc)[2][4], int, int) __attribute__((always_inline)) {
+            __syncthreads();               // the tile before is contracted
+#pragma unroll
+            for (int ps = 0; ps < 2; ++ps) {
+                char *row = s_A + (first + 4 * ps + grp) * AS + 8 * t;
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    unsigned h0, m0, l0, h1, m1, l1;
+                    split_bf3(acc[ps][0][jj], acc[ps][1][jj], h0, m0, l0);
+                    split_bf3(acc[ps][2][jj], acc[ps][3][jj], h1, m1, l1);
+                    char *d = row + 2 * jj * IC;
+                    *reinterpret_cast<uint2 *>(d) = make_uint2(h0, h1);
+                    *reinterpret_cast<uint2 *>(d + 2 * KD) = make_uint2(m0, m1);
+                    *reinterpret_cast<uint2 *>(d + 4 * KD) = make_uint2(l0, l1);
+                }
+            }
+            __syncthreads();               // the tile is complete
+        });
+        return;
+    }
+
+    // ---- contract: four 16-row blocks x two 16-column blocks of the partial per wave ----
+    constexpr int MBW = 4, NBW = 2, FLUSH = 4;
+    const int cw = wave - 8, q = lane >> 4, r16 = lane & 15, wn = cw & 1, wm = cw >> 1, ctid = threadIdx.x - 512;
+    v4f acc[MBW][NBW], tot[MBW][NBW];
+#pragma unroll
+    for (int c = 0; c < MBW; ++c)
+#pragma unroll
+        for (int n = 0; n < NBW; ++n) { acc[c][n] = v4f{0.f, 0.f, 0.f, 0.f}; tot[c][n] = v4f{0.f, 0.f, 0.f, 0.f}; }
+
+    TileWalk tw(sc, a.tpc);
+    v4f gv[2];                             // upstream gradient of a tile: two four-float chunks per thread
+    auto load_g = [&]() {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int pt = (ctid >> 4) + 32 * c, l = tw.tic * T + pt;
+            gv[c] = v4f{0.f, 0.f, 0.f, 0.f};                       // points past the cloud contribute nothing
+            if (l < a.N) gv[c] = *reinterpret_cast<const v4f *>(g_rows + ((int64_t)tw.b * a.N + l) * gst + OC * ho + 4 * (ctid & 15));
+        }
+    };
+    if (tiles > 0) load_g();
+    for (int k = 0; k < tiles; ++k) {
+        __syncthreads();                   // the tile before is contracted
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            char *d = s_G + ((ctid >> 4) + 32 * c) * GS + 8 * (ctid & 15);
+            unsigned h0, m0, l0, h1, m1, l1;
+            split_bf3(gv[c][0], gv[c][1], h0, m0, l0);
+            split_bf3(gv[c][2], gv[c][3], h1, m1, l1);
+            *reinterpret_cast<uint2 *>(d) = make_uint2(h0, h1);
+            *reinterpret_cast<uint2 *>(d + 2 * OC) = make_uint2(m0, m1);
+            *reinterpret_cast<uint2 *>(d + 4 * OC) = make_uint2(l0, l1);
+        }
+        tw.next_clamped();
+        load_g();
+        if (k % FLUSH == 0 && k > 0) {
+#pragma unroll
+            for (int c = 0; c < MBW; ++c)
+#pragma unroll
+                for (int n = 0; n < NBW; ++n) { tot[c][n] += acc[c][n]; acc[c][n] = v4f{0.f, 0.f, 0.f, 0.f}; }
+        }
+        __syncthreads();                   // the tile is complete
+#pragma unroll
+        for (int st = 0; st < T / 32; ++st) {
+            bf8 gH[NBW], gM[NBW], gL[NBW];
+#pragma unroll
+            for (int n = 0; n < NBW; ++n) {
+                const int col = 2 * 16 * (wn + 2 * n);
+                gH[n] = read_tr_frag(s_G, GS, 32 * st + 8 * q, col, r16);
+                gM[n] = read_tr_frag(s_G, GS, 32 * st + 8 * q, col + 2 * OC, r16);
+                gL[n] = read_tr_frag(s_G, GS, 32 * st + 8 * q, col + 4 * OC, r16);
+            }
+#pragma unroll
+            for (int c = 0; c < MBW; ++c) {
+                const int col = 2 * 16 * (wm + 4 * c);
+                const bf8 aH = read_tr_frag(s_A, AS, 32 * st + 8 * q, col, r16);
+                const bf8 aM = read_tr_frag(s_A, AS, 32 * st + 8 * q, col + 2 * KD, r16);
+                const bf8 aL = read_tr_frag(s_A, AS, 32 * st + 8 * q, col + 4 * KD, r16);
+#define FLEX_BF_MFMA(X, Y)                                                                         \
+    _Pragma("unroll") for (int n = 0; n < NBW; ++n)                                               \
+        acc[c][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(X, Y[n], acc[c][n], 0, 0, 0)
+                FLEX_BF_MFMA(aL, gH);   // small terms first
+                FLEX_BF_MFMA(aH, gL);
+                FLEX_BF_MFMA(aM, gM);
+                FLEX_BF_MFMA(aM, gH);
+                FLEX_BF_MFMA(aH, gM);
+                FLEX_BF_MFMA(aH, gH);
+#undef FLEX_BF_MFMA
+            }
+        }
+    }
+
+    float *dst = partials + (int64_t)blockIdx.x * KD * OC;
+#pragma unroll
+    for (int c = 0; c < MBW; ++c)
+#pragma unroll
+        for (int n = 0; n < NBW; ++n) {
+            const v4f sum = tot[c][n] + acc[c][n];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dst[(int64_t)((wm + 4 * c) * 16 + 4 * q + i) * OC + (wn + 2 * n) * 16 + r16] = sum[i];
+        }
 }
 
 }  // namespace flex

@@ -277,26 +277,6 @@ int split_wide_gt_chunks(int B, int N, int blocks)
     const int fill = persistent_grid(tot > 0x7fffffff ? 0x7fffffff : (int)tot, 1);
     return fill / blocks > 1 ? fill / blocks : 1;
 }
-
-// All n_hi x n_ho blocks of the parameter gradient of a wide layer in one launch (block p = feature channels
-// 64 * (p / n_ho).., upstream-gradient channels 64 * (p % n_ho)..); partials[p * chunks + share].
-hipError_t launch_gt_split_wide(const float *rows, int rs, const float *pos, const int32_t *nbr, const float *g_rows,
-                                int gst, float *partials, int n_hi, int n_ho, int chunks, int B, int N, int K,
-                                hipStream_t s)
-{
-    using WL = WsGeom<S, 2, 2>;
-    const int tpc = (N + WL::T - 1) / WL::T;
-    const int64_t tot64 = (int64_t)B * tpc, grid = (int64_t)n_hi * n_ho * chunks;
-    if (tot64 > 0x7fffffff || grid > 0x7fffffff) return hipErrorInvalidValue;
-    const int tot = (int)tot64;
-    if (K % 8 == 0)
-        hipLaunchKernelGGL((grad_theta_lean_blocks_kernel<S, false>), dim3((unsigned)grid), dim3(WL::NT), 0, s, rows,
-                           pos, nbr, g_rows, partials, N, K, tpc, tot, rs, gst, chunks, n_ho);
-    else
-        hipLaunchKernelGGL((grad_theta_lean_blocks_kernel<S, true>), dim3((unsigned)grid), dim3(WL::NT), 0, s, rows,
-                           pos, nbr, g_rows, partials, N, K, tpc, tot, rs, gst, chunks, n_ho);
-    return hipGetLastError();
-}
 #endif
 
 // One term of the location gradient; false / hipErrorNotSupported when this shape has no kernel for it.

@@ -1684,9 +1684,10 @@ __device__ __forceinline__ void split_bf3(float x0, float x1, unsigned &h, unsig
     const float r0 = x0 - __uint_as_float(b0 & 0xffff0000u), r1 = x1 - __uint_as_float(b1 & 0xffff0000u);
     const unsigned c0 = __float_as_uint(r0), c1 = __float_as_uint(r1);
     const float s0 = r0 - __uint_as_float(c0 & 0xffff0000u), s1 = r1 - __uint_as_float(c1 & 0xffff0000u);
-    h = (b0 >> 16) | (b1 & 0xffff0000u);
-    m = (c0 >> 16) | (c1 & 0xffff0000u);
-    l = (__float_as_uint(s0) >> 16) | (__float_as_uint(s1) & 0xffff0000u);
+    // the upper halves of two words in one instruction
+    h = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+    m = __builtin_amdgcn_perm(c1, c0, 0x07060302u);
+    l = __builtin_amdgcn_perm(__float_as_uint(s1), __float_as_uint(s0), 0x07060302u);
 }
 
 // operand fragment: 8 consecutive points (p0..p0+7 given by the lane's group) of column col0 + lane%16
@@ -1705,11 +1706,9 @@ template <class S, int RS, int GST, bool TAIL>
 __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ rows, const float *__restrict__ pos,
                                                      const int32_t *__restrict__ nbr,
                                                      const float *__restrict__ g_rows, float *__restrict__ partial,
-                                                     int N, int K, int tiles_per_cloud, const TileSchedule sc,
-                                                     int rs_rt, int gst_rt)
+                                                     int N, int K, int tiles_per_cloud, const TileSchedule sc)
 {
     // partial: where this workgroup's [KD x DOP] sums go; sc: the tiles it takes
-    const int gst = GST != 0 ? GST : gst_rt;
     using G = WsGeom<S, 2, 2>;
     static_assert(G::T == 32, "one 32-point depth step of the matrix op per tile");
     constexpr int AS = bf3_stride(S::KD), GS = bf3_stride(S::DOP);
@@ -1722,7 +1721,6 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
     if (w < G::NP) {
         LeanProducer<S, 2, false, RS, TAIL> P;
         P.init(rows, pos, nbr, N, K, w, sc, tiles_per_cloud);
-        P.set_row_stride(rs_rt);
         P.set_dp_stage(s_D[w]);
         // grad_out tile: T*DOP/4 four-float chunks over the producer threads, one tile ahead in registers
         constexpr int CPR = S::DOP / 4;                      // chunks per point
@@ -1736,7 +1734,7 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
                 const int pt = ch / CPR, o = 4 * (ch % CPR);
                 gv[c] = v4f{0.f, 0.f, 0.f, 0.f};
                 if (ch < G::T * CPR && l0 + pt < N) {        // points past the cloud contribute nothing
-                    const float *src = g_rows + ((int64_t)b * N + l0 + pt) * gst + o;
+                    const float *src = g_rows + ((int64_t)b * N + l0 + pt) * GST + o;
                     if constexpr (S::DO % 4 == 0) {
                         if (o < S::DO) gv[c] = *reinterpret_cast<const v4f *>(src);
                     } else {
@@ -1878,30 +1876,8 @@ void grad_theta_lean_kernel(const float *__restrict__ rows, const float *__restr
                             const int32_t *__restrict__ nbr, const float *__restrict__ g_rows,
                             float *__restrict__ partials, int N, int K, int tiles_per_cloud, int total_tiles)
 {
-    static_assert(RS != 0 && GST != 0, "run-time strides go through grad_theta_lean_blocks_kernel");
     grad_theta_lean_body<S, RS, GST, TAIL>(rows, pos, nbr, g_rows, partials + (int64_t)blockIdx.x * S::KD * S::DOP, N, K,
-                                           tiles_per_cloud, TileSchedule(total_tiles), 0, 0);
-}
-
-// Parameter gradients of a layer wider than this shape, point-major, in one launch: the (Din / S::DI) x
-// (Dout / S::DO) blocks of the result are independent jobs, and each job's tiles are shared by `chunks`
-// workgroups (output-stationary: a deep, low-resolution layer has many blocks and few points, so a workgroup
-// walks all points for one block instead of all workgroups walking a few tiles each for every block).
-// Workgroup x serves block p = x / chunks = (hi, ho) = (p / n_ho, p % n_ho) as share x % chunks: column block hi
-// of the feature rows (rs floats apart) against column block ho of the upstream gradient rows (gst floats apart);
-// its partial goes to partials[x].
-template <class S, bool TAIL>
-__global__ __launch_bounds__((WsGeom<S, 2, 2>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void grad_theta_lean_blocks_kernel(const float *__restrict__ rows, const float *__restrict__ pos,
-                                   const int32_t *__restrict__ nbr, const float *__restrict__ g_rows,
-                                   float *__restrict__ partials, int N, int K, int tiles_per_cloud, int total_tiles,
-                                   int rs, int gst, int chunks, int n_ho)
-{
-    const int p = blockIdx.x / chunks, q = blockIdx.x - p * chunks;
-    const int hi = p / n_ho, ho = p - hi * n_ho;
-    grad_theta_lean_body<S, 0, 0, TAIL>(rows + S::DI * hi, pos, nbr, g_rows + S::DO * ho,
-                                        partials + (int64_t)blockIdx.x * S::KD * S::DOP, N, K, tiles_per_cloud,
-                                        TileSchedule(total_tiles, q, chunks), rs, gst);
+                                           tiles_per_cloud, TileSchedule(total_tiles));
 }
 
 // ---------------------------------------------------------------------------
@@ -2310,7 +2286,7 @@ void grad_theta_lean_late_kernel(int *__restrict__ control, const float *__restr
         if (threadIdx.x == 0) *control = FUSED_UNRESOLVED;
     }
     grad_theta_lean_body<S, S::DI, S::DO, TAIL>(rows, pos, nbr, g_rows, partials + (int64_t)blockIdx.x * S::KD * S::DOP,
-                                                N, K, tiles_per_cloud, TileSchedule(total_tiles), 0, 0);
+                                                N, K, tiles_per_cloud, TileSchedule(total_tiles));
 }
 
 // ---------------------------------------------------------------------------

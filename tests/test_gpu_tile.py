@@ -46,3 +46,23 @@ def test_sizes_around_the_tile_and_its_blocks(B, N, K, Din, Dout, layout):
 def test_hub_point_and_empty_lists():
     check(5, 1, 500, 4, 128, 128, fx.BNC, hub=True)
     check(6, 2, 90, 8, 100, 70, fx.BNC, hub=True)
+
+
+@pytest.mark.parametrize("B,N,K,Din,Dout", [
+    (1, 1, 1, 128, 128), (1, 63, 7, 128, 256), (2, 65, 9, 256, 128), (3, 130, 16, 130, 70),
+    (1, 3001, 8, 1024, 128),     # six tiles per workgroup: the accumulators go into the running totals in between
+])
+def test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout):
+    say(f"tile parameter gradients: B={B} N={N} K={K} {Din}->{Dout}")
+    pos, nbr, feat, theta, bias, g = random_problem(40 + N, B, N, K, Din, Dout)
+    lay = lambda a: to_layout(a, fx.BNC)
+    edges = fx.flex_inedges_build(dev(nbr))
+    _, gt, gb = fx.flexconv_bwd(lay(feat), dev(pos), dev(nbr), dev(theta), dev(bias), lay(g), layout=fx.BNC, in_edges=edges)
+    rt, rb = np.zeros(theta.shape), np.zeros(bias.shape)
+    for b in range(B):
+        p, f, up = (a[b].astype(np.float64) for a in (pos, feat, g))
+        rows = f.T[nbr[b]]                                                   # [K, N, Din]
+        for d in range(3):
+            rt[d] += ((p[d][nbr[b]] - p[d])[:, :, None] * rows).sum(axis=0).T @ up.T
+        rb += rows.sum(axis=0).T @ up.T
+    assert rel_err(gt.cpu().numpy(), rt) <= TOL and rel_err(gb.cpu().numpy(), rb) <= TOL
