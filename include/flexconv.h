@@ -396,25 +396,26 @@ int flex_validate_neighbors(const int32_t *nbr, int B, int N, int K,
                             int32_t *bad_count_dev, void *stream);
 
 /* 1 if flexconv_fwd / flexconv_bwd run (Din,Dout) on the matrix-core kernels: the tiled widths 32->32, 64->64,
- * 128->128, 9->64, 64->9, 32->64, 64->32, 64->128, 128->64, and every pair of multiples of 128 (run as passes over
- * 64- / 128-channel column blocks; the deeper stages of the network of Sec. 4.3, whose feature length doubles from
- * stage to stage).  2: any other widths, which run zero-padded at the nearest widths of that list (padded copies
- * of the tensors live in the workspace, whose size flexconv_workspace_bytes reports).  0: the direct-form kernels
- * (orders of magnitude slower; only with padding or block passes switched off in the environment). */
+ * 128->128, 9->64, 64->9, 32->64, 64->32, 64->128, 128->64, and every pair of multiples of 128 (run on 64-point tiles,
+ * input block by input block; the deeper stages of the network of Sec. 4.3, whose feature length doubles from
+ * stage to stage).  2: any other widths: forward and feature gradient on 64-point tiles as they are,
+ * parameter gradients zero-padded at the nearest widths of that list (the copies live in the workspace, whose size
+ * flexconv_workspace_bytes reports).  0: the direct-form kernels
+ * (orders of magnitude slower; only with padding or the wide path switched off in the environment). */
 int flexconv_has_fast_path(int Din, int Dout);
 
 /* Which kernel family a flexconv_fwd (op = FLEX_OP_CONV_FWD) or the feature gradient of a flexconv_bwd
  * (op = FLEX_OP_CONV_BWD) call of these sizes runs on; -1 on bad sizes.  A host-side query (nothing is launched) of
  * the same decision the entry points dispatch on, so that the size limits of every family (32-bit byte offsets
- * inside a cloud for the lean kernels and the block passes) can be checked without running a cloud that large. */
+ * inside a cloud for the lean and the tile kernels) can be checked without running a cloud that large. */
 typedef enum {
     FLEX_ROUTE_DIRECT = 0,     /* direct-form kernels (Eq. 6 per neighbour, channel pair) */
     FLEX_ROUTE_SINGLE_ROLE = 1,/* tiled kernels, every wave gathers then contracts (fp32 matrix op) */
     FLEX_ROUTE_STAGED = 2,     /* wave-specialised kernels with LDS-staged producers */
     FLEX_ROUTE_LEAN = 3,       /* wave-specialised kernels with lean producers (the headline path) */
-    FLEX_ROUTE_SPLIT128 = 4,   /* 128 -> 128 point-major as two passes of the 64-wide lean kernels */
-    FLEX_ROUTE_WIDE = 5,       /* block passes over 64- / 128-channel column blocks */
-    FLEX_ROUTE_PADDED = 6,     /* zero-padded to the nearest widths with a matrix-core path */
+    FLEX_ROUTE_SPLIT128 = 4,   /* 128 -> 128 point-major: 64-point tile kernels */
+    FLEX_ROUTE_WIDE = 5,       /* other widths that are multiples of 128: 64-point tile kernels */
+    FLEX_ROUTE_PADDED = 6,     /* widths outside the list: tile kernels, parameter gradients zero-padded */
     FLEX_ROUTE_LEAN_FUSED = 7  /* flexconv_bwd only: lean kernels, and when grad_feat and grad_theta / grad_bias are
                                   all asked for, ONE kernel makes one pass over the in-edge lists for all of them
                                   (64 -> 64 layers); a call for a subset runs the FLEX_ROUTE_LEAN kernels */

@@ -615,6 +615,6 @@ def flex_calibrate_mfma_f16(iters, sink):
 
 
 def has_fast_path(Din, Dout):
-    """True if flexconv_fwd / flexconv_bwd run these widths on the matrix-core kernels (natively, as block passes or
+    """True if flexconv_fwd / flexconv_bwd run these widths on the matrix-core kernels (natively, on 64-point tiles or
     zero-padded) rather than on the direct-form kernels."""
     return bool(lib().flexconv_has_fast_path(int(Din), int(Dout)))

@@ -129,9 +129,8 @@ int lean_producer_mode()
 
 // Wide layers (both widths multiples of 128): the paper's network doubles the feature length at every resolution
 // stage while the point count drops by four (Sec. 4.3), so its deeper stages are of this kind.  They run on the 64-point
-// tile kernels (forward, feature gradient) and, for the parameter gradients, on 64 -> 64 lean kernels over column blocks
-// of the point-major tensors (FLEX_SPLIT=0 in the environment keeps 128 -> 128 on the single-pass fp32 kernels and the
-// wider ones on the direct form, for comparisons).
+// tile kernels, the parameter gradients block by block over columns of the point-major tensors (FLEX_SPLIT=0 in the
+// environment keeps 128 -> 128 on the single-pass fp32 kernels and the wider ones on the direct form, for comparisons).
 static bool split_disabled()
 {
     static const bool off = [] { const char *v = getenv("FLEX_SPLIT"); return v != nullptr && v[0] == '0'; }();
@@ -305,7 +304,7 @@ struct BwdPlan {
     size_t thetaP, featT, gT, partials, order, flag, in_off, in_src, inedge_ws, total;
 };
 
-// The route (block passes of the wide path / single-pass tiled kernels / direct form) is decided here, once, from
+// The route (tile kernels of the wide path / single-pass tiled kernels / direct form) is decided here, once, from
 // everything it depends on (sizes, layout, environment switches); the entry points dispatch on the plan's flags
 // and never re-decide, so what they write is what the plan reserved.
 static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layout)
@@ -515,7 +514,7 @@ int flexconv_has_fast_path(int Din, int Dout)
     return padded_shape(Din, Dout, &a, &b) ? 2 : 0;
 }
 
-// the block passes' name in the route query: 128 -> 128 point-major has one of its own
+// the wide path's name in the route query: 128 -> 128 point-major has one of its own
 static int wide_route(int Din, int Dout, int layout)
 {
     return Din == 128 && Dout == 128 && layout == FLEX_LAYOUT_BNC ? FLEX_ROUTE_SPLIT128 : FLEX_ROUTE_WIDE;

@@ -175,8 +175,9 @@ __global__ __launch_bounds__(256) void knn_fill_kernel(const float *__restrict__
 // (d2, id) as one number whose order is theirs: the bits of d2 (non-negative: they order like the value) above those
 // of id, read as a double -- positive, and finite since a float's exponent field fills only the upper bits of a
 // double's -- so that the sorted insertion is a minimum and a maximum per place.  (Double arithmetic keeps denormals
-// here, which the pairs with d2 == 0 are.)
-__device__ __forceinline__ double knn_key(float d2, int id) { return __hiloint2double(__float_as_int(d2), id); }
+// here, which the pairs with d2 == 0 are.)  A NaN distance keeps its operand's sign, and with the sign bit set it would be
+// the smallest key of all: without it, it is larger than that of any distance, or no number, and never taken.
+__device__ __forceinline__ double knn_key(float d2, int id) { return __hiloint2double(__float_as_int(d2) & 0x7fffffff, id); }
 
 // One thread per point, in cell order (neighbouring threads search neighbouring cells); lists[record][K].
 // What bounds it is the chain offsets -> records of one thread.  So the nine rows of cells of the first block (three

@@ -50,6 +50,19 @@ def test_knn_degenerate_shapes():
         _check(pos, K)
 
 
+@pytest.mark.parametrize("bits", [0x7fc00000, 0xffc00000])
+def test_knn_location_that_is_no_number(bits):
+    """A point without a location is nobody's neighbour, whichever sign its NaN has: the other points' lists are those
+    of the cloud without it."""
+    N, K, lost = 600, 8, 77
+    pos = np.random.default_rng(5).random((1, 3, N)).astype(np.float32)
+    keep = np.delete(np.arange(N, dtype=np.int32), lost)
+    ref = keep[oracle.knn(np.ascontiguousarray(pos[:, :, keep]), K)]
+    pos[0, 1, lost] = np.array(bits, np.uint32).view(np.float32)
+    got = fx.flex_knn(dev(pos), K).cpu().numpy()[:, :, keep]
+    assert np.array_equal(got, ref)
+
+
 def test_knn_room_cloud_matches_and_feeds_the_layers():
     """Room surfaces (the workload's geometry), 30k points: equal to the exhaustive search, and the tensor is a valid
     input of the other entry points."""
