@@ -39,6 +39,7 @@ def _jobs():
         jobs.append((os.path.join(CSRC, name + ".hip"), os.path.join(OBJ, name + ".o"), []))
     for csr in (0, 1):
         jobs.append((os.path.join(CSRC, "flex_tile.hip"), os.path.join(OBJ, f"flex_tile_{csr}.o"), [f"-DFLEX_TILE_CSR={csr}"]))
+        jobs.append((os.path.join(CSRC, "flex_narrow.hip"), os.path.join(OBJ, f"flex_narrow_{csr}.o"), [f"-DFLEX_NARROW_CSR={csr}"]))
     for (di, do, w, t, occ, ws) in shapes():
         jobs.append((os.path.join(CSRC, "flex_tiled_inst.hip"),
                      os.path.join(OBJ, f"flex_tiled_{di}_{do}.o"),

@@ -44,6 +44,9 @@ hipError_t launch_tile_0(const TileArgs &a, int outw, int grid, hipStream_t s);
 hipError_t launch_tile_1(const TileArgs &a, int outw, int grid, hipStream_t s);
 hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int gst, int n_hi, int n_ho, float *partials,
                                   hipStream_t s);
+// rows of at most 16 channels, one point per lane (flex_narrow.hip)
+hipError_t launch_narrow_0(const TileArgs &a, int grid, hipStream_t s);
+hipError_t launch_narrow_1(const TileArgs &a, int grid, hipStream_t s);
 
 bool gather_contract_supported(int DI, int DO)
 {
@@ -293,6 +296,38 @@ static hipError_t tile_launch(const TilePlan &p, const float *rows, int rs, int 
     return off != nullptr ? launch_tile_1(a, p.outw, grid, s) : launch_tile_0(a, p.outw, grid, s);
 }
 
+// ---- rows of at most 16 channels ----------------------------------------------------------
+// rs: row stride.  NARROW_RULE
+static bool use_narrow(int64_t N, int w_in, int rs) { return w_in <= 16 && tile_ok(N, rs); }
+static int narrow_rp(int w_in) { return w_in <= 8 ? 8 : 16; }
+static int narrow_blocks(int w_out) { return (w_out + 63) / 64; }
+static size_t narrow_bytes(int w_out) { return (size_t)narrow_blocks(w_out) * theta_f16_bytes(16, 64); }
+
+static hipError_t narrow_launch(const float *rows, int rs, int w_in, const float *pos, const int32_t *nbr,
+                                const int32_t *off, const int32_t *src, const int32_t *order, const void *theta,
+                                float *out, int w_out, int out_bcn, int B, int N, int K, hipStream_t s)
+{
+    const int rp = narrow_rp(w_in), n_out = narrow_blocks(w_out);
+    TileArgs a{};
+    a.rows = rows; a.pos = pos; a.nbr = nbr; a.off = off; a.src = src; a.order = order;
+    a.theta = (const char *)theta; a.out = out;
+    a.out_c = out_bcn ? N : 1; a.out_l = out_bcn ? 1 : w_out; a.out_b = (int64_t)N * w_out;
+    a.rs = rs; a.w_in = w_in; a.w_out = w_out;
+    a.blk_bytes = (int)theta_f16_bytes(rp, 64);
+    a.exp_off = (int)theta_f16_exp_offset(rp, 64);
+    a.rs_off = (int)theta_f16_rscale_offset(rp, 64);
+    a.N = N; a.K = K; a.tpc = (N + 63) / 64; a.n_in = 1;
+    const int64_t total = (int64_t)B * a.tpc;
+    if (total > 0x7fffffff) return hipErrorInvalidValue;
+    a.total = (int)total;
+    // eight one-wave workgroups per CU are what its registers and LDS hold; multiples of 8 per output block (XCDs)
+    int64_t chunks = (int64_t)device_cu_count() * 8 / n_out;
+    if (total < chunks) chunks = total;
+    a.chunks = (int)(chunks >= 8 ? (chunks + 7) / 8 * 8 : (chunks > 1 ? chunks : 1));
+    const int grid = n_out * a.chunks;
+    return off != nullptr ? launch_narrow_1(a, grid, s) : launch_narrow_0(a, grid, s);
+}
+
 // ---- workspace plans -----------------------------------------------------------
 struct FwdPlan {
     bool tiled, wide;
@@ -315,7 +350,7 @@ static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     size_t at = 0;
     if (p.tiled || p.wide) {
         size_t packed = p.wide ? 0 : theta_ws_bytes(Din, Dout);
-        if (tile_ok(N, Din)) packed = std::max(packed, tile_bytes(tile_plan(B, N, Din, Dout)));
+        if (tile_ok(N, Din)) packed = std::max({packed, tile_bytes(tile_plan(B, N, Din, Dout)), narrow_bytes(Dout)});
         p.thetaP = at; at += packed;
         if (layout == FLEX_LAYOUT_BCN) { p.featT = at; at += align256(sizeof(float) * (size_t)(B * N) * Din); }
     }
@@ -331,7 +366,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     size_t at = 0;
     if (p.tiled || p.wide) {
         size_t packed = p.wide ? 0 : theta_ws_bytes(Dout, Din);
-        if (tile_ok(N, Dout)) packed = std::max(packed, tile_bytes(tile_plan(B, N, Dout, Din)));
+        if (tile_ok(N, Dout)) packed = std::max({packed, tile_bytes(tile_plan(B, N, Dout, Din)), narrow_bytes(Din)});
         p.thetaP = at; at += packed;
         if (layout == FLEX_LAYOUT_BCN) {
             p.featT = at; at += align256(sizeof(float) * (size_t)(B * N) * Din);
@@ -588,6 +623,17 @@ int flexconv_fwd(const float *feat, const float *pos, const int32_t *nbr, const 
     void *thetaP = sub + p.thetaP;
     PrepList prep;
     const float *rows = feat;
+    if (use_narrow(N, Din, Dki)) {
+        if (bcn) {
+            float *copy = (float *)(padded ? ws + pp.featP : sub + p.featT);
+            prep.copy(feat, copy, B, N, Din, Din, 1, 0);
+            rows = copy;
+        }
+        prep.pack_theta(theta, bias, thetaP, Din, Dout, narrow_rp(Din), 64, 1, narrow_blocks(Dout), 0);
+        FLEX_HIP(prep.launch(s));
+        FLEX_HIP(narrow_launch(rows, Din, Din, pos, nbr, nullptr, nullptr, nullptr, thetaP, out, Dout, bcn, B, N, K, s));
+        return FLEX_OK;
+    }
     if (use_tile(N, Dki, padded)) {
         // rows of any width as they are; only channel-major ones have to be turned round
         const TilePlan ph = tile_plan(B, N, Dki, Dko);
@@ -715,10 +761,11 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
     int32_t *order = (int32_t *)(sub + p.order);
     int *control = (int *)(sub + p.flag);
     const bool fused = p.fused && grad_theta && grad_feat;
-    const bool tile = !fused && grad_feat && use_tile(N, Dko, padded);
+    const bool narrow = grad_feat && use_narrow(N, Dout, Dko);
+    const bool tile = !fused && !narrow && grad_feat && use_tile(N, Dko, padded);
     TilePlan ph{};
     if (tile) ph = tile_plan(B, N, Dko, Dki);
-    const int fmt = tile ? 1 : gather_contract_theta_format(Dko, Dki, N, K, 1);
+    const int fmt = tile || narrow ? 1 : gather_contract_theta_format(Dko, Dki, N, K, 1);
     PrepList prep;
     const float *rows = feat, *g_rows = grad_out;
     if (padded || bcn) {
@@ -729,14 +776,15 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
         rows = f_copy;
     }
     if (grad_feat) {
-        if (tile) tile_pack(prep, ph, theta, bias, thetaP, Din, Dout, 1);
+        if (narrow) prep.pack_theta(theta, bias, thetaP, Din, Dout, narrow_rp(Dout), 64, 1, narrow_blocks(Din), 1);
+        else if (tile) tile_pack(prep, ph, theta, bias, thetaP, Din, Dout, 1);
         else if (fmt) prep.pack_theta(theta, bias, thetaP, Din, Dout, pad4(Dko), pad16(Dki), 1, 1, 1);
         else FLEX_HIP(launch_pack_theta(theta, bias, (float *)thetaP, Din, Dout, pad4(Dko), pad16(Dki), 1, s));
         prep.order(in_off, B, N, order);
     }
     if (fused) prep.clear(control, FUSED_FLAG_INTS);
     FLEX_HIP(prep.launch(s));
-    float *dst = padded && !tile ? (float *)(ws + pp.gfP) : grad_feat;
+    float *dst = padded && !tile && !narrow ? (float *)(ws + pp.gfP) : grad_feat;
     const int out_bcn = bcn && !padded;
     if (fused) {
         int n_wg = 0;
@@ -755,7 +803,10 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
         else if (grad_theta)
             FLEX_HIP(launch_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, Dki, Dko, Din,
                                        Dout, s));
-        if (tile)
+        if (narrow)
+            FLEX_HIP(narrow_launch(g_rows, Dko, Dout, pos, nullptr, in_off, in_src, order, thetaP, grad_feat, Din, bcn, B, N,
+                                   K, s));
+        else if (tile)
             FLEX_HIP(tile_launch(ph, g_rows, Dko, std::max(Dout, 4), pos, nullptr, in_off, in_src, order, thetaP,
                                   grad_feat, Din, bcn, B, N, K, s));
         else if (grad_feat)

@@ -499,6 +499,7 @@ void tile_conv_kernel(const TileArgs a)
     }
 }
 
+#if defined(FLEX_TILE_CSR) && FLEX_TILE_CSR == 0     // one object holds it
 // ---------------------------------------------------------------------------
 // Parameter gradients of wide layers on 64-point tiles: partial[kd][o] = sum over the workgroup's points of A[pt][kd] g[pt][o]
 // for one block of 64 feature channels (kd = j*64 + c) and 64 output channels.
@@ -638,5 +639,6 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
             for (int i = 0; i < 4; ++i) dst[(int64_t)((wm + 4 * c) * 16 + 4 * q + i) * OC + (wn + 2 * n) * 16 + r16] = sum[i];
         }
 }
+#endif
 
 }  // namespace flex
