@@ -108,7 +108,10 @@ void narrow_conv_kernel(const TileArgs a)
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const float sg = CSR ? -1.f : 1.f;                       // CSR: point - listing centre
-                const float d0 = sg * (p[u][0] - c[0]), d1 = sg * (p[u][1] - c[1]), d2 = sg * (p[u][2] - c[2]);
+                // a slot without an entry weighs its zeros with zero, wherever the point lies
+                const bool has = e0 + u < deg;
+                const float d0 = has ? sg * (p[u][0] - c[0]) : 0.f, d1 = has ? sg * (p[u][1] - c[1]) : 0.f,
+                            d2 = has ? sg * (p[u][2] - c[2]) : 0.f;
 #pragma unroll
                 for (int i = 0; i < W; ++i) {
                     acc[0][i] = fmaf(d0, f[u][i], acc[0][i]);

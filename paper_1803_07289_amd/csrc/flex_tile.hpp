@@ -176,8 +176,9 @@ __device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedu
     };
     auto publish = [&](int buf, int id, bool has, const Positions &p) {
         const float sg = CSR ? -1.f : 1.f;          // CSR: point - listing centre
+        // a slot without an entry weighs its zeros with zero, wherever the point lies (it may lie at infinity or nowhere)
         *reinterpret_cast<v4f *>(ent[buf][lane]) =
-            v4f{sg * (p.n[0] - p.c[0]), sg * (p.n[1] - p.c[1]), sg * (p.n[2] - p.c[2]),
+            v4f{has ? sg * (p.n[0] - p.c[0]) : 0.f, has ? sg * (p.n[1] - p.c[1]) : 0.f, has ? sg * (p.n[2] - p.c[2]) : 0.f,
                 __uint_as_float(has ? (unsigned)id * (4u * (unsigned)a.rs) : 0u - 4u * (unsigned)a.rs)};
         wave_lds_sync();
     };

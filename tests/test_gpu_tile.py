@@ -66,3 +66,24 @@ def test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout):
             rt[d] += ((p[d][nbr[b]] - p[d])[:, :, None] * rows).sum(axis=0).T @ up.T
         rb += rows.sum(axis=0).T @ up.T
     assert rel_err(gt.cpu().numpy(), rt) <= TOL and rel_err(gb.cpu().numpy(), rb) <= TOL
+
+
+@pytest.mark.parametrize("Din,Dout", [(64, 13), (64, 9), (128, 128), (70, 90), (64, 64)])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_unlisted_point_without_a_location_has_no_gradient(Din, Dout, bad):
+    """A point that no centre lists gets a zero feature gradient also where its own location is no number."""
+    B, N, K, at, to = 1, 150, 7, 20, 3
+    say(f"tile: unlisted point at {bad}, {Din}->{Dout}")
+    pos, nbr, feat, theta, bias, g = random_problem(90, B, N, K, Din, Dout)
+    nbr[nbr == at] = at + 1
+    nbr[:, :, at] = to                       # it lists point 3 only, whose gradient is no number then
+    ref, _, _ = oracle.flexconv_bwd(feat, pos, nbr, theta, bias, g)
+    pos[:, :, at] = bad
+    edges = fx.flex_inedges_build(dev(nbr))
+    gf, _, _ = fx.flexconv_bwd(to_layout(feat, fx.BNC), dev(pos), dev(nbr), dev(theta), dev(bias), to_layout(g, fx.BNC),
+                               layout=fx.BNC, in_edges=edges, need_params=False)
+    torch.cuda.synchronize()
+    gf = from_layout(gf, fx.BNC)
+    assert (np.asarray(gf)[:, :, at] == 0).all()
+    rest = np.arange(N) != to
+    assert rel_err(np.asarray(gf)[:, :, rest], ref[:, :, rest]) <= TOL
