@@ -297,7 +297,12 @@ static hipError_t tile_launch(const TilePlan &p, const float *rows, int rs, int 
 }
 
 // ---- rows of at most 16 channels ----------------------------------------------------------
-// rs: row stride.  NARROW_RULE
+// rs: row stride.  Up to 16 channels, because there a lane per point was never the slower form and beyond it the 4 W sums
+// of a point do not fit a lane's registers.  us, forward / feature gradient (the wider sums in the other direction), on the
+// kernels these layers took before -> here: 1M points, K = 8: 3 and 32 channels 264 / 329 -> 59 / 171, 9 and 64
+// 169 / 308 -> 151 / 178, 16 and 64 219 / 339 -> 176 / 286; 100k points, K = 16: 9 and 64 35 / 58 -> 26 / 37, 16 and 64
+// 45 / 66 -> 30 / 56; 1k to 16k points, where a call is its launches: 17 / 19 -> 16 / 18 (16 channels backward 18 to 20
+// either way).
 static bool use_narrow(int64_t N, int w_in, int rs) { return w_in <= 16 && tile_ok(N, rs); }
 static int narrow_rp(int w_in) { return w_in <= 8 ? 8 : 16; }
 static int narrow_blocks(int w_out) { return (w_out + 63) / 64; }
@@ -761,7 +766,7 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
     int32_t *order = (int32_t *)(sub + p.order);
     int *control = (int *)(sub + p.flag);
     const bool fused = p.fused && grad_theta && grad_feat;
-    const bool narrow = grad_feat && use_narrow(N, Dout, Dko);
+    const bool narrow = !fused && grad_feat && use_narrow(N, Dout, Dko);
     const bool tile = !fused && !narrow && grad_feat && use_tile(N, Dko, padded);
     TilePlan ph{};
     if (tile) ph = tile_plan(B, N, Dko, Dki);
