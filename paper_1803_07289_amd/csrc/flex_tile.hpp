@@ -311,7 +311,6 @@ void tile_conv_kernel(const TileArgs a)
         static_assert(P::PASSES == 2 && P::G == 4, "two passes of four points");
         const int t = lane % P::LPR, grp = lane / P::LPR, first = 8 * wave;
         const bool ragged = a.w_in % IC != 0;
-        int ex_run[2] = {0, 0};
         int m_buf = 0;                                  // tile buffer of the tile being gathered
         gather_steps<CSR>(a, sc, tiles, first, 0, s_ent[wave], [&](v4f (&acc)[2][4], int step_ib, int point) __attribute__((always_inline)) {
             // ---- park ----
@@ -342,11 +341,7 @@ void tile_conv_kernel(const TileArgs a)
                     }
                 }
                 m = group_max<P::LPR>(m);
-                int ex = 15 - __builtin_amdgcn_frexp_expf(m);
-                if constexpr (MULTI) {     // one exponent per point over all input blocks so far, see the contraction
-                    ex = ib > 0 ? min(ex, ex_run[p]) : ex;
-                    ex_run[p] = ex;
-                }
+                const int ex = 15 - __builtin_amdgcn_frexp_expf(m);
                 const int pt = first + 4 * p + grp;
                 char *row = s_A[m_buf] + pt * P::ARS + 8 * t;
 #pragma unroll
@@ -375,127 +370,112 @@ void tile_conv_kernel(const TileArgs a)
     }
 
     // ---- contract ----
-    constexpr bool RESIDENT = !MULTI && NSW == 1;       // one block of parameters, 64 registers: kept
+    // An input block's product stands by itself: its own exponents per point and column, and two chains per accumulator
+    // block, hi*hi and the cross terms.  What is added up over the input blocks is the unscaled fp32 result, on the vector
+    // ALU, which rounds to nearest.  (The matrix op rounds every partial sum down: one chain over all products and blocks
+    // was 1.2e-7 off at one input block, 2.2e-7 at two, 3.3e-7 at four and 4.8e-7 at eight, where this is 1.1e-7 to
+    // 1.3e-7, in the same time but for 512 -> 512, 2 percent; and one scale for all blocks costs a block its bits next to
+    // a larger one.)
+    constexpr bool RESIDENT = !MULTI && WM == 2;        // parameters of one block, 64 registers: kept
     const int cw = wave - 8, q = lane >> 4, r16 = lane & 15;
     const int wm = cw % WM, wn = cw / WM;
     constexpr int PART = (P::OUTW / 16) * P::KS * 64 * 16;
-    constexpr int AHEAD = RESIDENT ? P::KS : NSW == 1 ? 4 : 2;     // depth steps whose parameters are held
-    h8 tH[AHEAD][NSW], tL[AHEAD][NSW];
-    // Sums over several input blocks stay in the accumulators.  They carry the scale 2^(e + ec) of the block being added
-    // (e: the tile row's exponent, the smallest of the point's so far, so that adding a block never pushes the sums up;
-    // ec: the column's exponent in the packed block), and are moved -- exactly -- to the next block's before it is added.
-    v4f cc[P::MB][NSW];
-    int e_now[P::MB];
-    v4i ec_now[NSW];
+    constexpr int STEPS = NSW * P::KS;                  // (slice, depth step) pairs of a tile and input block
+    constexpr int AHEAD = RESIDENT ? STEPS : MULTI && NSW == 2 ? 2 : 4;     // pairs whose parameters are held, as the registers allow
+    h8 tH[AHEAD], tL[AHEAD];
+    v4f sum[P::MB][NSW];                                // MULTI: the result over the input blocks so far
     const char *blk = theta_j;
     unsigned th_off = (unsigned)((wn * NSW) * P::KS * 64 + lane) * 16u;
-    auto load_theta = [&](int st, int n) __attribute__((always_inline)) {
-        tH[st % AHEAD][n] = *reinterpret_cast<const h8 *>(blk + (n * P::KS + st) * 1024 + th_off);
-        tL[st % AHEAD][n] = *reinterpret_cast<const h8 *>(blk + PART + (n * P::KS + st) * 1024 + th_off);
+    auto load_theta = [&](int i) __attribute__((always_inline)) {       // slice i / KS, depth step i % KS
+        tH[i % AHEAD] = *reinterpret_cast<const h8 *>(blk + i * 1024 + th_off);
+        tL[i % AHEAD] = *reinterpret_cast<const h8 *>(blk + PART + i * 1024 + th_off);
     };
     if constexpr (RESIDENT) {
 #pragma unroll
-        for (int st = 0; st < P::KS; ++st) load_theta(st, 0);
+        for (int i = 0; i < STEPS; ++i) load_theta(i);
     }
     TileWalk tw(sc, a.tpc);
     int ib = 0;
     for (int k = 0; k < tiles; ++k) {
         __syncthreads();                   // the tile is complete
         const int m_buf = k & 1, b = tw.b, l0 = tw.tic * 64;
-        {
-            // (the lane's offsets are formed anew for every tile: the compiler would otherwise read the parameters once
-            // and for all before the loop, and spill them)
-            unsigned a_off = (unsigned)((wm * P::MB * 16 + r16) * P::ARS + 16 * q);
-            int o_lane = wn * NSW * 16 + 4 * q, l_lane = wm * P::MB * 16 + r16;
-            asm volatile("" : "+v"(th_off), "+v"(a_off), "+v"(o_lane), "+v"(l_lane));
-            if constexpr (!RESIDENT) {
-                blk = theta_j + (int64_t)(MULTI ? ib : 0) * a.blk_bytes;
+        // (the lane's offsets are formed anew for every tile: the compiler would otherwise read the parameters once
+        // and for all before the loop, and spill them)
+        unsigned a_off = (unsigned)((wm * P::MB * 16 + r16) * P::ARS + 16 * q);
+        int o_lane = wn * NSW * 16 + 4 * q, l_lane = wm * P::MB * 16 + r16;
+        asm volatile("" : "+v"(th_off), "+v"(a_off), "+v"(o_lane), "+v"(l_lane));
+        if constexpr (!RESIDENT) {
+            blk = theta_j + (int64_t)(MULTI ? ib : 0) * a.blk_bytes;
 #pragma unroll
-                for (int st = 0; st < AHEAD; ++st)
+            for (int i = 0; i < AHEAD; ++i) load_theta(i);
+        }
+        const int *ecol = reinterpret_cast<const int *>(blk + a.exp_off) + o_lane;
+        const char *arow = s_A[m_buf] + a_off;
+        auto store = [&](int m, int n, const v4f &d) __attribute__((always_inline)) {
+            const int o = j * P::OUTW + 16 * n + o_lane, pt = m * 16 + l_lane;
+            if (l0 + pt >= a.N) return;
+            const int l = CSR ? s_P[m_buf][pt] : l0 + pt;
+            float *dst = a.out + b * a.out_b + l * a.out_l + o * a.out_c;
+            if (a.out_c == 1 && o + 3 < a.w_out) *reinterpret_cast<v4fu *>(dst) = d;
+            else {
 #pragma unroll
-                    for (int n = 0; n < NSW; ++n) load_theta(st, n);
+                for (int i = 0; i < 4; ++i)
+                    if (o + i < a.w_out) dst[i * a.out_c] = d[i];
             }
-            const int *ecol = reinterpret_cast<const int *>(blk + a.exp_off) + o_lane;
+        };
+        // One 16-channel slice after the other, two point blocks at a time, a depth step after the other; the fragments of
+        // the next two point blocks are read while the matrix ops of the current ones run.
+        constexpr int MH = (MULTI && NSW == 2) ? 1 : 2, HALVES = P::MB / MH, ITEMS = P::KS * HALVES;
+        h8 bh[2][MH], bl[2][MH];
+        auto load_b = [&](int item) __attribute__((always_inline)) {
+            const int st = item / HALVES % P::KS, m0 = item % HALVES * MH;
 #pragma unroll
-            for (int n = 0; n < NSW; ++n) {
-                const v4i ec = *reinterpret_cast<const v4i *>(ecol + 16 * n);
-#pragma unroll
-                for (int m = 0; m < P::MB; ++m) {
-                    const int e = s_E[m_buf][m * 16 + l_lane];
-                    if (MULTI && ib > 0) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) cc[m][n][i] = __builtin_ldexpf(cc[m][n][i], (e - e_now[m]) + (ec[i] - ec_now[n][i]));
-                    } else {
-                        cc[m][n] = v4f{0.f, 0.f, 0.f, 0.f};
-                    }
-                    if (n == NSW - 1) e_now[m] = e;
-                }
-                ec_now[n] = ec;
+            for (int m = 0; m < MH; ++m) {
+                bh[item & 1][m] = *reinterpret_cast<const h8 *>(arow + (m0 + m) * 16 * P::ARS + 64 * st);
+                bl[item & 1][m] = *reinterpret_cast<const h8 *>(arow + (m0 + m) * 16 * P::ARS + 64 * st + 2 * P::KD);
             }
-            const char *arow = s_A[m_buf] + a_off;
-            // Two point blocks at a time, a depth step after the other; the fragments of the next two are read while the
-            // matrix ops of the current ones run.
-            constexpr int MH = 2, HALVES = P::MB / MH, ITEMS = P::KS * HALVES;
-            h8 bh[2][MH], bl[2][MH];
-            auto load_b = [&](int item) __attribute__((always_inline)) {
-                const int st = item / HALVES, m0 = item % HALVES * MH;
+        };
+        load_b(0);
 #pragma unroll
-                for (int m = 0; m < MH; ++m) {
-                    bh[item & 1][m] = *reinterpret_cast<const h8 *>(arow + (m0 + m) * 16 * P::ARS + 64 * st);
-                    bl[item & 1][m] = *reinterpret_cast<const h8 *>(arow + (m0 + m) * 16 * P::ARS + 64 * st + 2 * P::KD);
-                }
-            };
-            load_b(0);
+        for (int n = 0; n < NSW; ++n) {
+            v4f main[P::MB], cross[P::MB];
 #pragma unroll
-            for (int item = 0; item < ITEMS; ++item) {
-                const int st = item / HALVES, m0 = item % HALVES * MH;
-                if (item + 1 < ITEMS) load_b(item + 1);
+            for (int m = 0; m < P::MB; ++m) main[m] = cross[m] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                const int item = n * ITEMS + i, at = n * P::KS + i / HALVES, m0 = i % HALVES * MH;
+                if (item + 1 < NSW * ITEMS) load_b(item + 1);
                 __builtin_amdgcn_sched_barrier(0);
+                const h8 H = tH[at % AHEAD], L = tL[at % AHEAD];
 #pragma unroll
-                for (int n = 0; n < NSW; ++n) {
-                    const h8 L = tL[st % AHEAD][n];
+                for (int m = 0; m < MH; ++m) main[m0 + m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(H, bh[item & 1][m], main[m0 + m], 0, 0, 0);
 #pragma unroll
-                    for (int m = 0; m < MH; ++m) cc[m0 + m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(L, bh[item & 1][m], cc[m0 + m][n], 0, 0, 0);
-                }
+                for (int m = 0; m < MH; ++m) cross[m0 + m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(L, bh[item & 1][m], cross[m0 + m], 0, 0, 0);
 #pragma unroll
-                for (int n = 0; n < NSW; ++n) {
-                    const h8 H = tH[st % AHEAD][n];
-#pragma unroll
-                    for (int m = 0; m < MH; ++m) cc[m0 + m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(H, bl[item & 1][m], cc[m0 + m][n], 0, 0, 0);
-                }
-#pragma unroll
-                for (int n = 0; n < NSW; ++n) {
-                    const h8 H = tH[st % AHEAD][n];
-#pragma unroll
-                    for (int m = 0; m < MH; ++m) cc[m0 + m][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(H, bh[item & 1][m], cc[m0 + m][n], 0, 0, 0);
-                    if constexpr (!RESIDENT)
-                        if (m0 + MH == P::MB && st + AHEAD < P::KS) load_theta(st + AHEAD, n);     // into the registers just read
-                }
+                for (int m = 0; m < MH; ++m) cross[m0 + m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(H, bl[item & 1][m], cross[m0 + m], 0, 0, 0);
+                if constexpr (!RESIDENT)
+                    if (m0 + MH == P::MB && at + AHEAD < STEPS) load_theta(at + AHEAD);     // into the registers just read
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (MULTI && ib + 1 < a.n_in) { ++ib; continue; }
+            const v4i ec = *reinterpret_cast<const v4i *>(ecol + 16 * n);
 #pragma unroll
-            for (int n = 0; n < NSW; ++n) {
-                const int o = j * P::OUTW + 16 * n + o_lane;
+            for (int m = 0; m < P::MB; ++m) {
+                const int e = s_E[m_buf][m * 16 + l_lane];
+                v4f d = main[m] + cross[m];
 #pragma unroll
-                for (int m = 0; m < P::MB; ++m) {
-                    const int pt = m * 16 + l_lane;
-                    v4f d = cc[m][n];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) d[i] = __builtin_ldexpf(d[i], -(e_now[m] + ec_now[n][i]));
-                    if (l0 + pt >= a.N) continue;
-                    const int l = CSR ? s_P[m_buf][pt] : l0 + pt;
-                    float *dst = a.out + b * a.out_b + l * a.out_l + o * a.out_c;
-                    if (a.out_c == 1 && o + 3 < a.w_out) *reinterpret_cast<v4fu *>(dst) = d;
-                    else {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (o + i < a.w_out) dst[i * a.out_c] = d[i];
-                    }
-                }
+                for (int i = 0; i < 4; ++i) d[i] = __builtin_ldexpf(d[i], -(e + ec[i]));
+                if constexpr (MULTI) sum[m][n] = ib == 0 ? d : sum[m][n] + d;
+                else store(m, n, d);
             }
         }
-        ib = 0;
+        if constexpr (MULTI) {
+            if (++ib < a.n_in) continue;
+            ib = 0;
+#pragma unroll
+            for (int n = 0; n < NSW; ++n)
+#pragma unroll
+                for (int m = 0; m < P::MB; ++m) store(m, n, sum[m][n]);
+        }
         tw.next();
     }
 }

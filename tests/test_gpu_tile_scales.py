@@ -1,0 +1,74 @@
+"""Wide gathers (more than one block of 64 input channels) where the blocks differ in scale: a block that is zero, groups of
+channels far apart in magnitude, and the rounding of the sum over the blocks.  A block's share of the result may cost
+bits only next to what it is added to, not next to what the point has in other blocks."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1803_07289_amd as fx
+from gpu_util import TOL, dev, to_layout, from_layout, say
+from test_gpu_dynamic_range import rel_err_per_channel
+from test_gpu_parity import random_problem
+
+pytestmark = pytest.mark.gpu
+
+
+def forward_and_feature_gradient(pos, nbr, feat, theta, bias, g, layout=fx.BNC):
+    a = (to_layout(feat, layout), dev(pos), dev(nbr), dev(theta), dev(bias))
+    out = fx.flexconv_fwd(*a, layout=layout)
+    gf, _, _ = fx.flexconv_bwd(*a, to_layout(g, layout), layout=layout, need_params=False)
+    torch.cuda.synchronize()
+    return from_layout(out, layout), from_layout(gf, layout)
+
+
+def check(pos, nbr, feat, theta, bias, g, layout=fx.BNC):
+    out, gf = forward_and_feature_gradient(pos, nbr, feat, theta, bias, g, layout)
+    rgf, _, _ = oracle.flexconv_bwd(feat, pos, nbr, theta, bias, g)
+    errs = (rel_err_per_channel(out, oracle.flexconv_fwd(feat, pos, nbr, theta, bias), 1), rel_err_per_channel(gf, rgf, 1))
+    say(f"  per-channel rel err: fwd {errs[0]:.2e} grad_feat {errs[1]:.2e}")
+    assert max(errs) <= TOL, errs
+
+
+@pytest.mark.parametrize("magnitude", [1.0, 1e-6, 1e-12])
+@pytest.mark.parametrize("zero", [0, 1, 2], ids=["first", "middle", "last"])
+@pytest.mark.parametrize("width,other", [(128, 64), (192, 192), (256, 128), (384, 256)])
+def test_a_block_of_zeros_costs_the_others_nothing(width, other, zero, magnitude):
+    blocks = (width + 63) // 64
+    at = {0: 0, 1: blocks // 2, 2: blocks - 1}[zero]
+    say(f"zero block {at} of {blocks}, {width}<->{other}, magnitude {magnitude}")
+    for Din, Dout in ((width, other), (other, width)):           # the forward pass, the feature gradient gather `width`
+        pos, nbr, feat, theta, bias, g = random_problem(60 + width + zero, 1, 150, 8, Din, Dout)
+        pos *= 0.02
+        wide = feat if Din == width else g
+        wide *= np.float32(magnitude)
+        wide[:, 64 * at:64 * at + 64] = 0
+        check(pos, nbr, feat, theta, bias, g)
+
+
+@pytest.mark.parametrize("second", [1e-8, 1e-16, 1e8, 1e16])
+@pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
+def test_groups_of_channels_keep_their_own_scale(second, layout):
+    """Two groups of 128 channels that do not meet (block-diagonal parameters), far apart in scale."""
+    say(f"groups, second at {second} of the first, layout={layout}")
+    C = 256
+    pos, nbr, feat, theta, bias, g = random_problem(77, 1, 200, 8, C, C)
+    theta[:, :128, 128:] = theta[:, 128:, :128] = bias[:128, 128:] = bias[128:, :128] = 0
+    feat[:, 128:] *= np.float32(second)
+    g[:, 128:] *= np.float32(second)
+    check(pos, nbr, feat, theta, bias, g, layout)
+
+
+@pytest.mark.parametrize("C", [64, 128, 512])
+def test_error_does_not_grow_with_the_input_blocks(C):
+    """2-norm error of ordinary data.  What every width has in common: eight fp32 sums per aggregate, 22-bit halves, and per
+    block eight partial sums that the matrix op rounds down by up to 2^-23, here 1.45e-7 together.  The blocks' results
+    are added to nearest, 2^-25 each at random: 1.57e-7 at eight.  The bound leaves a quarter; with all products of all
+    blocks in one chain of the matrix op's sums it was 2.7e-7 at two blocks and 5.1e-7 at eight."""
+    pos, nbr, feat, theta, bias, g = random_problem(5, 1, 400, 8, C, C)
+    out, gf = forward_and_feature_gradient(pos, nbr, feat, theta, bias, g)
+    ref = oracle.flexconv_fwd(feat, pos, nbr, theta, bias)
+    rgf, _, _ = oracle.flexconv_bwd(feat, pos, nbr, theta, bias, g)
+    errs = [float(np.linalg.norm(x - y) / np.linalg.norm(y)) for x, y in ((out, ref), (gf, rgf))]
+    say(f"{C}->{C}: 2-norm rel err fwd {errs[0]:.2e} grad_feat {errs[1]:.2e}")
+    assert max(errs) <= 2e-7, errs
