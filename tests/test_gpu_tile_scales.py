@@ -72,3 +72,31 @@ def test_error_does_not_grow_with_the_input_blocks(C):
     errs = [float(np.linalg.norm(x - y) / np.linalg.norm(y)) for x, y in ((out, ref), (gf, rgf))]
     say(f"{C}->{C}: 2-norm rel err fwd {errs[0]:.2e} grad_feat {errs[1]:.2e}")
     assert max(errs) <= 2e-7, errs
+
+
+@pytest.mark.parametrize("N,C,adds", [(500, 128, 2), (2000, 128, 2), (20_000, 128, 10), (40_000, 512, 128)])
+def test_error_of_the_parameter_gradients(N, C, adds):
+    """2-norm error of the sums over all points.  Terms carry three 8-bit pieces and 32 of them go through six sums of the
+    matrix op, which rounds down, with the sign of every second 32 turned round: with the aggregates' own rounding 1.0e-7,
+    taken as 1.2e-7.  The results are added to nearest: rms at most 2^-24 / sqrt(3) of the running total, whose square
+    grows with the additions, `adds` of them per total.  (Measured 1.0e-7, 1.0e-7, 1.1e-7, 2.2e-7; with chains of eight
+    steps of one sign 2.6e-7 and 3.2e-7 in the last two.)"""
+    bound = (1.2e-7 ** 2 + 2.0 ** -48 / 3 * adds / 2) ** 0.5
+    rng = np.random.default_rng(N + C)
+    pos = torch.from_numpy(rng.random((1, 3, N), dtype=np.float32)).cuda()
+    nbr = torch.from_numpy(((np.arange(N)[None, None] + rng.integers(-20, 21, size=(1, 8, N))) % N).astype(np.int32)).cuda()
+    feat, g = (torch.from_numpy(rng.standard_normal((1, N, C), dtype=np.float32)).cuda() for _ in range(2))
+    theta, bias = torch.zeros((3, C, C), device="cuda"), torch.zeros((C, C), device="cuda")
+    _, gt, gb = fx.flexconv_bwd(feat, pos, nbr, theta, bias, g, layout=fx.BNC, need_feat=False)
+    got = torch.cat([gt, gb[None]]).double().cpu().numpy()
+    p, n, f, up = pos[0].double().cpu(), nbr[0].long().cpu(), feat[0].double().cpu(), g[0].double().cpu()
+    agg = torch.zeros((4, N, C), dtype=torch.float64)
+    for k in range(8):
+        rows, dp = f[n[k]], p[:, n[k]] - p
+        for d in range(3):
+            agg[d] += dp[d][:, None] * rows
+        agg[3] += rows
+    ref = np.stack([(a.t() @ up).numpy() for a in agg])
+    err = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    say(f"{N} points {C}->{C}: 2-norm rel err of the parameter gradients {err:.2e}")
+    assert err <= bound, (err, bound)
