@@ -197,9 +197,7 @@ __device__ void pack_slice(const float *theta, const float *bias, char *thetaF_a
     if ((tid & 63) < 16) atomicMax(&s_ec[l16], __float_as_int(mc));
     __syncthreads();
     const float m = __int_as_float(s_ec[l16]);
-    // (at most 55: what the input blocks of a wide layer have in one column are brought to each other's scale while
-    // they are summed, within fp32's range; a column further down than 2^-40 of its rows still keeps its upper bits)
-    const int ec = m > 0.f ? min(15 - frexp_exp(m), 55) : 0;
+    const int ec = m > 0.f ? 15 - frexp_exp(m) : 0;
     if (tid < 16) reinterpret_cast<int *>(reinterpret_cast<char *>(thetaF) + p.exp_off)[col] = ec;
     const int per_part = NS * KS * 64 * 8;
 #pragma unroll

@@ -106,3 +106,24 @@ def test_first_layer_input_of_mixed_units(layout):
                 fwd_whole=rel_err(out, ref))
     say("  per-channel rel err: " + " ".join(f"{k} {v:.2e}" for k, v in errs.items()))
     assert max(errs.values()) <= TOL, errs
+
+
+@pytest.mark.parametrize("small", [1e-12, 1e-20, 1e-28])
+@pytest.mark.parametrize("Din,Dout", [(64, 64), (32, 32), (9, 64), (64, 13), (128, 128), (200, 96)])
+def test_a_column_far_below_its_rows(Din, Dout, small):
+    """An output channel (forward pass) or input channel (feature gradient) whose parameters are far below those of the other
+    channels: it has a scale of its own, however far."""
+    say(f"column at {small} of its rows, {Din}->{Dout}")
+    pos, nbr, feat, theta, bias, g = random_problem(500 + Din, 1, 200, 8, Din, Dout)
+    theta[:, :, 3] *= np.float32(small)
+    bias[:, 3] *= np.float32(small)
+    out, _, _, _ = run_all(pos, nbr, feat, theta, bias, g, fx.BNC)
+    fwd = rel_err_per_channel(out, oracle.flexconv_fwd(feat, pos, nbr, theta, bias), 1)
+    pos, nbr, feat, theta, bias, g = random_problem(501 + Din, 1, 200, 8, Din, Dout)
+    theta[:, 2] *= np.float32(small)
+    bias[2] *= np.float32(small)
+    _, gf, _, _ = run_all(pos, nbr, feat, theta, bias, g, fx.BNC)
+    rgf, _, _ = oracle.flexconv_bwd(feat, pos, nbr, theta, bias, g)
+    grad = rel_err_per_channel(gf, rgf, 1)
+    say(f"  per-channel rel err: fwd {fwd:.2e} grad_feat {grad:.2e}")
+    assert max(fwd, grad) <= TOL
