@@ -415,10 +415,18 @@ typedef enum {
     FLEX_ROUTE_LEAN = 3,       /* wave-specialised kernels with lean producers (the headline path) */
     FLEX_ROUTE_SPLIT128 = 4,   /* 128 -> 128 point-major: 64-point tile kernels */
     FLEX_ROUTE_WIDE = 5,       /* other widths that are multiples of 128: 64-point tile kernels */
-    FLEX_ROUTE_PADDED = 6,     /* widths outside the list: tile kernels, parameter gradients zero-padded */
-    FLEX_ROUTE_LEAN_FUSED = 7  /* flexconv_bwd only: lean kernels, and when grad_feat and grad_theta / grad_bias are
+    FLEX_ROUTE_PADDED = 6,     /* widths outside the list: the kernels of FLEX_ROUTE_NARROW (gathered rows of at most 16
+                                  channels) or FLEX_ROUTE_TILE at the tensors' own widths; parameter gradients on
+                                  zero-padded copies at the nearest listed widths */
+    FLEX_ROUTE_LEAN_FUSED = 7, /* flexconv_bwd only: lean kernels, and when grad_feat and grad_theta / grad_bias are
                                   all asked for, ONE kernel makes one pass over the in-edge lists for all of them
                                   (64 -> 64 layers); a call for a subset runs the FLEX_ROUTE_LEAN kernels */
+    FLEX_ROUTE_TILE = 8,       /* listed widths that gather more than 64 channels (128 -> 64 forward, the feature gradient
+                                  of 64 -> 128): 64-point tile kernels (f16 halves) */
+    FLEX_ROUTE_NARROW = 9,     /* listed widths that gather at most 16 channels (9 -> 64 forward, the feature gradient of
+                                  64 -> 9): one point per lane (f16 halves) */
+    FLEX_ROUTE_PADDED_COPIES = 10 /* widths outside the list past the tile kernels' 32-bit byte offsets: zero-padded copies
+                                  of features, upstream gradient and result at the nearest listed widths */
 } flex_route;
 int flexconv_kernel_route(int op, int B, int N, int K, int Din, int Dout, int layout);
 

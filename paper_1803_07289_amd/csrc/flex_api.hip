@@ -156,6 +156,9 @@ static bool wide_ok(int64_t N, int K, int Din, int Dout)
     return wide_shape(Din, Dout) && tile_ok(N, Din) && tile_ok(N, Dout) && (int64_t)K * N * 4 < (1ll << 32);
 }
 
+// Packed parameters of a wide layer, forward, as 64 x 128 blocks
+static size_t wide_packed_bytes(int Din, int Dout) { return (size_t)(Din / 64) * (Dout / 128) * theta_f16_bytes(64, 128); }
+
 // Parameter gradients of a wide layer: (Din/64) x (Dout/64) independent blocks of [4*64 x 64], two launches
 // (partial sums per block and workgroup, then their reduction in double).
 static size_t wide_partial_bytes(int B, int N, int Din, int Dout)
@@ -241,7 +244,9 @@ static hipError_t launch_grad_theta(const float *rows, const float *pos, const i
 // Do they?  Where the gathered rows are wider than the 64 channels that the wave-specialised kernels hold the parameters
 // of in registers (those would walk the cloud once per 64 channels: 128 -> 128, 1M points, forward 819 against 755 us,
 // feature gradient 965 against 809; 512 -> 512, 109k points, 1350 against 860 and 1580 against 860), and where those would
-// need zero-padded copies of the tensors (except rows of fewer than four channels, which have no lane to themselves).
+// need zero-padded copies of the tensors (K = 8, forward and feature gradient, copies against here: 50 -> 50, 4k points 37
+// and 43 against 22 and 20, 100k 88 and 121 against 40 and 58, 1M 600 and 867 against 270 and 407; 64 -> 13 forward, 4k,
+// 100k and 1M points 27, 63, 460 against 21, 36, 235; 20 -> 13 forward 27, 52, 323 against 20, 37, 218).
 static bool use_tile(int64_t N, int w_in, bool padded) { return tile_ok(N, w_in) && (w_in > 64 || padded); }
 
 struct TilePlan { int outw, n_in, n_out; };
@@ -264,12 +269,6 @@ static TilePlan tile_plan(int64_t B, int64_t N, int w_in, int w_out)
     return p;
 }
 static size_t tile_bytes(const TilePlan &p) { return (size_t)p.n_in * p.n_out * theta_f16_bytes(64, p.outw); }
-
-static void tile_pack(PrepList &prep, const TilePlan &p, const float *theta, const float *bias, void *thetaF, int Din,
-                       int Dout, int transpose)
-{
-    prep.pack_theta(theta, bias, thetaF, Din, Dout, 64, p.outw, p.n_in, p.n_out, transpose);
-}
 
 // rows [B*N, rs] (w_in channels used) onto out [B, N, w_out] or, out_bcn, [B, w_out, N]
 static hipError_t tile_launch(const TilePlan &p, const float *rows, int rs, int w_in, const float *pos,
@@ -306,7 +305,7 @@ static hipError_t tile_launch(const TilePlan &p, const float *rows, int rs, int 
 static bool use_narrow(int64_t N, int w_in, int rs) { return w_in <= 16 && tile_ok(N, rs); }
 static int narrow_rp(int w_in) { return w_in <= 8 ? 8 : 16; }
 static int narrow_blocks(int w_out) { return (w_out + 63) / 64; }
-static size_t narrow_bytes(int w_out) { return (size_t)narrow_blocks(w_out) * theta_f16_bytes(16, 64); }
+static size_t narrow_bytes(int w_in, int w_out) { return (size_t)narrow_blocks(w_out) * theta_f16_bytes(narrow_rp(w_in), 64); }
 
 static hipError_t narrow_launch(const float *rows, int rs, int w_in, const float *pos, const int32_t *nbr,
                                 const int32_t *off, const int32_t *src, const int32_t *order, const void *theta,
@@ -333,62 +332,172 @@ static hipError_t narrow_launch(const float *rows, int rs, int w_in, const float
     return off != nullptr ? launch_narrow_1(a, grid, s) : launch_narrow_0(a, grid, s);
 }
 
-// ---- workspace plans -----------------------------------------------------------
+// ---- plans -------------------------------------------------------------------------
+// The kernels of one gather (the forward pass; the feature gradient over in-edge lists): rows of w_in channels, rs floats
+// apart, onto w_out channels; (k_in, k_out): the listed widths that cover them.  Decided here, once, from everything it
+// depends on (sizes, environment switches); the entry points dispatch on it, the workspace and the route query follow it.
+struct GatherPlan {
+    int route;             // FLEX_ROUTE_NARROW, FLEX_ROUTE_TILE or what gather_contract_route answers
+    TilePlan tile;
+    int fmt;               // of the packed parameters (listed widths)
+    size_t packed;         // bytes of them
+    bool own_widths() const { return route == FLEX_ROUTE_NARROW || route == FLEX_ROUTE_TILE; }
+};
+static GatherPlan plan_gather(int64_t B, int64_t N, int K, int w_in, int w_out, int rs, int k_in, int k_out, bool padded,
+                              int csr)
+{
+    GatherPlan g{};
+    if (use_narrow(N, w_in, rs)) {
+        g.route = FLEX_ROUTE_NARROW;
+        g.packed = narrow_bytes(w_in, w_out);
+    } else if (use_tile(N, k_in, padded)) {
+        g.route = FLEX_ROUTE_TILE;
+        g.tile = tile_plan(B, N, k_in, k_out);
+        g.packed = tile_bytes(g.tile);
+    } else {
+        g.route = gather_contract_route(k_in, k_out, (int)N, K, csr);
+        g.fmt = gather_contract_theta_format(k_in, k_out, (int)N, K, csr);
+        g.packed = theta_ws_bytes(k_in, k_out);
+    }
+    return g;
+}
+
+// Packs the parameters the way the planned kernels want them (transpose: the feature gradient's direction).
+static hipError_t gather_pack(PrepList &prep, const GatherPlan &g, const float *theta, const float *bias, void *thetaP,
+                              int Din, int Dout, int k_in, int k_out, int transpose, hipStream_t s)
+{
+    const int w_in = transpose ? Dout : Din, w_out = transpose ? Din : Dout;
+    if (g.route == FLEX_ROUTE_NARROW)
+        prep.pack_theta(theta, bias, thetaP, Din, Dout, narrow_rp(w_in), 64, 1, narrow_blocks(w_out), transpose);
+    else if (g.route == FLEX_ROUTE_TILE)
+        prep.pack_theta(theta, bias, thetaP, Din, Dout, 64, g.tile.outw, g.tile.n_in, g.tile.n_out, transpose);
+    else if (g.fmt)
+        prep.pack_theta(theta, bias, thetaP, Din, Dout, pad4(k_in), pad16(k_out), 1, 1, transpose);
+    else
+        return launch_pack_theta(theta, bias, (float *)thetaP, Din, Dout, pad4(k_in), pad16(k_out), transpose, s);
+    return hipSuccess;
+}
+
+// rows [B*N, rs] onto out [B, N, w_out] or, out_bcn, [B, w_out, N]; on the listed widths' kernels rs = k_in, w_out = k_out
+static hipError_t gather_launch(const GatherPlan &g, const float *rows, int rs, int w_in, const float *pos,
+                                const int32_t *nbr, const int32_t *off, const int32_t *src, const int32_t *order,
+                                const void *thetaP, float *out, int w_out, int out_bcn, int B, int N, int K,
+                                hipStream_t s)
+{
+    if (g.route == FLEX_ROUTE_NARROW)
+        return narrow_launch(rows, rs, w_in, pos, nbr, off, src, order, thetaP, out, w_out, out_bcn, B, N, K, s);
+    if (g.route == FLEX_ROUTE_TILE)
+        return tile_launch(g.tile, rows, rs, w_in, pos, nbr, off, src, order, thetaP, out, w_out, out_bcn, B, N, K, s);
+    return launch_gather_contract(rows, pos, nbr, off, src, order, thetaP, g.fmt, out, B, N, K, rs, w_out, off != nullptr,
+                                  out_bcn, s);
+}
+
+static bool pad_disabled()
+{
+    static const bool off = [] { const char *v = getenv("FLEX_PAD"); return v != nullptr && v[0] == '0'; }();
+    return off;
+}
+
+// Widths with neither a tiled nor a wide path of their own (FLEX_PAD=0 in the environment keeps them on the direct-form
+// kernels, for comparisons): the nearest listed widths.  The parameter gradients run on zero-padded copies at those, and
+// so does a gather that the kernels for any width do not take: extra channels of the features / upstream gradient and
+// extra rows / columns of the parameters are zero, so they add nothing, and the results are the leading channels / the
+// leading block of what the padded layer returns.
+static bool padded_shape(int Din, int Dout, int *DIp, int *DOp)
+{
+    if (pad_disabled() || wide_shape(Din, Dout)) return false;
+    if (gather_contract_supported(Din, Dout) && gather_contract_supported(Dout, Din)) return false;
+    if (Din <= 128 && Dout <= 128) {
+        int64_t best = -1;
+#define FLEX_SHAPE(DI_, DO_, W, T, OCC, WS)                                                         \
+        if (DI_ >= Din && DO_ >= Dout && gather_contract_supported(DO_, DI_) &&                         \
+            (best < 0 || (int64_t)DI_ * DO_ < best)) {                                                  \
+            best = (int64_t)DI_ * DO_; *DIp = DI_; *DOp = DO_;                                          \
+        }
+#include "flex_shapes.def"
+#undef FLEX_SHAPE
+        return best > 0;
+    }
+    *DIp = (Din + 127) / 128 * 128;
+    *DOp = (Dout + 127) / 128 * 128;
+    return wide_shape(*DIp, *DOp);
+}
+
+static size_t rows_bytes(int64_t B, int64_t N, int width) { return align256(sizeof(float) * (size_t)(B * N) * width); }
+
 struct FwdPlan {
-    bool tiled, wide;
-    size_t thetaP, featT, total;         // byte offsets / total
+    bool direct, padded, wide;
+    int k_in, k_out;                     // the listed widths: the tensors' own unless padded
+    GatherPlan gather;
+    bool copy, copy_out;                 // rows are copied (turned round, padded); the result comes from a padded one
+    size_t thetaP, rows, out, total;     // byte offsets / total
 };
 struct BwdPlan {
-    bool tiled, wide;
+    bool direct, padded, wide;
+    int k_in, k_out;
+    GatherPlan gather;                   // of the feature gradient
+    bool copy, copy_out;
     bool fused;      // feature and parameter gradients, when both are asked for, come from the one-pass kernel
-    size_t thetaP, featT, gT, partials, order, flag, in_off, in_src, inedge_ws, total;
+    size_t thetaP, featT, gT, gfP, partials, order, flag, in_off, in_src, inedge_ws, total;
 };
 
-// The route (tile kernels of the wide path / single-pass tiled kernels / direct form) is decided here, once, from
-// everything it depends on (sizes, layout, environment switches); the entry points dispatch on the plan's flags
-// and never re-decide, so what they write is what the plan reserved.
 static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layout)
 {
     FwdPlan p{};
-    p.tiled = gather_contract_supported(Din, Dout);
-    p.wide = wide_ok(N, K, Din, Dout);
-    size_t at = 0;
-    if (p.tiled || p.wide) {
-        size_t packed = p.wide ? 0 : theta_ws_bytes(Din, Dout);
-        if (tile_ok(N, Din)) packed = std::max({packed, tile_bytes(tile_plan(B, N, Din, Dout)), narrow_bytes(Dout)});
-        p.thetaP = at; at += packed;
-        if (layout == FLEX_LAYOUT_BCN) { p.featT = at; at += align256(sizeof(float) * (size_t)(B * N) * Din); }
-    }
-    p.total = at > 0 ? at : 256;
+    p.k_in = Din; p.k_out = Dout;
+    p.padded = padded_shape(Din, Dout, &p.k_in, &p.k_out);
+    p.wide = wide_ok(N, K, p.k_in, p.k_out);
+    p.direct = !p.wide && !gather_contract_supported(p.k_in, p.k_out);
+    // What the listed widths' kernels ask for (copies of features, parameters and result, their own packed parameters) is
+    // what a call at padded widths is told to bring, whichever kernels it takes: the size, and with it what the static
+    // scratch of flexconv_fwd_noalloc takes, does not change where they hand over to one another.
+    const size_t copies = p.padded ? rows_bytes(B, N, p.k_in) + align256(sizeof(float) * (size_t)4 * p.k_in * p.k_out) +
+                                         rows_bytes(B, N, p.k_out) : 0;
+    p.total = copies + 256;
+    if (p.direct) return p;
+    const bool bcn = layout == FLEX_LAYOUT_BCN;
+    p.gather = plan_gather(B, N, K, Din, Dout, Din, p.k_in, p.k_out, p.padded, 0);
+    const bool own = p.gather.own_widths();
+    p.copy = bcn || (p.padded && !own);
+    p.copy_out = p.padded && !own;
+    size_t at = p.gather.packed;
+    if (p.copy) { p.rows = at; at += rows_bytes(B, N, own ? Din : p.k_in); }
+    if (p.copy_out) { p.out = at; at += rows_bytes(B, N, p.k_out); }
+    if (p.padded)
+        at = std::max(at, copies + (p.wide ? wide_packed_bytes(p.k_in, p.k_out) : theta_ws_bytes(p.k_in, p.k_out)));
+    p.total = at;
     return p;
 }
 
 static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layout, bool build)
 {
     BwdPlan p{};
-    p.tiled = gather_contract_supported(Din, Dout) && gather_contract_supported(Dout, Din);
-    p.wide = wide_ok(N, K, Din, Dout);
-    size_t at = 0;
-    if (p.tiled || p.wide) {
-        size_t packed = p.wide ? 0 : theta_ws_bytes(Dout, Din);
-        if (tile_ok(N, Dout)) packed = std::max({packed, tile_bytes(tile_plan(B, N, Dout, Din)), narrow_bytes(Din)});
-        p.thetaP = at; at += packed;
-        if (layout == FLEX_LAYOUT_BCN) {
-            p.featT = at; at += align256(sizeof(float) * (size_t)(B * N) * Din);
-            p.gT = at;    at += align256(sizeof(float) * (size_t)(B * N) * Dout);
-        }
-        p.partials = at;
-        at += p.wide ? wide_partial_bytes((int)B, (int)N, Din, Dout) : grad_theta_partial_bytes(B, N, Din, Dout);
-        p.order = at; at += inedges_order_bytes(B * N);      // walking order of the feature gradient's gather
-        p.fused = p.tiled && !p.wide && Din == 64 && Dout == 64 && bwd_fused_ok_64_64((int)N, K);
-        if (p.fused) { p.flag = at; at += align256(fused_control_bytes()); }   // the one-pass kernel's flag and records
-        if (build) {
-            p.in_off = at;    at += align256(sizeof(int32_t) * (size_t)(B * N + 1));
-            p.in_src = at;    at += align256(sizeof(int32_t) * (size_t)(B * N) * K);
-            p.inedge_ws = at; at += inedges_ws_bytes(B * N, K);
-        }
+    p.k_in = Din; p.k_out = Dout;
+    p.padded = padded_shape(Din, Dout, &p.k_in, &p.k_out);
+    p.wide = wide_ok(N, K, p.k_in, p.k_out);
+    p.direct = !p.wide && !(gather_contract_supported(p.k_in, p.k_out) && gather_contract_supported(p.k_out, p.k_in));
+    p.total = 256;
+    if (p.direct) return p;
+    p.gather = plan_gather(B, N, K, Dout, Din, p.k_out, p.k_out, p.k_in, p.padded, 1);
+    p.copy = p.padded || layout == FLEX_LAYOUT_BCN;          // the parameter gradients run at the listed widths
+    p.copy_out = p.padded && !p.gather.own_widths();
+    size_t at = p.gather.packed;
+    if (p.copy) {
+        p.featT = at; at += rows_bytes(B, N, p.k_in);
+        p.gT = at;    at += rows_bytes(B, N, p.k_out);
     }
-    p.total = at > 0 ? at : 256;
+    if (p.copy_out) { p.gfP = at; at += rows_bytes(B, N, p.k_in); }
+    p.partials = at;
+    at += p.wide ? wide_partial_bytes((int)B, (int)N, p.k_in, p.k_out) : grad_theta_partial_bytes(B, N, p.k_in, p.k_out);
+    p.order = at; at += inedges_order_bytes(B * N);          // walking order of the feature gradient's gather
+    p.fused = !p.padded && !p.wide && Din == 64 && Dout == 64 && bwd_fused_ok_64_64((int)N, K);
+    if (p.fused) { p.flag = at; at += align256(fused_control_bytes()); }   // the one-pass kernel's flag and records
+    if (build) {
+        p.in_off = at;    at += align256(sizeof(int32_t) * (size_t)(B * N + 1));
+        p.in_src = at;    at += align256(sizeof(int32_t) * (size_t)(B * N) * K);
+        p.inedge_ws = at; at += inedges_ws_bytes(B * N, K);
+    }
+    p.total = at;
     return p;
 }
 
@@ -397,11 +506,6 @@ struct PosPlan {
     size_t thetaC, thetaN, featT, gT, thB, in_off, in_src, inedge_ws, total;
 };
 static inline int pad32(int x) { return (x + 31) / 32 * 32; }
-static bool pad_disabled()
-{
-    static const bool off = [] { const char *v = getenv("FLEX_PAD"); return v != nullptr && v[0] == '0'; }();
-    return off;
-}
 
 static PosPlan plan_pos(int64_t B, int64_t N, int K, int Din, int Dout, int layout, bool build)
 {
@@ -437,58 +541,6 @@ static PosPlan plan_pos(int64_t B, int64_t N, int K, int Din, int Dout, int layo
         }
     }
     p.total = at > 0 ? at : 256;
-    return p;
-}
-
-// Widths with neither a tiled nor a wide path run on zero-padded copies at the nearest widths that have one
-// (FLEX_PAD=0 in the environment keeps them on the direct-form kernels, for comparisons): extra channels of the
-// features / upstream gradient and extra rows / columns of the parameters are zero, so they add nothing, and the
-// results are the leading channels / the leading block of what the padded layer returns.
-static bool padded_shape(int Din, int Dout, int *DIp, int *DOp)
-{
-    if (pad_disabled() || wide_shape(Din, Dout)) return false;
-    if (gather_contract_supported(Din, Dout) && gather_contract_supported(Dout, Din)) return false;
-    if (Din <= 128 && Dout <= 128) {
-        int64_t best = -1;
-#define FLEX_SHAPE(DI_, DO_, W, T, OCC, WS)                                                         \
-        if (DI_ >= Din && DO_ >= Dout && gather_contract_supported(DO_, DI_) &&                         \
-            (best < 0 || (int64_t)DI_ * DO_ < best)) {                                                  \
-            best = (int64_t)DI_ * DO_; *DIp = DI_; *DOp = DO_;                                          \
-        }
-#include "flex_shapes.def"
-#undef FLEX_SHAPE
-        return best > 0;
-    }
-    *DIp = (Din + 127) / 128 * 128;
-    *DOp = (Dout + 127) / 128 * 128;
-    return wide_shape(*DIp, *DOp);
-}
-
-static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layout);
-static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layout, bool build);
-
-struct PadPlan {
-    size_t featP, gP, thetaP, outP, gfP, gtP, sub, sub_bytes, total;   // thetaP / gtP: [3,DIp,DOp] then [DIp,DOp]
-};
-static PadPlan plan_pad(int64_t B, int64_t N, int K, int DIp, int DOp, bool bwd, bool build)
-{
-    PadPlan p{};
-    size_t at = 0;
-    const size_t rows_in = align256(sizeof(float) * (size_t)(B * N) * DIp);
-    const size_t rows_out = align256(sizeof(float) * (size_t)(B * N) * DOp);
-    const size_t params = align256(sizeof(float) * (size_t)4 * DIp * DOp);
-    p.featP = at; at += rows_in;
-    p.thetaP = at; at += params;
-    if (!bwd) { p.outP = at; at += rows_out; }
-    else {
-        p.gP = at;  at += rows_out;
-        p.gfP = at; at += rows_in;
-        p.gtP = at; at += params;
-    }
-    p.sub = at;
-    p.sub_bytes = bwd ? plan_bwd(B, N, K, DIp, DOp, FLEX_LAYOUT_BNC, build).total
-                      : plan_fwd(B, N, K, DIp, DOp, FLEX_LAYOUT_BNC).total;
-    p.total = at + p.sub_bytes;
     return p;
 }
 
@@ -565,19 +617,15 @@ int flexconv_kernel_route(int op, int B, int N, int K, int Din, int Dout, int la
     if (layout != FLEX_LAYOUT_BCN && layout != FLEX_LAYOUT_BNC) return -1;
     if (op != FLEX_OP_CONV_FWD && op != FLEX_OP_CONV_BWD) return -1;
     if (!sizes_ok(B, N, K, Din, Dout)) return -1;
-    int DIp, DOp;
-    if (padded_shape(Din, Dout, &DIp, &DOp)) return FLEX_ROUTE_PADDED;
-    if (op == FLEX_OP_CONV_FWD) {
-        const FwdPlan p = plan_fwd(B, N, K, Din, Dout, layout);
+    auto answer = [&](const auto &p) {
+        if (p.direct) return (int)FLEX_ROUTE_DIRECT;
+        if (p.padded) return (int)(p.gather.own_widths() ? FLEX_ROUTE_PADDED : FLEX_ROUTE_PADDED_COPIES);
         if (p.wide) return wide_route(Din, Dout, layout);
-        if (!p.tiled) return FLEX_ROUTE_DIRECT;
-        return gather_contract_route(Din, Dout, N, K, 0);
-    }
+        return p.gather.route;
+    };
+    if (op == FLEX_OP_CONV_FWD) return answer(plan_fwd(B, N, K, Din, Dout, layout));
     const BwdPlan p = plan_bwd(B, N, K, Din, Dout, layout, false);
-    if (p.wide) return wide_route(Din, Dout, layout);
-    if (!p.tiled) return FLEX_ROUTE_DIRECT;
-    if (p.fused) return FLEX_ROUTE_LEAN_FUSED;
-    return gather_contract_route(Dout, Din, N, K, 1);
+    return p.fused ? (int)FLEX_ROUTE_LEAN_FUSED : answer(p);
 }
 
 size_t flexconv_workspace_bytes(int op, int B, int N, int K, int Din, int Dout, int layout)
@@ -588,9 +636,6 @@ size_t flexconv_workspace_bytes(int op, int B, int N, int K, int Din, int Dout, 
     case FLEX_OP_CONV_BWD:
     case FLEX_OP_CONV_BWD_BUILD: {
         if (!sizes_ok(B, N, K, Din, Dout)) return 0;
-        int DIp, DOp;
-        if (padded_shape(Din, Dout, &DIp, &DOp))
-            return plan_pad(B, N, K, DIp, DOp, op != FLEX_OP_CONV_FWD, op == FLEX_OP_CONV_BWD_BUILD).total;
         if (op == FLEX_OP_CONV_FWD) return plan_fwd(B, N, K, Din, Dout, layout).total;
         return plan_bwd(B, N, K, Din, Dout, layout, op == FLEX_OP_CONV_BWD_BUILD).total;
     }
@@ -614,58 +659,27 @@ int flexconv_fwd(const float *feat, const float *pos, const int32_t *nbr, const 
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
     const int bcn = (layout == FLEX_LAYOUT_BCN);
-    int Dki = Din, Dko = Dout;               // the widths the kernels run at
-    const bool padded = padded_shape(Din, Dout, &Dki, &Dko);
-    PadPlan pp{};
-    if (padded) pp = plan_pad(B, N, K, Dki, Dko, false, false);
-    const FwdPlan p = plan_fwd(B, N, K, Dki, Dko, padded ? FLEX_LAYOUT_BNC : layout);
-    if (!ws_ok(workspace, workspace_bytes, padded ? pp.total : p.total)) return FLEX_ERR_WORKSPACE;
-    if (!p.tiled && !p.wide) {
+    const FwdPlan p = plan_fwd(B, N, K, Din, Dout, layout);
+    if (!ws_ok(workspace, workspace_bytes, p.total)) return FLEX_ERR_WORKSPACE;
+    if (p.direct) {
         FLEX_HIP(launch_generic_fwd(feat, pos, nbr, theta, bias, out, B, N, K, Din, Dout, !bcn, s));
         return FLEX_OK;
     }
-    char *sub = ws + pp.sub;
-    void *thetaP = sub + p.thetaP;
+    // the kernels for any width take rows as they are; only channel-major ones have to be turned round
+    const int w_in = p.gather.own_widths() ? Din : p.k_in, w_out = p.copy_out ? p.k_out : Dout;
     PrepList prep;
     const float *rows = feat;
-    if (use_narrow(N, Din, Dki)) {
-        if (bcn) {
-            float *copy = (float *)(padded ? ws + pp.featP : sub + p.featT);
-            prep.copy(feat, copy, B, N, Din, Din, 1, 0);
-            rows = copy;
-        }
-        prep.pack_theta(theta, bias, thetaP, Din, Dout, narrow_rp(Din), 64, 1, narrow_blocks(Dout), 0);
-        FLEX_HIP(prep.launch(s));
-        FLEX_HIP(narrow_launch(rows, Din, Din, pos, nbr, nullptr, nullptr, nullptr, thetaP, out, Dout, bcn, B, N, K, s));
-        return FLEX_OK;
+    if (p.copy) {
+        prep.copy(feat, (float *)(ws + p.rows), B, N, Din, w_in, bcn, 0);
+        rows = (const float *)(ws + p.rows);
     }
-    if (use_tile(N, Dki, padded)) {
-        // rows of any width as they are; only channel-major ones have to be turned round
-        const TilePlan ph = tile_plan(B, N, Dki, Dko);
-        const int w_in = std::max(Din, 4);
-        if (bcn || w_in > Din) {
-            float *copy = (float *)(padded ? ws + pp.featP : sub + p.featT);
-            prep.copy(feat, copy, B, N, Din, w_in, bcn, 0);
-            rows = copy;
-        }
-        tile_pack(prep, ph, theta, bias, thetaP, Din, Dout, 0);
-        FLEX_HIP(prep.launch(s));
-        FLEX_HIP(tile_launch(ph, rows, w_in, w_in, pos, nbr, nullptr, nullptr, nullptr, thetaP, out, Dout, bcn, B, N, K, s));
-        return FLEX_OK;
-    }
-    if (padded || bcn) {
-        float *copy = (float *)(padded ? ws + pp.featP : sub + p.featT);
-        prep.copy(feat, copy, B, N, Din, Dki, bcn, 0);
-        rows = copy;
-    }
-    float *dst = padded ? (float *)(ws + pp.outP) : out;
-    const int fmt = gather_contract_theta_format(Dki, Dko, N, K, 0);
-    if (fmt) prep.pack_theta(theta, bias, thetaP, Din, Dout, pad4(Dki), pad16(Dko), 1, 1, 0);
-    else FLEX_HIP(launch_pack_theta(theta, bias, (float *)thetaP, Din, Dout, pad4(Dki), pad16(Dko), 0, s));
+    void *thetaP = ws + p.thetaP;
+    FLEX_HIP(gather_pack(prep, p.gather, theta, bias, thetaP, Din, Dout, p.k_in, p.k_out, 0, s));
     FLEX_HIP(prep.launch(s));
-    FLEX_HIP(launch_gather_contract(rows, pos, nbr, nullptr, nullptr, nullptr, thetaP, fmt, dst, B, N, K, Dki, Dko, 0,
-                                    bcn && !padded, s));
-    if (dst != out) FLEX_HIP(launch_copy_rows(dst, out, B, N, Dko, Dout, 0, bcn, s));
+    float *dst = p.copy_out ? (float *)(ws + p.out) : out;
+    FLEX_HIP(gather_launch(p.gather, rows, w_in, w_in, pos, nbr, nullptr, nullptr, nullptr, thetaP, dst, w_out,
+                           bcn && !p.copy_out, B, N, K, s));
+    if (p.copy_out) FLEX_HIP(launch_copy_rows(dst, out, B, N, p.k_out, Dout, 0, bcn, s));
     return FLEX_OK;
 }
 
@@ -743,82 +757,61 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
     const int bcn = (layout == FLEX_LAYOUT_BCN);
-    int Dki = Din, Dko = Dout;               // the widths the kernels run at
-    const bool padded = padded_shape(Din, Dout, &Dki, &Dko);
-    PadPlan pp{};
-    if (padded) pp = plan_pad(B, N, K, Dki, Dko, true, build);
-    const BwdPlan p = plan_bwd(B, N, K, Dki, Dko, padded ? FLEX_LAYOUT_BNC : layout, build);
-    if (!ws_ok(workspace, workspace_bytes, padded ? pp.total : p.total)) return FLEX_ERR_WORKSPACE;
-    if (!p.tiled && !p.wide) {
+    const BwdPlan p = plan_bwd(B, N, K, Din, Dout, layout, build);
+    if (!ws_ok(workspace, workspace_bytes, p.total)) return FLEX_ERR_WORKSPACE;
+    if (p.direct) {
         FLEX_HIP(launch_generic_bwd(feat, pos, nbr, theta, bias, grad_out, grad_feat, grad_theta,
                                     grad_bias, B, N, K, Din, Dout, !bcn, s));
         return FLEX_OK;
     }
-    char *sub = ws + pp.sub;
     if (build) {
-        int32_t *off = (int32_t *)(sub + p.in_off), *src = (int32_t *)(sub + p.in_src);
-        FLEX_HIP(launch_inedges_build(nbr, B, N, K, off, src, sub + p.inedge_ws, s));
+        int32_t *off = (int32_t *)(ws + p.in_off), *src = (int32_t *)(ws + p.in_src);
+        FLEX_HIP(launch_inedges_build(nbr, B, N, K, off, src, ws + p.inedge_ws, s));
         in_off = off;
         in_src = src;
     }
-    void *thetaP = sub + p.thetaP;
-    float *partials = (float *)(sub + p.partials);
-    int32_t *order = (int32_t *)(sub + p.order);
-    int *control = (int *)(sub + p.flag);
+    void *thetaP = ws + p.thetaP;
+    float *partials = (float *)(ws + p.partials);
+    int32_t *order = (int32_t *)(ws + p.order);
+    int *control = (int *)(ws + p.flag);
     const bool fused = p.fused && grad_theta && grad_feat;
-    const bool narrow = !fused && grad_feat && use_narrow(N, Dout, Dko);
-    const bool tile = !fused && !narrow && grad_feat && use_tile(N, Dko, padded);
-    TilePlan ph{};
-    if (tile) ph = tile_plan(B, N, Dko, Dki);
-    const int fmt = tile || narrow ? 1 : gather_contract_theta_format(Dko, Dki, N, K, 1);
     PrepList prep;
     const float *rows = feat, *g_rows = grad_out;
-    if (padded || bcn) {
-        float *g_copy = (float *)(padded ? ws + pp.gP : sub + p.gT), *f_copy = (float *)(padded ? ws + pp.featP : sub + p.featT);
-        prep.copy(grad_out, g_copy, B, N, Dout, Dko, bcn, 0);
-        if (grad_theta) prep.copy(feat, f_copy, B, N, Din, Dki, bcn, 0);
-        g_rows = g_copy;
-        rows = f_copy;
+    if (p.copy) {
+        prep.copy(grad_out, (float *)(ws + p.gT), B, N, Dout, p.k_out, bcn, 0);
+        if (grad_theta) prep.copy(feat, (float *)(ws + p.featT), B, N, Din, p.k_in, bcn, 0);
+        g_rows = (const float *)(ws + p.gT);
+        rows = (const float *)(ws + p.featT);
     }
     if (grad_feat) {
-        if (narrow) prep.pack_theta(theta, bias, thetaP, Din, Dout, narrow_rp(Dout), 64, 1, narrow_blocks(Din), 1);
-        else if (tile) tile_pack(prep, ph, theta, bias, thetaP, Din, Dout, 1);
-        else if (fmt) prep.pack_theta(theta, bias, thetaP, Din, Dout, pad4(Dko), pad16(Dki), 1, 1, 1);
-        else FLEX_HIP(launch_pack_theta(theta, bias, (float *)thetaP, Din, Dout, pad4(Dko), pad16(Dki), 1, s));
+        FLEX_HIP(gather_pack(prep, p.gather, theta, bias, thetaP, Din, Dout, p.k_out, p.k_in, 1, s));
         prep.order(in_off, B, N, order);
     }
     if (fused) prep.clear(control, FUSED_FLAG_INTS);
     FLEX_HIP(prep.launch(s));
-    float *dst = padded && !tile && !narrow ? (float *)(ws + pp.gfP) : grad_feat;
-    const int out_bcn = bcn && !padded;
     if (fused) {
         int n_wg = 0;
-        FLEX_HIP(launch_bwd_fused_64_64(g_rows, rows, pos, nbr, in_off, in_src, order, thetaP, dst, partials, control, B,
-                                        N, K, out_bcn, &n_wg, s));
+        FLEX_HIP(launch_bwd_fused_64_64(g_rows, rows, pos, nbr, in_off, in_src, order, thetaP, grad_feat, partials, control,
+                                        B, N, K, bcn, &n_wg, s));
         FLEX_HIP(launch_reduce_partials_fused(partials, n_wg, control, Din, Dout, grad_theta, grad_bias, s));
         // is the result resolved by the f16 halves, and did no row overflow them?  if not (decided on the device), the
         // stand-alone kernel and a second reduction run; both return at once otherwise
         FLEX_HIP(launch_bwd_fused_late_64_64(g_rows, rows, pos, nbr, thetaP, grad_theta, grad_bias, Din, Dout, partials,
                                              control, B, N, K, s));
         FLEX_HIP(launch_reduce_partials_if(control, partials, n_wg, 64, 64, Din, Dout, grad_theta, grad_bias, s));
-    } else {
-        if (grad_theta && p.wide)
-            FLEX_HIP(wide_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, Dki, Dko, Din, Dout,
-                                     s));
-        else if (grad_theta)
-            FLEX_HIP(launch_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, Dki, Dko, Din,
-                                       Dout, s));
-        if (narrow)
-            FLEX_HIP(narrow_launch(g_rows, Dko, Dout, pos, nullptr, in_off, in_src, order, thetaP, grad_feat, Din, bcn, B, N,
-                                   K, s));
-        else if (tile)
-            FLEX_HIP(tile_launch(ph, g_rows, Dko, std::max(Dout, 4), pos, nullptr, in_off, in_src, order, thetaP,
-                                  grad_feat, Din, bcn, B, N, K, s));
-        else if (grad_feat)
-            FLEX_HIP(launch_gather_contract(g_rows, pos, nullptr, in_off, in_src, order, thetaP, fmt, dst, B, N, K, Dko,
-                                            Dki, 1, out_bcn, s));
+        return FLEX_OK;
     }
-    if (grad_feat && dst != grad_feat) FLEX_HIP(launch_copy_rows(dst, grad_feat, B, N, Dki, Din, 0, bcn, s));
+    if (grad_theta && p.wide)
+        FLEX_HIP(wide_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, p.k_in, p.k_out, Din,
+                                 Dout, s));
+    else if (grad_theta)
+        FLEX_HIP(launch_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, p.k_in, p.k_out, Din,
+                                   Dout, s));
+    if (!grad_feat) return FLEX_OK;
+    float *dst = p.copy_out ? (float *)(ws + p.gfP) : grad_feat;
+    FLEX_HIP(gather_launch(p.gather, g_rows, p.k_out, p.gather.own_widths() ? Dout : p.k_out, pos, nullptr, in_off, in_src,
+                           order, thetaP, dst, p.copy_out ? p.k_in : Din, bcn && !p.copy_out, B, N, K, s));
+    if (p.copy_out) FLEX_HIP(launch_copy_rows(dst, grad_feat, B, N, p.k_in, Din, 0, bcn, s));
     return FLEX_OK;
 }
 

@@ -293,3 +293,37 @@ def test_lean_kernels_stop_where_byte_offsets_leave_32_bits(L):
     assert route(0, 1, lim64, 24, 64, 64, 1) == ROUTE_SINGLE
     assert route(0, 1, 4096, 8, 5, 7, 1) == ROUTE_PADDED and route(0, 1, 4096, 8, 256, 512, 1) == ROUTE_WIDE
     assert route(0, 0, 4096, 8, 64, 64, 1) == -1 and route(3, 1, 4096, 8, 64, 64, 1) == -1
+
+
+ROUTE_TILE, ROUTE_NARROW, ROUTE_PADDED_COPIES = 8, 9, 10
+
+
+def test_route_query_names_the_kernels_of_narrow_and_wide_gathers(L):
+    # the gathered width decides: Din forward, Dout in the feature gradient
+    route = L.flexconv_kernel_route
+    assert route(0, 1, 4096, 8, 9, 64, 1) == ROUTE_NARROW and route(1, 1, 4096, 8, 9, 64, 1) == ROUTE_LEAN
+    assert route(0, 1, 4096, 8, 64, 9, 1) == ROUTE_LEAN and route(1, 1, 4096, 8, 64, 9, 1) == ROUTE_NARROW
+    assert route(0, 1, 4096, 8, 128, 64, 1) == ROUTE_TILE and route(1, 1, 4096, 8, 128, 64, 1) == ROUTE_LEAN
+    assert route(0, 1, 4096, 8, 64, 128, 1) == ROUTE_LEAN and route(1, 1, 4096, 8, 64, 128, 1) == ROUTE_TILE
+    # rows past 32-bit byte offsets: the kernels that do not need them
+    past = (1 << 32) // (128 * 4)
+    assert route(0, 1, past - 1, 8, 128, 64, 1) == ROUTE_TILE and route(0, 1, past, 8, 128, 64, 1) == ROUTE_SINGLE
+    past = (1 << 32) // (9 * 4)
+    assert route(0, 1, past - 1, 8, 9, 64, 1) == ROUTE_NARROW and route(0, 1, past + 1, 8, 9, 64, 1) == ROUTE_STAGED
+    # widths outside the list: at their own widths while those kernels reach, on zero-padded copies beyond
+    assert route(0, 1, 4096, 8, 20, 100, 1) == ROUTE_PADDED and route(1, 1, 4096, 8, 20, 100, 1) == ROUTE_PADDED
+    assert route(0, 1, (1 << 32) // (20 * 4) + 1, 8, 20, 100, 1) == ROUTE_PADDED_COPIES
+    past = (1 << 32) // (128 * 4)            # the upstream gradient's rows, padded for the parameter gradients
+    assert route(1, 1, past - 1, 8, 20, 100, 1) == ROUTE_PADDED and route(1, 1, past, 8, 20, 100, 1) == ROUTE_PADDED_COPIES
+    for env in ({"FLEX_CONTRACT": "f32"}, {"FLEX_PRODUCER": "staged"}):
+        r = _query(env, [("flexconv_kernel_route", [0, 1, 4096, 8, *w, 1]) for w in ((9, 64), (128, 64), (20, 100))])
+        assert ROUTE_NARROW not in r and ROUTE_TILE not in r and r[2] == ROUTE_PADDED_COPIES
+
+
+@pytest.mark.parametrize("Din,Dout,layout,points", [
+    (9, 64, 0, 57784), (32, 32, 0, 16250), (64, 64, 0, 7931), (128, 64, 0, 3835), (128, 128, 0, 1789),
+    (3, 32, 0, 7092), (5, 7, 1, 7092), (64, 13, 0, 5287), (64, 13, 1, 5287), (100, 40, 1, 2386), (17, 100, 0, 2387)])
+def test_static_scratch_holds_the_clouds_it_always_held(L, Din, Dout, layout, points):
+    # flexconv_fwd_noalloc takes a call whose workspace is at most 2 MiB: a channel-major or zero-padded layer of this many
+    # points has been one
+    assert 0 < L.flexconv_workspace_bytes(0, 1, points, 8, Din, Dout, layout) <= 2 << 20
