@@ -247,7 +247,8 @@ static hipError_t launch_grad_theta(const float *rows, const float *pos, const i
 // need zero-padded copies of the tensors (K = 8, forward and feature gradient, copies against here: 50 -> 50, 4k points 37
 // and 43 against 22 and 20, 100k 88 and 121 against 40 and 58, 1M 600 and 867 against 270 and 407; 64 -> 13 forward, 4k,
 // 100k and 1M points 27, 63, 460 against 21, 36, 235; 20 -> 13 forward 27, 52, 323 against 20, 37, 218).
-static bool use_tile(int64_t N, int w_in, bool padded) { return tile_ok(N, w_in) && (w_in > 64 || padded); }
+// rs: row stride.
+static bool use_tile(int64_t N, int w_in, int rs, bool padded) { return tile_ok(N, rs) && (w_in > 64 || padded); }
 
 struct TilePlan { int outw, n_in, n_out; };
 // How a gather is cut: input blocks of 64 channels, output blocks as wide as pays.  A wider output block gathers its rows
@@ -350,9 +351,9 @@ static GatherPlan plan_gather(int64_t B, int64_t N, int K, int w_in, int w_out, 
     if (use_narrow(N, w_in, rs)) {
         g.route = FLEX_ROUTE_NARROW;
         g.packed = narrow_bytes(w_in, w_out);
-    } else if (use_tile(N, k_in, padded)) {
+    } else if (use_tile(N, w_in, rs, padded)) {
         g.route = FLEX_ROUTE_TILE;
-        g.tile = tile_plan(B, N, k_in, k_out);
+        g.tile = tile_plan(B, N, w_in, w_out);
         g.packed = tile_bytes(g.tile);
     } else {
         g.route = gather_contract_route(k_in, k_out, (int)N, K, csr);

@@ -43,6 +43,16 @@ def test_sizes_around_the_tile_and_its_blocks(B, N, K, Din, Dout, layout):
     check(70 + N + K, B, N, K, Din, Dout, layout)
 
 
+@pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
+@pytest.mark.parametrize("B,N,K,Din,Dout", [
+    (1, 130, 8, 192, 192), (2, 65, 9, 129, 20), (1, 200, 8, 40, 130), (1, 97, 5, 17, 129), (1, 64, 8, 191, 257),
+    (1, 150, 16, 320, 200),
+])
+def test_blocks_of_widths_between_the_multiples_of_128(B, N, K, Din, Dout, layout):
+    """As many input blocks as the rows have, where the parameter gradients' padded copies have more."""
+    check(80 + N + K, B, N, K, Din, Dout, layout)
+
+
 def test_hub_point_and_empty_lists():
     check(5, 1, 500, 4, 128, 128, fx.BNC, hub=True)
     check(6, 2, 90, 8, 100, 70, fx.BNC, hub=True)
