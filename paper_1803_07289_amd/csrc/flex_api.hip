@@ -271,6 +271,16 @@ static TilePlan tile_plan(int64_t B, int64_t N, int w_in, int w_out)
 }
 static size_t tile_bytes(const TilePlan &p) { return (size_t)p.n_in * p.n_out * theta_f16_bytes(64, p.outw); }
 
+// Workgroups per output block of a persistent grid: as many as there are tiles, at most `most` (what the device holds at
+// once), in whole multiples of 8 where that leaves any, so that a share's number tells its XCD.  Never more than the
+// device holds: rounded up, three output blocks were 264 workgroups on 256 CUs, and the last eight ran alone for as long as
+// all the others before them (128 -> 768, 100k points, three 256-wide blocks: 502 us, 393 in one round).
+static int output_block_shares(int64_t tiles, int64_t most)
+{
+    const int64_t held = most >= 8 ? most / 8 * 8 : std::max<int64_t>(most, 1);
+    return (int)std::min((tiles + 7) / 8 * 8, held);
+}
+
 // rows [B*N, rs] (w_in channels used) onto out [B, N, w_out] or, out_bcn, [B, w_out, N]
 static hipError_t tile_launch(const TilePlan &p, const float *rows, int rs, int w_in, const float *pos,
                                const int32_t *nbr, const int32_t *off, const int32_t *src, const int32_t *order,
@@ -288,10 +298,7 @@ static hipError_t tile_launch(const TilePlan &p, const float *rows, int rs, int 
     const int64_t total = (int64_t)B * a.tpc;
     if (total > 0x7fffffff) return hipErrorInvalidValue;
     a.total = (int)total;
-    // workgroups per output block: whole multiples of 8 where there are that many, so that a share's number tells its XCD
-    int64_t chunks = device_cu_count() / p.n_out;
-    if (total < chunks) chunks = total;
-    a.chunks = (int)(chunks >= 8 ? (chunks + 7) / 8 * 8 : (chunks > 1 ? chunks : 1));
+    a.chunks = output_block_shares(total, device_cu_count() / p.n_out);
     const int grid = p.n_out * a.chunks;
     return off != nullptr ? launch_tile_1(a, p.outw, grid, s) : launch_tile_0(a, p.outw, grid, s);
 }
@@ -325,10 +332,8 @@ static hipError_t narrow_launch(const float *rows, int rs, int w_in, const float
     const int64_t total = (int64_t)B * a.tpc;
     if (total > 0x7fffffff) return hipErrorInvalidValue;
     a.total = (int)total;
-    // eight one-wave workgroups per CU are what its registers and LDS hold; multiples of 8 per output block (XCDs)
-    int64_t chunks = (int64_t)device_cu_count() * 8 / n_out;
-    if (total < chunks) chunks = total;
-    a.chunks = (int)(chunks >= 8 ? (chunks + 7) / 8 * 8 : (chunks > 1 ? chunks : 1));
+    // eight one-wave workgroups per CU are what its registers and LDS hold
+    a.chunks = output_block_shares(total, (int64_t)device_cu_count() * 8 / n_out);
     const int grid = n_out * a.chunks;
     return off != nullptr ? launch_narrow_1(a, grid, s) : launch_narrow_0(a, grid, s);
 }
