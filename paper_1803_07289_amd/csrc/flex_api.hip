@@ -251,25 +251,28 @@ static hipError_t launch_grad_theta(const float *rows, const float *pos, const i
 static bool use_tile(int64_t N, int w_in, int rs, bool padded) { return tile_ok(N, rs) && (w_in > 64 || padded); }
 
 struct TilePlan { int outw, n_in, n_out; };
+static size_t tile_bytes(const TilePlan &p) { return (size_t)p.n_in * p.n_out * theta_f16_bytes(64, p.outw); }
 // How a gather is cut: input blocks of 64 channels, output blocks as wide as pays.  A wider output block gathers its rows
 // for more channels; a narrower one makes more jobs for a cloud of few tiles.  The costs of a tile and input block
-// (thousands of clocks) are measured ones.
-static TilePlan tile_plan(int64_t B, int64_t N, int w_in, int w_out)
+// (units of 260 clocks) are measured ones.  Packed parameters within `room` bytes go before cheaper ones that are not: wide
+// output blocks reach further past the width.
+static TilePlan tile_plan(int64_t B, int64_t N, int w_in, int w_out, size_t room)
 {
     TilePlan p{};
     p.n_in = (w_in + 63) / 64;
     const int64_t tiles = B * cdiv64(N, 64);
     const int widths[3] = {64, 128, 256}, cost[3] = {50, 55, 75};
     int64_t best = -1;
+    bool best_fits = false;
     for (int i = 0; i < 3; ++i) {
         if (i > 0 && widths[i] >= 2 * w_out) break;
-        const int n_out = (w_out + widths[i] - 1) / widths[i];
-        const int64_t c = cdiv64(tiles * n_out, device_cu_count()) * cost[i];
-        if (best < 0 || c < best) { best = c; p.outw = widths[i]; p.n_out = n_out; }
+        TilePlan q{widths[i], p.n_in, (w_out + widths[i] - 1) / widths[i]};
+        const int64_t c = cdiv64(tiles * q.n_out, device_cu_count()) * cost[i];
+        const bool fits = tile_bytes(q) <= room;
+        if (best < 0 || (fits != best_fits ? fits : c < best)) { best = c; best_fits = fits; p = q; }
     }
     return p;
 }
-static size_t tile_bytes(const TilePlan &p) { return (size_t)p.n_in * p.n_out * theta_f16_bytes(64, p.outw); }
 
 // Workgroups per output block of a persistent grid: as many as there are tiles, at most `most` (what the device holds at
 // once), in whole multiples of 8 where that leaves any, so that a share's number tells its XCD.  Never more than the
@@ -342,6 +345,7 @@ static hipError_t narrow_launch(const float *rows, int rs, int w_in, const float
 // The kernels of one gather (the forward pass; the feature gradient over in-edge lists): rows of w_in channels, rs floats
 // apart, onto w_out channels; (k_in, k_out): the listed widths that cover them.  Decided here, once, from everything it
 // depends on (sizes, environment switches); the entry points dispatch on it, the workspace and the route query follow it.
+// room: bytes that the packed parameters should stay within where they can.
 struct GatherPlan {
     int route;             // FLEX_ROUTE_NARROW, FLEX_ROUTE_TILE or what gather_contract_route answers
     TilePlan tile;
@@ -350,7 +354,7 @@ struct GatherPlan {
     bool own_widths() const { return route == FLEX_ROUTE_NARROW || route == FLEX_ROUTE_TILE; }
 };
 static GatherPlan plan_gather(int64_t B, int64_t N, int K, int w_in, int w_out, int rs, int k_in, int k_out, bool padded,
-                              int csr)
+                              int csr, size_t room)
 {
     GatherPlan g{};
     if (use_narrow(N, w_in, rs)) {
@@ -358,7 +362,7 @@ static GatherPlan plan_gather(int64_t B, int64_t N, int K, int w_in, int w_out, 
         g.packed = narrow_bytes(w_in, w_out);
     } else if (use_tile(N, w_in, rs, padded)) {
         g.route = FLEX_ROUTE_TILE;
-        g.tile = tile_plan(B, N, w_in, w_out);
+        g.tile = tile_plan(B, N, w_in, w_out, room);
         g.packed = tile_bytes(g.tile);
     } else {
         g.route = gather_contract_route(k_in, k_out, (int)N, K, csr);
@@ -462,7 +466,10 @@ static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     p.total = copies + 256;
     if (p.direct) return p;
     const bool bcn = layout == FLEX_LAYOUT_BCN;
-    p.gather = plan_gather(B, N, K, Din, Dout, Din, p.k_in, p.k_out, p.padded, 0);
+    // a call whose parameters can be packed into the static scratch beside the turned rows is one that it takes
+    const size_t turned = bcn ? rows_bytes(B, N, Din) : 0;
+    p.gather = plan_gather(B, N, K, Din, Dout, Din, p.k_in, p.k_out, p.padded, 0,
+                           turned < FLEX_NOALLOC_SCRATCH_BYTES ? FLEX_NOALLOC_SCRATCH_BYTES - turned : 0);
     const bool own = p.gather.own_widths();
     p.copy = bcn || (p.padded && !own);
     p.copy_out = p.padded && !own;
@@ -484,7 +491,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     p.direct = !p.wide && !(gather_contract_supported(p.k_in, p.k_out) && gather_contract_supported(p.k_out, p.k_in));
     p.total = 256;
     if (p.direct) return p;
-    p.gather = plan_gather(B, N, K, Dout, Din, p.k_out, p.k_out, p.k_in, p.padded, 1);
+    p.gather = plan_gather(B, N, K, Dout, Din, p.k_out, p.k_out, p.k_in, p.padded, 1, SIZE_MAX);
     p.copy = p.padded || layout == FLEX_LAYOUT_BCN;          // the parameter gradients run at the listed widths
     p.copy_out = p.padded && !p.gather.own_widths();
     size_t at = p.gather.packed;

@@ -327,3 +327,14 @@ def test_static_scratch_holds_the_clouds_it_always_held(L, Din, Dout, layout, po
     # flexconv_fwd_noalloc takes a call whose workspace is at most 2 MiB: a channel-major or zero-padded layer of this many
     # points has been one
     assert 0 < L.flexconv_workspace_bytes(0, 1, points, 8, Din, Dout, layout) <= 2 << 20
+
+
+@pytest.mark.parametrize("Din,Dout", [(256, 384), (128, 896), (384, 256), (128, 384), (128, 640), (256, 256)])
+def test_static_scratch_holds_wide_layers_whatever_the_cloud(L, Din, Dout):
+    # point-major layers need the packed parameters only: 64 x 128 blocks of them fit, whichever blocks a cloud's tiles prefer
+    assert (Din // 64) * (Dout // 128) * (4 * 64 * 128 * 4 + 128 * 4 + 256 * 4) <= 2 << 20
+    for N in (100, 1000, 10_000, 100_000, 1_000_000):
+        assert 0 < L.flexconv_workspace_bytes(0, 1, N, 8, Din, Dout, 1) <= 2 << 20
+    # channel-major ones beside the turned rows (and, as it has been, room for the result)
+    N = ((2 << 20) - (Din // 64) * (Dout // 128) * 132608) // (4 * (Din + Dout)) - 1
+    assert 0 < L.flexconv_workspace_bytes(0, 1, N, 8, Din, Dout, 0) <= 2 << 20
