@@ -103,7 +103,7 @@ hipError_t FLEX_NAME(launch_gc, FLEX_DI, FLEX_DO)(const float *rows, const float
 #define FLEX_LEAN_LAUNCH(BCN_, PM_)                                                                              \
     do {                                                                                                         \
         if (K % 8 == 0) hipLaunchKernelGGL((gather_contract_lean_kernel<S, BCN_, PM_>), gl, bl, 0, s, FLEX_LEAN_ARGS); \
-        else hipLaunchKernelGGL((gather_contract_lean_kernel<S, BCN_, PM_, S::DI, S::DO, false, true>), gl, bl, 0, s, FLEX_LEAN_ARGS); \
+        else hipLaunchKernelGGL((gather_contract_lean_kernel<S, BCN_, PM_, true>), gl, bl, 0, s, FLEX_LEAN_ARGS); \
     } while (0)
                 if (wide && !out_bcn) FLEX_LEAN_LAUNCH(false, PMX);
                 else if (wide) FLEX_LEAN_LAUNCH(true, PMX);
@@ -186,7 +186,7 @@ hipError_t FLEX_NAME(launch_gt, FLEX_DI, FLEX_DO)(const float *rows, const float
             if (K % 8 == 0)
                 hipLaunchKernelGGL((grad_theta_lean_kernel<S>), dim3(*n_wg), dim3(WL::NT), 0, s, rows, pos, nbr, g_rows, partials, N, K, tpc, tot);
             else
-                hipLaunchKernelGGL((grad_theta_lean_kernel<S, S::DI, S::DO, true>), dim3(*n_wg), dim3(WL::NT), 0, s, rows, pos, nbr, g_rows, partials, N, K, tpc, tot);
+                hipLaunchKernelGGL((grad_theta_lean_kernel<S, true>), dim3(*n_wg), dim3(WL::NT), 0, s, rows, pos, nbr, g_rows, partials, N, K, tpc, tot);
             return hipGetLastError();
         }
     }

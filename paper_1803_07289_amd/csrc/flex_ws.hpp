@@ -545,12 +545,10 @@ __device__ __forceinline__ void producer_loop(Producer<S, CSR> &Pr, const TileSc
 // ---------------------------------------------------------------------------
 // SUM == true: only the plain neighbour sum (component j = 3 of the aggregate) is formed; no positions
 // are read (used by the location-gradient kernels).
-// RS = floats between consecutive rows of the gathered tensor (S::DI unless the rows are a column block of a wider
-// one); RS == 0: the stride is the run-time value set with set_row_stride() (one multiply per row instead of a shift).
 // TAIL: K is not a multiple of 8; the last batch of a tile has slots past K, which are read from slot K-1 and
 // weighted 0 (the weight travels as the fourth position component; in the plain-sum mode it is a wave-uniform
 // 0 / 1 per slot), and its rows 4..7 are skipped when empty.
-template <class S, int PM, bool SUM = false, int RS = S::DI, bool TAIL = false>
+template <class S, int PM, bool SUM = false, bool TAIL = false>
 struct LeanProducer {
     using G = WsGeom<S, PM>;
     static constexpr int U = 8;
@@ -564,9 +562,6 @@ struct LeanProducer {
     const float *rows, *pos;
     const int32_t *nbr;
     int N, K, KB, pw;
-    unsigned rs_rt = 0;          // row stride in floats when RS == 0
-    __device__ __forceinline__ void set_row_stride(int rs) { rs_rt = (unsigned)rs; }
-    __device__ __forceinline__ unsigned row_stride() const { if constexpr (RS != 0) return RS; else return rs_rt; }
     int count, tiles_per_cloud;  // tiles of this workgroup
     TileSchedule sched;
     // compute layout: lane = (row group grp, lane t inside the row)
@@ -659,7 +654,7 @@ struct LeanProducer {
 
     __device__ __forceinline__ void load_row(float (&fr)[S::VEC], int id, const char *rb) const
     {
-        const char *p = rb + ((unsigned)id * (4u * row_stride()) + lane_off);
+        const char *p = rb + ((unsigned)id * (4u * S::DI) + lane_off);
         if constexpr (S::VEC == 4) {
             const v4f v = *reinterpret_cast<const v4f *>(p);
             fr[0] = v.x; fr[1] = v.y; fr[2] = v.z; fr[3] = v.w;
@@ -715,7 +710,7 @@ struct LeanProducer {
             // end of every iteration: the wait at the loop top (for positions and ids) is one instruction
             // for both ways in, and a load issued after the rows would turn it into a wait for the rows.
             __builtin_amdgcn_sched_barrier(0);
-            const char *rb = reinterpret_cast<const char *>(rows + (int64_t)x0.b * N * row_stride());
+            const char *rb = reinterpret_cast<const char *>(rows + (int64_t)x0.b * N * (unsigned)S::DI);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (!TAIL || u < 4 || x0.k0 + 4 < K) load_row(f[u], spread(id0, perm_id, u), rb);
@@ -748,8 +743,8 @@ struct LeanProducer {
             int idc[ID_LDS ? 1 : U];
             if constexpr (ID_LDS) {
                 if ((threadIdx.x & 3) == 3) {
-                    dpe[0] = (int)((unsigned)idn[0] * (4u * row_stride()));
-                    dpe[1] = (int)((unsigned)idn[1] * (4u * row_stride()));
+                    dpe[0] = (int)((unsigned)idn[0] * (4u * S::DI));
+                    dpe[1] = (int)((unsigned)idn[1] * (4u * S::DI));
                 }
             } else {
 #pragma unroll
@@ -759,7 +754,7 @@ struct LeanProducer {
             advance(walk);
             const Batch x2 = get(walk);
             load_ids(idn, x2);
-            const char *rb = reinterpret_cast<const char *>(rows + (int64_t)x1.b * N * row_stride());
+            const char *rb = reinterpret_cast<const char *>(rows + (int64_t)x1.b * N * (unsigned)S::DI);
             const int nb = x1.b, nlw0 = x1.lw0;
             x1 = x2;
             float dpc[DP_LDS ? 1 : U];
@@ -862,7 +857,7 @@ struct LeanProducer {
 // nearby points, see inedge_order_kernel): the four points of a wave then have lists of (nearly) the same length
 // and so have the twelve waves of a tile, so hardly any slot of a batch is empty and no wave waits at the tile's
 // barrier for one with a longer list.  The points' ids travel with the tile (s_P) to the consumers' stores.
-template <class S, int PM, bool SUM = false, int RS = S::DI, bool ORD = false>
+template <class S, int PM, bool SUM = false, bool ORD = false>
 struct LeanCsrProducer {
     using G = WsGeom<S, PM>;
     static constexpr int U = 8;
@@ -873,9 +868,6 @@ struct LeanCsrProducer {
     const int32_t *off, *src;
     const int32_t *order = nullptr;
     int N, pw;
-    unsigned rs_rt = 0;          // row stride in floats when RS == 0
-    __device__ __forceinline__ void set_row_stride(int rs) { rs_rt = (unsigned)rs; }
-    __device__ __forceinline__ unsigned row_stride() const { if constexpr (RS != 0) return RS; else return rs_rt; }
     int count, tiles_per_cloud;
     TileSchedule sched;
     int grp, t;
@@ -1022,7 +1014,7 @@ struct LeanCsrProducer {
     }
     __device__ __forceinline__ void load_row(float (&fr)[S::VEC], int id, const char *rb) const
     {
-        const char *p = rb + ((unsigned)id * (4u * row_stride()) + lane_off);
+        const char *p = rb + ((unsigned)id * (4u * S::DI) + lane_off);
         if constexpr (S::VEC == 4) {
             const v4f v = *reinterpret_cast<const v4f *>(p);
             fr[0] = v.x; fr[1] = v.y; fr[2] = v.z; fr[3] = v.w;
@@ -1060,7 +1052,7 @@ struct LeanCsrProducer {
             pn[0] = pn[1] = pc = 0.f;
             if constexpr (!SUM) load_pos(pn, pc, id0, d0);
             __builtin_amdgcn_sched_barrier(0);      // rows youngest, as at the end of every iteration
-            const char *rb = reinterpret_cast<const char *>(rows + (int64_t)d0.b * N * row_stride());
+            const char *rb = reinterpret_cast<const char *>(rows + (int64_t)d0.b * N * (unsigned)S::DI);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (u < d0.nrows) load_row(f[u], spread(id0, perm_id, u), rb);
@@ -1082,7 +1074,7 @@ struct LeanCsrProducer {
 #pragma unroll
             for (int u = 0; u < U; ++u) idc[u] = spread(idn, perm_id, u);
             if constexpr (!SUM) load_pos(pn, pc, idn, d1);
-            const char *rb = reinterpret_cast<const char *>(rows + (int64_t)d1.b * N * row_stride());
+            const char *rb = reinterpret_cast<const char *>(rows + (int64_t)d1.b * N * (unsigned)S::DI);
             d0 = d1;
             fetch(c, idn, d1);
             constexpr bool DP_LDS = FLEX_DP_LDS && !SUM;
@@ -1158,8 +1150,6 @@ struct LeanCsrProducer {
 
 // One consumer wave of the split-half contraction: out tile = A tile * Theta for every tile of
 // the workgroup.  cw = consumer index; G = the workgroup geometry; barriers pair with the producers'.
-// OS = floats between consecutive output rows (point-major form; 0: the run-time value os_rt), ACC (or the
-// run-time flag acc_rt): add to what out holds.
 // ORD: tile slot pt holds the point s_P[pt] (the producers walk the cloud in a given order), not position l0 + pt.
 // NBUF: tile buffers the producers cycle through (tile k sits in buffer k % NBUF).
 // hook.begin(k, kb, b) runs right after tile k's barrier (kb = its buffer, b = its cloud), hook.end(k) after the
@@ -1168,14 +1158,13 @@ struct NoTileHook {
     __device__ __forceinline__ void begin(int, int, int) {}
     __device__ __forceinline__ void end(int) {}
 };
-template <class S, class G, bool OUT_BCN, int OS = S::DO, bool ACC = false, bool ORD = false, int NBUF = 2,
+template <class S, class G, bool OUT_BCN, bool ORD = false, int NBUF = 2,
           class Hook = NoTileHook, bool SWZ = false>
 __device__ __forceinline__ void consumer_f16(int cw, const void *__restrict__ thetaP, int theta_exp_off,
                                              float *__restrict__ out, int N, const TileSchedule &sc,
-                                             int tiles_per_cloud, const char *s_A, const int *s_E, int os_rt = 0,
-                                             bool acc_rt = false, const int *s_P = nullptr, Hook hook = Hook())
+                                             int tiles_per_cloud, const char *s_A, const int *s_E,
+                                             const int *s_P = nullptr, Hook hook = Hook())
 {
-    const int os = OS != 0 ? OS : os_rt;
     const int lane = threadIdx.x & 63, q = lane >> 4, r16 = lane & 15;
     // item = (slice, block); consumer cw owns items cw, cw+NC, ... ; all share one slice
     static_assert(G::NS <= G::NC, "one parameter slice per consumer wave");
@@ -1197,12 +1186,9 @@ __device__ __forceinline__ void consumer_f16(int cw, const void *__restrict__ th
                 for (int i = 0; i < 4; ++i)
                     if (o + i < S::DO) dst[(int64_t)i * N] = d[i];
             } else {
-                float *dst = out + ((int64_t)r.b * N + l) * os + o;
+                float *dst = out + ((int64_t)r.b * N + l) * S::DO + o;
                 if constexpr (S::DO % 4 == 0) {
-                    if (o < S::DO) {
-                        if (ACC || acc_rt) d += *reinterpret_cast<const v4f *>(dst);
-                        *reinterpret_cast<v4f *>(dst) = d;
-                    }
+                    if (o < S::DO) *reinterpret_cast<v4f *>(dst) = d;
                 } else {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
@@ -1311,18 +1297,19 @@ __device__ __forceinline__ void consumer_f16(int cw, const void *__restrict__ th
 // counts is how many rows the CU has in flight; the f16 contraction is cheap enough for a
 // quarter of the waves.
 // ---------------------------------------------------------------------------
-template <class S, bool OUT_BCN, int PM, int RS, int OS, bool ACC, bool TAIL>
-__device__ __forceinline__ void gather_contract_lean_body(const float *__restrict__ rows, const float *__restrict__ pos,
-                                                          const int32_t *__restrict__ nbr,
-                                                          const void *__restrict__ thetaP, int theta_exp_off,
-                                                          float *__restrict__ out, int N, int K, int tiles_per_cloud,
-                                                          const TileSchedule sc, int rs_rt, int os_rt, bool acc_rt)
+template <class S, bool OUT_BCN, int PM, bool TAIL = false>
+__global__ __launch_bounds__((WsGeom<S, PM>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void gather_contract_lean_kernel(const float *__restrict__ rows, const float *__restrict__ pos,
+                                 const int32_t *__restrict__ nbr, const void *__restrict__ thetaP,
+                                 int theta_exp_off, float *__restrict__ out, int N, int K,
+                                 int tiles_per_cloud, int total_tiles)
 {
     using G = WsGeom<S, PM>;
     __shared__ __attribute__((aligned(16))) char s_A[2 * G::T * G::ROWB];
     __shared__ int s_E[2 * G::T];
     __shared__ __attribute__((aligned(16))) float s_D[G::NP][128];     // per producer wave: a batch's position differences
 
+    const TileSchedule sc(total_tiles);
     const int w = threadIdx.x >> 6;
 
     if constexpr (G::KDP > S::KD) {
@@ -1337,9 +1324,8 @@ __device__ __forceinline__ void gather_contract_lean_body(const float *__restric
     }
 
     if (w < G::NP) {
-        LeanProducer<S, PM, false, RS, TAIL> P;
+        LeanProducer<S, PM, false, TAIL> P;
         P.init(rows, pos, nbr, N, K, w, sc, tiles_per_cloud);
-        P.set_row_stride(rs_rt);
         P.set_dp_stage(s_D[w]);
         float rsc[S::VEC][4];
         load_row_scales<S>(rsc, thetaP, theta_exp_off, P.t);
@@ -1350,30 +1336,17 @@ __device__ __forceinline__ void gather_contract_lean_body(const float *__restric
         });
         return;
     }
-    consumer_f16<S, G, OUT_BCN, OS, ACC>(w - G::NP, thetaP, theta_exp_off, out, N, sc, tiles_per_cloud, s_A, s_E,
-                                         os_rt, acc_rt);
-}
-
-template <class S, bool OUT_BCN, int PM, int RS = S::DI, int OS = S::DO, bool ACC = false, bool TAIL = false>
-__global__ __launch_bounds__((WsGeom<S, PM>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void gather_contract_lean_kernel(const float *__restrict__ rows, const float *__restrict__ pos,
-                                 const int32_t *__restrict__ nbr, const void *__restrict__ thetaP,
-                                 int theta_exp_off, float *__restrict__ out, int N, int K,
-                                 int tiles_per_cloud, int total_tiles)
-{
-    gather_contract_lean_body<S, OUT_BCN, PM, RS, OS, ACC, TAIL>(rows, pos, nbr, thetaP, theta_exp_off, out, N, K,
-                                                                  tiles_per_cloud, TileSchedule(total_tiles), 0, 0,
-                                                                  false);
+    consumer_f16<S, G, OUT_BCN>(w - G::NP, thetaP, theta_exp_off, out, N, sc, tiles_per_cloud, s_A, s_E);
 }
 
 // Feature gradient with the lean in-edge producers (same consumers as the forward kernel).
-template <class S, bool OUT_BCN, int PM, int RS, int OS, bool ACC>
-__device__ __forceinline__ void grad_feat_lean_body(const float *__restrict__ rows, const float *__restrict__ pos,
-                                                    const int32_t *__restrict__ off, const int32_t *__restrict__ src,
-                                                    const int32_t *__restrict__ order,
-                                                    const void *__restrict__ thetaP, int theta_exp_off,
-                                                    float *__restrict__ out, int N, int tiles_per_cloud,
-                                                    const TileSchedule sc, int rs_rt, int os_rt, bool acc_rt)
+template <class S, bool OUT_BCN, int PM>
+__global__ __launch_bounds__((WsGeom<S, PM>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void grad_feat_lean_kernel(const float *__restrict__ rows, const float *__restrict__ pos,
+                           const int32_t *__restrict__ off, const int32_t *__restrict__ src,
+                           const int32_t *__restrict__ order,
+                           const void *__restrict__ thetaP, int theta_exp_off, float *__restrict__ out,
+                           int N, int tiles_per_cloud, int total_tiles)
 {
     using G = WsGeom<S, PM>;
     __shared__ __attribute__((aligned(16))) char s_A[2 * G::T * G::ROWB];
@@ -1381,6 +1354,7 @@ __device__ __forceinline__ void grad_feat_lean_body(const float *__restrict__ ro
     __shared__ int s_P[2 * G::T];       // the point in every tile slot (the tiles walk the cloud in `order`)
     __shared__ __attribute__((aligned(16))) float s_D[G::NP][128];     // per producer wave: a batch's position differences
 
+    const TileSchedule sc(total_tiles);
     const int w = threadIdx.x >> 6;
 
     if constexpr (G::KDP > S::KD) {
@@ -1393,10 +1367,9 @@ __device__ __forceinline__ void grad_feat_lean_body(const float *__restrict__ ro
     }
 
     if (w < G::NP) {
-        LeanCsrProducer<S, PM, false, RS, true> P;
+        LeanCsrProducer<S, PM, false, true> P;
         P.init(rows, pos, off, src, N, w, sc, tiles_per_cloud);
         P.order = order;
-        P.set_row_stride(rs_rt);
         P.set_dp_stage(s_D[w]);
         float rsc[S::VEC][4];
         load_row_scales<S>(rsc, thetaP, theta_exp_off, P.t);
@@ -1409,20 +1382,7 @@ __device__ __forceinline__ void grad_feat_lean_body(const float *__restrict__ ro
         });
         return;
     }
-    consumer_f16<S, G, OUT_BCN, OS, ACC, true>(w - G::NP, thetaP, theta_exp_off, out, N, sc, tiles_per_cloud, s_A, s_E,
-                                               os_rt, acc_rt, s_P);
-}
-
-template <class S, bool OUT_BCN, int PM, int RS = S::DI, int OS = S::DO, bool ACC = false>
-__global__ __launch_bounds__((WsGeom<S, PM>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void grad_feat_lean_kernel(const float *__restrict__ rows, const float *__restrict__ pos,
-                           const int32_t *__restrict__ off, const int32_t *__restrict__ src,
-                           const int32_t *__restrict__ order,
-                           const void *__restrict__ thetaP, int theta_exp_off, float *__restrict__ out,
-                           int N, int tiles_per_cloud, int total_tiles)
-{
-    grad_feat_lean_body<S, OUT_BCN, PM, RS, OS, ACC>(rows, pos, off, src, order, thetaP, theta_exp_off, out, N,
-                                                     tiles_per_cloud, TileSchedule(total_tiles), 0, 0, false);
+    consumer_f16<S, G, OUT_BCN, true>(w - G::NP, thetaP, theta_exp_off, out, N, sc, tiles_per_cloud, s_A, s_E, s_P);
 }
 
 template <class S, bool CSR, bool OUT_BCN, bool F16>
@@ -1701,8 +1661,7 @@ __device__ __forceinline__ bf8 read_tr_frag(const char *tile, int stride, int p0
     return __builtin_bit_cast(bf8, v);
 }
 
-// RS / GST = floats between consecutive rows of the gathered tensor / of the upstream gradient
-template <class S, int RS, int GST, bool TAIL>
+template <class S, bool TAIL>
 __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ rows, const float *__restrict__ pos,
                                                      const int32_t *__restrict__ nbr,
                                                      const float *__restrict__ g_rows, float *__restrict__ partial,
@@ -1719,7 +1678,7 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
     const int w = threadIdx.x >> 6;
 
     if (w < G::NP) {
-        LeanProducer<S, 2, false, RS, TAIL> P;
+        LeanProducer<S, 2, false, TAIL> P;
         P.init(rows, pos, nbr, N, K, w, sc, tiles_per_cloud);
         P.set_dp_stage(s_D[w]);
         // grad_out tile: T*DOP/4 four-float chunks over the producer threads, one tile ahead in registers
@@ -1734,7 +1693,7 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
                 const int pt = ch / CPR, o = 4 * (ch % CPR);
                 gv[c] = v4f{0.f, 0.f, 0.f, 0.f};
                 if (ch < G::T * CPR && l0 + pt < N) {        // points past the cloud contribute nothing
-                    const float *src = g_rows + ((int64_t)b * N + l0 + pt) * GST + o;
+                    const float *src = g_rows + ((int64_t)b * N + l0 + pt) * S::DO + o;
                     if constexpr (S::DO % 4 == 0) {
                         if (o < S::DO) gv[c] = *reinterpret_cast<const v4f *>(src);
                     } else {
@@ -1869,15 +1828,14 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
     }
 }
 
-// RS / GST = floats between consecutive rows of the gathered tensor / of the upstream gradient
-template <class S, int RS = S::DI, int GST = S::DO, bool TAIL = false>
+template <class S, bool TAIL = false>
 __global__ __launch_bounds__((WsGeom<S, 2, 2>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void grad_theta_lean_kernel(const float *__restrict__ rows, const float *__restrict__ pos,
                             const int32_t *__restrict__ nbr, const float *__restrict__ g_rows,
                             float *__restrict__ partials, int N, int K, int tiles_per_cloud, int total_tiles)
 {
-    grad_theta_lean_body<S, RS, GST, TAIL>(rows, pos, nbr, g_rows, partials + (int64_t)blockIdx.x * S::KD * S::DOP, N, K,
-                                           tiles_per_cloud, TileSchedule(total_tiles));
+    grad_theta_lean_body<S, TAIL>(rows, pos, nbr, g_rows, partials + (int64_t)blockIdx.x * S::KD * S::DOP, N, K,
+                                  tiles_per_cloud, TileSchedule(total_tiles));
 }
 
 // ---------------------------------------------------------------------------
@@ -2011,7 +1969,7 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
     __syncthreads();
 
     if (w < G::NP) {
-        LeanCsrProducer<S, 2, false, S::DI, true> P;
+        LeanCsrProducer<S, 2, false, true> P;
         P.init(g_rows, pos, off, src, N, w, sc, tiles_per_cloud);
         P.order = order;
         P.set_dp_stage(s_D[w]);
@@ -2080,9 +2038,9 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
         OwnRows hook;
         hook.own_rows = own_rows; hook.s_P = s_P; hook.s_E = s_E; hook.s_cs = s_cs; hook.s_F = s_F;
         hook.overflow = overflow; hook.N = N; hook.cw = w - G::NP; hook.lane = threadIdx.x & 63;
-        consumer_f16<S, G, OUT_BCN, S::DO, false, true, F::NBUF, OwnRows &, true>(w - G::NP, thetaP, theta_exp_off,
+        consumer_f16<S, G, OUT_BCN, true, F::NBUF, OwnRows &, true>(w - G::NP, thetaP, theta_exp_off,
                                                                                   grad_feat, N, sc, tiles_per_cloud,
-                                                                                  s_A, s_E, 0, false, s_P, hook);
+                                                                                  s_A, s_E, s_P, hook);
         if (any) __syncthreads();
         return;
     }
@@ -2285,7 +2243,7 @@ void grad_theta_lean_late_kernel(int *__restrict__ control, const float *__restr
         if (fused_result_resolved(control, rscale, grad_theta, grad_bias, Din, Dout, s_col)) return;
         if (threadIdx.x == 0) *control = FUSED_UNRESOLVED;
     }
-    grad_theta_lean_body<S, S::DI, S::DO, TAIL>(rows, pos, nbr, g_rows, partials + (int64_t)blockIdx.x * S::KD * S::DOP,
+    grad_theta_lean_body<S, TAIL>(rows, pos, nbr, g_rows, partials + (int64_t)blockIdx.x * S::KD * S::DOP,
                                                 N, K, tiles_per_cloud, TileSchedule(total_tiles));
 }
 
@@ -2408,7 +2366,7 @@ void grad_pos_kernel(const float *__restrict__ rows, const int32_t *__restrict__
                 load_y(nb, nlw0 - P.pw * G::PW);
             });
         } else {
-            LeanProducer<S, PM, true, S::DI, TAIL> P;
+            LeanProducer<S, PM, true, TAIL> P;
             P.init(rows, nullptr, nbr, N, K, w, sc, tiles_per_cloud);
             if (P.count > 0) {
                 int b0, lw00;
