@@ -3,14 +3,15 @@
 // result does not depend on the order in which atomics land (and so that
 // repeated sources sit next to each other).
 //
-// Two ways.  Up to EDGE_BUCKETS_MAX buckets (134 M edges): edges are first dealt
-// into buckets of consecutive target points, then each bucket is sorted in LDS
-// by one workgroup.  Global atomics per (workgroup, bucket) instead of per edge:
+// Two ways.  Up to EDGE_BUCKETS_MAX buckets (16384 << bucket_shift(K) points, 16.7 M
+// at K = 8): edges are first dealt into buckets of consecutive target points, then
+// each bucket is sorted in LDS by one workgroup.  Global atomics per (workgroup, bucket) instead of per edge:
 // a random-address atomic per edge (twice) and the scattered 4-byte writes behind
 // it were 600 us of the 650 us that 1M points x 8 neighbours in the sensor's
 // order took; this takes 85 us.  Beyond that: counting sort by target point with
 // an atomic per edge (count -> exclusive scan -> fill -> sort each list).
 #include "flex_common.hpp"
+#include <stdlib.h>
 
 namespace flex {
 
@@ -500,10 +501,16 @@ static int bucket_shift(int K)
     while (shift > 0 && ((int64_t)K << shift) > (1 << BUCKET_EDGES_LOG2)) --shift;
     return shift > 11 ? 11 : shift;               // BUCKET_TARGETS_MAX
 }
+// (FLEX_EDGE_BUCKETS in the environment lowers the most there may be: 0 = always the counting sort)
 static int64_t bucket_count(int64_t BN, int K)
 {
+    static const int most = [] {
+        const char *v = getenv("FLEX_EDGE_BUCKETS");
+        const int n = v ? atoi(v) : EDGE_BUCKETS_MAX;
+        return n >= 0 && n < EDGE_BUCKETS_MAX ? n : EDGE_BUCKETS_MAX;
+    }();
     const int64_t n = cdiv64(BN, (int64_t)1 << bucket_shift(K));
-    return n <= EDGE_BUCKETS_MAX ? n : 0;
+    return n <= most ? n : 0;
 }
 
 size_t inedges_ws_bytes(int64_t BN, int K)

@@ -338,3 +338,14 @@ def test_static_scratch_holds_wide_layers_whatever_the_cloud(L, Din, Dout):
     # channel-major ones beside the turned rows (and, as it has been, room for the result)
     N = ((2 << 20) - (Din // 64) * (Dout // 128) * 132608) // (4 * (Din + Dout)) - 1
     assert 0 < L.flexconv_workspace_bytes(0, 1, N, 8, Din, Dout, 0) <= 2 << 20
+
+
+def test_in_edge_lists_past_the_buckets(L):
+    # op 3: staged edges (6 bytes each) beside the buckets' counters up to 16384 << shift points (shift: targets whose K
+    # edges fill a bucket of 8192, at most 2048), a counter per point beyond
+    for K, most in ((8, 16384 << 10), (9, 16384 << 9), (3, 16384 << 11), (1, 16384 << 11)):
+        at, past = (L.flexconv_workspace_bytes(3, 1, n, K, 1, 1, 0) for n in (most, most + 1))
+        assert at >= 6 * K * most and past < 5 * most
+    small, none = (_query(env, [("flexconv_workspace_bytes", [3, 1, 100_000, 8, 1, 1, 0])])[0]
+                   for env in ({}, {"FLEX_EDGE_BUCKETS": "0"}))
+    assert small >= 6 * 800_000 and none < 5 * 100_000

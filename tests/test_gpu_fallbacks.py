@@ -19,6 +19,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
                          ids=["staged_producers", "fp32_contraction", "single_pass_128", "direct_form_kernels",
                               "separate_backward_kernels", "planned_pooling_at_every_size"])
 def test_parity_file_under_switch(env):
+    run_files(env)
+
+
+def run_files(env):
     child_env = dict(os.environ)
     child_env.update(env)
     files = [os.path.join(HERE, "test_gpu_parity.py")]
@@ -27,9 +31,17 @@ def test_parity_file_under_switch(env):
     if "FLEX_POOL_PLAN" in env:
         # the planned pooling kernel on the small and ragged clouds that it is otherwise not chosen for
         files = [os.path.join(HERE, "test_gpu_pool_plan.py")]
+    if "FLEX_EDGE_BUCKETS" in env:
+        files = [os.path.join(HERE, "test_gpu_inedges.py")]
     r = subprocess.run([sys.executable, "-u", "-m", "pytest", *files, "-x", "-q",
                         "-m", "gpu", "--timeout", "120", "--timeout-method", "thread", "-p", "no:cacheprovider"],
                        capture_output=True, text=True, env=child_env, cwd=os.path.dirname(HERE), timeout=600)
     tail = "\n".join((r.stdout + r.stderr).splitlines()[-15:])
     assert r.returncode == 0, tail
     assert " passed" in r.stdout, tail
+
+
+def test_in_edge_lists_by_counting_sort():
+    """The build that clouds of more buckets than the bucketed one has counters for take (at K = 8 past 16.7 M points): the
+    list tests, kept centres and a hub point among them, without buckets."""
+    run_files({"FLEX_EDGE_BUCKETS": "0"})
