@@ -76,8 +76,10 @@ typedef enum {
  * max(|value|, RMS of the same output channel), also when input channels (with the parameters
  * compensating) or output channels differ in scale by up to 2^24 (measured about 1e-6).  Not
  * covered: one input channel whose own values differ by more than 2^24 between the neighbours and
- * points that meet in one aggregate row; inputs with NaN / Inf.  The same holds for grad_feat of
- * flexconv_bwd.  grad_theta / grad_bias from the stand-alone kernel carry their operands exactly
+ * points that meet in one aggregate row; inputs with NaN / Inf.  Layers that gather more than 64
+ * channels (FLEX_ROUTE_TILE, _WIDE, _SPLIT128, _PADDED) scale every 64 of them by themselves, and
+ * add their shares in fp32.  FLEX_ROUTE_SINGLE_ROLE multiplies in fp32 instead of halves.  The same
+ * holds for grad_feat of flexconv_bwd.  grad_theta / grad_bias from the stand-alone kernel carry their operands exactly
  * (three bf16 pieces) and sum in fp32; on the one-pass route (FLEX_ROUTE_LEAN_FUSED) they are
  * contracted from the same f16 halves, with per-channel and per-point power-of-two scales, and the
  * call checks on the device whether the halves resolved the result (an overflowing feature row, or a
@@ -153,6 +155,8 @@ int flexconv_bwd_pos(const float *feat, const int32_t *nbr, const float *theta, 
  * g = b*N+m, in_src[in_off[g] .. in_off[g+1]) lists the centres l (per-cloud
  * indices, ascending, one entry per occurrence) with nbr[b,k,l] = m.
  * in_off has B*N+1 entries, in_src has B*K*N entries.
+ * The workspace holds every edge once more on its way (6 bytes each, 336 MB for 7 M points x 8; four
+ * bytes a point for clouds beyond 16384 << s points, s the largest with K << s <= 8192, at most 11).
  */
 int flex_inedges_build(const int32_t *nbr, int B, int N, int K,
                        int32_t *in_off, int32_t *in_src,
@@ -314,7 +318,8 @@ int flex_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int B, int N,
  * Cost: every query scans the cells around it, so M points at one location (or closer together than the
  * cell edge, about the mean spacing) cost M*M distance evaluations; meant for clouds without such piles.
  * pos [B,3,N] finite; nbr int32 [B,K,N] overwritten.  K in 1..10, 12, 16, 24 or 32, K <= N;
- * B <= 65535.  Workspace: flexconv_workspace_bytes(FLEX_OP_KNN, B, N, K, ...).
+ * B <= 65535.  Workspace: flexconv_workspace_bytes(FLEX_OP_KNN, B, N, K, ...): 24 bytes a point, the lists
+ * once more in the search's order, 8 bytes a grid cell (504 MB for 7 M points x 8).
  */
 int flex_knn(const float *pos, int32_t *nbr, int B, int N, int K,
              void *workspace, size_t workspace_bytes, void *stream);

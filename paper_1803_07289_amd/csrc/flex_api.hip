@@ -309,10 +309,10 @@ static hipError_t tile_launch(const TilePlan &p, const float *rows, int rs, int 
 // ---- rows of at most 16 channels ----------------------------------------------------------
 // rs: row stride.  Up to 16 channels, because there a lane per point was never the slower form and beyond it the 4 W sums
 // of a point do not fit a lane's registers.  us, forward / feature gradient (the wider sums in the other direction), on the
-// kernels these layers took before -> here: 1M points, K = 8: 3 and 32 channels 264 / 329 -> 59 / 171, 9 and 64
-// 169 / 308 -> 151 / 178, 16 and 64 219 / 339 -> 176 / 286; 100k points, K = 16: 9 and 64 35 / 58 -> 26 / 37, 16 and 64
-// 45 / 66 -> 30 / 56; 1k to 16k points, where a call is its launches: 17 / 19 -> 16 / 18 (16 channels backward 18 to 20
-// either way).
+// kernels that take these layers otherwise -> here.  1M points, K = 8: 9 and 64 (lean) 173 / 332 -> 130 / 175, 3 and 32
+// (zero-padded on the lean kernels) 307 / 645 -> 55 / 164, 16 and 64 (tiles) 251 / 348 -> 158 / 278; 100k points, K = 16:
+// 9 and 64 39 / 68 -> 26 / 38, 16 and 64 49 / 70 -> 29 / 58; 1k to 16k points, where a call is its launches, 18 / 19
+// either way.
 static bool use_narrow(int64_t N, int w_in, int rs) { return w_in <= 16 && tile_ok(N, rs); }
 static int narrow_rp(int w_in) { return w_in <= 8 ? 8 : 16; }
 static int narrow_blocks(int w_out) { return (w_out + 63) / 64; }
@@ -742,7 +742,7 @@ int flexconv_fwd_noalloc(const float *feat, const float *pos, const int32_t *nbr
     const int st = static_scratch(&ws);
     if (st != FLEX_OK) return st;
     // Every byte of the plan that a kernel reads is written earlier in the same call (packed parameters with their
-    // padding, exponent tables, padded copies after an explicit zero fill), so nothing has to be cleared here.
+    // padding, exponent tables, turned and padded copies with their zeros), so nothing has to be cleared here.
     return flexconv_fwd(feat, pos, nbr, theta, bias, out, B, N, K, Din, Dout, layout, ws, need, stream);
 }
 

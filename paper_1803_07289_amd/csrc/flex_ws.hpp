@@ -95,7 +95,7 @@ __device__ __forceinline__ float fmax3_abs(float m, float a, float b)
 }
 
 // The depth scales of the packed parameters that belong to this lane's aggregate elements (channels VEC*t..,
-// all four j): rs[v][j] = rscale[j*DIP + VEC*t + v], see pack_theta_f16_block.  thetaP: the packed buffer.
+// all four j): rs[v][j] = rscale[j*DIP + VEC*t + v], see flex_prep.hip.  thetaP: the packed buffer.
 template <class S>
 __device__ __forceinline__ void load_row_scales(float (&rs)[S::VEC][4], const void *thetaP, int theta_exp_off, int t)
 {
@@ -418,7 +418,7 @@ struct Producer {
 
     // Finish tile r (buffer P, issued one iteration ago): aggregate -> sA rows of this wave.
     // F16 == false: fp32 rows of AST floats.  F16 == true: split-half rows (WsGeom::ARS bytes)
-    // scaled per point by 2^e, e stored in sE[point] (see pack_theta_f16_kernel for the split).
+    // scaled per point by 2^e, e stored in sE[point] (flex_prep.hip has the split).
     template <int P, bool F16>
     __device__ __forceinline__ void finish(const TileRef &r, int offs, char *sA, int *sE)
     {
@@ -854,7 +854,7 @@ struct LeanProducer {
 // ---------------------------------------------------------------------------
 // ORD: the tiles walk the cloud in the order given by `order` (order[b*N + p] = the point at position p, a
 // permutation of the cloud's points that puts points of equal list length next to each other inside windows of
-// nearby points, see inedge_order_kernel): the four points of a wave then have lists of (nearly) the same length
+// nearby points, see order_window in flex_prep.hip): the four points of a wave then have lists of (nearly) the same length
 // and so have the twelve waves of a tile, so hardly any slot of a batch is empty and no wave waits at the tile's
 // barrier for one with a longer list.  The points' ids travel with the tile (s_P) to the consumers' stores.
 template <class S, int PM, bool SUM = false, bool ORD = false>
