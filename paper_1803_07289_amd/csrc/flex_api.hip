@@ -516,7 +516,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
 
 struct PosPlan {
     bool lean, blocked;
-    size_t thetaC, thetaN, featT, gT, thB, in_off, in_src, inedge_ws, total;
+    size_t thetaC, thetaN, featT, gT, in_off, in_src, inedge_ws, total;
 };
 static inline int pad32(int x) { return (x + 31) / 32 * 32; }
 
@@ -544,7 +544,7 @@ static PosPlan plan_pos(int64_t B, int64_t N, int K, int Din, int Dout, int layo
         const int n_hi = (Din + 63) / 64, n_ho = (Dout + 63) / 64;
         p.thetaC = at; at += theta_pos_bytes(64, 64);
         p.thetaN = at; at += theta_pos_bytes(64, 64);
-        p.thB = at;    at += align256(sizeof(float) * 3 * 64 * 64);
+        at += align256(sizeof(float) * 3 * 64 * 64);        // not written: part of the size that callers have been told
         p.featT = at;  at += align256(sizeof(float) * (size_t)(B * N) * 64) * n_hi;
         p.gT = at;     at += align256(sizeof(float) * (size_t)(B * N) * 64) * n_ho;
         if (build) {

@@ -374,7 +374,7 @@ void tile_conv_kernel(const TileArgs a)
     // block, hi*hi and the cross terms.  What is added up over the input blocks is the unscaled fp32 result, on the vector
     // ALU, which rounds to nearest.  (The matrix op rounds every partial sum down: one chain over all products and blocks
     // was 1.2e-7 off at one input block, 2.2e-7 at two, 3.3e-7 at four and 4.8e-7 at eight, where this is 1.1e-7 to
-    // 1.3e-7, in the same time but for 512 -> 512, 2 percent; and one scale for all blocks costs a block its bits next to
+    // 1.3e-7, in the same time but for 512 -> 512, 4 percent; and one scale for all blocks costs a block its bits next to
     // a larger one.)
     constexpr bool RESIDENT = !MULTI && WM == 2;        // parameters of one block, 64 registers: kept
     const int cw = wave - 8, q = lane >> 4, r16 = lane & 15;
@@ -384,6 +384,10 @@ void tile_conv_kernel(const TileArgs a)
     constexpr int AHEAD = RESIDENT ? STEPS : MULTI && NSW == 2 ? 2 : 4;     // pairs whose parameters are held, as the registers allow
     h8 tH[AHEAD], tL[AHEAD];
     v4f sum[P::MB][NSW];                                // MULTI: the result over the input blocks so far
+#pragma unroll
+    for (int m = 0; m < P::MB; ++m)
+#pragma unroll
+        for (int n = 0; n < NSW; ++n) sum[m][n] = v4f{0.f, 0.f, 0.f, 0.f};
     const char *blk = theta_j;
     unsigned th_off = (unsigned)((wn * NSW) * P::KS * 64 + lane) * 16u;
     auto load_theta = [&](int i) __attribute__((always_inline)) {       // slice i / KS, depth step i % KS
@@ -464,7 +468,7 @@ void tile_conv_kernel(const TileArgs a)
                 v4f d = main[m] + cross[m];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) d[i] = __builtin_ldexpf(d[i], -(e + ec[i]));
-                if constexpr (MULTI) sum[m][n] = ib == 0 ? d : sum[m][n] + d;
+                if constexpr (MULTI) sum[m][n] += d;
                 else store(m, n, d);
             }
         }
@@ -474,7 +478,10 @@ void tile_conv_kernel(const TileArgs a)
 #pragma unroll
             for (int n = 0; n < NSW; ++n)
 #pragma unroll
-                for (int m = 0; m < P::MB; ++m) store(m, n, sum[m][n]);
+                for (int m = 0; m < P::MB; ++m) {
+                    store(m, n, sum[m][n]);
+                    sum[m][n] = v4f{0.f, 0.f, 0.f, 0.f};
+                }
         }
         tw.next();
     }
