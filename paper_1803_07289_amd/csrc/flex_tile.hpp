@@ -9,9 +9,9 @@
 // sums kept in the contracting waves' registers, so a row is gathered once per OUTW output channels (up to 256) and
 // nothing but the result leaves the chip.
 //
-// The kernels of flex_ws.hpp keep their parameters in registers whatever the width and walk a wide layer in passes over
-// the whole cloud, adding to the output in memory, with 32-point tiles; their gathering waves spend some 540
-// instructions on four points.  Here parameters of more than one input block stream from L2, 64 points to a pass, and
+// The kernels of flex_ws.hpp keep their parameters in registers whatever the width: a wide layer would walk the whole
+// cloud with them once per 64 input channels, adding to the output in memory, on 32-point tiles; their gathering waves
+// spend some 540 instructions on four points.  Here parameters of more than one input block stream from L2, 64 points to a pass, and
 // what a lane needs to gather a row -- the position difference and the row's offset -- is prepared one entry per lane
 // (eight slots of the wave's eight points: a step) and a step ahead, through LDS: 300 instructions per four points.
 // Both matter because a wave issues at most one instruction per five clocks.

@@ -1763,7 +1763,7 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
     const int lane = threadIdx.x & 63, q = lane >> 4, r16 = lane & 15;
     const int wn = cw % WN, wm = cw / WN;
 
-    // The matrix op's internal accumulation rounds toward zero, a bias that would grow with the
+    // The matrix op rounds its partial sums down, a bias that would grow with the
     // thousands of tiles a workgroup sums; so its accumulators (acc) only ever hold FLUSH tiles and
     // are then added to the running totals (tot) on the vector ALU, which rounds to nearest.
     constexpr int FLUSH = 8;
@@ -1862,7 +1862,7 @@ void grad_theta_lean_kernel(const float *__restrict__ rows, const float *__restr
 // (fused_result_resolved).
 // Pipeline: producers fill tile k+1 while the Theta^T waves contract tile k and fetch, scale and split the own rows
 // of tile k (ids and exponents are known only once the tile is complete) and the T waves contract tile k-1; hence
-// three tile buffers and one trailing barrier.  The matrix op accumulates with round-toward-zero, so the T waves add their
+// three tile buffers and one trailing barrier.  The matrix op rounds its partial sums down, so the T waves add their
 // accumulators to the workgroup's partial in global memory (each lane its own elements, so no ordering issue) every
 // FLUSH tiles.  Partial layout = that of grad_theta_lean_kernel: [(j, c)][o], one per workgroup.
 // S = (gathered width = the layer's Dout, output width = the layer's Din).
