@@ -100,3 +100,35 @@ def test_error_of_the_parameter_gradients(N, C, adds):
     err = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
     say(f"{N} points {C}->{C}: 2-norm rel err of the parameter gradients {err:.2e}")
     assert err <= bound, (err, bound)
+
+
+def test_replays_of_a_captured_wide_layer():
+    """Forward and all gradients of a layer whose parameter gradients' totals move to the partials in memory (more than 64
+    tiles per workgroup), in a graph: every replay gives the eager call's bits, with eager work in between."""
+    N, C = 20_000, 512
+    rng = np.random.default_rng(3)
+    pos = dev(rng.random((1, 3, N), dtype=np.float32))
+    nbr = dev(((np.arange(N)[None, None] + rng.integers(-20, 21, size=(1, 8, N))) % N).astype(np.int32))
+    feat, g = (dev(rng.standard_normal((1, N, C), dtype=np.float32)) for _ in range(2))
+    theta, bias = dev(rng.standard_normal((3, C, C), dtype=np.float32)), dev(rng.standard_normal((C, C), dtype=np.float32))
+    edges = fx.flex_inedges_build(nbr)
+    ws = [torch.empty(fx.workspace_bytes(op, 1, N, 8, C, C, fx.BNC), dtype=torch.uint8, device="cuda")
+          for op in (fx.OP_CONV_FWD, fx.OP_CONV_BWD)]
+
+    def step():
+        return (fx.flexconv_fwd(feat, pos, nbr, theta, bias, layout=fx.BNC, workspace=ws[0]),
+                *fx.flexconv_bwd(feat, pos, nbr, theta, bias, g, layout=fx.BNC, in_edges=edges, workspace=ws[1]))
+
+    want = [t.clone() for t in step()]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        outs = step()
+    for r in range(3):
+        say(f"replay {r}")
+        for t in (*outs, *ws):
+            t.fill_(7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs, want))
+        assert all(torch.equal(a, b) for a, b in zip(step(), want))
