@@ -395,6 +395,10 @@ int flex_validate_selection(const int32_t *sel, int B, int Ns, int Nf, int32_t *
 
 /* Bytes of workspace needed by op (a flex_op) at these sizes. 0 on bad sizes. */
 size_t flexconv_workspace_bytes(int op, int B, int N, int K, int Din, int Dout, int layout);
+/* Bytes of workspace with which op runs fastest: at least flexconv_workspace_bytes.  The convolution's forward and
+ * backward pass use what lies beyond for the point locations as 16-byte records (a gather of neighbours' locations then
+ * touches one cache line per neighbour, not three); results are the same bits either way. */
+size_t flexconv_workspace_bytes_best(int op, int B, int N, int K, int Din, int Dout, int layout);
 
 /* Debug aid: *bad_count_dev (device int32) = number of nbr entries outside [0,N). */
 int flex_validate_neighbors(const int32_t *nbr, int B, int N, int K,

@@ -52,6 +52,7 @@ _SIGS = {
     "flexupsample_bwd": (_i, [_vp] * 6 + [_i] * 6 + [_vp]),
     "flex_validate_selection": (_i, [_vp, _i, _i, _i, _vp, _vp, _sz, _vp]),
     "flexconv_workspace_bytes": (_sz, [_i] * 7),
+    "flexconv_workspace_bytes_best": (_sz, [_i] * 7),
     "flex_validate_neighbors": (_i, [_vp, _i, _i, _i, _vp, _vp]),
     "flexconv_has_fast_path": (_i, [_i, _i]),
     "flexconv_kernel_route": (_i, [_i] * 7),
@@ -127,6 +128,11 @@ def workspace_bytes(op, B, N, K, Din, Dout, layout=BCN):
     return int(lib().flexconv_workspace_bytes(op, B, N, K, Din, Dout, _layout(layout)))
 
 
+def _best_bytes(op, B, N, K, Din, Dout, layout):
+    """What the binding's own workspace has room for: the size with which the call runs fastest."""
+    return int(lib().flexconv_workspace_bytes_best(op, B, N, K, Din, Dout, layout))
+
+
 def _workspace(device, nbytes):
     """A cached, grow-only scratch tensor per device (256-byte aligned by the allocator)."""
     key = (device.type, device.index)
@@ -169,7 +175,7 @@ def flexconv_fwd(feat, pos, nbr, theta, bias, layout=BCN, out=None, workspace=No
         out = torch.empty(shape, dtype=torch.float32, device=feat.device)
     elif tuple(_dev(out, torch.float32, "out").shape) != shape:
         raise ValueError("out has the wrong shape")
-    need = workspace_bytes(OP_CONV_FWD, B, N, K, Din, Dout, layout)
+    need = _best_bytes(OP_CONV_FWD, B, N, K, Din, Dout, layout)
     ws, ws_bytes = _ws_arg(workspace, feat.device, need)
     _check(lib().flexconv_fwd(_ptr(feat), _ptr(pos), _ptr(nbr), _ptr(theta), _ptr(bias), _ptr(out),
                               B, N, K, Din, Dout, layout, _ptr(ws), ws_bytes, _stream()), "flexconv_fwd")
@@ -236,7 +242,7 @@ def flexconv_bwd(feat, pos, nbr, theta, bias, grad_out, layout=BCN, in_edges=Non
         if off.numel() != B * N + 1 or src.numel() != B * K * N:
             raise ValueError("in_edges do not match nbr")
     op = OP_CONV_BWD if in_edges is not None else OP_CONV_BWD_BUILD
-    need = workspace_bytes(op, B, N, K, Din, Dout, layout)
+    need = _best_bytes(op, B, N, K, Din, Dout, layout)
     ws, ws_bytes = _ws_arg(workspace, feat.device, need)
     _check(lib().flexconv_bwd(_ptr(feat), _ptr(pos), _ptr(nbr), _ptr(theta), _ptr(bias), _ptr(grad_out),
                               _ptr(gf), _ptr(gt), _ptr(gb), _ptr(off), _ptr(src),

@@ -9,7 +9,7 @@ namespace flex {
 
 // ---- per-shape launchers generated from flex_shapes.def ------------------------
 #define FLEX_SHAPE(DI, DO, W, T, OCC, WS)                                                             \
-    hipError_t launch_gc_##DI##_##DO(const float *, const float *, const int32_t *, const int32_t *, \
+    hipError_t launch_gc_##DI##_##DO(const float *, const float *, const PosRef &, const int32_t *, const int32_t *, \
                                      const int32_t *, const int32_t *, const void *, int, float *, int, int, int, \
                                      int, int, hipStream_t);                                         \
     int theta_format_##DI##_##DO(int, int, int);                                                       \
@@ -18,18 +18,18 @@ namespace flex {
     hipError_t launch_gp_##DI##_##DO(const float *, const int32_t *, const int32_t *, const int32_t *, \
                                      const void *, const float *, float *, float, int, int, int, int,  \
                                      int, hipStream_t);                                                        \
-    hipError_t launch_gt_##DI##_##DO(const float *, const float *, const int32_t *, const float *,   \
+    hipError_t launch_gt_##DI##_##DO(const float *, const float *, const PosRef &, const int32_t *, const float *, \
                                      float *, int, int, int, int *, hipStream_t);
 #include "flex_shapes.def"
 #undef FLEX_SHAPE
 
 // 64 -> 64 layers: feature and parameter gradients in one pass over the in-edge lists (flex_tiled_inst.hip, shape 64x64)
 bool bwd_fused_ok_64_64(int N, int K);
-hipError_t launch_bwd_fused_64_64(const float *g_rows, const float *own_rows, const float *pos, const int32_t *nbr,
+hipError_t launch_bwd_fused_64_64(const float *g_rows, const float *own_rows, const PosRef &pos, const int32_t *nbr,
                                   const int32_t *off, const int32_t *src, const int32_t *order, const void *thetaP,
                                   float *grad_feat, float *partials, int *control, int B, int N, int K, int out_bcn,
                                   int *n_wg, hipStream_t s);
-hipError_t launch_bwd_fused_late_64_64(const float *g_rows, const float *own_rows, const float *pos,
+hipError_t launch_bwd_fused_late_64_64(const float *g_rows, const float *own_rows, const PosRef &pos,
                                        const int32_t *nbr, const void *thetaP, const float *grad_theta,
                                        const float *grad_bias, int Din, int Dout, float *partials, int *control, int B,
                                        int N, int K, hipStream_t s);
@@ -57,14 +57,14 @@ bool gather_contract_supported(int DI, int DO)
     return false;
 }
 
-hipError_t launch_gather_contract(const float *rows, const float *pos, const int32_t *nbr,
+hipError_t launch_gather_contract(const float *rows, const float *pos, const PosRef &pr, const int32_t *nbr,
                                   const int32_t *off, const int32_t *src, const int32_t *order, const void *thetaP,
                                   int theta_fmt, float *out, int B, int N, int K, int DI, int DO,
                                   int csr, int out_bcn, hipStream_t s)
 {
 #define FLEX_SHAPE(DI_, DO_, W, T, OCC, WS) \
     if (DI == DI_ && DO == DO_)         \
-        return launch_gc_##DI_##_##DO_(rows, pos, nbr, off, src, order, thetaP, theta_fmt, out, B, N, K, csr, out_bcn, s);
+        return launch_gc_##DI_##_##DO_(rows, pos, pr, nbr, off, src, order, thetaP, theta_fmt, out, B, N, K, csr, out_bcn, s);
 #include "flex_shapes.def"
 #undef FLEX_SHAPE
     return hipErrorNotSupported;
@@ -225,7 +225,7 @@ size_t grad_theta_partial_bytes(int64_t B, int64_t N, int Din, int Dout)
 }
 
 // (Dki, Dko): the widths of the rows, which may be padded; (Din, Dout): the parameters'.
-static hipError_t launch_grad_theta(const float *rows, const float *pos, const int32_t *nbr, const float *g_rows,
+static hipError_t launch_grad_theta(const float *rows, const float *pos, const PosRef &pr, const int32_t *nbr, const float *g_rows,
                                     float *partials, float *grad_theta, float *grad_bias, int B, int N, int K, int Dki,
                                     int Dko, int Din, int Dout, hipStream_t s)
 {
@@ -233,7 +233,7 @@ static hipError_t launch_grad_theta(const float *rows, const float *pos, const i
     hipError_t e = hipErrorNotSupported;
 #define FLEX_SHAPE(DI_, DO_, W, T, OCC, WS)                                                    \
     if (Dki == DI_ && Dko == DO_)                                                         \
-        e = launch_gt_##DI_##_##DO_(rows, pos, nbr, g_rows, partials, B, N, K, &n_wg, s);
+        e = launch_gt_##DI_##_##DO_(rows, pos, pr, nbr, g_rows, partials, B, N, K, &n_wg, s);
 #include "flex_shapes.def"
 #undef FLEX_SHAPE
     if (e != hipSuccess) return e;
@@ -389,7 +389,7 @@ static hipError_t gather_pack(PrepList &prep, const GatherPlan &g, const float *
 }
 
 // rows [B*N, rs] onto out [B, N, w_out] or, out_bcn, [B, w_out, N]; on the listed widths' kernels rs = k_in, w_out = k_out
-static hipError_t gather_launch(const GatherPlan &g, const float *rows, int rs, int w_in, const float *pos,
+static hipError_t gather_launch(const GatherPlan &g, const float *rows, int rs, int w_in, const float *pos, const PosRef &pr,
                                 const int32_t *nbr, const int32_t *off, const int32_t *src, const int32_t *order,
                                 const void *thetaP, float *out, int w_out, int out_bcn, int B, int N, int K,
                                 hipStream_t s)
@@ -398,7 +398,7 @@ static hipError_t gather_launch(const GatherPlan &g, const float *rows, int rs, 
         return narrow_launch(rows, rs, w_in, pos, nbr, off, src, order, thetaP, out, w_out, out_bcn, B, N, K, s);
     if (g.route == FLEX_ROUTE_TILE)
         return tile_launch(g.tile, rows, rs, w_in, pos, nbr, off, src, order, thetaP, out, w_out, out_bcn, B, N, K, s);
-    return launch_gather_contract(rows, pos, nbr, off, src, order, thetaP, g.fmt, out, B, N, K, rs, w_out, off != nullptr,
+    return launch_gather_contract(rows, pos, pr, nbr, off, src, order, thetaP, g.fmt, out, B, N, K, rs, w_out, off != nullptr,
                                   out_bcn, s);
 }
 
@@ -435,12 +435,27 @@ static bool padded_shape(int Din, int Dout, int *DIp, int *DOp)
 
 static size_t rows_bytes(int64_t B, int64_t N, int width) { return align256(sizeof(float) * (size_t)(B * N) * width); }
 
+// Room for packed point locations (PosRef) behind a plan's own bytes: a call whose workspace has it reads the locations
+// as records, any other reads the tensor.  The results are the same bits.
+struct PosPack {
+    size_t at, best;                     // where they go; the workspace that has room for them (the plan's own: no use for them)
+    bool fits(size_t have) const { return at != 0 && have >= best; }
+};
+static PosPack plan_pos_pack(int64_t B, int64_t N, int route, size_t total)
+{
+    const bool use = route == FLEX_ROUTE_LEAN && N * 16 < (1ll << 32);
+    if (!use) return PosPack{0, total};
+    const size_t at = align256(total);
+    return PosPack{at, at + align256((size_t)(B * N) * 16)};
+}
+
 struct FwdPlan {
     bool direct, padded, wide;
     int k_in, k_out;                     // the listed widths: the tensors' own unless padded
     GatherPlan gather;
     bool copy, copy_out;                 // rows are copied (turned round, padded); the result comes from a padded one
     size_t thetaP, rows, out, total;     // byte offsets / total
+    PosPack pos;
 };
 struct BwdPlan {
     bool direct, padded, wide;
@@ -449,6 +464,7 @@ struct BwdPlan {
     bool copy, copy_out;
     bool fused;      // feature and parameter gradients, when both are asked for, come from the one-pass kernel
     size_t thetaP, featT, gT, gfP, partials, order, flag, in_off, in_src, inedge_ws, total;
+    PosPack pos;
 };
 
 static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layout)
@@ -464,6 +480,7 @@ static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     const size_t copies = p.padded ? rows_bytes(B, N, p.k_in) + align256(sizeof(float) * (size_t)4 * p.k_in * p.k_out) +
                                          rows_bytes(B, N, p.k_out) : 0;
     p.total = copies + 256;
+    p.pos = PosPack{0, p.total};
     if (p.direct) return p;
     const bool bcn = layout == FLEX_LAYOUT_BCN;
     // a call whose parameters can be packed into the static scratch beside the turned rows is one that it takes
@@ -479,6 +496,7 @@ static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     if (p.padded)
         at = std::max(at, copies + (p.wide ? wide_packed_bytes(p.k_in, p.k_out) : theta_ws_bytes(p.k_in, p.k_out)));
     p.total = at;
+    p.pos = plan_pos_pack(B, N, p.gather.route, at);
     return p;
 }
 
@@ -490,6 +508,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     p.wide = wide_ok(N, K, p.k_in, p.k_out);
     p.direct = !p.wide && !(gather_contract_supported(p.k_in, p.k_out) && gather_contract_supported(p.k_out, p.k_in));
     p.total = 256;
+    p.pos = PosPack{0, p.total};
     if (p.direct) return p;
     p.gather = plan_gather(B, N, K, Dout, Din, p.k_out, p.k_out, p.k_in, p.padded, 1, SIZE_MAX);
     p.copy = p.padded || layout == FLEX_LAYOUT_BCN;          // the parameter gradients run at the listed widths
@@ -511,6 +530,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
         p.inedge_ws = at; at += inedges_ws_bytes(B * N, K);
     }
     p.total = at;
+    p.pos = plan_pos_pack(B, N, p.gather.route, at);
     return p;
 }
 
@@ -662,6 +682,15 @@ size_t flexconv_workspace_bytes(int op, int B, int N, int K, int Din, int Dout, 
     }
 }
 
+size_t flexconv_workspace_bytes_best(int op, int B, int N, int K, int Din, int Dout, int layout)
+{
+    const bool conv = op == FLEX_OP_CONV_FWD || op == FLEX_OP_CONV_BWD || op == FLEX_OP_CONV_BWD_BUILD;
+    if (!conv || (layout != FLEX_LAYOUT_BCN && layout != FLEX_LAYOUT_BNC) || !sizes_ok(B, N, K, Din, Dout))
+        return flexconv_workspace_bytes(op, B, N, K, Din, Dout, layout);
+    if (op == FLEX_OP_CONV_FWD) return plan_fwd(B, N, K, Din, Dout, layout).pos.best;
+    return plan_bwd(B, N, K, Din, Dout, layout, op == FLEX_OP_CONV_BWD_BUILD).pos.best;
+}
+
 int flexconv_fwd(const float *feat, const float *pos, const int32_t *nbr, const float *theta,
                  const float *bias, float *out, int B, int N, int K, int Din, int Dout, int layout,
                  void *workspace, size_t workspace_bytes, void *stream)
@@ -688,9 +717,11 @@ int flexconv_fwd(const float *feat, const float *pos, const int32_t *nbr, const 
     }
     void *thetaP = ws + p.thetaP;
     FLEX_HIP(gather_pack(prep, p.gather, theta, bias, thetaP, Din, Dout, p.k_in, p.k_out, 0, s));
+    const PosRef pr = p.pos.fits(workspace_bytes) ? pos_packed((const float *)(ws + p.pos.at), N) : pos_planar(pos, N);
+    if (pr.p != pos) prep.pack_pos(pos, (float *)(ws + p.pos.at), B, N);
     FLEX_HIP(prep.launch(s));
     float *dst = p.copy_out ? (float *)(ws + p.out) : out;
-    FLEX_HIP(gather_launch(p.gather, rows, w_in, w_in, pos, nbr, nullptr, nullptr, nullptr, thetaP, dst, w_out,
+    FLEX_HIP(gather_launch(p.gather, rows, w_in, w_in, pos, pr, nbr, nullptr, nullptr, nullptr, thetaP, dst, w_out,
                            bcn && !p.copy_out, B, N, K, s));
     if (p.copy_out) FLEX_HIP(launch_copy_rows(dst, out, B, N, p.k_out, Dout, 0, bcn, s));
     return FLEX_OK;
@@ -801,15 +832,17 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
         prep.order(in_off, B, N, order);
     }
     if (fused) prep.clear(control, FUSED_FLAG_INTS);
+    const PosRef pr = p.pos.fits(workspace_bytes) ? pos_packed((const float *)(ws + p.pos.at), N) : pos_planar(pos, N);
+    if (pr.p != pos) prep.pack_pos(pos, (float *)(ws + p.pos.at), B, N);
     FLEX_HIP(prep.launch(s));
     if (fused) {
         int n_wg = 0;
-        FLEX_HIP(launch_bwd_fused_64_64(g_rows, rows, pos, nbr, in_off, in_src, order, thetaP, grad_feat, partials, control,
+        FLEX_HIP(launch_bwd_fused_64_64(g_rows, rows, pr, nbr, in_off, in_src, order, thetaP, grad_feat, partials, control,
                                         B, N, K, bcn, &n_wg, s));
         FLEX_HIP(launch_reduce_partials_fused(partials, n_wg, control, Din, Dout, grad_theta, grad_bias, s));
         // is the result resolved by the f16 halves, and did no row overflow them?  if not (decided on the device), the
         // stand-alone kernel and a second reduction run; both return at once otherwise
-        FLEX_HIP(launch_bwd_fused_late_64_64(g_rows, rows, pos, nbr, thetaP, grad_theta, grad_bias, Din, Dout, partials,
+        FLEX_HIP(launch_bwd_fused_late_64_64(g_rows, rows, pr, nbr, thetaP, grad_theta, grad_bias, Din, Dout, partials,
                                              control, B, N, K, s));
         FLEX_HIP(launch_reduce_partials_if(control, partials, n_wg, 64, 64, Din, Dout, grad_theta, grad_bias, s));
         return FLEX_OK;
@@ -818,11 +851,11 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
         FLEX_HIP(wide_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, p.k_in, p.k_out, Din,
                                  Dout, s));
     else if (grad_theta)
-        FLEX_HIP(launch_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, p.k_in, p.k_out, Din,
+        FLEX_HIP(launch_grad_theta(rows, pos, pr, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, p.k_in, p.k_out, Din,
                                    Dout, s));
     if (!grad_feat) return FLEX_OK;
     float *dst = p.copy_out ? (float *)(ws + p.gfP) : grad_feat;
-    FLEX_HIP(gather_launch(p.gather, g_rows, p.k_out, p.gather.own_widths() ? Dout : p.k_out, pos, nullptr, in_off, in_src,
+    FLEX_HIP(gather_launch(p.gather, g_rows, p.k_out, p.gather.own_widths() ? Dout : p.k_out, pos, pr, nullptr, in_off, in_src,
                            order, thetaP, dst, p.copy_out ? p.k_in : Din, bcn && !p.copy_out, B, N, K, s));
     if (p.copy_out) FLEX_HIP(launch_copy_rows(dst, grad_feat, B, N, p.k_in, Din, 0, bcn, s));
     return FLEX_OK;

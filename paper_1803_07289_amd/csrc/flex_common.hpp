@@ -55,6 +55,8 @@ struct PrepList {
     void order(const int32_t *in_off, int B, int N, int32_t *order);
     // dst[b, n, c] = src[b, n, c_off + c] where that channel exists, else 0 (c < Cd); *_bcn: that tensor is channel-major
     void copy(const float *src, float *dst, int B, int N, int Cs, int Cd, int src_bcn, int dst_bcn, int c_off = 0);
+    // pos4[b*N + n] = (x, y, z, 0)
+    void pack_pos(const float *pos, float *pos4, int B, int N);
     void clear(void *dst, int words);
     hipError_t launch(hipStream_t s);
 };
@@ -95,6 +97,17 @@ hipError_t launch_generic_bwd_pos(const float *feat, const int32_t *nbr, const f
 hipError_t launch_copy_rows(const float *src, float *dst, int B, int N, int Cs, int Cd, int src_bcn, int dst_bcn,
                             hipStream_t s, int c_off = 0);
 
+// Point locations as the lean and tile kernels read them: the tensor [B,3,N] itself, or packed as (x, y, z, 0) records
+// (PrepList::pack_pos).  A component's byte offset inside a cloud is (point << shift) + component * col.
+struct PosRef {
+    const float *p;
+    unsigned col;            // bytes from component to component
+    int shift;               // log2 of the bytes from point to point
+    int64_t cloud;           // bytes from cloud to cloud
+};
+inline PosRef pos_planar(const float *pos, int N) { return PosRef{pos, 4u * (unsigned)N, 2, 12 * (int64_t)N}; }
+inline PosRef pos_packed(const float *pos4, int N) { return PosRef{pos4, 4u, 4, 16 * (int64_t)N}; }
+
 // Tiled matrix-core path.  `rows` is point-major [B*N, DI].  Returns
 // hipErrorNotSupported when (DI,DO) has no instantiation.
 //   csr == 0: neighbours from nbr [B,K,N], dp = pos[nbr]-pos[centre]
@@ -103,7 +116,7 @@ hipError_t launch_copy_rows(const float *src, float *dst, int B, int N, int Cs, 
 //   (DI, DO, N, K, csr): 0 = fp32 ThetaP (launch_pack_theta), 1 = split-half fragments
 //   (PrepList::pack_theta).
 //   order (csr == 1 only): the walking order of these lists (PrepList::order)
-hipError_t launch_gather_contract(const float *rows, const float *pos, const int32_t *nbr,
+hipError_t launch_gather_contract(const float *rows, const float *pos, const PosRef &pr, const int32_t *nbr,
                                   const int32_t *off, const int32_t *src, const int32_t *order,
                                   const void *thetaP, int theta_fmt, float *out, int B, int N, int K, int DI,
                                   int DO, int csr, int out_bcn, hipStream_t s);

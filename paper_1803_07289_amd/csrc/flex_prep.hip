@@ -461,6 +461,26 @@ __device__ void copy_tile(const float *__restrict__ src, float *__restrict__ dst
     }
 }
 
+// ---- point locations as records ---------------------------------------------------------------------
+// pos4[b*N + n] = (x, y, z, 0).  A gather asks the texture path for a cache line per quarter wave and component out of
+// [B,3,N], for one per point out of these.
+static constexpr int POINTS_PER_THREAD = 4;
+
+__device__ void pack_points(const float *__restrict__ pos, float *__restrict__ pos4, int N, int bpc, int block)
+{
+    const int b = block / bpc, n0 = (block - b * bpc) * (PREP_NT * POINTS_PER_THREAD) + threadIdx.x;
+    const float *p = pos + (int64_t)b * 3 * N;
+    v4f *dst = reinterpret_cast<v4f *>(pos4) + (int64_t)b * N;
+    float x[POINTS_PER_THREAD][3];
+#pragma unroll
+    for (int i = 0; i < POINTS_PER_THREAD; ++i)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) x[i][d] = p[(int64_t)d * N + min(n0 + PREP_NT * i, N - 1)];
+#pragma unroll
+    for (int i = 0; i < POINTS_PER_THREAD; ++i)
+        if (n0 + PREP_NT * i < N) dst[n0 + PREP_NT * i] = v4f{x[i][0], x[i][1], x[i][2], 0.f};
+}
+
 // ---- the launch ----------------------------------------------------------------------------------
 struct PrepJob {
     int kind, blocks;
@@ -471,10 +491,11 @@ struct PrepJob {
         PackPosArgs pos;
         CopyArgs copy;
         struct { int N, wpc, windows; } order;
+        struct { int N, bpc; } points;
         struct { int words; } clear;
     };
 };
-enum { PREP_PACK, PREP_PACK_POS, PREP_ORDER, PREP_COPY, PREP_CLEAR };
+enum { PREP_PACK, PREP_PACK_POS, PREP_ORDER, PREP_COPY, PREP_POINTS, PREP_CLEAR };
 static_assert(sizeof(PrepJob) <= PREP_JOB_BYTES, "PrepList's storage");
 struct PrepJobs {
     PrepJob job[PREP_MAX_JOBS];
@@ -500,6 +521,9 @@ __global__ __launch_bounds__(PREP_NT) __attribute__((amdgpu_waves_per_eu(8, 8)))
         break;
     case PREP_COPY:
         copy_tile((const float *)j.a, (float *)j.dst, j.copy, block, lds);
+        break;
+    case PREP_POINTS:
+        pack_points((const float *)j.a, (float *)j.dst, j.points.N, j.points.bpc, block);
         break;
     default:
         for (int w = threadIdx.x; w < j.clear.words; w += PREP_NT) ((uint32_t *)j.dst)[w] = 0u;
@@ -548,6 +572,12 @@ void PrepList::copy(const float *src, float *dst, int B, int N, int Cs, int Cd, 
         const bool vec = al && (src_bcn ? N % 4 == 0 : (Cs | c_off) % 4 == 0) && (dst_bcn ? N % 4 == 0 : Cd % 4 == 0);
         j->copy = CopyArgs{N, Cs, Cd, c_off, src_bcn, dst_bcn, tn, tc, vec};
     }
+}
+
+void PrepList::pack_pos(const float *pos, float *pos4, int B, int N)
+{
+    const int bpc = (N + PREP_NT * POINTS_PER_THREAD - 1) / (PREP_NT * POINTS_PER_THREAD);
+    if (PrepJob *j = next_job(*this, PREP_POINTS, (int64_t)B * bpc, pos, nullptr, pos4)) { j->points.N = N; j->points.bpc = bpc; }
 }
 
 void PrepList::clear(void *dst, int words)

@@ -29,7 +29,7 @@ struct TileGeom {
     static constexpr int LPR = IC / 4, G = 64 / LPR;     // lanes per row, points a wave gathers at a time
     static constexpr int PASSES = 8 / G;
     static constexpr int KD = 4 * IC, KS = KD / 32;      // depth, depth steps of the matrix op
-    static constexpr int ARS = 4 * KD + 16;              // tile row: [hi: KD halves][lo: KD halves][16 B], = 16 mod 128
+    static constexpr int ARS = 4 * KD + 32;              // tile row: [hi: KD halves][lo: KD halves][32 B], = 32 mod 256 (WsGeom)
     static constexpr int MB = 4 / WM;                    // 16-point blocks per contracting wave
     static constexpr int OUTW = 16 * WN * NSW;
 };
@@ -159,7 +159,14 @@ __device__ __forceinline__ int tile_lane_channel(const TileArgs &a, int ib) { re
 // What a gathering wave does: the sums of its eight points (from `first` of every tile) over input blocks ib0 .. ib0 + n_in - 1,
 // acc[pass][channel][component]; park(acc, ib, point) takes them when a (tile, input block) is complete.
 // Eight rows are in flight at all times.
-template <bool CSR, class Park>
+// How a slot's row is weighed with its (dx, dy, dz, 1).  MX: by outer products on the matrix cores (outer_slot): an entry is
+// then needed once per wave, in the layout lane = 16 * point + 4 * slot + component, and its row's offset, the fourth
+// component, reaches the address by a DPP add.  Else by fused multiply-adds, every lane reading its point's entry from LDS,
+// 16 bytes a slot.  The 4 x 4 x 1 op holds the matrix cores for 8 clocks and the vector ALU with them, the sixteen
+// multiply-adds that four of them replace hold the vector ALU for 40, the reads LDS for as long.  512 -> 512, 109k points, us: forward 796
+// by multiply-adds, 778 by outer products, feature gradient 852 and 836; the parameter gradient, whose contraction
+// already fills the matrix cores twice as far, 1681 and 1728.
+template <bool CSR, bool MX, class Park>
 __device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedule &sc, int tiles, int first, int ib0,
                                              float (*ent)[64][4], Park &&park)
 {
@@ -187,16 +194,31 @@ __device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedu
         return row_buffer(a.rows + (int64_t)d.b * a.N * a.rs, (unsigned)a.N * (unsigned)a.rs * 4u);
     };
 
+    // MX: the entries of four slots of a pass's four points, slots 4 * half ..
+    const float *my_ent = &ent[0][8 * ((lane >> 2) & 3) + grp][lane & 3];
+    struct Entries { float v[2][2]; };              // [pass][half]
+    auto entries = [&](int buf) {
+        Entries e;
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) e.v[p][h] = my_ent[buf * 256 + 128 * h + 16 * p];
+        return e;
+    };
+    const bool is_weight = (lane & 3) == 3;
+    auto row_offset = [&](float e, int slot) { return (unsigned)row_bcast_offset(__float_as_int(e), slot); };
+
     TileStep d0, d1, d2;
     int id1, id2, pt1, pt2, pt0;                    // this lane's entries of the next two steps
     bool has1, has2;
     Positions p1;
+    Entries e0;
     v4f f[8];                                       // rows in flight
     // how far ahead of its use LDS is read, as the registers allow: the differences EA slots, the offsets of four
     // points from slot to slot over the four points before (fixed lists) or at once in front of them
     constexpr int EA = CSR ? 2 : 4;
     constexpr bool OFF_AHEAD = !CSR;
-    unsigned off[8];
+    unsigned off[MX ? 1 : 8];
     {
         int id0;
         bool has0;
@@ -207,12 +229,16 @@ __device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedu
         d2 = walk.fetch(a, first, id2, pt2, has2);
         publish(0, id0, has0, p0);
         request(d1, id1, pt1, p1);
+        if constexpr (MX) e0 = entries(0);
         const auto rows = rows_of(d0);
         const unsigned lane_off = 4u * (unsigned)lane_channel(d0.ib);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) f[u] = load_row4(rows, __float_as_uint(ent[0][8 * u + grp][3]) + lane_off);
-        if constexpr (OFF_AHEAD) {
+        for (int u = 0; u < 8; ++u) {
+            if constexpr (MX) f[u] = load_row4(rows, row_offset(e0.v[0][u >> 2], u & 3) + lane_off);
+            else f[u] = load_row4(rows, __float_as_uint(ent[0][8 * u + grp][3]) + lane_off);
+        }
+        if constexpr (OFF_AHEAD && !MX) {
 #pragma unroll
             for (int u = 0; u < 8; ++u) off[u] = __float_as_uint(ent[0][8 * u + 4 + grp][3]);
         }
@@ -230,6 +256,8 @@ __device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedu
     for (int s = 0, k = 0; k < tiles; ++s) {
         const int buf = s & 1;
         publish(buf ^ 1, id1, has1, p1);            // the next step's entries
+        Entries e1;
+        if constexpr (MX) e1 = entries(buf ^ 1);
         request(d2, id2, pt2, p1);                  // positions of the step after it, entries of the one after that
         int id3, pt3;
         bool has3;
@@ -240,12 +268,18 @@ __device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedu
         const auto rows0 = rows_of(d0), rows1 = rows_of(d1);
         const unsigned lane_off0 = 4u * (unsigned)lane_channel(d0.ib), lane_off1 = 4u * (unsigned)lane_channel(d1.ib);
         v4f e[EA + 1];
+        if constexpr (!MX) {
 #pragma unroll
-        for (int u = 0; u < EA; ++u) e[u] = *reinterpret_cast<const v4f *>(ent[buf][8 * u + grp]);
+            for (int u = 0; u < EA; ++u) e[u] = *reinterpret_cast<const v4f *>(ent[buf][8 * u + grp]);
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            if constexpr (!OFF_AHEAD) {
+            float w[2];                             // MX: the slots' weights
+            if constexpr (MX) {
+                w[0] = is_weight ? 1.f : e0.v[p][0];
+                w[1] = is_weight ? 1.f : e0.v[p][1];
+            } else if constexpr (!OFF_AHEAD) {
 #pragma unroll
                 for (int u = 0; u < 8; ++u) off[u] = __float_as_uint(p == 0 ? ent[buf][8 * u + 4 + grp][3] : ent[buf ^ 1][8 * u + grp][3]);
             }
@@ -253,19 +287,29 @@ __device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedu
             for (int u = 0; u < 8; ++u) {
                 constexpr int R = EA + 1;
                 const int i = 8 * p + u;
-                if (i + EA < 16) e[(i + EA) % R] = *reinterpret_cast<const v4f *>(ent[buf][8 * ((i + EA) & 7) + 4 * ((i + EA) >> 3) + grp]);
-                const v4f d = e[i % R];
+                if constexpr (!MX)
+                    if (i + EA < 16) e[(i + EA) % R] = *reinterpret_cast<const v4f *>(ent[buf][8 * ((i + EA) & 7) + 4 * ((i + EA) >> 3) + grp]);
                 if (u < (p == 0 ? d0.n0 : d0.n1)) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
+                        if constexpr (MX) {
+                            acc[p][v] = outer_slot(w[u >> 2], f[u][v], acc[p][v], u & 3);
+                            continue;
+                        }
+                        const v4f d = e[i % R];
                         acc[p][v][0] = fmaf(d[0], f[u][v], acc[p][v][0]);
                         acc[p][v][1] = fmaf(d[1], f[u][v], acc[p][v][1]);
                         acc[p][v][2] = fmaf(d[2], f[u][v], acc[p][v][2]);
                         acc[p][v][3] += f[u][v];
                     }
                 }
-                f[u] = p == 0 ? load_row4(rows0, off[u] + lane_off0) : load_row4(rows1, off[u] + lane_off1);
-                if constexpr (OFF_AHEAD) off[u] = __float_as_uint(ent[buf ^ 1][8 * u + 4 * p + grp][3]);
+                if constexpr (MX) {
+                    f[u] = p == 0 ? load_row4(rows0, row_offset(e0.v[1][u >> 2], u & 3) + lane_off0)
+                                  : load_row4(rows1, row_offset(e1.v[0][u >> 2], u & 3) + lane_off1);
+                } else {
+                    f[u] = p == 0 ? load_row4(rows0, off[u] + lane_off0) : load_row4(rows1, off[u] + lane_off1);
+                }
+                if constexpr (OFF_AHEAD && !MX) off[u] = __float_as_uint(ent[buf ^ 1][8 * u + 4 * p + grp][3]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -274,6 +318,7 @@ __device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedu
             ++k;
             clear();
         }
+        if constexpr (MX) e0 = e1;
         d0 = d1; d1 = d2; d2 = d3;
         pt0 = pt1; pt1 = pt2; pt2 = pt3;
         id1 = id2; id2 = id3;
@@ -312,7 +357,7 @@ void tile_conv_kernel(const TileArgs a)
         const int t = lane % P::LPR, grp = lane / P::LPR, first = 8 * wave;
         const bool ragged = a.w_in % IC != 0;
         int m_buf = 0;                                  // tile buffer of the tile being gathered
-        gather_steps<CSR>(a, sc, tiles, first, 0, s_ent[wave], [&](v4f (&acc)[2][4], int step_ib, int point) __attribute__((always_inline)) {
+        gather_steps<CSR, true>(a, sc, tiles, first, 0, s_ent[wave], [&](v4f (&acc)[2][4], int step_ib, int point) __attribute__((always_inline)) {
             // ---- park ----
             const int ib = MULTI ? step_ib : 0;
 #pragma unroll
@@ -530,17 +575,18 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
         // ---- gather ----
         if (tiles == 0) return;
         const int t = lane & 15, grp = lane >> 4, first = 8 * wave;
-        gather_steps<false>(a, sc, tiles, first, hi, s_ent[wave], [&](v4f (&acc)[2][4], int, int) __attribute__((always_inline)) {
+        gather_steps<false, false>(a, sc, tiles, first, hi, s_ent[wave], [&](v4f (&acc)[2][4], int, int) __attribute__((always_inline)) {
             __syncthreads();               // the tile before is contracted
 #pragma unroll
             for (int ps = 0; ps < 2; ++ps) {
-                char *row = s_A + (first + 4 * ps + grp) * AS + 8 * t;
+                char *row = s_A + (first + 4 * ps + grp) * AS;
+                const int swap = bf3_swap(first);            // of all eight points of the wave
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
                     unsigned h0, m0, l0, h1, m1, l1;
                     split_bf3(acc[ps][0][jj], acc[ps][1][jj], h0, m0, l0);
                     split_bf3(acc[ps][2][jj], acc[ps][3][jj], h1, m1, l1);
-                    char *d = row + 2 * jj * IC;
+                    char *d = row + bf3_at(8 * t, 2 * jj * IC, swap);
                     *reinterpret_cast<uint2 *>(d) = make_uint2(h0, h1);
                     *reinterpret_cast<uint2 *>(d + 2 * KD) = make_uint2(m0, m1);
                     *reinterpret_cast<uint2 *>(d + 4 * KD) = make_uint2(l0, l1);
@@ -596,14 +642,15 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
         __syncthreads();                   // the tile before is contracted
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            char *d = s_G + ((ctid >> 4) + 32 * c) * GS + 8 * (ctid & 15);
+            char *row = s_G + ((ctid >> 4) + 32 * c) * GS;
+            const int swap = bf3_swap(ctid >> 4), v = 8 * (ctid & 15);
             unsigned h0, m0, l0, h1, m1, l1;
             const v4f g = c == 0 ? gv[c] : -gv[c];                 // (the second 32 points: see above)
             split_bf3(g[0], g[1], h0, m0, l0);
             split_bf3(g[2], g[3], h1, m1, l1);
-            *reinterpret_cast<uint2 *>(d) = make_uint2(h0, h1);
-            *reinterpret_cast<uint2 *>(d + 2 * OC) = make_uint2(m0, m1);
-            *reinterpret_cast<uint2 *>(d + 4 * OC) = make_uint2(l0, l1);
+            *reinterpret_cast<uint2 *>(row + bf3_at(v, 0, swap)) = make_uint2(h0, h1);
+            *reinterpret_cast<uint2 *>(row + bf3_at(v, 2 * OC, swap)) = make_uint2(m0, m1);
+            *reinterpret_cast<uint2 *>(row + bf3_at(v, 4 * OC, swap)) = make_uint2(l0, l1);
         }
         tw.next_clamped();
         load_g();
@@ -614,17 +661,15 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
             bf8 gH[NBW], gM[NBW], gL[NBW];
 #pragma unroll
             for (int n = 0; n < NBW; ++n) {
-                const int col = 2 * 16 * (wn + 2 * n);
-                gH[n] = read_tr_frag(s_G, GS, 32 * st + 8 * q, col, r16);
-                gM[n] = read_tr_frag(s_G, GS, 32 * st + 8 * q, col + 2 * OC, r16);
-                gL[n] = read_tr_frag(s_G, GS, 32 * st + 8 * q, col + 4 * OC, r16);
+                gH[n] = read_bf3_frag(s_G, GS, 32 * st + 8 * q, 32 * wn, 64 * n, r16);
+                gM[n] = read_bf3_frag(s_G, GS, 32 * st + 8 * q, 32 * wn, 64 * n + 2 * OC, r16);
+                gL[n] = read_bf3_frag(s_G, GS, 32 * st + 8 * q, 32 * wn, 64 * n + 4 * OC, r16);
             }
 #pragma unroll
             for (int c = 0; c < MBW; ++c) {
-                const int col = 2 * 16 * (wm + 4 * c);
-                const bf8 aH = read_tr_frag(s_A, AS, 32 * st + 8 * q, col, r16);
-                const bf8 aM = read_tr_frag(s_A, AS, 32 * st + 8 * q, col + 2 * KD, r16);
-                const bf8 aL = read_tr_frag(s_A, AS, 32 * st + 8 * q, col + 4 * KD, r16);
+                const bf8 aH = read_bf3_frag(s_A, AS, 32 * st + 8 * q, 32 * wm, 128 * c, r16);
+                const bf8 aM = read_bf3_frag(s_A, AS, 32 * st + 8 * q, 32 * wm, 128 * c + 2 * KD, r16);
+                const bf8 aL = read_bf3_frag(s_A, AS, 32 * st + 8 * q, 32 * wm, 128 * c + 4 * KD, r16);
                 v4f acc[NBW];
 #pragma unroll
                 for (int n = 0; n < NBW; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};

@@ -61,7 +61,7 @@ int FLEX_NAME(route, FLEX_DI, FLEX_DO)(int N, int K, int csr)
     return gc_route(N, K, csr, FLEX_NAME(theta_format, FLEX_DI, FLEX_DO)(N, K, csr));
 }
 
-hipError_t FLEX_NAME(launch_gc, FLEX_DI, FLEX_DO)(const float *rows, const float *pos,
+hipError_t FLEX_NAME(launch_gc, FLEX_DI, FLEX_DO)(const float *rows, const float *pos, const PosRef &pr,
                                                   const int32_t *nbr, const int32_t *off,
                                                   const int32_t *src, const int32_t *order, const void *thetaP,
                                                   int theta_fmt, float *out, int B, int N, int K,
@@ -99,7 +99,7 @@ hipError_t FLEX_NAME(launch_gc, FLEX_DI, FLEX_DO)(const float *rows, const float
                 const int tpcl = (N + tl - 1) / tl;
                 const int totl = B * tpcl;
                 const dim3 gl(persistent_grid(totl, wide ? WL::WG_PER_CU : W::WG_PER_CU)), bl(wide ? WL::NT : W::NT);
-#define FLEX_LEAN_ARGS rows, pos, nbr, thetaP, exp_off, out, N, K, tpcl, totl
+#define FLEX_LEAN_ARGS rows, pr, nbr, thetaP, exp_off, out, N, K, tpcl, totl
 #define FLEX_LEAN_LAUNCH(BCN_, PM_)                                                                              \
     do {                                                                                                         \
         if (K % 8 == 0) hipLaunchKernelGGL((gather_contract_lean_kernel<S, BCN_, PM_>), gl, bl, 0, s, FLEX_LEAN_ARGS); \
@@ -125,7 +125,7 @@ hipError_t FLEX_NAME(launch_gc, FLEX_DI, FLEX_DO)(const float *rows, const float
                 const int tpcl = (N + tl - 1) / tl;
                 const int totl = B * tpcl;
                 const dim3 gl(persistent_grid(totl, wide ? WL::WG_PER_CU : W::WG_PER_CU)), bl(wide ? WL::NT : W::NT);
-#define FLEX_LEAN_ARGS rows, pos, off, src, order, thetaP, exp_off, out, N, tpcl, totl
+#define FLEX_LEAN_ARGS rows, pr, off, src, order, thetaP, exp_off, out, N, tpcl, totl
                 if (wide && !out_bcn) hipLaunchKernelGGL((grad_feat_lean_kernel<S, false, PMX>), gl, bl, 0, s, FLEX_LEAN_ARGS);
                 else if (wide) hipLaunchKernelGGL((grad_feat_lean_kernel<S, true, PMX>), gl, bl, 0, s, FLEX_LEAN_ARGS);
                 else if (!out_bcn) hipLaunchKernelGGL((grad_feat_lean_kernel<S, false, 1>), gl, bl, 0, s, FLEX_LEAN_ARGS);
@@ -164,7 +164,7 @@ hipError_t FLEX_NAME(launch_gc, FLEX_DI, FLEX_DO)(const float *rows, const float
 }
 
 // Launches the per-workgroup partial kernel; *n_wg = number of partial blocks written.
-hipError_t FLEX_NAME(launch_gt, FLEX_DI, FLEX_DO)(const float *rows, const float *pos,
+hipError_t FLEX_NAME(launch_gt, FLEX_DI, FLEX_DO)(const float *rows, const float *pos, const PosRef &pr,
                                                   const int32_t *nbr, const float *g_rows,
                                                   float *partials, int B, int N, int K, int *n_wg,
                                                   hipStream_t s)
@@ -184,9 +184,9 @@ hipError_t FLEX_NAME(launch_gt, FLEX_DI, FLEX_DO)(const float *rows, const float
             const int tot = B * tpc;
             *n_wg = persistent_grid(tot, 1);
             if (K % 8 == 0)
-                hipLaunchKernelGGL((grad_theta_lean_kernel<S>), dim3(*n_wg), dim3(WL::NT), 0, s, rows, pos, nbr, g_rows, partials, N, K, tpc, tot);
+                hipLaunchKernelGGL((grad_theta_lean_kernel<S>), dim3(*n_wg), dim3(WL::NT), 0, s, rows, pr, nbr, g_rows, partials, N, K, tpc, tot);
             else
-                hipLaunchKernelGGL((grad_theta_lean_kernel<S, true>), dim3(*n_wg), dim3(WL::NT), 0, s, rows, pos, nbr, g_rows, partials, N, K, tpc, tot);
+                hipLaunchKernelGGL((grad_theta_lean_kernel<S, true>), dim3(*n_wg), dim3(WL::NT), 0, s, rows, pr, nbr, g_rows, partials, N, K, tpc, tot);
             return hipGetLastError();
         }
     }
@@ -223,7 +223,7 @@ bool bwd_fused_ok_64_64(int N, int K)
 // g_rows / own_rows: upstream gradient and features, point-major; partials: *n_wg blocks of [4*64 x 64];
 // control: fused_control_bytes() whose flag word the caller has zeroed on the stream.  Leaves the partials of the
 // parameter gradients and the workgroups' records for the check after the reduction.
-hipError_t launch_bwd_fused_64_64(const float *g_rows, const float *own_rows, const float *pos, const int32_t *nbr,
+hipError_t launch_bwd_fused_64_64(const float *g_rows, const float *own_rows, const PosRef &pos, const int32_t *nbr,
                                   const int32_t *off, const int32_t *src, const int32_t *order, const void *thetaP,
                                   float *grad_feat, float *partials, int *control, int B, int N, int K, int out_bcn,
                                   int *n_wg, hipStream_t s)
@@ -249,7 +249,7 @@ hipError_t launch_bwd_fused_64_64(const float *g_rows, const float *own_rows, co
 
 // The hand-over after the first reduction (grad_theta / grad_bias: its result): the stand-alone kernel over the same
 // grid, which decides on the device whether it runs.
-hipError_t launch_bwd_fused_late_64_64(const float *g_rows, const float *own_rows, const float *pos,
+hipError_t launch_bwd_fused_late_64_64(const float *g_rows, const float *own_rows, const PosRef &pos,
                                        const int32_t *nbr, const void *thetaP, const float *grad_theta,
                                        const float *grad_bias, int Din, int Dout, float *partials, int *control, int B,
                                        int N, int K, hipStream_t s)

@@ -28,15 +28,6 @@
 #pragma once
 #include "flex_tiled.hpp"
 
-#ifndef FLEX_LEAN_VALU_AGG
-#define FLEX_LEAN_VALU_AGG 1
-#endif
-// 1: the position differences reach the compute lanes as (dx, dy, dz, w) through a wave-private LDS array (one
-// 16-byte read per row); 0: one component per lane by ds_bpermute, then three quad broadcasts per row
-#ifndef FLEX_DP_LDS
-#define FLEX_DP_LDS 1
-#endif
-
 namespace flex {
 
 template <class S, int PM = 1, int CM = 1>
@@ -62,8 +53,9 @@ struct WsGeom {
     // split-half aggregate tile: per point [hi: KDP halves][lo: KDP halves][16 B pad]
     static constexpr int KDP = rup_c(S::KD, 32);         // depth padded to the f16 matrix op
     static constexpr int KS2 = KDP / 32;                 // depth steps of v_mfma_f32_16x16x32_f16
-    static constexpr int ARS = 4 * KDP + 16;             // row stride in bytes (= 16 mod 128: 16-byte reads of
-                                                         // 8 consecutive rows hit distinct banks)
+    // row stride in bytes, 32 mod 256 (or 160): a turn of the 16-byte reads (tile_swizzle has the turns) finds its sixteen rows
+    // and chunks in distinct banks; 16 mod 128 doubled the time of half the reads
+    static constexpr int ARS = 4 * KDP + 32;
     static constexpr int ROWB_F32 = 4 * AST;
     static constexpr int ROWB = ARS > ROWB_F32 ? ARS : ROWB_F32;
 };
@@ -110,18 +102,21 @@ __device__ __forceinline__ void load_row_scales(float (&rs)[S::VEC][4], const vo
         }
 }
 
-// The swizzled form of the split-half tile (SWZ): rows exactly 4*KDP bytes apart and, inside every 128-byte block
-// of a row, the 16-byte chunk index XORed with tile_swizzle(row).  Both ways the tile is read are then free of
-// bank conflicts: 16-byte fragments of 8 consecutive rows at one column (the contraction with the parameters) and
-// 32-byte runs of 4 consecutive rows (the transposing reads of the contraction over the tile's points).
-__device__ __forceinline__ int tile_swizzle(int row) { return (2 * (row & 3) + ((row >> 2) & 1)) << 4; }
+// The swizzled form of the split-half tile (SWZ): rows exactly 4*KDP bytes apart and the byte address inside every 256-byte
+// block of a row XORed with tile_swizzle(row).  Both ways the tile is read are then free of bank conflicts.  LDS has 64
+// banks and serves a 16-byte read in four turns of 16 lanes -- lanes 0-3, 12-15 and 20-27; 4-11, 16-19 and 28-31; and the
+// same of the upper half --, an 8-byte one in two turns of 32: the contraction with the parameters reads one 16-byte chunk of sixteen rows per lane quarter (a
+// turn: eight rows of one chunk and the other eight of the next), the contraction over the tile's points 32-byte runs of
+// rows 0-3 and 8-11 (mod 16) in one turn.  (XORing inside 128-byte blocks, for 32 banks, cost 13 percent of the one-pass
+// backward kernel's cycles in conflicts.)
+__device__ __forceinline__ int tile_swizzle(int row) { return ((row & 3) << 5) | (((row >> 3) & 1) << 7); }
 
 template <class S, bool SWZ = false>
 __device__ __forceinline__ void store_split_rows(const v4f (&acc_in)[S::VEC], const float (&rs)[S::VEC][4], char *sA,
                                                  int *sE, int pt, int t, bool writer)
 {
     using G = WsGeom<S>;   // row format only: the same for every producer multiple
-    static_assert(!SWZ || (S::VEC == 4 && (2 * S::DIP) % 128 == 0 && G::KDP == S::KD), "swizzle inside 128-byte blocks");
+    static_assert(!SWZ || (S::VEC == 4 && (2 * S::KD) % 256 == 0 && G::KDP == S::KD), "swizzle inside 256-byte blocks");
     v4f acc[S::VEC];
     float m = 0.f;
 #pragma unroll
@@ -135,7 +130,9 @@ __device__ __forceinline__ void store_split_rows(const v4f (&acc_in)[S::VEC], co
     const int e = 15 - __builtin_amdgcn_frexp_expf(m);
     if (writer) {
         if (t == 0) sE[pt] = e;
-        char *row = SWZ ? sA + pt * (4 * G::KDP) + ((2 * S::VEC * t) ^ tile_swizzle(pt)) : sA + pt * G::ARS + 2 * S::VEC * t;
+        char *row = SWZ ? sA + pt * (4 * G::KDP) : sA + pt * G::ARS;
+        const int swz = SWZ ? tile_swizzle(pt) : 0;
+        auto at = [&](int half) { return row + ((2 * (S::VEC * t + half)) ^ swz); };      // of the half at this place of the row
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
             if constexpr (S::VEC == 4) {
@@ -149,13 +146,13 @@ __device__ __forceinline__ void store_split_rows(const v4f (&acc_in)[S::VEC], co
                     const f2 back = __builtin_convertvector(h[p2], f2);
                     l[p2] = __builtin_convertvector(x - back, h2);
                 }
-                *reinterpret_cast<h4 *>(row + 2 * jj * S::DIP) = h4{h[0][0], h[0][1], h[1][0], h[1][1]};
-                *reinterpret_cast<h4 *>(row + 2 * (G::KDP + jj * S::DIP)) = h4{l[0][0], l[0][1], l[1][0], l[1][1]};
+                *reinterpret_cast<h4 *>(at(jj * S::DIP)) = h4{h[0][0], h[0][1], h[1][0], h[1][1]};
+                *reinterpret_cast<h4 *>(at(G::KDP + jj * S::DIP)) = h4{l[0][0], l[0][1], l[1][0], l[1][1]};
             } else {
                 const float x = __builtin_ldexpf(acc[0][jj], e);
                 const _Float16 h = (_Float16)x;
-                *reinterpret_cast<_Float16 *>(row + 2 * jj * S::DIP) = h;
-                *reinterpret_cast<_Float16 *>(row + 2 * (G::KDP + jj * S::DIP)) = (_Float16)(x - (float)h);
+                *reinterpret_cast<_Float16 *>(at(jj * S::DIP)) = h;
+                *reinterpret_cast<_Float16 *>(at(G::KDP + jj * S::DIP)) = (_Float16)(x - (float)h);
             }
         }
     }
@@ -529,13 +526,37 @@ __device__ __forceinline__ void producer_loop(Producer<S, CSR> &Pr, const TileSc
     }
 }
 
+// value of lane SRC of every 16-lane row, in all of the row's lanes (one vector instruction, usually folded into its use)
+template <int SRC>
+__device__ __forceinline__ int row_bcast(int x)
+{
+    return __builtin_amdgcn_update_dpp(0, x, 0x150 + SRC, 0xf, 0xf, true);   // row_newbcast:SRC
+}
+__device__ __forceinline__ int row_bcast_slot(int x, int slot)               // lane 4 * slot; slot: a constant after unrolling
+{
+    return slot == 0 ? row_bcast<0>(x) : slot == 1 ? row_bcast<4>(x) : slot == 2 ? row_bcast<8>(x) : row_bcast<12>(x);
+}
+__device__ __forceinline__ int row_bcast_offset(int x, int slot)              // lane 4 * slot + 3
+{
+    return slot == 0 ? row_bcast<3>(x) : slot == 1 ? row_bcast<7>(x) : slot == 2 ? row_bcast<11>(x) : row_bcast<15>(x);
+}
+// acc[i] (component i) of the lane's channel += dp_i * f, with dp_i in lane 4 * slot + i of the lane's 16-lane row: sixteen
+// 4 x 4 outer products, one per quad of lanes, whose first operand the op itself broadcasts from quad `slot` of four
+__device__ __forceinline__ v4f outer_slot(float dp, float f, v4f acc, int slot)
+{
+    return slot == 0   ? __builtin_amdgcn_mfma_f32_4x4x1f32(dp, f, acc, 2, 0, 0)
+           : slot == 1 ? __builtin_amdgcn_mfma_f32_4x4x1f32(dp, f, acc, 2, 1, 0)
+           : slot == 2 ? __builtin_amdgcn_mfma_f32_4x4x1f32(dp, f, acc, 2, 2, 0)
+                       : __builtin_amdgcn_mfma_f32_4x4x1f32(dp, f, acc, 2, 3, 0);
+}
+
 // ---------------------------------------------------------------------------
 // Lean producer for the fixed-K neighbour tensor (K a multiple of 8, every per-cloud byte
-// offset below 2^32).  Nothing is staged in LDS: each lane of a row group loads its
-// point's neighbour ids itself (a broadcast read), turns them into 32-bit row offsets,
-// and lane i of every 4-lane block loads component i (x, y, z) of the neighbour's
-// position directly, so the (dx,dy,dz,1) operand of the 4x4x1 matrix op is formed in
-// registers.  Tail points are clamped to the cloud's last point (computed, never stored).
+// offset below 2^32).  Entry layout: four lanes an entry (a slot of a point), which load its id
+// and turn it into a 32-bit row offset; lane i of the four loads component i (x, y, z) of the
+// neighbour's position, so a register holds the (dx,dy,dz,1) of sixteen entries.  Compute layout:
+// a lane group per point, four channels of its rows a lane.
+// Tail points are clamped to the cloud's last point (computed, never stored).
 //
 // The work of a wave is a stream of batches, one batch = 8 neighbours of the wave's points
 // of one tile (K/8 batches per tile).  Eight rows per lane are in flight at all times: as
@@ -554,12 +575,18 @@ struct LeanProducer {
     static constexpr int U = 8;
     static constexpr bool FULL = (S::LPR * S::VEC == S::DI);   // every lane of a group reads real channels
     static_assert(G::PW == 4, "entry layout below: 4 points x 8 neighbours per batch");
-    // The aggregate runs on the vector ALU: the fp32 4x4x1 matrix op would need fewer issue slots, but
-    // it holds both the vector ALU and the f16/bf16 matrix pipe of the SIMD while it executes, so the
-    // consumers' matrix ops could never overlap the producers' work.
-    static constexpr bool VALU_AGG = FLEX_LEAN_VALU_AGG;
+    // How a row is weighed with its (dx, dy, dz, w).  ROW16, rows of sixteen lanes: by outer products (outer_slot) straight from
+    // the entry layout, whose lanes 4 * slot .. of a row's sixteen hold that point's slot; the row offsets go to the addresses by
+    // DPP adds, and nothing passes LDS.  Else by multiply-adds, the entries read from LDS, sixteen bytes a row.  The 4x4x1 op holds the
+    // vector ALU and the matrix cores of its SIMD for 8 clocks; the sixteen multiply-adds that four of them replace hold the
+    // vector ALU for 40 (alone) to 70 (beside the consumers' matrix ops, which hold it for 9 of their 16 clocks).  With
+    // the tiles' conflict-free strides and the packed locations, 64 -> 64, 7M points, us: forward 1361 -> 1303, one-pass backward
+    // 2690 -> 2550.
+    static constexpr bool ROW16 = S::LPR == 16;
+    static constexpr bool MX = ROW16 && !SUM;
 
-    const float *rows, *pos;
+    const float *rows;
+    PosRef pos;
     const int32_t *nbr;
     int N, K, KB, pw;
     int count, tiles_per_cloud;  // tiles of this workgroup
@@ -569,16 +596,16 @@ struct LeanProducer {
     bool lane_on;
     unsigned lane_off;           // byte offset of the lane's channels in a row
     int perm_id, perm_dp;        // ds_bpermute byte addresses of entry (k = 0, g) in the entry layout
-    // entry layout: lane = (entry e = lane>>2 of 16, component c = lane&3); register half h holds the
-    // entries 16h+e, entry i = (neighbour slot i>>2, point i&3)
+    // entry layout: lane = (entry e = lane>>2 of 16, component c = lane&3); register half h holds slots 4h .. 4h+3 of the
+    // four points, ROW16: e = 4 * point + slot, so that an entry stands in its point's lane group, else e = 4 * slot + point
     int e_g, e_k;                // point and slot (within half 0) of this lane's entry
-    unsigned e_col;              // position component to read: x, y, z (lane 3 reads z, value unused)
+    unsigned e_col;              // byte offset of the position component to read: x, y, z (lane 3 reads z, value unused)
     float e_mul, e_fix;          // dp component = (pn - pc)*e_mul + e_fix   (component lane 3: the constant 1)
     float *s_dp = nullptr;       // this wave's LDS array of 32 entries x (dx, dy, dz, w), entry = 4 * slot + point
     int dp_rd = 0;               // float offset of this lane's entry of slot 0 in it
     __device__ __forceinline__ void set_dp_stage(float *p) { s_dp = p; dp_rd = 4 * (grp % G::PW); }
 
-    __device__ __forceinline__ void init(const float *rows_, const float *pos_, const int32_t *nbr_, int N_,
+    __device__ __forceinline__ void init(const float *rows_, const PosRef &pos_, const int32_t *nbr_, int N_,
                                          int K_, int pw_, const TileSchedule &sc, int tiles_per_cloud_)
     {
         rows = rows_; pos = pos_; nbr = nbr_; N = N_; K = K_; KB = (K_ + U - 1) / U; pw = pw_;
@@ -589,10 +616,10 @@ struct LeanProducer {
         const int g = grp % G::PW, dsel = lane & 3;
         perm_id = 4 * (4 * g);
         perm_dp = 4 * (4 * g + dsel);
-        e_g = (lane >> 2) & 3;
-        e_k = lane >> 4;
+        e_g = ROW16 ? lane >> 4 : (lane >> 2) & 3;
+        e_k = ROW16 ? (lane >> 2) & 3 : lane >> 4;
         const int c = lane & 3;
-        e_col = c < 3 ? c : 2;
+        e_col = (c < 3 ? c : 2) * pos_.col;
         e_mul = c < 3 ? 1.f : 0.f;
         e_fix = c < 3 ? 0.f : 1.f;
         sched = sc; tiles_per_cloud = tiles_per_cloud_;
@@ -640,16 +667,16 @@ struct LeanProducer {
     // entry layout: position component of the neighbours (both halves) and of the centre
     __device__ __forceinline__ void load_pos(float (&pn)[2], float &pc, const int (&id)[2], const Batch &x) const
     {
-        const char *pb = reinterpret_cast<const char *>(pos + (int64_t)x.b * 3 * N);
-        const unsigned col = e_col * (unsigned)N;
-        pn[0] = *reinterpret_cast<const float *>(pb + 4u * (col + (unsigned)id[0]));
-        pn[1] = *reinterpret_cast<const float *>(pb + 4u * (col + (unsigned)id[1]));
-        pc = *reinterpret_cast<const float *>(pb + 4u * (col + (unsigned)min(x.lw0 + e_g, N - 1)));
+        const char *pb = reinterpret_cast<const char *>(pos.p) + x.b * pos.cloud;
+        pn[0] = *reinterpret_cast<const float *>(pb + (((unsigned)id[0] << pos.shift) + e_col));
+        pn[1] = *reinterpret_cast<const float *>(pb + (((unsigned)id[1] << pos.shift) + e_col));
+        pc = *reinterpret_cast<const float *>(pb + (((unsigned)min(x.lw0 + e_g, N - 1) << pos.shift) + e_col));
     }
     // entry layout -> compute layout: value of entry (slot u, this lane's point), component lane `base`
     __device__ __forceinline__ int spread(const int (&v)[2], int base, int u) const
     {
-        return __builtin_amdgcn_ds_bpermute(base + 64 * (u & 3), v[u >> 2]);
+        if constexpr (ROW16) return row_bcast_slot(v[u >> 2], u & 3);
+        else return __builtin_amdgcn_ds_bpermute(base + 64 * (u & 3), v[u >> 2]);
     }
 
     __device__ __forceinline__ void load_row(float (&fr)[S::VEC], int id, const char *rb) const
@@ -736,12 +763,14 @@ struct LeanProducer {
             const int k0_acc = k0_cur;
             k0_cur = x1.k0;
             // ids of batch m+1 are here: their positions and (below) rows go in flight; ids of batch m+2 too
-            constexpr bool DP_LDS = FLEX_DP_LDS && VALU_AGG && !SUM;
+            constexpr bool DP_LDS = !SUM && !MX;
             // with a full last batch the fourth component of an entry (the constant 1) is not needed as a weight:
             // it carries the byte offset of the NEXT batch's row instead, which saves that batch's id permutes
             constexpr bool ID_LDS = DP_LDS && !TAIL;
             int idc[ID_LDS ? 1 : U];
-            if constexpr (ID_LDS) {
+            const int ro[2] = {(int)((unsigned)idn[0] * (4u * S::DI)), (int)((unsigned)idn[1] * (4u * S::DI))};
+            if constexpr (MX) {
+            } else if constexpr (ID_LDS) {
                 if ((threadIdx.x & 3) == 3) {
                     dpe[0] = (int)((unsigned)idn[0] * (4u * S::DI));
                     dpe[1] = (int)((unsigned)idn[1] * (4u * S::DI));
@@ -757,7 +786,6 @@ struct LeanProducer {
             const char *rb = reinterpret_cast<const char *>(rows + (int64_t)x1.b * N * (unsigned)S::DI);
             const int nb = x1.b, nlw0 = x1.lw0;
             x1 = x2;
-            float dpc[DP_LDS ? 1 : U];
             v4f dpv[DP_LDS ? 3 : 1];
             if constexpr (DP_LDS) {
                 // entry (16 h + e), component c sits at float 4 * (16 h + e) + c = 64 h + lane
@@ -767,9 +795,6 @@ struct LeanProducer {
                 wave_lds_sync();
                 dpv[0] = *reinterpret_cast<const v4f *>(s_dp + dp_rd);          // rows 0 and 1 now, row u + 2 while
                 dpv[1] = *reinterpret_cast<const v4f *>(s_dp + 16 + dp_rd);     // row u is accumulated
-            } else {
-#pragma unroll
-                for (int u = 0; u < U; ++u) dpc[u] = SUM ? 0.f : __int_as_float(spread(dpe, perm_dp, u));
             }
             const bool first = (kb == 0);            // first batch of a tile: its first row starts the sums
 
@@ -793,15 +818,17 @@ struct LeanProducer {
                                 else acc[v][3] += fv[v];
                             }
                         }
-                    } else if constexpr (VALU_AGG) {
-                        float dx, dy, dz, one;
-                        if constexpr (DP_LDS) {
-                            dx = dpv[u % 3][0]; dy = dpv[u % 3][1]; dz = dpv[u % 3][2]; one = dpv[u % 3][3];
+                    } else if constexpr (MX) {
+                        const float d = __int_as_float(dpe[u >> 2]);
+                        if (u == 0 && first) {
+#pragma unroll
+                            for (int v = 0; v < S::VEC; ++v) acc[v] = outer_slot(d, fv[v], v4f{0.f, 0.f, 0.f, 0.f}, u & 3);
                         } else {
-                            // the four lanes of a block hold (dx, dy, dz, 1): broadcast inside the quad
-                            dx = dpp_move<0x00>(dpc[u]); dy = dpp_move<0x55>(dpc[u]); dz = dpp_move<0xAA>(dpc[u]);
-                            one = TAIL ? dpp_move<0xFF>(dpc[u]) : 1.f;             // 0 for a slot past K
+#pragma unroll
+                            for (int v = 0; v < S::VEC; ++v) acc[v] = outer_slot(d, fv[v], acc[v], u & 3);
                         }
+                    } else {
+                        const float dx = dpv[u % 3][0], dy = dpv[u % 3][1], dz = dpv[u % 3][2], one = dpv[u % 3][3];
                         if (u == 0 && first) {
 #pragma unroll
                             for (int v = 0; v < S::VEC; ++v)
@@ -816,16 +843,12 @@ struct LeanProducer {
                                 else acc[v][3] += fv[v];
                             }
                         }
-                    } else {
-                        if (u == 0 && first) {
-#pragma unroll
-                            for (int v = 0; v < S::VEC; ++v) acc[v] = v4f{0.f, 0.f, 0.f, 0.f};
-                        }
-                        fma_row<S>(acc, dpc[u], fv);
                     }
                 }
                 // row u of batch m+1 takes the freed registers
-                if constexpr (ID_LDS) {
+                if constexpr (MX) {
+                    if (!TAIL || u < 4 || next_upper) load_row_at(f[u], (unsigned)row_bcast_slot(ro[u >> 2], u & 3), rb);
+                } else if constexpr (ID_LDS) {
                     load_row_at(f[u], __float_as_uint(dpv[u % 3][3]), rb);
                 } else {
                     if (!TAIL || u < 4 || next_upper) load_row(f[u], idc[u], rb);
@@ -862,9 +885,12 @@ struct LeanCsrProducer {
     using G = WsGeom<S, PM>;
     static constexpr int U = 8;
     static constexpr bool FULL = (S::LPR * S::VEC == S::DI);
+    static constexpr bool ROW16 = S::LPR == 16, MX = ROW16 && !SUM;     // LeanProducer
+    static constexpr unsigned ENTRY0 = ROW16 ? 15 : 0x33;      // lane & ENTRY0 == 0: slot 0, component 0 of a point
     static_assert(G::PW == 4, "entry layout: 4 points x 8 list slots per batch");
 
-    const float *rows, *pos;
+    const float *rows;
+    PosRef pos;
     const int32_t *off, *src;
     const int32_t *order = nullptr;
     int N, pw;
@@ -881,7 +907,7 @@ struct LeanCsrProducer {
     int dp_rd = 0;               // float offset of this lane's entry of slot 0 in it
     __device__ __forceinline__ void set_dp_stage(float *p) { s_dp = p; dp_rd = 4 * (grp % G::PW); }
 
-    __device__ __forceinline__ void init(const float *rows_, const float *pos_, const int32_t *off_,
+    __device__ __forceinline__ void init(const float *rows_, const PosRef &pos_, const int32_t *off_,
                                          const int32_t *src_, int N_, int pw_, const TileSchedule &sc,
                                          int tiles_per_cloud_)
     {
@@ -893,10 +919,10 @@ struct LeanCsrProducer {
         const int g = grp % G::PW, dsel = lane & 3;
         perm_id = 4 * (4 * g);
         perm_dp = 4 * (4 * g + dsel);
-        e_g = (lane >> 2) & 3;
-        e_k = lane >> 4;
+        e_g = ROW16 ? lane >> 4 : (lane >> 2) & 3;
+        e_k = ROW16 ? (lane >> 2) & 3 : lane >> 4;
         const int c = lane & 3;
-        e_col = c < 3 ? c : 2;
+        e_col = (c < 3 ? c : 2) * pos_.col;
         e_mul = c < 3 ? 1.f : 0.f;
         e_fix = c < 3 ? 0.f : 1.f;
         sched = sc; tiles_per_cloud = tiles_per_cloud_;
@@ -958,8 +984,9 @@ struct LeanCsrProducer {
         c.lo = c.lo_n;
         c.pid = c.pid_n;
         c.deg = (c.lw0 + e_g < N) ? c.hi_n - c.lo_n : 0;      // positions past the cloud have no list
-        const int d = max(max(__builtin_amdgcn_readlane(c.deg, 0), __builtin_amdgcn_readlane(c.deg, 4)),
-                          max(__builtin_amdgcn_readlane(c.deg, 8), __builtin_amdgcn_readlane(c.deg, 12)));
+        constexpr int PL = ROW16 ? 16 : 4;           // lanes from one point's first entry to the next one's
+        const int d = max(max(__builtin_amdgcn_readlane(c.deg, 0), __builtin_amdgcn_readlane(c.deg, PL)),
+                          max(__builtin_amdgcn_readlane(c.deg, 2 * PL), __builtin_amdgcn_readlane(c.deg, 3 * PL)));
         c.nb = max(1, (d + U - 1) / U);
         c.dmax = d;
         c.tw.next_clamped();
@@ -1002,19 +1029,29 @@ struct LeanCsrProducer {
     }
     __device__ __forceinline__ void load_pos(float (&pn)[2], float &pc, const int (&id)[2], const Desc &d) const
     {
-        const char *pb = reinterpret_cast<const char *>(pos + (int64_t)d.b * 3 * N);
-        const unsigned col = e_col * (unsigned)N;
-        pn[0] = *reinterpret_cast<const float *>(pb + 4u * (col + (unsigned)id[0]));
-        pn[1] = *reinterpret_cast<const float *>(pb + 4u * (col + (unsigned)id[1]));
-        pc = *reinterpret_cast<const float *>(pb + 4u * (col + (unsigned)d.pid));
+        const char *pb = reinterpret_cast<const char *>(pos.p) + d.b * pos.cloud;
+        pn[0] = *reinterpret_cast<const float *>(pb + (((unsigned)id[0] << pos.shift) + e_col));
+        pn[1] = *reinterpret_cast<const float *>(pb + (((unsigned)id[1] << pos.shift) + e_col));
+        pc = *reinterpret_cast<const float *>(pb + (((unsigned)d.pid << pos.shift) + e_col));
     }
     __device__ __forceinline__ int spread(const int (&v)[2], int base, int u) const
     {
-        return __builtin_amdgcn_ds_bpermute(base + 64 * (u & 3), v[u >> 2]);
+        if constexpr (ROW16) return row_bcast_slot(v[u >> 2], u & 3);
+        else return __builtin_amdgcn_ds_bpermute(base + 64 * (u & 3), v[u >> 2]);
     }
     __device__ __forceinline__ void load_row(float (&fr)[S::VEC], int id, const char *rb) const
     {
         const char *p = rb + ((unsigned)id * (4u * S::DI) + lane_off);
+        if constexpr (S::VEC == 4) {
+            const v4f v = *reinterpret_cast<const v4f *>(p);
+            fr[0] = v.x; fr[1] = v.y; fr[2] = v.z; fr[3] = v.w;
+        } else {
+            fr[0] = *reinterpret_cast<const float *>(p);
+        }
+    }
+    __device__ __forceinline__ void load_row_at(float (&fr)[S::VEC], unsigned off, const char *rb) const
+    {
+        const char *p = rb + (off + lane_off);
         if constexpr (S::VEC == 4) {
             const v4f v = *reinterpret_cast<const v4f *>(p);
             fr[0] = v.x; fr[1] = v.y; fr[2] = v.z; fr[3] = v.w;
@@ -1071,14 +1108,17 @@ struct LeanCsrProducer {
             const int pid_cur = d0.pid;
             // batch d1: positions and (below) rows go in flight; the cursor's batch: ids
             int idc[U];
+            const int ro[2] = {(int)((unsigned)idn[0] * (4u * S::DI)), (int)((unsigned)idn[1] * (4u * S::DI))};
+            if constexpr (!ROW16) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) idc[u] = spread(idn, perm_id, u);
+                for (int u = 0; u < U; ++u) idc[u] = spread(idn, perm_id, u);
+            }
             if constexpr (!SUM) load_pos(pn, pc, idn, d1);
             const char *rb = reinterpret_cast<const char *>(rows + (int64_t)d1.b * N * (unsigned)S::DI);
             d0 = d1;
             fetch(c, idn, d1);
-            constexpr bool DP_LDS = FLEX_DP_LDS && !SUM;
-            float dpc[DP_LDS ? 1 : U];
+            constexpr bool DP_LDS = !SUM && !MX;
+            float dpc[SUM ? U : 1];
             v4f dpv[DP_LDS ? 3 : 1];
             if constexpr (DP_LDS) {
                 // entry (16 h + e), component c sits at float 4 * (16 h + e) + c = 64 h + lane
@@ -1088,7 +1128,7 @@ struct LeanCsrProducer {
                 wave_lds_sync();
                 dpv[0] = *reinterpret_cast<const v4f *>(s_dp + dp_rd);          // rows 0 and 1 now, row u + 2 while
                 dpv[1] = *reinterpret_cast<const v4f *>(s_dp + 16 + dp_rd);     // row u is accumulated
-            } else {
+            } else if constexpr (SUM) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) dpc[u] = __int_as_float(spread(dpe, perm_dp, u));
             }
@@ -1109,14 +1149,18 @@ struct LeanCsrProducer {
 #pragma unroll
                             for (int v = 0; v < S::VEC; ++v) acc[v][3] = fmaf(dpc[u], fv[v], acc[v][3]);
                         }
-                    } else {
-                        float dx, dy, dz, one;           // one: 1 for a real entry, 0 for a missing one
-                        if constexpr (DP_LDS) {
-                            dx = dpv[u % 3][0]; dy = dpv[u % 3][1]; dz = dpv[u % 3][2]; one = dpv[u % 3][3];
+                    } else if constexpr (MX) {
+                        const float d = __int_as_float(dpe[u >> 2]);
+                        if (u == 0 && first) {
+#pragma unroll
+                            for (int v = 0; v < S::VEC; ++v) acc[v] = outer_slot(d, fv[v], v4f{0.f, 0.f, 0.f, 0.f}, u & 3);
                         } else {
-                            dx = dpp_move<0x00>(dpc[u]); dy = dpp_move<0x55>(dpc[u]); dz = dpp_move<0xAA>(dpc[u]);
-                            one = dpp_move<0xFF>(dpc[u]);
+#pragma unroll
+                            for (int v = 0; v < S::VEC; ++v) acc[v] = outer_slot(d, fv[v], acc[v], u & 3);
                         }
+                    } else {
+                        // one: 1 for a real entry, 0 for a missing one
+                        const float dx = dpv[u % 3][0], dy = dpv[u % 3][1], dz = dpv[u % 3][2], one = dpv[u % 3][3];
                         if (u == 0 && first) {
 #pragma unroll
                             for (int v = 0; v < S::VEC; ++v)
@@ -1132,7 +1176,10 @@ struct LeanCsrProducer {
                         }
                     }
                 }
-                if (u < next_rows) load_row(f[u], idc[u], rb);
+                if (u < next_rows) {
+                    if constexpr (ROW16) load_row_at(f[u], (unsigned)row_bcast_slot(ro[u >> 2], u & 3), rb);
+                    else load_row(f[u], idc[u], rb);
+                }
                 // keep the loop's shape: the scheduler would otherwise collect the eight loads at the end
                 // of the iteration and wait for all of them at its start (no row would be in flight
                 // while the previous ones are accumulated)
@@ -1222,20 +1269,18 @@ __device__ __forceinline__ void consumer_f16(int cw, const void *__restrict__ th
     constexpr int RSTR = SWZ ? 4 * G::KDP : G::ARS;                    // bytes between tile rows
     constexpr int BUFB = SWZ ? G::T * 4 * G::KDP : G::T * G::ROWB;     // bytes per tile buffer
     int a_off[G::IPW];                // byte offset of this lane's 16-byte fragment (hi part, step 0)
-    int a_odd[G::IPW];                // SWZ: the same for step 1 minus 64 (the XOR reaches into bit 6)
 #pragma unroll
     for (int it = 0; it < G::IPW; ++it) {
         const int idx = active ? cw + it * G::NC : 0;
         const int row = (idx / G::NS) * 16 + r16;
         if constexpr (SWZ) {
             a_off[it] = row * RSTR + ((16 * q) ^ tile_swizzle(row));
-            a_odd[it] = row * RSTR + ((16 * q + 64) ^ tile_swizzle(row)) - 64;
         } else {
             a_off[it] = row * RSTR + 16 * q;
-            a_odd[it] = a_off[it];
         }
     }
-    auto frag_off = [&](int it, int st) { return ((SWZ && (st & 1)) ? a_odd[it] : a_off[it]) + 64 * st; };
+    // step st: 64 * st bytes on; SWZ: its two lowest bits meet the swizzle's (rows and buffers are multiples of 256 bytes)
+    auto frag_off = [&](int it, int st) { return SWZ ? (a_off[it] ^ (64 * (st & 3))) + 256 * (st >> 2) : a_off[it] + 64 * st; };
 
     TileWalk tw(sc, tiles_per_cloud);
     int kb = 0;                       // k % NBUF
@@ -1299,7 +1344,7 @@ __device__ __forceinline__ void consumer_f16(int cw, const void *__restrict__ th
 // ---------------------------------------------------------------------------
 template <class S, bool OUT_BCN, int PM, bool TAIL = false>
 __global__ __launch_bounds__((WsGeom<S, PM>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void gather_contract_lean_kernel(const float *__restrict__ rows, const float *__restrict__ pos,
+void gather_contract_lean_kernel(const float *__restrict__ rows, const PosRef pos,
                                  const int32_t *__restrict__ nbr, const void *__restrict__ thetaP,
                                  int theta_exp_off, float *__restrict__ out, int N, int K,
                                  int tiles_per_cloud, int total_tiles)
@@ -1342,7 +1387,7 @@ void gather_contract_lean_kernel(const float *__restrict__ rows, const float *__
 // Feature gradient with the lean in-edge producers (same consumers as the forward kernel).
 template <class S, bool OUT_BCN, int PM>
 __global__ __launch_bounds__((WsGeom<S, PM>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void grad_feat_lean_kernel(const float *__restrict__ rows, const float *__restrict__ pos,
+void grad_feat_lean_kernel(const float *__restrict__ rows, const PosRef pos,
                            const int32_t *__restrict__ off, const int32_t *__restrict__ src,
                            const int32_t *__restrict__ order,
                            const void *__restrict__ thetaP, int theta_exp_off, float *__restrict__ out,
@@ -1373,7 +1418,7 @@ void grad_feat_lean_kernel(const float *__restrict__ rows, const float *__restri
         P.set_dp_stage(s_D[w]);
         float rsc[S::VEC][4];
         load_row_scales<S>(rsc, thetaP, theta_exp_off, P.t);
-        const bool id_writer = (threadIdx.x & 0x33) == 0;        // entry lanes (slot 0, component 0) of the four points
+        const bool id_writer = (threadIdx.x & P.ENTRY0) == 0;        // entry lanes (slot 0, component 0) of the four points
         P.run([&](const v4f (&acc)[S::VEC], int i, int, int, int pid) {
             const int buf = i & 1;
             store_split_rows<S>(acc, rsc, s_A + buf * (G::T * G::ROWB), s_E + buf * G::T, P.pw * G::PW + P.grp, P.t,
@@ -1633,9 +1678,15 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 
-// row stride of a three-piece bf16 tile of W columns: = 32 mod 128 bytes, so the four rows one
-// 16-lane group reads (32 bytes each) and the rows four lane groups write fall on distinct banks
-constexpr int bf3_stride(int W) { return 6 * W + ((32 - (6 * W) % 128) + 128) % 128; }
+// A three-piece bf16 tile of W columns: row stride = 32 mod 256 bytes, and the byte address inside a row XORed with
+// bf3_swap(row).  A turn of the transposing reads (32 lanes, 64 banks) takes 32 bytes each of rows 0-3 and 8-11 (mod 16):
+// the stride spreads the four rows, the XOR parts the two fours, whose places would otherwise be the same banks (15 percent
+// of the wide layers' parameter-gradient kernel went into those conflicts).
+constexpr int bf3_stride(int W) { return rup_c(6 * W, 256) + 32; }
+__device__ __forceinline__ int bf3_swap(int row) { return (row & 8) << 4; }
+// byte address v + K inside a row, XORed with the swap; K: a constant, so that what is left of it is an offset in the instruction.
+// v below 128, or K a multiple of 256.
+__device__ __forceinline__ int bf3_at(int v, int K, int swap) { return (K & 128) ? (v ^ swap ^ 128) + (K - 128) : (v ^ swap) + K; }
 
 // x -> (h, m, l) by truncation, two values at a time, packed as bf16 pairs (first value low)
 __device__ __forceinline__ void split_bf3(float x0, float x1, unsigned &h, unsigned &m, unsigned &l)
@@ -1651,18 +1702,26 @@ __device__ __forceinline__ void split_bf3(float x0, float x1, unsigned &h, unsig
 }
 
 // operand fragment: 8 consecutive points (p0..p0+7 given by the lane's group) of column col0 + lane%16
-__device__ __forceinline__ bf8 read_tr_frag(const char *tile, int stride, int p0, int byte_col0, int j16)
+__device__ __forceinline__ bf8 read_tr_at(const char *a, int stride)
 {
     typedef __attribute__((address_space(3))) v4s *lds_v4s;
-    const char *a = tile + (p0 + (j16 >> 2)) * stride + byte_col0 + 8 * (j16 & 3);
     const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(__attribute__((address_space(3))) char *)a);
     const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(__attribute__((address_space(3))) char *)(a + 4 * stride));
     const v8s v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf8, v);
 }
+__device__ __forceinline__ bf8 read_tr_frag(const char *tile, int stride, int p0, int byte_col0, int j16)
+{
+    return read_tr_at(tile + (p0 + (j16 >> 2)) * stride + byte_col0 + 8 * (j16 & 3), stride);
+}
+// the same from a three-piece bf16 tile, the column at byte v + K of a row (bf3_at); p0 a multiple of 8
+__device__ __forceinline__ bf8 read_bf3_frag(const char *tile, int stride, int p0, int v, int K, int j16)
+{
+    return read_tr_at(tile + (p0 + (j16 >> 2)) * stride + bf3_at(v + 8 * (j16 & 3), K, bf3_swap(p0)), stride);
+}
 
 template <class S, bool TAIL>
-__device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ rows, const float *__restrict__ pos,
+__device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ rows, const PosRef pos,
                                                      const int32_t *__restrict__ nbr,
                                                      const float *__restrict__ g_rows, float *__restrict__ partial,
                                                      int N, int K, int tiles_per_cloud, const TileSchedule sc)
@@ -1713,23 +1772,24 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
             const int buf = i & 1;
             // aggregate rows, three bf16 pieces
             if (P.grp < G::PW && (S::VEC * P.t) < S::DIP) {
-                char *row = s_A[buf] + (P.pw * G::PW + P.grp) * AS + 2 * S::VEC * P.t;
+                char *row = s_A[buf] + (P.pw * G::PW + P.grp) * AS;
+                const int swap = bf3_swap(P.pw * G::PW);     // of all four points of the wave
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
-                    char *d = row + 2 * jj * S::DIP;
+                    auto d = [&](int part) { return row + ((2 * S::VEC * P.t + 2 * jj * S::DIP + 2 * part * S::KD) ^ swap); };
                     if constexpr (S::VEC == 4) {
                         unsigned h0, m0, l0, h1, m1, l1;
                         split_bf3(acc[0][jj], acc[1][jj], h0, m0, l0);
                         split_bf3(acc[2][jj], acc[3][jj], h1, m1, l1);
-                        *reinterpret_cast<uint2 *>(d) = make_uint2(h0, h1);
-                        *reinterpret_cast<uint2 *>(d + 2 * S::KD) = make_uint2(m0, m1);
-                        *reinterpret_cast<uint2 *>(d + 4 * S::KD) = make_uint2(l0, l1);
+                        *reinterpret_cast<uint2 *>(d(0)) = make_uint2(h0, h1);
+                        *reinterpret_cast<uint2 *>(d(1)) = make_uint2(m0, m1);
+                        *reinterpret_cast<uint2 *>(d(2)) = make_uint2(l0, l1);
                     } else {
                         unsigned h, m, l;
                         split_bf3(acc[0][jj], 0.f, h, m, l);
-                        *reinterpret_cast<unsigned short *>(d) = (unsigned short)h;
-                        *reinterpret_cast<unsigned short *>(d + 2 * S::KD) = (unsigned short)m;
-                        *reinterpret_cast<unsigned short *>(d + 4 * S::KD) = (unsigned short)l;
+                        *reinterpret_cast<unsigned short *>(d(0)) = (unsigned short)h;
+                        *reinterpret_cast<unsigned short *>(d(1)) = (unsigned short)m;
+                        *reinterpret_cast<unsigned short *>(d(2)) = (unsigned short)l;
                     }
                 }
             }
@@ -1738,13 +1798,15 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
             for (int c = 0; c < NCH; ++c) {
                 const int ch = threadIdx.x + c * 64 * G::NP;
                 if (ch < G::T * CPR) {
-                    char *d = s_G[buf] + (ch / CPR) * GS + 2 * 4 * (ch % CPR);
+                    char *row = s_G[buf] + (ch / CPR) * GS;
+                    const int swap = bf3_swap(ch / CPR);
+                    auto d = [&](int part) { return row + ((2 * 4 * (ch % CPR) + 2 * part * S::DOP) ^ swap); };
                     unsigned h0, m0, l0, h1, m1, l1;
                     split_bf3(gv[c][0], gv[c][1], h0, m0, l0);
                     split_bf3(gv[c][2], gv[c][3], h1, m1, l1);
-                    *reinterpret_cast<uint2 *>(d) = make_uint2(h0, h1);
-                    *reinterpret_cast<uint2 *>(d + 2 * S::DOP) = make_uint2(m0, m1);
-                    *reinterpret_cast<uint2 *>(d + 4 * S::DOP) = make_uint2(l0, l1);
+                    *reinterpret_cast<uint2 *>(d(0)) = make_uint2(h0, h1);
+                    *reinterpret_cast<uint2 *>(d(1)) = make_uint2(m0, m1);
+                    *reinterpret_cast<uint2 *>(d(2)) = make_uint2(l0, l1);
                 }
             }
             load_g(nb, nlw0);
@@ -1787,18 +1849,22 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
 #pragma unroll
         for (int a = 0; a < NBW; ++a) {
             const int col = 2 * 16 * (wn + a * WN);
-            gH[a] = read_tr_frag(sG, GS, 8 * q, col, r16);
-            gM[a] = read_tr_frag(sG, GS, 8 * q, col + 2 * S::DOP, r16);
-            gL[a] = read_tr_frag(sG, GS, 8 * q, col + 4 * S::DOP, r16);
+            gH[a] = read_bf3_frag(sG, GS, 8 * q, col + 0 * S::DOP, 0, r16);
+            gM[a] = read_bf3_frag(sG, GS, 8 * q, col + 2 * S::DOP, 0, r16);
+            gL[a] = read_bf3_frag(sG, GS, 8 * q, col + 4 * S::DOP, 0, r16);
         }
 #pragma unroll
         for (int c = 0; c < MBW; ++c) {
             const int mb = wm + c * WM;
             if (mb >= MB) continue;
-            const int col = 2 * 16 * mb;
-            const bf8 aH = read_tr_frag(sA, AS, 8 * q, col, r16);
-            const bf8 aM = read_tr_frag(sA, AS, 8 * q, col + 2 * S::KD, r16);
-            const bf8 aL = read_tr_frag(sA, AS, 8 * q, col + 4 * S::KD, r16);
+            // where a piece and a step of c are whole multiples of 128 bytes they stay constants
+            constexpr bool EVEN = (2 * S::KD) % 256 == 0 && 32 * WM == 128;
+            const int v = EVEN ? 32 * wm : 32 * mb, K = EVEN ? 32 * WM * c : 0;
+            auto frag = [&](int part) {
+                return EVEN ? read_bf3_frag(sA, AS, 8 * q, v, K + 2 * part * S::KD, r16)
+                            : read_bf3_frag(sA, AS, 8 * q, v + 2 * part * S::KD, 0, r16);
+            };
+            const bf8 aH = frag(0), aM = frag(1), aL = frag(2);
 #define FLEX_BF_MFMA(X, Y)                                                                         \
     _Pragma("unroll") for (int a = 0; a < NBW; ++a)                                               \
         acc[c][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(X, Y[a], acc[c][a], 0, 0, 0)
@@ -1830,7 +1896,7 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
 
 template <class S, bool TAIL = false>
 __global__ __launch_bounds__((WsGeom<S, 2, 2>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void grad_theta_lean_kernel(const float *__restrict__ rows, const float *__restrict__ pos,
+void grad_theta_lean_kernel(const float *__restrict__ rows, const PosRef pos,
                             const int32_t *__restrict__ nbr, const float *__restrict__ g_rows,
                             float *__restrict__ partials, int N, int K, int tiles_per_cloud, int total_tiles)
 {
@@ -1873,7 +1939,10 @@ struct FusedGeom {
     static constexpr int NTW = 4;                       // T waves
     static constexpr int NT = 64 * (G::NP + G::NC + NTW);
     static constexpr int NBUF = 3;
-    static constexpr int FS = 4 * S::DO + 32;           // own' row: [hi: DO halves][lo: DO halves], = 32 mod 128 bytes
+    static constexpr int FS = 4 * S::DO + 32;           // own' row: [hi: DO halves][lo: DO halves], = 32 mod 256 bytes
+    // a turn of the transposing reads takes rows 0-3 and 8-11 (mod 16), whose places 8 rows apart would be the same
+    // banks: rows with bit 3 hold their halves the other way round
+    static __device__ __forceinline__ int own_swap(int row) { return ((row >> 3) & 1) * (2 * S::DO); }
     static constexpr int ARS = 4 * G::KDP;              // aggregate tile rows, swizzled form
     static constexpr int RB = S::DI / 16, CB = S::DO / 16;
     static constexpr int FLUSH = 64;
@@ -1918,7 +1987,7 @@ __device__ __forceinline__ h8 read_tr_frag_swz(const char *tile, int stride, int
 template <class S, bool OUT_BCN>
 __global__ __launch_bounds__((FusedGeom<S>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__restrict__ own_rows,
-                           const float *__restrict__ pos, const int32_t *__restrict__ off,
+                           const PosRef pos, const int32_t *__restrict__ off,
                            const int32_t *__restrict__ src, const int32_t *__restrict__ order,
                            const void *__restrict__ thetaP, int theta_exp_off, float *__restrict__ grad_feat,
                            float *__restrict__ partials, int *__restrict__ overflow, int N, int tiles_per_cloud,
@@ -1926,12 +1995,12 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
 {
     using F = FusedGeom<S>;
     using G = typename F::G;
-    __shared__ __attribute__((aligned(128))) char s_A[F::NBUF * G::T * F::ARS];
+    __shared__ __attribute__((aligned(256))) char s_A[F::NBUF * G::T * F::ARS];
     __shared__ __attribute__((aligned(16))) char s_F[2 * G::T * F::FS];
     __shared__ int s_E[F::NBUF * G::T];
     __shared__ int s_P[F::NBUF * G::T];
     __shared__ __attribute__((aligned(16))) float s_D[G::NP][128];
-    __shared__ __attribute__((aligned(16))) int s_cs[S::DO];
+    __shared__ int s_cs[S::DO];
 
     const TileSchedule sc(total_tiles);
     const int w = threadIdx.x >> 6;
@@ -1975,7 +2044,7 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
         P.set_dp_stage(s_D[w]);
         float rsc[S::VEC][4];
         load_row_scales<S>(rsc, thetaP, theta_exp_off, P.t);
-        const bool id_writer = (threadIdx.x & 0x33) == 0;
+        const bool id_writer = (threadIdx.x & P.ENTRY0) == 0;
         int buf = 0;
         P.run([&](const v4f (&acc)[S::VEC], int, int, int, int pid) {
             store_split_rows<S, true>(acc, rsc, s_A + buf * (G::T * F::ARS), s_E + buf * G::T, P.pw * G::PW + P.grp,
@@ -2025,8 +2094,8 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
                 }
                 if (!(m < 65504.f)) *overflow = FUSED_OVERFLOW;      // also a NaN: the stand-alone kernel takes over
                 char *row = s_F + (fb * G::T + slot) * F::FS + 8 * r16;
-                *reinterpret_cast<h4 *>(row) = h4{h[0][0], h[0][1], h[1][0], h[1][1]};
-                *reinterpret_cast<h4 *>(row + 2 * S::DO) = h4{l[0][0], l[0][1], l[1][0], l[1][1]};
+                *reinterpret_cast<h4 *>(row + F::own_swap(slot)) = h4{h[0][0], h[0][1], h[1][0], h[1][1]};
+                *reinterpret_cast<h4 *>(row + (2 * S::DO - F::own_swap(slot))) = h4{l[0][0], l[0][1], l[1][0], l[1][1]};
             }
             __device__ __forceinline__ void end(int k)
             {
@@ -2114,11 +2183,11 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
         // waits for LDS once per tile and not once per row block
         h8 fh[F::CB], fl[F::CB];
 #pragma unroll
-        for (int cb = 0; cb < F::CB; ++cb) fh[cb] = read_tr_frag_h(sF, F::FS, 8 * qv, 2 * 16 * cb, r16v);
+        for (int cb = 0; cb < F::CB; ++cb) fh[cb] = read_tr_frag_h(sF, F::FS, 8 * qv, F::own_swap(8 * qv) + 2 * 16 * cb, r16v);
         h8 bl = read_tr_frag_swz(sA, F::ARS, 8 * qv, 2 * (S::DIP * j) + 2 * G::KDP, r16v);
         h8 bh = read_tr_frag_swz(sA, F::ARS, 8 * qv, 2 * (S::DIP * j), r16v);
 #pragma unroll
-        for (int cb = 0; cb < F::CB; ++cb) fl[cb] = read_tr_frag_h(sF, F::FS, 8 * qv, 2 * S::DO + 2 * 16 * cb, r16v);
+        for (int cb = 0; cb < F::CB; ++cb) fl[cb] = read_tr_frag_h(sF, F::FS, 8 * qv, 2 * S::DO - F::own_swap(8 * qv) + 2 * 16 * cb, r16v);
 #pragma unroll
         for (int rb = 0; rb < F::RB; ++rb) {
             h8 bl_n = bl, bh_n = bh;
@@ -2229,7 +2298,7 @@ template <class S, bool TAIL>
 __global__ __launch_bounds__((WsGeom<S, 2, 2>::NT)) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void grad_theta_lean_late_kernel(int *__restrict__ control, const float *__restrict__ rscale,
                                  const float *__restrict__ grad_theta, const float *__restrict__ grad_bias, int Din, int Dout,
-                                 const float *__restrict__ rows, const float *__restrict__ pos,
+                                 const float *__restrict__ rows, const PosRef pos,
                                  const int32_t *__restrict__ nbr, const float *__restrict__ g_rows,
                                  float *__restrict__ partials, int N, int K, int tiles_per_cloud, int total_tiles)
 {
@@ -2354,7 +2423,7 @@ void grad_pos_kernel(const float *__restrict__ rows, const int32_t *__restrict__
         };
         if constexpr (CSR) {
             LeanCsrProducer<S, PM, true> P;
-            P.init(rows, nullptr, off, src, N, w, sc, tiles_per_cloud);
+            P.init(rows, PosRef{}, off, src, N, w, sc, tiles_per_cloud);
             if (P.count > 0) {
                 int b0, lw00;
                 P.first_coords(b0, lw00);
@@ -2367,7 +2436,7 @@ void grad_pos_kernel(const float *__restrict__ rows, const int32_t *__restrict__
             });
         } else {
             LeanProducer<S, PM, true, TAIL> P;
-            P.init(rows, nullptr, nbr, N, K, w, sc, tiles_per_cloud);
+            P.init(rows, PosRef{}, nbr, N, K, w, sc, tiles_per_cloud);
             if (P.count > 0) {
                 int b0, lw00;
                 P.first_coords(b0, lw00);
