@@ -1199,8 +1199,9 @@ struct LeanCsrProducer {
 // the workgroup.  cw = consumer index; G = the workgroup geometry; barriers pair with the producers'.
 // ORD: tile slot pt holds the point s_P[pt] (the producers walk the cloud in a given order), not position l0 + pt.
 // NBUF: tile buffers the producers cycle through (tile k sits in buffer k % NBUF).
-// hook.begin(k, kb, b) runs right after tile k's barrier (kb = its buffer, b = its cloud), hook.end(k) after the
-// wave's stores of tile k: extra per-tile work a kernel hangs on its consumer waves.
+// hook.begin(k, kb, b) runs right after tile k's barrier (kb = its buffer, b = its cloud), hook.end(k) after its matrix ops:
+// extra per-tile work a kernel hangs on its consumer waves.  (Before the stores: a wave's loads and stores retire in the order
+// they were issued, so what waits for a load behind this tile's stores waits for those to reach memory.)
 struct NoTileHook {
     __device__ __forceinline__ void begin(int, int, int) {}
     __device__ __forceinline__ void end(int) {}
@@ -1322,6 +1323,7 @@ __device__ __forceinline__ void consumer_f16(int cw, const void *__restrict__ th
             for (int it = 0; it < G::IPW; ++it)
                 if (s + 1 < KS2) bl[it] = *reinterpret_cast<const h8 *>(sA + frag_off(it, s + 1) + 2 * G::KDP);
         }
+        hook.end(k);
 #pragma unroll
         for (int it = 0; it < G::IPW; ++it) {
             const int idx = active ? cw + it * G::NC : 0;
@@ -1331,7 +1333,6 @@ __device__ __forceinline__ void consumer_f16(int cw, const void *__restrict__ th
             for (int i = 0; i < 4; ++i) d[i] = __builtin_ldexpf(d[i], -(e_pt + e_col[i]));   // undo both scalings
             store_item(r, it, d, ORD ? s_P + kb * G::T : nullptr);
         }
-        hook.end(k);
     }
 }
 
