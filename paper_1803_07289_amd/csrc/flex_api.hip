@@ -47,6 +47,8 @@ hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int gs
 // rows of at most 16 channels, one point per lane (flex_narrow.hip)
 hipError_t launch_narrow_0(const TileArgs &a, int grid, hipStream_t s);
 hipError_t launch_narrow_1(const TileArgs &a, int grid, hipStream_t s);
+hipError_t launch_narrow_records_0(const TileArgs &a, const float *rec, const float *rec4, int grid, hipStream_t s);
+hipError_t launch_narrow_records_1(const TileArgs &a, const float *rec, const float *rec4, int grid, hipStream_t s);
 
 bool gather_contract_supported(int DI, int DO)
 {
@@ -318,7 +320,8 @@ static int narrow_rp(int w_in) { return w_in <= 8 ? 8 : 16; }
 static int narrow_blocks(int w_out) { return (w_out + 63) / 64; }
 static size_t narrow_bytes(int w_in, int w_out) { return (size_t)narrow_blocks(w_out) * theta_f16_bytes(narrow_rp(w_in), 64); }
 
-static hipError_t narrow_launch(const float *rows, int rs, int w_in, const float *pos, const int32_t *nbr,
+// rec (null: none): the rows' records, the fourth channels of four-channel quads behind them
+static hipError_t narrow_launch(const float *rows, int rs, int w_in, const float *pos, const float *rec, const int32_t *nbr,
                                 const int32_t *off, const int32_t *src, const int32_t *order, const void *theta,
                                 float *out, int w_out, int out_bcn, int B, int N, int K, hipStream_t s)
 {
@@ -335,6 +338,12 @@ static hipError_t narrow_launch(const float *rows, int rs, int w_in, const float
     const int64_t total = (int64_t)B * a.tpc;
     if (total > 0x7fffffff) return hipErrorInvalidValue;
     a.total = (int)total;
+    if (rec != nullptr) {
+        a.chunks = output_block_shares(total, (int64_t)device_cu_count() * 3 / n_out);     // three workgroups of four waves per CU
+        const float *rec4 = rec + (int64_t)B * N * 16;
+        const int grid = n_out * a.chunks;
+        return off != nullptr ? launch_narrow_records_1(a, rec, rec4, grid, s) : launch_narrow_records_0(a, rec, rec4, grid, s);
+    }
     // eight one-wave workgroups per CU are what its registers and LDS hold
     a.chunks = output_block_shares(total, (int64_t)device_cu_count() * 8 / n_out);
     const int grid = n_out * a.chunks;
@@ -388,17 +397,27 @@ static hipError_t gather_pack(PrepList &prep, const GatherPlan &g, const float *
     return hipSuccess;
 }
 
+// The records that the planned kernels gather instead of the tensors (Packed; packed null: none)
+static void pack_points(PrepList &prep, const GatherPlan &g, const float *pos, const float *rows, float *packed, int B, int N, int w_in, int bcn)
+{
+    if (packed == nullptr) return;
+    if (g.route == FLEX_ROUTE_NARROW) prep.records(pos, rows, packed, packed + (int64_t)B * N * 16, B, N, w_in, bcn);
+    else prep.pack_pos(pos, packed, B, N);
+}
+static PosRef pos_ref(const float *pos, const float *packed, int N) { return packed ? pos_packed(packed, N) : pos_planar(pos, N); }
+
 // rows [B*N, rs] onto out [B, N, w_out] or, out_bcn, [B, w_out, N]; on the listed widths' kernels rs = k_in, w_out = k_out
-static hipError_t gather_launch(const GatherPlan &g, const float *rows, int rs, int w_in, const float *pos, const PosRef &pr,
+// packed (null: none): the point locations, on the narrow route the rows with them, as Packed says
+static hipError_t gather_launch(const GatherPlan &g, const float *rows, int rs, int w_in, const float *pos, const float *packed,
                                 const int32_t *nbr, const int32_t *off, const int32_t *src, const int32_t *order,
                                 const void *thetaP, float *out, int w_out, int out_bcn, int B, int N, int K,
                                 hipStream_t s)
 {
     if (g.route == FLEX_ROUTE_NARROW)
-        return narrow_launch(rows, rs, w_in, pos, nbr, off, src, order, thetaP, out, w_out, out_bcn, B, N, K, s);
+        return narrow_launch(rows, rs, w_in, pos, packed, nbr, off, src, order, thetaP, out, w_out, out_bcn, B, N, K, s);
     if (g.route == FLEX_ROUTE_TILE)
         return tile_launch(g.tile, rows, rs, w_in, pos, nbr, off, src, order, thetaP, out, w_out, out_bcn, B, N, K, s);
-    return launch_gather_contract(rows, pos, pr, nbr, off, src, order, thetaP, g.fmt, out, B, N, K, rs, w_out, off != nullptr,
+    return launch_gather_contract(rows, pos, pos_ref(pos, packed, N), nbr, off, src, order, thetaP, g.fmt, out, B, N, K, rs, w_out, off != nullptr,
                                   out_bcn, s);
 }
 
@@ -435,18 +454,22 @@ static bool padded_shape(int Din, int Dout, int *DIp, int *DOp)
 
 static size_t rows_bytes(int64_t B, int64_t N, int width) { return align256(sizeof(float) * (size_t)(B * N) * width); }
 
-// Room for packed point locations (PosRef) behind a plan's own bytes: a call whose workspace has it reads the locations
-// as records, any other reads the tensor.  The results are the same bits.
-struct PosPack {
+// Room for records behind a plan's own bytes: the point locations (PrepList::pack_pos) for the wave-specialised
+// kernels, rows of at most 16 channels together with the locations (PrepList::records) for theirs.  A call whose workspace
+// has it gathers records, any other the tensors; the results are the same bits.  (The tile kernels read the location tensor
+// either way: a lane of theirs reads an entry's three components, the entries of a quarter wave are two slots of eight adjacent points,
+// whose neighbours' components lie in a few lines of the tensor and in as many as sixteen of the records.  128 -> 128, 1M points,
+// parameter gradient 1020 us, from records 1180; 64 -> 13, 2 x 50 021 points, forward 36 and 42.)
+struct Packed {
     size_t at, best;                     // where they go; the workspace that has room for them (the plan's own: no use for them)
-    bool fits(size_t have) const { return at != 0 && have >= best; }
+    const float *in(const char *ws, size_t have) const { return at != 0 && have >= best ? (const float *)(ws + at) : nullptr; }
 };
-static PosPack plan_pos_pack(int64_t B, int64_t N, int route, size_t total)
+static Packed plan_packed(int64_t B, int64_t N, int route, int w_in, size_t total)
 {
-    const bool use = route == FLEX_ROUTE_LEAN && N * 16 < (1ll << 32);
-    if (!use) return PosPack{0, total};
+    const int64_t per_point = route == FLEX_ROUTE_LEAN ? 16 : route == FLEX_ROUTE_NARROW ? 64 + (narrow_record_channels(w_in) == 4 ? 16 : 0) : 0;
+    if (per_point == 0 || N * 64 > (1ll << 32) - 128) return Packed{0, total};       // 32-bit offsets, and one past the end
     const size_t at = align256(total);
-    return PosPack{at, at + align256((size_t)(B * N) * 16)};
+    return Packed{at, at + align256((size_t)(B * N) * per_point)};
 }
 
 struct FwdPlan {
@@ -455,7 +478,7 @@ struct FwdPlan {
     GatherPlan gather;
     bool copy, copy_out;                 // rows are copied (turned round, padded); the result comes from a padded one
     size_t thetaP, rows, out, total;     // byte offsets / total
-    PosPack pos;
+    Packed packed;
 };
 struct BwdPlan {
     bool direct, padded, wide;
@@ -464,7 +487,7 @@ struct BwdPlan {
     bool copy, copy_out;
     bool fused;      // feature and parameter gradients, when both are asked for, come from the one-pass kernel
     size_t thetaP, featT, gT, gfP, partials, order, flag, in_off, in_src, inedge_ws, total;
-    PosPack pos;
+    Packed packed;
 };
 
 static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layout)
@@ -480,7 +503,7 @@ static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     const size_t copies = p.padded ? rows_bytes(B, N, p.k_in) + align256(sizeof(float) * (size_t)4 * p.k_in * p.k_out) +
                                          rows_bytes(B, N, p.k_out) : 0;
     p.total = copies + 256;
-    p.pos = PosPack{0, p.total};
+    p.packed = Packed{0, p.total};
     if (p.direct) return p;
     const bool bcn = layout == FLEX_LAYOUT_BCN;
     // a call whose parameters can be packed into the static scratch beside the turned rows is one that it takes
@@ -496,7 +519,7 @@ static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     if (p.padded)
         at = std::max(at, copies + (p.wide ? wide_packed_bytes(p.k_in, p.k_out) : theta_ws_bytes(p.k_in, p.k_out)));
     p.total = at;
-    p.pos = plan_pos_pack(B, N, p.gather.route, at);
+    p.packed = plan_packed(B, N, p.gather.route, Din, at);
     return p;
 }
 
@@ -508,7 +531,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     p.wide = wide_ok(N, K, p.k_in, p.k_out);
     p.direct = !p.wide && !(gather_contract_supported(p.k_in, p.k_out) && gather_contract_supported(p.k_out, p.k_in));
     p.total = 256;
-    p.pos = PosPack{0, p.total};
+    p.packed = Packed{0, p.total};
     if (p.direct) return p;
     p.gather = plan_gather(B, N, K, Dout, Din, p.k_out, p.k_out, p.k_in, p.padded, 1, SIZE_MAX);
     p.copy = p.padded || layout == FLEX_LAYOUT_BCN;          // the parameter gradients run at the listed widths
@@ -530,7 +553,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
         p.inedge_ws = at; at += inedges_ws_bytes(B * N, K);
     }
     p.total = at;
-    p.pos = plan_pos_pack(B, N, p.gather.route, at);
+    p.packed = plan_packed(B, N, p.gather.route, Dout, at);
     return p;
 }
 
@@ -687,8 +710,8 @@ size_t flexconv_workspace_bytes_best(int op, int B, int N, int K, int Din, int D
     const bool conv = op == FLEX_OP_CONV_FWD || op == FLEX_OP_CONV_BWD || op == FLEX_OP_CONV_BWD_BUILD;
     if (!conv || (layout != FLEX_LAYOUT_BCN && layout != FLEX_LAYOUT_BNC) || !sizes_ok(B, N, K, Din, Dout))
         return flexconv_workspace_bytes(op, B, N, K, Din, Dout, layout);
-    if (op == FLEX_OP_CONV_FWD) return plan_fwd(B, N, K, Din, Dout, layout).pos.best;
-    return plan_bwd(B, N, K, Din, Dout, layout, op == FLEX_OP_CONV_BWD_BUILD).pos.best;
+    if (op == FLEX_OP_CONV_FWD) return plan_fwd(B, N, K, Din, Dout, layout).packed.best;
+    return plan_bwd(B, N, K, Din, Dout, layout, op == FLEX_OP_CONV_BWD_BUILD).packed.best;
 }
 
 int flexconv_fwd(const float *feat, const float *pos, const int32_t *nbr, const float *theta,
@@ -710,18 +733,18 @@ int flexconv_fwd(const float *feat, const float *pos, const int32_t *nbr, const 
     // the kernels for any width take rows as they are; only channel-major ones have to be turned round
     const int w_in = p.gather.own_widths() ? Din : p.k_in, w_out = p.copy_out ? p.k_out : Dout;
     PrepList prep;
-    const float *rows = feat;
-    if (p.copy) {
+    const float *rows = feat, *packed = p.packed.in(ws, workspace_bytes);
+    const bool records = packed != nullptr && p.gather.route == FLEX_ROUTE_NARROW;       // made from the tensor as it is
+    if (p.copy && !records) {
         prep.copy(feat, (float *)(ws + p.rows), B, N, Din, w_in, bcn, 0);
         rows = (const float *)(ws + p.rows);
     }
     void *thetaP = ws + p.thetaP;
     FLEX_HIP(gather_pack(prep, p.gather, theta, bias, thetaP, Din, Dout, p.k_in, p.k_out, 0, s));
-    const PosRef pr = p.pos.fits(workspace_bytes) ? pos_packed((const float *)(ws + p.pos.at), N) : pos_planar(pos, N);
-    if (pr.p != pos) prep.pack_pos(pos, (float *)(ws + p.pos.at), B, N);
+    pack_points(prep, p.gather, pos, feat, (float *)packed, B, N, Din, bcn);
     FLEX_HIP(prep.launch(s));
     float *dst = p.copy_out ? (float *)(ws + p.out) : out;
-    FLEX_HIP(gather_launch(p.gather, rows, w_in, w_in, pos, pr, nbr, nullptr, nullptr, nullptr, thetaP, dst, w_out,
+    FLEX_HIP(gather_launch(p.gather, rows, w_in, w_in, pos, packed, nbr, nullptr, nullptr, nullptr, thetaP, dst, w_out,
                            bcn && !p.copy_out, B, N, K, s));
     if (p.copy_out) FLEX_HIP(launch_copy_rows(dst, out, B, N, p.k_out, Dout, 0, bcn, s));
     return FLEX_OK;
@@ -820,8 +843,9 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
     int *control = (int *)(ws + p.flag);
     const bool fused = p.fused && grad_theta && grad_feat;
     PrepList prep;
-    const float *rows = feat, *g_rows = grad_out;
-    if (p.copy) {
+    const float *rows = feat, *g_rows = grad_out, *packed = p.packed.in(ws, workspace_bytes);
+    const bool records = packed != nullptr && p.gather.route == FLEX_ROUTE_NARROW;       // made from the tensor as it is
+    if (p.copy && (grad_theta || !records)) {
         prep.copy(grad_out, (float *)(ws + p.gT), B, N, Dout, p.k_out, bcn, 0);
         if (grad_theta) prep.copy(feat, (float *)(ws + p.featT), B, N, Din, p.k_in, bcn, 0);
         g_rows = (const float *)(ws + p.gT);
@@ -832,8 +856,8 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
         prep.order(in_off, B, N, order);
     }
     if (fused) prep.clear(control, FUSED_FLAG_INTS);
-    const PosRef pr = p.pos.fits(workspace_bytes) ? pos_packed((const float *)(ws + p.pos.at), N) : pos_planar(pos, N);
-    if (pr.p != pos) prep.pack_pos(pos, (float *)(ws + p.pos.at), B, N);
+    if (grad_feat || !records) pack_points(prep, p.gather, pos, grad_out, (float *)packed, B, N, Dout, bcn);
+    const PosRef pr = pos_ref(pos, records ? nullptr : packed, N);
     FLEX_HIP(prep.launch(s));
     if (fused) {
         int n_wg = 0;
@@ -855,7 +879,7 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
                                    Dout, s));
     if (!grad_feat) return FLEX_OK;
     float *dst = p.copy_out ? (float *)(ws + p.gfP) : grad_feat;
-    FLEX_HIP(gather_launch(p.gather, g_rows, p.k_out, p.gather.own_widths() ? Dout : p.k_out, pos, pr, nullptr, in_off, in_src,
+    FLEX_HIP(gather_launch(p.gather, g_rows, p.k_out, p.gather.own_widths() ? Dout : p.k_out, pos, packed, nullptr, in_off, in_src,
                            order, thetaP, dst, p.copy_out ? p.k_in : Din, bcn && !p.copy_out, B, N, K, s));
     if (p.copy_out) FLEX_HIP(launch_copy_rows(dst, grad_feat, B, N, p.k_in, Din, 0, bcn, s));
     return FLEX_OK;

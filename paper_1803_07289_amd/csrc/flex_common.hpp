@@ -57,6 +57,9 @@ struct PrepList {
     void copy(const float *src, float *dst, int B, int N, int Cs, int Cd, int src_bcn, int dst_bcn, int c_off = 0);
     // pos4[b*N + n] = (x, y, z, 0)
     void pack_pos(const float *pos, float *pos4, int B, int N);
+    // the records of rows of W <= 16 channels (flex_narrow.hip): rec [B*N, 16], rec4 [B*N, 4] (only with four channels a quad);
+    // feat as the caller has it, *_bcn: channel-major
+    void records(const float *pos, const float *feat, float *rec, float *rec4, int B, int N, int W, int bcn);
     void clear(void *dst, int words);
     hipError_t launch(hipStream_t s);
 };
@@ -107,6 +110,9 @@ struct PosRef {
 };
 inline PosRef pos_planar(const float *pos, int N) { return PosRef{pos, 4u * (unsigned)N, 2, 12 * (int64_t)N}; }
 inline PosRef pos_packed(const float *pos4, int N) { return PosRef{pos4, 4u, 4, 16 * (int64_t)N}; }
+
+// channels of a row of w of at most 16 in each quad of its record
+constexpr int narrow_record_channels(int w) { return (w + 3) / 4; }
 
 // Tiled matrix-core path.  `rows` is point-major [B*N, DI].  Returns
 // hipErrorNotSupported when (DI,DO) has no instantiation.

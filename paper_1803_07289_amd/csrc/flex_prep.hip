@@ -481,6 +481,43 @@ __device__ void pack_points(const float *__restrict__ pos, float *__restrict__ p
         if (n0 + PREP_NT * i < N) dst[n0 + PREP_NT * i] = v4f{x[i][0], x[i][1], x[i][2], 0.f};
 }
 
+// ---- rows of at most 16 channels with their locations, as records -----------------------------------------------------
+// rec[(b*N + n)*16 + 4 t ..] = (component t of (x, y, z, 1), channels R t .. R t + 2), rec4[(b*N + n)*4 + t] = channel 4 t + 3 (R = 4);
+// channels past the row's end are zero.  A thread makes a quad: what a wave writes is contiguous.
+struct RecordArgs {
+    int N, W, bcn, bpc;
+    float *rec4;
+};
+static constexpr int RECORDS_PER_THREAD = 2;
+
+__device__ void make_records(const float *__restrict__ pos, const float *__restrict__ feat, float *__restrict__ rec,
+                             const RecordArgs &p, int block)
+{
+    const int b = block / p.bpc, n0 = (block - b * p.bpc) * (PREP_NT / 4 * RECORDS_PER_THREAD) + (threadIdx.x >> 2), t = threadIdx.x & 3;
+    const int R = narrow_record_channels(p.W);
+    const float *xyz = pos + (int64_t)b * 3 * p.N, *f = feat + (int64_t)b * p.N * p.W;
+    const int64_t sn = p.bcn ? 1 : p.W, sc = p.bcn ? p.N : 1;
+#pragma unroll
+    for (int i = 0; i < RECORDS_PER_THREAD; ++i) {
+        const int n = n0 + PREP_NT / 4 * i, at = min(n, p.N - 1);
+        const float x = xyz[(int64_t)min(t, 2) * p.N + at];
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = R * t + r;
+            v[r] = 0.f;
+            if (r < R) {
+                const float y = f[at * sn + min(c, p.W - 1) * sc];
+                v[r] = c < p.W ? y : 0.f;
+            }
+        }
+        if (n < p.N) {
+            reinterpret_cast<v4f *>(rec)[((int64_t)b * p.N + n) * 4 + t] = v4f{t < 3 ? x : 1.f, v[0], v[1], v[2]};
+            if (R == 4) p.rec4[((int64_t)b * p.N + n) * 4 + t] = v[3];
+        }
+    }
+}
+
 // ---- the launch ----------------------------------------------------------------------------------
 struct PrepJob {
     int kind, blocks;
@@ -492,10 +529,11 @@ struct PrepJob {
         CopyArgs copy;
         struct { int N, wpc, windows; } order;
         struct { int N, bpc; } points;
+        RecordArgs records;
         struct { int words; } clear;
     };
 };
-enum { PREP_PACK, PREP_PACK_POS, PREP_ORDER, PREP_COPY, PREP_POINTS, PREP_CLEAR };
+enum { PREP_PACK, PREP_PACK_POS, PREP_ORDER, PREP_COPY, PREP_POINTS, PREP_RECORDS, PREP_CLEAR };
 static_assert(sizeof(PrepJob) <= PREP_JOB_BYTES, "PrepList's storage");
 struct PrepJobs {
     PrepJob job[PREP_MAX_JOBS];
@@ -524,6 +562,9 @@ __global__ __launch_bounds__(PREP_NT) __attribute__((amdgpu_waves_per_eu(8, 8)))
         break;
     case PREP_POINTS:
         pack_points((const float *)j.a, (float *)j.dst, j.points.N, j.points.bpc, block);
+        break;
+    case PREP_RECORDS:
+        make_records((const float *)j.a, (const float *)j.b, (float *)j.dst, j.records, block);
         break;
     default:
         for (int w = threadIdx.x; w < j.clear.words; w += PREP_NT) ((uint32_t *)j.dst)[w] = 0u;
@@ -578,6 +619,13 @@ void PrepList::pack_pos(const float *pos, float *pos4, int B, int N)
 {
     const int bpc = (N + PREP_NT * POINTS_PER_THREAD - 1) / (PREP_NT * POINTS_PER_THREAD);
     if (PrepJob *j = next_job(*this, PREP_POINTS, (int64_t)B * bpc, pos, nullptr, pos4)) { j->points.N = N; j->points.bpc = bpc; }
+}
+
+void PrepList::records(const float *pos, const float *feat, float *rec, float *rec4, int B, int N, int W, int bcn)
+{
+    constexpr int PER_BLOCK = PREP_NT / 4 * RECORDS_PER_THREAD;
+    const int bpc = (N + PER_BLOCK - 1) / PER_BLOCK;
+    if (PrepJob *j = next_job(*this, PREP_RECORDS, (int64_t)B * bpc, pos, feat, rec)) j->records = RecordArgs{N, W, bcn, bpc, rec4};
 }
 
 void PrepList::clear(void *dst, int words)

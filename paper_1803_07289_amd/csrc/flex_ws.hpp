@@ -2001,7 +2001,7 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
     __shared__ int s_E[F::NBUF * G::T];
     __shared__ int s_P[F::NBUF * G::T];
     __shared__ __attribute__((aligned(16))) float s_D[G::NP][128];
-    __shared__ int s_cs[S::DO];
+    __shared__ __attribute__((aligned(16))) int s_cs[S::DO];
 
     const TileSchedule sc(total_tiles);
     const int w = threadIdx.x >> 6;

@@ -1,6 +1,6 @@
-"""The convolution with room for packed point locations behind its workspace (flexconv_workspace_bytes_best) against the
-same call in a workspace of the smallest size, which reads the location tensor itself: the same bits, and both within the
-oracle's tolerance."""
+"""The convolution with room for packed point locations, or records of narrow rows with theirs, behind its workspace
+(flexconv_workspace_bytes_best) against the same call in a workspace of the smallest size, which reads the tensors
+themselves: the same bits, and both within the oracle's tolerance."""
 import pytest
 import torch
 
@@ -22,6 +22,32 @@ class BestWorkspace(ExactWorkspace):
         self.ws = self.buf[:self.need]
 
 
+def compare(B, N, K, Din, Dout, layout, backward, hub=False):
+    say(f"packed: B={B} N={N} K={K} {Din}->{Dout} layout={layout} hub={hub}")
+    pos, nbr, feat, theta, bias, g = random_problem(40 + N + K, B, N, K, Din, Dout)
+    if hub:                                  # point 3 is listed by every centre: a list of N entries, empty ones elsewhere
+        nbr[:, -1, :] = 3
+    a = (to_layout(feat, layout), dev(pos), dev(nbr), dev(theta), dev(bias))
+    gd = to_layout(g, layout)
+    edges = fx.flex_inedges_build(a[2])
+    results = []
+    for kind in (ExactWorkspace, BestWorkspace):
+        w = kind(fx.OP_CONV_BWD if backward else fx.OP_CONV_FWD, B, N, K, Din, Dout, layout)
+        if backward:
+            r = fx.flexconv_bwd(*a, gd, layout=layout, in_edges=edges, workspace=w.ws)
+            r += fx.flexconv_bwd(*a, gd, layout=layout, in_edges=edges, need_params=False, workspace=w.ws)[:1]
+        else:
+            r = (fx.flexconv_fwd(*a, layout=layout, workspace=w.ws),)
+        w.check()
+        results.append(r)
+    for x, y in zip(*results):
+        assert torch.equal(x, y)
+    if backward:
+        assert rel_err(from_layout(results[1][0], layout), oracle.flexconv_bwd(feat, pos, nbr, theta, bias, g)[0]) <= TOL
+    else:
+        assert rel_err(from_layout(results[1][0], layout), oracle.flexconv_fwd(feat, pos, nbr, theta, bias)) <= TOL
+
+
 # clouds around a tile of 32 / 48 points and around a packing block of 2048, K around a batch of eight, several clouds;
 # gathered widths of one lane group per row (64) and of half a one (32), in both directions
 @pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
@@ -30,21 +56,23 @@ class BestWorkspace(ExactWorkspace):
     (2, 33, 3, 64, 128), (1, 300, 8, 64, 32), (1, 300, 12, 32, 64), (2, 2047, 8, 32, 32),
 ])
 def test_packed_locations_change_no_bit(B, N, K, Din, Dout, layout):
-    say(f"packed locations: B={B} N={N} K={K} {Din}->{Dout} layout={layout}")
-    pos, nbr, feat, theta, bias, g = random_problem(40 + N + K, B, N, K, Din, Dout)
-    a = (to_layout(feat, layout), dev(pos), dev(nbr), dev(theta), dev(bias))
-    gd = to_layout(g, layout)
-    edges = fx.flex_inedges_build(a[2])
-    results = []
-    for kind in (ExactWorkspace, BestWorkspace):
-        wf, wb = (kind(op, B, N, K, Din, Dout, layout) if op == fx.OP_CONV_FWD or Dout <= 64 else None
-                  for op in (fx.OP_CONV_FWD, fx.OP_CONV_BWD))
-        r = [fx.flexconv_fwd(*a, layout=layout, workspace=wf.ws)]
-        if wb is not None:                   # (rows wider than 64 channels read the tensor either way)
-            r += fx.flexconv_bwd(*a, gd, layout=layout, in_edges=edges, workspace=wb.ws)
-            wb.check()
-        wf.check()
-        results.append(r)
-    for x, y in zip(*results):
-        assert torch.equal(x, y)
-    assert rel_err(from_layout(results[1][0], layout), oracle.flexconv_fwd(feat, pos, nbr, theta, bias)) <= TOL
+    compare(B, N, K, Din, Dout, layout, False)
+    if Dout <= 64:                           # (rows wider than 64 channels read the tensor either way)
+        compare(B, N, K, Din, Dout, layout, True)
+
+
+# one to four channels a quad with every remainder, clouds around the sixteen points of a wave and the 64 of a tile, result
+# widths that fill, leave and barely enter a block of 64, K around a batch of eight
+@pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
+@pytest.mark.parametrize("B,N,K,W,other", [
+    (1, 1, 1, 1, 4), (1, 15, 3, 2, 64), (2, 16, 8, 3, 32), (1, 17, 9, 4, 65), (3, 63, 8, 5, 68), (1, 65, 16, 8, 3),
+    (1, 257, 17, 9, 64), (2, 130, 8, 11, 130), (1, 300, 8, 12, 64), (2, 97, 5, 13, 64), (1, 5000, 8, 16, 20),
+])
+def test_records_change_no_bit(B, N, K, W, other, layout):
+    compare(B, N, K, W, other, layout, False)
+    compare(B, N, K, other, W, layout, True)
+
+
+def test_records_of_a_hub_point_and_empty_lists():
+    compare(1, 500, 4, 64, 13, fx.BNC, True, hub=True)
+    compare(2, 90, 8, 9, 9, fx.BCN, True, hub=True)
