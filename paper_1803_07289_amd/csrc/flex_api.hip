@@ -47,8 +47,8 @@ hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int gs
 // rows of at most 16 channels, one point per lane (flex_narrow.hip)
 hipError_t launch_narrow_0(const TileArgs &a, int grid, hipStream_t s);
 hipError_t launch_narrow_1(const TileArgs &a, int grid, hipStream_t s);
-hipError_t launch_narrow_records_0(const TileArgs &a, const float *rec, const float *rec4, int grid, hipStream_t s);
-hipError_t launch_narrow_records_1(const TileArgs &a, const float *rec, const float *rec4, int grid, hipStream_t s);
+hipError_t launch_narrow_records_0(const TileArgs &a, const float *rec, const float *rec4, int B, int n_out, hipStream_t s);
+hipError_t launch_narrow_records_1(const TileArgs &a, const float *rec, const float *rec4, int B, int n_out, hipStream_t s);
 
 bool gather_contract_supported(int DI, int DO)
 {
@@ -339,10 +339,8 @@ static hipError_t narrow_launch(const float *rows, int rs, int w_in, const float
     if (total > 0x7fffffff) return hipErrorInvalidValue;
     a.total = (int)total;
     if (rec != nullptr) {
-        a.chunks = output_block_shares(total, (int64_t)device_cu_count() * 3 / n_out);     // three workgroups of four waves per CU
         const float *rec4 = rec + (int64_t)B * N * 16;
-        const int grid = n_out * a.chunks;
-        return off != nullptr ? launch_narrow_records_1(a, rec, rec4, grid, s) : launch_narrow_records_0(a, rec, rec4, grid, s);
+        return off != nullptr ? launch_narrow_records_1(a, rec, rec4, B, n_out, s) : launch_narrow_records_0(a, rec, rec4, B, n_out, s);
     }
     // eight one-wave workgroups per CU are what its registers and LDS hold
     a.chunks = output_block_shares(total, (int64_t)device_cu_count() * 8 / n_out);
@@ -398,10 +396,12 @@ static hipError_t gather_pack(PrepList &prep, const GatherPlan &g, const float *
 }
 
 // The records that the planned kernels gather instead of the tensors (Packed; packed null: none)
-static void pack_points(PrepList &prep, const GatherPlan &g, const float *pos, const float *rows, float *packed, int B, int N, int w_in, int bcn)
+// nbr: what they will be gathered by (null: in-edge lists).
+static void pack_points(PrepList &prep, const GatherPlan &g, const float *pos, const float *rows, float *packed, int B, int N, int w_in, int bcn, const int32_t *nbr, int K)
 {
     if (packed == nullptr) return;
-    if (g.route == FLEX_ROUTE_NARROW) prep.records(pos, rows, packed, packed + (int64_t)B * N * 16, B, N, w_in, bcn);
+    if (g.route == FLEX_ROUTE_NARROW) prep.records(pos, rows, packed, packed + (int64_t)B * N * 16, B, N, w_in, bcn,
+                                                 (int64_t)B * N * K * 4 <= (96ll << 20) ? nbr : nullptr, K);     // (beside the records)
     else prep.pack_pos(pos, packed, B, N);
 }
 static PosRef pos_ref(const float *pos, const float *packed, int N) { return packed ? pos_packed(packed, N) : pos_planar(pos, N); }
@@ -464,9 +464,16 @@ struct Packed {
     size_t at, best;                     // where they go; the workspace that has room for them (the plan's own: no use for them)
     const float *in(const char *ws, size_t have) const { return at != 0 && have >= best ? (const float *)(ws + at) : nullptr; }
 };
-static Packed plan_packed(int64_t B, int64_t N, int route, int w_in, size_t total)
+// Records of rows of 5 to 12 channels from 2^17 points on, of 5 to 16 over in-edge lists: shorter rows are not worth 64 bytes
+// (3 -> 32, 500k points: 32 us, from records 44), with a second array they gain nothing where the ids stand in order (16 -> 64,
+// 400k: 50 and 52), and a call of few points is its launches (9 -> 64, K = 8, 20k, 100k, 1M points: 18.8, 20.4, 136 and 19.7,
+// 20.8, 98; K = 16, channel-major, 300k 67 and 47; 6 -> 64, 200k points in no order, 45 and 29).  Over lists, forward and backward:
+// 64 -> 13, 20k points, 61 and 57 us; 64 -> 9, 200k, 128 and 117.
+static bool use_records(int64_t points, int w_in, int csr) { return w_in >= 5 && (csr || (w_in <= 12 && points >= 1 << 17)); }
+static Packed plan_packed(int64_t B, int64_t N, int route, int w_in, int csr, size_t total)
 {
-    const int64_t per_point = route == FLEX_ROUTE_LEAN ? 16 : route == FLEX_ROUTE_NARROW ? 64 + (narrow_record_channels(w_in) == 4 ? 16 : 0) : 0;
+    const int64_t record = use_records(B * N, w_in, csr) ? 64 + (narrow_record_channels(w_in) == 4 ? 16 : 0) : 0;
+    const int64_t per_point = route == FLEX_ROUTE_LEAN ? 16 : route == FLEX_ROUTE_NARROW ? record : 0;
     if (per_point == 0 || N * 64 > (1ll << 32) - 128) return Packed{0, total};       // 32-bit offsets, and one past the end
     const size_t at = align256(total);
     return Packed{at, at + align256((size_t)(B * N) * per_point)};
@@ -519,7 +526,7 @@ static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     if (p.padded)
         at = std::max(at, copies + (p.wide ? wide_packed_bytes(p.k_in, p.k_out) : theta_ws_bytes(p.k_in, p.k_out)));
     p.total = at;
-    p.packed = plan_packed(B, N, p.gather.route, Din, at);
+    p.packed = plan_packed(B, N, p.gather.route, Din, 0, at);
     return p;
 }
 
@@ -553,7 +560,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
         p.inedge_ws = at; at += inedges_ws_bytes(B * N, K);
     }
     p.total = at;
-    p.packed = plan_packed(B, N, p.gather.route, Dout, at);
+    p.packed = plan_packed(B, N, p.gather.route, Dout, 1, at);
     return p;
 }
 
@@ -741,7 +748,7 @@ int flexconv_fwd(const float *feat, const float *pos, const int32_t *nbr, const 
     }
     void *thetaP = ws + p.thetaP;
     FLEX_HIP(gather_pack(prep, p.gather, theta, bias, thetaP, Din, Dout, p.k_in, p.k_out, 0, s));
-    pack_points(prep, p.gather, pos, feat, (float *)packed, B, N, Din, bcn);
+    pack_points(prep, p.gather, pos, feat, (float *)packed, B, N, Din, bcn, nbr, K);
     FLEX_HIP(prep.launch(s));
     float *dst = p.copy_out ? (float *)(ws + p.out) : out;
     FLEX_HIP(gather_launch(p.gather, rows, w_in, w_in, pos, packed, nbr, nullptr, nullptr, nullptr, thetaP, dst, w_out,
@@ -856,7 +863,7 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
         prep.order(in_off, B, N, order);
     }
     if (fused) prep.clear(control, FUSED_FLAG_INTS);
-    if (grad_feat || !records) pack_points(prep, p.gather, pos, grad_out, (float *)packed, B, N, Dout, bcn);
+    if (grad_feat || !records) pack_points(prep, p.gather, pos, grad_out, (float *)packed, B, N, Dout, bcn, nullptr, 0);
     const PosRef pr = pos_ref(pos, records ? nullptr : packed, N);
     FLEX_HIP(prep.launch(s));
     if (fused) {

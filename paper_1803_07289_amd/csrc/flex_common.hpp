@@ -58,8 +58,8 @@ struct PrepList {
     // pos4[b*N + n] = (x, y, z, 0)
     void pack_pos(const float *pos, float *pos4, int B, int N);
     // the records of rows of W <= 16 channels (flex_narrow.hip): rec [B*N, 16], rec4 [B*N, 4] (only with four channels a quad);
-    // feat as the caller has it, *_bcn: channel-major
-    void records(const float *pos, const float *feat, float *rec, float *rec4, int B, int N, int W, int bcn);
+    // feat as the caller has it, *_bcn: channel-major; nbr [B,K,N] or null: read on the way (flex_prep.hip)
+    void records(const float *pos, const float *feat, float *rec, float *rec4, int B, int N, int W, int bcn, const int32_t *nbr, int K);
     void clear(void *dst, int words);
     hipError_t launch(hipStream_t s);
 };

@@ -198,12 +198,14 @@ void narrow_conv_kernel(const TileArgs a)
 // array.  Four lanes are a point; each loads a quad, so a neighbour is ONE access of the texture path (two with R = 4)
 // where a lane's own loads of its row and location are six.  What a lane holds is just what the 4 x 4 x 1 matrix op
 // takes: lane t's location difference as the first operand (component t), a channel as the second, so the four lanes'
-// sums need R ops a neighbour and no exchange at all.  Sixteen points per wave at a time, eight neighbours under way, the
-// next sixteen points' requested while these are contracted; a wave works by itself.  The sums run in the order of the
-// kernel above, and the result is the same bits.
-// Whole rows leave by streaming stores, which keep the gathered records in L2 and are written back at once: with plain
-// ones the kernel took 100 us, with them 63, and the call's preparation, which meets what the call before has left to
-// write back, 29 and 19 (9 -> 64, 1M points, K = 8 in Z-order; the kernel above 124 and 6).
+// sums need R ops a neighbour and no exchange at all.  Sixteen points per wave, whose result leaves by whole rows.  The sums run in the
+// order of the kernel above, and the result is the same bits.
+//
+// A wave serves its sixteen points and ends, and workgroups are dispatched in order, three of eight waves per CU.  What bounds it
+// is the latency of what is not in a cache, ids above all, beside the result's stores.  A wave's loads and stores retire in
+// the order they were issued, so in a wave that goes on to other points every load waits for the stores before it to reach
+// memory, however far ahead it was asked for.  9 -> 64, K = 8, 1M points in Z-order, nothing in a cache: 129 us by the kernel
+// above, 102 by three resident waves per SIMD, 96 here, 69 where the preparation has read the ids (make_records); the preparation 25 and 30.
 template <int CTRL>
 __device__ __forceinline__ unsigned quad_bcast(unsigned x) { return (unsigned)dpp_movi<CTRL>((int)x); }
 __device__ __forceinline__ unsigned quad_lane(unsigned x, int slot)          // slot: a constant after unrolling
@@ -211,296 +213,196 @@ __device__ __forceinline__ unsigned quad_lane(unsigned x, int slot)          // 
     return slot == 0 ? quad_bcast<0x00>(x) : slot == 1 ? quad_bcast<0x55>(x) : slot == 2 ? quad_bcast<0xAA>(x) : quad_bcast<0xFF>(x);
 }
 
-// Walks a wave's batches: eight list slots of its sixteen points of a tile.  A lane's point is lane / 4 of them, its slots lane % 4
-// and four more of the batch.
-template <bool CSR>
-struct RecordWalk {
-    struct Batch {
-        int b, l0;                   // cloud, first point (position) of the wave
-        int n;                       // slots that some point has
-        bool last, real;
-        unsigned self;               // this lane's point
-        int left;                    // CSR: entries of its list from this batch on
-    };
-    TileWalk tw;
-    int k0;                          // first slot of the next batch
-    bool real;
-    int point, lo, deg, most;        // CSR: of the current tile
-    TileWalk tw1;
-    int point1, lo1, hi1;            // and of the next one, in flight
+static constexpr int RECORD_NT = 512, RECORD_POINTS = RECORD_NT / 4;         // threads, points per workgroup
 
-    __device__ __forceinline__ int first_of(const TileWalk &w) const { return w.tic * 64 + 16 * ((int)threadIdx.x >> 6); }
-    __device__ __forceinline__ int at_of(const TileArgs &a, const TileWalk &w) const
-    {
-        return min(first_of(w) + (((int)threadIdx.x >> 2) & 15), a.N - 1);
-    }
-    __device__ __forceinline__ void request(const TileArgs &a)
-    {
-        point1 = a.order[(int64_t)tw1.b * a.N + at_of(a, tw1)];
-        lo1 = a.off[(int64_t)tw1.b * a.N + point1];
-        hi1 = a.off[(int64_t)tw1.b * a.N + point1 + 1];
-    }
-    __device__ __forceinline__ void enter(const TileArgs &a)
-    {
-        tw = tw1; point = point1; lo = lo1;
-        deg = hi1 - lo1;                 // (positions past the cloud: the last one's again)
-        most = max(wave_max(deg), 1);
-        tw1.next_clamped();
-        request(a);
-    }
-    __device__ __forceinline__ RecordWalk(const TileArgs &a, const TileSchedule &sc) : tw(sc, a.tpc), tw1(sc, a.tpc)
-    {
-        k0 = 0;
-        real = true;
-        if constexpr (CSR) { request(a); enter(a); }
-    }
-    // the next batch and this lane's ids of it; past the last tile it repeats that tile
-    __device__ __forceinline__ Batch fetch(const TileArgs &a, int (&id)[2])
-    {
-        Batch d;
-        d.b = tw.b; d.l0 = first_of(tw); d.real = real;
-        const int t = threadIdx.x & 3;
-        int len;
-        if constexpr (CSR) {
-            d.self = (unsigned)point; d.left = deg - k0; len = most;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) id[h] = a.src[k0 + t + 4 * h < deg ? lo + k0 + t + 4 * h : 0];   // a list entry is always there
-        } else {
-            d.self = (unsigned)at_of(a, tw); d.left = 0; len = a.K;
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                id[h] = a.nbr[((int64_t)d.b * a.K + min(k0 + t + 4 * h, a.K - 1)) * a.N + (int)d.self];
-        }
-        d.n = len - k0;
-        k0 += 8;
-        d.last = k0 >= len;
-        if (d.last) {
-            k0 = 0;
-            const bool more = tw.has_next();
-            real = real && more;
-            if constexpr (CSR) enter(a);
-            else tw.next_clamped();
-        }
-        return d;
-    }
-};
-
-// FULL: point-major results, at least four channels in every output block
-template <int R, bool CSR, bool FULL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
+template <int R, bool CSR>
+__global__ __launch_bounds__(RECORD_NT) __attribute__((amdgpu_waves_per_eu(6, 6)))
 void narrow_record_kernel(const TileArgs a, const float *__restrict__ rec, const float *__restrict__ rec4)
 {
-    constexpr int RP = R <= 2 ? 8 : 16, KD = 4 * RP, KS = KD / 32, ARS = 4 * KD + 32, NS = 4, U = 8;
+    constexpr int RP = R <= 2 ? 8 : 16, KD = 4 * RP, KS = KD / 32, ARS = 4 * KD + 32, NS = 4, U = 8, NW = RECORD_NT / 64;
     constexpr int ORS = 64 + 4;                                          // floats of a result row in LDS
-    __shared__ __attribute__((aligned(16))) char s_A[4][16 * ARS];
-    __shared__ __attribute__((aligned(16))) float s_out[4][16 * ORS];
-    __shared__ __attribute__((aligned(16))) char s_th[2 * NS * KS * 1024];      // the parameters' fragments: [hi, lo][slice][step][lane]
+    constexpr int WB = 16 * (ARS > 4 * ORS ? ARS : 4 * ORS);             // a wave's LDS: its split-half rows, then its result
+    constexpr int TH = 2 * NS * KS * 1024;
+    __shared__ __attribute__((aligned(16))) char s_th[TH];               // the parameters' fragments: [hi, lo][slice][step][lane]
+    __shared__ __attribute__((aligned(16))) char s_w[NW][WB];
     __shared__ __attribute__((aligned(16))) int s_ec[64];
+    __shared__ __attribute__((aligned(16))) float s_rs[KD];
 
-    const int j = blockIdx.x / a.chunks;
-    const TileSchedule sc(a.total, (int)blockIdx.x - j * a.chunks, a.chunks);
-    if (!(sc.first < sc.end)) return;
+    // workgroup: output block, XCD's share of the tiles, place in it
+    const int j = blockIdx.x / a.chunks, w = blockIdx.x - j * a.chunks;
+    const int tile = (w & 7) * (a.chunks >> 3) + (w >> 3);
+    if (tile >= a.total) return;
+    const int b = tile / a.tpc, l0 = (tile - b * a.tpc) * RECORD_POINTS + 16 * (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = lane >> 2, t = lane & 3, q = lane >> 4, r16 = lane & 15;
     const char *blk = a.theta + (int64_t)j * a.blk_bytes;
-    if (threadIdx.x < 64) s_ec[threadIdx.x] = reinterpret_cast<const int *>(blk + a.exp_off)[threadIdx.x];
-    for (int i = lane; i < 16 * ARS / 16; i += 64) *reinterpret_cast<v4i *>(s_A[wave] + 16 * i) = v4i{0, 0, 0, 0};   // depth padding
-    for (int i = threadIdx.x; i < 2 * NS * KS * 64; i += 256) *reinterpret_cast<v4i *>(s_th + 16 * i) = *reinterpret_cast<const v4i *>(blk + 16 * i);
-    __syncthreads();
-    float rs[R][4];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) rs[r][jj] = reinterpret_cast<const float *>(blk + a.rs_off)[jj * RP + R * t + r];
 
+    // this lane's point (past the cloud's end its last one again) and the ids of its slots of the first batch: lane % 4 and four more
+    int self = min(l0 + p, a.N - 1), lo = 0, deg = a.K;
+    if constexpr (CSR) {
+        self = a.order[(int64_t)b * a.N + self];
+        lo = a.off[(int64_t)b * a.N + self];
+        deg = a.off[(int64_t)b * a.N + self + 1] - lo;
+    }
+    auto ids = [&](int (&id)[2], int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = k0 + t + 4 * h;
+            if constexpr (CSR) id[h] = a.src[k < deg ? lo + k : 0];      // a list entry is always there (K >= 1)
+            else id[h] = a.nbr[((int64_t)b * a.K + min(k, a.K - 1)) * a.N + self];
+        }
+    };
     const unsigned lane_off = 16u * (unsigned)t, none = 0u - 64u;
-    auto records = [&](const float *base, int b, unsigned bytes) {
+    auto records = [&](const float *base, unsigned bytes) {
         return row_buffer(reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + (int64_t)b * a.N * bytes), (unsigned)a.N * bytes);
     };
-    // byte offsets of the records of this lane's two slots; a slot without an entry: past the end, reads zeros
-    auto offsets = [&](unsigned (&ro)[2], const int (&id)[2], int left) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) ro[h] = !CSR || t + 4 * h < left ? (unsigned)id[h] * 64u : none;
-    };
-    v4f f[U];                                                            // quads under way
-    float f4[R == 4 ? U : 1];
-    auto load = [&](int u, const unsigned (&ro)[2], __amdgpu_buffer_rsrc_t rb, __amdgpu_buffer_rsrc_t rb4) __attribute__((always_inline)) {
-        const unsigned o = quad_lane(ro[u >> 2], u & 3) + lane_off;
-        f[u] = load_row4(rb, o);
-        if constexpr (R == 4) f4[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb4, (int)(o >> 2), 0, 0));
-    };
-    auto own = [&](__amdgpu_buffer_rsrc_t rb, unsigned self) {
-        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, (int)(self * 64u + lane_off), 0, 0));
-    };
+    const auto rb = records(rec, 64u), rb4 = records(rec4, 16u);
+    int id[2];
+    ids(id, 0);
+    // lane 3's component is the constant 1, in the neighbour's record and in the point's own
+    const float own = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, (int)((unsigned)self * 64u + lane_off), 0, 0));
 
-    using Walk = RecordWalk<CSR>;
-    Walk walk(a, sc);
-    int id1[2], id2[2];
-    typename Walk::Batch d0, d1, d2;
-    float c0, c1;
-    {
-        int id0[2];
-        d0 = walk.fetch(a, id0);
-        d1 = walk.fetch(a, id1);
-        unsigned ro[2];
-        offsets(ro, id0, d0.left);
-        const auto rb = records(rec, d0.b, 64u), rb4 = records(rec4, d0.b, 16u);
-        c0 = own(rb, d0.self);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < U; ++u) load(u, ro, rb, rb4);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    // the result's rows of this lane's part of a tile of the wave (FULL): channel and the store of point 4 i + q
-    const int o_full = min(4 * r16, min(64, a.w_out - 64 * j) - 4);
-    auto store_row = [&](int b, int self, int i, const v4f &d) __attribute__((always_inline)) {
-        const int l = __shfl(self, 4 * (4 * i + q), 64);
-        __builtin_nontemporal_store(d, reinterpret_cast<v4fu *>(a.out + b * a.out_b + l * a.out_l + 64 * j + o_full));
-    };
-    if constexpr (FULL) {        // as many stores behind the first rows as behind all others (see below); written again by the same lanes
-        const int self = (int)d0.self, b = d0.b;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) store_row(b, self, i, v4f{0.f, 0.f, 0.f, 0.f});
-        __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int i = threadIdx.x; i < TH / 16; i += RECORD_NT) *reinterpret_cast<v4i *>(s_th + 16 * i) = *reinterpret_cast<const v4i *>(blk + 16 * i);
+    if (threadIdx.x < 64) s_ec[threadIdx.x] = reinterpret_cast<const int *>(blk + a.exp_off)[threadIdx.x];
+    if (threadIdx.x < KD) s_rs[threadIdx.x] = reinterpret_cast<const float *>(blk + a.rs_off)[threadIdx.x];
+    __syncthreads();
+
+    // ---- gather ----
+    const int most = CSR ? max(wave_max(deg), 1) : a.K;
+    const float cen = t == 3 ? (CSR ? 2.f : 0.f) : own;
     v4f acc[R];                                                          // [channel][component]
-    // sums the batch whose rows are under way and sends the next one's off
-    auto batch = [&]() __attribute__((always_inline)) {
-        unsigned ro[2];
-        offsets(ro, id1, d1.left);
-        const auto rb = records(rec, d1.b, 64u), rb4 = records(rec4, d1.b, 16u);
-        c1 = own(rb, d1.self);
-        d2 = walk.fetch(a, id2);
-        // lane 3's component is the constant 1, in the neighbour's record and in the point's own
-        const float cen = t == 3 ? (CSR ? 2.f : 0.f) : c0;
-        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < most; k0 += U) {
+        unsigned ro[2];                                                  // a slot without an entry: past the end, reads zeros
+#pragma unroll
+        for (int h = 0; h < 2; ++h) ro[h] = !CSR || k0 + t + 4 * h < deg ? (unsigned)id[h] * 64u : none;
+        v4f f[U];
+        float f4[R == 4 ? U : 1];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (u < d0.n) {
+            const unsigned o = quad_lane(ro[u >> 2], u & 3) + lane_off;
+            f[u] = load_row4(rb, o);
+            if constexpr (R == 4) f4[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb4, (int)(o >> 2), 0, 0));
+        }
+        ids(id, k0 + U);                                                 // (past the last batch: read, not used)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k0 + u < most) {
                 float dp = CSR ? cen - f[u][0] : f[u][0] - cen;
-                if (CSR) dp = u < d0.left ? dp : 0.f;                    // weighs its zeros with zero, wherever the point lies
+                if (CSR) dp = k0 + u < deg ? dp : 0.f;                   // weighs its zeros with zero, wherever the point lies
 #pragma unroll
                 for (int r = 0; r < R; ++r)
                     acc[r] = __builtin_amdgcn_mfma_f32_4x4x1f32(dp, r < 3 ? f[u][1 + (r < 3 ? r : 0)] : f4[R == 4 ? u : 0], acc[r], 0, 0, 0);
             }
-            load(u, ro, rb, rb4);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        d0 = d1; d1 = d2;
-        c0 = c1;
-        id1[0] = id2[0]; id1[1] = id2[1];
-    };
-    // A wave's loads and stores retire in the order they were issued, and the compiler waits for a load by counting what was
-    // issued after it.  So a tile's first batch stands in a straight line with its stores, whose number is fixed (FULL), and
-    // a wave never waits for a store to reach memory (plain stores, 1M points, 9 -> 64: 100 us where it did, 94 here).
-    while (d0.real) {
-        const int self = (int)d0.self, b = d0.b, l0 = d0.l0;
-        bool more = !d0.last;
-#pragma unroll
-        for (int r = 0; r < R; ++r) acc[r] = v4f{0.f, 0.f, 0.f, 0.f};
-        batch();
-        while (more) {
-            more = !d0.last;
-            batch();
-        }
-        // ---- the points' split-half rows ----
-        float m = 0.f;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                acc[r][jj] *= rs[r][jj];
-                m = __builtin_amdgcn_fmed3f(m, __builtin_fabsf(acc[r][jj]), __builtin_inff());
-            }
-        m = group_max<4>(m);
-        const int ex = 15 - __builtin_amdgcn_frexp_expf(m);
-        wave_lds_sync();                                             // the rows of the points before have been read
-        char *row = s_A[wave] + p * ARS;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const float x = __builtin_ldexpf(acc[r][jj], ex);
-                const _Float16 h = (_Float16)x;
-                *reinterpret_cast<_Float16 *>(row + 2 * (jj * RP + R * t + r)) = h;
-                *reinterpret_cast<_Float16 *>(row + 2 * (KD + jj * RP + R * t + r)) = (_Float16)(x - (float)h);
-            }
-        wave_lds_sync();
+    }
 
-        // ---- contract ----
-        const char *arow = s_A[wave] + r16 * ARS + 16 * q;
-        v4f cc[NS];
+    // ---- the points' split-half rows ----
+    float m = 0.f;
 #pragma unroll
-        for (int n = 0; n < NS; ++n) cc[n] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int st = 0; st < KS; ++st) {
-            const h8 bh = *reinterpret_cast<const h8 *>(arow + 64 * st);
-            const h8 bl = *reinterpret_cast<const h8 *>(arow + 64 * st + 2 * KD);
-            h8 tH[NS], tL[NS];
-#pragma unroll
-            for (int n = 0; n < NS; ++n) {
-                tL[n] = *reinterpret_cast<const h8 *>(s_th + (((NS + n) * KS + st) * 64 + lane) * 16);
-                tH[n] = *reinterpret_cast<const h8 *>(s_th + ((n * KS + st) * 64 + lane) * 16);
-            }
-#pragma unroll
-            for (int n = 0; n < NS; ++n) cc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tL[n], bh, cc[n], 0, 0, 0);
-#pragma unroll
-            for (int n = 0; n < NS; ++n) cc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tH[n], bl, cc[n], 0, 0, 0);
-#pragma unroll
-            for (int n = 0; n < NS; ++n) cc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tH[n], bh, cc[n], 0, 0, 0);
+        for (int jj = 0; jj < 4; ++jj) {
+            acc[r][jj] *= s_rs[jj * RP + R * t + r];
+            m = __builtin_amdgcn_fmed3f(m, __builtin_fabsf(acc[r][jj]), __builtin_inff());
         }
-        const int e = __shfl(ex, 4 * r16, 64);
+    m = group_max<4>(m);
+    const int ex = 15 - __builtin_amdgcn_frexp_expf(m);
+    char *row = s_w[wave] + p * ARS;
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float x = __builtin_ldexpf(acc[r][jj], ex);
+            const _Float16 h = (_Float16)x;
+            *reinterpret_cast<_Float16 *>(row + 2 * (jj * RP + R * t + r)) = h;
+            *reinterpret_cast<_Float16 *>(row + 2 * (KD + jj * RP + R * t + r)) = (_Float16)(x - (float)h);
+        }
+        if constexpr (4 * R < RP) {                                      // four channels of padding
+            *reinterpret_cast<_Float16 *>(row + 2 * (jj * RP + 4 * R + t)) = (_Float16)0.f;
+            *reinterpret_cast<_Float16 *>(row + 2 * (KD + jj * RP + 4 * R + t)) = (_Float16)0.f;
+        }
+    }
+    wave_lds_sync();
+
+    // ---- contract ----
+    const char *arow = s_w[wave] + r16 * ARS + 16 * q;
+    v4f cc[NS];
+#pragma unroll
+    for (int n = 0; n < NS; ++n) cc[n] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < KS; ++st) {
+        const h8 bh = *reinterpret_cast<const h8 *>(arow + 64 * st);
+        const h8 bl = *reinterpret_cast<const h8 *>(arow + 64 * st + 2 * KD);
 #pragma unroll
         for (int n = 0; n < NS; ++n) {
-            const v4i ec = *reinterpret_cast<const v4i *>(s_ec + 16 * n + 4 * q);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) cc[n][i] = __builtin_ldexpf(cc[n][i], -(e + ec[i]));
+            const h8 tL = *reinterpret_cast<const h8 *>(s_th + (((NS + n) * KS + st) * 64 + lane) * 16);
+            const h8 tH = *reinterpret_cast<const h8 *>(s_th + ((n * KS + st) * 64 + lane) * 16);
+            cc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tL, bh, cc[n], 0, 0, 0);
+            cc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tH, bl, cc[n], 0, 0, 0);
+            cc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tH, bh, cc[n], 0, 0, 0);
         }
-        if constexpr (FULL) {
-            // through LDS, so that sixteen lanes write a point's row: 16 accesses a store, where lanes of sixteen different points
-            // take 64.  Every lane stores: past the cloud's end and the result's width it writes what another one writes too
+    }
+    const int e = __shfl(ex, 4 * r16, 64);
 #pragma unroll
-            for (int n = 0; n < NS; ++n) *reinterpret_cast<v4f *>(s_out[wave] + r16 * ORS + 16 * n + 4 * q) = cc[n];
-            wave_lds_sync();
+    for (int n = 0; n < NS; ++n) {
+        const v4i ec = *reinterpret_cast<const v4i *>(s_ec + 16 * n + 4 * q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cc[n][i] = __builtin_ldexpf(cc[n][i], -(e + ec[i]));
+    }
+    if (a.out_c == 1) {
+        // Point-major: through LDS, so that sixteen lanes write a point's row, 16 accesses a store where lanes of sixteen
+        // different points take 64; streaming stores, which leave the records in L2
+        float *s_out = reinterpret_cast<float *>(s_w[wave]);
+        wave_lds_sync();                                                 // the split-half rows have been read
+#pragma unroll
+        for (int n = 0; n < NS; ++n) *reinterpret_cast<v4f *>(s_out + r16 * ORS + 16 * n + 4 * q) = cc[n];
+        wave_lds_sync();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int pt = 4 * i + q, o = 64 * j + 4 * r16;
+            const int l = CSR ? __shfl(self, 4 * pt, 64) : l0 + pt;
+            const v4f d = *reinterpret_cast<const v4f *>(s_out + pt * ORS + 4 * r16);
+            if (l0 + pt < a.N) {
+                float *dst = a.out + b * a.out_b + l * a.out_l + o;
+                if (o + 3 < a.w_out) __builtin_nontemporal_store(d, reinterpret_cast<v4fu *>(dst));
+                else {
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        if (o + x < a.w_out) dst[x] = d[x];
+                }
+            }
+        }
+    } else {
+        const int at = CSR ? __shfl(self, 4 * r16, 64) : l0 + r16;
+        if (l0 + r16 >= a.N) return;
+#pragma unroll
+        for (int n = 0; n < NS; ++n) {
+            const int o = 64 * j + 16 * n + 4 * q;
+            float *dst = a.out + b * a.out_b + at * a.out_l + o * a.out_c;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                store_row(b, self, i, *reinterpret_cast<const v4fu *>(s_out[wave] + (4 * i + q) * ORS + o_full));
-        } else {
-            const int l = __shfl(self, 4 * r16, 64);
-            if (l0 + r16 < a.N)
-#pragma unroll
-                for (int n = 0; n < NS; ++n) {
-                    const int o = 64 * j + 16 * n + 4 * q;
-                    float *dst = a.out + b * a.out_b + l * a.out_l + o * a.out_c;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (o + i < a.w_out) dst[i * a.out_c] = cc[n][i];
-                }
+                if (o + i < a.w_out) dst[i * a.out_c] = cc[n][i];
         }
     }
 }
 
-hipError_t FLEX_NARROW_NAME(launch_narrow_records_, FLEX_NARROW_CSR)(const TileArgs &a, const float *rec, const float *rec4,
-                                                                     int grid, hipStream_t s)
+hipError_t FLEX_NARROW_NAME(launch_narrow_records_, FLEX_NARROW_CSR)(const TileArgs &args, const float *rec, const float *rec4,
+                                                                     int B, int n_out, hipStream_t s)
 {
     constexpr bool CSR = FLEX_NARROW_CSR != 0;
-    const bool full = a.out_c == 1 && (a.w_out - 1) % 64 >= 3;
+    TileArgs a = args;                                   // tiles of this kernel's own
+    a.tpc = (a.N + RECORD_POINTS - 1) / RECORD_POINTS;
+    const int64_t total = (int64_t)B * a.tpc, chunks = (total + 7) / 8 * 8;
+    if (chunks * n_out > 0x7fffffff) return hipErrorInvalidValue;
+    a.total = (int)total;
+    a.chunks = (int)chunks;
+    const dim3 grid((unsigned)(chunks * n_out)), block(RECORD_NT);
     switch (narrow_record_channels(a.w_in)) {
-    case 1:
-        if (full) hipLaunchKernelGGL((narrow_record_kernel<1, CSR, true>), dim3(grid), dim3(256), 0, s, a, rec, rec4);
-        else hipLaunchKernelGGL((narrow_record_kernel<1, CSR, false>), dim3(grid), dim3(256), 0, s, a, rec, rec4);
-        break;
-    case 2:
-        if (full) hipLaunchKernelGGL((narrow_record_kernel<2, CSR, true>), dim3(grid), dim3(256), 0, s, a, rec, rec4);
-        else hipLaunchKernelGGL((narrow_record_kernel<2, CSR, false>), dim3(grid), dim3(256), 0, s, a, rec, rec4);
-        break;
-    case 3:
-        if (full) hipLaunchKernelGGL((narrow_record_kernel<3, CSR, true>), dim3(grid), dim3(256), 0, s, a, rec, rec4);
-        else hipLaunchKernelGGL((narrow_record_kernel<3, CSR, false>), dim3(grid), dim3(256), 0, s, a, rec, rec4);
-        break;
-    case 4:
-        if (full) hipLaunchKernelGGL((narrow_record_kernel<4, CSR, true>), dim3(grid), dim3(256), 0, s, a, rec, rec4);
-        else hipLaunchKernelGGL((narrow_record_kernel<4, CSR, false>), dim3(grid), dim3(256), 0, s, a, rec, rec4);
-        break;
+    case 2: hipLaunchKernelGGL((narrow_record_kernel<2, CSR>), grid, block, 0, s, a, rec, rec4); break;
+    case 3: hipLaunchKernelGGL((narrow_record_kernel<3, CSR>), grid, block, 0, s, a, rec, rec4); break;
+    case 4:                                              // (the forward pass has no use for these)
+        if constexpr (CSR) { hipLaunchKernelGGL((narrow_record_kernel<4, CSR>), grid, block, 0, s, a, rec, rec4); break; }
+        [[fallthrough]];
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

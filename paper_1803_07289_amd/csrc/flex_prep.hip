@@ -484,9 +484,12 @@ __device__ void pack_points(const float *__restrict__ pos, float *__restrict__ p
 // ---- rows of at most 16 channels with their locations, as records -----------------------------------------------------
 // rec[(b*N + n)*16 + 4 t ..] = (component t of (x, y, z, 1), channels R t .. R t + 2), rec4[(b*N + n)*4 + t] = channel 4 t + 3 (R = 4);
 // channels past the row's end are zero.  A thread makes a quad: what a wave writes is contiguous.
+// nbr: the neighbour tensor that the records are gathered by, read and dropped here, so that it stands in the memory-side cache
+// (256 MB) when the gather waits for it; null where it is too large to stay there, or lists are walked.
 struct RecordArgs {
-    int N, W, bcn, bpc;
+    int N, W, bcn, bpc, K;
     float *rec4;
+    const int32_t *nbr;
 };
 static constexpr int RECORDS_PER_THREAD = 2;
 
@@ -514,6 +517,18 @@ __device__ void make_records(const float *__restrict__ pos, const float *__restr
         if (n < p.N) {
             reinterpret_cast<v4f *>(rec)[((int64_t)b * p.N + n) * 4 + t] = v4f{t < 3 ? x : 1.f, v[0], v[1], v[2]};
             if (R == 4) p.rec4[((int64_t)b * p.N + n) * 4 + t] = v[3];
+        }
+    }
+    if (p.nbr != nullptr) {
+        constexpr int PER_BLOCK = PREP_NT / 4 * RECORDS_PER_THREAD;
+        const int first = (block - b * p.bpc) * PER_BLOCK + (threadIdx.x % PER_BLOCK);
+        const int32_t *ids = p.nbr + (int64_t)b * p.K * p.N + min(first, p.N - 1);
+        for (int k = threadIdx.x / PER_BLOCK; k < p.K; k += 4 * (PREP_NT / PER_BLOCK)) {
+            int x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = ids[(int64_t)min(k + u * (PREP_NT / PER_BLOCK), p.K - 1) * p.N];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) asm volatile("" : : "v"(x[u]));
         }
     }
 }
@@ -621,11 +636,11 @@ void PrepList::pack_pos(const float *pos, float *pos4, int B, int N)
     if (PrepJob *j = next_job(*this, PREP_POINTS, (int64_t)B * bpc, pos, nullptr, pos4)) { j->points.N = N; j->points.bpc = bpc; }
 }
 
-void PrepList::records(const float *pos, const float *feat, float *rec, float *rec4, int B, int N, int W, int bcn)
+void PrepList::records(const float *pos, const float *feat, float *rec, float *rec4, int B, int N, int W, int bcn, const int32_t *nbr, int K)
 {
     constexpr int PER_BLOCK = PREP_NT / 4 * RECORDS_PER_THREAD;
     const int bpc = (N + PER_BLOCK - 1) / PER_BLOCK;
-    if (PrepJob *j = next_job(*this, PREP_RECORDS, (int64_t)B * bpc, pos, feat, rec)) j->records = RecordArgs{N, W, bcn, bpc, rec4};
+    if (PrepJob *j = next_job(*this, PREP_RECORDS, (int64_t)B * bpc, pos, feat, rec)) j->records = RecordArgs{N, W, bcn, bpc, K, rec4, nbr};
 }
 
 void PrepList::clear(void *dst, int words)

@@ -61,18 +61,24 @@ def test_packed_locations_change_no_bit(B, N, K, Din, Dout, layout):
         compare(B, N, K, Din, Dout, layout, True)
 
 
-# one to four channels a quad with every remainder, clouds around the sixteen points of a wave and the 64 of a tile, result
-# widths that fill, leave and barely enter a block of 64, K around a batch of eight
+# the feature gradient: two to four channels a quad with every remainder, clouds around the sixteen points of a wave and the 128
+# of a workgroup, result widths that fill, leave and barely enter a block of 64, K around a batch of eight
 @pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
 @pytest.mark.parametrize("B,N,K,W,other", [
-    (1, 1, 1, 1, 4), (1, 15, 3, 2, 64), (2, 16, 8, 3, 32), (1, 17, 9, 4, 65), (3, 63, 8, 5, 68), (1, 65, 16, 8, 3),
+    (1, 1, 1, 5, 4), (1, 15, 3, 6, 64), (2, 16, 8, 7, 32), (1, 17, 9, 8, 65), (3, 63, 8, 9, 68), (1, 65, 16, 10, 3),
     (1, 257, 17, 9, 64), (2, 130, 8, 11, 130), (1, 300, 8, 12, 64), (2, 97, 5, 13, 64), (1, 5000, 8, 16, 20),
 ])
-def test_records_change_no_bit(B, N, K, W, other, layout):
-    compare(B, N, K, W, other, layout, False)
+def test_records_over_lists_change_no_bit(B, N, K, W, other, layout):
     compare(B, N, K, other, W, layout, True)
 
 
 def test_records_of_a_hub_point_and_empty_lists():
     compare(1, 500, 4, 64, 13, fx.BNC, True, hub=True)
     compare(2, 90, 8, 9, 9, fx.BCN, True, hub=True)
+
+
+# the forward pass takes records from 2^17 points on
+@pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
+@pytest.mark.parametrize("B,N,K,W,other", [(1, 131072, 3, 5, 4), (2, 65537, 9, 9, 64), (1, 131073, 8, 12, 65), (3, 43701, 8, 7, 70)])
+def test_records_change_no_bit(B, N, K, W, other, layout):
+    compare(B, N, K, W, other, layout, False)
