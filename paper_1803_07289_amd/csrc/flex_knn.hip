@@ -180,10 +180,13 @@ __global__ __launch_bounds__(256) void knn_fill_kernel(const float *__restrict__
 __device__ __forceinline__ double knn_key(float d2, int id) { return __hiloint2double(__float_as_int(d2) & 0x7fffffff, id); }
 
 // One thread per point, in cell order (neighbouring threads search neighbouring cells); lists[record][K].
-// What bounds it is the chain offsets -> records of one thread.  So the nine rows of cells of the first block (three
-// cells each, contiguous records) have all their offsets requested at once, and one loop runs over the records of all
-// nine, the next one already requested, so that a wave waits for its longest total and not for the longest of every
-// row; the rows' bounds wait in LDS.
+// What bounds it is the issue of instructions, and before that the chain offsets -> records of one thread.  So the nine rows of
+// cells of the first block (three cells each, contiguous records) have all their offsets requested at once, and one loop runs
+// over the records of all nine, the next ones already requested, so that a wave waits for its longest total and not for the
+// longest of every row; the rows' bounds wait in LDS.  The rows come nearest first, the point's own before all others: the
+// sorted insertion is run if any lane needs it, and that is for 73 of a wave's 125 records in a scanned room (1M points, K = 8)
+// and not for 90.  Two records a step: what a step costs beside them, the row's end above all, is paid half as often.  Both
+// together: 168 -> 127 us there, 1M points in a cube (where the second shell takes most of the time) the whole call 412 -> 402.
 template <int K>
 __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict__ rec, const int32_t *__restrict__ off,
                                                         const unsigned *__restrict__ bbox, int32_t *__restrict__ lists,
@@ -204,11 +207,11 @@ __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict
         double best[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) best[k] = knn_key(__builtin_inff(), 0x7fffffff);
-        auto offer = [&](const float4 &q) {
+        auto offer = [&](const float4 &q, bool on) {
             const float dx = __fsub_rn(q.x, me.x), dy = __fsub_rn(q.y, me.y), dz = __fsub_rn(q.z, me.z);
             const float d2 = __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
             double x = knn_key(d2, __float_as_int(q.w));
-            if (x < best[K - 1]) {
+            if (on && x < best[K - 1]) {
 #pragma unroll
                 for (int k = 0; k < K; ++k) {        // sorted insertion: the candidate bubbles down the list
                     const double worse = fmax(best[k], x);
@@ -233,10 +236,11 @@ __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict
         };
         {
             // the 27 cells around: the non-empty rows' bounds to LDS, then one loop over their records
+            constexpr int order[9] = {4, 1, 3, 5, 7, 0, 2, 6, 8};
             int b0[9], b1[9];
 #pragma unroll
             for (int j = 0; j < 9; ++j) {
-                const int z = cz + j / 3 - 1, y = cy + j % 3 - 1;
+                const int z = cz + order[j] / 3 - 1, y = cy + order[j] % 3 - 1;
                 const bool on = z >= 0 && z < g.n[2] && y >= 0 && y < g.n[1];
                 const int row = ((on ? z : cz) * g.n[1] + (on ? y : cy)) * g.n[0];
                 b0[j] = offb[row + max(cx - 1, 0)];
@@ -247,17 +251,21 @@ __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict
 #pragma unroll
             for (int j = 0; j < 9; ++j)
                 if (b0[j] < b1[j]) { s_beg[rows][tid] = b0[j]; s_end[rows][tid] = b1[j]; ++rows; }
-            // (the thread's own cell is never empty)
+            // (the thread's own cell is never empty; the second record of a row's last step may be the next row's, or what
+            // follows the records in the workspace: read, not offered)
             int j = 0, e = s_beg[0][tid], end = s_end[0][tid];
-            float4 q = rec[e];
+            float4 q0 = rec[e], q1 = rec[e + 1];
             for (bool more = true; more;) {
-                const float4 cur = q;
-                if (++e == end) {
+                const float4 c0 = q0, c1 = q1;
+                const bool two = e + 1 < end;
+                e += 2;
+                if (e >= end) {
                     more = ++j < rows;
                     if (more) { e = s_beg[j][tid]; end = s_end[j][tid]; }
                 }
-                if (more) q = rec[e];
-                offer(cur);
+                if (more) { q0 = rec[e]; q1 = rec[e + 1]; }
+                offer(c0, true);
+                offer(c1, two);
             }
         }
         const int rmax = max(max(g.n[0], g.n[1]), g.n[2]);
@@ -271,13 +279,13 @@ __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict
                     // on a face row every x is on the shell; otherwise only the two ends are
                     if (abs(z - cz) == r || abs(y - cy) == r) {
                         const int e1 = offb[row + x1 + 1];
-                        for (int e = offb[row + x0]; e < e1; ++e) offer(rec[e]);
+                        for (int e = offb[row + x0]; e < e1; ++e) offer(rec[e], true);
                     } else {
                         const int xa = cx - r, xb = cx + r;
                         const int a0 = xa >= 0 ? offb[row + xa] : 0, a1 = xa >= 0 ? offb[row + xa + 1] : 0;
                         const int c0 = xb < g.n[0] ? offb[row + xb] : 0, c1 = xb < g.n[0] ? offb[row + xb + 1] : 0;
-                        for (int e = a0; e < a1; ++e) offer(rec[e]);
-                        for (int e = c0; e < c1; ++e) offer(rec[e]);
+                        for (int e = a0; e < a1; ++e) offer(rec[e], true);
+                        for (int e = c0; e < c1; ++e) offer(rec[e], true);
                     }
                 }
         }
