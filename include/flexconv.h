@@ -332,6 +332,16 @@ int flex_knn(const float *pos, int32_t *nbr, int B, int N, int K,
 int flex_idiss_phi(const float *pos, const int32_t *nbr, float *phi, int B, int N, int K, void *stream);
 
 /*
+ * The same with scratch memory, in which a large cloud's locations are packed first, so that a neighbour's costs one cache
+ * line and not three; the result is the same bits.  flex_idiss_phi_workspace_bytes: how much to give it (0: none, at sizes
+ * where that does not pay).  It packs in any workspace of 16 bytes a point, 256-byte aligned, and takes any other, null
+ * among them, as flex_idiss_phi does.
+ */
+size_t flex_idiss_phi_workspace_bytes(int B, int N, int K);
+int flex_idiss_phi_ws(const float *pos, const int32_t *nbr, float *phi, int B, int N, int K, void *workspace,
+                      size_t workspace_bytes, void *stream);
+
+/*
  * Inverse density importance sub-sampling, step 2: Ns points per cloud drawn with probability
  * proportional to phi in one pass over the points.  The paper asks for proportional sampling
  * in O(n) and fixes no procedure; the one used is stratified sampling on the running sum, in

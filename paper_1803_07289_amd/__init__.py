@@ -44,6 +44,8 @@ _SIGS = {
     "flex_selection_make_distinct": (_i, [_vp, _i, _i, _i, _vp, _sz, _vp]),
     "flex_knn": (_i, [_vp, _vp, _i, _i, _i, _vp, _sz, _vp]),
     "flex_idiss_phi": (_i, [_vp] * 3 + [_i] * 3 + [_vp]),
+    "flex_idiss_phi_ws": (_i, [_vp] * 3 + [_i] * 3 + [_vp, _sz, _vp]),
+    "flex_idiss_phi_workspace_bytes": (_sz, [_i] * 3),
     "flex_idiss_sample": (_i, [_vp] * 3 + [_i] * 3 + [_vp, _sz, _vp]),
     "flexpool_sub_fwd": (_i, [_vp] * 5 + [_i] * 6 + [_vp]),
     "flexpool_sub_bwd": (_i, [_vp] * 5 + [_i] * 6 + [_vp]),
@@ -436,7 +438,11 @@ def flex_idiss_phi(pos, nbr):
     if tuple(pos.shape) != (B, 3, N):
         raise ValueError("pos must be [B,3,N]")
     phi = torch.empty((B, N), dtype=torch.float32, device=pos.device)
-    _check(lib().flex_idiss_phi(_ptr(pos.contiguous()), _ptr(nbr), _ptr(phi), B, N, K, _stream()), "flex_idiss_phi")
+    need = int(lib().flex_idiss_phi_workspace_bytes(B, N, K))
+    # of this call's own: calls on several streams share no scratch memory here
+    ws = torch.empty(need, dtype=torch.uint8, device=pos.device) if need else None
+    _check(lib().flex_idiss_phi_ws(_ptr(pos.contiguous()), _ptr(nbr), _ptr(phi), B, N, K, _ptr(ws), need, _stream()),
+           "flex_idiss_phi")
     return phi
 
 

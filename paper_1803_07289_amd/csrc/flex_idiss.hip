@@ -14,14 +14,19 @@ namespace flex {
 static constexpr int IDISS_ITEMS = 8;                       // points per thread in the scans
 static constexpr int IDISS_CHUNK = 256 * IDISS_ITEMS;       // points per block
 
-__global__ __launch_bounds__(256) void idiss_phi_kernel(const float *__restrict__ pos, const int32_t *__restrict__ nbr,
-                                                        float *__restrict__ phi, int64_t BN, int N, int K)
+// What bounds it is the lines that the neighbours' locations lie in.  PACKED: they come from records (x, y, z, 0) (pos4), one
+// line each instead of three: 1M points of a room in the sensor's order, K = 8, 84 -> 45 us and 5 for the packing.
+template <bool PACKED>
+__global__ __launch_bounds__(256) void idiss_phi_kernel(const float *__restrict__ pos, const float *__restrict__ pos4,
+                                                        const int32_t *__restrict__ nbr, float *__restrict__ phi, int64_t BN,
+                                                        int N, int K)
 {
     constexpr int UN = 8;
     for (int64_t gp = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; gp < BN; gp += (int64_t)gridDim.x * blockDim.x) {
         const int64_t b = gp / N;
         const int l = (int)(gp - b * N);
         const float *p = pos + b * 3 * N;
+        const v4f *p4 = reinterpret_cast<const v4f *>(pos4) + b * N;
         const int32_t *nb = nbr + b * K * N + l;
         const float cx = p[l], cy = p[(int64_t)N + l], cz = p[2 * (int64_t)N + l];
         // the ids of eight neighbours together, then their 24 position components: on a cloud stored without locality
@@ -33,7 +38,14 @@ __global__ __launch_bounds__(256) void idiss_phi_kernel(const float *__restrict_
 #pragma unroll
             for (int u = 0; u < UN; ++u) n[u] = nb[(int64_t)min(k0 + u, K - 1) * N];
 #pragma unroll
-            for (int u = 0; u < UN; ++u) { x[u] = p[n[u]]; y[u] = p[(int64_t)N + n[u]]; z[u] = p[2 * (int64_t)N + n[u]]; }
+            for (int u = 0; u < UN; ++u) {
+                if constexpr (PACKED) {
+                    const v4f q = p4[n[u]];
+                    x[u] = q[0]; y[u] = q[1]; z[u] = q[2];
+                } else {
+                    x[u] = p[n[u]]; y[u] = p[(int64_t)N + n[u]]; z[u] = p[2 * (int64_t)N + n[u]];
+                }
+            }
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
                 const float dx = x[u] - cx, dy = y[u] - cy, dz = z[u] - cz;
@@ -289,12 +301,21 @@ size_t idiss_ws_bytes(int B, int N)
            align256(sizeof(unsigned long long) * (size_t)B * (idiss_nblk(N) + 1)) + align256(sizeof(unsigned) * (size_t)B);
 }
 
-hipError_t launch_idiss_phi(const float *pos, const int32_t *nbr, float *phi, int B, int N, int K, hipStream_t s)
+// pos4: room for the records, 16 bytes a point, or null
+hipError_t launch_idiss_phi(const float *pos, const int32_t *nbr, float *phi, float *pos4, int B, int N, int K, hipStream_t s)
 {
     const int64_t BN = (int64_t)B * N;
     int64_t blocks = (BN + 255) / 256;
     if (blocks > (1 << 20)) blocks = 1 << 20;
-    hipLaunchKernelGGL(idiss_phi_kernel, dim3((unsigned)blocks), dim3(256), 0, s, pos, nbr, phi, BN, N, K);
+    if (pos4 == nullptr) {
+        hipLaunchKernelGGL(idiss_phi_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, pos, pos4, nbr, phi, BN, N, K);
+        return hipGetLastError();
+    }
+    PrepList prep;
+    prep.pack_pos(pos, pos4, B, N);
+    const hipError_t e = prep.launch(s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(idiss_phi_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, pos, pos4, nbr, phi, BN, N, K);
     return hipGetLastError();
 }
 

@@ -127,6 +127,8 @@ def test_upsampling_and_location_gradient_errors_precede_any_launch(L):
     # flex_idiss_phi(pos, nbr, phi, B, N, K, stream); flex_idiss_sample(phi, u, sel, B, N, Ns, ws, ws_bytes, stream)
     assert L.flex_idiss_phi(one, none, one, 1, 16, 4, None) == 1
     assert L.flex_idiss_phi(one, one, one, 1, 16, 17, None) == 2
+    assert L.flex_idiss_phi_ws(one, none, one, 1, 16, 4, none, 0, None) == 1
+    assert L.flex_idiss_phi_ws(one, one, one, 1, 16, 17, none, 0, None) == 2
     assert L.flex_idiss_sample(one, one, none, 1, 16, 4, one, big, None) == 1
     assert L.flex_idiss_sample(one, one, one, 1, 16, 17, one, big, None) == 2
     assert L.flex_idiss_sample(one, one, one, 1, (1 << 25) + 1, 4, one, big, None) == 2
