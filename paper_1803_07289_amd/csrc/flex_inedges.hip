@@ -8,7 +8,7 @@
 // each bucket is sorted in LDS by one workgroup.  Global atomics per (workgroup, bucket) instead of per edge:
 // a random-address atomic per edge (twice) and the scattered 4-byte writes behind
 // it were 600 us of the 650 us that 1M points x 8 neighbours in the sensor's
-// order took; this takes 170 us, 120 in Z-order (324).  Beyond that: counting sort by target point with
+// order took; this takes 139 us, 121 in Z-order (324).  Beyond that: counting sort by target point with
 // an atomic per edge (count -> exclusive scan -> fill -> sort each list).
 #include "flex_common.hpp"
 #include <stdlib.h>
@@ -250,6 +250,10 @@ static constexpr int BUCKET_CAP = BUCKET_NT * BUCKET_PER_THREAD; // edges a buck
 static constexpr int BUCKET_TARGETS_MAX = 2048;
 static constexpr int EDGE_BUCKETS_MAX = 16384;                   // counters of the count / deal steps: 64 KB of LDS
 
+static constexpr int DEAL_PER_THREAD = 32;                       // edges a thread of the deal step keeps
+static constexpr int DEAL_BUCKETS_MAX = 3 * BUCKET_NT;           // buckets up to which it orders them in LDS (152 KB)
+static constexpr int DEAL_RUN_MIN = 16 * BUCKET_NT;              // edges a workgroup from which it does
+
 struct EdgeRuns {
     const int32_t *nbr, *sel;        // sel == nullptr: every point is a centre
     int N, Nc, K;                    // points and centres per cloud
@@ -287,8 +291,8 @@ struct EdgeWalk {
 
 // counter[key] += 1 for every lane with on, returning the value before the lane's own addition.  On a cloud stored with
 // locality most of a wave's lanes share a key, and as many atomics on one LDS word would queue up: the lanes of the
-// first two keys met are counted by a ballot, only the rest go one by one.
-__device__ __forceinline__ int lds_count(int *counter, int key, bool on)
+// first two keys met are counted by a ballot, only the rest go one by one (alone: how often this lane did).
+__device__ __forceinline__ int lds_count(int *counter, int key, bool on, int &alone)
 {
     const int lane = threadIdx.x & 63;
     const uint64_t below = (1ull << lane) - 1ull;
@@ -306,7 +310,7 @@ __device__ __forceinline__ int lds_count(int *counter, int key, bool on)
         base = __builtin_amdgcn_readlane(base, first);
         if (todo && key == lead) { old = base + __popcll(same & below); todo = false; }
     }
-    if (todo) old = atomicAdd(&counter[key], 1);
+    if (todo) { old = atomicAdd(&counter[key], 1); ++alone; }
     return old;
 }
 
@@ -319,6 +323,7 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_count_kernel(const EdgeRuns p,
     const int64_t first = (int64_t)blockIdx.x * p.run;
     const int n = (int)min((int64_t)p.run, p.E - first);
     constexpr int UN = 8;
+    int alone = 0;
     EdgeWalk w(p, min(first + threadIdx.x, (int64_t)p.E - 1));
     for (int e0 = 0; e0 < n; e0 += BUCKET_NT * UN) {
         int t[UN];
@@ -329,7 +334,7 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_count_kernel(const EdgeRuns p,
             if (e0 + BUCKET_NT * (u + 1) + (int)threadIdx.x < n) w.next(p);
         }
 #pragma unroll
-        for (int u = 0; u < UN; ++u) lds_count(s_cnt, t[u] >> p.shift, t[u] >= 0);
+        for (int u = 0; u < UN; ++u) lds_count(s_cnt, t[u] >> p.shift, t[u] >= 0, alone);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < buckets; i += BUCKET_NT)
@@ -367,36 +372,113 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_scan_kernel(const int32_t *__r
     if (threadIdx.x == BUCKET_NT - 1) off[buckets] = run;
 }
 
+// What bounds it is the stores: on a cloud stored without locality the edges of a wave go to as many buckets, 64 lines a store
+// where a line would hold 32 edges of one bucket.  STAGED: where that is so (most lanes met neither of the first two
+// keys of their wave), the run is put in bucket order in LDS first, targets, then sources through the same array, and leaves in
+// that order.  1M points of a room in the sensor's order, K = 8: this kernel 81 -> 49 us, the build 170 -> 139; 2.9M in a cube 715 -> 393.  On clouds with
+// locality the waves' own stores are whole lines already (Z-order, 1M points: the build 121 us, 124 with every run ordered in LDS).
+// Up to DEAL_BUCKETS_MAX buckets, what LDS holds beside a run, and from DEAL_RUN_MIN edges a run on: 300k and 100k points in the sensor's
+// order, K = 8, runs of 10 and 4 edges a thread: the build 72.5 and 42 us, by LDS 74 and 48; 600k, 19 edges, 115 and 102.
+template <bool STAGED>
 __global__ __launch_bounds__(BUCKET_NT) void edge_deal_kernel(const EdgeRuns p, int32_t *__restrict__ bucket_cur,
                                                               int32_t *__restrict__ st_src, uint16_t *__restrict__ st_tgt,
                                                               int buckets)
 {
+    constexpr int MAXE = DEAL_PER_THREAD;        // p.run <= MAXE * BUCKET_NT
+    constexpr int BPT = DEAL_BUCKETS_MAX / BUCKET_NT;
+    __shared__ int s_edge[STAGED ? MAXE * BUCKET_NT : 1], s_move[STAGED ? DEAL_BUCKETS_MAX : 1], s_wave[BUCKET_NT / 64 + 1], s_alone;
     extern __shared__ int s_cnt[];
-    for (int i = threadIdx.x; i < buckets; i += BUCKET_NT) s_cnt[i] = 0;
+    const int tid = threadIdx.x;
+    for (int i = tid; i < buckets; i += BUCKET_NT) s_cnt[i] = 0;
+    if (tid == 0) s_alone = 0;
     __syncthreads();
     const int64_t first = (int64_t)blockIdx.x * p.run;
     const int n = (int)min((int64_t)p.run, p.E - first);
-    constexpr int MAXE = 32;                     // p.run <= MAXE * BUCKET_NT
-    int t[MAXE], rank[MAXE];
+    int t[MAXE], rank[MAXE], alone = 0;
     {
-        EdgeWalk w(p, min(first + threadIdx.x, (int64_t)p.E - 1));
+        EdgeWalk w(p, min(first + tid, (int64_t)p.E - 1));
 #pragma unroll
         for (int u = 0; u < MAXE; ++u) {
             t[u] = -1;
             if (BUCKET_NT * u < n) {             // uniform
-                if (BUCKET_NT * u + (int)threadIdx.x < n) t[u] = w.target(p);
-                if (BUCKET_NT * (u + 1) + (int)threadIdx.x < n) w.next(p);
+                if (BUCKET_NT * u + tid < n) t[u] = w.target(p);
+                if (BUCKET_NT * (u + 1) + tid < n) w.next(p);
             }
         }
     }
 #pragma unroll
     for (int u = 0; u < MAXE; ++u)
-        if (BUCKET_NT * u < n) rank[u] = lds_count(s_cnt, t[u] >> p.shift, t[u] >= 0);
+        if (BUCKET_NT * u < n) rank[u] = lds_count(s_cnt, t[u] >> p.shift, t[u] >= 0, alone);
+    if constexpr (STAGED) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) alone += __shfl_xor(alone, d, 64);
+        if ((tid & 63) == 0) atomicAdd(&s_alone, alone);
+    }
     __syncthreads();
-    for (int i = threadIdx.x; i < buckets; i += BUCKET_NT)
+    if (STAGED && 2 * s_alone > n) {             // (the same for the whole workgroup)
+        // counts -> the buckets' starts in the run; s_move: from there to the reserved stretch
+        const int lane = tid & 63, wave = tid >> 6;
+        int c[BPT], sum = 0;
+#pragma unroll
+        for (int i = 0; i < BPT; ++i) {
+            c[i] = BPT * tid + i < buckets ? s_cnt[BPT * tid + i] : 0;
+            sum += c[i];
+        }
+        int x = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(x, d, 64);
+            if (lane >= d) x += y;
+        }
+        if (lane == 63) s_wave[wave] = x;
+        __syncthreads();
+        int at = x - sum;
+        for (int w = 0; w < wave; ++w) at += s_wave[w];
+#pragma unroll
+        for (int i = 0; i < BPT; ++i)
+            if (c[i]) {
+                const int g = BPT * tid + i;
+                s_cnt[g] = at;
+                s_move[g] = atomicAdd(&bucket_cur[g], c[i]) - at;
+                at += c[i];
+            }
+        if (tid == BUCKET_NT - 1) s_wave[BUCKET_NT / 64] = at;
+        __syncthreads();
+        const int all = s_wave[BUCKET_NT / 64];  // the run's edges
+#pragma unroll
+        for (int u = 0; u < MAXE; ++u)
+            if (BUCKET_NT * u < n) {
+                rank[u] = t[u] >= 0 ? rank[u] + s_cnt[t[u] >> p.shift] : -1;
+                if (t[u] >= 0) s_edge[rank[u]] = t[u];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < MAXE; ++u) {
+            const int i = BUCKET_NT * u + tid;
+            if (i < all) {
+                const int target = s_edge[i];
+                t[u] = i + s_move[target >> p.shift];
+                st_tgt[t[u]] = (uint16_t)(target & ((1 << p.shift) - 1));
+            }
+        }
+        __syncthreads();
+        EdgeWalk w(p, min(first + tid, (int64_t)p.E - 1));
+#pragma unroll
+        for (int u = 0; u < MAXE; ++u)
+            if (BUCKET_NT * u < n) {
+                if (rank[u] >= 0) s_edge[rank[u]] = w.j;
+                if (BUCKET_NT * (u + 1) + tid < n) w.next(p);
+            }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < MAXE; ++u)
+            if (BUCKET_NT * u + tid < all) st_src[t[u]] = s_edge[BUCKET_NT * u + tid];
+        return;
+    }
+    for (int i = tid; i < buckets; i += BUCKET_NT)
         if (const int c = s_cnt[i]) s_cnt[i] = atomicAdd(&bucket_cur[i], c);
     __syncthreads();
-    EdgeWalk w(p, min(first + threadIdx.x, (int64_t)p.E - 1));
+    EdgeWalk w(p, min(first + tid, (int64_t)p.E - 1));
 #pragma unroll
     for (int u = 0; u < MAXE; ++u)
         if (BUCKET_NT * u < n) {
@@ -405,7 +487,7 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_deal_kernel(const EdgeRuns p, 
                 st_src[at] = w.j;
                 st_tgt[at] = (uint16_t)(t[u] & ((1 << p.shift) - 1));
             }
-            if (BUCKET_NT * (u + 1) + (int)threadIdx.x < n) w.next(p);
+            if (BUCKET_NT * (u + 1) + tid < n) w.next(p);
         }
 }
 
@@ -541,7 +623,7 @@ hipError_t launch_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int 
         uint16_t *st_tgt = (uint16_t *)((char *)st_src + align256(sizeof(int32_t) * (size_t)BN * K));
         // runs of edges: a workgroup per CU while they are short, at most what the deal step's registers hold
         int64_t run = cdiv64(cdiv64(E, device_cu_count()), BUCKET_NT) * BUCKET_NT;
-        if (run > 32 * BUCKET_NT) run = 32 * BUCKET_NT;
+        if (run > DEAL_PER_THREAD * BUCKET_NT) run = DEAL_PER_THREAD * BUCKET_NT;
         const EdgeRuns p{nbr, sel, N, sel ? Ns : N, K, (int)E, (int)run, bucket_shift(K)};
         const dim3 g((unsigned)cdiv64(E, run)), blk(BUCKET_NT);
         const size_t lds = sizeof(int) * (size_t)buckets;
@@ -549,7 +631,8 @@ hipError_t launch_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int 
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(edge_count_kernel, g, blk, lds, s, p, cnt, buckets);
         hipLaunchKernelGGL(edge_scan_kernel, dim3(1), blk, 0, s, cnt, off, cur, buckets);
-        hipLaunchKernelGGL(edge_deal_kernel, g, blk, lds, s, p, cur, st_src, st_tgt, buckets);
+        if (buckets <= DEAL_BUCKETS_MAX && run >= DEAL_RUN_MIN) hipLaunchKernelGGL(edge_deal_kernel<true>, g, blk, lds, s, p, cur, st_src, st_tgt, buckets);
+        else hipLaunchKernelGGL(edge_deal_kernel<false>, g, blk, lds, s, p, cur, st_src, st_tgt, buckets);
         hipLaunchKernelGGL(edge_sort_kernel, dim3((unsigned)buckets), blk, 0, s, off, st_src, st_tgt, in_off, in_src, BN,
                            (int)E, p.shift);
         return hipGetLastError();

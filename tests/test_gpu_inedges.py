@@ -56,3 +56,15 @@ def test_kept_centres():
     nbr = rng.integers(0, 5000, size=(2, 8, 5000)).astype(np.int32)
     sel = np.sort(np.stack([rng.choice(5000, 1250, replace=False) for _ in range(2)])).astype(np.int32)
     check(nbr, sel)
+
+
+# full runs of the deal step, and both sides of the number of buckets up to which it orders a run in LDS (3072 of 1024 points)
+@pytest.mark.parametrize("N", [1_100_001, 3_145_728, 3_145_729])
+def test_random_tensors_of_many_buckets(N):
+    say(f"in-edges N={N} K=8")
+    g = torch.Generator("cuda").manual_seed(N)
+    nbr = torch.randint(0, N, (1, 8, N), device="cuda", dtype=torch.int32, generator=g)
+    off, src = fx.flex_inedges_build(nbr)
+    tgt, at = torch.sort(nbr[0].t().reshape(-1), stable=True)
+    assert torch.equal(src, (at // 8).int())
+    assert torch.equal(off, torch.searchsorted(tgt, torch.arange(N + 1, device="cuda", dtype=torch.int32)).int())
