@@ -600,7 +600,7 @@ struct LeanProducer {
     // four points, ROW16: e = 4 * point + slot, so that an entry stands in its point's lane group, else e = 4 * slot + point
     int e_g, e_k;                // point and slot (within half 0) of this lane's entry
     unsigned e_col;              // byte offset of the position component to read: x, y, z (lane 3 reads z, value unused)
-    float e_mul, e_fix;          // dp component = (pn - pc)*e_mul + e_fix   (component lane 3: the constant 1)
+    bool e_one;                  // component lane 3: the constant 1, wherever the points lie
     float *s_dp = nullptr;       // this wave's LDS array of 32 entries x (dx, dy, dz, w), entry = 4 * slot + point
     int dp_rd = 0;               // float offset of this lane's entry of slot 0 in it
     __device__ __forceinline__ void set_dp_stage(float *p) { s_dp = p; dp_rd = 4 * (grp % G::PW); }
@@ -620,8 +620,7 @@ struct LeanProducer {
         e_k = ROW16 ? (lane >> 2) & 3 : lane >> 4;
         const int c = lane & 3;
         e_col = (c < 3 ? c : 2) * pos_.col;
-        e_mul = c < 3 ? 1.f : 0.f;
-        e_fix = c < 3 ? 0.f : 1.f;
+        e_one = c == 3;
         sched = sc; tiles_per_cloud = tiles_per_cloud_;
         count = (sc.first < sc.end) ? (sc.end - sc.first + sc.step - 1) / sc.step : 0;
     }
@@ -753,8 +752,8 @@ struct LeanProducer {
         for (int m = 0; m < total; ++m) {
             // position differences of batch m, entry layout -> this lane's component per slot
             int dpe[2];
-            dpe[0] = __float_as_int(fmaf(pn[0] - pc, e_mul, e_fix));
-            dpe[1] = __float_as_int(fmaf(pn[1] - pc, e_mul, e_fix));
+            dpe[0] = __float_as_int(e_one ? 1.f : pn[0] - pc);
+            dpe[1] = __float_as_int(e_one ? 1.f : pn[1] - pc);
             if constexpr (TAIL) {                    // slots past K weigh nothing
                 if (k0_cur + e_k >= K) dpe[0] = 0;
                 if (k0_cur + e_k + 4 >= K) dpe[1] = 0;
@@ -902,7 +901,7 @@ struct LeanCsrProducer {
     int perm_id, perm_dp;
     int e_g, e_k;
     unsigned e_col;
-    float e_mul, e_fix;
+    bool e_one;
     float *s_dp = nullptr;       // this wave's LDS array of 32 entries x (dx, dy, dz, w), entry = 4 * slot + point
     int dp_rd = 0;               // float offset of this lane's entry of slot 0 in it
     __device__ __forceinline__ void set_dp_stage(float *p) { s_dp = p; dp_rd = 4 * (grp % G::PW); }
@@ -923,8 +922,7 @@ struct LeanCsrProducer {
         e_k = ROW16 ? (lane >> 2) & 3 : lane >> 4;
         const int c = lane & 3;
         e_col = (c < 3 ? c : 2) * pos_.col;
-        e_mul = c < 3 ? 1.f : 0.f;
-        e_fix = c < 3 ? 0.f : 1.f;
+        e_one = c == 3;
         sched = sc; tiles_per_cloud = tiles_per_cloud_;
         count = (sc.first < sc.end) ? (sc.end - sc.first + sc.step - 1) / sc.step : 0;
     }
@@ -1066,8 +1064,8 @@ struct LeanCsrProducer {
             dpe[0] = d.valid0 ? __float_as_int(1.f) : 0;
             dpe[1] = d.valid1 ? __float_as_int(1.f) : 0;
         } else {
-            dpe[0] = d.valid0 ? __float_as_int(fmaf(pc - pn[0], e_mul, e_fix)) : 0;
-            dpe[1] = d.valid1 ? __float_as_int(fmaf(pc - pn[1], e_mul, e_fix)) : 0;
+            dpe[0] = d.valid0 ? __float_as_int(e_one ? 1.f : pc - pn[0]) : 0;
+            dpe[1] = d.valid1 ? __float_as_int(e_one ? 1.f : pc - pn[1]) : 0;
         }
     }
 

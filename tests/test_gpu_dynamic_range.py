@@ -127,3 +127,20 @@ def test_a_column_far_below_its_rows(Din, Dout, small):
     grad = rel_err_per_channel(gf, rgf, 1)
     say(f"  per-channel rel err: fwd {fwd:.2e} grad_feat {grad:.2e}")
     assert max(fwd, grad) <= TOL
+
+
+# the fourth component of a slot's weight is 1 wherever the points lie: the bias gradient does not see the locations.  K that
+# fills its batches of eight and that does not; alone (stand-alone kernels) and with the feature gradient (one pass at 64 -> 64)
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("K", [8, 9])
+@pytest.mark.parametrize("Din,Dout", [(64, 64), (64, 32), (64, 9), (32, 32), (128, 128)])
+def test_bias_gradient_of_a_cloud_with_a_location_that_is_not_finite(Din, Dout, K, bad):
+    say(f"location not finite: {Din}->{Dout} K={K} {bad}")
+    pos, nbr, feat, theta, bias, g = random_problem(7 + Din + K, 1, 500, K, Din, Dout)
+    want = oracle.flexconv_bwd(feat, pos, nbr, theta, bias, g)[2]
+    pos[0, 2, nbr[0, 0, 5]] = bad                     # a listed point, and a centre
+    a = (to_layout(feat, fx.BNC), dev(pos), dev(nbr), dev(theta), dev(bias), to_layout(g, fx.BNC))
+    for need_feat in (False, True):
+        gb = fx.flexconv_bwd(*a, layout=fx.BNC, need_feat=need_feat)[2].cpu().numpy()
+        assert np.isfinite(gb).all()
+        assert rel_err(gb, want) <= TOL
