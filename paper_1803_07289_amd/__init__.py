@@ -23,7 +23,6 @@ OP_KNN = 8
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libflexconv.so")
 _lib = None
-_workspaces = {}
 
 _vp, _i, _sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t
 _SIGS = {
@@ -107,11 +106,17 @@ def _dev(t, dtype, name):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# the current stream's handle without a Stream object around it, which costs a call as much as its scratch tensor does
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dims(feat, nbr, layout):
@@ -136,24 +141,20 @@ def _best_bytes(op, B, N, K, Din, Dout, layout):
 
 
 def _workspace(device, nbytes):
-    """A cached, grow-only scratch tensor per device (256-byte aligned by the allocator)."""
-    key = (device.type, device.index)
-    ws = _workspaces.get(key)
-    if ws is None or ws.numel() < nbytes:
-        _workspaces[key] = None
-        ws = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
-        _workspaces[key] = ws
-    return ws
+    """Scratch memory of one call's own (256-byte aligned by the allocator).  Nothing is kept here between calls: calls on
+    several streams or threads, and graphs that hold the address, share no scratch; the caching allocator hands a block on in
+    the order of its stream."""
+    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
 
 
 def _ws_arg(workspace, device, need):
-    """(tensor, byte count handed to the library): a caller's workspace with its own size, else the cached one
+    """(tensor, byte count handed to the library): a caller's workspace with its own size, else one of the call's own
     with exactly the size the library asked for, so that the library's own size check sees `need`."""
     if workspace is not None:
         if not workspace.is_cuda or workspace.dtype != torch.uint8 or not workspace.is_contiguous():
             raise TypeError("workspace must be a contiguous CUDA uint8 tensor")
         return workspace, workspace.numel()
-    return _workspace(device, need), max(int(need), 256)
+    return _workspace(device, need), max(need, 256)
 
 
 def kernel_route(op, B, N, K, Din, Dout, layout=BCN):
@@ -439,8 +440,7 @@ def flex_idiss_phi(pos, nbr):
         raise ValueError("pos must be [B,3,N]")
     phi = torch.empty((B, N), dtype=torch.float32, device=pos.device)
     need = int(lib().flex_idiss_phi_workspace_bytes(B, N, K))
-    # of this call's own: calls on several streams share no scratch memory here
-    ws = torch.empty(need, dtype=torch.uint8, device=pos.device) if need else None
+    ws = _workspace(pos.device, need) if need else None
     _check(lib().flex_idiss_phi_ws(_ptr(pos.contiguous()), _ptr(nbr), _ptr(phi), B, N, K, _ptr(ws), need, _stream()),
            "flex_idiss_phi")
     return phi

@@ -351,3 +351,14 @@ def test_in_edge_lists_past_the_buckets(L):
     small, none = (_query(env, [("flexconv_workspace_bytes", [3, 1, 100_000, 8, 1, 1, 0])])[0]
                    for env in ({}, {"FLEX_EDGE_BUCKETS": "0"}))
     assert small >= 6 * 800_000 and none < 5 * 100_000
+
+
+def test_the_bindings_scratch_is_each_calls_own():
+    # two calls under way at once (two streams, two threads) never share scratch; nothing is kept when they are done
+    import torch
+    import paper_1803_07289_amd as fx
+    a = fx._ws_arg(None, torch.device("cpu"), 4096)
+    b = fx._ws_arg(None, torch.device("cpu"), 4096)
+    assert a[1] == b[1] == 4096 and a[0].numel() == 4096
+    assert a[0].data_ptr() != b[0].data_ptr()
+    assert fx._ws_arg(None, torch.device("cpu"), 0)[1] == 256

@@ -33,7 +33,7 @@ def test_layer_step_replays_from_a_graph(cfg_i, n, widths):
         pg = fx.flexpool_bwd(gpool, pa, layout=L, in_edges=edges)
         return out, gf, gt, gb, po, pa, pg
 
-    eager = [t.clone() for t in step()]            # also sizes the cached workspaces before capture
+    eager = [t.clone() for t in step()]
     torch.cuda.synchronize()
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())

@@ -68,3 +68,30 @@ def test_layouts_agree():
         res[layout] = (from_layout(out, layout), from_layout(gf, layout), gt.cpu().numpy(), gb.cpu().numpy(), gp.cpu().numpy())
     for x, y in zip(res[fx.BNC], res[fx.BCN]):
         assert rel_err(x, y) <= 1e-5
+
+
+def test_calls_on_two_streams_without_workspaces_of_their_own():
+    # forward and backward of two layers, one per stream, queued in turn with nothing between them that waits
+    sets = []
+    for i, (N, Din, Dout) in enumerate([(60000, 64, 64), (50000, 64, 9)]):
+        pos, nbr, feat, theta, bias, g = random_problem(70 + i, 1, N, 8, Din, Dout)
+        a = (to_layout(feat, fx.BNC), dev(pos), dev(nbr), dev(theta), dev(bias))
+        sets.append((a, to_layout(g, fx.BNC), fx.flex_inedges_build(a[2])))
+
+    def step(x):
+        a, g, edges = x
+        return (fx.flexconv_fwd(*a, layout=fx.BNC),) + fx.flexconv_bwd(*a, g, layout=fx.BNC, in_edges=edges)
+
+    want = [step(x) for x in sets]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in sets]
+    got = [[], []]
+    for _ in range(20):
+        for x, s, r in zip(sets, streams, got):
+            with torch.cuda.stream(s):
+                r.append(step(x))
+    torch.cuda.synchronize()
+    for w, r in zip(want, got):
+        for one in r:
+            for x, y in zip(w, one):
+                assert torch.equal(x, y)
