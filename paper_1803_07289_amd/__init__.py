@@ -135,11 +135,6 @@ def workspace_bytes(op, B, N, K, Din, Dout, layout=BCN):
     return int(lib().flexconv_workspace_bytes(op, B, N, K, Din, Dout, _layout(layout)))
 
 
-def _best_bytes(op, B, N, K, Din, Dout, layout):
-    """What the binding's own workspace has room for: the size with which the call runs fastest."""
-    return int(lib().flexconv_workspace_bytes_best(op, B, N, K, Din, Dout, layout))
-
-
 def _workspace(device, nbytes):
     """Scratch memory of one call's own (256-byte aligned by the allocator).  Nothing is kept here between calls: calls on
     several streams or threads, and graphs that hold the address, share no scratch; the caching allocator hands a block on in
@@ -155,6 +150,17 @@ def _ws_arg(workspace, device, need):
             raise TypeError("workspace must be a contiguous CUDA uint8 tensor")
         return workspace, workspace.numel()
     return _workspace(device, need), max(need, 256)
+
+
+def _conv_ws_arg(workspace, device, op, *sizes):
+    """_ws_arg with the size with which the convolution runs fastest or, where the device has no room for that, with the
+    smallest one that it runs with."""
+    if workspace is not None:
+        return _ws_arg(workspace, device, 0)
+    try:
+        return _ws_arg(None, device, lib().flexconv_workspace_bytes_best(op, *sizes))
+    except torch.OutOfMemoryError:
+        return _ws_arg(None, device, lib().flexconv_workspace_bytes(op, *sizes))
 
 
 def kernel_route(op, B, N, K, Din, Dout, layout=BCN):
@@ -178,8 +184,7 @@ def flexconv_fwd(feat, pos, nbr, theta, bias, layout=BCN, out=None, workspace=No
         out = torch.empty(shape, dtype=torch.float32, device=feat.device)
     elif tuple(_dev(out, torch.float32, "out").shape) != shape:
         raise ValueError("out has the wrong shape")
-    need = _best_bytes(OP_CONV_FWD, B, N, K, Din, Dout, layout)
-    ws, ws_bytes = _ws_arg(workspace, feat.device, need)
+    ws, ws_bytes = _conv_ws_arg(workspace, feat.device, OP_CONV_FWD, B, N, K, Din, Dout, layout)
     _check(lib().flexconv_fwd(_ptr(feat), _ptr(pos), _ptr(nbr), _ptr(theta), _ptr(bias), _ptr(out),
                               B, N, K, Din, Dout, layout, _ptr(ws), ws_bytes, _stream()), "flexconv_fwd")
     return out
@@ -245,8 +250,7 @@ def flexconv_bwd(feat, pos, nbr, theta, bias, grad_out, layout=BCN, in_edges=Non
         if off.numel() != B * N + 1 or src.numel() != B * K * N:
             raise ValueError("in_edges do not match nbr")
     op = OP_CONV_BWD if in_edges is not None else OP_CONV_BWD_BUILD
-    need = _best_bytes(op, B, N, K, Din, Dout, layout)
-    ws, ws_bytes = _ws_arg(workspace, feat.device, need)
+    ws, ws_bytes = _conv_ws_arg(workspace, feat.device, op, B, N, K, Din, Dout, layout)
     _check(lib().flexconv_bwd(_ptr(feat), _ptr(pos), _ptr(nbr), _ptr(theta), _ptr(bias), _ptr(grad_out),
                               _ptr(gf), _ptr(gt), _ptr(gb), _ptr(off), _ptr(src),
                               B, N, K, Din, Dout, layout, _ptr(ws), ws_bytes, _stream()), "flexconv_bwd")
@@ -439,8 +443,11 @@ def flex_idiss_phi(pos, nbr):
     if tuple(pos.shape) != (B, 3, N):
         raise ValueError("pos must be [B,3,N]")
     phi = torch.empty((B, N), dtype=torch.float32, device=pos.device)
-    need = int(lib().flex_idiss_phi_workspace_bytes(B, N, K))
-    ws = _workspace(pos.device, need) if need else None
+    need = lib().flex_idiss_phi_workspace_bytes(B, N, K)
+    try:
+        ws = _workspace(pos.device, need) if need else None
+    except torch.OutOfMemoryError:                   # it runs without as well
+        ws, need = None, 0
     _check(lib().flex_idiss_phi_ws(_ptr(pos.contiguous()), _ptr(nbr), _ptr(phi), B, N, K, _ptr(ws), need, _stream()),
            "flex_idiss_phi")
     return phi

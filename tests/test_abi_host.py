@@ -362,3 +362,27 @@ def test_the_bindings_scratch_is_each_calls_own():
     assert a[1] == b[1] == 4096 and a[0].numel() == 4096
     assert a[0].data_ptr() != b[0].data_ptr()
     assert fx._ws_arg(None, torch.device("cpu"), 0)[1] == 256
+
+
+@pytest.mark.parametrize("Din,Dout", [(64, 64), (9, 64), (64, 13)])
+def test_a_device_without_room_for_records_takes_the_call_in_the_smallest_workspace(L, monkeypatch, Din, Dout):
+    import torch
+    import paper_1803_07289_amd as fx
+    whole, asked = fx._workspace, []
+
+    def full(device, nbytes):                        # a device with room for the smallest workspace and not a byte more
+        asked.append(nbytes)
+        if nbytes > least:
+            raise torch.OutOfMemoryError("full")
+        return whole(device, nbytes)
+
+    monkeypatch.setattr(fx, "_workspace", full)
+    best_is_more = False
+    for op in (fx.OP_CONV_FWD, fx.OP_CONV_BWD):
+        sizes = (op, 1, 1 << 20, 8, Din, Dout, fx.BNC)
+        least, best = fx.workspace_bytes(*sizes), L.flexconv_workspace_bytes_best(*sizes)
+        best_is_more |= best > least
+        asked.clear()
+        ws, have = fx._conv_ws_arg(None, torch.device("cpu"), *sizes)
+        assert asked == ([best, least] if best > least else [best]) and have == ws.numel() == least
+    assert best_is_more
