@@ -469,10 +469,14 @@ struct Packed {
 // 400k: 50 and 52), and a call of few points is its launches (9 -> 64, K = 8, 20k, 100k, 1M points: 18.8, 20.4, 136 and 19.7,
 // 20.8, 98; K = 16, channel-major, 300k 67 and 47; 6 -> 64, 200k points in no order, 45 and 29).  Over lists, forward and backward:
 // 64 -> 13, 20k points, 61 and 57 us; 64 -> 9, 200k, 128 and 117.
-static bool use_records(int64_t points, int w_in, int csr) { return w_in >= 5 && (csr || (w_in <= 12 && points >= 1 << 17)); }
+static bool use_records(int64_t B, int64_t N, int w_in, int csr)
+{
+    if (B * ((N + 15) / 16) > NARROW_RECORD_WAVES_MAX) return false;
+    return w_in >= 5 && (csr || (w_in <= 12 && B * N >= 1 << 17));
+}
 static Packed plan_packed(int64_t B, int64_t N, int route, int w_in, int csr, size_t total)
 {
-    const int64_t record = use_records(B * N, w_in, csr) ? 64 + (narrow_record_channels(w_in) == 4 ? 16 : 0) : 0;
+    const int64_t record = use_records(B, N, w_in, csr) ? 64 + (narrow_record_channels(w_in) == 4 ? 16 : 0) : 0;
     const int64_t per_point = route == FLEX_ROUTE_LEAN ? 16 : route == FLEX_ROUTE_NARROW ? record : 0;
     if (per_point == 0 || N * 64 > (1ll << 32) - 128) return Packed{0, total};       // 32-bit offsets, and one past the end
     const size_t at = align256(total);

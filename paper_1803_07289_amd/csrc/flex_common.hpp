@@ -113,6 +113,8 @@ inline PosRef pos_packed(const float *pos4, int N) { return PosRef{pos4, 4u, 4, 
 
 // channels of a row of w of at most 16 in each quad of its record
 constexpr int narrow_record_channels(int w) { return (w + 3) / 4; }
+// sixteens of points that a call from such records has at most (32-bit wave numbers)
+static constexpr int64_t NARROW_RECORD_WAVES_MAX = 1 << 27;
 
 // Tiled matrix-core path.  `rows` is point-major [B*N, DI].  Returns
 // hipErrorNotSupported when (DI,DO) has no instantiation.

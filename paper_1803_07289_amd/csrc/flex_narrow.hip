@@ -198,8 +198,9 @@ void narrow_conv_kernel(const TileArgs a)
 // array.  Four lanes are a point; each loads a quad, so a neighbour is ONE access of the texture path (two with R = 4)
 // where a lane's own loads of its row and location are six.  What a lane holds is just what the 4 x 4 x 1 matrix op
 // takes: lane t's location difference as the first operand (component t), a channel as the second, so the four lanes'
-// sums need R ops a neighbour and no exchange at all.  Sixteen points per wave, whose result leaves by whole rows.  The sums run in the
-// order of the kernel above, and the result is the same bits.
+// sums need R ops a neighbour and no exchange at all.  Sixteen points of a cloud per wave, whose result leaves by whole rows; a
+// workgroup's waves may serve several clouds (2048 clouds of 64 points, 9 -> 64, K = 8, the call: 29.3 us with tiles of 128 points
+// of one cloud and the preparation likewise, 20.3 here).  The sums run in the order of the kernel above, and the result is the same bits.
 //
 // A wave serves its sixteen points and ends, and workgroups are dispatched in order, three of eight waves per CU.  What bounds it
 // is the latency of what is not in a cache, ids above all, beside the result's stores.  A wave's loads and stores retire in
@@ -213,27 +214,30 @@ __device__ __forceinline__ unsigned quad_lane(unsigned x, int slot)          // 
     return slot == 0 ? quad_bcast<0x00>(x) : slot == 1 ? quad_bcast<0x55>(x) : slot == 2 ? quad_bcast<0xAA>(x) : quad_bcast<0xFF>(x);
 }
 
-static constexpr int RECORD_NT = 512, RECORD_POINTS = RECORD_NT / 4;         // threads, points per workgroup
+static constexpr int RECORD_NT = 512, RECORD_WAVES = RECORD_NT / 64;         // threads, waves per workgroup
 
 template <int R, bool CSR>
 __global__ __launch_bounds__(RECORD_NT) __attribute__((amdgpu_waves_per_eu(6, 6)))
 void narrow_record_kernel(const TileArgs a, const float *__restrict__ rec, const float *__restrict__ rec4)
 {
-    constexpr int RP = R <= 2 ? 8 : 16, KD = 4 * RP, KS = KD / 32, ARS = 4 * KD + 32, NS = 4, U = 8, NW = RECORD_NT / 64;
+    constexpr int RP = R <= 2 ? 8 : 16, KD = 4 * RP, KS = KD / 32, ARS = 4 * KD + 32, NS = 4, U = 8;
     constexpr int ORS = 64 + 4;                                          // floats of a result row in LDS
     constexpr int WB = 16 * (ARS > 4 * ORS ? ARS : 4 * ORS);             // a wave's LDS: its split-half rows, then its result
     constexpr int TH = 2 * NS * KS * 1024;
     __shared__ __attribute__((aligned(16))) char s_th[TH];               // the parameters' fragments: [hi, lo][slice][step][lane]
-    __shared__ __attribute__((aligned(16))) char s_w[NW][WB];
+    __shared__ __attribute__((aligned(16))) char s_w[RECORD_WAVES][WB];
     __shared__ __attribute__((aligned(16))) int s_ec[64];
     __shared__ __attribute__((aligned(16))) float s_rs[KD];
 
-    // workgroup: output block, XCD's share of the tiles, place in it
+    // workgroup: output block, XCD's share of the workgroups, place in it; wave: cloud and first point (past the last wave's: past
+    // the cloud, whose last point it gathers and does not store)
     const int j = blockIdx.x / a.chunks, w = blockIdx.x - j * a.chunks;
-    const int tile = (w & 7) * (a.chunks >> 3) + (w >> 3);
-    if (tile >= a.total) return;
-    const int b = tile / a.tpc, l0 = (tile - b * a.tpc) * RECORD_POINTS + 16 * (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = lane >> 2, t = lane & 3, q = lane >> 4, r16 = lane & 15;
+    const int wg = (w & 7) * (a.chunks >> 3) + (w >> 3);
+    if (wg * RECORD_WAVES >= a.total) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), at_wave = wg * RECORD_WAVES + wave;
+    const int b = __builtin_amdgcn_readfirstlane(min(at_wave, a.total - 1) / a.tpc);
+    const int l0 = at_wave < a.total ? 16 * (at_wave - b * a.tpc) : a.N;
+    const int lane = threadIdx.x & 63, p = lane >> 2, t = lane & 3, q = lane >> 4, r16 = lane & 15;
     const char *blk = a.theta + (int64_t)j * a.blk_bytes;
 
     // this lane's point (past the cloud's end its last one again) and the ids of its slots of the first batch: lane % 4 and four more
@@ -390,10 +394,10 @@ hipError_t FLEX_NARROW_NAME(launch_narrow_records_, FLEX_NARROW_CSR)(const TileA
                                                                      int B, int n_out, hipStream_t s)
 {
     constexpr bool CSR = FLEX_NARROW_CSR != 0;
-    TileArgs a = args;                                   // tiles of this kernel's own
-    a.tpc = (a.N + RECORD_POINTS - 1) / RECORD_POINTS;
-    const int64_t total = (int64_t)B * a.tpc, chunks = (total + 7) / 8 * 8;
-    if (chunks * n_out > 0x7fffffff) return hipErrorInvalidValue;
+    TileArgs a = args;                                   // tiles of this kernel's own: waves
+    a.tpc = (a.N + 15) / 16;
+    const int64_t total = (int64_t)B * a.tpc, chunks = (total + 8 * RECORD_WAVES - 1) / (8 * RECORD_WAVES) * 8;
+    if (total > NARROW_RECORD_WAVES_MAX || chunks * n_out > 0x7fffffff) return hipErrorInvalidValue;
     a.total = (int)total;
     a.chunks = (int)chunks;
     const dim3 grid((unsigned)(chunks * n_out)), block(RECORD_NT);

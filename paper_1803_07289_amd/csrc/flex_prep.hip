@@ -464,21 +464,27 @@ __device__ void copy_tile(const float *__restrict__ src, float *__restrict__ dst
 // ---- point locations as records ---------------------------------------------------------------------
 // pos4[b*N + n] = (x, y, z, 0).  A gather asks the texture path for a cache line per quarter wave and component out of
 // [B,3,N], for one per point out of these.
+// Threads run over the points of all clouds (total: B * N), here and below.  In blocks of one cloud each, 16384 clouds of 16
+// points, K = 8: 64 -> 64 forward 145 us, 130 here; 9 -> 64 from the records below 150 and 30.
 static constexpr int POINTS_PER_THREAD = 4;
 
-__device__ void pack_points(const float *__restrict__ pos, float *__restrict__ pos4, int N, int bpc, int block)
+__device__ __forceinline__ unsigned cloud_of(unsigned g, int N, int total) { return total == N ? 0u : g / (unsigned)N; }
+
+__device__ void pack_points(const float *__restrict__ pos, float *__restrict__ pos4, int N, int total, int block)
 {
-    const int b = block / bpc, n0 = (block - b * bpc) * (PREP_NT * POINTS_PER_THREAD) + threadIdx.x;
-    const float *p = pos + (int64_t)b * 3 * N;
-    v4f *dst = reinterpret_cast<v4f *>(pos4) + (int64_t)b * N;
+    const unsigned g0 = (unsigned)block * (PREP_NT * POINTS_PER_THREAD) + threadIdx.x;
+    v4f *dst = reinterpret_cast<v4f *>(pos4);
     float x[POINTS_PER_THREAD][3];
 #pragma unroll
-    for (int i = 0; i < POINTS_PER_THREAD; ++i)
+    for (int i = 0; i < POINTS_PER_THREAD; ++i) {
+        const unsigned g = min(g0 + PREP_NT * i, (unsigned)total - 1), b = cloud_of(g, N, total);
+        const float *p = pos + (int64_t)b * 3 * N + (g - b * (unsigned)N);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) x[i][d] = p[(int64_t)d * N + min(n0 + PREP_NT * i, N - 1)];
+        for (int d = 0; d < 3; ++d) x[i][d] = p[(int64_t)d * N];
+    }
 #pragma unroll
     for (int i = 0; i < POINTS_PER_THREAD; ++i)
-        if (n0 + PREP_NT * i < N) dst[n0 + PREP_NT * i] = v4f{x[i][0], x[i][1], x[i][2], 0.f};
+        if (g0 + PREP_NT * i < (unsigned)total) dst[g0 + PREP_NT * i] = v4f{x[i][0], x[i][1], x[i][2], 0.f};
 }
 
 // ---- rows of at most 16 channels with their locations, as records -----------------------------------------------------
@@ -487,7 +493,7 @@ __device__ void pack_points(const float *__restrict__ pos, float *__restrict__ p
 // nbr: the neighbour tensor that the records are gathered by, read and dropped here, so that it stands in the memory-side cache
 // (256 MB) when the gather waits for it; null where it is too large to stay there, or lists are walked.
 struct RecordArgs {
-    int N, W, bcn, bpc, K;
+    int N, total, W, bcn, K;             // total: B * N
     float *rec4;
     const int32_t *nbr;
 };
@@ -496,14 +502,16 @@ static constexpr int RECORDS_PER_THREAD = 2;
 __device__ void make_records(const float *__restrict__ pos, const float *__restrict__ feat, float *__restrict__ rec,
                              const RecordArgs &p, int block)
 {
-    const int b = block / p.bpc, n0 = (block - b * p.bpc) * (PREP_NT / 4 * RECORDS_PER_THREAD) + (threadIdx.x >> 2), t = threadIdx.x & 3;
-    const int R = narrow_record_channels(p.W);
-    const float *xyz = pos + (int64_t)b * 3 * p.N, *f = feat + (int64_t)b * p.N * p.W;
+    constexpr int PER_BLOCK = PREP_NT / 4 * RECORDS_PER_THREAD;
+    const int t = threadIdx.x & 3, R = narrow_record_channels(p.W);
+    const unsigned first = (unsigned)block * PER_BLOCK;                  // below total
     const int64_t sn = p.bcn ? 1 : p.W, sc = p.bcn ? p.N : 1;
 #pragma unroll
     for (int i = 0; i < RECORDS_PER_THREAD; ++i) {
-        const int n = n0 + PREP_NT / 4 * i, at = min(n, p.N - 1);
-        const float x = xyz[(int64_t)min(t, 2) * p.N + at];
+        const unsigned n = first + (threadIdx.x >> 2) + PREP_NT / 4 * i, g = min(n, (unsigned)p.total - 1), b = cloud_of(g, p.N, p.total);
+        const int64_t at = g - b * (unsigned)p.N;
+        const float *f = feat + (int64_t)b * p.N * p.W;
+        const float x = pos[((int64_t)b * 3 + min(t, 2)) * p.N + at];
         float v[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -514,15 +522,14 @@ __device__ void make_records(const float *__restrict__ pos, const float *__restr
                 v[r] = c < p.W ? y : 0.f;
             }
         }
-        if (n < p.N) {
-            reinterpret_cast<v4f *>(rec)[((int64_t)b * p.N + n) * 4 + t] = v4f{t < 3 ? x : 1.f, v[0], v[1], v[2]};
-            if (R == 4) p.rec4[((int64_t)b * p.N + n) * 4 + t] = v[3];
+        if (n < (unsigned)p.total) {
+            reinterpret_cast<v4f *>(rec)[(int64_t)n * 4 + t] = v4f{t < 3 ? x : 1.f, v[0], v[1], v[2]};
+            if (R == 4) p.rec4[(int64_t)n * 4 + t] = v[3];
         }
     }
     if (p.nbr != nullptr) {
-        constexpr int PER_BLOCK = PREP_NT / 4 * RECORDS_PER_THREAD;
-        const int first = (block - b * p.bpc) * PER_BLOCK + (threadIdx.x % PER_BLOCK);
-        const int32_t *ids = p.nbr + (int64_t)b * p.K * p.N + min(first, p.N - 1);
+        const unsigned g = min(first + threadIdx.x % PER_BLOCK, (unsigned)p.total - 1), b = cloud_of(g, p.N, p.total);
+        const int32_t *ids = p.nbr + (int64_t)b * p.K * p.N + (g - b * (unsigned)p.N);
         for (int k = threadIdx.x / PER_BLOCK; k < p.K; k += 4 * (PREP_NT / PER_BLOCK)) {
             int x[4];
 #pragma unroll
@@ -543,7 +550,7 @@ struct PrepJob {
         PackPosArgs pos;
         CopyArgs copy;
         struct { int N, wpc, windows; } order;
-        struct { int N, bpc; } points;
+        struct { int N, total; } points;
         RecordArgs records;
         struct { int words; } clear;
     };
@@ -576,7 +583,7 @@ __global__ __launch_bounds__(PREP_NT) __attribute__((amdgpu_waves_per_eu(8, 8)))
         copy_tile((const float *)j.a, (float *)j.dst, j.copy, block, lds);
         break;
     case PREP_POINTS:
-        pack_points((const float *)j.a, (float *)j.dst, j.points.N, j.points.bpc, block);
+        pack_points((const float *)j.a, (float *)j.dst, j.points.N, j.points.total, block);
         break;
     case PREP_RECORDS:
         make_records((const float *)j.a, (const float *)j.b, (float *)j.dst, j.records, block);
@@ -632,15 +639,19 @@ void PrepList::copy(const float *src, float *dst, int B, int N, int Cs, int Cd, 
 
 void PrepList::pack_pos(const float *pos, float *pos4, int B, int N)
 {
-    const int bpc = (N + PREP_NT * POINTS_PER_THREAD - 1) / (PREP_NT * POINTS_PER_THREAD);
-    if (PrepJob *j = next_job(*this, PREP_POINTS, (int64_t)B * bpc, pos, nullptr, pos4)) { j->points.N = N; j->points.bpc = bpc; }
+    constexpr int PER_BLOCK = PREP_NT * POINTS_PER_THREAD;
+    const int64_t total = (int64_t)B * N;
+    if (PrepJob *j = next_job(*this, PREP_POINTS, (total + PER_BLOCK - 1) / PER_BLOCK, pos, nullptr, pos4)) {
+        j->points.N = N; j->points.total = (int)total;
+    }
 }
 
 void PrepList::records(const float *pos, const float *feat, float *rec, float *rec4, int B, int N, int W, int bcn, const int32_t *nbr, int K)
 {
     constexpr int PER_BLOCK = PREP_NT / 4 * RECORDS_PER_THREAD;
-    const int bpc = (N + PER_BLOCK - 1) / PER_BLOCK;
-    if (PrepJob *j = next_job(*this, PREP_RECORDS, (int64_t)B * bpc, pos, feat, rec)) j->records = RecordArgs{N, W, bcn, bpc, K, rec4, nbr};
+    const int64_t total = (int64_t)B * N;
+    if (PrepJob *j = next_job(*this, PREP_RECORDS, (total + PER_BLOCK - 1) / PER_BLOCK, pos, feat, rec))
+        j->records = RecordArgs{N, (int)total, W, bcn, K, rec4, nbr};
 }
 
 void PrepList::clear(void *dst, int words)

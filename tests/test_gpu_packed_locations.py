@@ -53,7 +53,7 @@ def compare(B, N, K, Din, Dout, layout, backward, hub=False):
 @pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
 @pytest.mark.parametrize("B,N,K,Din,Dout", [
     (1, 1, 1, 64, 64), (2, 47, 8, 64, 64), (1, 49, 9, 64, 64), (3, 97, 16, 64, 64), (1, 2049, 5, 64, 64),
-    (2, 33, 3, 64, 128), (1, 300, 8, 64, 32), (1, 300, 12, 32, 64), (2, 2047, 8, 32, 32),
+    (2, 33, 3, 64, 128), (1, 300, 8, 64, 32), (1, 300, 12, 32, 64), (2, 2047, 8, 32, 32), (150, 17, 8, 64, 64),
 ])
 def test_packed_locations_change_no_bit(B, N, K, Din, Dout, layout):
     compare(B, N, K, Din, Dout, layout, False)
@@ -61,12 +61,13 @@ def test_packed_locations_change_no_bit(B, N, K, Din, Dout, layout):
         compare(B, N, K, Din, Dout, layout, True)
 
 
-# the feature gradient: two to four channels a quad with every remainder, clouds around the sixteen points of a wave and the 128
-# of a workgroup, result widths that fill, leave and barely enter a block of 64, K around a batch of eight
+# the feature gradient: two to four channels a quad with every remainder, clouds around the sixteen points of a wave and many
+# that share a workgroup of eight waves, result widths that fill, leave and barely enter a block of 64, K around a batch of eight
 @pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
 @pytest.mark.parametrize("B,N,K,W,other", [
     (1, 1, 1, 5, 4), (1, 15, 3, 6, 64), (2, 16, 8, 7, 32), (1, 17, 9, 8, 65), (3, 63, 8, 9, 68), (1, 65, 16, 10, 3),
     (1, 257, 17, 9, 64), (2, 130, 8, 11, 130), (1, 300, 8, 12, 64), (2, 97, 5, 13, 64), (1, 5000, 8, 16, 20),
+    (67, 17, 8, 9, 64), (300, 1, 1, 16, 8), (41, 16, 4, 5, 70), (19, 33, 9, 13, 64),
 ])
 def test_records_over_lists_change_no_bit(B, N, K, W, other, layout):
     compare(B, N, K, other, W, layout, True)
@@ -79,6 +80,7 @@ def test_records_of_a_hub_point_and_empty_lists():
 
 # the forward pass takes records from 2^17 points on
 @pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
-@pytest.mark.parametrize("B,N,K,W,other", [(1, 131072, 3, 5, 4), (2, 65537, 9, 9, 64), (1, 131073, 8, 12, 65), (3, 43701, 8, 7, 70)])
+@pytest.mark.parametrize("B,N,K,W,other", [(1, 131072, 3, 5, 4), (2, 65537, 9, 9, 64), (1, 131073, 8, 12, 65), (3, 43701, 8, 7, 70),
+                                             (8193, 16, 3, 8, 65), (1009, 130, 8, 9, 64)])
 def test_records_change_no_bit(B, N, K, W, other, layout):
     compare(B, N, K, W, other, layout, False)
