@@ -854,7 +854,11 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
     int *control = (int *)(ws + p.flag);
     const bool fused = p.fused && grad_theta && grad_feat;
     PrepList prep;
-    const float *rows = feat, *g_rows = grad_out, *packed = p.packed.in(ws, workspace_bytes);
+    const float *rows = feat, *g_rows = grad_out;
+    // The parameter gradients alone have nothing else to prepare unless tensors are copied: the packing would be a launch of its
+    // own, which only a cloud in no order earns back.  K = 8, us without and with it: 32 -> 32, 4k points 8.7 and 10.8, 300k 59 and 63,
+    // 1M 173 and 180; 64 -> 64, 300k 96 and 100 (in no order 105 and 97).
+    const float *packed = grad_feat || p.copy ? p.packed.in(ws, workspace_bytes) : nullptr;
     const bool records = packed != nullptr && p.gather.route == FLEX_ROUTE_NARROW;       // made from the tensor as it is
     if (p.copy && (grad_theta || !records)) {
         prep.copy(grad_out, (float *)(ws + p.gT), B, N, Dout, p.k_out, bcn, 0);

@@ -84,3 +84,19 @@ def test_records_of_a_hub_point_and_empty_lists():
                                              (8193, 16, 3, 8, 65), (1009, 130, 8, 9, 64)])
 def test_records_change_no_bit(B, N, K, W, other, layout):
     compare(B, N, K, W, other, layout, False)
+
+
+def test_parameter_gradients_alone_pack_only_beside_copies():
+    # point-major tensors of listed widths are read as they are, and the packing would be the call's only preparation
+    B, N, K, Din, Dout = 1, 700, 8, 64, 64
+    pos, nbr, feat, theta, bias, g = random_problem(5, B, N, K, Din, Dout)
+    for layout, packs in ((fx.BNC, False), (fx.BCN, True)):
+        a = (to_layout(feat, layout), dev(pos), dev(nbr), dev(theta), dev(bias), to_layout(g, layout))
+        edges = fx.flex_inedges_build(a[2])
+        w = BestWorkspace(fx.OP_CONV_BWD, B, N, K, Din, Dout, layout)
+        least = fx.workspace_bytes(fx.OP_CONV_BWD, B, N, K, Din, Dout, layout)
+        w.ws[least:] = 0x5A
+        _, gt, gb = fx.flexconv_bwd(*a, layout=layout, in_edges=edges, need_feat=False, workspace=w.ws)
+        w.check()
+        assert bool((w.ws[least:] != 0x5A).any()) == packs
+        assert rel_err(gt.cpu().numpy(), oracle.flexconv_bwd(feat, pos, nbr, theta, bias, g)[1]) <= TOL
