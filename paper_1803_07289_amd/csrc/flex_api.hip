@@ -464,19 +464,32 @@ struct Packed {
     size_t at, best;                     // where they go; the workspace that has room for them (the plan's own: no use for them)
     const float *in(const char *ws, size_t have) const { return at != 0 && have >= best ? (const float *)(ws + at) : nullptr; }
 };
-// Records of rows of 5 to 12 channels from 2^17 points on, of 5 to 16 over in-edge lists: shorter rows are not worth 64 bytes
-// (3 -> 32, 500k points: 32 us, from records 44), with a second array they gain nothing where the ids stand in order (16 -> 64,
-// 400k: 50 and 52), and a call of few points is its launches (9 -> 64, K = 8, 20k, 100k, 1M points: 18.8, 20.4, 136 and 19.7,
-// 20.8, 98; K = 16, channel-major, 300k 67 and 47; 6 -> 64, 200k points in no order, 45 and 29).  Over lists, forward and backward:
-// 64 -> 13, 20k points, 61 and 57 us; 64 -> 9, 200k, 128 and 117.
-static bool use_records(int64_t B, int64_t N, int w_in, int csr)
+// Which rows travel as records.  Shorter ones than 5 channels are not worth 64 bytes (3 -> 32, 500k points: 32 us, from records 44).
+// Over in-edge lists all others do (us, K = 8, without and with: 64 -> 5, 256 points 11.6 and 10.0, 20k 16.0 and 12.9, 400k 84 and
+// 46; 64 -> 9, 2k 14.1 and 12.7, 200k 40 and 33; 64 -> 16, 50k 27.9 and 17.2; only rows of 9 channels and lists of 3 and fewer
+// lose between 100k and 1M points: K = 2, 200k 27 and 30, 1.2M 144 and 113).  The forward pass is decided by clouds in Z-order, nothing in a
+// cache; a cloud in no order gains at all of these sizes (K = 4, 9 -> 64, 131k: 29 and 22, 300k 53 and 36):
+// - Channel-major tensors are not copied for it then, from 2^17 points on (5 -> 64, K = 4, 131k: 25.9 and 20.4; 12 -> 13, 300k, 38.8 and 35.8).
+// - Point-major, up to 32 result channels: their few stores hold up nothing (9 -> 32, K = 4, 1M 88 and 94; 9 -> 13, K = 8, 1M 86 and 95);
+//   from K = 12 on (K = 16, 200k 36 and 33, 1M 138 and 117).
+// - Wider results, K as long rows need fewer of: 9 -> 64, K = 8, 131k 21.6 and 21.7, 300k 38.8 and 35.5, 1M 142 and 93; 12 -> 64, K = 6,
+//   200k 29.1 and 27.6; 6 -> 64, K = 8, 200k 25.9 and 26.1; 5 -> 64, K = 8, 300k 30.6 and 33.6, K = 10, 200k 30.8 and 28.7.
+// - Below that K from 2^19 points on: 5 -> 64, K = 8, 400k 38.4 and 41.5, 500k 56 and 48, K = 4, 500k 42 and 47, 600k 64 and 53; 12 -> 64,
+//   K = 4, 200k 24.7 and 27.3, 600k 72 and 59.
+// A second array is not worth it there (16 -> 64, 400k: 50 and 52).
+static bool use_records(int64_t B, int64_t N, int K, int w_in, int w_out, int csr, int bcn)
 {
-    if (B * ((N + 15) / 16) > NARROW_RECORD_WAVES_MAX) return false;
-    return w_in >= 5 && (csr || (w_in <= 12 && B * N >= 1 << 17));
+    const int64_t points = B * N;
+    if (w_in < 5 || B * ((N + 15) / 16) > NARROW_RECORD_WAVES_MAX) return false;
+    if (csr) return true;
+    if (w_in > 12 || points < 1 << 17) return false;
+    if (bcn) return true;
+    if (w_out <= 32) return K >= 12;
+    return K >= (w_in >= 8 ? 6 : w_in >= 6 ? 8 : 10) || points >= 1 << 19;
 }
-static Packed plan_packed(int64_t B, int64_t N, int route, int w_in, int csr, size_t total)
+static Packed plan_packed(int64_t B, int64_t N, int K, int route, int w_in, int w_out, int csr, int bcn, size_t total)
 {
-    const int64_t record = use_records(B, N, w_in, csr) ? 64 + (narrow_record_channels(w_in) == 4 ? 16 : 0) : 0;
+    const int64_t record = use_records(B, N, K, w_in, w_out, csr, bcn) ? 64 + (narrow_record_channels(w_in) == 4 ? 16 : 0) : 0;
     const int64_t per_point = route == FLEX_ROUTE_LEAN ? 16 : route == FLEX_ROUTE_NARROW ? record : 0;
     if (per_point == 0 || N * 64 > (1ll << 32) - 128) return Packed{0, total};       // 32-bit offsets, and one past the end
     const size_t at = align256(total);
@@ -530,7 +543,7 @@ static FwdPlan plan_fwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     if (p.padded)
         at = std::max(at, copies + (p.wide ? wide_packed_bytes(p.k_in, p.k_out) : theta_ws_bytes(p.k_in, p.k_out)));
     p.total = at;
-    p.packed = plan_packed(B, N, p.gather.route, Din, 0, at);
+    p.packed = plan_packed(B, N, K, p.gather.route, Din, Dout, 0, bcn, at);
     return p;
 }
 
@@ -564,7 +577,7 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
         p.inedge_ws = at; at += inedges_ws_bytes(B * N, K);
     }
     p.total = at;
-    p.packed = plan_packed(B, N, p.gather.route, Dout, 1, at);
+    p.packed = plan_packed(B, N, K, p.gather.route, Dout, Din, 1, layout == FLEX_LAYOUT_BCN, at);
     return p;
 }
 

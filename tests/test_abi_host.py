@@ -386,3 +386,26 @@ def test_a_device_without_room_for_records_takes_the_call_in_the_smallest_worksp
         ws, have = fx._conv_ws_arg(None, torch.device("cpu"), *sizes)
         assert asked == ([best, least] if best > least else [best]) and have == ws.numel() == least
     assert best_is_more
+
+
+# both sides of every line of the rule: (layout, points, K, Din, Dout) of the forward pass, then over in-edge lists
+@pytest.mark.parametrize("layout,N,K,Din,Dout,takes", [
+    (1, 1 << 17, 8, 9, 64, True), (1, (1 << 17) - 1, 8, 9, 64, False), (1, 1 << 17, 5, 9, 64, False), (1, 1 << 19, 5, 9, 64, True),
+    (1, 1 << 17, 6, 8, 33, True), (1, 1 << 17, 7, 7, 64, False), (1, 1 << 17, 8, 6, 64, True), (1, 1 << 17, 9, 5, 64, False),
+    (1, 1 << 17, 10, 5, 64, True), (1, 1 << 19, 1, 5, 64, True), (1, 1 << 19, 11, 9, 32, False), (1, 1 << 17, 12, 9, 32, True),
+    (1, 1 << 20, 16, 4, 64, False), (1, 1 << 20, 16, 13, 64, False), (0, 1 << 17, 1, 5, 4, True), (0, (1 << 17) - 1, 16, 9, 64, False),
+])
+def test_which_forward_calls_have_room_for_records(L, layout, N, K, Din, Dout, takes):
+    import paper_1803_07289_amd as fx
+    least = fx.workspace_bytes(fx.OP_CONV_FWD, 1, N, K, Din, Dout, layout)
+    best = L.flexconv_workspace_bytes_best(fx.OP_CONV_FWD, 1, N, K, Din, Dout, layout)
+    assert best - least >= 64 * N if takes else best == least
+
+
+@pytest.mark.parametrize("W,per_point", [(4, 0), (5, 64), (12, 64), (13, 80), (16, 80)])
+def test_which_feature_gradients_have_room_for_records(L, W, per_point):
+    import paper_1803_07289_amd as fx
+    for N in (16, 4096):
+        sizes = (fx.OP_CONV_BWD, 1, N, 2, 64, W, fx.BNC)
+        room = L.flexconv_workspace_bytes_best(*sizes) - fx.workspace_bytes(*sizes)
+        assert per_point * N <= room < per_point * N + 512

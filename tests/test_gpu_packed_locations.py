@@ -78,10 +78,10 @@ def test_records_of_a_hub_point_and_empty_lists():
     compare(2, 90, 8, 9, 9, fx.BCN, True, hub=True)
 
 
-# the forward pass takes records from 2^17 points on
+# the forward pass takes records from 2^17 points on, point-major where K is large enough for the widths
 @pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
-@pytest.mark.parametrize("B,N,K,W,other", [(1, 131072, 3, 5, 4), (2, 65537, 9, 9, 64), (1, 131073, 8, 12, 65), (3, 43701, 8, 7, 70),
-                                             (8193, 16, 3, 8, 65), (1009, 130, 8, 9, 64)])
+@pytest.mark.parametrize("B,N,K,W,other", [(1, 131072, 12, 5, 4), (2, 65537, 9, 9, 64), (1, 131073, 8, 12, 65), (3, 43701, 8, 7, 70),
+                                             (8193, 16, 9, 8, 65), (1009, 130, 8, 9, 64)])
 def test_records_change_no_bit(B, N, K, W, other, layout):
     compare(B, N, K, W, other, layout, False)
 
