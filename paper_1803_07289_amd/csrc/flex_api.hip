@@ -395,13 +395,21 @@ static hipError_t gather_pack(PrepList &prep, const GatherPlan &g, const float *
     return hipSuccess;
 }
 
+// Reading the ids ahead pays while they still stand in the memory-side cache (256 MB) when the gather asks for them, beside what the
+// preparation reads and writes; beyond that it is a read more.  9 -> 64 in Z-order, nothing in a cache, us without and with: K = 8,
+// 500k points (bytes below: 88 MB) 66 and 55, 1M (176) 123 and 99, 1.5M (264) 181 and 172, 1.7M (299) 202 and 203, 3M 366 and 390; K = 16,
+// 1M (240) 147 and 123, 1.2M (288) 177 and 182, 2M 288 and 319; 5 -> 64, K = 8, 1.7M (272) 192 and 179.
+static bool read_ids_ahead(int64_t points, int K, int w_in) { return points * (64 + 12 + 4 * w_in + 8 * K) <= 272ll << 20; }
+
 // The records that the planned kernels gather instead of the tensors (Packed; packed null: none)
 // nbr: what they will be gathered by (null: in-edge lists).
-static void pack_points(PrepList &prep, const GatherPlan &g, const float *pos, const float *rows, float *packed, int B, int N, int w_in, int bcn, const int32_t *nbr, int K)
+static void pack_points(PrepList &prep, const GatherPlan &g, const float *pos, const float *rows, float *packed, int B, int N,
+                        int w_in, int bcn, const int32_t *nbr, int K)
 {
     if (packed == nullptr) return;
-    if (g.route == FLEX_ROUTE_NARROW) prep.records(pos, rows, packed, packed + (int64_t)B * N * 16, B, N, w_in, bcn,
-                                                 (int64_t)B * N * K * 4 <= (96ll << 20) ? nbr : nullptr, K);     // (beside the records)
+    if (g.route == FLEX_ROUTE_NARROW)
+        prep.records(pos, rows, packed, packed + (int64_t)B * N * 16, B, N, w_in, bcn,
+                     read_ids_ahead((int64_t)B * N, K, w_in) ? nbr : nullptr, K);
     else prep.pack_pos(pos, packed, B, N);
 }
 static PosRef pos_ref(const float *pos, const float *packed, int N) { return packed ? pos_packed(packed, N) : pos_planar(pos, N); }
