@@ -1048,9 +1048,10 @@ int flex_idiss_phi(const float *pos, const int32_t *nbr, float *phi, int B, int 
     return flex_idiss_phi_ws(pos, nbr, phi, B, N, K, nullptr, 0, stream);
 }
 
-// Packing pays from 2^22 neighbours on.  us without and with it, tensors not in a cache, a room in the sensor's order | in
-// Z-order: 100k points, K = 8: 13.3, 13.5 | 8.2, 11.2; 300k, K = 8: 27.7, 22.1 | 12.0, 14.6; 1M, K = 4: 65.4, 39.7 | 23.3, 24.1;
-// 300k, K = 16: 53.1, 35.3 | 19.6, 19.4; 1M, K = 8: 93.0, 56.5 | 26.0, 26.9; 3M, K = 16: 739, 371 | 129, 111.
+// Packing is a launch, and pays on clouds in no order from 2^22 neighbours on; which order a cloud has is not known here, and a scan
+// comes in its sensor's.  us without and with it, nothing in a cache, a room in the sensor's order | in Z-order: 100k points, K = 8: 13.3,
+// 13.5 | 8.2, 11.2; 300k, K = 8: 27.7, 22.1 | 12.0, 14.6; 600k, K = 8: 51.3, 35.6 | 14.7, 20.6; 1M, K = 8: 87.4, 53.7 | 21.6, 25.0; 1M,
+// K = 16: 184, 100 | 41.2, 36.9; 2.9M, K = 8 in Z-order 56.3, 55.0.
 size_t flex_idiss_phi_workspace_bytes(int B, int N, int K)
 {
     if (!sizes_ok(B, N, K, 1, 1) || (int64_t)B * N * K < 1 << 22) return 0;

@@ -15,7 +15,8 @@ static constexpr int IDISS_ITEMS = 8;                       // points per thread
 static constexpr int IDISS_CHUNK = 256 * IDISS_ITEMS;       // points per block
 
 // What bounds it is the lines that the neighbours' locations lie in.  PACKED: they come from records (x, y, z, 0) (pos4), one
-// line each instead of three: 1M points of a room in the sensor's order, K = 8, 84 -> 45 us and 5 for the packing.
+// line each instead of three: 1M points of a room in the sensor's order, K = 8, 84 -> 45 us and 5 for the packing.  The point's own
+// too, which some neighbour asks for anyway (Z-order, 2.9M points, tensors in a cache: the call 49.9 us with it from pos, 46.2).
 template <bool PACKED>
 __global__ __launch_bounds__(256) void idiss_phi_kernel(const float *__restrict__ pos, const float *__restrict__ pos4,
                                                         const int32_t *__restrict__ nbr, float *__restrict__ phi, int64_t BN,
@@ -28,7 +29,13 @@ __global__ __launch_bounds__(256) void idiss_phi_kernel(const float *__restrict_
         const float *p = pos + b * 3 * N;
         const v4f *p4 = reinterpret_cast<const v4f *>(pos4) + b * N;
         const int32_t *nb = nbr + b * K * N + l;
-        const float cx = p[l], cy = p[(int64_t)N + l], cz = p[2 * (int64_t)N + l];
+        float cx, cy, cz;
+        if constexpr (PACKED) {
+            const v4f me = p4[l];
+            cx = me[0]; cy = me[1]; cz = me[2];
+        } else {
+            cx = p[l]; cy = p[(int64_t)N + l]; cz = p[2 * (int64_t)N + l];
+        }
         // the ids of eight neighbours together, then their 24 position components: on a cloud stored without locality
         // every one of those is a line of its own, and what counts is how many are on their way
         float s = 0.f;
