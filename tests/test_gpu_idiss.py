@@ -35,8 +35,9 @@ def test_phi_matches_oracle(B, N, K):
     assert rel_err(phi.cpu().numpy(), oracle.idiss_phi(pos, nbr)) <= 2e-6
 
 
-# around a packing block of 1024 points, K around a batch of eight; the last one packs by the binding's own choice
-@pytest.mark.parametrize("B,N,K", [(1, 1, 1), (2, 1023, 8), (3, 1025, 9), (1, 4097, 7), (2, 131073, 16)])
+# around a packing block of 2048 points, K around a batch of eight; the last one packs by the binding's own choice
+@pytest.mark.parametrize("B,N,K", [(1, 1, 1), (2, 1023, 8), (3, 1025, 9), (1, 2048, 7), (2, 2047, 8), (3, 2049, 9), (150, 17, 8), (1, 4097, 7),
+                                   (2, 131073, 16)])
 def test_phi_from_packed_locations_is_the_same_bits(B, N, K):
     say(f"idiss phi packed B={B} N={N} K={K}")
     rng = np.random.default_rng(N)
@@ -44,13 +45,17 @@ def test_phi_from_packed_locations_is_the_same_bits(B, N, K):
     nbr = dev(rng.integers(0, N, size=(B, K, N)).astype(np.int32))
     assert (fx.lib().flex_idiss_phi_workspace_bytes(B, N, K) > 0) == (B * N * K >= 1 << 22)
     ws = torch.empty(16 * B * N + 256, dtype=torch.uint8, device="cuda")
-    ws[16 * B * N:] = 0xA5
+    ws[:] = 0xA5
     phi = [torch.full((B, N), -1.0, device="cuda") for _ in range(2)]
     for out, have in zip(phi, (16 * B * N - 1, 16 * B * N)):             # one byte short: as without a workspace
         fx._check(fx.lib().flex_idiss_phi_ws(fx._ptr(pos), fx._ptr(nbr), fx._ptr(out), B, N, K, fx._ptr(ws), have,
                                              fx._stream()), "flex_idiss_phi_ws")
+        if have < 16 * B * N:
+            assert bool((ws == 0xA5).all())
     assert torch.equal(phi[0], phi[1]) and torch.equal(phi[0], fx.flex_idiss_phi(pos, nbr))
     assert bool((ws[16 * B * N:] == 0xA5).all())
+    assert torch.equal(ws[:16 * B * N].view(torch.float32).view(B, N, 4),                # the second call packed
+                       torch.cat([pos.transpose(1, 2), torch.zeros(B, N, 1, device="cuda")], 2))
 
 
 @pytest.mark.parametrize("B,N,Ns", [(2, 1000, 250), (1, 2048, 2048), (3, 77, 1), (1, 5000, 1250), (2, 2049, 700)])

@@ -58,13 +58,45 @@ def test_kept_centres():
     check(nbr, sel)
 
 
-# full runs of the deal step, and both sides of the number of buckets up to which it orders a run in LDS (3072 of 1024 points)
-@pytest.mark.parametrize("N", [1_100_001, 3_145_728, 3_145_729])
-def test_random_tensors_of_many_buckets(N):
-    say(f"in-edges N={N} K=8")
+def check_large(nbr, sel=None):
+    """The same on the device: the edges in (cloud, centre, slot) order, sorted by target without disturbing it."""
+    B, K, N = nbr.shape
+    off, src = fx.flex_inedges_build(nbr) if sel is None else fx.flex_inedges_build_sub(nbr, sel)
+    cols = nbr if sel is None else nbr.gather(2, sel.long()[:, None, :].expand(-1, K, -1))
+    tgt = (cols + N * torch.arange(B, device="cuda", dtype=torch.int32)[:, None, None]).transpose(1, 2).reshape(-1)
+    tgt, at = torch.sort(tgt, stable=True)
+    assert torch.equal(src, (at // K % cols.shape[2]).int())
+    assert torch.equal(off, torch.searchsorted(tgt, torch.arange(B * N + 1, device="cuda", dtype=torch.int32)).int())
+
+
+# full runs of the deal step, and both sides of the number of buckets up to which it orders a run in LDS (3072 of 1024 points); runs
+# that cross clouds and slots, buckets of other sizes (512, 2048 points)
+@pytest.mark.parametrize("B,N,K", [(1, 1_100_001, 8), (1, 3_145_728, 8), (1, 3_145_729, 8), (3, 250_001, 9), (2, 200_003, 16), (7, 300_001, 3)])
+def test_random_tensors_of_many_buckets(B, N, K):
+    say(f"in-edges B={B} N={N} K={K}")
     g = torch.Generator("cuda").manual_seed(N)
-    nbr = torch.randint(0, N, (1, 8, N), device="cuda", dtype=torch.int32, generator=g)
-    off, src = fx.flex_inedges_build(nbr)
-    tgt, at = torch.sort(nbr[0].t().reshape(-1), stable=True)
-    assert torch.equal(src, (at // 8).int())
-    assert torch.equal(off, torch.searchsorted(tgt, torch.arange(N + 1, device="cuda", dtype=torch.int32)).int())
+    check_large(torch.randint(0, N, (B, K, N), device="cuda", dtype=torch.int32, generator=g))
+
+
+# runs that are ordered in LDS beside runs that are stored as they come, and one that a hub point's entries fill
+@pytest.mark.parametrize("hub", [False, True])
+def test_runs_with_and_without_locality(hub):
+    N, K = 900_001, 8
+    say(f"in-edges, half of the runs local, hub={hub}")
+    g = torch.Generator("cuda").manual_seed(3)
+    nbr = torch.randint(0, N, (1, K, N), device="cuda", dtype=torch.int32, generator=g)
+    near = (torch.arange(N, device="cuda")[None] + torch.randint(-20, 21, (K // 2, N), device="cuda", generator=g)).clamp_(0, N - 1)
+    nbr[0, ::2] = near.int()
+    if hub:
+        nbr[0, 3, 400_000:425_000] = 7       # 25 000 entries in one list
+    check_large(nbr)
+
+
+def test_many_kept_centres():
+    # B * K * Ns edges enough for full runs; entries of a selection in no order
+    B, N, K, Ns = 2, 500_001, 8, 330_001
+    say(f"in-edges over kept centres B={B} N={N} Ns={Ns}")
+    g = torch.Generator("cuda").manual_seed(4)
+    nbr = torch.randint(0, N, (B, K, N), device="cuda", dtype=torch.int32, generator=g)
+    sel = torch.stack([torch.randperm(N, device="cuda", generator=g)[:Ns] for _ in range(B)]).int()
+    check_large(nbr, sel)

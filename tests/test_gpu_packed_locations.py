@@ -1,6 +1,7 @@
 """The convolution with room for packed point locations, or records of narrow rows with theirs, behind its workspace
 (flexconv_workspace_bytes_best) against the same call in a workspace of the smallest size, which reads the tensors
-themselves: the same bits, and both within the oracle's tolerance."""
+themselves: the same bits, and both within the oracle's tolerance.  That the records were made, and where they lie, is read from
+the workspace."""
 import pytest
 import torch
 
@@ -22,6 +23,27 @@ class BestWorkspace(ExactWorkspace):
         self.ws = self.buf[:self.need]
 
 
+def up256(n):
+    return -(-n // 256) * 256
+
+
+def expected_records(pos, rows):
+    """numpy [B,3,N] and the gathered rows [B,W,N] -> the bytes behind the workspace: (x, y, z, 0) a point, or for W <= 16 four quads
+    (component t of (x, y, z, 1), channels R t .. R t + 2) and, R = 4, behind all of them the channels 4 t + 3."""
+    B, _, N = pos.shape
+    at = torch.from_numpy(pos).transpose(1, 2)
+    if rows.shape[1] > 16:
+        return torch.cat([at, torch.zeros(B, N, 1)], 2).reshape(-1)
+    R = -(-rows.shape[1] // 4)
+    ch = torch.zeros(B, N, 4 * R)
+    ch[:, :, :rows.shape[1]] = torch.from_numpy(rows).transpose(1, 2)
+    ch = ch.reshape(B, N, 4, R)
+    rec = torch.zeros(B, N, 4, 4)
+    rec[..., 0] = torch.cat([at, torch.ones(B, N, 1)], 2)
+    rec[..., 1:1 + min(R, 3)] = ch[..., :3]
+    return torch.cat([rec.reshape(-1)] + ([ch[..., 3].reshape(-1)] if R == 4 else []))
+
+
 def compare(B, N, K, Din, Dout, layout, backward, hub=False):
     say(f"packed: B={B} N={N} K={K} {Din}->{Dout} layout={layout} hub={hub}")
     pos, nbr, feat, theta, bias, g = random_problem(40 + N + K, B, N, K, Din, Dout)
@@ -33,12 +55,19 @@ def compare(B, N, K, Din, Dout, layout, backward, hub=False):
     results = []
     for kind in (ExactWorkspace, BestWorkspace):
         w = kind(fx.OP_CONV_BWD if backward else fx.OP_CONV_FWD, B, N, K, Din, Dout, layout)
+        w.ws.fill_(0x5A)
         if backward:
             r = fx.flexconv_bwd(*a, gd, layout=layout, in_edges=edges, workspace=w.ws)
             r += fx.flexconv_bwd(*a, gd, layout=layout, in_edges=edges, need_params=False, workspace=w.ws)[:1]
         else:
             r = (fx.flexconv_fwd(*a, layout=layout, workspace=w.ws),)
         w.check()
+        if kind is BestWorkspace:
+            want = expected_records(pos, g if backward else feat)
+            at = w.need - up256(4 * want.numel())
+            assert at >= fx.workspace_bytes(fx.OP_CONV_BWD if backward else fx.OP_CONV_FWD, B, N, K, Din, Dout, layout)
+            got = w.ws[at:at + 4 * want.numel()].view(torch.int32).cpu()
+            assert torch.equal(got, want.view(torch.int32))
         results.append(r)
     for x, y in zip(*results):
         assert torch.equal(x, y)
