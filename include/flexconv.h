@@ -406,8 +406,10 @@ int flex_validate_selection(const int32_t *sel, int B, int Ns, int Nf, int32_t *
 /* Bytes of workspace needed by op (a flex_op) at these sizes. 0 on bad sizes. */
 size_t flexconv_workspace_bytes(int op, int B, int N, int K, int Din, int Dout, int layout);
 /* Bytes of workspace with which op runs fastest: at least flexconv_workspace_bytes.  The convolution's forward and
- * backward pass use what lies beyond for the point locations as 16-byte records (a gather of neighbours' locations then
- * touches one cache line per neighbour, not three); results are the same bits either way. */
+ * backward pass use what lies beyond for records that a gather of neighbours reads in one cache line each: the point
+ * locations, 16 bytes a point, or, where rows of 5 to 16 channels are gathered, locations and rows together, 64 bytes a
+ * point up to 12 channels and 80 beyond (9 -> 64 on 7 M points: 448 MB).  How much there is depends on all the sizes and
+ * the layout; results are the same bits with and without.  flexconv_fwd_noalloc runs without. */
 size_t flexconv_workspace_bytes_best(int op, int B, int N, int K, int Din, int Dout, int layout);
 
 /* Debug aid: *bad_count_dev (device int32) = number of nbr entries outside [0,N). */

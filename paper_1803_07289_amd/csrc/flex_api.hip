@@ -467,7 +467,10 @@ static size_t rows_bytes(int64_t B, int64_t N, int width) { return align256(size
 // has it gathers records, any other the tensors; the results are the same bits.  (The tile kernels read the location tensor
 // either way: a lane of theirs reads an entry's three components, the entries of a quarter wave are two slots of eight adjacent points,
 // whose neighbours' components lie in a few lines of the tensor and in as many as sixteen of the records.  128 -> 128, 1M points,
-// parameter gradient 1020 us, from records 1180; 64 -> 13, 2 x 50 021 points, forward 36 and 42.)
+// parameter gradient 1020 us, from records 1180; 64 -> 13, 2 x 50 021 points, forward 36 and 42.)  The wave-specialised kernels have
+// them at every size: in Z-order they cost nothing beyond what two runs differ by (64 -> 64, K = 8, us without and with: forward, 4k
+// points 12.3 and 12.1, 60k 23.6 and 23.3, 1M 225 and 224, all gradients 33, 52, 379 and 33, 52, 376; 32 -> 32 the same), in no order
+// they gain from the smallest sizes on (forward, 60k 26.2 and 24.1, 300k 96 and 86; all gradients, 300k 151 and 143).
 struct Packed {
     size_t at, best;                     // where they go; the workspace that has room for them (the plan's own: no use for them)
     const float *in(const char *ws, size_t have) const { return at != 0 && have >= best ? (const float *)(ws + at) : nullptr; }

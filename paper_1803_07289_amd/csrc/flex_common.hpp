@@ -100,8 +100,8 @@ hipError_t launch_generic_bwd_pos(const float *feat, const int32_t *nbr, const f
 hipError_t launch_copy_rows(const float *src, float *dst, int B, int N, int Cs, int Cd, int src_bcn, int dst_bcn,
                             hipStream_t s, int c_off = 0);
 
-// Point locations as the lean and tile kernels read them: the tensor [B,3,N] itself, or packed as (x, y, z, 0) records
-// (PrepList::pack_pos).  A component's byte offset inside a cloud is (point << shift) + component * col.
+// Point locations as the lean kernels read them: the tensor [B,3,N] itself, or packed as (x, y, z, 0) records
+// (PrepList::pack_pos; the tile kernels read the tensor).  A component's byte offset inside a cloud is (point << shift) + component * col.
 struct PosRef {
     const float *p;
     unsigned col;            // bytes from component to component

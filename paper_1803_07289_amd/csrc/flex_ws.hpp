@@ -50,7 +50,7 @@ struct WsGeom {
     static_assert(NITEMS % NC == 0 || NC % NITEMS == 0, "items per consumer wave");
     static constexpr int IPW = cdiv_c(NITEMS, NC);
     static_assert(IPW == 1 || NS % NC == 0 || NC % NS == 0, "slice split");
-    // split-half aggregate tile: per point [hi: KDP halves][lo: KDP halves][16 B pad]
+    // split-half aggregate tile: per point [hi: KDP halves][lo: KDP halves][32 B pad]
     static constexpr int KDP = rup_c(S::KD, 32);         // depth padded to the f16 matrix op
     static constexpr int KS2 = KDP / 32;                 // depth steps of v_mfma_f32_16x16x32_f16
     // row stride in bytes, 32 mod 256 (or 160): a turn of the 16-byte reads (tile_swizzle has the turns) finds its sixteen rows
@@ -583,7 +583,7 @@ struct LeanProducer {
     // the tiles' conflict-free strides and the packed locations, 64 -> 64, 7M points, us: forward 1361 -> 1303, one-pass backward
     // 2690 -> 2550.
     static constexpr bool ROW16 = S::LPR == 16;
-    static constexpr bool MX = ROW16 && !SUM;
+    static constexpr bool MX = ROW16 && !SUM, DP_LDS = !ROW16 && !SUM;
 
     const float *rows;
     PosRef pos;
@@ -595,7 +595,7 @@ struct LeanProducer {
     int grp, t;
     bool lane_on;
     unsigned lane_off;           // byte offset of the lane's channels in a row
-    int perm_id, perm_dp;        // ds_bpermute byte addresses of entry (k = 0, g) in the entry layout
+    int perm_id;                 // not ROW16: ds_bpermute byte address of entry (k = 0, g) in the entry layout
     // entry layout: lane = (entry e = lane>>2 of 16, component c = lane&3); register half h holds slots 4h .. 4h+3 of the
     // four points, ROW16: e = 4 * point + slot, so that an entry stands in its point's lane group, else e = 4 * slot + point
     int e_g, e_k;                // point and slot (within half 0) of this lane's entry
@@ -613,9 +613,7 @@ struct LeanProducer {
         grp = lane / S::LPR; t = lane % S::LPR;
         lane_on = (S::VEC * t) < S::DI;
         lane_off = lane_on ? 4u * S::VEC * t : 0u;       // lanes past the row read its start, value unused
-        const int g = grp % G::PW, dsel = lane & 3;
-        perm_id = 4 * (4 * g);
-        perm_dp = 4 * (4 * g + dsel);
+        perm_id = 4 * (4 * (grp % G::PW));
         e_g = ROW16 ? lane >> 4 : (lane >> 2) & 3;
         e_k = ROW16 ? (lane >> 2) & 3 : lane >> 4;
         const int c = lane & 3;
@@ -762,7 +760,6 @@ struct LeanProducer {
             const int k0_acc = k0_cur;
             k0_cur = x1.k0;
             // ids of batch m+1 are here: their positions and (below) rows go in flight; ids of batch m+2 too
-            constexpr bool DP_LDS = !SUM && !MX;
             // with a full last batch the fourth component of an entry (the constant 1) is not needed as a weight:
             // it carries the byte offset of the NEXT batch's row instead, which saves that batch's id permutes
             constexpr bool ID_LDS = DP_LDS && !TAIL;
@@ -868,7 +865,7 @@ struct LeanProducer {
 // ---------------------------------------------------------------------------
 // Lean producer over in-edge lists (feature gradient): the rows are grad_out rows of the
 // centres that list a point, dp = pos[point] - pos[centre].  Same machinery as LeanProducer
-// (entry-layout loads, ds_bpermute spread, rolling 8-row window, vector-ALU aggregate); a
+// (entry-layout loads, rolling 8-row window, the aggregate by outer products or multiply-adds); a
 // batch is list slots 8*bi .. 8*bi+7 of each of the wave's 4 points, a tile takes
 // max(1, ceil(longest list / 8)) batches, which differs from wave to wave and tile to tile.
 // Slots past a list's end gather the point's own row with dp = (0,0,0,0), i.e. add nothing.
@@ -884,7 +881,7 @@ struct LeanCsrProducer {
     using G = WsGeom<S, PM>;
     static constexpr int U = 8;
     static constexpr bool FULL = (S::LPR * S::VEC == S::DI);
-    static constexpr bool ROW16 = S::LPR == 16, MX = ROW16 && !SUM;     // LeanProducer
+    static constexpr bool ROW16 = S::LPR == 16, MX = ROW16 && !SUM, DP_LDS = !ROW16 && !SUM;     // LeanProducer
     static constexpr unsigned ENTRY0 = ROW16 ? 15 : 0x33;      // lane & ENTRY0 == 0: slot 0, component 0 of a point
     static_assert(G::PW == 4, "entry layout: 4 points x 8 list slots per batch");
 
@@ -1115,7 +1112,6 @@ struct LeanCsrProducer {
             const char *rb = reinterpret_cast<const char *>(rows + (int64_t)d1.b * N * (unsigned)S::DI);
             d0 = d1;
             fetch(c, idn, d1);
-            constexpr bool DP_LDS = !SUM && !MX;
             float dpc[SUM ? U : 1];
             v4f dpv[DP_LDS ? 3 : 1];
             if constexpr (DP_LDS) {
@@ -1351,7 +1347,8 @@ void gather_contract_lean_kernel(const float *__restrict__ rows, const PosRef po
     using G = WsGeom<S, PM>;
     __shared__ __attribute__((aligned(16))) char s_A[2 * G::T * G::ROWB];
     __shared__ int s_E[2 * G::T];
-    __shared__ __attribute__((aligned(16))) float s_D[G::NP][128];     // per producer wave: a batch's position differences
+    using Gatherer = LeanProducer<S, PM, false, TAIL>;
+    __shared__ __attribute__((aligned(16))) float s_D[Gatherer::DP_LDS ? G::NP : 1][Gatherer::DP_LDS ? 128 : 1];     // per producer wave: a batch's position differences
 
     const TileSchedule sc(total_tiles);
     const int w = threadIdx.x >> 6;
@@ -1368,9 +1365,9 @@ void gather_contract_lean_kernel(const float *__restrict__ rows, const PosRef po
     }
 
     if (w < G::NP) {
-        LeanProducer<S, PM, false, TAIL> P;
+        Gatherer P;
         P.init(rows, pos, nbr, N, K, w, sc, tiles_per_cloud);
-        P.set_dp_stage(s_D[w]);
+        if constexpr (Gatherer::DP_LDS) P.set_dp_stage(s_D[w]);
         float rsc[S::VEC][4];
         load_row_scales<S>(rsc, thetaP, theta_exp_off, P.t);
         P.run([&](const v4f (&acc)[S::VEC], int i, int, int) {
@@ -1396,7 +1393,8 @@ void grad_feat_lean_kernel(const float *__restrict__ rows, const PosRef pos,
     __shared__ __attribute__((aligned(16))) char s_A[2 * G::T * G::ROWB];
     __shared__ int s_E[2 * G::T];
     __shared__ int s_P[2 * G::T];       // the point in every tile slot (the tiles walk the cloud in `order`)
-    __shared__ __attribute__((aligned(16))) float s_D[G::NP][128];     // per producer wave: a batch's position differences
+    using Gatherer = LeanCsrProducer<S, PM, false, true>;
+    __shared__ __attribute__((aligned(16))) float s_D[Gatherer::DP_LDS ? G::NP : 1][Gatherer::DP_LDS ? 128 : 1];     // per producer wave: a batch's position differences
 
     const TileSchedule sc(total_tiles);
     const int w = threadIdx.x >> 6;
@@ -1411,10 +1409,10 @@ void grad_feat_lean_kernel(const float *__restrict__ rows, const PosRef pos,
     }
 
     if (w < G::NP) {
-        LeanCsrProducer<S, PM, false, true> P;
+        Gatherer P;
         P.init(rows, pos, off, src, N, w, sc, tiles_per_cloud);
         P.order = order;
-        P.set_dp_stage(s_D[w]);
+        if constexpr (Gatherer::DP_LDS) P.set_dp_stage(s_D[w]);
         float rsc[S::VEC][4];
         load_row_scales<S>(rsc, thetaP, theta_exp_off, P.t);
         const bool id_writer = (threadIdx.x & P.ENTRY0) == 0;        // entry lanes (slot 0, component 0) of the four points
@@ -1731,14 +1729,15 @@ __device__ __forceinline__ void grad_theta_lean_body(const float *__restrict__ r
     constexpr int AS = bf3_stride(S::KD), GS = bf3_stride(S::DOP);
     __shared__ __attribute__((aligned(16))) char s_A[2][G::T * AS];
     __shared__ __attribute__((aligned(16))) char s_G[2][G::T * GS];
-    __shared__ __attribute__((aligned(16))) float s_D[G::NP][128];     // per producer wave: a batch's position differences
+    using Gatherer = LeanProducer<S, 2, false, TAIL>;
+    __shared__ __attribute__((aligned(16))) float s_D[Gatherer::DP_LDS ? G::NP : 1][Gatherer::DP_LDS ? 128 : 1];     // per producer wave: a batch's position differences
 
     const int w = threadIdx.x >> 6;
 
     if (w < G::NP) {
-        LeanProducer<S, 2, false, TAIL> P;
+        Gatherer P;
         P.init(rows, pos, nbr, N, K, w, sc, tiles_per_cloud);
-        P.set_dp_stage(s_D[w]);
+        if constexpr (Gatherer::DP_LDS) P.set_dp_stage(s_D[w]);
         // grad_out tile: T*DOP/4 four-float chunks over the producer threads, one tile ahead in registers
         constexpr int CPR = S::DOP / 4;                      // chunks per point
         constexpr int NCH = cdiv_c(G::T * CPR, 64 * G::NP);  // chunks per thread
@@ -1998,7 +1997,8 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
     __shared__ __attribute__((aligned(16))) char s_F[2 * G::T * F::FS];
     __shared__ int s_E[F::NBUF * G::T];
     __shared__ int s_P[F::NBUF * G::T];
-    __shared__ __attribute__((aligned(16))) float s_D[G::NP][128];
+    using Gatherer = LeanCsrProducer<S, 2, false, true>;
+    __shared__ __attribute__((aligned(16))) float s_D[Gatherer::DP_LDS ? G::NP : 1][Gatherer::DP_LDS ? 128 : 1];     // per producer wave: a batch's position differences
     __shared__ __attribute__((aligned(16))) int s_cs[S::DO];
 
     const TileSchedule sc(total_tiles);
@@ -2037,10 +2037,10 @@ void bwd_fused_lean_kernel(const float *__restrict__ g_rows, const float *__rest
     __syncthreads();
 
     if (w < G::NP) {
-        LeanCsrProducer<S, 2, false, true> P;
+        Gatherer P;
         P.init(g_rows, pos, off, src, N, w, sc, tiles_per_cloud);
         P.order = order;
-        P.set_dp_stage(s_D[w]);
+        if constexpr (Gatherer::DP_LDS) P.set_dp_stage(s_D[w]);
         float rsc[S::VEC][4];
         load_row_scales<S>(rsc, thetaP, theta_exp_off, P.t);
         const bool id_writer = (threadIdx.x & P.ENTRY0) == 0;
