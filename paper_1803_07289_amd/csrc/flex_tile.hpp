@@ -551,7 +551,8 @@ void tile_conv_kernel(const TileArgs a)
 // The gathering waves are those of the convolution above, and the contracting waves fetch the
 // upstream gradient.  One tile buffer (100 KB of LDS): the gathering waves sum the next tile in registers while this one is
 // contracted, and park it between two barriers.
-// What bounds it is the vector ALU (three quarters busy, the matrix cores 39 percent): the gather alone takes 140 us of 203
+// What bounds it is the vector ALU (at 4 clocks an instruction 81 percent of its time at 128 -> 128 and 1M points, 83 at 512 -> 512
+// and 109k; the matrix cores 41 and 42, no bank conflicts): before the present strides the gather alone took 140 us of 203
 // at 128 -> 128 and 200k points, the contraction alone 143.  A block of 128 output channels would gather half as often, but
 // its accumulators and their running totals do not fit the registers.  Against lean waves on 32-point tiles with
 // run-time strides, us: 256 -> 256 100k points 411 -> 393, K = 9 33k points 200 -> 170; 512 -> 512 33k points K = 9

