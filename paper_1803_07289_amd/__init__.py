@@ -10,6 +10,7 @@ call raises.
 """
 import ctypes
 import os
+import threading
 
 import torch
 
@@ -135,15 +136,41 @@ def workspace_bytes(op, B, N, K, Din, Dout, layout=BCN):
     return int(lib().flexconv_workspace_bytes(op, B, N, K, Din, Dout, _layout(layout)))
 
 
+_kept = threading.local()        # .scratch: {(device index, stream): tensor}, oldest use first
+_KEPT_STREAMS = 4
+
+
+def _capturing():
+    return torch.cuda.is_current_stream_capturing()
+
+
 def _workspace(device, nbytes):
-    """Scratch memory of one call's own (256-byte aligned by the allocator).  Nothing is kept here between calls: calls on
-    several streams or threads, and graphs that hold the address, share no scratch; the caching allocator hands a block on in
-    the order of its stream."""
-    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+    """Scratch memory for one call (256-byte aligned by the allocator).  A thread keeps one tensor, of the largest size so far,
+    for each of the streams that it last used, so that calls share scratch only where the stream orders them; the allocator hands
+    a tensor that is replaced on in its stream's order.  A captured call has scratch of its own, which belongs to its graph."""
+    nbytes = max(nbytes, 256)
+    if _capturing():
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    kept = _kept.__dict__.setdefault("scratch", {})
+    key = (device.index, _stream())
+    ws = kept.pop(key, None)
+    if ws is None or ws.numel() < nbytes:
+        ws = None                                    # (given back before the larger one is asked for)
+        if len(kept) >= _KEPT_STREAMS:
+            del kept[next(iter(kept))]
+        try:
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            if not kept:
+                raise
+            kept.clear()
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    kept[key] = ws
+    return ws
 
 
 def _ws_arg(workspace, device, need):
-    """(tensor, byte count handed to the library): a caller's workspace with its own size, else one of the call's own
+    """(tensor, byte count handed to the library): a caller's workspace with its own size, else the binding's
     with exactly the size the library asked for, so that the library's own size check sees `need`."""
     if workspace is not None:
         if not workspace.is_cuda or workspace.dtype != torch.uint8 or not workspace.is_contiguous():

@@ -353,19 +353,41 @@ def test_in_edge_lists_past_the_buckets(L):
     assert small >= 6 * 800_000 and none < 5 * 100_000
 
 
-def test_the_bindings_scratch_is_each_calls_own():
-    # two calls under way at once (two streams, two threads) never share scratch; nothing is kept when they are done
+def test_the_bindings_scratch_is_shared_along_a_stream_only(monkeypatch):
+    # calls that may be under way at once (two streams, two threads, a captured call) never share scratch
+    import threading
     import torch
     import paper_1803_07289_amd as fx
-    a = fx._ws_arg(None, torch.device("cpu"), 4096)
-    b = fx._ws_arg(None, torch.device("cpu"), 4096)
-    assert a[1] == b[1] == 4096 and a[0].numel() == 4096
-    assert a[0].data_ptr() != b[0].data_ptr()
-    assert fx._ws_arg(None, torch.device("cpu"), 0)[1] == 256
+    cpu, now = torch.device("cpu"), {"stream": 1, "capturing": False}
+    monkeypatch.setattr(fx, "_stream", lambda: now["stream"])
+    monkeypatch.setattr(fx, "_capturing", lambda: now["capturing"])
+    monkeypatch.setattr(fx, "_kept", threading.local())
+    take = lambda n=4096: fx._ws_arg(None, cpu, n)
+    first, have = take()
+    assert have == first.numel() == 4096 and take(0)[1] == 256
+    assert take(1000)[0] is first and take(1000)[1] == 1000
+    others = [first]
+    now["stream"] = 2
+    others.append(take()[0])
+    t = threading.Thread(target=lambda: others.append(take()[0]))
+    t.start()
+    t.join()
+    now["capturing"] = True
+    others += [take()[0], take()[0]]
+    now["capturing"] = False
+    assert len({x.data_ptr() for x in others}) == len(others)
+    assert take()[0] is others[1]                    # what was captured is not kept
+    now["stream"] = 1
+    assert take(5000)[0].numel() == 5000             # a larger one takes the first one's place
+    for s in range(3, 20):                           # many streams: the last few
+        now["stream"] = s
+        take()
+    assert len(fx._kept.scratch) == fx._KEPT_STREAMS and list(fx._kept.scratch)[-1] == (None, 19)
 
 
 @pytest.mark.parametrize("Din,Dout", [(64, 64), (9, 64), (64, 13)])
 def test_a_device_without_room_for_records_takes_the_call_in_the_smallest_workspace(L, monkeypatch, Din, Dout):
+    import threading
     import torch
     import paper_1803_07289_amd as fx
     whole, asked = fx._workspace, []
@@ -377,6 +399,9 @@ def test_a_device_without_room_for_records_takes_the_call_in_the_smallest_worksp
         return whole(device, nbytes)
 
     monkeypatch.setattr(fx, "_workspace", full)
+    monkeypatch.setattr(fx, "_stream", lambda: 1)
+    monkeypatch.setattr(fx, "_capturing", lambda: False)
+    monkeypatch.setattr(fx, "_kept", threading.local())
     best_is_more = False
     for op in (fx.OP_CONV_FWD, fx.OP_CONV_BWD):
         sizes = (op, 1, 1 << 20, 8, Din, Dout, fx.BNC)
