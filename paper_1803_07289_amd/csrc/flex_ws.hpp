@@ -550,6 +550,12 @@ __device__ __forceinline__ v4f outer_slot(float dp, float f, v4f acc, int slot)
                        : __builtin_amdgcn_mfma_f32_4x4x1f32(dp, f, acc, 2, 3, 0);
 }
 
+// x + add with the bits that mask leaves of x
+__device__ __forceinline__ int entry_component(float x, int mask, float add)
+{
+    return __float_as_int(__int_as_float(__float_as_int(x) & mask) + add);
+}
+
 // ---------------------------------------------------------------------------
 // Lean producer for the fixed-K neighbour tensor (K a multiple of 8, every per-cloud byte
 // offset below 2^32).  Entry layout: four lanes an entry (a slot of a point), which load its id
@@ -600,9 +606,11 @@ struct LeanProducer {
     // four points, ROW16: e = 4 * point + slot, so that an entry stands in its point's lane group, else e = 4 * slot + point
     int e_g, e_k;                // point and slot (within half 0) of this lane's entry
     unsigned e_col;              // byte offset of the position component to read: x, y, z (lane 3 reads z, value unused)
-    // dp component = bits of pn - pc & e_and | e_or: component lane 3 is the constant 1 wherever the points lie (by a select, whose
-    // mask takes registers the loop misses, 32 -> 32, 300k points, K = 8, all gradients 140.7 us, so 138.6)
-    int e_and, e_or;
+    // dp component = (pn - pc, its bits masked) + e_add: component lane 3 is the constant 1 wherever the points lie.  (By a select,
+    // which holds a mask pair through the loop, all gradients of 32 -> 32, 300k points, K = 8, took 140.7 us, so 138.6; with the constant or'ed
+    // in, K = 9, 64 -> 64, channel-major, 900k points, forward 311, so 308.)
+    int e_and;
+    float e_add;
     float *s_dp = nullptr;       // this wave's LDS array of 32 entries x (dx, dy, dz, w), entry = 4 * slot + point
     int dp_rd = 0;               // float offset of this lane's entry of slot 0 in it
     __device__ __forceinline__ void set_dp_stage(float *p) { s_dp = p; dp_rd = 4 * (grp % G::PW); }
@@ -621,8 +629,8 @@ struct LeanProducer {
         const int c = lane & 3;
         e_col = (c < 3 ? c : 2) * pos_.col;
         e_and = c < 3 ? ~0 : 0;
-        e_or = c < 3 ? 0 : __float_as_int(1.f);
-        asm("" : "+v"(e_and), "+v"(e_or));           // (the compiler would see a select in them)
+        e_add = c < 3 ? 0.f : 1.f;
+        asm("" : "+v"(e_and));                        // (the compiler would see a select in it)
         sched = sc; tiles_per_cloud = tiles_per_cloud_;
         count = (sc.first < sc.end) ? (sc.end - sc.first + sc.step - 1) / sc.step : 0;
     }
@@ -754,8 +762,8 @@ struct LeanProducer {
         for (int m = 0; m < total; ++m) {
             // position differences of batch m, entry layout -> this lane's component per slot
             int dpe[2];
-            dpe[0] = (__float_as_int(pn[0] - pc) & e_and) | e_or;
-            dpe[1] = (__float_as_int(pn[1] - pc) & e_and) | e_or;
+            dpe[0] = entry_component(pn[0] - pc, e_and, e_add);
+            dpe[1] = entry_component(pn[1] - pc, e_and, e_add);
             if constexpr (TAIL) {                    // slots past K weigh nothing
                 if (k0_cur + e_k >= K) dpe[0] = 0;
                 if (k0_cur + e_k + 4 >= K) dpe[1] = 0;
@@ -902,7 +910,8 @@ struct LeanCsrProducer {
     int perm_id, perm_dp;
     int e_g, e_k;
     unsigned e_col;
-    int e_and, e_or;
+    int e_and;
+    float e_add;
     float *s_dp = nullptr;       // this wave's LDS array of 32 entries x (dx, dy, dz, w), entry = 4 * slot + point
     int dp_rd = 0;               // float offset of this lane's entry of slot 0 in it
     __device__ __forceinline__ void set_dp_stage(float *p) { s_dp = p; dp_rd = 4 * (grp % G::PW); }
@@ -924,8 +933,8 @@ struct LeanCsrProducer {
         const int c = lane & 3;
         e_col = (c < 3 ? c : 2) * pos_.col;
         e_and = c < 3 ? ~0 : 0;
-        e_or = c < 3 ? 0 : __float_as_int(1.f);
-        asm("" : "+v"(e_and), "+v"(e_or));           // (the compiler would see a select in them)
+        e_add = c < 3 ? 0.f : 1.f;
+        asm("" : "+v"(e_and));                        // (the compiler would see a select in it)
         sched = sc; tiles_per_cloud = tiles_per_cloud_;
         count = (sc.first < sc.end) ? (sc.end - sc.first + sc.step - 1) / sc.step : 0;
     }
@@ -1067,8 +1076,8 @@ struct LeanCsrProducer {
             dpe[0] = d.valid0 ? __float_as_int(1.f) : 0;
             dpe[1] = d.valid1 ? __float_as_int(1.f) : 0;
         } else {
-            dpe[0] = d.valid0 ? (__float_as_int(pc - pn[0]) & e_and) | e_or : 0;
-            dpe[1] = d.valid1 ? (__float_as_int(pc - pn[1]) & e_and) | e_or : 0;
+            dpe[0] = d.valid0 ? entry_component(pc - pn[0], e_and, e_add) : 0;
+            dpe[1] = d.valid1 ? entry_component(pc - pn[1], e_and, e_add) : 0;
         }
     }
 
