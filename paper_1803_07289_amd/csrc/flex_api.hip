@@ -35,14 +35,13 @@ hipError_t launch_bwd_fused_late_64_64(const float *g_rows, const float *own_row
                                        int N, int K, hipStream_t s);
 
 // parameter gradients of layers with both widths multiples of 128, block by block (same file, same shape)
-int split_wide_gt_chunks(int B, int N, int blocks);
 hipError_t launch_reduce_partials(const float *partials, int n_wg, int DIP, int DOP, int n_blocks, int n_ho, int Din,
                                   int Dout, float *grad_theta, float *grad_bias, hipStream_t s);
 
 // the 64-point tile kernels over fixed-K neighbour tensors / in-edge lists
 hipError_t launch_tile_0(const TileArgs &a, int outw, int grid, hipStream_t s);
 hipError_t launch_tile_1(const TileArgs &a, int outw, int grid, hipStream_t s);
-hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int gst, int n_hi, int n_ho, float *partials,
+hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int gst, int n_hi, int n_ho, int oc, float *partials,
                                   hipStream_t s);
 // rows of at most 16 channels, one point per lane (flex_narrow.hip)
 hipError_t launch_narrow_0(const TileArgs &a, int grid, hipStream_t s);
@@ -161,12 +160,31 @@ static bool wide_ok(int64_t N, int K, int Din, int Dout)
 // Packed parameters of a wide layer, forward, as 64 x 128 blocks
 static size_t wide_packed_bytes(int Din, int Dout) { return (size_t)(Din / 64) * (Dout / 128) * theta_f16_bytes(64, 128); }
 
-// Parameter gradients of a wide layer: (Din/64) x (Dout/64) independent blocks of [4*64 x 64], two launches
-// (partial sums per block and workgroup, then their reduction in double).
+// Parameter gradients of a wide layer: (Din/64) x (Dout/oc) independent blocks of [4*64 x oc], `chunks` workgroups each,
+// two launches (partial sums per block and workgroup, then their reduction in double).
+// Blocks of 128 output channels gather half as often, ones of 64 make twice the workgroups for a cloud of few tiles.  Costs in
+// tenths of a microsecond, as measured: a tile 3.2 us for 64 channels and 5.0 for 128, whose larger partials take 3 more.
+// us, 64 and 128: 128 -> 128, 2k points 15.8 and 17.9, 8k 23.5 and 24.7, 16k 29.8 and 29.6, 60k 66.6 and 60.9, 1M 970 and 782;
+// 256 -> 256, 2k 24.6 and 28.5, 12k 59.5 and 52.6; 512 -> 512, 1k 30.6 and 34.6, 2k 43.2 and 43.1, 8k 126 and 109, 109k 1620 and 1270.
+struct WideGradPlan { int oc, blocks, chunks; };
+static WideGradPlan wide_grad_plan(int64_t B, int64_t N, int Din, int Dout)
+{
+    const int64_t tiles = B * cdiv64(N, 64), cus = device_cu_count();
+    WideGradPlan best{};
+    int64_t least = 0;
+    for (const int oc : {64, 128}) {
+        WideGradPlan p{oc, (Din / 64) * (Dout / oc), 1};
+        p.chunks = (int)std::max<int64_t>(1, std::min(tiles, cus / p.blocks));
+        const int64_t rounds = cdiv64((int64_t)p.blocks * p.chunks, cus) * cdiv64(tiles, p.chunks);
+        const int64_t cost = oc == 64 ? 32 * rounds : 50 * rounds + 30;
+        if (oc == 64 || cost < least) { least = cost; best = p; }
+    }
+    return best;
+}
 static size_t wide_partial_bytes(int B, int N, int Din, int Dout)
 {
-    const int blocks = (Din / 64) * (Dout / 64);
-    return align256(sizeof(float) * (size_t)blocks * split_wide_gt_chunks(B, N, blocks) * 4 * 64 * 64);
+    const WideGradPlan p = wide_grad_plan(B, N, Din, Dout);
+    return align256(sizeof(float) * (size_t)p.blocks * p.chunks * 4 * 64 * p.oc);
 }
 
 // (Dki, Dko): the widths of the rows, which may be padded; (Din, Dout): the parameters'.
@@ -174,7 +192,8 @@ static hipError_t wide_grad_theta(const float *rows, const float *pos, const int
                                   float *partials, float *grad_theta, float *grad_bias, int B, int N, int K, int Dki,
                                   int Dko, int Din, int Dout, hipStream_t s)
 {
-    const int n_hi = Dki / 64, n_ho = Dko / 64, chunks = split_wide_gt_chunks(B, N, n_hi * n_ho);
+    const WideGradPlan p = wide_grad_plan(B, N, Dki, Dko);
+    const int n_hi = Dki / 64, n_ho = Dko / p.oc, chunks = p.chunks;
     TileArgs a{};
     a.rows = rows; a.pos = pos; a.nbr = nbr;
     a.rs = Dki; a.w_in = Dki;
@@ -182,9 +201,9 @@ static hipError_t wide_grad_theta(const float *rows, const float *pos, const int
     const int64_t total = (int64_t)B * a.tpc;
     if (total > 0x7fffffff || (int64_t)n_hi * n_ho * chunks > 0x7fffffff) return hipErrorInvalidValue;
     a.total = (int)total;
-    hipError_t e = launch_tile_grad_theta(a, g_rows, Dko, n_hi, n_ho, partials, s);
+    hipError_t e = launch_tile_grad_theta(a, g_rows, Dko, n_hi, n_ho, p.oc, partials, s);
     if (e != hipSuccess) return e;
-    return launch_reduce_partials(partials, chunks, 64, 64, n_hi * n_ho, n_ho, Din, Dout, grad_theta, grad_bias, s);
+    return launch_reduce_partials(partials, chunks, 64, p.oc, p.blocks, n_ho, Din, Dout, grad_theta, grad_bias, s);
 }
 
 // Workspace bytes of the packed parameters in either format (rows padded to 4, columns to 16).

@@ -78,24 +78,26 @@ __device__ __forceinline__ void reduce_store(const ReduceArgs &p, int block, int
     (j < 3 ? grad_theta + (int64_t)j * p.Din * p.Dout : grad_bias)[(int64_t)c * p.Dout + o] = (float)v;
 }
 
-// Returns the sum that thread t < 64 stored (element 64 * segment + t).
+// Returns the sum that thread t < 64 stored (element 64 * segment + t).  GROUPS: partials at a time, 16 threads each.
+template <int GROUPS>
 __device__ __forceinline__ double reduce_segment(const float *__restrict__ partials, const ReduceArgs &p, int block,
                                                  int segment, float *__restrict__ grad_theta,
                                                  float *__restrict__ grad_bias, double (*s_sum)[64])
 {
+    constexpr int UN = 4;                    // rounds requested together
     const int64_t E = (int64_t)4 * p.DIP * p.DOP;
     const int tid = threadIdx.x, q = tid & 15, grp = tid >> 4, wave = tid >> 6;
     const float *src = partials + (int64_t)block * p.n_wg * E + 64 * (int64_t)segment + 4 * q;
     double sum[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int g0 = grp; g0 < p.n_wg; g0 += 256) {
-        v4f x[4];
+    for (int g0 = grp; g0 < p.n_wg; g0 += UN * GROUPS) {
+        v4f x[UN];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int g = g0 + 64 * u;
+        for (int u = 0; u < UN; ++u) {
+            const int g = g0 + GROUPS * u;
             x[u] = g < p.n_wg ? *reinterpret_cast<const v4f *>(src + g * E) : v4f{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < UN; ++u)
 #pragma unroll
             for (int i = 0; i < 4; ++i) sum[i] += (double)x[u][i];
     }
@@ -109,7 +111,7 @@ __device__ __forceinline__ double reduce_segment(const float *__restrict__ parti
     if (tid >= 64) return 0.0;
     double v = 0.0;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) v += s_sum[w][tid];
+    for (int w = 0; w < GROUPS / 4; ++w) v += s_sum[w][tid];
     reduce_store(p, block, 64 * segment + tid, v, grad_theta, grad_bias);
     return v;
 }
@@ -118,6 +120,10 @@ __device__ __forceinline__ double reduce_segment(const float *__restrict__ parti
 // four elements reads them all.  512 x 512 channels, four partials per block: 9 us (61 in the form above, most of whose
 // threads would have nothing to read).
 constexpr int REDUCE_FEW = 16;
+// Up to here 16 partials at a time, workgroups of 256 threads: most of 1024 would have nothing to read.  Parameter gradients, us, 64
+// partials at a time and 16: 256 -> 256, 4k points (32 partials) 43.3 and 32.5, 2k (32) 39.3 and 28.5; 128 -> 128, 4k (63) 22.2 and
+// 20.0, 12k (64) 28.8 and 27.0, 30k (128) 41.5 and 40.9, 60k (128) 60.8 and 60.9.
+constexpr int REDUCE_SOME = 128;
 __global__ __launch_bounds__(256) void reduce_partials_few_kernel(const float *__restrict__ partials, const ReduceArgs p,
                                                                   float *__restrict__ grad_theta,
                                                                   float *__restrict__ grad_bias)
@@ -141,12 +147,13 @@ __global__ __launch_bounds__(256) void reduce_partials_few_kernel(const float *_
 }
 
 // grid: (64-element segments of a partial, blocks of the result)
-__global__ __launch_bounds__(1024) void reduce_partials_kernel(const float *__restrict__ partials, const ReduceArgs p,
-                                                               float *__restrict__ grad_theta,
-                                                               float *__restrict__ grad_bias)
+template <int GROUPS>
+__global__ __launch_bounds__(16 * GROUPS) void reduce_partials_kernel(const float *__restrict__ partials, const ReduceArgs p,
+                                                                      float *__restrict__ grad_theta,
+                                                                      float *__restrict__ grad_bias)
 {
-    __shared__ double s_sum[16][64];
-    reduce_segment(partials, p, blockIdx.y, blockIdx.x, grad_theta, grad_bias, s_sum);
+    __shared__ double s_sum[GROUPS / 4][64];
+    reduce_segment<GROUPS>(partials, p, blockIdx.y, blockIdx.x, grad_theta, grad_bias, s_sum);
 }
 
 // The same, run only if the one-pass backward handed over (*flag != 0): the second reduction behind its fall-back.
@@ -157,7 +164,7 @@ __global__ __launch_bounds__(1024) void reduce_partials_if_kernel(const int *__r
 {
     __shared__ double s_sum[16][64];
     if (*flag == 0) return;
-    reduce_segment(partials, p, blockIdx.y, blockIdx.x, grad_theta, grad_bias, s_sum);
+    reduce_segment<64>(partials, p, blockIdx.y, blockIdx.x, grad_theta, grad_bias, s_sum);
 }
 
 // n_blocks blocks of DIP x DOP channels, n_ho per row of blocks; block b's partials start at partials[b * n_wg].
@@ -168,8 +175,11 @@ hipError_t launch_reduce_partials(const float *partials, int n_wg, int DIP, int 
     if (n_wg <= REDUCE_FEW)
         hipLaunchKernelGGL(reduce_partials_few_kernel, dim3((4 * DIP * DOP + 1023) / 1024, (unsigned)n_blocks), dim3(256), 0,
                            s, partials, a, grad_theta, grad_bias);
+    else if (n_wg <= REDUCE_SOME)
+        hipLaunchKernelGGL(reduce_partials_kernel<16>, dim3(4 * DIP * DOP / 64, (unsigned)n_blocks), dim3(256), 0, s, partials,
+                           a, grad_theta, grad_bias);
     else
-        hipLaunchKernelGGL(reduce_partials_kernel, dim3(4 * DIP * DOP / 64, (unsigned)n_blocks), dim3(1024), 0, s, partials,
+        hipLaunchKernelGGL(reduce_partials_kernel<64>, dim3(4 * DIP * DOP / 64, (unsigned)n_blocks), dim3(1024), 0, s, partials,
                            a, grad_theta, grad_bias);
     return hipGetLastError();
 }
@@ -192,7 +202,7 @@ __global__ __launch_bounds__(1024) void reduce_partials_fused_kernel(const float
 {
     __shared__ double s_sum[16][64];
     if (blockIdx.x + 1 < gridDim.x) {
-        double v = reduce_segment(partials, p, 0, blockIdx.x, grad_theta, grad_bias, s_sum);    // row kd = blockIdx.x
+        double v = reduce_segment<64>(partials, p, 0, blockIdx.x, grad_theta, grad_bias, s_sum);    // row kd = blockIdx.x
         if (threadIdx.x < 64) {
             v = (double)(float)v;
             v *= v;

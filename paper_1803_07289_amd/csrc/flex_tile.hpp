@@ -157,7 +157,8 @@ struct StepWalk {
 __device__ __forceinline__ int tile_lane_channel(const TileArgs &a, int ib) { return min(ib * 64 + 4 * ((int)threadIdx.x & 15), a.w_in - 4); }
 
 // What a gathering wave does: the sums of its eight points (from `first` of every tile) over input blocks ib0 .. ib0 + n_in - 1,
-// acc[pass][channel][component]; park(acc, ib, point) takes them when a (tile, input block) is complete.
+// acc[pass][channel][component]; park(acc, ib, point) takes them when a (tile, input block) is complete, HALVES: park(acc[pass], pass)
+// those of the first four points and of the second four as each is.
 // Eight rows are in flight at all times.
 // How a slot's row is weighed with its (dx, dy, dz, 1).  MX: by outer products on the matrix cores (outer_slot): an entry is
 // then needed once per wave, in the layout lane = 16 * point + 4 * slot + component, and its row's offset, the fourth
@@ -166,7 +167,7 @@ __device__ __forceinline__ int tile_lane_channel(const TileArgs &a, int ib) { re
 // multiply-adds that four of them replace hold the vector ALU for 40, the reads LDS for as long.  512 -> 512, 109k points, us: forward 796
 // by multiply-adds, 778 by outer products, feature gradient 852 and 836; the parameter gradient, whose contraction
 // already fills the matrix cores twice as far, 1681 and 1728.
-template <bool CSR, bool MX, class Park>
+template <bool CSR, bool MX, bool HALVES, class Park>
 __device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedule &sc, int tiles, int first, int ib0,
                                              float (*ent)[64][4], Park &&park)
 {
@@ -312,11 +313,21 @@ __device__ __forceinline__ void gather_steps(const TileArgs &a, const TileSchedu
                 if constexpr (OFF_AHEAD && !MX) off[u] = __float_as_uint(ent[buf ^ 1][8 * u + 4 * p + grp][3]);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if constexpr (HALVES) {
+                if (d0.last) {
+                    park(acc[p], p);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[p][v] = v4f{0.f, 0.f, 0.f, 0.f};
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         if (d0.last) {
-            park(acc, d0.ib, pt0);
+            if constexpr (!HALVES) {
+                park(acc, d0.ib, pt0);
+                clear();
+            }
             ++k;
-            clear();
         }
         if constexpr (MX) e0 = e1;
         d0 = d1; d1 = d2; d2 = d3;
@@ -357,7 +368,7 @@ void tile_conv_kernel(const TileArgs a)
         const int t = lane % P::LPR, grp = lane / P::LPR, first = 8 * wave;
         const bool ragged = a.w_in % IC != 0;
         int m_buf = 0;                                  // tile buffer of the tile being gathered
-        gather_steps<CSR, true>(a, sc, tiles, first, 0, s_ent[wave], [&](v4f (&acc)[2][4], int step_ib, int point) __attribute__((always_inline)) {
+        gather_steps<CSR, true, false>(a, sc, tiles, first, 0, s_ent[wave], [&](v4f (&acc)[2][4], int step_ib, int point) __attribute__((always_inline)) {
             // ---- park ----
             const int ib = MULTI ? step_ib : 0;
 #pragma unroll
@@ -552,11 +563,8 @@ void tile_conv_kernel(const TileArgs a)
 // upstream gradient.  One tile buffer (100 KB of LDS): the gathering waves sum the next tile in registers while this one is
 // contracted, and park it between two barriers.
 // What bounds it is the vector ALU (at 4 clocks an instruction 81 percent of its time at 128 -> 128 and 1M points, 83 at 512 -> 512
-// and 109k; the matrix cores 41 and 42, no bank conflicts): before the present strides the gather alone took 140 us of 203
-// at 128 -> 128 and 200k points, the contraction alone 143.  A block of 128 output channels would gather half as often, but
-// its accumulators and their running totals do not fit the registers.  Against lean waves on 32-point tiles with
-// run-time strides, us: 256 -> 256 100k points 411 -> 393, K = 9 33k points 200 -> 170; 512 -> 512 33k points K = 9
-// 776 -> 656.
+// and 109k; the matrix cores 41 and 42, no bank conflicts).  Clouds of more than a few tiles a workgroup run tile_grad_theta128_kernel
+// below; the rule and both sides' times are beside wide_grad_plan (flex_api.hip).
 // ---------------------------------------------------------------------------
 static __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, int gst, int n_ho, float *__restrict__ partials)
@@ -576,7 +584,7 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
         // ---- gather ----
         if (tiles == 0) return;
         const int t = lane & 15, grp = lane >> 4, first = 8 * wave;
-        gather_steps<false, false>(a, sc, tiles, first, hi, s_ent[wave], [&](v4f (&acc)[2][4], int, int) __attribute__((always_inline)) {
+        gather_steps<false, false, false>(a, sc, tiles, first, hi, s_ent[wave], [&](v4f (&acc)[2][4], int, int) __attribute__((always_inline)) {
             __syncthreads();               // the tile before is contracted
 #pragma unroll
             for (int ps = 0; ps < 2; ++ps) {
@@ -691,6 +699,216 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
     }
 
     flush(tiles > FLUSH);                  // a workgroup without tiles still writes its (zero) partial
+}
+
+// ---------------------------------------------------------------------------
+// The same for blocks of 128 output channels: rows are gathered and weighed half as often (at 64 channels that is what the vector ALU
+// does most of the time).  The 256 x 128 sums fill half of a contracting wave's registers, and the tiles all of LDS: 160 KB.
+//
+// A tile goes through in halves of 32 points -- the first four of every gathering wave's eight, then the others --, one depth
+// step of the matrix op each, in two buffers: a half is parked while the one before it is contracted, and one barrier hands
+// both over.  (Whole tiles in one buffer, parked between two barriers: 855 us at 128 -> 128 and 1M points where halves take 780,
+// and 759 with the contracting waves' priority raised; blocks of 64 channels in halves lose, 1005 -> 1050.)
+// Sums and their rounding are those of the kernel above, and the chains half as long: 2-norm error 128 -> 128 at 30k points 1.2e-7 ->
+// 1.1e-7, at 200k 2.0e-7 -> 1.6e-7, at 1M 2.27e-7 -> 2.25e-7.
+// What bounds it: the matrix cores 56 percent of the time, the vector ALU as much, LDS 27 (counters at 128 -> 128, 1M points); the
+// contraction alone would take 520 us of the 759, the gathering alone 415.  us, 64 channels a block -> 128: 128 -> 128, 1M points
+// 960 -> 759; 256 -> 256, 250k 918 -> 760; 512 -> 512, 109k 1600 -> 1240; K = 16: 1290 -> 940, 1246 -> 905, 2130 -> 1540.
+// ---------------------------------------------------------------------------
+
+// Three-piece bf16 tiles whose rows are whole multiples of 256 bytes: the byte address inside a row XORed with bf3x_swizzle(row).
+// A turn of the transposing reads (32 lanes, 64 banks) takes 32 bytes each of rows 0-3 and 8-11 (mod 16), eight places that the
+// three bits part; a turn of the 8-byte stores takes 128 bytes each of rows 2i and 2i + 1, which bit 7 parts.
+__device__ __forceinline__ int bf3x_swizzle(int row) { return ((row & 1) << 7) | ((row & 2) << 4) | ((row & 8) << 3); }
+// byte address v + K inside a row; K: a constant, so that all but its bit 7 is an offset in the instruction.
+// v below 128, or K a multiple of 256.
+__device__ __forceinline__ int bf3x_at(int v, int K, int swizzle) { return (v ^ swizzle ^ (K & 128)) + (K & ~128); }
+
+static __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void tile_grad_theta128_kernel(const TileArgs a, const float *__restrict__ g_rows, int gst, int n_ho, float *__restrict__ partials)
+{
+    constexpr int IC = 64, KD = 4 * IC, OC = 128, T = 64, H = 32;
+    constexpr int AS = 6 * KD, GS = 6 * OC;
+    static_assert(AS % 256 == 0 && GS % 256 == 0, "rows of whole bank turns");
+    __shared__ __attribute__((aligned(16))) char s_A[2][H * AS];
+    __shared__ __attribute__((aligned(16))) char s_G[2][H * GS];
+    __shared__ __attribute__((aligned(16))) float s_ent[8][2][64][4];
+
+    const int p = blockIdx.x / a.chunks, hi = p / n_ho, ho = p - hi * n_ho;
+    const TileSchedule sc(a.total, (int)blockIdx.x - p * a.chunks, a.chunks);
+    const int tiles = sc.first < sc.end ? (sc.end - sc.first + sc.step - 1) / sc.step : 0;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+    if (wave < 8) {
+        // ---- gather ----
+        if (tiles == 0) return;
+        const int lane = threadIdx.x & 63, t = lane & 15, grp = lane >> 4;
+        const int row = 4 * wave + grp, swizzle = bf3x_swizzle(row);
+        gather_steps<false, false, true>(a, sc, tiles, 8 * wave, hi, s_ent[wave], [&](const v4f (&acc)[4], int half) __attribute__((always_inline)) {
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                unsigned h0, m0, l0, h1, m1, l1;
+                split_bf3(acc[0][jj], acc[1][jj], h0, m0, l0);
+                split_bf3(acc[2][jj], acc[3][jj], h1, m1, l1);
+                char *d = s_A[half] + row * AS + bf3x_at(8 * t, 2 * jj * IC, swizzle);
+                *reinterpret_cast<uint2 *>(d) = make_uint2(h0, h1);
+                *reinterpret_cast<uint2 *>(d + 2 * KD) = make_uint2(m0, m1);
+                *reinterpret_cast<uint2 *>(d + 4 * KD) = make_uint2(l0, l1);
+            }
+            __syncthreads();               // this half is complete, the one before it is contracted
+        });
+        return;
+    }
+
+    // ---- contract: MBW 16-row blocks x two 16-column blocks of the partial per wave ----
+    constexpr int NBW = 2, WN = OC / (16 * NBW), WM = 8 / WN, MBW = KD / 16 / WM, FLUSH = 64;
+    // a wave's row blocks: half of them in each 256 bytes of a row
+    constexpr int MBH = MBW / 2;
+    const int cw = wave - 8, wn = cw % WN, wm = cw / WN;
+    __builtin_amdgcn_s_setprio(3);         // the matrix cores' chain is the longer one: 780 -> 759 us at 128 -> 128, 1M points
+    v4f tot[MBW][NBW];                     // the sums since the last move to the partial
+
+    float *dst = partials + (int64_t)blockIdx.x * KD * OC;
+    // What a lane needs of its number is formed where it is used, not kept through the loop: the registers are full.
+    auto lane_now = [&]() {
+        int l;
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+        return l;
+    };
+    auto flush = [&](bool add) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < MBW; ++c) {
+            const int l = lane_now();
+            const unsigned at = 4u * (unsigned)((16 * (MBH * wm + c % MBH + 8 * (c / MBH)) + 4 * (l >> 4)) * OC + 32 * wn + (l & 15));
+            auto place = [&](int n, int i) { return reinterpret_cast<float *>(reinterpret_cast<char *>(dst) + (at + 4u * (unsigned)(i * OC + 16 * n))); };
+            if (add) {
+                v4f old[NBW];
+#pragma unroll
+                for (int n = 0; n < NBW; ++n)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) old[n][i] = *place(n, i);
+#pragma unroll
+                for (int n = 0; n < NBW; ++n) tot[c][n] = old[n] + tot[c][n];
+            }
+#pragma unroll
+            for (int n = 0; n < NBW; ++n)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *place(n, i) = tot[c][n][i];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    // Upstream gradient of a half: row r of its tile is point 8 * (r / 4) + 4 * half + r % 4 of the 64, as the gathering
+    // waves have it; CH four-float chunks per thread, ROWS rows apart.
+    constexpr int CPR = OC / 4, ROWS = 512 / CPR, CH = H / ROWS;
+    TileWalk tw(sc, a.tpc);
+    v4f gv[CH];
+    auto load_g = [&](int half) __attribute__((always_inline)) {
+        const int ctid = 64 * cw + lane_now(), r = ctid / CPR;
+        const auto rows = row_buffer(g_rows + (int64_t)tw.b * a.N * gst, 4u * (unsigned)a.N * (unsigned)gst);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            // the row behind the cloud's last reads as zeros
+            const int l = min(tw.tic * T + 8 * ((r + ROWS * c) >> 2) + 4 * half + (r & 3), a.N);
+            gv[c] = load_row4(rows, 4u * ((unsigned)l * (unsigned)gst + (unsigned)(OC * ho + 4 * (ctid % CPR))));
+        }
+    };
+    auto store_g = [&](int half) __attribute__((always_inline)) {
+        const int ctid = 64 * cw + lane_now(), r = ctid / CPR, v = 8 * (ctid % CPR);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            char *row = s_G[half] + (r + ROWS * c) * GS;
+            const int swizzle = bf3x_swizzle(r + ROWS * c);
+            unsigned h0, m0, l0, h1, m1, l1;
+            const v4f g = half == 0 ? gv[c] : -gv[c];              // (the second 32 points: see above)
+            split_bf3(g[0], g[1], h0, m0, l0);
+            split_bf3(g[2], g[3], h1, m1, l1);
+            *reinterpret_cast<uint2 *>(row + bf3x_at(v, 0, swizzle)) = make_uint2(h0, h1);
+            *reinterpret_cast<uint2 *>(row + bf3x_at(v, 2 * OC, swizzle)) = make_uint2(m0, m1);
+            *reinterpret_cast<uint2 *>(row + bf3x_at(v, 4 * OC, swizzle)) = make_uint2(l0, l1);
+        }
+    };
+    // A row block's three pieces are multiplied one after the other, small terms first, and the next block's take the
+    // registers as they fall free.
+    auto contract = [&](int half) __attribute__((always_inline)) {
+        unsigned a_at[MBH], g_at[NBW];         // byte places of the wave's blocks
+        const int l = lane_now(), r = 8 * (l >> 4) + ((l >> 2) & 3), col = 8 * (l & 3);
+#pragma unroll
+        for (int c = 0; c < MBH; ++c) a_at[c] = (unsigned)(r * AS + bf3x_at(32 * (MBH * wm + c) + col, 0, bf3x_swizzle(r)));
+#pragma unroll
+        for (int n = 0; n < NBW; ++n) g_at[n] = (unsigned)(r * GS + bf3x_at(64 * wn + 32 * n + col, 0, bf3x_swizzle(r)));
+        auto frag_a = [&](int c, int piece) __attribute__((always_inline)) {
+            return read_tr_at(s_A[half] + a_at[c % MBH] + (256 * (c / MBH) + 2 * KD * piece), AS);
+        };
+        auto frag_g = [&](int n, int piece) __attribute__((always_inline)) {
+            return read_tr_at(s_G[half] + g_at[n] + 2 * OC * piece, GS);
+        };
+        bf8 aL = frag_a(0, 2), aM = frag_a(0, 1), aH = frag_a(0, 0), gH[NBW], gM[NBW], gL[NBW];
+#pragma unroll
+        for (int n = 0; n < NBW; ++n) {
+            gH[n] = frag_g(n, 0);
+            gM[n] = frag_g(n, 1);
+            gL[n] = frag_g(n, 2);
+        }
+#pragma unroll
+        for (int c = 0; c < MBW; ++c) {
+            v4f acc[NBW];
+#pragma unroll
+            for (int n = 0; n < NBW; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
+            __builtin_amdgcn_sched_barrier(0);
+#define FLEX_BF_MFMA(X, Y)                                                                         \
+    _Pragma("unroll") for (int n = 0; n < NBW; ++n)                                               \
+        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(X, Y[n], acc[n], 0, 0, 0)
+            FLEX_BF_MFMA(aL, gH);
+            if (c + 1 < MBW) aL = frag_a(c + 1, 2);
+            __builtin_amdgcn_sched_barrier(0);
+            FLEX_BF_MFMA(aM, gM);
+            FLEX_BF_MFMA(aM, gH);
+            if (c + 1 < MBW) aM = frag_a(c + 1, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            FLEX_BF_MFMA(aH, gL);
+            FLEX_BF_MFMA(aH, gM);
+            FLEX_BF_MFMA(aH, gH);
+            if (c + 1 < MBW) aH = frag_a(c + 1, 0);
+            __builtin_amdgcn_sched_barrier(0);
+#undef FLEX_BF_MFMA
+#pragma unroll
+            for (int n = 0; n < NBW; ++n) {
+                tot[c][n] = half == 0 ? tot[c][n] + acc[n] : tot[c][n] - acc[n];
+                asm volatile("" : "+v"(tot[c][n]));        // here: put off, the products would wait in registers
+            }
+        }
+    };
+
+    if (tiles > 0) {
+        load_g(0);
+        store_g(0);
+        load_g(1);
+        __syncthreads();                   // the first half is complete
+    }
+    int k = 0;
+    do {                                   // (a workgroup without tiles still writes its partial, zeros)
+#pragma unroll
+        for (int c = 0; c < MBW; ++c)
+#pragma unroll
+            for (int n = 0; n < NBW; ++n) tot[c][n] = v4f{0.f, 0.f, 0.f, 0.f};
+        const int k0 = k, stop = min(tiles, k + FLUSH);
+        for (; k < stop; ++k) {
+            const bool more = k + 1 < tiles;
+            store_g(1);
+            tw.next_clamped();
+            if (more) load_g(0);
+            contract(0);
+            __syncthreads();               // the second half is complete
+            if (more) {
+                store_g(0);
+                load_g(1);
+            }
+            contract(1);
+            if (more) __syncthreads();     // the next tile's first half is complete
+        }
+        flush(k0 > 0);
+    } while (k < tiles);
 }
 #endif
 

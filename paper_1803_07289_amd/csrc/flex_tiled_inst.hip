@@ -267,18 +267,6 @@ hipError_t launch_bwd_fused_late_64_64(const float *g_rows, const float *own_row
 }
 #endif
 
-#if FLEX_WS && FLEX_DI == 64 && FLEX_DO == 64
-// Workgroups that share one [4*64 x 64] block of a wide layer's parameter gradient: enough to fill the device
-// when the blocks are few, one when they are many.
-int split_wide_gt_chunks(int B, int N, int blocks)
-{
-    using WL = WsGeom<S, 2, 2>;
-    const int64_t tot = (int64_t)B * ((N + WL::T - 1) / WL::T);
-    const int fill = persistent_grid(tot > 0x7fffffff ? 0x7fffffff : (int)tot, 1);
-    return fill / blocks > 1 ? fill / blocks : 1;
-}
-#endif
-
 // One term of the location gradient; false / hipErrorNotSupported when this shape has no kernel for it.
 bool FLEX_NAME(gp_ok, FLEX_DI, FLEX_DO)(int N, int K)
 {

@@ -78,6 +78,22 @@ def test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout):
     assert rel_err(gt.cpu().numpy(), rt) <= TOL and rel_err(gb.cpu().numpy(), rb) <= TOL
 
 
+@pytest.mark.parametrize("B,N,K,Din,Dout", [
+    (1, 2049, 8, 512, 512),      # one point in the last tile
+    (1, 2111, 16, 512, 512),     # one short of whole tiles, two steps of slots
+    (2, 1056, 5, 512, 640),      # the last tile ends at half its points
+    (3, 700, 9, 640, 384),       # several clouds, a workgroup's tiles across them
+])
+def test_parameter_gradients_in_blocks_of_128_channels(B, N, K, Din, Dout):
+    """Clouds of enough tiles for the wider blocks (wide_grad_plan)."""
+    test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout)
+
+
+@pytest.mark.parametrize("N", [16 * 64 + 1, 64 * 64, 8129])     # 17 and 64 partials a block of 64 channels, 128 and one tile twice
+def test_partials_of_every_reduction(N):
+    test_parameter_gradients_of_wide_layers(1, N, 8, 128, 128)
+
+
 @pytest.mark.parametrize("Din,Dout", [(64, 13), (64, 9), (128, 128), (70, 90), (64, 64)])
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
 def test_unlisted_point_without_a_location_has_no_gradient(Din, Dout, bad):
