@@ -41,8 +41,7 @@ hipError_t launch_reduce_partials(const float *partials, int n_wg, int DIP, int 
 // the 64-point tile kernels over fixed-K neighbour tensors / in-edge lists
 hipError_t launch_tile_0(const TileArgs &a, int outw, int grid, hipStream_t s);
 hipError_t launch_tile_1(const TileArgs &a, int outw, int grid, hipStream_t s);
-hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int gst, int n_hi, int n_ho, int oc, float *partials,
-                                  hipStream_t s);
+hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int n_hi, int n_ho, int oc, float *partials, hipStream_t s);
 // rows of at most 16 channels, one point per lane (flex_narrow.hip)
 hipError_t launch_narrow_0(const TileArgs &a, int grid, hipStream_t s);
 hipError_t launch_narrow_1(const TileArgs &a, int grid, hipStream_t s);
@@ -133,8 +132,8 @@ int lean_producer_mode()
 
 // Wide layers (both widths multiples of 128): the paper's network doubles the feature length at every resolution
 // stage while the point count drops by four (Sec. 4.3), so its deeper stages are of this kind.  They run on the 64-point
-// tile kernels, the parameter gradients block by block over columns of the point-major tensors (FLEX_SPLIT=0 in the
-// environment keeps 128 -> 128 on the single-pass fp32 kernels and the wider ones on the direct form, for comparisons).
+// tile kernels (FLEX_SPLIT=0 in the environment keeps 128 -> 128 on the single-pass fp32 kernels and the wider ones on the
+// direct form, for comparisons).
 static bool split_disabled()
 {
     static const bool off = [] { const char *v = getenv("FLEX_SPLIT"); return v != nullptr && v[0] == '0'; }();
@@ -160,50 +159,51 @@ static bool wide_ok(int64_t N, int K, int Din, int Dout)
 // Packed parameters of a wide layer, forward, as 64 x 128 blocks
 static size_t wide_packed_bytes(int Din, int Dout) { return (size_t)(Din / 64) * (Dout / 128) * theta_f16_bytes(64, 128); }
 
-// Parameter gradients of a wide layer: (Din/64) x (Dout/oc) independent blocks of [4*64 x oc], `chunks` workgroups each,
-// two launches (partial sums per block and workgroup, then their reduction in double).
+// Parameter gradients on the 64-point tile kernels: blocks of [4*64 x oc], `chunks` workgroups each, two launches (partial sums
+// per block and workgroup, then their reduction in double).  Rows are read at their own widths; what a block reaches past
+// them is dropped by the reduction.
 // Blocks of 128 output channels gather half as often, ones of 64 make twice the workgroups for a cloud of few tiles.  Costs in
 // tenths of a microsecond, as measured: a tile 3.2 us for 64 channels and 5.0 for 128, whose larger partials take 3 more.
 // us, 64 and 128: 128 -> 128, 2k points 15.8 and 17.9, 8k 23.5 and 24.7, 16k 29.8 and 29.6, 60k 66.6 and 60.9, 1M 970 and 782;
 // 256 -> 256, 2k 24.6 and 28.5, 12k 59.5 and 52.6; 512 -> 512, 1k 30.6 and 34.6, 2k 43.2 and 43.1, 8k 126 and 109, 109k 1620 and 1270.
-struct WideGradPlan { int oc, blocks, chunks; };
-static WideGradPlan wide_grad_plan(int64_t B, int64_t N, int Din, int Dout)
+struct TileGradPlan { int oc, n_hi, n_ho, chunks; };
+static TileGradPlan tile_grad_plan(int64_t B, int64_t N, int Din, int Dout)
 {
     const int64_t tiles = B * cdiv64(N, 64), cus = device_cu_count();
-    WideGradPlan best{};
+    TileGradPlan best{};
     int64_t least = 0;
     for (const int oc : {64, 128}) {
-        WideGradPlan p{oc, (Din / 64) * (Dout / oc), 1};
-        p.chunks = (int)std::max<int64_t>(1, std::min(tiles, cus / p.blocks));
-        const int64_t rounds = cdiv64((int64_t)p.blocks * p.chunks, cus) * cdiv64(tiles, p.chunks);
+        TileGradPlan p{oc, (Din + 63) / 64, (Dout + oc - 1) / oc, 1};
+        const int64_t blocks = (int64_t)p.n_hi * p.n_ho;
+        p.chunks = (int)std::max<int64_t>(1, std::min(tiles, cus / blocks));
+        const int64_t rounds = cdiv64(blocks * p.chunks, cus) * cdiv64(tiles, p.chunks);
         const int64_t cost = oc == 64 ? 32 * rounds : 50 * rounds + 30;
         if (oc == 64 || cost < least) { least = cost; best = p; }
     }
     return best;
 }
-static size_t wide_partial_bytes(int B, int N, int Din, int Dout)
+static size_t tile_grad_partial_bytes(int64_t B, int64_t N, int Din, int Dout)
 {
-    const WideGradPlan p = wide_grad_plan(B, N, Din, Dout);
-    return align256(sizeof(float) * (size_t)p.blocks * p.chunks * 4 * 64 * p.oc);
+    const TileGradPlan p = tile_grad_plan(B, N, Din, Dout);
+    return align256(sizeof(float) * (size_t)p.n_hi * p.n_ho * p.chunks * 4 * 64 * p.oc);
 }
 
-// (Dki, Dko): the widths of the rows, which may be padded; (Din, Dout): the parameters'.
-static hipError_t wide_grad_theta(const float *rows, const float *pos, const int32_t *nbr, const float *g_rows,
-                                  float *partials, float *grad_theta, float *grad_bias, int B, int N, int K, int Dki,
-                                  int Dko, int Din, int Dout, hipStream_t s)
+// rows [B*N, w_in], g_rows [B*N, w_out]: the tensors, or copies of at least four channels; (Din, Dout): the parameters' widths.
+static hipError_t tile_grad_theta(const float *rows, int w_in, const float *pos, const int32_t *nbr, const float *g_rows, int w_out,
+                                  float *partials, float *grad_theta, float *grad_bias, int B, int N, int K, int Din, int Dout,
+                                  hipStream_t s)
 {
-    const WideGradPlan p = wide_grad_plan(B, N, Dki, Dko);
-    const int n_hi = Dki / 64, n_ho = Dko / p.oc, chunks = p.chunks;
+    const TileGradPlan p = tile_grad_plan(B, N, Din, Dout);
     TileArgs a{};
     a.rows = rows; a.pos = pos; a.nbr = nbr;
-    a.rs = Dki; a.w_in = Dki;
-    a.N = N; a.K = K; a.tpc = (N + 63) / 64; a.n_in = 1; a.chunks = chunks;
+    a.rs = a.w_in = w_in; a.w_out = w_out;
+    a.N = N; a.K = K; a.tpc = (N + 63) / 64; a.n_in = 1; a.chunks = p.chunks;
     const int64_t total = (int64_t)B * a.tpc;
-    if (total > 0x7fffffff || (int64_t)n_hi * n_ho * chunks > 0x7fffffff) return hipErrorInvalidValue;
+    if (total > 0x7fffffff || (int64_t)p.n_hi * p.n_ho * p.chunks > 0x7fffffff) return hipErrorInvalidValue;
     a.total = (int)total;
-    hipError_t e = launch_tile_grad_theta(a, g_rows, Dko, n_hi, n_ho, p.oc, partials, s);
+    hipError_t e = launch_tile_grad_theta(a, g_rows, p.n_hi, p.n_ho, p.oc, partials, s);
     if (e != hipSuccess) return e;
-    return launch_reduce_partials(partials, chunks, 64, p.oc, p.blocks, n_ho, Din, Dout, grad_theta, grad_bias, s);
+    return launch_reduce_partials(partials, p.chunks, 64, p.oc, p.n_hi * p.n_ho, p.n_ho, Din, Dout, grad_theta, grad_bias, s);
 }
 
 // Workspace bytes of the packed parameters in either format (rows padded to 4, columns to 16).
@@ -455,8 +455,8 @@ static bool pad_disabled()
 }
 
 // Widths with neither a tiled nor a wide path of their own (FLEX_PAD=0 in the environment keeps them on the direct-form
-// kernels, for comparisons): the nearest listed widths.  The parameter gradients run on zero-padded copies at those, and
-// so does a gather that the kernels for any width do not take: extra channels of the features / upstream gradient and
+// kernels, for comparisons): the nearest listed widths.  Parameter gradients and gathers that the kernels for any width do not
+// take run on zero-padded copies at those: extra channels of the features / upstream gradient and
 // extra rows / columns of the parameters are zero, so they add nothing, and the results are the leading channels / the
 // leading block of what the padded layer returns.
 static bool padded_shape(int Din, int Dout, int *DIp, int *DOp)
@@ -477,6 +477,26 @@ static bool padded_shape(int Din, int Dout, int *DIp, int *DOp)
     *DIp = (Din + 127) / 128 * 128;
     *DOp = (Dout + 127) / 128 * 128;
     return wide_shape(*DIp, *DOp);
+}
+
+// Do the parameter gradients run on the 64-point tile kernels, at the tensors' own widths?  (k_in, k_out): the listed widths.
+// - Where a side is wider than 64 channels, always: 64 and 128 channels ran on the fp32 matrix op, other widths on zero-padded copies.
+//   us, K = 8, those and tiles: 64 -> 128, 3k points 22.9 and 16.3, 20k 45 and 24.5, 300k 370 and 126; 128 -> 64, 300k 488 and 148; 100 -> 50,
+//   3k 29.3 and 16.3, 300k 550 and 141; 3 -> 100, 300k 431 and 179; 160 -> 160, 3k 42 and 22, 300k 1124 and 650.
+// - Below that the wave-specialised kernels take fewer points at a time.  Point-major tensors that they need copies of: at 64 x 64 channels
+//   from 8k points on (all gradients, copies and tiles: 50 -> 50, 3k 30.8 and 31.1, 20k 45.8 and 44.7, 300k 210 and 165; 33 -> 64, 3k 28.3
+//   and 29.2, 20k 43.4 and 42.5, 300k 182 and 159), at fewer where both tensors are copied, from 2^17 points on (20 -> 13, 50k 42.2 and
+//   43.5, 300k 128 and 112; 12 -> 60, 50k 55.1 and 53.1, 300k 179 and 154; only the features, 6 -> 64, 300k 149 and 154, 16 -> 32 149 and
+//   154).  Channel-major ones are copied either way (64 -> 13, 100k 73 and 82; 50 -> 50 93 and 96).
+static bool use_tile_params(int64_t B, int64_t N, int K, int Din, int Dout, int k_in, int k_out, int bcn)
+{
+    const bool padded = k_in != Din || k_out != Dout;
+    if (!tile_ok(N, std::max(Din, 4)) || !tile_ok(N, std::max(Dout, 4)) || (int64_t)K * N * 4 >= (1ll << 32)) return false;
+    if ((int64_t)((Din + 63) / 64) * ((Dout + 63) / 64) > 65535) return false;       // one grid row of the reduction per block
+    if (Din > 64 || Dout > 64) return true;
+    if (!padded || bcn || Din < 4 || Dout < 4) return false;
+    if (k_in == 64 && k_out == 64) return B * N >= 8192;
+    return k_in != Din && k_out != Dout && B * N >= 1 << 17;
 }
 
 static size_t rows_bytes(int64_t B, int64_t N, int width) { return align256(sizeof(float) * (size_t)(B * N) * width); }
@@ -538,7 +558,9 @@ struct BwdPlan {
     bool direct, padded, wide;
     int k_in, k_out;
     GatherPlan gather;                   // of the feature gradient
-    bool copy, copy_out;
+    bool tile_params;                    // the parameter gradients run on the tile kernels
+    bool copy_f, copy_g, copy_out;       // features, upstream gradient, result
+    int c_in, c_out;                     // widths of the rows that the kernels read, the copies' or the tensors'
     bool fused;      // feature and parameter gradients, when both are asked for, come from the one-pass kernel
     size_t thetaP, featT, gT, gfP, partials, order, flag, in_off, in_src, inedge_ws, total;
     Packed packed;
@@ -588,16 +610,21 @@ static BwdPlan plan_bwd(int64_t B, int64_t N, int K, int Din, int Dout, int layo
     p.packed = Packed{0, p.total};
     if (p.direct) return p;
     p.gather = plan_gather(B, N, K, Dout, Din, p.k_out, p.k_out, p.k_in, p.padded, 1, SIZE_MAX);
-    p.copy = p.padded || layout == FLEX_LAYOUT_BCN;          // the parameter gradients run at the listed widths
+    p.tile_params = (!p.padded || p.gather.own_widths()) &&      // (both then read rows of one stride)
+                    use_tile_params(B, N, K, Din, Dout, p.k_in, p.k_out, layout == FLEX_LAYOUT_BCN);
+    const bool own = p.gather.own_widths() && (p.tile_params || !p.padded);
+    p.c_in = own ? std::max(Din, 4) : p.k_in;
+    p.c_out = own ? std::max(Dout, 4) : p.k_out;
+    p.copy_f = layout == FLEX_LAYOUT_BCN || p.c_in != Din;
+    p.copy_g = layout == FLEX_LAYOUT_BCN || p.c_out != Dout;
     p.copy_out = p.padded && !p.gather.own_widths();
     size_t at = p.gather.packed;
-    if (p.copy) {
-        p.featT = at; at += rows_bytes(B, N, p.k_in);
-        p.gT = at;    at += rows_bytes(B, N, p.k_out);
-    }
+    // (padded: the room for copies at the listed widths stays part of the size that callers are told, as in the forward plan)
+    if (p.copy_f || p.padded) { p.featT = at; at += rows_bytes(B, N, std::max(p.c_in, p.k_in)); }
+    if (p.copy_g || p.padded) { p.gT = at;    at += rows_bytes(B, N, std::max(p.c_out, p.k_out)); }
     if (p.copy_out) { p.gfP = at; at += rows_bytes(B, N, p.k_in); }
     p.partials = at;
-    at += p.wide ? wide_partial_bytes((int)B, (int)N, p.k_in, p.k_out) : grad_theta_partial_bytes(B, N, p.k_in, p.k_out);
+    at += p.tile_params ? tile_grad_partial_bytes(B, N, Din, Dout) : grad_theta_partial_bytes(B, N, p.k_in, p.k_out);
     p.order = at; at += inedges_order_bytes(B * N);          // walking order of the feature gradient's gather
     p.fused = !p.padded && !p.wide && Din == 64 && Dout == 64 && bwd_fused_ok_64_64((int)N, K);
     if (p.fused) { p.flag = at; at += align256(fused_control_bytes()); }   // the one-pass kernel's flag and records
@@ -901,12 +928,14 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
     // The parameter gradients alone have nothing else to prepare unless tensors are copied: the packing would be a launch of its
     // own, which only a cloud in no order earns back.  K = 8, us without and with it: 32 -> 32, 4k points 8.7 and 10.8, 300k 59 and 63,
     // 1M 173 and 180; 64 -> 64, 300k 96 and 100 (in no order 105 and 97).
-    const float *packed = grad_feat || p.copy ? p.packed.in(ws, workspace_bytes) : nullptr;
+    const float *packed = grad_feat || p.copy_f || p.copy_g ? p.packed.in(ws, workspace_bytes) : nullptr;
     const bool records = packed != nullptr && p.gather.route == FLEX_ROUTE_NARROW;       // made from the tensor as it is
-    if (p.copy && (grad_theta || !records)) {
-        prep.copy(grad_out, (float *)(ws + p.gT), B, N, Dout, p.k_out, bcn, 0);
-        if (grad_theta) prep.copy(feat, (float *)(ws + p.featT), B, N, Din, p.k_in, bcn, 0);
+    if (p.copy_g && (grad_theta || !records)) {
+        prep.copy(grad_out, (float *)(ws + p.gT), B, N, Dout, p.c_out, bcn, 0);
         g_rows = (const float *)(ws + p.gT);
+    }
+    if (p.copy_f && grad_theta) {
+        prep.copy(feat, (float *)(ws + p.featT), B, N, Din, p.c_in, bcn, 0);
         rows = (const float *)(ws + p.featT);
     }
     if (grad_feat) {
@@ -929,15 +958,14 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
         FLEX_HIP(launch_reduce_partials_if(control, partials, n_wg, 64, 64, Din, Dout, grad_theta, grad_bias, s));
         return FLEX_OK;
     }
-    if (grad_theta && p.wide)
-        FLEX_HIP(wide_grad_theta(rows, pos, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, p.k_in, p.k_out, Din,
-                                 Dout, s));
+    if (grad_theta && p.tile_params)
+        FLEX_HIP(tile_grad_theta(rows, p.c_in, pos, nbr, g_rows, p.c_out, partials, grad_theta, grad_bias, B, N, K, Din, Dout, s));
     else if (grad_theta)
         FLEX_HIP(launch_grad_theta(rows, pos, pr, nbr, g_rows, partials, grad_theta, grad_bias, B, N, K, p.k_in, p.k_out, Din,
                                    Dout, s));
     if (!grad_feat) return FLEX_OK;
     float *dst = p.copy_out ? (float *)(ws + p.gfP) : grad_feat;
-    FLEX_HIP(gather_launch(p.gather, g_rows, p.k_out, p.gather.own_widths() ? Dout : p.k_out, pos, packed, nullptr, in_off, in_src,
+    FLEX_HIP(gather_launch(p.gather, g_rows, p.c_out, p.gather.own_widths() ? Dout : p.k_out, pos, packed, nullptr, in_off, in_src,
                            order, thetaP, dst, p.copy_out ? p.k_in : Din, bcn && !p.copy_out, B, N, K, s));
     if (p.copy_out) FLEX_HIP(launch_copy_rows(dst, grad_feat, B, N, p.k_in, Din, 0, bcn, s));
     return FLEX_OK;

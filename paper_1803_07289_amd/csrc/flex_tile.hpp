@@ -160,6 +160,22 @@ __device__ __forceinline__ int tile_lane_channel(const TileArgs &a, int ib) { re
 // acc[pass][channel][component]; park(acc, ib, point) takes them when a (tile, input block) is complete, HALVES: park(acc[pass], pass)
 // those of the first four points and of the second four as each is.
 // Eight rows are in flight at all times.
+// Four channels (X: numbers, or sums of several components) that were read `shift` places early, back in their own places: what lies
+// past the row's end becomes zero.
+template <class X>
+__device__ __forceinline__ void put_channels_right(X &&c, int shift)
+{
+    typedef std::remove_reference_t<decltype(c[0])> E;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        E x = E{};
+#pragma unroll
+        for (int w = v; w < 4; ++w)
+            if (w - v == shift) x = c[w];
+        c[v] = x;
+    }
+}
+
 // How a slot's row is weighed with its (dx, dy, dz, 1).  MX: by outer products on the matrix cores (outer_slot): an entry is
 // then needed once per wave, in the layout lane = 16 * point + 4 * slot + component, and its row's offset, the fourth
 // component, reaches the address by a DPP add.  Else by fused multiply-adds, every lane reading its point's entry from LDS,
@@ -374,16 +390,7 @@ void tile_conv_kernel(const TileArgs a)
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
                 const int shift = ib * IC + 4 * t - tile_lane_channel(a, ib);
-                if (ragged && shift > 0) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        v4f x = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int w = v + 1; w < 4; ++w)
-                            if (w - v == shift) x = acc[p][w];
-                        acc[p][v] = x;
-                    }
-                }
+                if (ragged && shift > 0) put_channels_right(acc[p], shift);
                 float m = 0.f;
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
@@ -567,7 +574,7 @@ void tile_conv_kernel(const TileArgs a)
 // below; the rule and both sides' times are beside wide_grad_plan (flex_api.hip).
 // ---------------------------------------------------------------------------
 static __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, int gst, int n_ho, float *__restrict__ partials)
+void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, int n_ho, float *__restrict__ partials)
 {
     constexpr int IC = 64, KD = 4 * IC, OC = 64, T = 64;
     constexpr int AS = bf3_stride(KD), GS = bf3_stride(OC);
@@ -585,9 +592,11 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
         if (tiles == 0) return;
         const int t = lane & 15, grp = lane >> 4, first = 8 * wave;
         gather_steps<false, false, false>(a, sc, tiles, first, hi, s_ent[wave], [&](v4f (&acc)[2][4], int, int) __attribute__((always_inline)) {
+            const int shift = 64 * hi + 4 * t - tile_lane_channel(a, hi);        // channels past the row's end: not in the result
             __syncthreads();               // the tile before is contracted
 #pragma unroll
             for (int ps = 0; ps < 2; ++ps) {
+                if (a.w_in % 4 != 0) put_channels_right(acc[ps], shift);
                 char *row = s_A + (first + 4 * ps + grp) * AS;
                 const int swap = bf3_swap(first);            // of all eight points of the wave
 #pragma unroll
@@ -638,12 +647,14 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
 
     TileWalk tw(sc, a.tpc);
     v4f gv[2];                             // upstream gradient of a tile: two four-float chunks per thread
+    const int g_col = OC * ho + 4 * (ctid & 15), g_at = min(g_col, a.w_out - 4);      // past the row's end the last four again
     auto load_g = [&]() {
+        const auto g = row_buffer(g_rows + (int64_t)tw.b * a.N * a.w_out, 4u * (unsigned)a.N * (unsigned)a.w_out);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            const int pt = (ctid >> 4) + 32 * c, l = tw.tic * T + pt;
-            gv[c] = v4f{0.f, 0.f, 0.f, 0.f};                       // points past the cloud contribute nothing
-            if (l < a.N) gv[c] = *reinterpret_cast<const v4f *>(g_rows + ((int64_t)tw.b * a.N + l) * gst + OC * ho + 4 * (ctid & 15));
+            // the row behind the cloud's last reads as zeros: points past the cloud contribute nothing
+            const int l = min(tw.tic * T + (ctid >> 4) + 32 * c, a.N);
+            gv[c] = load_row4(g, 4u * ((unsigned)l * (unsigned)a.w_out + (unsigned)g_at));
         }
     };
     if (tiles > 0) load_g();
@@ -654,6 +665,7 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
             char *row = s_G + ((ctid >> 4) + 32 * c) * GS;
             const int swap = bf3_swap(ctid >> 4), v = 8 * (ctid & 15);
             unsigned h0, m0, l0, h1, m1, l1;
+            if (a.w_out % 4 != 0) put_channels_right(gv[c], g_col - g_at);
             const v4f g = c == 0 ? gv[c] : -gv[c];                 // (the second 32 points: see above)
             split_bf3(g[0], g[1], h0, m0, l0);
             split_bf3(g[2], g[3], h1, m1, l1);
@@ -725,7 +737,7 @@ __device__ __forceinline__ int bf3x_swizzle(int row) { return ((row & 1) << 7) |
 __device__ __forceinline__ int bf3x_at(int v, int K, int swizzle) { return (v ^ swizzle ^ (K & 128)) + (K & ~128); }
 
 static __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void tile_grad_theta128_kernel(const TileArgs a, const float *__restrict__ g_rows, int gst, int n_ho, float *__restrict__ partials)
+void tile_grad_theta128_kernel(const TileArgs a, const float *__restrict__ g_rows, int n_ho, float *__restrict__ partials)
 {
     constexpr int IC = 64, KD = 4 * IC, OC = 128, T = 64, H = 32;
     constexpr int AS = 6 * KD, GS = 6 * OC;
@@ -744,7 +756,8 @@ void tile_grad_theta128_kernel(const TileArgs a, const float *__restrict__ g_row
         if (tiles == 0) return;
         const int lane = threadIdx.x & 63, t = lane & 15, grp = lane >> 4;
         const int row = 4 * wave + grp, swizzle = bf3x_swizzle(row);
-        gather_steps<false, false, true>(a, sc, tiles, 8 * wave, hi, s_ent[wave], [&](const v4f (&acc)[4], int half) __attribute__((always_inline)) {
+        gather_steps<false, false, true>(a, sc, tiles, 8 * wave, hi, s_ent[wave], [&](v4f (&acc)[4], int half) __attribute__((always_inline)) {
+            if (a.w_in % 4 != 0) put_channels_right(acc, 64 * hi + 4 * t - tile_lane_channel(a, hi));
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 unsigned h0, m0, l0, h1, m1, l1;
@@ -805,12 +818,13 @@ void tile_grad_theta128_kernel(const TileArgs a, const float *__restrict__ g_row
     v4f gv[CH];
     auto load_g = [&](int half) __attribute__((always_inline)) {
         const int ctid = 64 * cw + lane_now(), r = ctid / CPR;
-        const auto rows = row_buffer(g_rows + (int64_t)tw.b * a.N * gst, 4u * (unsigned)a.N * (unsigned)gst);
+        const auto rows = row_buffer(g_rows + (int64_t)tw.b * a.N * a.w_out, 4u * (unsigned)a.N * (unsigned)a.w_out);
+        const int col = min(OC * ho + 4 * (ctid % CPR), a.w_out - 4);      // past the row's end the last four again
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             // the row behind the cloud's last reads as zeros
             const int l = min(tw.tic * T + 8 * ((r + ROWS * c) >> 2) + 4 * half + (r & 3), a.N);
-            gv[c] = load_row4(rows, 4u * ((unsigned)l * (unsigned)gst + (unsigned)(OC * ho + 4 * (ctid % CPR))));
+            gv[c] = load_row4(rows, 4u * ((unsigned)l * (unsigned)a.w_out + (unsigned)col));
         }
     };
     auto store_g = [&](int half) __attribute__((always_inline)) {
@@ -820,6 +834,7 @@ void tile_grad_theta128_kernel(const TileArgs a, const float *__restrict__ g_row
             char *row = s_G[half] + (r + ROWS * c) * GS;
             const int swizzle = bf3x_swizzle(r + ROWS * c);
             unsigned h0, m0, l0, h1, m1, l1;
+            if (a.w_out % 4 != 0) put_channels_right(gv[c], max(0, OC * ho + 4 * (ctid % CPR) - (a.w_out - 4)));
             const v4f g = half == 0 ? gv[c] : -gv[c];              // (the second 32 points: see above)
             split_bf3(g[0], g[1], h0, m0, l0);
             split_bf3(g[2], g[3], h1, m1, l1);

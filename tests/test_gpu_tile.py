@@ -62,12 +62,12 @@ def test_hub_point_and_empty_lists():
     (1, 1, 1, 128, 128), (1, 63, 7, 128, 256), (2, 65, 9, 256, 128), (3, 130, 16, 130, 70),
     (1, 3001, 8, 1024, 128),     # six tiles per workgroup: the accumulators go into the running totals in between
 ])
-def test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout):
-    say(f"tile parameter gradients: B={B} N={N} K={K} {Din}->{Dout}")
+def test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout, layout=fx.BNC):
+    say(f"tile parameter gradients: B={B} N={N} K={K} {Din}->{Dout} layout={layout}")
     pos, nbr, feat, theta, bias, g = random_problem(40 + N, B, N, K, Din, Dout)
-    lay = lambda a: to_layout(a, fx.BNC)
+    lay = lambda a: to_layout(a, layout)
     edges = fx.flex_inedges_build(dev(nbr))
-    _, gt, gb = fx.flexconv_bwd(lay(feat), dev(pos), dev(nbr), dev(theta), dev(bias), lay(g), layout=fx.BNC, in_edges=edges)
+    _, gt, gb = fx.flexconv_bwd(lay(feat), dev(pos), dev(nbr), dev(theta), dev(bias), lay(g), layout=layout, in_edges=edges)
     rt, rb = np.zeros(theta.shape), np.zeros(bias.shape)
     for b in range(B):
         p, f, up = (a[b].astype(np.float64) for a in (pos, feat, g))
@@ -86,6 +86,25 @@ def test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout):
 ])
 def test_parameter_gradients_in_blocks_of_128_channels(B, N, K, Din, Dout):
     """Clouds of enough tiles for the wider blocks (wide_grad_plan)."""
+    test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout)
+
+
+@pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
+@pytest.mark.parametrize("B,N,K,Din,Dout", [
+    (1, 65, 8, 3, 100), (2, 70, 9, 101, 2),            # rows of fewer than four channels: copied
+    (1, 1, 1, 65, 65), (1, 130, 8, 66, 129), (1, 97, 5, 67, 130), (2, 64, 16, 128, 131),     # a lane's four channels across the rows' end
+    (1, 64, 8, 64, 128), (1, 33, 8, 128, 64), (1, 150, 8, 1, 65),
+    (1, 2500, 8, 515, 514),                            # blocks of 128 channels
+])
+def test_parameter_gradients_at_the_rows_own_widths(B, N, K, Din, Dout, layout):
+    test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout, layout)
+
+
+@pytest.mark.parametrize("B,N,K,Din,Dout", [
+    (1, 8192, 4, 33, 64), (2, 4096, 4, 50, 47), (1, 8191, 4, 50, 47),         # 64 x 64 channels, both sides of the line
+    (1, 1 << 17, 3, 5, 6), (2, 1 << 16, 3, 20, 13), (1, (1 << 17) - 1, 3, 20, 13), (1, 1 << 17, 3, 5, 64), (1, 1 << 17, 3, 3, 5),
+])
+def test_parameter_gradients_of_narrow_layers_on_tiles(B, N, K, Din, Dout):
     test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout)
 
 
