@@ -21,6 +21,30 @@ int device_cu_count();
 int persistent_grid(int64_t total_tiles, int wg_per_cu);
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+
+// Rows of C channels, four to a lane.  ODD: C (at least 4) is no multiple of four: rows begin at any element, and the last lane takes the
+// row's last four channels, of which it stores those that the lane before has not.
+template <class T, bool ODD>
+struct RowChunk {
+    typedef T V __attribute__((ext_vector_type(4), aligned(ODD ? 4 : 16)));
+    typedef T V16 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ int first(int c4, int C) { return ODD ? min(4 * c4, C - 4) : 4 * c4; }
+    // at: the chunk's first channel in the row
+    static __device__ __forceinline__ V16 load(const T *at) { return *reinterpret_cast<const V *>(at); }
+    // STREAM: outputs that are not read again by their kernel should not displace gathered rows in L2
+    template <bool STREAM = true>
+    static __device__ __forceinline__ void store(T *at, int c4, int C, const V16 &v)
+    {
+        if (!ODD || 4 * c4 + 4 <= C) {
+            if (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<V *>(at));
+            else *reinterpret_cast<V *>(at) = v;
+            return;
+        }
+#pragma unroll
+        for (int i = 1; i < 4; ++i)
+            if (i >= 4 - C % 4) at[i] = v[i];
+    }
+};
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 

@@ -37,17 +37,21 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t total_tiles)
 }
 static inline unsigned xcd_grid(int64_t total_tiles) { return (unsigned)(((total_tiles + 7) >> 3) << 3); }
 
-// Point-major, C % 4 == 0: one thread per (point, 4 channels); a block owns PT consecutive points.
+// Point-major, C >= 4: one thread per (point, 4 channels); a block owns PT consecutive points.
 // The gather is latency-bound, so a thread first requests the ids of 8 neighbours, then their 8
 // rows (16 bytes each), and only then compares: 8 rows per lane are in flight instead of one.
 // SUB: pooling with subsampling, only the kept centres sel[b,j] are evaluated (BN = B*Ns output rows).
-template <bool SUB>
+// ODD: C is no multiple of four.  An element per thread, as such rows were taken before, asks for every id once a channel; us, that and
+// here, K = 8: C = 33, K = 6, 1.5M points forward 552 and 142, backward 1001 and 290; 150, 100k 170 and 48, 283 and 59; 13, 3k 10.1 and 9.7,
+// 8.4 and 8.3.  (Rows of fewer than four channels still are.)
+template <bool SUB, bool ODD>
 __device__ __forceinline__ void pool_fwd_bnc4_tile(const float *__restrict__ feat, const int32_t *__restrict__ nbr,
                                                    const int32_t *__restrict__ sel, float *__restrict__ out,
                                                    int32_t *__restrict__ argmax, int64_t BN, int N, int Ns, int K,
-                                                   int C4, int PT, int64_t tile)
+                                                   int C, int PT, int64_t tile)
 {
     constexpr int U = 8;
+    const int C4 = ODD ? (C + 3) / 4 : C / 4;
     for (int i = threadIdx.x; i < PT * C4; i += 256) {
         const int c4 = i % C4;
         const int64_t gp = tile * PT + i / C4;
@@ -56,7 +60,8 @@ __device__ __forceinline__ void pool_fwd_bnc4_tile(const float *__restrict__ fea
         if constexpr (SUB) { b = (int)(gp / Ns); l = min(max(sel[gp], 0), N - 1); }
         else { b = (int)(gp / N); l = (int)(gp % N); }
         const int32_t *nb = nbr + (int64_t)b * K * N + l;
-        const v4f *rows = reinterpret_cast<const v4f *>(feat) + (int64_t)b * N * C4 + c4;
+        const int c0 = RowChunk<float, ODD>::first(c4, C);
+        const float *rows = feat + (int64_t)b * N * C + c0;
         float v0 = 0.f, v1 = 0.f, v2 = 0.f, v3 = 0.f;
         int b0 = 0, b1 = 0, b2 = 0, b3 = 0;
         // slots k0 .. k0+W-1: ids, then rows, then the comparisons
@@ -66,7 +71,7 @@ __device__ __forceinline__ void pool_fwd_bnc4_tile(const float *__restrict__ fea
             v4f v[W];                                                                                      \
             _Pragma("unroll") for (int u = 0; u < W; ++u)                                                  \
                 n[u] = nb[(int64_t)min(k0 + u, K - 1) * N]; /* past K: the last slot again */              \
-            _Pragma("unroll") for (int u = 0; u < W; ++u) v[u] = rows[(int64_t)n[u] * C4];                 \
+            _Pragma("unroll") for (int u = 0; u < W; ++u) v[u] = RowChunk<float, ODD>::load(rows + (int64_t)n[u] * C);  \
             if (k0 == 0) {                                                                                 \
                 v0 = v[0].x; v1 = v[0].y; v2 = v[0].z; v3 = v[0].w;                                        \
                 b0 = b1 = b2 = b3 = n[0];                                                                  \
@@ -83,25 +88,24 @@ __device__ __forceinline__ void pool_fwd_bnc4_tile(const float *__restrict__ fea
         if (k0 < K) FLEX_POOL_SLOTS(4)      // a tail of up to four slots
 #undef FLEX_POOL_SLOTS
         const v4f bv = {v0, v1, v2, v3};
-        // streaming stores: the outputs are not read again by this kernel and should not displace gathered rows in L2
-        __builtin_nontemporal_store(bv, &reinterpret_cast<v4f *>(out)[gp * C4 + c4]);
+        RowChunk<float, ODD>::store(out + gp * C + c0, c4, C, bv);
         const i4v bi = {b0, b1, b2, b3};
-        __builtin_nontemporal_store(bi, &reinterpret_cast<i4v *>(argmax)[gp * C4 + c4]);
+        RowChunk<int, ODD>::store(argmax + gp * C + c0, c4, C, bi);
     }
 }
 
-template <bool SUB>
+template <bool SUB, bool ODD>
 __global__ __launch_bounds__(256) void pool_fwd_bnc4_kernel(const float *__restrict__ feat,
                                                             const int32_t *__restrict__ nbr,
                                                             const int32_t *__restrict__ sel,
                                                             float *__restrict__ out,
                                                             int32_t *__restrict__ argmax, int64_t BN,
-                                                            int N, int Ns, int K, int C4, int PT,
+                                                            int N, int Ns, int K, int C, int PT,
                                                             int64_t total_tiles)
 {
     const int64_t tile = xcd_tile(total_tiles);
     if (tile < 0) return;
-    pool_fwd_bnc4_tile<SUB>(feat, nbr, sel, out, argmax, BN, N, Ns, K, C4, PT, tile);
+    pool_fwd_bnc4_tile<SUB, ODD>(feat, nbr, sel, out, argmax, BN, N, Ns, K, C, PT, tile);
 }
 
 // value of lane SRC of the caller's 16-lane row (all 16 lanes must be active)
@@ -214,12 +218,13 @@ __global__ __launch_bounds__(256) void pool_fwd_generic_kernel(const float *__re
 hipError_t launch_pool_fwd(const float *feat, const int32_t *nbr, float *out, int32_t *argmax,
                            int B, int N, int K, int C, int bnc, hipStream_t s)
 {
-    if (bnc && (C % 4 == 0)) {
-        const int C4 = C / 4;
+    if (bnc && C >= 4) {
+        const int C4 = (C + 3) / 4;
         const int PT = C4 >= 256 ? 1 : 256 / C4;
         const int64_t BN = (int64_t)B * N, tiles = (BN + PT - 1) / PT;
-        hipLaunchKernelGGL(pool_fwd_bnc4_kernel<false>, dim3(xcd_grid(tiles)), dim3(256), 0, s, feat, nbr,
-                           (const int32_t *)nullptr, out, argmax, BN, N, N, K, C4, PT, tiles);
+        const auto kernel = C % 4 == 0 ? pool_fwd_bnc4_kernel<false, false> : pool_fwd_bnc4_kernel<false, true>;
+        hipLaunchKernelGGL(kernel, dim3(xcd_grid(tiles)), dim3(256), 0, s, feat, nbr,
+                           (const int32_t *)nullptr, out, argmax, BN, N, N, K, C, PT, tiles);
     } else if (!bnc && N < (1 << 30)) {
         const int tpc = (N + 63) / 64;
         const int64_t tiles = (int64_t)B * tpc;
@@ -239,12 +244,13 @@ hipError_t launch_pool_fwd(const float *feat, const int32_t *nbr, float *out, in
 hipError_t launch_pool_sub_fwd(const float *feat, const int32_t *nbr, const int32_t *sel, float *out,
                                int32_t *argmax, int B, int N, int Ns, int K, int C, int bnc, hipStream_t s)
 {
-    if (bnc && (C % 4 == 0)) {
-        const int C4 = C / 4;
+    if (bnc && C >= 4) {
+        const int C4 = (C + 3) / 4;
         const int PT = C4 >= 256 ? 1 : 256 / C4;
         const int64_t BNs = (int64_t)B * Ns, tiles = (BNs + PT - 1) / PT;
-        hipLaunchKernelGGL(pool_fwd_bnc4_kernel<true>, dim3(xcd_grid(tiles)), dim3(256), 0, s, feat, nbr, sel,
-                           out, argmax, BNs, N, Ns, K, C4, PT, tiles);
+        const auto kernel = C % 4 == 0 ? pool_fwd_bnc4_kernel<true, false> : pool_fwd_bnc4_kernel<true, true>;
+        hipLaunchKernelGGL(kernel, dim3(xcd_grid(tiles)), dim3(256), 0, s, feat, nbr, sel,
+                           out, argmax, BNs, N, Ns, K, C, PT, tiles);
     } else if (!bnc && N < (1 << 30)) {
         const int tpc = (Ns + 63) / 64;
         const int64_t tiles = (int64_t)B * tpc;
@@ -285,35 +291,40 @@ __global__ __launch_bounds__(256) void pool_bwd_kernel(const float *__restrict__
 // Entries are taken four at a time: their ids first, then the eight rows (winner table and
 // gradient), so that a lane has 128 bytes in flight instead of 32 (eight at a time is slower:
 // the mean in-degree is K, so most of a second batch would be padding).
-template <int U>
+template <int U, bool ODD>
 __global__ __launch_bounds__(256) void pool_bwd_gather_bnc4_kernel(
     const float *__restrict__ grad_out, const int32_t *__restrict__ argmax,
     const int32_t *__restrict__ in_off, const int32_t *__restrict__ in_src,
-    float *__restrict__ grad_feat, int64_t BN, int N, int L, int C4, int PT, int64_t total_tiles)
+    float *__restrict__ grad_feat, int64_t BN, int N, int L, int C, int PT, int64_t total_tiles)
 {
     // L = rows of grad_out / argmax per cloud: N, or the kept centres of a subsampled pooling (the lists
     // then hold row numbers among the kept centres).  U = entries per batch: about half the mean list length.
     const int64_t tile = xcd_tile(total_tiles);
     if (tile < 0) return;
+    const int C4 = ODD ? (C + 3) / 4 : C / 4;
     for (int i = threadIdx.x; i < PT * C4; i += 256) {
         const int c4 = i % C4;
         const int64_t gp = tile * PT + i / C4;
         if (gp >= BN) break;
         const int64_t b = gp / N;
         const int m = (int)(gp - b * N);
-        const v4f *g4 = reinterpret_cast<const v4f *>(grad_out) + b * L * C4 + c4;
-        const int4 *a4 = reinterpret_cast<const int4 *>(argmax) + b * L * C4 + c4;
+        const int c0 = RowChunk<float, ODD>::first(c4, C);
+        const float *g_rows = grad_out + b * L * C + c0;
+        const int32_t *a_rows = argmax + b * L * C + c0;
         v4f acc = {0.f, 0.f, 0.f, 0.f};
         const int e0 = in_off[gp], e1 = in_off[gp + 1];
         int prev = -1;
         for (int e = e0; e < e1; e += U) {
             int l[U];
-            int4 a[U];
+            i4v a[U];
             v4f g[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) l[u] = in_src[min(e + u, e1 - 1)];     // past the end: the last entry again
 #pragma unroll
-            for (int u = 0; u < U; ++u) { a[u] = a4[(int64_t)l[u] * C4]; g[u] = g4[(int64_t)l[u] * C4]; }
+            for (int u = 0; u < U; ++u) {
+                a[u] = RowChunk<int, ODD>::load(a_rows + (int64_t)l[u] * C);
+                g[u] = RowChunk<float, ODD>::load(g_rows + (int64_t)l[u] * C);
+            }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 // a centre that lists m twice (adjacent entries, also the repeats past the end) routes one gradient
@@ -325,7 +336,7 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bnc4_kernel(
                 acc.w += (fresh && a[u].w == m) ? g[u].w : 0.f;
             }
         }
-        __builtin_nontemporal_store(acc, &reinterpret_cast<v4f *>(grad_feat)[gp * C4 + c4]);
+        RowChunk<float, ODD>::store(grad_feat + gp * C + c0, c4, C, acc);
     }
 }
 
@@ -1122,26 +1133,28 @@ hipError_t launch_pool_sub_bwd_gather(const float *grad_out, const int32_t *argm
                                       const int32_t *in_src, float *grad_feat, int B, int N, int L, int C,
                                       int bnc, hipStream_t s)
 {
-    if (bnc && (C % 4 == 0)) {
-        const int C4 = C / 4;
+    if (bnc && C >= 4) {
+        const int C4 = (C + 3) / 4;
         const int PT = C4 >= 256 ? 1 : 256 / C4;
         const int64_t BN = (int64_t)B * N, tiles = (BN + PT - 1) / PT;
         const int64_t tiles4 = (BN + 4 * PT - 1) / (4 * PT);
-        if (C4 % 16 == 0 && 2 * (int64_t)L <= N && C4 <= 256 && tiles4 >= 2048)       // eight workgroups per CU
+        if (C % 64 == 0 && 2 * (int64_t)L <= N && C4 <= 256 && tiles4 >= 2048)       // eight workgroups per CU
             hipLaunchKernelGGL((pool_bwd_gather_row16_kernel<2, 4>), dim3(xcd_grid(tiles4)), dim3(256), 0, s, grad_out,
                                argmax, in_off, in_src, grad_feat, BN, N, L, C4, 4 * PT, tiles4);
-        else if (C4 % 16 == 0 && 2 * (int64_t)L <= N)
+        else if (C % 64 == 0 && 2 * (int64_t)L <= N)
             hipLaunchKernelGGL((pool_bwd_gather_row16_kernel<2, 1>), dim3(xcd_grid(tiles)), dim3(256), 0, s, grad_out,
                                argmax, in_off, in_src, grad_feat, BN, N, L, C4, PT, tiles);
-        else if (C4 % 16 == 0)
+        else if (C % 64 == 0)
             hipLaunchKernelGGL((pool_bwd_gather_row16_kernel<4, 1>), dim3(xcd_grid(tiles)), dim3(256), 0, s, grad_out,
                                argmax, in_off, in_src, grad_feat, BN, N, L, C4, PT, tiles);
-        else if (2 * (int64_t)L <= N)     // lists a quarter as long (subsampling keeps a quarter of the centres)
-            hipLaunchKernelGGL(pool_bwd_gather_bnc4_kernel<2>, dim3(xcd_grid(tiles)), dim3(256), 0, s, grad_out,
-                               argmax, in_off, in_src, grad_feat, BN, N, L, C4, PT, tiles);
-        else
-            hipLaunchKernelGGL(pool_bwd_gather_bnc4_kernel<4>, dim3(xcd_grid(tiles)), dim3(256), 0, s, grad_out,
-                               argmax, in_off, in_src, grad_feat, BN, N, L, C4, PT, tiles);
+        else {
+            // lists a quarter as long (subsampling keeps a quarter of the centres): entries two at a time
+            const bool few = 2 * (int64_t)L <= N;
+            const auto kernel = C % 4 == 0 ? (few ? pool_bwd_gather_bnc4_kernel<2, false> : pool_bwd_gather_bnc4_kernel<4, false>)
+                                           : (few ? pool_bwd_gather_bnc4_kernel<2, true> : pool_bwd_gather_bnc4_kernel<4, true>);
+            hipLaunchKernelGGL(kernel, dim3(xcd_grid(tiles)), dim3(256), 0, s, grad_out,
+                               argmax, in_off, in_src, grad_feat, BN, N, L, C, PT, tiles);
+        }
     } else if (!bnc && L < (1 << 30)) {
         const int tpc = (N + 63) / 64;
         const int64_t tiles = (int64_t)B * tpc;

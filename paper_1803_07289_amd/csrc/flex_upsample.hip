@@ -46,19 +46,21 @@ __global__ __launch_bounds__(256) void upsample_inv_scatter_kernel(const int32_t
     }
 }
 
-// Point-major, C % 4 == 0: a workgroup takes `points` consecutive points of the larger layer.  First eight lanes per point
+// Point-major, C >= 4 (ODD: no multiple of four): a workgroup takes `points` consecutive points of the larger layer.  First eight lanes per point
 // sort its neighbours out: those with a row in the smaller layer go to the point's list in LDS, all the zero-filled ones
 // together are one candidate, the value 0 with the lowest of their indices.  Then a thread per (point, 4 channels) compares
 // the rows of the list and that candidate.  What bounds it is the vector ALU and the chain neighbour -> inverse map -> row:
 // compared one by one, the three quarters of the neighbours that are zero-filled cost as much as the others, and every lane
 // of a point loaded the same ids and map entries (437.5k points x 128, K = 8, a quarter kept: 215 -> 138 us, of which the outputs alone are 72).
-// K * points entries of LDS; points: a power of two, at most 32.
+// K * points entries of LDS; points: a power of two, at most 32.  (C = 113, 500k points, a quarter kept: an element per thread 716 us
+// and 377 backward, here 151 and 118.)
+template <bool ODD>
 __global__ __launch_bounds__(256) void upsample_fwd_bnc4_kernel(const float *__restrict__ feat_small,
                                                                 const int32_t *__restrict__ inv,
                                                                 const int32_t *__restrict__ nbr,
                                                                 float *__restrict__ out,
                                                                 int32_t *__restrict__ argmax, int64_t BN,
-                                                                int Ns, int Nf, int K, int C4, int points,
+                                                                int Ns, int Nf, int K, int C, int points,
                                                                 int64_t total_tiles)
 {
     constexpr int U = 4;
@@ -91,11 +93,13 @@ __global__ __launch_bounds__(256) void upsample_fwd_bnc4_kernel(const float *__r
         }
     }
     __syncthreads();
+    const int C4 = ODD ? (C + 3) / 4 : C / 4;
     for (int i = threadIdx.x; i < points * C4; i += 256) {
         const int p = i / C4, c4 = i - p * C4;
         const int64_t gp = tile * points + p;
         if (gp >= BN) break;
-        const v4f *rows = reinterpret_cast<const v4f *>(feat_small) + gp / Nf * Ns * C4 + c4;
+        const int c0 = RowChunk<float, ODD>::first(c4, C);
+        const float *rows = feat_small + gp / Nf * Ns * C + c0;
         const int2 head = s_head[p];
         const int entries = head.x & 0x3fffffff, zero = head.y;
         const int2 *list = s_list + p * K;
@@ -108,7 +112,7 @@ __global__ __launch_bounds__(256) void upsample_fwd_bnc4_kernel(const float *__r
 #pragma unroll
             for (int u = 0; u < U; ++u) en[u] = list[min(e0 + u, entries - 1)];        // past the end: the last entry again
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = rows[(int64_t)en[u].y * C4];
+            for (int u = 0; u < U; ++u) v[u] = RowChunk<float, ODD>::load(rows + (int64_t)en[u].y * C);
             if (e0 == 0 && head.x >> 30) {
                 v0 = v[0].x; v1 = v[0].y; v2 = v[0].z; v3 = v[0].w;
                 b0 = b1 = b2 = b3 = en[0].x;
@@ -128,11 +132,10 @@ __global__ __launch_bounds__(256) void upsample_fwd_bnc4_kernel(const float *__r
             take_up(0.f, zero, v3, b3);
         }
         const v4f bv = {v0, v1, v2, v3};
-        // streaming stores, as in the pooling kernels
         typedef int i4v __attribute__((ext_vector_type(4)));
-        __builtin_nontemporal_store(bv, &reinterpret_cast<v4f *>(out)[gp * C4 + c4]);
+        RowChunk<float, ODD>::store(out + gp * C + c0, c4, C, bv);
         const i4v bi = {b0, b1, b2, b3};
-        __builtin_nontemporal_store(bi, &reinterpret_cast<i4v *>(argmax)[gp * C4 + c4]);
+        RowChunk<int, ODD>::store(argmax + gp * C + c0, c4, C, bi);
     }
 }
 
@@ -169,12 +172,15 @@ __global__ __launch_bounds__(256) void upsample_fwd_generic_kernel(const float *
 
 // Backward as a gather over the in-edge lists of the larger layer (sorted, repeats adjacent):
 //   grad_small[j][c] = sum over centres l that list m = sel[j] of (argmax[l][c] == m ? grad_out[l][c] : 0)
+template <bool ODD>
 __global__ __launch_bounds__(256) void upsample_bwd_bnc4_kernel(
     const float *__restrict__ grad_out, const int32_t *__restrict__ argmax, const int32_t *__restrict__ sel,
     const int32_t *__restrict__ in_off, const int32_t *__restrict__ in_src, float *__restrict__ grad_small,
-    int64_t BNs, int Ns, int Nf, int C4, int PT, int64_t total_tiles)
+    int64_t BNs, int Ns, int Nf, int C, int PT, int64_t total_tiles)
 {
     constexpr int U = 4;
+    typedef int i4v __attribute__((ext_vector_type(4)));
+    const int C4 = ODD ? (C + 3) / 4 : C / 4;
     const int64_t tile = xcd_tile_up(total_tiles);
     if (tile < 0) return;
     for (int i = threadIdx.x; i < PT * C4; i += 256) {
@@ -183,21 +189,25 @@ __global__ __launch_bounds__(256) void upsample_bwd_bnc4_kernel(
         if (gj >= BNs) break;
         const int64_t b = gj / Ns;
         const int m = sel[gj];
+        const int c0 = RowChunk<float, ODD>::first(c4, C);
         v4f acc = {0.f, 0.f, 0.f, 0.f};
         if (m >= 0 && m < Nf) {
-            const v4f *g4 = reinterpret_cast<const v4f *>(grad_out) + b * Nf * C4 + c4;
-            const int4 *a4 = reinterpret_cast<const int4 *>(argmax) + b * Nf * C4 + c4;
+            const float *g_rows = grad_out + b * Nf * C + c0;
+            const int32_t *a_rows = argmax + b * Nf * C + c0;
             const int64_t gp = b * Nf + m;
             const int e0 = in_off[gp], e1 = in_off[gp + 1];
             int prev = -1;
             for (int e = e0; e < e1; e += U) {
                 int l[U];
-                int4 a[U];
+                i4v a[U];
                 v4f g[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) l[u] = in_src[min(e + u, e1 - 1)];     // past the end: the last entry again
 #pragma unroll
-                for (int u = 0; u < U; ++u) { a[u] = a4[(int64_t)l[u] * C4]; g[u] = g4[(int64_t)l[u] * C4]; }
+                for (int u = 0; u < U; ++u) {
+                    a[u] = RowChunk<int, ODD>::load(a_rows + (int64_t)l[u] * C);
+                    g[u] = RowChunk<float, ODD>::load(g_rows + (int64_t)l[u] * C);
+                }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const bool fresh = l[u] != prev;   // a centre that lists m twice routes one gradient
@@ -209,7 +219,7 @@ __global__ __launch_bounds__(256) void upsample_bwd_bnc4_kernel(
                 }
             }
         }
-        reinterpret_cast<v4f *>(grad_small)[gj * C4 + c4] = acc;
+        RowChunk<float, ODD>::template store<false>(grad_small + gj * C + c0, c4, C, acc);
     }
 }
 
@@ -282,9 +292,10 @@ hipError_t launch_upsample_fwd(const float *feat_small, const int32_t *inv, cons
     int points = 32;
     while (points > 1 && (int64_t)points * K > 2048) points >>= 1;
     const int64_t BN = (int64_t)B * Nf, tiles = (BN + points - 1) / points;
-    if (bnc && C % 4 == 0 && K <= 8192) {          // one point's list of up to 64 KB
-        hipLaunchKernelGGL(upsample_fwd_bnc4_kernel, dim3(xcd_grid_up(tiles)), dim3(256), sizeof(int2) * points * K, s, feat_small,
-                           inv, nbr, out, argmax, BN, Ns, Nf, K, C / 4, points, tiles);
+    if (bnc && C >= 4 && K <= 8192) {          // one point's list of up to 64 KB
+        const auto kernel = C % 4 == 0 ? upsample_fwd_bnc4_kernel<false> : upsample_fwd_bnc4_kernel<true>;
+        hipLaunchKernelGGL(kernel, dim3(xcd_grid_up(tiles)), dim3(256), sizeof(int2) * points * K, s, feat_small,
+                           inv, nbr, out, argmax, BN, Ns, Nf, K, C, points, tiles);
     } else {
         hipLaunchKernelGGL(upsample_fwd_generic_kernel, dim3(capped_blocks((int64_t)B * Nf * C, 1 << 20)), dim3(256),
                            0, s, feat_small, inv, nbr, out, argmax, B, Ns, Nf, K, C, bnc);
@@ -296,12 +307,13 @@ hipError_t launch_upsample_bwd(const float *grad_out, const int32_t *argmax, con
                                const int32_t *in_off, const int32_t *in_src, float *grad_small, int B, int Ns,
                                int Nf, int C, int bnc, hipStream_t s)
 {
-    if (bnc && (C % 4 == 0)) {
-        const int C4 = C / 4;
+    if (bnc && C >= 4) {
+        const int C4 = (C + 3) / 4;
         const int PT = C4 >= 256 ? 1 : 256 / C4;
         const int64_t BNs = (int64_t)B * Ns, tiles = (BNs + PT - 1) / PT;
-        hipLaunchKernelGGL(upsample_bwd_bnc4_kernel, dim3(xcd_grid_up(tiles)), dim3(256), 0, s, grad_out, argmax, sel,
-                           in_off, in_src, grad_small, BNs, Ns, Nf, C4, PT, tiles);
+        const auto kernel = C % 4 == 0 ? upsample_bwd_bnc4_kernel<false> : upsample_bwd_bnc4_kernel<true>;
+        hipLaunchKernelGGL(kernel, dim3(xcd_grid_up(tiles)), dim3(256), 0, s, grad_out, argmax, sel,
+                           in_off, in_src, grad_small, BNs, Ns, Nf, C, PT, tiles);
     } else {
         hipLaunchKernelGGL(upsample_bwd_generic_kernel, dim3(capped_blocks((int64_t)B * Ns * C, 1 << 20)), dim3(256),
                            0, s, grad_out, argmax, sel, in_off, in_src, grad_small, B, Ns, Nf, C, bnc);

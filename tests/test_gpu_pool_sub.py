@@ -53,6 +53,21 @@ def test_flexpool_sub_matches_oracle(B, N, Ns, K, C, layout):
     assert torch.equal(gf_gather, gf_gather2)                                  # fixed summation order
 
 
+# rows whose last lane has fewer channels of its own, and whose places in memory are no multiple of 16 bytes
+@pytest.mark.parametrize("C", [3, 4, 5, 6, 7, 33, 63, 129, 255, 1027])
+def test_rows_of_any_width(C):
+    test_flexpool_sub_matches_oracle(2, 70, 18, 9, C, fx.BNC)
+    rng = np.random.default_rng(C)
+    feat, g = (rng.integers(-2, 3, size=(2, C, 70)).astype(np.float32) for _ in range(2))
+    nbr = rng.integers(0, 70, size=(2, 9, 70)).astype(np.int32)
+    ro, ra = oracle.flexpool_fwd(feat, nbr)
+    out, arg = fx.flexpool_fwd(to_layout(feat, fx.BNC), dev(nbr), layout=fx.BNC)
+    gf = fx.flexpool_bwd(to_layout(g, fx.BNC), arg, layout=fx.BNC, in_edges=fx.flex_inedges_build(dev(nbr)))
+    torch.cuda.synchronize()
+    assert np.array_equal(from_layout(arg, fx.BNC), ra) and np.array_equal(from_layout(out, fx.BNC), ro)
+    assert np.array_equal(from_layout(gf, fx.BNC), oracle.flexpool_bwd(g, ra))          # sums of small whole numbers
+
+
 def test_flexpool_sub_equals_full_pooling_on_kept_rows():
     rng = np.random.default_rng(5)
     B, N, K, C, Ns = 2, 3000, 8, 64, 750

@@ -40,6 +40,12 @@ def test_flexupsample_matches_oracle(B, Nf, Ns, K, C, layout):
     assert torch.equal(gs, gs2)                                               # fixed summation order
 
 
+# rows whose last lane has fewer channels of its own, and whose places in memory are no multiple of 16 bytes
+@pytest.mark.parametrize("C", [3, 4, 5, 6, 7, 33, 63, 129, 255, 1027])
+def test_rows_of_any_width(C):
+    test_flexupsample_matches_oracle(2, 70, 18, 9, C, fx.BNC)
+
+
 def test_selection_check_counts_bad_entries():
     sel = np.stack([np.arange(10), np.arange(10) + 3]).astype(np.int32)
     assert fx.flex_validate_selection(dev(sel), 40) == 0
