@@ -22,6 +22,16 @@ int persistent_grid(int64_t total_tiles, int wg_per_cu);
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+// The channel-major kernels' workgroups take 64 points and 16 channels at a time: into how many parts their channels are dealt, so that
+// a cloud of few tiles fills the device (full: the workgroups that do).  A part sorts its tile's neighbours out for itself.
+// us, in one part and in as many, pooling forward / backward: 2k points x 112 channels 12.0 / 67 and 9.1 / 11.0; 10k x 64 9.7 / 39 and
+// 10.2 / 16.0; 26k x 128 to a quarter, K = 12, 29.4 / 44.6 and 16.9 / 30.3.
+static inline unsigned channel_parts(int64_t tiles, int C, int64_t full)
+{
+    const int64_t most = (C + 15) / 16, wanted = full / (tiles > 0 ? tiles : 1);
+    return (unsigned)(wanted < 1 ? 1 : wanted < most ? wanted : most);
+}
+
 // Rows of C channels, four to a lane.  ODD: C (at least 4) is no multiple of four: rows begin at any element, and the last lane takes the
 // row's last four channels, of which it stores those that the lane before has not.
 template <class T, bool ODD>
@@ -234,6 +244,8 @@ hipError_t launch_upsample_fwd(const float *feat_small, const int32_t *inv, cons
 hipError_t launch_upsample_bwd(const float *grad_out, const int32_t *argmax, const int32_t *sel,
                                const int32_t *in_off, const int32_t *in_src, float *grad_small, int B, int Ns,
                                int Nf, int C, int bnc, hipStream_t s);
+hipError_t launch_upsample_bwd_bcn(const float *grad_out, const int32_t *argmax, const int32_t *sel, const int32_t *in_off,
+                                   const int32_t *in_src, float *grad_small, int B, int Ns, int Nf, int C, hipStream_t s);
 hipError_t launch_upsample_check_sel(const int32_t *sel, const int32_t *inv, int B, int Ns, int Nf, int32_t *bad,
                                      hipStream_t s);
 

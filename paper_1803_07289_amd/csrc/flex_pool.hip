@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) void pool_fwd_bcn_kernel(const float *__restri
     int n0[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) n0[u] = nb[(int64_t)min(u, K - 1) * N];      // past K: the last slot again
-    for (int c0 = w * CH; c0 < C; c0 += 4 * CH) {
+    for (int c0 = (blockIdx.y * 4 + w) * CH; c0 < C; c0 += 4 * CH * gridDim.y) {
         const float *row[CH];
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch) row[ch] = feat + (b * C + min(c0 + ch, C - 1)) * N;
@@ -228,7 +228,7 @@ hipError_t launch_pool_fwd(const float *feat, const int32_t *nbr, float *out, in
     } else if (!bnc && N < (1 << 30)) {
         const int tpc = (N + 63) / 64;
         const int64_t tiles = (int64_t)B * tpc;
-        hipLaunchKernelGGL(pool_fwd_bcn_kernel<4>, dim3(xcd_grid(tiles)), dim3(256), 0, s, feat, nbr,
+        hipLaunchKernelGGL(pool_fwd_bcn_kernel<4>, dim3(xcd_grid(tiles), channel_parts(tiles, C, 2048)), dim3(256), 0, s, feat, nbr,
                            (const int32_t *)nullptr, out, argmax, N, N, K, C, tpc, tiles);
     } else {
         const int64_t total = (int64_t)B * N * C;
@@ -254,7 +254,7 @@ hipError_t launch_pool_sub_fwd(const float *feat, const int32_t *nbr, const int3
     } else if (!bnc && N < (1 << 30)) {
         const int tpc = (Ns + 63) / 64;
         const int64_t tiles = (int64_t)B * tpc;
-        hipLaunchKernelGGL(pool_fwd_bcn_kernel<4>, dim3(xcd_grid(tiles)), dim3(256), 0, s, feat, nbr, sel, out,
+        hipLaunchKernelGGL(pool_fwd_bcn_kernel<4>, dim3(xcd_grid(tiles), channel_parts(tiles, C, 2048)), dim3(256), 0, s, feat, nbr, sel, out,
                            argmax, N, Ns, K, C, tpc, tiles);
     } else {
         const int64_t total = (int64_t)B * Ns * C;
@@ -1003,15 +1003,19 @@ hipError_t launch_pool_fwd_planned(const float *feat, const int32_t *nbr, void *
 // the point each belongs to in LDS, every wave gathers winner-table and gradient values of its CH channels
 // for all entries (CH x 4 pairs in flight per lane) and parks what each entry routes, and then, with
 // lane = point, adds up each point's own stretch in list order.
-template <int ECH>
+// SEL: the points are sel[b, 0..N) of the Nf whose lists in_off bounds (those outside have none): their lists are anywhere,
+// and the block numbers their entries one list after the other.
+template <int ECH, bool SEL>
 __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
     const float *__restrict__ grad_out, const int32_t *__restrict__ argmax,
     const int32_t *__restrict__ in_off, const int32_t *__restrict__ in_src,
-    float *__restrict__ grad_feat, int N, int L, int C, int tiles_per_cloud, int64_t total_tiles)
+    const int32_t *__restrict__ sel, float *__restrict__ grad_feat, int N, int Nf, int L, int C, int tiles_per_cloud,
+    int64_t total_tiles)
 {
     constexpr int CH = 4, U = 4, J = ECH / 64;
     static_assert(ECH % (64 * U) == 0, "a lane takes U entries of a chunk at a time");
     __shared__ int s_off[65];
+    __shared__ int s_m[SEL ? 64 : 1], s_from[SEL ? 64 : 1];     // SEL: the points, where their lists begin
     __shared__ int s_l[ECH];            // source row of each entry
     __shared__ unsigned char s_t[ECH];  // its point (0..63), +64 unless it repeats the entry before it
     // what the entry routes, per channel of the pass (rows private to a wave); entry i of point p sits at
@@ -1024,11 +1028,29 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: channel rows get scalar base addresses
     const int m0 = (int)(tile - b * tiles_per_cloud) * 64;
     const int np = min(64, N - m0);
-    if (threadIdx.x <= 64) s_off[threadIdx.x] = in_off[b * N + m0 + min((int)threadIdx.x, np)];   // past the cloud: empty lists
+    if constexpr (SEL) {
+        if (w == 0) {
+            const int m = lane < np ? sel[b * N + m0 + lane] : -1;
+            const bool has = m >= 0 && m < Nf;
+            const int from = has ? in_off[b * Nf + m] : 0, count = has ? in_off[b * Nf + m + 1] - from : 0;
+            int sum = count;                             // of the lanes so far
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int below = __shfl_up(sum, d, 64);
+                if (lane >= d) sum += below;
+            }
+            s_m[lane] = m;
+            s_from[lane] = from;
+            s_off[lane + 1] = sum;
+            if (lane == 0) s_off[0] = 0;
+        }
+    } else if (threadIdx.x <= 64) {
+        s_off[threadIdx.x] = in_off[b * N + m0 + min((int)threadIdx.x, np)];   // past the cloud: empty lists
+    }
     __syncthreads();
     const int E0 = s_off[0], E1 = s_off[64];
     const int my0 = s_off[lane], my1 = s_off[lane + 1];
-    for (int cg = 0; cg < C; cg += 4 * CH) {
+    for (int cg = blockIdx.y * 4 * CH; cg < C; cg += 4 * CH * gridDim.y) {
         const int c0 = cg + w * CH;
         const int32_t *arow[CH];
         const float *grow[CH];
@@ -1045,6 +1067,14 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
             const int nEc = min(ECH, E1 - Ec);
             const int lo = max(my0, Ec) - Ec, hi = min(my1, Ec + nEc) - Ec;   // this lane's point, within the chunk
             __syncthreads();                            // every wave is done with the chunk before
+            if constexpr (SEL) {
+                const int32_t *list = in_src + s_from[lane];
+                for (int i = lo + w; i < hi; i += 4) {
+                    const int e = Ec + i - my0, l = list[e];
+                    s_l[i] = l;
+                    s_t[i] = (unsigned char)(lane + (e == 0 || list[e - 1] != l ? 64 : 0));
+                }
+            } else {
             for (int i = threadIdx.x; i < nEc; i += 256) s_l[i] = in_src[Ec + i];
             if (w == 0)
                 for (int i = lo; i < hi; ++i) {
@@ -1053,6 +1083,7 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
                     const bool fresh = e == my0 || in_src[e] != in_src[e - 1];
                     s_t[i] = (unsigned char)(lane + (fresh ? 64 : 0));
                 }
+            }
             __syncthreads();
 #pragma unroll
             for (int j0 = 0; j0 < J; j0 += U) {
@@ -1075,7 +1106,7 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int i = (j0 + u) * 64 + lane;
-                        const int m = m0 + (t[u] & 63);
+                        const int m = SEL ? s_m[t[u] & 63] : m0 + (t[u] & 63);
 #pragma unroll
                         for (int ch = 0; ch < CH; ++ch)
                             if (i < nEc) s_c[w * CH + ch][i + (t[u] & 63)] = ((t[u] & 64) && a[ch][u] == m) ? g[ch][u] : 0.f;
@@ -1158,8 +1189,8 @@ hipError_t launch_pool_sub_bwd_gather(const float *grad_out, const int32_t *argm
     } else if (!bnc && L < (1 << 30)) {
         const int tpc = (N + 63) / 64;
         const int64_t tiles = (int64_t)B * tpc;
-        hipLaunchKernelGGL(pool_bwd_gather_bcn_kernel<512>, dim3(xcd_grid(tiles)), dim3(256), 0, s, grad_out,
-                           argmax, in_off, in_src, grad_feat, N, L, C, tpc, tiles);
+        hipLaunchKernelGGL((pool_bwd_gather_bcn_kernel<512, false>), dim3(xcd_grid(tiles), channel_parts(tiles, C, 1024)), dim3(256), 0, s, grad_out,
+                           argmax, in_off, in_src, (const int32_t *)nullptr, grad_feat, N, N, L, C, tpc, tiles);
     } else {
         const int64_t total = (int64_t)B * N * C;
         int64_t blocks = (total + 255) / 256;
@@ -1167,6 +1198,17 @@ hipError_t launch_pool_sub_bwd_gather(const float *grad_out, const int32_t *argm
         hipLaunchKernelGGL(pool_bwd_gather_generic_kernel, dim3((unsigned)blocks), dim3(256), 0, s,
                            grad_out, argmax, in_off, in_src, grad_feat, B, N, L, C, bnc);
     }
+    return hipGetLastError();
+}
+
+// Channel-major upsampling, backward: the sums of the kept points alone, over the larger layer's lists
+hipError_t launch_upsample_bwd_bcn(const float *grad_out, const int32_t *argmax, const int32_t *sel, const int32_t *in_off,
+                                   const int32_t *in_src, float *grad_small, int B, int Ns, int Nf, int C, hipStream_t s)
+{
+    const int tpc = (Ns + 63) / 64;
+    const int64_t tiles = (int64_t)B * tpc;
+    hipLaunchKernelGGL((pool_bwd_gather_bcn_kernel<512, true>), dim3(xcd_grid(tiles), channel_parts(tiles, C, 1024)), dim3(256), 0, s, grad_out, argmax,
+                       in_off, in_src, sel, grad_small, Ns, Nf, Nf, C, tpc, tiles);
     return hipGetLastError();
 }
 

@@ -139,6 +139,99 @@ __global__ __launch_bounds__(256) void upsample_fwd_bnc4_kernel(const float *__r
     }
 }
 
+// Channel-major.  A workgroup owns 64 consecutive points of the larger layer: lane = point, so ids, outputs and winners move
+// as whole 256-byte rows, and the four waves split the channels in chunks of CH.  First they sort the neighbours out as above,
+// a quarter of the slots each: entries in slot order, lane by lane, in LDS.  Then a wave compares the entries of its points,
+// CH x U four-byte values in flight per lane.  (An element per thread asked for every id and map entry once a channel: 235k points x
+// 128, K = 16, 744 us, here 158; 1.46M x 64, K = 6, 1158 and 343; 26k x 128, K = 12, 72 and 31; 4k x 33 18.1 and 17.1.)
+// Dynamic LDS: K * 64 entries.
+template <int CH>
+__global__ __launch_bounds__(256) void upsample_fwd_bcn_kernel(const float *__restrict__ feat_small, const int32_t *__restrict__ inv,
+                                                               const int32_t *__restrict__ nbr, float *__restrict__ out,
+                                                               int32_t *__restrict__ argmax, int Ns, int Nf, int K, int C,
+                                                               int tiles_per_cloud, int64_t total_tiles)
+{
+    constexpr int U = 4;
+    extern __shared__ int2 s_list[];               // [K][64]: (index in the larger layer, row of the smaller one)
+    __shared__ int s_count[4][64], s_zero[4][64];  // per quarter of the slots: entries, lowest zero-filled index
+    const int64_t tile = xcd_tile_up(total_tiles);
+    if (tile < 0) return;
+    const int64_t b = tile / tiles_per_cloud;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: channel rows get scalar base addresses
+    const int l = (int)(tile - b * tiles_per_cloud) * 64 + lane, lc = min(l, Nf - 1);
+    const int32_t *nb = nbr + b * K * Nf + lc, *iv = inv + b * Nf;
+    const int per = (K + 3) / 4, k_from = w * per, k_to = min(K, k_from + per);
+    int mine = 0, zero = INT_MAX;
+    for (int k = k_from; k < k_to; ++k) {
+        const int n = nb[(int64_t)k * Nf];
+        const bool has = iv[n] >= 0;
+        mine += has;
+        zero = has ? zero : min(zero, n);
+    }
+    s_count[w][lane] = mine;
+    s_zero[w][lane] = zero;
+    __syncthreads();
+    int entries = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (q == w) mine = entries;                // where this wave's begin
+        entries += s_count[q][lane];
+        zero = min(zero, s_zero[q][lane]);
+    }
+    for (int k = k_from; k < k_to; ++k) {
+        const int n = nb[(int64_t)k * Nf], j = iv[n];
+        if (j >= 0) s_list[64 * mine++ + lane] = make_int2(n, j);
+    }
+    __syncthreads();
+    // the first neighbour is what the others are compared with
+    const bool first = iv[nb[0]] >= 0;
+    int most = entries;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) most = max(most, __shfl_xor(most, d, 64));
+    most = __builtin_amdgcn_readfirstlane(most);
+    const int last = max(entries - 1, 0);
+    for (int c0 = (blockIdx.y * 4 + w) * CH; c0 < C; c0 += 4 * CH * gridDim.y) {
+        const char *row[CH];
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) row[ch] = reinterpret_cast<const char *>(feat_small + (b * C + min(c0 + ch, C - 1)) * Ns);
+        float bv[CH];
+        int bn[CH];
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) { bv[ch] = 0.f; bn[ch] = zero; }
+        for (int e0 = 0; e0 < most; e0 += U) {
+            int2 en[U];
+            float v[CH][U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {          // past the end: the last entry again; no entry: row 0, not looked at
+                en[u] = s_list[64 * min(e0 + u, last) + lane];
+                en[u].y = entries > 0 ? en[u].y : 0;
+            }
+#pragma unroll
+            for (int ch = 0; ch < CH; ++ch)
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[ch][u] = *reinterpret_cast<const float *>(row[ch] + 4u * (unsigned)en[u].y);
+            if (entries > 0) {
+#pragma unroll
+                for (int ch = 0; ch < CH; ++ch) {
+                    if (e0 == 0 && first) { bv[ch] = v[ch][0]; bn[ch] = en[0].x; }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) take_up(v[ch][u], en[u].x, bv[ch], bn[ch]);
+                }
+            }
+        }
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+            if (zero != INT_MAX) take_up(0.f, zero, bv[ch], bn[ch]);
+            if (l < Nf && c0 + ch < C) {
+                const int64_t at = (b * C + c0 + ch) * Nf + l;
+                __builtin_nontemporal_store(bv[ch], &out[at]);
+                __builtin_nontemporal_store(bn[ch], &argmax[at]);
+            }
+        }
+    }
+}
+
 // Any C, either layout: one thread per output element.
 __global__ __launch_bounds__(256) void upsample_fwd_generic_kernel(const float *__restrict__ feat_small,
                                                                    const int32_t *__restrict__ inv,
@@ -296,6 +389,11 @@ hipError_t launch_upsample_fwd(const float *feat_small, const int32_t *inv, cons
         const auto kernel = C % 4 == 0 ? upsample_fwd_bnc4_kernel<false> : upsample_fwd_bnc4_kernel<true>;
         hipLaunchKernelGGL(kernel, dim3(xcd_grid_up(tiles)), dim3(256), sizeof(int2) * points * K, s, feat_small,
                            inv, nbr, out, argmax, BN, Ns, Nf, K, C, points, tiles);
+    } else if (!bnc && K <= 64 && Ns < 1 << 30) {
+        const int tpc = (Nf + 63) / 64;
+        const int64_t tiles64 = (int64_t)B * tpc;
+        hipLaunchKernelGGL(upsample_fwd_bcn_kernel<4>, dim3(xcd_grid_up(tiles64), channel_parts(tiles64, C, 2048)), dim3(256),
+                           sizeof(int2) * 64 * K, s, feat_small, inv, nbr, out, argmax, Ns, Nf, K, C, tpc, tiles64);
     } else {
         hipLaunchKernelGGL(upsample_fwd_generic_kernel, dim3(capped_blocks((int64_t)B * Nf * C, 1 << 20)), dim3(256),
                            0, s, feat_small, inv, nbr, out, argmax, B, Ns, Nf, K, C, bnc);
@@ -314,6 +412,10 @@ hipError_t launch_upsample_bwd(const float *grad_out, const int32_t *argmax, con
         const auto kernel = C % 4 == 0 ? upsample_bwd_bnc4_kernel<false> : upsample_bwd_bnc4_kernel<true>;
         hipLaunchKernelGGL(kernel, dim3(xcd_grid_up(tiles)), dim3(256), 0, s, grad_out, argmax, sel,
                            in_off, in_src, grad_small, BNs, Ns, Nf, C, PT, tiles);
+    } else if (!bnc && Nf < 1 << 30 && (int64_t)B * Ns * C >= 1 << 16) {
+        // below that an element per thread is all at once and has no lists to set out (us, it and here: 1.5k of 6k points x 16 channels
+        // 9.4 and 12.5, 1k x 33 9.5 and 12.3, 300 x 128 9.4 and 8.9, 5k x 64 17.7 and 12.4, 59k x 128, K = 16, 1530 and 266)
+        return launch_upsample_bwd_bcn(grad_out, argmax, sel, in_off, in_src, grad_small, B, Ns, Nf, C, s);
     } else {
         hipLaunchKernelGGL(upsample_bwd_generic_kernel, dim3(capped_blocks((int64_t)B * Ns * C, 1 << 20)), dim3(256),
                            0, s, grad_out, argmax, sel, in_off, in_src, grad_small, B, Ns, Nf, C, bnc);

@@ -68,6 +68,11 @@ def test_rows_of_any_width(C):
     assert np.array_equal(from_layout(gf, fx.BNC), oracle.flexpool_bwd(g, ra))          # sums of small whole numbers
 
 
+@pytest.mark.parametrize("C", [15, 16, 17, 33, 130])          # around 16 channels a workgroup
+def test_channels_dealt_over_workgroups(C):
+    test_flexpool_sub_matches_oracle(2, 130, 65, 9, C, fx.BCN)
+
+
 def test_flexpool_sub_equals_full_pooling_on_kept_rows():
     rng = np.random.default_rng(5)
     B, N, K, C, Ns = 2, 3000, 8, 64, 750

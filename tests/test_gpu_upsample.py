@@ -46,6 +46,29 @@ def test_rows_of_any_width(C):
     test_flexupsample_matches_oracle(2, 70, 18, 9, C, fx.BNC)
 
 
+# channel-major: several workgroups to a tile's channels, entries in several rounds (a point that every centre lists), places of the
+# selection that name no point, more slots than the lists hold, the sizes on both sides of the backward kernels' line
+@pytest.mark.parametrize("B,Nf,Ns,K,C", [(2, 1040, 260, 9, 130), (1, 1040, 260, 64, 256), (1, 300, 75, 65, 17), (1, 4100, 1024, 8, 64), (1, 4100, 1023, 8, 64),
+                                         (3, 130, 65, 5, 400)])
+def test_layouts_agree_bit_for_bit(B, Nf, Ns, K, C):
+    say(f"upsample layouts B={B} Nf={Nf} Ns={Ns} K={K} C={C}")
+    rng = np.random.default_rng(Nf + K)
+    feat, g = rng.integers(-3, 4, size=(B, C, Ns)).astype(np.float32), rng.standard_normal((B, C, Nf)).astype(np.float32)
+    sel = np.stack([rng.permutation(Nf)[:Ns] for _ in range(B)]).astype(np.int32)
+    nbr = rng.integers(0, Nf, size=(B, K, Nf)).astype(np.int32)
+    nbr[:, -1, :] = sel[:, 1:2]
+    sel[:, 5], sel[:, 9] = -1, Nf
+    edges = fx.flex_inedges_build(dev(nbr))
+    got = {}
+    for layout in (fx.BNC, fx.BCN):
+        out, arg = fx.flexupsample_fwd(to_layout(feat, layout), dev(sel), dev(nbr), layout=layout)
+        gs = fx.flexupsample_bwd(to_layout(g, layout), arg, dev(sel), edges, layout=layout)
+        torch.cuda.synchronize()
+        got[layout] = [np.ascontiguousarray(from_layout(t, layout)) for t in (out, arg, gs)]
+    for a, b in zip(got[fx.BNC], got[fx.BCN]):
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+
+
 def test_selection_check_counts_bad_entries():
     sel = np.stack([np.arange(10), np.arange(10) + 3]).astype(np.int32)
     assert fx.flex_validate_selection(dev(sel), 40) == 0
