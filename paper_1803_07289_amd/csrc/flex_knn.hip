@@ -6,10 +6,11 @@
 //
 // Steps per call: bounding box of each cloud -> grid of cubic cells (at most 2^24) -> counting sort
 // of the points by cell (count, scan, fill of (x,y,z,id) records) -> one thread per point, in cell
-// order, searches the 27 cells around its own, then shell by shell, keeps the K best in registers
-// and stops once the K-th distance is inside the block of cells already searched -> the lists, so
-// far in cell order, go to their places.
+// order (several lanes to a point where the points are few), searches the 27 cells around its own, then shell by shell, keeps
+// the K best in registers and stops once the K-th distance is inside the block of cells already searched -> the lists, so
+// far in cell order, go to their places.  Small clouds: every point against all of its cloud, in one launch.
 #include "flex_common.hpp"
+#include <algorithm>
 
 namespace flex {
 
@@ -295,6 +296,205 @@ __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict
     }
 }
 
+// ---- several lanes to a point ---------------------------------------------------------------------------
+// minimum over the S lanes (a power of two, at most 16) of the caller's group, in each of them
+template <int CTRL>
+__device__ __forceinline__ double dpp_min(double x)
+{
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+    return fmin(x, __hiloint2double(hi, lo));
+}
+template <int S>
+__device__ __forceinline__ double lanes_min(double x)
+{
+    x = dpp_min<0xB1>(x);                            // the neighbour, the other pair of the four, the other four, the other eight
+    x = dpp_min<0x4E>(x);
+    if constexpr (S >= 8) x = dpp_min<0x141>(x);
+    if constexpr (S >= 16) x = dpp_min<0x140>(x);
+    return x;
+}
+
+// The K best of a group of S lanes: each keeps those of the candidates that it was offered.
+template <int K, int S>
+struct GroupBest {
+    double best[K], merged[K];
+    __device__ __forceinline__ static double none() { return knn_key(__builtin_inff(), 0x7fffffff); }
+    __device__ __forceinline__ GroupBest()
+    {
+#pragma unroll
+        for (int k = 0; k < K; ++k) best[k] = merged[k] = none();
+    }
+    __device__ __forceinline__ void offer(float mx, float my, float mz, float x, float y, float z, int id)
+    {
+        const float dx = __fsub_rn(x, mx), dy = __fsub_rn(y, my), dz = __fsub_rn(z, mz);
+        double c = knn_key(__fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz)), id);
+        if (c < best[K - 1]) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {            // sorted insertion: the candidate bubbles down the list
+                const double worse = fmax(best[k], c);
+                best[k] = fmin(best[k], c);
+                c = worse;
+            }
+        }
+    }
+    // merged: the K best of the group; the smallest head is taken K times
+    __device__ __forceinline__ void merge()
+    {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            merged[k] = lanes_min<S>(best[0]);
+            if (best[0] == merged[k]) {
+#pragma unroll
+                for (int j = 0; j + 1 < K; ++j) best[j] = best[j + 1];
+                best[K - 1] = none();
+            }
+        }
+    }
+    // goes on with what the group has: its first lane keeps it, the others keep what is better than its last
+    __device__ __forceinline__ void resume(int sub)
+    {
+#pragma unroll
+        for (int k = 0; k < K; ++k) best[k] = sub == 0 ? merged[k] : merged[K - 1];
+    }
+};
+
+// The search above with S lanes to a point, for clouds whose points are too few to fill the device a thread each: the nine rows'
+// bounds are asked for by as many lanes, the records of all of them dealt out one by one, a shell's rows one by one.
+template <int K, int S>
+__global__ __launch_bounds__(256) void knn_query_group_kernel(const float4 *__restrict__ rec, const int32_t *__restrict__ off,
+                                                              const unsigned *__restrict__ bbox, int32_t *__restrict__ lists,
+                                                              int N, int64_t cells_per_cloud)
+{
+    constexpr int G = 256 / S;
+    __shared__ int s_beg[9][G], s_end[9][G];
+    const int b = blockIdx.y, sub = threadIdx.x % S, grp = threadIdx.x / S;
+    const KnnGrid g = knn_grid(bbox, b, cells_per_cloud);
+    const int32_t *offb = off + b * cells_per_cloud;
+    const float span = fmaxf(fmaxf(g.n[0], g.n[1]), (float)g.n[2]) * g.h;
+    const float far = fmaxf(fmaxf(fabsf(g.lo[0]), fabsf(g.lo[1])), fabsf(g.lo[2])) + span;
+    const float eps = 4e-6f * span + 2e-6f * far;
+    for (int64_t i0 = (int64_t)blockIdx.x * G; i0 < N; i0 += (int64_t)gridDim.x * G) {
+        const int64_t i = i0 + grp < N ? i0 + grp : N - 1;               // past the cloud: its last point, not stored
+        const float4 me = rec[(int64_t)b * N + i];
+        int cx, cy, cz;
+        knn_cell_of(g, me.x, me.y, me.z, cx, cy, cz);
+        GroupBest<K, S> found;
+        auto offer = [&](const float4 &q) { found.offer(me.x, me.y, me.z, q.x, q.y, q.z, __float_as_int(q.w)); };
+        auto settled = [&](int r) {
+            float reach = __builtin_inff();
+            if (cx - r > 0) reach = fminf(reach, me.x - (g.lo[0] + (float)(cx - r) * g.h));
+            if (cx + r < g.n[0] - 1) reach = fminf(reach, (g.lo[0] + (float)(cx + r + 1) * g.h) - me.x);
+            if (cy - r > 0) reach = fminf(reach, me.y - (g.lo[1] + (float)(cy - r) * g.h));
+            if (cy + r < g.n[1] - 1) reach = fminf(reach, (g.lo[1] + (float)(cy + r + 1) * g.h) - me.y);
+            if (cz - r > 0) reach = fminf(reach, me.z - (g.lo[2] + (float)(cz - r) * g.h));
+            if (cz + r < g.n[2] - 1) reach = fminf(reach, (g.lo[2] + (float)(cz + r + 1) * g.h) - me.z);
+            reach -= eps;
+            if (reach == __builtin_inff()) return true;                 // the block is the whole grid
+            const float kth = __int_as_float(__double2hiint(found.merged[K - 1]));
+            return reach > 0.f && kth < reach * reach * 0.999999f;
+        };
+        __syncthreads();                   // the bounds of the points before are done with
+        for (int j = sub; j < 9; j += S) {
+            const int at = j == 0 ? 4 : j <= 4 ? 2 * j - 1 : j == 5 ? 0 : j == 6 ? 2 : j == 7 ? 6 : 8;     // nearest rows first
+            const int z = cz + at / 3 - 1, y = cy + at % 3 - 1;
+            const bool on = z >= 0 && z < g.n[2] && y >= 0 && y < g.n[1];
+            const int row = ((on ? z : cz) * g.n[1] + (on ? y : cy)) * g.n[0];
+            const int b0 = offb[row + max(cx - 1, 0)], b1 = offb[row + min(cx + 1, g.n[0] - 1) + 1];
+            s_beg[j][grp] = b0;
+            s_end[j][grp] = on ? b1 : b0;
+        }
+        __syncthreads();
+        {
+            int j = 0, e = s_beg[0][grp] + sub, end = s_end[0][grp];
+            // this lane's next record: past a row's end, as far into the next one
+            auto there = [&]() {
+                while (e >= end) {
+                    if (++j == 9) return false;
+                    e += s_beg[j][grp] - end;
+                    end = s_end[j][grp];
+                }
+                return true;
+            };
+            bool more = there();
+            float4 q = me;
+            if (more) q = rec[e];
+            while (more) {
+                const float4 c = q;
+                e += S;
+                more = there();
+                if (more) q = rec[e];
+                offer(c);
+            }
+        }
+        found.merge();
+        const int rmax = max(max(g.n[0], g.n[1]), g.n[2]);
+        for (int r = 2; !settled(r - 1) && r <= rmax; ++r) {
+            found.resume(sub);
+            const int z0 = max(cz - r, 0), z1 = min(cz + r, g.n[2] - 1);
+            const int y0 = max(cy - r, 0), y1 = min(cy + r, g.n[1] - 1), ny = y1 - y0 + 1;
+            const int x0 = max(cx - r, 0), x1 = min(cx + r, g.n[0] - 1);
+            for (int t = sub; t < (z1 - z0 + 1) * ny; t += S) {
+                const int z = z0 + t / ny, y = y0 + t % ny, row = (z * g.n[1] + y) * g.n[0];
+                // on a face row every x is on the shell; otherwise only the two ends are
+                if (abs(z - cz) == r || abs(y - cy) == r) {
+                    const int e1 = offb[row + x1 + 1];
+                    for (int e = offb[row + x0]; e < e1; ++e) offer(rec[e]);
+                } else {
+                    const int xa = cx - r, xb = cx + r;
+                    const int a0 = xa >= 0 ? offb[row + xa] : 0, a1 = xa >= 0 ? offb[row + xa + 1] : 0;
+                    const int c0 = xb < g.n[0] ? offb[row + xb] : 0, c1 = xb < g.n[0] ? offb[row + xb + 1] : 0;
+                    for (int e = a0; e < a1; ++e) offer(rec[e]);
+                    for (int e = c0; e < c1; ++e) offer(rec[e]);
+                }
+            }
+            found.merge();
+        }
+        if (i0 + grp < N) {
+            int32_t *dst = lists + ((int64_t)b * N + i) * K;
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (k % S == sub) dst[k] = __double2loint(found.merged[k]);
+        }
+    }
+}
+
+// Small clouds: every point against all of its cloud, sixteen lanes to a point, in one launch.
+template <int K>
+__global__ __launch_bounds__(256) void knn_all_kernel(const float *__restrict__ pos, int32_t *__restrict__ nbr, int N)
+{
+    constexpr int S = 16, G = 256 / S, U = 4;
+    const int b = blockIdx.y, sub = threadIdx.x % S, l = blockIdx.x * G + threadIdx.x / S, lc = min(l, N - 1);
+    const float *px = pos + (int64_t)b * 3 * N, *py = px + N, *pz = py + N;
+    const float mx = px[lc], my = py[lc], mz = pz[lc];
+    GroupBest<K, S> found;
+    float x[U], y[U], z[U];
+    auto request = [&](int n0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int n = min(n0 + S * u, N - 1);
+            x[u] = px[n]; y[u] = py[n]; z[u] = pz[n];
+        }
+    };
+    request(sub);
+    for (int n0 = sub; n0 < N; n0 += S * U) {
+        float cx[U], cy[U], cz[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) { cx[u] = x[u]; cy[u] = y[u]; cz[u] = z[u]; }
+        request(n0 + S * U);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (n0 + S * u < N) found.offer(mx, my, mz, cx[u], cy[u], cz[u], n0 + S * u);
+    }
+    found.merge();
+    if (l < N) {
+        int32_t *dst = nbr + (int64_t)b * K * N + l;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (k % S == sub) dst[(int64_t)k * N] = __double2loint(found.merged[k]);
+    }
+}
+
 // nbr[b][k][l] = lists[b][place of l][k]: a list is read as one stretch and the tensor written in its own order.  (The
 // search writing to the points' own columns, on a cloud in the sensor's order 4 bytes per line of memory, took 100 us
 // of the 365 that 1M points x 8 cost.)
@@ -325,8 +525,37 @@ size_t knn_ws_bytes(int B, int N, int K)
            exclusive_scan_ws_bytes(cells) + align256(sizeof(unsigned) * 6 * (size_t)B);
 }
 
+// Is every point compared with all of its cloud?  One launch in place of nine, and no grid; the work grows with the square.  us (the whole
+// call, K = 8, the grid with a thread per point / sixteen lanes, and here): 300 points 68 / 32 and 9.1, 1024 75 / 35 and 11.9, 4096 79 / 36
+// and 35, 8 x 1000 132 / 48 and 15, 100 x 300 111 / 60 and 17.5, 3 x 2500, K = 10, 99 / 40 and 31, 2 x 4096 81 / 40 and 45.
+static bool knn_all(int64_t B, int64_t N) { return N <= 4096 && B * N * N <= 25 << 20; }
+
+// Lanes to a point.  A thread's search is a chain of dependent reads that few points leave uncovered; merging costs the more the
+// more lanes.  us, the whole call, with 1, 4, 8 and 16 lanes: surfaces, K = 8, 30k points 126, 73, 58, 52; 65k 140, 82, 69, 68; 100k 171, 92,
+// 84, 87; 250k 139, 123, 132, 155; 1M 221, 321; K = 16, 8k 243, 127, 94, 70; a filled cube, K = 8, 5.5k 90, 50, 42, 36; 65k 88, 66, 71, 83;
+// 100k 94, 88, 100, 115; 300k 138, 176.  With K = 1 a list is one number: 50k 33, 35, 35, 38.
+static int knn_lanes(int64_t points, int K)
+{
+    if (points <= 1 << 15) return 16;
+    if (K < 4) return 1;
+    return points <= 1 << 16 ? 8 : points <= 1 << 17 ? 4 : 1;
+}
+
+#define FLEX_KNN_KS(CASE) \
+    CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(12) CASE(16) CASE(24) CASE(32)
+
 hipError_t launch_knn(const float *pos, int32_t *nbr, int B, int N, int K, void *ws, hipStream_t s)
 {
+    if (knn_all(B, N)) {
+#define FLEX_KNN_ALL(KK) \
+    case KK: hipLaunchKernelGGL(knn_all_kernel<KK>, dim3((N + 15) / 16, B), dim3(256), 0, s, pos, nbr, N); break;
+        switch (K) {
+            FLEX_KNN_KS(FLEX_KNN_ALL)
+        default: return hipErrorInvalidValue;
+        }
+#undef FLEX_KNN_ALL
+        return hipGetLastError();
+    }
     const int64_t cpc = knn_cell_cap(N, K), cells = (int64_t)B * cpc;
     char *at = (char *)ws;
     float4 *rec = (float4 *)at;       at += align256(sizeof(float4) * (size_t)B * N);
@@ -349,15 +578,23 @@ hipError_t launch_knn(const float *pos, int32_t *nbr, int B, int N, int K, void 
     hipLaunchKernelGGL(knn_fill_kernel, dim3(nb, B), dim3(256), 0, s, pos, cell, off, place, rec, N, cpc);
     int qb = (int)((N + 255) / 256);
     if (qb > 65535) qb = 65535;
+    const int lanes = knn_lanes((int64_t)B * N, K);
+    const dim3 group_grid((unsigned)std::min<int64_t>(((int64_t)N * lanes + 255) / 256, 65535), B);
+#define FLEX_KNN_GROUP(KK, S) \
+    hipLaunchKernelGGL((knn_query_group_kernel<KK, S>), group_grid, dim3(256), 0, s, rec, off, bbox, lists, N, cpc)
 #define FLEX_KNN_CASE(KK) \
-    case KK: hipLaunchKernelGGL(knn_query_kernel<KK>, dim3(qb, B), dim3(256), 0, s, rec, off, bbox, lists, N, cpc); break;
+    case KK: \
+        if (lanes == 16) FLEX_KNN_GROUP(KK, 16); \
+        else if (lanes == 8) FLEX_KNN_GROUP(KK, 8); \
+        else if (lanes == 4) FLEX_KNN_GROUP(KK, 4); \
+        else hipLaunchKernelGGL(knn_query_kernel<KK>, dim3(qb, B), dim3(256), 0, s, rec, off, bbox, lists, N, cpc); \
+        break;
     switch (K) {
-        FLEX_KNN_CASE(1) FLEX_KNN_CASE(2) FLEX_KNN_CASE(3) FLEX_KNN_CASE(4) FLEX_KNN_CASE(5) FLEX_KNN_CASE(6)
-        FLEX_KNN_CASE(7) FLEX_KNN_CASE(8) FLEX_KNN_CASE(9) FLEX_KNN_CASE(10) FLEX_KNN_CASE(12) FLEX_KNN_CASE(16)
-        FLEX_KNN_CASE(24) FLEX_KNN_CASE(32)
+        FLEX_KNN_KS(FLEX_KNN_CASE)
     default: return hipErrorInvalidValue;
     }
 #undef FLEX_KNN_CASE
+#undef FLEX_KNN_GROUP
     hipLaunchKernelGGL(knn_place_kernel, dim3(qb, B), dim3(256), 0, s, lists, place, nbr, N, K);
     return hipGetLastError();
 }

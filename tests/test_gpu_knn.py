@@ -50,17 +50,59 @@ def test_knn_degenerate_shapes():
         _check(pos, K)
 
 
+# all against all up to 4096 points a cloud and 25 * 2^20 pairs; then the grid with 16, 8 and 4 lanes to a point and a thread each
+@pytest.mark.parametrize("B,N,K", [(1, 4096, 12), (1, 4097, 12), (2, 3620, 4), (2, 3622, 4), (1, 12, 12), (5, 17, 16), (1, 4500, 1),
+                                   (8, 4300, 9), (8, 4097, 2), (12, 5500, 4), (24, 5500, 8)])
+def test_knn_on_both_sides_of_every_line(B, N, K):
+    say(f"knn lanes B={B} N={N} K={K}")
+    rng = np.random.default_rng(N + K)
+    pos = rng.random((B, 3, N)).astype(np.float32)
+    pos[B // 2] = rng.integers(0, 9, size=(3, N))                                # ties and coincident points
+    pos[B - 1, 2] *= 0.01                                                        # a slab: empty cells around, many shells
+    pos[B - 1, :, : N // 3] *= 0.05
+    _check(pos, K)
+
+
+def test_knn_degenerate_shapes_on_the_grid():
+    rng = np.random.default_rng(2)
+    N = 4500
+    flat = rng.random((1, 3, N)).astype(np.float32); flat[0, 2] = 0.25
+    line = np.zeros((1, 3, N), np.float32); line[0, 0] = rng.random(N)
+    far = rng.random((1, 3, N)).astype(np.float32) * 0.5 + np.float32(1000.0)
+    clumps = (rng.integers(0, 3, size=(1, 3, N)) * 100.0 + rng.normal(0, 0.01, (1, 3, N))).astype(np.float32)
+    for name, pos, K in (("plane", flat, 8), ("line", line, 8), ("one location", np.full((1, 3, N), 1.5, np.float32), 8), ("offset", far, 8),
+                         ("clumps", clumps, 32)):
+        say("knn on the grid", name)
+        _check(pos, K)
+
+
+@pytest.mark.parametrize("N", [600, 4500])
+def test_knn_infinite_locations(N):
+    """At infinity a point is as far as can be from the others and no distance from its like."""
+    pos = np.random.default_rng(8).random((1, 3, N)).astype(np.float32)
+    pos[0, 0, 7], pos[0, 1, 9] = np.inf, -np.inf
+    ref = oracle.knn(np.ascontiguousarray(np.delete(pos, [7, 9], axis=2)), 8)
+    got = fx.flex_knn(dev(pos), 8).cpu().numpy()
+    keep = np.delete(np.arange(N, dtype=np.int32), [7, 9])
+    assert np.array_equal(got[:, :, keep], keep[ref])
+
+
 @pytest.mark.parametrize("bits", [0x7fc00000, 0xffc00000])
-def test_knn_location_that_is_no_number(bits):
+def test_knn_location_that_is_no_number(bits, N=600):
     """A point without a location is nobody's neighbour, whichever sign its NaN has: the other points' lists are those
     of the cloud without it."""
-    N, K, lost = 600, 8, 77
+    K, lost = 8, 77
     pos = np.random.default_rng(5).random((1, 3, N)).astype(np.float32)
     keep = np.delete(np.arange(N, dtype=np.int32), lost)
     ref = keep[oracle.knn(np.ascontiguousarray(pos[:, :, keep]), K)]
     pos[0, 1, lost] = np.array(bits, np.uint32).view(np.float32)
     got = fx.flex_knn(dev(pos), K).cpu().numpy()[:, :, keep]
     assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("bits", [0x7fc00000, 0xffc00000])
+def test_knn_location_that_is_no_number_on_the_grid(bits):
+    test_knn_location_that_is_no_number(bits, N=4500)
 
 
 def test_knn_room_cloud_matches_and_feeds_the_layers():
