@@ -172,7 +172,23 @@ __global__ __launch_bounds__(256) void idiss_running_sum_kernel(const float *__r
     }
 }
 
-// sel[b][j] = first point whose running sum exceeds the threshold of stratum j
+// The draw of stratum j: the first point whose running sum exceeds its threshold.  sum(l): the inclusive running sum of point l; Q: the last.
+template <class Sum>
+__device__ __forceinline__ int idiss_pick(Sum &&sum, unsigned long long Q, uint32_t u, int j, int N, int Ns)
+{
+    const unsigned long long width = Q / (unsigned long long)Ns, rem = Q % (unsigned long long)Ns;
+    const unsigned long long jj = (unsigned long long)j;
+    const unsigned long long start = jj * width + (jj < rem ? jj : rem);
+    const unsigned long long len = width + (jj < rem ? 1u : 0u);
+    const unsigned long long t = start + __umul64hi((unsigned long long)u << 32, len);
+    int lo = 0, hi = N - 1;            // Q > t, so the last point always qualifies
+    while (lo < hi) {
+        const int mid = lo + ((hi - lo) >> 1);
+        if (sum(mid) > t) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+
 __global__ __launch_bounds__(256) void idiss_select_kernel(const unsigned long long *__restrict__ C,
                                                            const unsigned long long *__restrict__ bsum,
                                                            const uint32_t *__restrict__ u, int32_t *__restrict__ sel,
@@ -180,20 +196,66 @@ __global__ __launch_bounds__(256) void idiss_select_kernel(const unsigned long l
 {
     const int b = blockIdx.y;
     const unsigned long long Q = bsum[(int64_t)b * (nblk + 1) + nblk];
-    const unsigned long long width = Q / (unsigned long long)Ns, rem = Q % (unsigned long long)Ns;
     const unsigned long long *Cb = C + (int64_t)b * N;
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < Ns; j += gridDim.x * blockDim.x) {
-        const unsigned long long jj = (unsigned long long)j;
-        const unsigned long long start = jj * width + (jj < rem ? jj : rem);
-        const unsigned long long len = width + (jj < rem ? 1u : 0u);
-        const unsigned long long t = start + __umul64hi((unsigned long long)u[(int64_t)b * Ns + j] << 32, len);
-        int lo = 0, hi = N - 1;            // Q > t, so the last point always qualifies
-        while (lo < hi) {
-            const int mid = lo + ((hi - lo) >> 1);
-            if (Cb[mid] > t) hi = mid; else lo = mid + 1;
-        }
-        sel[(int64_t)b * Ns + j] = lo;
+    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < Ns; j += gridDim.x * blockDim.x)
+        sel[(int64_t)b * Ns + j] = idiss_pick([&](int l) { return Cb[l]; }, Q, u[(int64_t)b * Ns + j], j, N, Ns);
+}
+
+// Clouds of up to IDISS_SMALL points: one workgroup per cloud, maximum, running sums (in LDS) and draw in one launch where the
+// steps above are six.  What bounds either is the chain of launches and block-wide steps: 1k points 23.6 us, here 9.6; 16k 23.7 and 12.3.
+static constexpr int IDISS_SMALL_NT = 1024, IDISS_SMALL_ITEMS = 16, IDISS_SMALL = IDISS_SMALL_NT * IDISS_SMALL_ITEMS;
+// a place in an array that 16 consecutive entries of belong to a thread: one in seventeen is left out, for the banks
+__device__ __forceinline__ int small_at(int i) { return i + (i >> 4); }
+
+__global__ __launch_bounds__(IDISS_SMALL_NT) void idiss_sample_small_kernel(const float *__restrict__ phi, const uint32_t *__restrict__ u,
+                                                                            int32_t *__restrict__ sel, int N, int Ns, int bits)
+{
+    extern __shared__ unsigned long long s_C[];                  // inclusive running sums of the quanta, small_at(N)
+    __shared__ unsigned long long s_wave[IDISS_SMALL_NT / 64];
+    __shared__ unsigned s_max[IDISS_SMALL_NT / 64];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    float x[IDISS_SMALL_ITEMS];
+    unsigned m = 0;                                              // phi >= 0: the float order is the order of the bit patterns
+#pragma unroll
+    for (int i = 0; i < IDISS_SMALL_ITEMS; ++i) {
+        const int l = tid + IDISS_SMALL_NT * i;
+        x[i] = l < N ? phi[(int64_t)b * N + l] : 0.f;
     }
+#pragma unroll
+    for (int i = 0; i < IDISS_SMALL_ITEMS; ++i) m = max(m, __float_as_uint(x[i]));
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, d, 64));
+    if (lane == 0) s_max[w] = m;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < IDISS_SMALL_NT / 64; ++i) m = max(m, s_max[i]);
+#pragma unroll
+    for (int i = 0; i < IDISS_SMALL_ITEMS; ++i) {
+        const int l = tid + IDISS_SMALL_NT * i;
+        if (l < N) s_C[small_at(l)] = idiss_quantum(x[i], __uint_as_float(m), bits);
+    }
+    __syncthreads();
+    const int l0 = tid * IDISS_SMALL_ITEMS;
+    unsigned long long sum = 0;
+    for (int i = 0; i < IDISS_SMALL_ITEMS && l0 + i < N; ++i) sum += s_C[small_at(l0 + i)];
+    unsigned long long run = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned long long y = __shfl_up(run, d, 64);
+        if (lane >= d) run += y;
+    }
+    if (lane == 63) s_wave[w] = run;
+    __syncthreads();
+    run -= sum;
+    for (int i = 0; i < w; ++i) run += s_wave[i];
+    for (int i = 0; i < IDISS_SMALL_ITEMS && l0 + i < N; ++i) {
+        run += s_C[small_at(l0 + i)];
+        s_C[small_at(l0 + i)] = run;
+    }
+    __syncthreads();
+    const unsigned long long Q = s_C[small_at(N - 1)];
+    for (int j = tid; j < Ns; j += IDISS_SMALL_NT)
+        sel[(int64_t)b * Ns + j] = idiss_pick([&](int l) { return s_C[small_at(l)]; }, Q, u[(int64_t)b * Ns + j], j, N, Ns);
 }
 
 // ---- repeats removed from an ascending selection ---------------------------------------------
@@ -281,10 +343,45 @@ __global__ __launch_bounds__(256) void distinct_apply_kernel(int32_t *__restrict
     }
 }
 
+// Up to IDISS_SMALL kept points a cloud: the same in one launch, a workgroup per cloud (256 of them 12.9 us, here 7.2; 7.5k 12.7 and 7.1).
+__global__ __launch_bounds__(IDISS_SMALL_NT) void distinct_small_kernel(int32_t *__restrict__ sel, int N, int Ns)
+{
+    extern __shared__ int s_v[];                                 // sel[j] - j, small_at(Ns)
+    __shared__ int s_wave[IDISS_SMALL_NT / 64];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    int32_t *mine = sel + (int64_t)b * Ns;
+    for (int j = tid; j < Ns; j += IDISS_SMALL_NT) s_v[small_at(j)] = mine[j] - j;
+    __syncthreads();
+    const int j0 = tid * IDISS_SMALL_ITEMS;
+    int most = INT_MIN;
+    for (int i = 0; i < IDISS_SMALL_ITEMS && j0 + i < Ns; ++i) most = max(most, s_v[small_at(j0 + i)]);
+    int run = most;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(run, d, 64);
+        if (lane >= d) run = max(run, y);
+    }
+    if (lane == 63) s_wave[w] = run;
+    run = __shfl_up(run, 1, 64);                                 // of the threads before
+    if (lane == 0) run = INT_MIN;
+    __syncthreads();
+    for (int i = 0; i < w; ++i) run = max(run, s_wave[i]);
+    for (int i = 0; i < IDISS_SMALL_ITEMS && j0 + i < Ns; ++i) {
+        run = max(run, s_v[small_at(j0 + i)]);
+        s_v[small_at(j0 + i)] = run;
+    }
+    __syncthreads();
+    for (int j = tid; j < Ns; j += IDISS_SMALL_NT) mine[j] = min(s_v[small_at(j)], N - Ns) + j;
+}
+
 size_t distinct_ws_bytes(int B, int Ns) { return align256(sizeof(int) * (size_t)B * cdiv64(Ns, IDISS_CHUNK)); }
 
 hipError_t launch_selection_make_distinct(int32_t *sel, int B, int N, int Ns, void *ws, hipStream_t s)
 {
+    if (Ns <= IDISS_SMALL) {
+        hipLaunchKernelGGL(distinct_small_kernel, dim3(B), dim3(IDISS_SMALL_NT), sizeof(int) * (Ns + Ns / 16 + 1), s, sel, N, Ns);
+        return hipGetLastError();
+    }
     const int nblk = (int)cdiv64(Ns, IDISS_CHUNK);
     int *cm = (int *)ws;
     hipLaunchKernelGGL(distinct_chunk_max_kernel, dim3(nblk, B), dim3(256), 0, s, sel, cm, Ns, nblk);
@@ -330,6 +427,11 @@ hipError_t launch_idiss_sample(const float *phi, const uint32_t *u, int32_t *sel
                                hipStream_t s)
 {
     const int nblk = idiss_nblk(N), bits = idiss_bits(N);
+    if (N <= IDISS_SMALL) {
+        const size_t lds = sizeof(unsigned long long) * (size_t)(N + N / 16 + 1);
+        hipLaunchKernelGGL(idiss_sample_small_kernel, dim3(B), dim3(IDISS_SMALL_NT), lds, s, phi, u, sel, N, Ns, bits);
+        return hipGetLastError();
+    }
     unsigned long long *C = (unsigned long long *)ws;
     unsigned long long *bsum = (unsigned long long *)((char *)ws + align256(sizeof(unsigned long long) * (size_t)B * N));
     unsigned *mx = (unsigned *)((char *)bsum + align256(sizeof(unsigned long long) * (size_t)B * (nblk + 1)));

@@ -3,7 +3,7 @@
 // result does not depend on the order in which atomics land (and so that
 // repeated sources sit next to each other).
 //
-// Two ways.  Up to EDGE_BUCKETS_MAX buckets (16384 << bucket_shift(K) points, 16.7 M
+// Small clouds: one launch (edge_small_kernel).  Else two ways.  Up to EDGE_BUCKETS_MAX buckets (16384 << bucket_shift(K) points, 16.7 M
 // at K = 8): edges are first dealt into buckets of consecutive target points, then
 // each bucket is sorted in LDS by one workgroup.  Global atomics per (workgroup, bucket) instead of per edge:
 // a random-address atomic per edge (twice) and the scattered 4-byte writes behind
@@ -576,6 +576,99 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_sort_kernel(const int32_t *__r
     for (int i = tid; i < targets; i += BUCKET_NT) sort_list(in_src + beg + s_off[i], s_off[i + 1] - s_off[i]);
 }
 
+// Small clouds, one launch: a workgroup owns a stretch of consecutive targets of one cloud and walks all of that cloud's edges
+// twice, counting its own and those of earlier targets (which gives its lists' place), then taking its own to LDS; the lists
+// are ordered as above.  The five launches in its place are what such a cloud waits for.  No edge of another cloud names its targets.
+static constexpr int SMALL_CAP = 8192;                           // edges a workgroup orders in LDS (four times the average)
+
+__global__ __launch_bounds__(BUCKET_NT) void edge_small_kernel(const EdgeRuns p, int per_cloud, int targets,
+                                                               int32_t *__restrict__ in_off, int32_t *__restrict__ in_src, int64_t BN)
+{
+    __shared__ int s_off[BUCKET_TARGETS_MAX + 1], s_cur[BUCKET_TARGETS_MAX];      // list starts inside the stretch, next places
+    __shared__ int s_src[SMALL_CAP];
+    __shared__ uint16_t s_tgt[SMALL_CAP];
+    __shared__ int s_wave[BUCKET_NT / 64], s_before;
+    constexpr int UN = 8;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int b = blockIdx.x / per_cloud, t0 = (int)(blockIdx.x - b * per_cloud) * targets, nt = min(targets, p.N - t0);
+    const int edges = p.K * p.Nc;
+    const int64_t first = (int64_t)b * edges;
+    for (int i = tid; i < targets; i += BUCKET_NT) s_cur[i] = 0;
+    if (tid == 0) s_before = 0;
+    __syncthreads();
+    // take(t, j): edge of centre j to the stretch's target t; earlier targets' edges are counted
+    auto walk = [&](auto &&take) {
+        int earlier = 0;
+        EdgeWalk w(p, first + min(tid, edges - 1));
+        for (int e0 = 0; e0 < edges; e0 += BUCKET_NT * UN) {
+            int t[UN], j[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const bool on = e0 + BUCKET_NT * u + tid < edges;
+                t[u] = on ? w.target(p) - b * p.N - t0 : nt;
+                j[u] = w.j;
+                if (e0 + BUCKET_NT * (u + 1) + tid < edges) w.next(p);
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                earlier += t[u] < 0;
+                if (t[u] >= 0 && t[u] < nt) take(t[u], j[u]);
+            }
+        }
+        return earlier;
+    };
+    {
+        int earlier = walk([&](int t, int) { atomicAdd(&s_cur[t], 1); });
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) earlier += __shfl_xor(earlier, d, 64);
+        if (lane == 0 && earlier) atomicAdd(&s_before, earlier);
+    }
+    __syncthreads();
+    const int64_t beg = first + s_before;
+    {   // counts -> list starts, two targets per thread
+        const int i0 = 2 * tid;
+        const int a = i0 < nt ? s_cur[i0] : 0, c = i0 + 1 < nt ? s_cur[i0 + 1] : 0;
+        int x = a + c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(x, d, 64);
+            if (lane >= d) x += y;
+        }
+        if (lane == 63) s_wave[wave] = x;
+        __syncthreads();
+        int run = x - (a + c);
+        for (int w = 0; w < wave; ++w) run += s_wave[w];
+        if (i0 < nt) { s_off[i0] = s_cur[i0] = run; in_off[(int64_t)b * p.N + t0 + i0] = (int)(beg + run); }
+        if (i0 + 1 < nt) { s_off[i0 + 1] = s_cur[i0 + 1] = run + a; in_off[(int64_t)b * p.N + t0 + i0 + 1] = (int)(beg + run + a); }
+        if (tid == BUCKET_NT - 1) {
+            s_off[nt] = run + a + c;
+            if (blockIdx.x == gridDim.x - 1) in_off[BN] = p.E;
+        }
+    }
+    __syncthreads();
+    const int n = s_off[nt];
+    const bool fits = n <= SMALL_CAP;
+    walk([&](int t, int j) {
+        const int at = atomicAdd(&s_cur[t], 1);
+        if (fits) { s_src[at] = j; s_tgt[at] = (uint16_t)t; }
+        else in_src[beg + at] = j;
+    });
+    __syncthreads();                              // (the workgroup's own writes, read back below)
+    if (!fits) {
+        for (int i = tid; i < nt; i += BUCKET_NT) sort_list(in_src + beg + s_off[i], s_off[i + 1] - s_off[i]);
+        return;
+    }
+    for (int me = tid; me < n; me += BUCKET_NT) {
+        const int src = s_src[me], lo = s_off[s_tgt[me]], hi = s_off[s_tgt[me] + 1];
+        int r = lo;
+        for (int i = lo; i < hi; ++i) {
+            const int o = s_src[i];
+            r += (o < src || (o == src && i < me)) ? 1 : 0;
+        }
+        in_src[beg + r] = src;
+    }
+}
+
 // the bucketed way's geometry; buckets == 0: too many of them
 static int bucket_shift(int K)
 {
@@ -605,6 +698,20 @@ size_t inedges_ws_bytes(int64_t BN, int K)
     return align256(sizeof(int32_t) * (size_t)BN) + align256(sizeof(int32_t) * (size_t)(nblk + 1));
 }
 
+// Targets a workgroup of the one-launch build owns; 0: the cloud is not for it.  Every workgroup of a cloud walks all of its edges, so
+// those are at most 2^15, and 2^15 a CU over all workgroups; more than 2048 workgroups are a launch longer than five.  us, five launches
+// and one, K = 8: 300 points 20 and 11, 2048 27 and 16, 4096 27 and 23.5, 1024 with K = 16 34 and 18, 100 x 300 29 and 11, 30 x 2000 31 and
+// 16, 30 x 4096 34 and 32, 60 x 4096 41 and 65, 2000 x 300 89 and 65, 3000 x 64 47 and 56.
+static int small_targets(int64_t B, int64_t N, int64_t Nc, int K)
+{
+    const int64_t edges = K * Nc, cus = device_cu_count();
+    if (bucket_count(B * N, K) == 0 || edges > 1 << 15) return 0;
+    const int64_t own = B * edges > 2048 * cus ? 4096 : 2048;
+    const int64_t targets = own / K < 1 ? 1 : own / K < BUCKET_TARGETS_MAX ? own / K : BUCKET_TARGETS_MAX;
+    const int64_t groups = B * cdiv64(N, targets);
+    return groups <= 2048 && groups * edges <= cus << 15 ? (int)targets : 0;
+}
+
 hipError_t launch_inedges_build(const int32_t *nbr, int B, int N, int K, int32_t *in_off,
                                 int32_t *in_src, void *ws, hipStream_t s)
 {
@@ -617,6 +724,13 @@ hipError_t launch_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int 
                                     int32_t *in_off, int32_t *in_src, void *ws, hipStream_t s)
 {
     const int64_t BN = (int64_t)B * N, KN = (int64_t)K * N, E = (int64_t)B * K * (sel ? Ns : N);
+    if (const int targets = small_targets(B, N, sel ? Ns : N, K)) {
+        const int per_cloud = (int)cdiv64(N, targets);
+        const EdgeRuns p{nbr, sel, N, sel ? Ns : N, K, (int)E, 0, 0};
+        hipLaunchKernelGGL(edge_small_kernel, dim3((unsigned)((int64_t)B * per_cloud)), dim3(BUCKET_NT), 0, s, p, per_cloud, targets, in_off,
+                           in_src, BN);
+        return hipGetLastError();
+    }
     if (const int buckets = (int)bucket_count(BN, K)) {
         int32_t *cnt = (int32_t *)ws, *off = cnt + buckets, *cur = off + buckets + 1;
         int32_t *st_src = (int32_t *)((char *)ws + align256(sizeof(int32_t) * (size_t)(3 * buckets + 1)));

@@ -69,6 +69,12 @@ def test_draw_is_bit_exact(B, N, Ns):
     assert np.array_equal(_draw(phi, u), oracle.idiss_sample(phi, u))
 
 
+@pytest.mark.parametrize("B,N,Ns", [(1, 1, 1), (5, 17, 16), (2, 1025, 1025), (3, 16384, 16384), (2, 16383, 4097), (1, 16385, 16385)])
+def test_draw_and_distinct_around_what_a_workgroup_holds(B, N, Ns):
+    test_draw_is_bit_exact(B, N, Ns)
+    test_make_distinct_is_bit_exact(B, N, Ns)
+
+
 def test_draw_degenerate_clouds():
     rng = np.random.default_rng(7)
     u = _words(rng, 2, 64)

@@ -51,6 +51,30 @@ def test_hub_points_past_a_buckets_lds():
     check(nbr)
 
 
+# the one-launch build of small clouds: both sides of its lines (2^15 edges a cloud, 2048 workgroups), stretches of one target and of
+# many, lists past what a workgroup orders in LDS, kept centres of which some name no point
+@pytest.mark.parametrize("B,N,K", [(1, 4096, 8), (1, 4097, 8), (3, 257, 9), (1, 2100, 1), (1, 180, 170), (2, 2600, 7), (2048, 16, 3), (2049, 16, 3), (1, 2, 2)])
+def test_small_clouds(B, N, K):
+    say(f"in-edges of small clouds B={B} N={N} K={K}")
+    rng = np.random.default_rng(B + N)
+    nbr = rng.integers(0, N, size=(B, K, N)).astype(np.int32)
+    nbr[:, -1] = N // 2                                          # a hub in every cloud
+    check(nbr)
+    sel = rng.integers(-1, N + 1, size=(B, (N + 3) // 4)).astype(np.int32)
+    got = fx.flex_inedges_build_sub(dev(nbr), dev(sel))
+    torch.cuda.synchronize()
+    for a, b in zip(got, lists(nbr, np.clip(sel, 0, N - 1))):
+        assert np.array_equal(a.cpu().numpy(), b)
+
+
+def test_hub_point_of_a_small_cloud():
+    rng = np.random.default_rng(3)
+    nbr = rng.integers(0, 4000, size=(2, 8, 4000)).astype(np.int32)
+    nbr[1, 2:5] = 11                                             # 12 000 entries in one list
+    nbr[1, 5, :300] = 12
+    check(nbr)
+
+
 def test_kept_centres():
     rng = np.random.default_rng(2)
     nbr = rng.integers(0, 5000, size=(2, 8, 5000)).astype(np.int32)
