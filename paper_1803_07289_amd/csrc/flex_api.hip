@@ -339,15 +339,16 @@ static int narrow_rp(int w_in) { return w_in <= 8 ? 8 : 16; }
 static int narrow_blocks(int w_out) { return (w_out + 63) / 64; }
 static size_t narrow_bytes(int w_in, int w_out) { return (size_t)narrow_blocks(w_out) * theta_f16_bytes(narrow_rp(w_in), 64); }
 
+// theta: packed; bias not null (forward, no records): theta and bias are the tensors, which the kernel's waves pack themselves
 // rec (null: none): the rows' records, the fourth channels of four-channel quads behind them
 static hipError_t narrow_launch(const float *rows, int rs, int w_in, const float *pos, const float *rec, const int32_t *nbr,
-                                const int32_t *off, const int32_t *src, const int32_t *order, const void *theta,
+                                const int32_t *off, const int32_t *src, const int32_t *order, const void *theta, const float *bias,
                                 float *out, int w_out, int out_bcn, int B, int N, int K, hipStream_t s)
 {
     const int rp = narrow_rp(w_in), n_out = narrow_blocks(w_out);
     TileArgs a{};
     a.rows = rows; a.pos = pos; a.nbr = nbr; a.off = off; a.src = src; a.order = order;
-    a.theta = (const char *)theta; a.out = out;
+    a.theta = (const char *)theta; a.bias = bias; a.out = out;
     a.out_c = out_bcn ? N : 1; a.out_l = out_bcn ? 1 : w_out; a.out_b = (int64_t)N * w_out;
     a.rs = rs; a.w_in = w_in; a.w_out = w_out;
     a.blk_bytes = (int)theta_f16_bytes(rp, 64);
@@ -441,7 +442,7 @@ static hipError_t gather_launch(const GatherPlan &g, const float *rows, int rs, 
                                 hipStream_t s)
 {
     if (g.route == FLEX_ROUTE_NARROW)
-        return narrow_launch(rows, rs, w_in, pos, packed, nbr, off, src, order, thetaP, out, w_out, out_bcn, B, N, K, s);
+        return narrow_launch(rows, rs, w_in, pos, packed, nbr, off, src, order, thetaP, nullptr, out, w_out, out_bcn, B, N, K, s);
     if (g.route == FLEX_ROUTE_TILE)
         return tile_launch(g.tile, rows, rs, w_in, pos, nbr, off, src, order, thetaP, out, w_out, out_bcn, B, N, K, s);
     return launch_gather_contract(rows, pos, pos_ref(pos, packed, N), nbr, off, src, order, thetaP, g.fmt, out, B, N, K, rs, w_out, off != nullptr,
@@ -819,6 +820,10 @@ int flexconv_fwd(const float *feat, const float *pos, const int32_t *nbr, const 
     if (p.copy && !records) {
         prep.copy(feat, (float *)(ws + p.rows), B, N, Din, w_in, bcn, 0);
         rows = (const float *)(ws + p.rows);
+    }
+    if (p.gather.route == FLEX_ROUTE_NARROW && !records && !p.copy) {       // nothing to prepare but the parameters
+        FLEX_HIP(narrow_launch(feat, Din, Din, pos, nullptr, nbr, nullptr, nullptr, nullptr, theta, bias, out, Dout, 0, B, N, K, s));
+        return FLEX_OK;
     }
     void *thetaP = ws + p.thetaP;
     FLEX_HIP(gather_pack(prep, p.gather, theta, bias, thetaP, Din, Dout, p.k_in, p.k_out, 0, s));

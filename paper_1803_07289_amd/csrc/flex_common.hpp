@@ -177,6 +177,7 @@ struct TileArgs {
     const float *rows, *pos;
     const int32_t *nbr, *off, *src, *order;
     const char *theta;           // packed blocks [output block][input block]
+    const float *bias;           // null; or theta is the tensor [3, w_in, w_out], this one [w_in, w_out] (narrow_conv_kernel)
     float *out;
     int64_t out_c, out_l, out_b; // output strides: channel, point, cloud
     int rs, w_in, w_out;         // row stride (floats), real widths

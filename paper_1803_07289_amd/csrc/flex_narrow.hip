@@ -41,7 +41,89 @@ __device__ __forceinline__ void load_narrow(__amdgpu_buffer_rsrc_t rows, unsigne
     if constexpr (R & 1) f[W - 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, (int)(offset + 4u * (W - 1)), 0, 0));
 }
 
-template <int W, bool CSR>
+// A wave packs the parameters of an output block for itself, as pack_slice does (flex_prep.hip): the rows' scales to LDS, the
+// fragments and column exponents to registers, the same bits.  What it costs, some 600 instructions a wave, is less than a launch in
+// front of the kernel costs a call.  us, with that launch and here, called one after another (replayed from a graph): 9 -> 64, K = 8, 1024
+// points 15.2 and 12.3 (10.5 and 9.8), 100k 18.8 and 17.2; 3 -> 32, 300 points 15.2 and 12.2 (9.2 and 5.9), 500k 31.0 and 27.9.
+template <int W>
+struct OwnParameters {
+    static constexpr int RP = W <= 8 ? 8 : 16, KS = W <= 8 ? 1 : 2, NS = 4;
+    float y[NS][KS][8];
+    // a.theta, a.bias: the tensors; output block j
+    __device__ __forceinline__ void request(const TileArgs &a, int j)
+    {
+        const int lane = threadIdx.x, q = lane >> 4, r16 = lane & 15;
+#pragma unroll
+        for (int st = 0; st < KS; ++st) {
+            // eight rows of one component: kd = 32 * st + 8 * q ..
+            const int jj = (32 * st + 8 * q) / RP, r0 = 8 * q % RP;
+            const float *rows = jj < 3 ? reinterpret_cast<const float *>(a.theta) + (int64_t)jj * W * a.w_out : a.bias;
+#pragma unroll
+            for (int n = 0; n < NS; ++n) {
+                const int col = 64 * j + 16 * n + r16;
+                const float *at = rows + min(col, a.w_out - 1);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[n][st][e] = at[min(r0 + e, W - 1) * a.w_out];      // past the tensor: a place inside it
+            }
+        }
+        // all of them are asked for before any is looked at
+#pragma unroll
+        for (int st = 0; st < KS; ++st)
+#pragma unroll
+            for (int n = 0; n < NS; ++n)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    asm volatile("" : "+v"(y[n][st][e]));
+                    if (!(8 * q % RP + e < W && 64 * j + 16 * n + r16 < a.w_out)) y[n][st][e] = 0.f;
+                }
+    }
+    __device__ __forceinline__ void pack(h8 (&tH)[NS][KS], h8 (&tL)[NS][KS], v4i (&ec)[NS], float *s_rs)
+    {
+        const int lane = threadIdx.x, q = lane >> 4, r16 = lane & 15;
+        auto finite = [](float m, float x) {             // non-finite entries do not count
+            const float v = __builtin_fabsf(x);
+            return v < __builtin_inff() && v > m ? v : m;
+        };
+#pragma unroll
+        for (int st = 0; st < KS; ++st)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float m = 0.f;
+#pragma unroll
+                for (int n = 0; n < NS; ++n) m = finite(m, y[n][st][e]);
+                m = group_max<16>(m);
+                const int er = m > 0.f ? min(max(-__builtin_amdgcn_frexp_expf(m), -60), 60) : 0;
+#pragma unroll
+                for (int n = 0; n < NS; ++n) y[n][st][e] = __builtin_ldexpf(y[n][st][e], er);
+                if (r16 == 0) s_rs[32 * st + 8 * q + e] = __builtin_ldexpf(1.f, -er);
+            }
+#pragma unroll
+        for (int n = 0; n < NS; ++n) {
+            float m = 0.f;
+#pragma unroll
+            for (int st = 0; st < KS; ++st)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m = finite(m, y[n][st][e]);
+            m = fmaxf(m, __shfl_xor(m, 16, 64));
+            m = fmaxf(m, __shfl_xor(m, 32, 64));
+            const int x = m > 0.f ? 15 - __builtin_amdgcn_frexp_expf(m) : 0;
+#pragma unroll
+            for (int st = 0; st < KS; ++st)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float v = __builtin_ldexpf(y[n][st][e], x);
+                    tH[n][st][e] = (_Float16)v;
+                    tL[n][st][e] = (_Float16)(v - (float)tH[n][st][e]);
+                }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ec[n][i] = __shfl(x, 4 * q + i, 64);
+        }
+        wave_lds_sync();
+    }
+};
+
+// RAW: the parameters come as the caller has them (OwnParameters)
+template <int W, bool CSR, bool RAW>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void narrow_conv_kernel(const TileArgs a)
 {
@@ -57,8 +139,14 @@ void narrow_conv_kernel(const TileArgs a)
     const int lane = threadIdx.x, q = lane >> 4, r16 = lane & 15;
     const char *blk = a.theta + (int64_t)j * a.blk_bytes;
     const float *rscale = reinterpret_cast<const float *>(blk + a.rs_off);
+    __shared__ float s_rs[RAW ? KD : 1];
     h8 tH[NS][KS], tL[NS][KS];
     v4i ec[NS];
+    if constexpr (RAW) {
+        OwnParameters<W> own;
+        own.request(a, j);
+        own.pack(tH, tL, ec, s_rs);
+    } else
 #pragma unroll
     for (int n = 0; n < NS; ++n) {
 #pragma unroll
@@ -131,7 +219,7 @@ void narrow_conv_kernel(const TileArgs a)
         for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
             for (int i = 0; i < W; ++i) {
-                acc[jj][i] *= rscale[jj * RP + i];
+                acc[jj][i] *= RAW ? s_rs[jj * RP + i] : rscale[jj * RP + i];
                 m = __builtin_amdgcn_fmed3f(m, __builtin_fabsf(acc[jj][i]), __builtin_inff());
             }
         const int ex = 15 - __builtin_amdgcn_frexp_expf(m);
@@ -417,7 +505,10 @@ hipError_t FLEX_NARROW_NAME(launch_narrow_, FLEX_NARROW_CSR)(const TileArgs &a, 
     constexpr bool CSR = FLEX_NARROW_CSR != 0;
     switch (a.w_in) {
 #define FLEX_NARROW_CASE(W) \
-    case W: hipLaunchKernelGGL((narrow_conv_kernel<W, CSR>), dim3(grid), dim3(64), 0, s, a); break;
+    case W: \
+        if constexpr (!CSR) if (a.bias != nullptr) { hipLaunchKernelGGL((narrow_conv_kernel<W, CSR, true>), dim3(grid), dim3(64), 0, s, a); break; } \
+        hipLaunchKernelGGL((narrow_conv_kernel<W, CSR, false>), dim3(grid), dim3(64), 0, s, a); \
+        break;
         FLEX_NARROW_CASE(1) FLEX_NARROW_CASE(2) FLEX_NARROW_CASE(3) FLEX_NARROW_CASE(4) FLEX_NARROW_CASE(5)
         FLEX_NARROW_CASE(6) FLEX_NARROW_CASE(7) FLEX_NARROW_CASE(8) FLEX_NARROW_CASE(9) FLEX_NARROW_CASE(10)
         FLEX_NARROW_CASE(11) FLEX_NARROW_CASE(12) FLEX_NARROW_CASE(13) FLEX_NARROW_CASE(14) FLEX_NARROW_CASE(15)
