@@ -205,8 +205,6 @@ hipError_t launch_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int 
                                     int32_t *in_off, int32_t *in_src, void *ws, hipStream_t s);
 size_t inedges_ws_bytes(int64_t BN, int K);
 size_t inedges_order_bytes(int64_t BN);
-size_t exclusive_scan_ws_bytes(int64_t n);
-hipError_t launch_exclusive_scan_i32(const int32_t *cnt, int32_t *off, int64_t n, void *ws, hipStream_t s);
 size_t knn_ws_bytes(int B, int N, int K);
 bool knn_k_supported(int K);
 hipError_t launch_knn(const float *pos, int32_t *nbr, int B, int N, int K, void *ws, hipStream_t s);

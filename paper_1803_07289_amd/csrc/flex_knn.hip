@@ -4,8 +4,8 @@
 // ((dx*dx + dy*dy) + dz*dz) with every operation rounded on its own, the form the CPU check uses, so
 // that the ranking (an integer-valued decision) comes out identical.
 //
-// Steps per call: bounding box of each cloud -> grid of cubic cells (at most 2^24) -> counting sort
-// of the points by cell (count, scan, fill of (x,y,z,id) records) -> one thread per point, in cell
+// Steps per call: bounding box of each cloud -> grid of cubic cells (at most 2^24) -> (x,y,z,id)
+// records in cell order, by way of buckets of cells (count, scan, deal, sort) -> one thread per point, in that
 // order (several lanes to a point where the points are few), searches the 27 cells around its own, then shell by shell, keeps
 // the K best in registers and stops once the K-th distance is inside the block of cells already searched -> the lists, so
 // far in cell order, go to their places.  Small clouds: every point against all of its cloud, in one launch.
@@ -43,14 +43,14 @@ __device__ __forceinline__ float from_ordered_bits(unsigned u)
     return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
 }
 
-// bbox[b][0..2] = min, [3..5] = max, as order-preserving unsigned keys (min starts at ~0, max at 0); the cells' counters
+// bbox[b][0..2] = min, [3..5] = max, as order-preserving unsigned keys (min starts at ~0, max at 0); the buckets' counters
 // start at zero
 __global__ __launch_bounds__(256) void knn_init_kernel(unsigned *__restrict__ bbox, int B, int32_t *__restrict__ cnt,
-                                                       int64_t cells)
+                                                       int64_t buckets)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < 6 * B) bbox[i] = (i % 6 < 3) ? 0xffffffffu : 0u;
-    for (int64_t c = i; c < cells; c += (int64_t)gridDim.x * blockDim.x) cnt[c] = 0;
+    for (int64_t c = i; c < buckets; c += (int64_t)gridDim.x * blockDim.x) cnt[c] = 0;
 }
 
 __global__ __launch_bounds__(1024) void knn_bbox_kernel(const float *__restrict__ pos, unsigned *__restrict__ bbox, int N)
@@ -142,34 +142,184 @@ __device__ __forceinline__ void knn_cell_of(const KnnGrid &g, float x, float y, 
     cz = min(g.n[2] - 1, max(0, (int)((z - g.lo[2]) * g.inv_h)));
 }
 
-// cell[b*N + l] = linear cell of the point, place[b*N + l] = its number among the cell's points (in no set order)
-__global__ __launch_bounds__(256) void knn_count_kernel(const float *__restrict__ pos, const unsigned *__restrict__ bbox,
-                                                        int32_t *__restrict__ cell, int32_t *__restrict__ place,
-                                                        int32_t *__restrict__ cnt, int N, int64_t cells_per_cloud)
+// ---- points in cell order ---------------------------------------------------------------------------------
+// bucket = 2^shift consecutive cells of a cloud.  The points are counted per bucket, dealt into the buckets, and each bucket is put in
+// cell order by one workgroup, which writes its cells' bounds on the way.  Counters are in LDS; a workgroup meets the global ones once
+// per bucket that it has points for.  (A counter per cell in memory: one returning atomic per point, 46 us at 1M points, and a table of
+// 2M counters to clear and to sum, 27.)  us of the whole search, with a counter per cell and so: 1M points of a room in the order drawn
+// 242 and 205, in Z-order 222 and 188, 1.5M of a hall with 12 neighbours 433 and 378, 7M of it 1538 and 1377, a cube of 1M 397 and 363.  Positions that another stream overwrites meanwhile can make the count and the deal differ:
+// places and ids are clamped, so that the answer is wrong then and no more.
+static constexpr int KNN_BUCKETS_MAX = 4096, KNN_DEAL_NT = 1024;
+struct KnnBuckets {
+    int shift, n;                                // n: per cloud
+};
+static KnnBuckets knn_buckets(int64_t cells_per_cloud)
 {
-    const int b = blockIdx.y;
+    int shift = 9;
+    while (cdiv64(cells_per_cloud, (int64_t)1 << shift) > KNN_BUCKETS_MAX) ++shift;
+    return KnnBuckets{shift, (int)cdiv64(cells_per_cloud, (int64_t)1 << shift)};
+}
+
+__device__ __forceinline__ int knn_linear_cell(const KnnGrid &g, float x, float y, float z)
+{
+    int cx, cy, cz;
+    knn_cell_of(g, x, y, z, cx, cy, cz);
+    return (cz * g.n[1] + cy) * g.n[0] + cx;
+}
+
+template <int POINTS>                           // a thread
+__global__ __launch_bounds__(KNN_DEAL_NT) void knn_count_kernel(const float *__restrict__ pos, const unsigned *__restrict__ bbox,
+                                                                int32_t *__restrict__ bucket_cnt, int N, int64_t cells_per_cloud,
+                                                                const KnnBuckets k)
+{
+    __shared__ int s_cnt[KNN_BUCKETS_MAX];
+    const int b = blockIdx.y, tid = threadIdx.x;
+    for (int i = tid; i < k.n; i += KNN_DEAL_NT) s_cnt[i] = 0;
     const KnnGrid g = knn_grid(bbox, b, cells_per_cloud);
     const float *p = pos + (int64_t)b * 3 * N;
-    for (int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; l < N; l += (int64_t)gridDim.x * blockDim.x) {
-        int cx, cy, cz;
-        knn_cell_of(g, p[l], p[(int64_t)N + l], p[2 * (int64_t)N + l], cx, cy, cz);
-        const int c = (cz * g.n[1] + cy) * g.n[0] + cx;
-        cell[(int64_t)b * N + l] = c;
-        place[(int64_t)b * N + l] = atomicAdd(&cnt[b * cells_per_cloud + c], 1);
+    const int64_t l0 = (int64_t)blockIdx.x * (KNN_DEAL_NT * POINTS) + tid;
+    float x[POINTS][3];
+#pragma unroll
+    for (int u = 0; u < POINTS; ++u)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) x[u][d] = p[(int64_t)d * N + min(l0 + KNN_DEAL_NT * u, (int64_t)N - 1)];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < POINTS; ++u)
+        if (l0 + KNN_DEAL_NT * u < N) atomicAdd(&s_cnt[knn_linear_cell(g, x[u][0], x[u][1], x[u][2]) >> k.shift], 1);
+    __syncthreads();
+    for (int i = tid; i < k.n; i += KNN_DEAL_NT)
+        if (s_cnt[i]) atomicAdd(&bucket_cnt[(int64_t)b * k.n + i], s_cnt[i]);
+}
+
+// bucket_off = where the buckets' points begin over all clouds, bucket_cur = a copy for the reservations; a workgroup per cloud
+__global__ __launch_bounds__(1024) void knn_bucket_scan_kernel(const int32_t *__restrict__ cnt, int32_t *__restrict__ off,
+                                                               int32_t *__restrict__ cur, int N, int n)
+{
+    __shared__ int s_wave[16];
+    constexpr int PER = KNN_BUCKETS_MAX / 1024;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int v[PER], sum = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        v[i] = PER * tid + i < n ? cnt[(int64_t)b * n + PER * tid + i] : 0;
+        sum += v[i];
+    }
+    int x = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(x, d, 64);
+        if (lane >= d) x += y;
+    }
+    if (lane == 63) s_wave[wave] = x;
+    __syncthreads();
+    int run = b * N + x - sum;
+    for (int w = 0; w < wave; ++w) run += s_wave[w];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (PER * tid + i < n) { off[(int64_t)b * n + PER * tid + i] = run; cur[(int64_t)b * n + PER * tid + i] = run; }
+        run += v[i];
+    }
+    if (b == (int)gridDim.x - 1 && tid == 1023) off[(int64_t)gridDim.x * n] = (b + 1) * N;
+}
+
+// staged: (x, y, z, id), bucket by bucket in no set order
+template <int POINTS>                           // a thread
+__global__ __launch_bounds__(KNN_DEAL_NT) void knn_deal_kernel(const float *__restrict__ pos, const unsigned *__restrict__ bbox,
+                                                               int32_t *__restrict__ bucket_cur, float4 *__restrict__ st_rec,
+                                                               int N, int64_t cells_per_cloud, const KnnBuckets k)
+{
+    __shared__ int s_cnt[KNN_BUCKETS_MAX];
+    const int b = blockIdx.y, tid = threadIdx.x;
+    for (int i = tid; i < k.n; i += KNN_DEAL_NT) s_cnt[i] = 0;
+    const KnnGrid g = knn_grid(bbox, b, cells_per_cloud);
+    const float *p = pos + (int64_t)b * 3 * N;
+    const int64_t l0 = (int64_t)blockIdx.x * (KNN_DEAL_NT * POINTS) + tid;
+    float x[POINTS][3];
+    int bucket[POINTS], rank[POINTS];
+#pragma unroll
+    for (int u = 0; u < POINTS; ++u)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) x[u][d] = p[(int64_t)d * N + min(l0 + KNN_DEAL_NT * u, (int64_t)N - 1)];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < POINTS; ++u) {
+        bucket[u] = knn_linear_cell(g, x[u][0], x[u][1], x[u][2]) >> k.shift;
+        rank[u] = l0 + KNN_DEAL_NT * u < N ? atomicAdd(&s_cnt[bucket[u]], 1) : 0;
+    }
+    __syncthreads();
+    for (int i = tid; i < k.n; i += KNN_DEAL_NT)
+        if (const int c = s_cnt[i]) s_cnt[i] = atomicAdd(&bucket_cur[(int64_t)b * k.n + i], c);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < POINTS; ++u) {
+        const int64_t l = l0 + KNN_DEAL_NT * u;
+        if (l >= N) continue;
+        st_rec[min(s_cnt[bucket[u]] + rank[u], (int)gridDim.y * N - 1)] = make_float4(x[u][0], x[u][1], x[u][2], __int_as_float((int)l));
     }
 }
 
-// rec[off[cell] + place] = (x, y, z, id); place becomes the record's number inside the cloud
-__global__ __launch_bounds__(256) void knn_fill_kernel(const float *__restrict__ pos, const int32_t *__restrict__ cell,
-                                                       const int32_t *__restrict__ off, int32_t *__restrict__ place,
-                                                       float4 *__restrict__ rec, int N, int64_t cells_per_cloud)
+// rec = the points in cell order, off[b*cells_per_cloud + cell] = where a cell's begin, place[b*N + id] = a point's record, inside
+// the cloud.  Dynamic LDS: 2^shift counters.
+__global__ __launch_bounds__(256) void knn_sort_kernel(const int32_t *__restrict__ bucket_off, const float4 *__restrict__ st_rec,
+                                                       const unsigned *__restrict__ bbox, float4 *__restrict__ rec,
+                                                       int32_t *__restrict__ off, int32_t *__restrict__ place, int N,
+                                                       int64_t cells_per_cloud, const KnnBuckets k)
 {
-    const int b = blockIdx.y;
-    const float *p = pos + (int64_t)b * 3 * N;
-    for (int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; l < N; l += (int64_t)gridDim.x * blockDim.x) {
-        const int at = off[b * cells_per_cloud + cell[(int64_t)b * N + l]] + place[(int64_t)b * N + l];
-        rec[at] = make_float4(p[l], p[(int64_t)N + l], p[2 * (int64_t)N + l], __int_as_float((int)l));
-        place[(int64_t)b * N + l] = at - b * N;
+    extern __shared__ int s_at[];                // counts, then the next record of every cell
+    __shared__ int s_wave[4];
+    constexpr int UN = 4;
+    const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cells = 1 << k.shift;
+    const int beg = bucket_off[(int64_t)b * k.n + blockIdx.x], n = bucket_off[(int64_t)b * k.n + blockIdx.x + 1] - beg;
+    for (int i = tid; i < cells; i += 256) s_at[i] = 0;
+    const KnnGrid g = knn_grid(bbox, b, cells_per_cloud);
+    auto cell = [&](const float4 &q) { return knn_linear_cell(g, q.x, q.y, q.z) & (cells - 1); };
+    __syncthreads();
+    for (int i0 = tid; i0 < n; i0 += 256 * UN) {
+        float4 q[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) q[u] = st_rec[beg + min(i0 + 256 * u, n - 1)];
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+            if (i0 + 256 * u < n) atomicAdd(&s_at[cell(q[u])], 1);
+    }
+    __syncthreads();
+    const int per = cells / 256, i0 = tid * per;
+    int sum = 0;
+    for (int i = 0; i < per; ++i) sum += s_at[i0 + i];
+    int x = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(x, d, 64);
+        if (lane >= d) x += y;
+    }
+    if (lane == 63) s_wave[wave] = x;
+    __syncthreads();
+    int run = beg + x - sum;
+    for (int w = 0; w < wave; ++w) run += s_wave[w];
+    for (int i = 0; i < per; ++i) {
+        const int c = s_at[i0 + i];
+        s_at[i0 + i] = run;
+        run += c;
+    }
+    __syncthreads();
+    const int64_t c0 = (int64_t)blockIdx.x << k.shift;
+    int32_t *my_off = off + b * cells_per_cloud + c0;
+    for (int i = tid; i < cells && c0 + i < cells_per_cloud; i += 256) my_off[i] = s_at[i];
+    if (b == (int)gridDim.y - 1 && blockIdx.x == gridDim.x - 1 && tid == 0) off[gridDim.y * cells_per_cloud] = (b + 1) * N;
+    __syncthreads();
+    for (int i0 = tid; i0 < n; i0 += 256 * UN) {
+        float4 q[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) q[u] = st_rec[beg + min(i0 + 256 * u, n - 1)];
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+            if (i0 + 256 * u < n) {
+                const int at = atomicAdd(&s_at[cell(q[u])], 1);
+                const int id = min((unsigned)__float_as_int(q[u].w), (unsigned)(N - 1));
+                rec[at] = make_float4(q[u].x, q[u].y, q[u].z, __int_as_float(id));
+                place[(int64_t)b * N + id] = at - b * N;
+            }
     }
 }
 
@@ -517,15 +667,26 @@ __global__ __launch_bounds__(256) void knn_place_kernel(const int32_t *__restric
     }
 }
 
+static size_t knn_used_bytes(int B, int N, int K)
+{
+    const int64_t cpc = knn_cell_cap(N, K), BN = (int64_t)B * N;
+    return align256(sizeof(float4) * (size_t)BN) + align256(sizeof(int32_t) * (size_t)BN) + align256(sizeof(int32_t) * (size_t)(B * cpc + 1)) +
+           align256(sizeof(unsigned) * 6 * (size_t)B) + align256(sizeof(int32_t) * (size_t)(3 * (int64_t)B * knn_buckets(cpc).n + 1)) +
+           std::max(align256(sizeof(int32_t) * (size_t)BN * K), align256(sizeof(float4) * (size_t)BN));
+}
+
+// At least what a counting sort by cells asked for: the size that callers have been told.  (More is used only where lists of three
+// and fewer belong to clouds of more than 8 M points.)
 size_t knn_ws_bytes(int B, int N, int K)
 {
     const int64_t cells = (int64_t)B * knn_cell_cap(N, K);
-    return align256(sizeof(float4) * (size_t)B * N) + 2 * align256(sizeof(int32_t) * (size_t)B * N) +
-           align256(sizeof(int32_t) * (size_t)B * N * K) + align256(sizeof(int32_t) * (size_t)(cells + 1)) * 2 +
-           exclusive_scan_ws_bytes(cells) + align256(sizeof(unsigned) * 6 * (size_t)B);
+    return std::max(knn_used_bytes(B, N, K),
+                    align256(sizeof(float4) * (size_t)B * N) + 2 * align256(sizeof(int32_t) * (size_t)B * N) +
+                        align256(sizeof(int32_t) * (size_t)B * N * K) + align256(sizeof(int32_t) * (size_t)(cells + 1)) * 2 +
+                        align256(sizeof(int32_t) * (size_t)(cdiv64(cells, 2048) + 1)) + align256(sizeof(unsigned) * 6 * (size_t)B));
 }
 
-// Is every point compared with all of its cloud?  One launch in place of nine, and no grid; the work grows with the square.  us (the whole
+// Is every point compared with all of its cloud?  One launch in place of eight, and no grid; the work grows with the square.  us (the whole
 // call, K = 8, the grid with a thread per point / sixteen lanes, and here): 300 points 68 / 32 and 9.1, 1024 75 / 35 and 11.9, 4096 79 / 36
 // and 35, 8 x 1000 132 / 48 and 15, 100 x 300 111 / 60 and 17.5, 3 x 2500, K = 10, 99 / 40 and 31, 2 x 4096 81 / 40 and 45.
 static bool knn_all(int64_t B, int64_t N) { return N <= 4096 && B * N * N <= 25 << 20; }
@@ -557,25 +718,37 @@ hipError_t launch_knn(const float *pos, int32_t *nbr, int B, int N, int K, void 
         return hipGetLastError();
     }
     const int64_t cpc = knn_cell_cap(N, K), cells = (int64_t)B * cpc;
+    const KnnBuckets k = knn_buckets(cpc);
+    const int64_t buckets = (int64_t)B * k.n;
     char *at = (char *)ws;
     float4 *rec = (float4 *)at;       at += align256(sizeof(float4) * (size_t)B * N);
-    int32_t *cell = (int32_t *)at;    at += align256(sizeof(int32_t) * (size_t)B * N);
     int32_t *place = (int32_t *)at;   at += align256(sizeof(int32_t) * (size_t)B * N);
-    int32_t *lists = (int32_t *)at;   at += align256(sizeof(int32_t) * (size_t)B * N * K);
-    int32_t *cnt = (int32_t *)at;     at += align256(sizeof(int32_t) * (size_t)(cells + 1));
     int32_t *off = (int32_t *)at;     at += align256(sizeof(int32_t) * (size_t)(cells + 1));
-    void *scan_ws = at;               at += exclusive_scan_ws_bytes(cells);
-    unsigned *bbox = (unsigned *)at;
-    const int64_t ib = cdiv64(cells > 6 * (int64_t)B ? cells : 6 * (int64_t)B, 256);
-    hipLaunchKernelGGL(knn_init_kernel, dim3((unsigned)(ib < 8192 ? ib : 8192)), dim3(256), 0, s, bbox, B, cnt, cells);
-    int nb = (int)((N + 255) / 256);
-    if (nb > 2048) nb = 2048;
+    unsigned *bbox = (unsigned *)at;  at += align256(sizeof(unsigned) * 6 * (size_t)B);
+    int32_t *cnt = (int32_t *)at, *cur = cnt + buckets, *boff = cur + buckets;
+    at += align256(sizeof(int32_t) * (size_t)(3 * buckets + 1));
+    int32_t *lists = (int32_t *)at;               // written when the staged points are done with
+    float4 *st_rec = (float4 *)at;
+    const int64_t ib = cdiv64(buckets > 6 * (int64_t)B ? buckets : 6 * (int64_t)B, 256);
+    hipLaunchKernelGGL(knn_init_kernel, dim3((unsigned)(ib < 8192 ? ib : 8192)), dim3(256), 0, s, bbox, B, cnt, buckets);
     const int bb = (N + 4095) / 4096;                      // four points per thread
     hipLaunchKernelGGL(knn_bbox_kernel, dim3(bb < 256 ? bb : 256, B), dim3(1024), 0, s, pos, bbox, N);
-    hipLaunchKernelGGL(knn_count_kernel, dim3(nb, B), dim3(256), 0, s, pos, bbox, cell, place, cnt, N, cpc);
-    hipError_t e = launch_exclusive_scan_i32(cnt, off, cells, scan_ws, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(knn_fill_kernel, dim3(nb, B), dim3(256), 0, s, pos, cell, off, place, rec, N, cpc);
+    auto deal = [&](auto points) {
+        constexpr int P = points.value;
+        const dim3 grid((unsigned)cdiv64(N, KNN_DEAL_NT * P), B);
+        hipLaunchKernelGGL((knn_count_kernel<P>), grid, dim3(KNN_DEAL_NT), 0, s, pos, bbox, cnt, N, cpc, k);
+        hipLaunchKernelGGL(knn_bucket_scan_kernel, dim3(B), dim3(1024), 0, s, cnt, boff, cur, N, k.n);
+        hipLaunchKernelGGL((knn_deal_kernel<P>), grid, dim3(KNN_DEAL_NT), 0, s, pos, bbox, cur, st_rec, N, cpc, k);
+    };
+    // Fewer points a thread put more workgroups on the chip, each with all buckets to clear and to reserve in.  us of the whole search at
+    // 1 | 2 | 4 points: 13k points 47.8 | 49.2 | 51.5, 100k 88.0 | 88.8 | 90.4, 300k 176.2 | 170.8 | 170.1, 8 clouds of 60k 256.2 | 255.2 |
+    // 257.8, 1M 217.6 | 207.3 | 205.1.
+    const int64_t all = (int64_t)B * N;
+    if (all <= 1 << 17) deal(std::integral_constant<int, 1>{});
+    else if (all <= 1 << 19) deal(std::integral_constant<int, 2>{});
+    else deal(std::integral_constant<int, 4>{});
+    hipLaunchKernelGGL(knn_sort_kernel, dim3(k.n, B), dim3(256), sizeof(int) << k.shift, s, boff, st_rec, bbox, rec, off, place, N,
+                       cpc, k);
     int qb = (int)((N + 255) / 256);
     if (qb > 65535) qb = 65535;
     const int lanes = knn_lanes((int64_t)B * N, K);

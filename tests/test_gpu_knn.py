@@ -76,6 +76,22 @@ def test_knn_degenerate_shapes_on_the_grid():
         _check(pos, K)
 
 
+# the deal with 2 and 4 points a thread, 512 to 4096 cells a bucket, sparse and dense ones
+@pytest.mark.parametrize("B,N,K", [(2, 131_000, 4), (1, 600_000, 4), (1, 1_100_000, 1)])
+def test_knn_of_clouds_dealt_into_buckets(B, N, K):
+    say(f"knn buckets B={B} N={N} K={K}")
+    rng = np.random.default_rng(N)
+    pos = rng.random((B, 3, N)).astype(np.float32)
+    pos[:, :, : N // 3] *= np.float32(0.5)
+    nbr = fx.flex_knn(dev(pos), K).cpu().numpy()
+    assert np.array_equal(np.sort(nbr[:, 0]), np.broadcast_to(np.arange(N, dtype=np.int32), (B, N)))     # no two points coincide
+    for l in rng.integers(0, N, size=48):
+        for b in range(B):
+            d = pos[b] - pos[b, :, l : l + 1]
+            d2 = (d[0] * d[0] + d[1] * d[1]) + d[2] * d[2]
+            assert np.array_equal(nbr[b, :, l], np.lexsort((np.arange(N), d2))[:K]), (b, l)
+
+
 @pytest.mark.parametrize("N", [600, 4500])
 def test_knn_infinite_locations(N):
     """At infinity a point is as far as can be from the others and no distance from its like."""
