@@ -8,7 +8,7 @@
 // each bucket is sorted in LDS by one workgroup.  Global atomics per (workgroup, bucket) instead of per edge:
 // a random-address atomic per edge (twice) and the scattered 4-byte writes behind
 // it were 600 us of the 650 us that 1M points x 8 neighbours in the sensor's
-// order took; this takes 139 us, 121 in Z-order (324).  Beyond that: counting sort by target point with
+// order took; this takes 104 us, 91 in Z-order.  Beyond that: counting sort by target point with
 // an atomic per edge (count -> exclusive scan -> fill -> sort each list).
 #include "flex_common.hpp"
 #include <stdlib.h>
@@ -228,8 +228,7 @@ __global__ __launch_bounds__(256) void inedge_sort_kernel(const int32_t *__restr
 //   deal     the same runs again: a workgroup reserves a stretch of every bucket it has edges for (one atomic each)
 //            and writes source and target-within-bucket of its edges there
 //   sort     one workgroup per bucket: its edges into registers, counts per target and their running sum in LDS
-//            (= the list bounds), every edge's rank inside its list by comparing with the list, the sorted bucket
-//            out as one contiguous write
+//            (= the list bounds), the lists put together in LDS and sorted there, the bucket out as one contiguous write
 static constexpr int BUCKET_EDGES_LOG2 = 13;
 static constexpr int BUCKET_NT = 1024;                           // threads per workgroup, all four steps
 static constexpr int BUCKET_PER_THREAD = 12;                     // edges a thread of the sort keeps
@@ -362,10 +361,10 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_scan_kernel(const int32_t *__r
 // What bounds it is the stores: on a cloud stored without locality the edges of a wave go to as many buckets, 64 lines a store
 // where a line would hold 32 edges of one bucket.  STAGED: where that is so (most lanes met neither of the first two
 // keys of their wave), the run is put in bucket order in LDS first, targets, then sources through the same array, and leaves in
-// that order.  1M points of a room in the sensor's order, K = 8: this kernel 81 -> 49 us, the build 170 -> 139; 2.9M in a cube 715 -> 393.  On clouds with
-// locality the waves' own stores are whole lines already (Z-order, 1M points: the build 121 us, 124 with every run ordered in LDS).
+// that order.  1M points of a room in the sensor's order, K = 8: this kernel 81 -> 49 us, the build 135 -> 104; 2.9M in a cube 322 us less.  On clouds with
+// locality the waves' own stores are whole lines already (Z-order, 1M points: the build 3 us longer with every run ordered in LDS).
 // Up to DEAL_BUCKETS_MAX buckets, what LDS holds beside a run, and from DEAL_RUN_MIN edges a run on: 300k and 100k points in the sensor's
-// order, K = 8, runs of 10 and 4 edges a thread: the build 72.5 and 42 us, by LDS 74 and 48; 600k, 19 edges, 115 and 102.
+// order, K = 8, runs of 10 and 4 edges a thread: the build 1.5 and 6 us shorter than by LDS; 600k, 19 edges, 13 longer.
 template <bool STAGED>
 __global__ __launch_bounds__(BUCKET_NT) void edge_deal_kernel(const EdgeRuns p, int32_t *__restrict__ bucket_cur,
                                                               int32_t *__restrict__ st_src, uint16_t *__restrict__ st_tgt,
@@ -478,7 +477,39 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_deal_kernel(const EdgeRuns p, 
         }
 }
 
-__global__ __launch_bounds__(BUCKET_NT) void edge_sort_kernel(const int32_t *__restrict__ bucket_off,
+// The d <= W ids at p ascending, one thread: Batcher's odd-even merge exchange in registers.
+template <int W>
+__device__ __forceinline__ void sort_short(int *p, int d)
+{
+    int v[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        const int x = p[max(min(i, d - 1), 0)];
+        v[i] = i < d ? x : 0x7fffffff;
+    }
+#pragma unroll
+    for (int run = 1; run < W; run *= 2)
+#pragma unroll
+        for (int step = run; step >= 1; step /= 2)
+#pragma unroll
+            for (int i = 0; i + step < W; ++i)
+                if (i >= step % run && (i - step % run) / step % 2 == 0 && i / (2 * run) == (i + step) / (2 * run)) {
+                    const int a = v[i], c = v[i + step];
+                    v[i] = min(a, c); v[i + step] = max(a, c);
+                }
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+        if (i < d) p[i] = v[i];
+}
+
+// Lists of up to W edges are sorted by a thread each, up to 64 by a wave, longer ones by the whole workgroup.  What bounded it was LDS:
+// a rank for every edge, by reading all of its list, is some 13 reads an edge at K = 8 with 64 lanes in as many places (the longest list of
+// a wave's counts), and the arrays for it left one workgroup to a CU; a list in registers is read and written once, target and slot share
+// a register, and two workgroups fit.  us of the build, ranks and so: 1M points, K = 8, 135 and 104 (Z-order 121 and 91), 100k, K = 16, 64
+// and 52, 500k, K = 16, 167 and 116, K = 12 110 and 76, 400k, K = 10, 84 and 61, 200k, K = 32, 199 and 156.  With W = 32 at K = 16 the
+// 100k were 66.
+template <int W>
+__global__ __launch_bounds__(BUCKET_NT, 8) void edge_sort_kernel(const int32_t *__restrict__ bucket_off,
                                                               const int32_t *__restrict__ st_src,
                                                               const uint16_t *__restrict__ st_tgt,
                                                               int32_t *__restrict__ in_off, int32_t *__restrict__ in_src,
@@ -486,30 +517,14 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_sort_kernel(const int32_t *__r
 {
     __shared__ int s_off[BUCKET_TARGETS_MAX + 1];     // counts, then list starts inside the bucket
     __shared__ int s_src[BUCKET_CAP];
-    __shared__ int s_wave[BUCKET_NT / 64];
+    __shared__ int s_wave[BUCKET_NT / 64], s_more[BUCKET_CAP / (W + 1) + 1], s_most[BUCKET_CAP / 65 + 1], s_long[2];
     const int targets = 1 << shift, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int beg = bucket_off[blockIdx.x], n = bucket_off[blockIdx.x + 1] - beg;
     const int64_t g0 = (int64_t)blockIdx.x << shift;
     for (int i = tid; i < targets; i += BUCKET_NT) s_off[i] = 0;
-    const bool fits = n <= BUCKET_CAP;
-    int src[BUCKET_PER_THREAD], tgt[BUCKET_PER_THREAD], slot[BUCKET_PER_THREAD];
-    if (fits) {
-#pragma unroll
-        for (int u = 0; u < BUCKET_PER_THREAD; ++u) {
-            const int i = tid + BUCKET_NT * u;
-            src[u] = i < n ? st_src[beg + i] : 0;
-            tgt[u] = i < n ? st_tgt[beg + i] : -1;
-        }
-    }
-    __syncthreads();
-    if (fits) {
-#pragma unroll
-        for (int u = 0; u < BUCKET_PER_THREAD; ++u) slot[u] = tgt[u] >= 0 ? atomicAdd(&s_off[tgt[u]], 1) : 0;
-    } else {
-        for (int i = tid; i < n; i += BUCKET_NT) atomicAdd(&s_off[st_tgt[beg + i]], 1);
-    }
-    __syncthreads();
-    {   // counts -> list starts, two targets per thread
+    if (tid < 2) s_long[tid] = 0;
+    auto starts = [&] {   // counts -> list starts, two targets per thread
+        __syncthreads();
         const int i0 = 2 * tid;
         const int a = i0 < targets ? s_off[i0] : 0, c = i0 + 1 < targets ? s_off[i0 + 1] : 0;
         int x = a + c;
@@ -528,34 +543,76 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_sort_kernel(const int32_t *__r
             s_off[targets] = n;
             if (blockIdx.x == gridDim.x - 1) in_off[BN] = E;
         }
-    }
-    __syncthreads();
-    if (fits) {
-#pragma unroll
-        for (int u = 0; u < BUCKET_PER_THREAD; ++u)
-            if (tgt[u] >= 0) s_src[s_off[tgt[u]] + slot[u]] = src[u];
         __syncthreads();
-        // rank inside the list: sources before mine (equal ones: in slot order)
+    };
+    if (n <= BUCKET_CAP) {
+        constexpr unsigned NONE = ~0u;
+        static_assert(BUCKET_TARGETS_MAX <= 1 << 12 && BUCKET_CAP <= 1 << 15, "");
+        int src[BUCKET_PER_THREAD];
+        unsigned own[BUCKET_PER_THREAD];              // target, and above 12 bits the slot in its list
+        const int from = min(beg, E - 1);             // (an empty bucket's beginning may lie past the last edge)
+        const int32_t *const my_src = st_src + from;
+        const uint16_t *const my_tgt = st_tgt + from;
+#pragma unroll
+        for (int u = 0; u < BUCKET_PER_THREAD; ++u) {
+            const unsigned i = min((unsigned)(tid + BUCKET_NT * u), (unsigned)max(n - 1, 0));
+            src[u] = my_src[i];
+            own[u] = my_tgt[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < BUCKET_PER_THREAD; ++u) {
+            if (tid + BUCKET_NT * u < n) own[u] |= (unsigned)atomicAdd(&s_off[own[u]], 1) << 12;
+            else own[u] = NONE;
+        }
+        starts();
 #pragma unroll
         for (int u = 0; u < BUCKET_PER_THREAD; ++u)
-            if (tgt[u] >= 0) {
-                const int lo = s_off[tgt[u]], hi = s_off[tgt[u] + 1], me = lo + slot[u];
-                int r = lo;
-                for (int i = lo; i < hi; ++i) {
-                    const int o = s_src[i];
-                    r += (o < src[u] || (o == src[u] && i < me)) ? 1 : 0;
-                }
-                slot[u] = r;
+            if (own[u] != NONE) s_src[s_off[own[u] & 0xfff] + (own[u] >> 12)] = src[u];
+        __syncthreads();
+        for (int i = tid; i < targets; i += BUCKET_NT) {
+            const int lo = s_off[i], d = s_off[i + 1] - lo;
+            if (d <= W) sort_short<W>(s_src + lo, d);
+            else if (d <= 64) s_more[atomicAdd(&s_long[0], 1)] = i;
+            else s_most[atomicAdd(&s_long[1], 1)] = i;
+        }
+        __syncthreads();
+        // rank inside the list: sources before mine (equal ones: in the order that they stand in)
+        for (int m = wave; m < s_long[0]; m += BUCKET_NT / 64) {
+            const int lo = __builtin_amdgcn_readfirstlane(s_off[s_more[m]]);
+            const int d = __builtin_amdgcn_readfirstlane(s_off[s_more[m] + 1]) - lo;
+            const int me = lane < d ? s_src[lo + lane] : 0x7fffffff;
+            int r = lo;
+            for (int i = 0; i < d; ++i) {
+                const int o = __builtin_amdgcn_readlane(me, i);
+                r += (o < me || (o == me && i < lane)) ? 1 : 0;
             }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < BUCKET_PER_THREAD; ++u)
-            if (tgt[u] >= 0) s_src[slot[u]] = src[u];
+            if (lane < d) s_src[r] = me;
+        }
+        // bitonic, every exchange ascending (the first of a merge between mirrored places): what lies past the end counts as larger
+        for (int m = 0; m < s_long[1]; ++m) {
+            const int lo = s_off[s_most[m]], d = s_off[s_most[m] + 1] - lo;
+            for (int size = 2; size < 2 * d; size *= 2)
+                for (int step = size / 2; step >= 1; step /= 2) {
+                    for (int q = tid; 2 * q < d + size; q += BUCKET_NT) {
+                        const int at = q / step * 2 * step, in = q % step;
+                        const int i = at + in, j = step == size / 2 ? at + 2 * step - 1 - in : i + step;
+                        if (j < d) {
+                            const int x = s_src[lo + i], y = s_src[lo + j];
+                            if (x > y) { s_src[lo + i] = y; s_src[lo + j] = x; }
+                        }
+                    }
+                    __syncthreads();
+                }
+        }
         __syncthreads();
         for (int i = tid; i < n; i += BUCKET_NT) in_src[beg + i] = s_src[i];
         return;
     }
     // a bucket of far more edges than its share (hub points): the lists are filled and sorted in global memory
+    __syncthreads();
+    for (int i = tid; i < n; i += BUCKET_NT) atomicAdd(&s_off[st_tgt[beg + i]], 1);
+    starts();
     for (int i = tid; i < targets; i += BUCKET_NT) s_src[i] = s_off[i];
     __syncthreads();
     for (int i = tid; i < n; i += BUCKET_NT) in_src[beg + atomicAdd(&s_src[st_tgt[beg + i]], 1)] = st_src[beg + i];
@@ -686,13 +743,14 @@ size_t inedges_ws_bytes(int64_t BN, int K)
 }
 
 // Targets a workgroup of the one-launch build owns; 0: the cloud is not for it.  Every workgroup of a cloud walks all of its edges, so
-// those are at most 2^15, and 2^15 a CU over all workgroups; more than 2048 workgroups are a launch longer than five.  us, five launches
-// and one, K = 8: 300 points 20 and 11, 2048 27 and 16, 4096 27 and 23.5, 1024 with K = 16 34 and 18, 100 x 300 29 and 11, 30 x 2000 31 and
-// 16, 30 x 4096 34 and 32, 60 x 4096 41 and 65, 2000 x 300 89 and 65, 3000 x 64 47 and 56.
+// those are at most 24576, and 2^15 a CU over all workgroups; more than 2048 workgroups are a launch longer than five.  us, five launches
+// and one, K = 8: 300 points 21 and 10.7, 2048 22.3 and 16.3, 3000 22.5 and 20.1, 4096 22.2 and 24.5, 1024 with K = 16 22.3 and 18.4, 2048
+// 22.6 and 27.1, 100 x 300 24.5 and 10.5, 30 x 2000 26.2 and 16.5, 4 x 4096 24.6 and 24.0, 2000 x 300 67.1 and 65.3; of an earlier five
+// launches, 60 x 4096 41 and 65, 3000 x 64 47 and 56.
 static int small_targets(int64_t B, int64_t N, int64_t Nc, int K)
 {
     const int64_t edges = K * Nc, cus = device_cu_count();
-    if (bucket_count(B * N, K) == 0 || edges > 1 << 15) return 0;
+    if (bucket_count(B * N, K) == 0 || edges > 3 << 13) return 0;
     const int64_t own = B * edges > 2048 * cus ? 4096 : 2048;
     const int64_t targets = own / K < 1 ? 1 : own / K < BUCKET_TARGETS_MAX ? own / K : BUCKET_TARGETS_MAX;
     const int64_t groups = B * cdiv64(N, targets);
@@ -734,8 +792,8 @@ hipError_t launch_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int 
         hipLaunchKernelGGL(edge_scan_kernel, dim3(1), blk, 0, s, cnt, off, cur, buckets);
         if (buckets <= DEAL_BUCKETS_MAX && run >= DEAL_RUN_MIN) hipLaunchKernelGGL(edge_deal_kernel<true>, g, blk, lds, s, p, cur, st_src, st_tgt, buckets);
         else hipLaunchKernelGGL(edge_deal_kernel<false>, g, blk, lds, s, p, cur, st_src, st_tgt, buckets);
-        hipLaunchKernelGGL(edge_sort_kernel, dim3((unsigned)buckets), blk, 0, s, off, st_src, st_tgt, in_off, in_src, BN,
-                           (int)E, p.shift);
+        const auto sort = K <= 10 ? edge_sort_kernel<16> : K <= 16 ? edge_sort_kernel<24> : edge_sort_kernel<32>;
+        hipLaunchKernelGGL(sort, dim3((unsigned)buckets), blk, 0, s, off, st_src, st_tgt, in_off, in_src, BN, (int)E, p.shift);
         return hipGetLastError();
     }
     const int64_t nblk64 = cdiv64(BN, SCAN_CHUNK);

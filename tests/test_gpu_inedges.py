@@ -51,9 +51,24 @@ def test_hub_points_past_a_buckets_lds():
     check(nbr)
 
 
-# the one-launch build of small clouds: both sides of its lines (2^15 edges a cloud, 2048 workgroups), stretches of one target and of
+# lists on both sides of what a thread (16, 24 or 32, by K), a wave (64) and a workgroup order in a bucket's LDS, half of them with
+# every centre twice
+@pytest.mark.parametrize("K", [8, 10, 11, 16, 17])
+def test_lists_of_every_length(K):
+    say(f"in-edges, lists of every length, K={K}")
+    N, sizes = 20_000, [1, 2, 15, 16, 17, 23, 24, 25, 31, 32, 33, 63, 64, 65, 66, 127, 128, 129, 1000, 2049]
+    rng = np.random.default_rng(K)
+    nbr = rng.integers(len(sizes), N, size=(1, K, N))
+    for i, n in enumerate(sizes):
+        own = rng.permutation(N)[:n] if i % 2 else np.repeat(rng.permutation(N)[: (n + 1) // 2], 2)[:n]
+        for l in own:                        # a slot of this centre that no other list has taken
+            nbr[0, np.argmax(nbr[0, :, l] >= len(sizes)), l] = i
+    check(nbr.astype(np.int32))
+
+
+# the one-launch build of small clouds: both sides of its lines (24576 edges a cloud, 2048 workgroups), stretches of one target and of
 # many, lists past what a workgroup orders in LDS, kept centres of which some name no point
-@pytest.mark.parametrize("B,N,K", [(1, 4096, 8), (1, 4097, 8), (3, 257, 9), (1, 2100, 1), (1, 180, 170), (2, 2600, 7), (2048, 16, 3), (2049, 16, 3), (1, 2, 2)])
+@pytest.mark.parametrize("B,N,K", [(1, 4096, 8), (1, 4097, 8), (1, 3072, 8), (1, 3073, 8), (3, 257, 9), (1, 2100, 1), (1, 180, 170), (2, 2600, 7), (2048, 16, 3), (2049, 16, 3), (1, 2, 2)])
 def test_small_clouds(B, N, K):
     say(f"in-edges of small clouds B={B} N={N} K={K}")
     rng = np.random.default_rng(B + N)
