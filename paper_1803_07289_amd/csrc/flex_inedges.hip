@@ -8,7 +8,7 @@
 // each bucket is sorted in LDS by one workgroup.  Global atomics per (workgroup, bucket) instead of per edge:
 // a random-address atomic per edge (twice) and the scattered 4-byte writes behind
 // it were 600 us of the 650 us that 1M points x 8 neighbours in the sensor's
-// order took; this takes 104 us, 91 in Z-order.  Beyond that: counting sort by target point with
+// order took; this takes 95 us, 78 in Z-order.  Beyond that: counting sort by target point with
 // an atomic per edge (count -> exclusive scan -> fill -> sort each list).
 #include "flex_common.hpp"
 #include <stdlib.h>
@@ -267,13 +267,35 @@ struct EdgeWalk {
             if (++k == p.K) { k = 0; ++b; }
         }
     }
-    // the point this edge names (over all clouds); entries of sel outside [0,N) are clamped
-    __device__ __forceinline__ int target(const EdgeRuns &p) const
-    {
-        const int l = p.sel ? min(max(p.sel[(int64_t)b * p.Nc + j], 0), p.N - 1) : j;
-        return b * p.N + p.nbr[((int64_t)b * p.K + k) * p.N + l];
-    }
 };
+
+// Targets (over all clouds; -1: past the n edges of the run) and centres of a thread's next UN edges, the first of them e0 edges into the
+// run.  Places first, then the loads, none of them under a condition: behind one, each waits for the one before it.  Past the end the last
+// edge is read again.  Entries of sel outside [0,N) are clamped.  us of the build, a load at a time and so: 1M points, K = 8, 104 and 95,
+// in Z-order 91 and 78, 500k, K = 16, 116 and 106, 3000 points (one launch) 20 and 17.
+template <int UN>
+__device__ __forceinline__ void edge_targets(const EdgeRuns &p, EdgeWalk &w, int e0, int n, int *t, int *j)
+{
+    int at[UN], base[UN], row[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+        j[u] = w.j;
+        base[u] = w.b * p.N;
+        at[u] = p.sel ? w.b * p.Nc + w.j : w.i;
+        row[u] = (w.b * p.K + w.k) * p.N;
+        if (e0 + BUCKET_NT * (u + 1) < n) w.next(p);
+    }
+    if (p.sel) {
+#pragma unroll
+        for (int u = 0; u < UN; ++u) at[u] = p.sel[at[u]];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) at[u] = row[u] + min(max(at[u], 0), p.N - 1);
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) t[u] = p.nbr[at[u]];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) t[u] = e0 + BUCKET_NT * u < n ? t[u] + base[u] : -1;
+}
 
 // counter[key] += 1 for every lane with on, returning the value before the lane's own addition.  On a cloud stored with
 // locality most of a wave's lanes share a key, and as many atomics on one LDS word would queue up: the lanes of the
@@ -312,13 +334,8 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_count_kernel(const EdgeRuns p,
     int alone = 0;
     EdgeWalk w(p, min(first + threadIdx.x, (int64_t)p.E - 1));
     for (int e0 = 0; e0 < n; e0 += BUCKET_NT * UN) {
-        int t[UN];
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const bool on = e0 + BUCKET_NT * u + (int)threadIdx.x < n;
-            t[u] = on ? w.target(p) : -1;
-            if (e0 + BUCKET_NT * (u + 1) + (int)threadIdx.x < n) w.next(p);
-        }
+        int t[UN], j[UN];
+        edge_targets<UN>(p, w, e0 + (int)threadIdx.x, n, t, j);
 #pragma unroll
         for (int u = 0; u < UN; ++u) lds_count(s_cnt, t[u] >> p.shift, t[u] >= 0, alone);
     }
@@ -382,13 +399,16 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_deal_kernel(const EdgeRuns p, 
     const int n = (int)min((int64_t)p.run, p.E - first);
     int t[MAXE], rank[MAXE], alone = 0;
     {
+        constexpr int UN = 8;
         EdgeWalk w(p, min(first + tid, (int64_t)p.E - 1));
+        int j[UN];
 #pragma unroll
-        for (int u = 0; u < MAXE; ++u) {
-            t[u] = -1;
+        for (int u = 0; u < MAXE; u += UN) {
             if (BUCKET_NT * u < n) {             // uniform
-                if (BUCKET_NT * u + tid < n) t[u] = w.target(p);
-                if (BUCKET_NT * (u + 1) + tid < n) w.next(p);
+                edge_targets<UN>(p, w, BUCKET_NT * u + tid, n, t + u, j);
+            } else {
+#pragma unroll
+                for (int v = 0; v < UN; ++v) t[u + v] = -1;
             }
         }
     }
@@ -646,15 +666,10 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_small_kernel(const EdgeRuns p,
         EdgeWalk w(p, first + min(tid, edges - 1));
         for (int e0 = 0; e0 < edges; e0 += BUCKET_NT * UN) {
             int t[UN], j[UN];
+            edge_targets<UN>(p, w, e0 + tid, edges, t, j);
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
-                const bool on = e0 + BUCKET_NT * u + tid < edges;
-                t[u] = on ? w.target(p) - b * p.N - t0 : nt;
-                j[u] = w.j;
-                if (e0 + BUCKET_NT * (u + 1) + tid < edges) w.next(p);
-            }
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
+                t[u] = t[u] >= 0 ? t[u] - b * p.N - t0 : nt;
                 earlier += t[u] < 0;
                 if (t[u] >= 0 && t[u] < nt) take(t[u], j[u]);
             }
@@ -744,9 +759,9 @@ size_t inedges_ws_bytes(int64_t BN, int K)
 
 // Targets a workgroup of the one-launch build owns; 0: the cloud is not for it.  Every workgroup of a cloud walks all of its edges, so
 // those are at most 24576, and 2^15 a CU over all workgroups; more than 2048 workgroups are a launch longer than five.  us, five launches
-// and one, K = 8: 300 points 21 and 10.7, 2048 22.3 and 16.3, 3000 22.5 and 20.1, 4096 22.2 and 24.5, 1024 with K = 16 22.3 and 18.4, 2048
-// 22.6 and 27.1, 100 x 300 24.5 and 10.5, 30 x 2000 26.2 and 16.5, 4 x 4096 24.6 and 24.0, 2000 x 300 67.1 and 65.3; of an earlier five
-// launches, 60 x 4096 41 and 65, 3000 x 64 47 and 56.
+// and one, K = 8, before the loads went out together (which took up to 3 us off either): 300 points 21 and 10.7, 2048 22.3 and 16.3, 3000 22.5
+// and 20.1, 4096 22.2 and 24.5, 1024 with K = 16 22.3 and 18.4, 2048 22.6 and 27.1, 100 x 300 24.5 and 10.5, 30 x 2000 26.2 and 16.5, 4 x 4096
+// 24.6 and 24.0, 2000 x 300 67.1 and 65.3; with the edges ranked, 60 x 4096 41 and 65, 3000 x 64 47 and 56.
 static int small_targets(int64_t B, int64_t N, int64_t Nc, int K)
 {
     const int64_t edges = K * Nc, cus = device_cu_count();
