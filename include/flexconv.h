@@ -319,7 +319,8 @@ int flex_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int B, int N,
  * cell edge, about the mean spacing) cost M*M distance evaluations; meant for clouds without such piles.
  * pos [B,3,N] finite; nbr int32 [B,K,N] overwritten.  K in 1..10, 12, 16, 24 or 32, K <= N;
  * B <= 65535.  Workspace: flexconv_workspace_bytes(FLEX_OP_KNN, B, N, K, ...): 24 bytes a point, the lists
- * once more in the search's order, 8 bytes a grid cell (504 MB for 7 M points x 8).
+ * once more in the search's order, 8 bytes a grid cell (504 MB for 7 M points x 8; for lists of three and fewer a
+ * little more beyond 8 M points).
  */
 int flex_knn(const float *pos, int32_t *nbr, int B, int N, int K,
              void *workspace, size_t workspace_bytes, void *stream);
@@ -419,9 +420,9 @@ int flex_validate_neighbors(const int32_t *nbr, int B, int N, int K,
 /* 1 if flexconv_fwd / flexconv_bwd run (Din,Dout) on the matrix-core kernels: the tiled widths 32->32, 64->64,
  * 128->128, 9->64, 64->9, 32->64, 64->32, 64->128, 128->64, and every pair of multiples of 128 (run on 64-point tiles,
  * input block by input block; the deeper stages of the network of Sec. 4.3, whose feature length doubles from
- * stage to stage).  2: any other widths: forward and feature gradient on 64-point tiles as they are,
- * parameter gradients zero-padded at the nearest widths of that list (the copies live in the workspace, whose size
- * flexconv_workspace_bytes reports).  0: the direct-form kernels
+ * stage to stage).  2: any other widths: forward and feature gradient on 64-point tiles as they are, parameter
+ * gradients too where a side has more than 64 channels or the cloud is large, else zero-padded at the nearest widths of that list
+ * (the copies live in the workspace, whose size flexconv_workspace_bytes reports).  0: the direct-form kernels
  * (orders of magnitude slower; only with padding or the wide path switched off in the environment). */
 int flexconv_has_fast_path(int Din, int Dout);
 
@@ -437,7 +438,7 @@ typedef enum {
     FLEX_ROUTE_SPLIT128 = 4,   /* 128 -> 128 point-major: 64-point tile kernels */
     FLEX_ROUTE_WIDE = 5,       /* other widths that are multiples of 128: 64-point tile kernels */
     FLEX_ROUTE_PADDED = 6,     /* widths outside the list: the kernels of FLEX_ROUTE_NARROW (gathered rows of at most 16
-                                  channels) or FLEX_ROUTE_TILE at the tensors' own widths; parameter gradients on
+                                  channels) or FLEX_ROUTE_TILE at the tensors' own widths; parameter gradients too, or on
                                   zero-padded copies at the nearest listed widths */
     FLEX_ROUTE_LEAN_FUSED = 7, /* flexconv_bwd only: lean kernels, and when grad_feat and grad_theta / grad_bias are
                                   all asked for, ONE kernel makes one pass over the in-edge lists for all of them
