@@ -147,8 +147,10 @@ __device__ __forceinline__ void knn_cell_of(const KnnGrid &g, float x, float y, 
 // cell order by one workgroup, which writes its cells' bounds on the way.  Counters are in LDS; a workgroup meets the global ones once
 // per bucket that it has points for.  (A counter per cell in memory: one returning atomic per point, 46 us at 1M points, and a table of
 // 2M counters to clear and to sum, 27.)  us of the whole search, with a counter per cell and so: 1M points of a room in the order drawn
-// 242 and 205, in Z-order 222 and 188, 1.5M of a hall with 12 neighbours 433 and 378, 7M of it 1538 and 1377, a cube of 1M 397 and 363.  Positions that another stream overwrites meanwhile can make the count and the deal differ:
-// places and ids are clamped, so that the answer is wrong then and no more.
+// 242 and 205, in Z-order 222 and 188, 1.5M of a hall with 12 neighbours 433 and 378, 7M of it 1538 and 1377, a cube of 1M 397 and 363.
+// Positions have to stay as they are while a call runs.  (Overwritten by another stream meanwhile they could make the count and the deal
+// differ, and places, ids and records be what the workspace held: those are clamped where they become an index, and a record whose cell
+// has no points starts at itself, so that such an answer means nothing but no access leaves the buffers.)
 static constexpr int KNN_BUCKETS_MAX = 4096, KNN_DEAL_NT = 1024;
 struct KnnBuckets {
     int shift, n;                                // n: per cloud
@@ -402,7 +404,8 @@ __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict
 #pragma unroll
             for (int j = 0; j < 9; ++j)
                 if (b0[j] < b1[j]) { s_beg[rows][tid] = b0[j]; s_end[rows][tid] = b1[j]; ++rows; }
-            // (the thread's own cell is never empty; the second record of a row's last step may be the next row's, or what
+            if (rows == 0) { s_beg[0][tid] = b * N + (int)i; s_end[0][tid] = b * N + (int)i + 1; }     // (see above the bucket kernels)
+            // (the second record of a row's last step may be the next row's, or what
             // follows the records in the workspace: read, not offered)
             int j = 0, e = s_beg[0][tid], end = s_end[0][tid];
             float4 q0 = rec[e], q1 = rec[e + 1];
@@ -654,7 +657,8 @@ __global__ __launch_bounds__(256) void knn_place_kernel(const int32_t *__restric
 {
     const int b = blockIdx.y;
     for (int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; l < N; l += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t *src = lists + ((int64_t)b * N + place[(int64_t)b * N + l]) * K;
+        const int at = (int)min((unsigned)place[(int64_t)b * N + l], (unsigned)(N - 1));      // (clamped: see above the bucket kernels)
+        const int32_t *src = lists + ((int64_t)b * N + at) * K;
         int32_t *dst = nbr + (int64_t)b * K * N + l;
         for (int k0 = 0; k0 < K; k0 += 8) {
             int v[8];

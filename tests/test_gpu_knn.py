@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import paper_1803_07289_amd as fx
-from gpu_util import dev, say
+from gpu_util import ExactWorkspace, dev, say
 from workloads import CONFIGS, make_inputs
 
 pytestmark = pytest.mark.gpu
@@ -90,6 +90,23 @@ def test_knn_of_clouds_dealt_into_buckets(B, N, K):
             d = pos[b] - pos[b, :, l : l + 1]
             d2 = (d[0] * d[0] + d[1] * d[1]) + d[2] * d[2]
             assert np.array_equal(nbr[b, :, l], np.lexsort((np.arange(N), d2))[:K]), (b, l)
+
+
+# a lane group and a thread to a point
+@pytest.mark.parametrize("N", [9000, 140_000])
+@pytest.mark.parametrize("left", [0, 0x7F, 0xFF])
+def test_knn_takes_nothing_from_what_the_workspace_held(N, left, K=8):
+    say(f"knn N={N} in a workspace of {left:#x}")
+    pos = np.random.default_rng(N).random((1, 3, N)).astype(np.float32)
+    pos[0, :, : N // 2] *= np.float32(0.2)
+    ws = ExactWorkspace(fx.OP_KNN, 1, N, K, 1, 1, fx.BCN)
+    ws.ws.fill_(left)
+    got = fx.flex_knn(dev(pos), K, workspace=ws.ws)
+    ws.check()
+    assert fx.flex_validate_neighbors(got) == 0
+    assert torch.equal(got, fx.flex_knn(dev(pos), K))
+    if N < 10_000:
+        assert np.array_equal(got.cpu().numpy(), oracle.knn(pos, K))
 
 
 @pytest.mark.parametrize("N", [600, 4500])
