@@ -497,14 +497,14 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_deal_kernel(const EdgeRuns p, 
         }
 }
 
-// The d <= W ids at p ascending, one thread: Batcher's odd-even merge exchange in registers.
+// The d ids at p ascending, 1 <= d <= W, one thread: Batcher's odd-even merge exchange in registers.
 template <int W>
 __device__ __forceinline__ void sort_short(int *p, int d)
 {
     int v[W];
 #pragma unroll
     for (int i = 0; i < W; ++i) {
-        const int x = p[max(min(i, d - 1), 0)];
+        const int x = p[min(i, d - 1)];
         v[i] = i < d ? x : 0x7fffffff;
     }
 #pragma unroll
@@ -592,6 +592,7 @@ __global__ __launch_bounds__(BUCKET_NT, 8) void edge_sort_kernel(const int32_t *
         __syncthreads();
         for (int i = tid; i < targets; i += BUCKET_NT) {
             const int lo = s_off[i], d = s_off[i + 1] - lo;
+            if (d < 2) continue;             // (an empty list's place may lie past the last edge)
             if (d <= W) sort_short<W>(s_src + lo, d);
             else if (d <= 64) s_more[atomicAdd(&s_long[0], 1)] = i;
             else s_most[atomicAdd(&s_long[1], 1)] = i;

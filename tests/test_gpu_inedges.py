@@ -66,6 +66,17 @@ def test_lists_of_every_length(K):
     check(nbr.astype(np.int32))
 
 
+@pytest.mark.parametrize("over", [-1, 0, 1])
+def test_bucket_that_is_exactly_full(over):
+    """As many edges as a bucket orders in LDS (12288), one fewer and one more, and no edge for its last targets."""
+    say(f"in-edges, 12288 {over:+d} edges in a bucket")
+    N, K, targets, full = 4096, 8, 1024, 12288 + over
+    rng = np.random.default_rng(12)
+    to = rng.integers(targets, N, size=K * N)
+    to[rng.permutation(K * N)[:full]] = rng.integers(0, targets - 100, size=full)
+    check(to.reshape(1, K, N).astype(np.int32))
+
+
 # the one-launch build of small clouds: both sides of its lines (24576 edges a cloud, 2048 workgroups), stretches of one target and of
 # many, lists past what a workgroup orders in LDS, kept centres of which some name no point
 @pytest.mark.parametrize("B,N,K", [(1, 4096, 8), (1, 4097, 8), (1, 3072, 8), (1, 3073, 8), (3, 257, 9), (1, 2100, 1), (1, 180, 170), (2, 2600, 7), (2048, 16, 3), (2049, 16, 3), (1, 2, 2)])
