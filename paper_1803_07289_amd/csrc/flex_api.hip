@@ -41,7 +41,7 @@ hipError_t launch_reduce_partials(const float *partials, int n_wg, int DIP, int 
 // the 64-point tile kernels over fixed-K neighbour tensors / in-edge lists
 hipError_t launch_tile_0(const TileArgs &a, int outw, int grid, hipStream_t s);
 hipError_t launch_tile_1(const TileArgs &a, int outw, int grid, hipStream_t s);
-hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int n_hi, int n_ho, int oc, float *partials, hipStream_t s);
+hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int n_hi, int n_ho, int oc, bool f32, float *partials, hipStream_t s);
 // rows of at most 16 channels, one point per lane (flex_narrow.hip)
 hipError_t launch_narrow_0(const TileArgs &a, int grid, hipStream_t s);
 hipError_t launch_narrow_1(const TileArgs &a, int grid, hipStream_t s);
@@ -166,14 +166,18 @@ static size_t wide_packed_bytes(int Din, int Dout) { return (size_t)(Din / 64) *
 // tenths of a microsecond, as measured: a tile 3.2 us for 64 channels and 5.0 for 128, whose larger partials take 3 more.
 // us, 64 and 128: 128 -> 128, 2k points 15.8 and 17.9, 8k 23.5 and 24.7, 16k 29.8 and 29.6, 60k 66.6 and 60.9, 1M 970 and 782;
 // 256 -> 256, 2k 24.6 and 28.5, 12k 59.5 and 52.6; 512 -> 512, 1k 30.6 and 34.6, 2k 43.2 and 43.1, 8k 126 and 109, 109k 1620 and 1270.
-struct TileGradPlan { int oc, n_hi, n_ho, chunks; };
+// f32: one side of at most 64 channels and the other of 65 to 128.  These widths have no kernel that splits its operands elsewhere (their
+// listed ones, 64 -> 128 and 128 -> 64, contract in fp32), and are contracted in fp32 here too, in blocks of 64.
+struct TileGradPlan { int oc, n_hi, n_ho, chunks; bool f32; };
 static TileGradPlan tile_grad_plan(int64_t B, int64_t N, int Din, int Dout)
 {
     const int64_t tiles = B * cdiv64(N, 64), cus = device_cu_count();
     TileGradPlan best{};
     int64_t least = 0;
+    const bool f32 = std::min(Din, Dout) <= 64 && std::max(Din, Dout) > 64 && std::max(Din, Dout) <= 128;
     for (const int oc : {64, 128}) {
-        TileGradPlan p{oc, (Din + 63) / 64, (Dout + oc - 1) / oc, 1};
+        if (f32 && oc > 64) break;
+        TileGradPlan p{oc, (Din + 63) / 64, (Dout + oc - 1) / oc, 1, f32};
         const int64_t blocks = (int64_t)p.n_hi * p.n_ho;
         p.chunks = (int)std::max<int64_t>(1, std::min(tiles, cus / blocks));
         const int64_t rounds = cdiv64(blocks * p.chunks, cus) * cdiv64(tiles, p.chunks);
@@ -201,7 +205,7 @@ static hipError_t tile_grad_theta(const float *rows, int w_in, const float *pos,
     const int64_t total = (int64_t)B * a.tpc;
     if (total > 0x7fffffff || (int64_t)p.n_hi * p.n_ho * p.chunks > 0x7fffffff) return hipErrorInvalidValue;
     a.total = (int)total;
-    hipError_t e = launch_tile_grad_theta(a, g_rows, p.n_hi, p.n_ho, p.oc, partials, s);
+    hipError_t e = launch_tile_grad_theta(a, g_rows, p.n_hi, p.n_ho, p.oc, p.f32, partials, s);
     if (e != hipSuccess) return e;
     return launch_reduce_partials(partials, p.chunks, 64, p.oc, p.n_hi * p.n_ho, p.n_ho, Din, Dout, grad_theta, grad_bias, s);
 }
@@ -481,9 +485,10 @@ static bool padded_shape(int Din, int Dout, int *DIp, int *DOp)
 }
 
 // Do the parameter gradients run on the 64-point tile kernels, at the tensors' own widths?  (k_in, k_out): the listed widths.
-// - Where a side is wider than 64 channels, always: 64 and 128 channels ran on the fp32 matrix op, other widths on zero-padded copies.
-//   us, K = 8, those and tiles: 64 -> 128, 3k points 22.9 and 16.3, 20k 45 and 24.5, 300k 370 and 126; 128 -> 64, 300k 488 and 148; 100 -> 50,
-//   3k 29.3 and 16.3, 300k 550 and 141; 3 -> 100, 300k 431 and 179; 160 -> 160, 3k 42 and 22, 300k 1124 and 650.
+// - Where a side is wider than 64 channels, always: 64 and 128 channels ran a workgroup's points in one chain of sums, other widths on
+//   zero-padded copies.  us, K = 8, those and tiles: 64 -> 128, 3k points 23.9 and 17.2, 20k 47 and 33, 300k 378 and 236; 128 -> 64, 300 points
+//   14.0 and 14.2, 3k 25.2 and 17.2, 300k 489 and 233; 100 -> 50, 3k 30.3 and 17.3, 300k 556 and 221; 3 -> 100, 300k 439 and 246; 160 -> 160,
+//   3k 42 and 22, 300k 1124 and 650.
 // - Below that the wave-specialised kernels take fewer points at a time.  Point-major tensors that they need copies of: at 64 x 64 channels
 //   from 8k points on (all gradients, copies and tiles: 50 -> 50, 3k 30.8 and 31.1, 20k 45.8 and 44.7, 300k 210 and 165; 33 -> 64, 3k 28.3
 //   and 29.2, 20k 43.4 and 42.5, 300k 182 and 159), at fewer where both tensors are copied, from 2^17 points on (20 -> 13, 50k 42.2 and

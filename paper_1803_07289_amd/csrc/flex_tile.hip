@@ -32,11 +32,12 @@ hipError_t FLEX_TILE_NAME(launch_tile_, FLEX_TILE_CSR)(const TileArgs &a, int ou
 }
 
 #if FLEX_TILE_CSR == 0
-hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int n_hi, int n_ho, int oc, float *partials, hipStream_t s)
+hipError_t launch_tile_grad_theta(const TileArgs &a, const float *g_rows, int n_hi, int n_ho, int oc, bool f32, float *partials, hipStream_t s)
 {
     const dim3 grid(n_hi * n_ho * a.chunks), block(1024);
     if (oc == 128) hipLaunchKernelGGL(tile_grad_theta128_kernel, grid, block, 0, s, a, g_rows, n_ho, partials);
-    else hipLaunchKernelGGL(tile_grad_theta_kernel, grid, block, 0, s, a, g_rows, n_ho, partials);
+    else if (f32) hipLaunchKernelGGL(tile_grad_theta_kernel<true>, grid, block, 0, s, a, g_rows, n_ho, partials);
+    else hipLaunchKernelGGL(tile_grad_theta_kernel<false>, grid, block, 0, s, a, g_rows, n_ho, partials);
     return hipGetLastError();
 }
 #endif

@@ -137,8 +137,9 @@ struct StepWalk {
             d.n0 = most(0); d.n1 = most(4);
         } else {
             d.n0 = d.n1 = a.K - 8 * c;
-            point = min(position(tw, first), a.N - 1);
-            has = slot < a.K;
+            const int at = position(tw, first);
+            point = min(at, a.N - 1);
+            has = slot < a.K && at < a.N;                        // positions past the cloud have no slots
             id = a.nbr[((int64_t)d.b * a.K + min(slot, a.K - 1)) * a.N + point];
         }
         if (++c == nc) {
@@ -571,13 +572,22 @@ void tile_conv_kernel(const TileArgs a)
 // contracted, and park it between two barriers.
 // What bounds it is the vector ALU (at 4 clocks an instruction 81 percent of its time at 128 -> 128 and 1M points, 83 at 512 -> 512
 // and 109k; the matrix cores 41 and 42, no bank conflicts).  Clouds of more than a few tiles a workgroup run tile_grad_theta128_kernel
-// below; the rule and both sides' times are beside wide_grad_plan (flex_api.hip).
+// below; the rule and both sides' times are beside tile_grad_plan (flex_api.hip).
+//
+// F32: products and sums on the fp32 matrix op, which rounds to nearest and takes infinities as they are.  In the pieces above an
+// infinity becomes no number, terms of up to 2^-21 of a product (2^-24.7 on average) are dropped, and sums of few points carry the matrix
+// op's one-sided rounding: 64 -> 128, one point 7.4e-8 where products rounded once leave 2.5e-8, eight points of 4096 with a gradient 9.1e-8
+// and 6.8e-8.  A tile's points are summed eight at a time and those sums in pairs: 2-norm error 64 -> 128 at 64, 4k, 30k and 200k points
+// 0.9e-7, 0.9e-7, 1.0e-7, 1.3e-7 (chains over a workgroup's points: 1.2e-7, 1.2e-7, 2.0e-7, 5.0e-7).  The fp32 op holds the vector ALU
+// with the matrix cores (8192 clocks a tile), so that gathering and contracting add up: 300k points 236 us, 128 -> 64 233.
 // ---------------------------------------------------------------------------
-static __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+template <bool F32>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, int n_ho, float *__restrict__ partials)
 {
     constexpr int IC = 64, KD = 4 * IC, OC = 64, T = 64;
-    constexpr int AS = bf3_stride(KD), GS = bf3_stride(OC);
+    // bytes of a row: 16 mod 64 words, so that the four rows of a read lie in banks of their own
+    constexpr int AS = F32 ? 4 * KD + 64 : bf3_stride(KD), GS = F32 ? 4 * OC + 64 : bf3_stride(OC);
     __shared__ __attribute__((aligned(16))) char s_A[T * AS];
     __shared__ __attribute__((aligned(16))) char s_G[T * GS];
     __shared__ __attribute__((aligned(16))) float s_ent[8][2][64][4];
@@ -601,6 +611,10 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
                 const int swap = bf3_swap(first);            // of all eight points of the wave
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
+                    if constexpr (F32) {
+                        *reinterpret_cast<v4f *>(row + 4 * (jj * IC + 4 * t)) = v4f{acc[ps][0][jj], acc[ps][1][jj], acc[ps][2][jj], acc[ps][3][jj]};
+                        continue;
+                    }
                     unsigned h0, m0, l0, h1, m1, l1;
                     split_bf3(acc[ps][0][jj], acc[ps][1][jj], h0, m0, l0);
                     split_bf3(acc[ps][2][jj], acc[ps][3][jj], h1, m1, l1);
@@ -666,6 +680,10 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
             const int swap = bf3_swap(ctid >> 4), v = 8 * (ctid & 15);
             unsigned h0, m0, l0, h1, m1, l1;
             if (a.w_out % 4 != 0) put_channels_right(gv[c], g_col - g_at);
+            if constexpr (F32) {
+                *reinterpret_cast<v4f *>(row + 16 * (ctid & 15)) = gv[c];
+                continue;
+            }
             const v4f g = c == 0 ? gv[c] : -gv[c];                 // (the second 32 points: see above)
             split_bf3(g[0], g[1], h0, m0, l0);
             split_bf3(g[2], g[3], h1, m1, l1);
@@ -677,6 +695,50 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
         load_g();
         if (k % FLUSH == 0 && k > 0) flush(k > FLUSH);
         __syncthreads();                   // the tile is complete
+        if constexpr (F32) {
+            // Sixteen points of a row block at a time, as two chains of eight; what they leave is added, in pairs over the tile, while
+            // the next ones run.
+            constexpr int SETS = T / 16;
+            const float *sA = reinterpret_cast<const float *>(s_A) + q * (AS / 4) + 16 * wm + r16;
+            const float *sG = reinterpret_cast<const float *>(s_G) + q * (GS / 4) + 16 * wn + r16;
+            float fa[2][4], fg[2][4][NBW];
+            v4f x[2][2][NBW], y[NBW], z[NBW];
+            auto fetch = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const int row = 16 * (j % SETS) + 4 * s;
+                    fa[j & 1][s] = sA[row * (AS / 4) + 64 * (j / SETS)];
+#pragma unroll
+                    for (int n = 0; n < NBW; ++n) fg[j & 1][s][n] = sG[row * (GS / 4) + 32 * n];
+                }
+            };
+            fetch(0);
+#pragma unroll
+            for (int j = 0; j <= SETS * MBW; ++j) {
+                if (j < SETS * MBW) {
+                    if (j + 1 < SETS * MBW) fetch(j + 1);
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+#pragma unroll
+                        for (int n = 0; n < NBW; ++n)
+                            x[j & 1][s & 1][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                fa[j & 1][(s & 1) * 2 + s / 2], fg[j & 1][(s & 1) * 2 + s / 2][n], s < 2 ? v4f{0.f, 0.f, 0.f, 0.f} : x[j & 1][s & 1][n], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (j == 0) continue;
+                const int i = (j - 1) % SETS, c = (j - 1) / SETS;
+#pragma unroll
+                for (int n = 0; n < NBW; ++n) {
+                    v4f sum = x[(j - 1) & 1][0][n] + x[(j - 1) & 1][1][n];
+                    if (i % 2 == 1) sum = y[n] + sum;
+                    if (i % 2 == 0) y[n] = sum;
+                    else if (i == 1) z[n] = sum;
+                    else tot[c][n] += z[n] + sum;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            continue;
+        }
 #pragma unroll
         for (int st = 0; st < T / 32; ++st) {
             bf8 gH[NBW], gM[NBW], gL[NBW];

@@ -1678,7 +1678,8 @@ void grad_theta_ws_kernel(const float *__restrict__ rows, const float *__restric
 // contracts over POINTS, so no per-point scaling can be taken out of the sum; instead every
 // fp32 value is carried as three bf16 pieces by truncation (x = h + m + l exactly: 3 x 8
 // significand bits, bf16 has fp32's exponent range, nothing to scale) and six products
-// h*h, h*m, m*h, h*l, l*h, m*m go through v_mfma_f32_16x16x32_bf16 (dropped terms ~2^-24).
+// h*h, h*m, m*h, h*l, l*h, m*m go through v_mfma_f32_16x16x32_bf16 (dropped: up to 2^-21 of a
+// product, 2^-24.7 on average; an infinity becomes no number).
 // Both tiles sit point-major in LDS, [pt][h: W][m: W][l: W] bf16; the matrix operands want
 // 8 consecutive points per lane, which ds_read_b64_tr_b16 delivers: in a group of 16 lanes,
 // lane i supplies the address of 4 consecutive columns of one row and lane j receives

@@ -100,6 +100,61 @@ def test_parameter_gradients_at_the_rows_own_widths(B, N, K, Din, Dout, layout):
     test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout, layout)
 
 
+# widths that are contracted in fp32: one side of at most 64 channels, the other of 65 to 128
+FP32_WIDTHS = [(64, 128), (128, 64), (100, 50), (3, 100), (65, 64), (64, 65), (127, 2)]
+
+
+def parameter_gradients(pos, nbr, feat, g):
+    theta, bias = np.zeros((3, feat.shape[1], g.shape[1]), np.float32), np.zeros((feat.shape[1], g.shape[1]), np.float32)
+    lay = lambda a: to_layout(a, fx.BNC)
+    edges = fx.flex_inedges_build(dev(nbr))
+    _, gt, gb = fx.flexconv_bwd(lay(feat), dev(pos), dev(nbr), dev(theta), dev(bias), lay(g), layout=fx.BNC, in_edges=edges, need_feat=False)
+    return gt.cpu().numpy(), gb.cpu().numpy()
+
+
+@pytest.mark.parametrize("Din,Dout", FP32_WIDTHS)
+@pytest.mark.parametrize("N,at", [(1, 0), (300, 299), (20_000, 7777)])
+def test_parameter_gradients_of_one_point_are_products_rounded_once(Din, Dout, N, at):
+    say(f"tile parameter gradients of point {at} of {N}, {Din}->{Dout}")
+    pos, nbr, feat, theta, bias, g = random_problem(13, 1, N, 1, Din, Dout)
+    g[:, :, np.arange(N) != at] = 0
+    gt, gb = parameter_gradients(pos, nbr, feat, g)
+    n = nbr[0, 0, at]
+    f, up = feat[0, :, n], g[0, :, at]
+    assert np.array_equal(gb, f[:, None] * up[None])
+    for d in range(3):
+        assert np.array_equal(gt[d], ((pos[0, d, n] - pos[0, d, at]) * f)[:, None] * up[None])
+
+
+@pytest.mark.parametrize("Din,Dout", FP32_WIDTHS)
+@pytest.mark.parametrize("where", ["gradient", "feature", "feature of the last point's neighbour"])
+@pytest.mark.parametrize("N", [300, 9000])
+def test_infinities_reach_the_parameter_gradients_as_such(Din, Dout, where, N, K=8):
+    say(f"tile parameter gradients, an infinite {where} among {N}, {Din}->{Dout}")
+    pos, nbr, feat, theta, bias, g = random_problem(14, 1, N, K, Din, Dout)
+    g = np.abs(g) + np.float32(0.1)                    # one sign: what is infinite stays so in the sum
+    if where == "gradient":
+        g[0, 1, 17] = -np.inf
+    else:
+        nbr[nbr == 17] = 18
+        if where != "feature":
+            nbr[0, 3, N - 1] = 17
+        else:
+            nbr[0, 3, 40:60] = 17
+        feat[0, 1, 17] = np.inf
+    gt, gb = parameter_gradients(pos, nbr, feat, g)
+    with np.errstate(invalid="ignore"):
+        p, f, up = (a[0].astype(np.float64) for a in (pos, feat, g))
+        rows = f.T[nbr[0]]
+        ref = [np.einsum("nc,no->co", ((p[d][nbr[0]] - p[d])[:, :, None] * rows).sum(axis=0), up.T) for d in range(3)]
+        ref.append(np.einsum("nc,no->co", rows.sum(axis=0), up.T))
+    assert np.isinf(ref[3]).any() and not np.isnan(ref[3]).any()
+    for got, want in zip([gt[0], gt[1], gt[2], gb], ref):
+        odd = ~np.isfinite(want)
+        assert np.array_equal(got[odd], want[odd].astype(np.float32), equal_nan=True)
+        assert rel_err(got[~odd], want[~odd]) <= TOL
+
+
 @pytest.mark.parametrize("B,N,K,Din,Dout", [
     (1, 8192, 4, 33, 64), (2, 4096, 4, 50, 47), (1, 8191, 4, 50, 47),         # 64 x 64 channels, both sides of the line
     (1, 1 << 17, 3, 5, 6), (2, 1 << 16, 3, 20, 13), (1, (1 << 17) - 1, 3, 20, 13), (1, 1 << 17, 3, 5, 64), (1, 1 << 17, 3, 3, 5),
