@@ -24,8 +24,8 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 // The channel-major kernels' workgroups take 64 points and 16 channels at a time: into how many parts their channels are dealt, so that
 // a cloud of few tiles fills the device (full: the workgroups that do).  A part sorts its tile's neighbours out for itself.
-// us, in one part and in as many, pooling forward / backward: 2k points x 112 channels 12.0 / 67 and 9.1 / 11.0; 10k x 64 9.7 / 39 and
-// 10.2 / 16.0; 26k x 128 to a quarter, K = 12, 29.4 / 44.6 and 16.9 / 30.3.
+// us, in one part and in as many, upsampling forward, 26k points x 128, K = 12, 35 and 27, 10k x 64, K = 8, 14.2 and 11.6; pooling to a quarter, 200k x 64,
+// K = 4, 26.8 and 25.2.
 static inline unsigned channel_parts(int64_t tiles, int C, int64_t full)
 {
     const int64_t most = (C + 15) / 16, wanted = full / (tiles > 0 ? tiles : 1);

@@ -6,6 +6,7 @@
 // fixed order), and that gather through a static per-tile plan that fetches
 // every listing row once per 32 points.
 #include "flex_common.hpp"
+#include <algorithm>
 #include <type_traits>
 
 namespace flex {
@@ -36,6 +37,25 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t total_tiles)
     return (slot < per_xcd && tile < total_tiles) ? tile : -1;
 }
 static inline unsigned xcd_grid(int64_t total_tiles) { return (unsigned)(((total_tiles + 7) >> 3) << 3); }
+
+// The channel-major kernels' workgroups take 64 points and 16 channels at a time, their channels dealt over `parts`.  Part by part: an
+// XCD takes all tiles of its channels one after the other, so that its L2 holds 16 rows of N values instead of pieces of all C, and no
+// other XCD reads them too.  What that gives where neighbours are anywhere in memory is beside the launches.  (grid.y: parts in
+// place of these, each XCD with its tiles of all of them.)
+struct PartTile { int part, parts; int64_t tile; };
+__device__ __forceinline__ PartTile xcd_part_tile(int64_t total_tiles, int parts)
+{
+    const int64_t at = xcd_tile(total_tiles * parts);
+    if (at < 0) return PartTile{0, 1, -1};
+    const int part = (int)((unsigned)at / (unsigned)total_tiles);       // (a grid has fewer than 2^24 workgroups of 256 threads)
+    return PartTile{part + (int)blockIdx.y, parts * (int)gridDim.y, at - part * total_tiles};
+}
+// every 16 channels a part of their own, as far as the grid reaches
+static inline int all_parts(int64_t tiles, int C)
+{
+    const int64_t most = (C + 15) / 16, reach = ((1 << 24) - 8) / (tiles > 0 ? tiles : 1);
+    return (int)std::max<int64_t>(1, std::min(most, reach));
+}
 
 // Point-major, C >= 4: one thread per (point, 4 channels); a block owns PT consecutive points.
 // The gather is latency-bound, so a thread first requests the ids of 8 neighbours, then their 8
@@ -127,10 +147,11 @@ __global__ __launch_bounds__(256) void pool_fwd_bcn_kernel(const float *__restri
                                                            float *__restrict__ out,
                                                            int32_t *__restrict__ argmax, int N, int L,
                                                            int K, int C, int tiles_per_cloud,
-                                                           int64_t total_tiles)
+                                                           int64_t total_tiles, int parts)
 {
     constexpr int U = 8;
-    const int64_t tile = xcd_tile(total_tiles);
+    const PartTile pt = xcd_part_tile(total_tiles, parts);
+    const int64_t tile = pt.tile;
     if (tile < 0) return;
     const int64_t b = tile / tiles_per_cloud;
     const int lane = threadIdx.x & 63;
@@ -143,7 +164,7 @@ __global__ __launch_bounds__(256) void pool_fwd_bcn_kernel(const float *__restri
     int n0[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) n0[u] = nb[(int64_t)min(u, K - 1) * N];      // past K: the last slot again
-    for (int c0 = (blockIdx.y * 4 + w) * CH; c0 < C; c0 += 4 * CH * gridDim.y) {
+    for (int c0 = (pt.part * 4 + w) * CH; c0 < C; c0 += 4 * CH * pt.parts) {
         const float *row[CH];
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch) row[ch] = feat + (b * C + min(c0 + ch, C - 1)) * N;
@@ -228,8 +249,12 @@ hipError_t launch_pool_fwd(const float *feat, const int32_t *nbr, float *out, in
     } else if (!bnc && N < (1 << 30)) {
         const int tpc = (N + 63) / 64;
         const int64_t tiles = (int64_t)B * tpc;
-        hipLaunchKernelGGL(pool_fwd_bcn_kernel<4>, dim3(xcd_grid(tiles), channel_parts(tiles, C, 2048)), dim3(256), 0, s, feat, nbr,
-                           (const int32_t *)nullptr, out, argmax, N, N, K, C, tpc, tiles);
+        // us, all channels a workgroup | dealt over grid.y to fill the device | part by part, K = 8, Z-order: 2k points x 112 channels 11.7 | 4.2 | 4.2,
+        // 26k x 128, K = 12, 51 | 40 | 37, 77k x 128 108 | 109 | 86, 1M x 128 777 | 783 | 765; in the order drawn: 2k x 112 15 | 4.8 | 4.7, 63k x 113, K = 6,
+        // 215 | 247 | 178, 77k x 128 503 | 501 | 336, 250k x 128 1438 | 1428 | 594
+        const int parts = all_parts(tiles, C);
+        hipLaunchKernelGGL(pool_fwd_bcn_kernel<4>, dim3(xcd_grid(tiles * parts)), dim3(256), 0, s, feat, nbr,
+                           (const int32_t *)nullptr, out, argmax, N, N, K, C, tpc, tiles, parts);
     } else {
         const int64_t total = (int64_t)B * N * C;
         int64_t blocks = (total + 255) / 256;
@@ -254,8 +279,12 @@ hipError_t launch_pool_sub_fwd(const float *feat, const int32_t *nbr, const int3
     } else if (!bnc && N < (1 << 30)) {
         const int tpc = (Ns + 63) / 64;
         const int64_t tiles = (int64_t)B * tpc;
-        hipLaunchKernelGGL(pool_fwd_bcn_kernel<4>, dim3(xcd_grid(tiles), channel_parts(tiles, C, 2048)), dim3(256), 0, s, feat, nbr, sel, out,
-                           argmax, N, Ns, K, C, tpc, tiles);
+        // Centres in Z-order share few of their neighbours' lines, and part by part asks for the lines' other channels again: us, K = 8, dealt over
+        // grid.y | part by part: 26k points x 128, K = 12, 18.5 | 16.1, 63k x 113, K = 6, 26.5 | 27.4, 130k x 128 30.2 | 30.6, 250k x 256 117 | 135, 1M x 128 273 |
+        // 301; in the order drawn 26k 43 | 23, 63k 61 | 53.
+        const int parts = tiles <= 384 ? all_parts(tiles, C) : 1;
+        hipLaunchKernelGGL(pool_fwd_bcn_kernel<4>, dim3(xcd_grid(tiles * parts), parts > 1 ? 1 : channel_parts(tiles, C, 2048)), dim3(256), 0, s, feat, nbr,
+                           sel, out, argmax, N, Ns, K, C, tpc, tiles, parts);
     } else {
         const int64_t total = (int64_t)B * Ns * C;
         int64_t blocks = (total + 255) / 256;
@@ -1005,12 +1034,14 @@ hipError_t launch_pool_fwd_planned(const float *feat, const int32_t *nbr, void *
 // lane = point, adds up each point's own stretch in list order.
 // SEL: the points are sel[b, 0..N) of the Nf whose lists in_off bounds (those outside have none): their lists are anywhere,
 // and the block numbers their entries one list after the other.
-template <int ECH, bool SEL>
+// WON: gradients are read where the winner is the entry's point, which it is for about one of K; else with the winners, which saves a
+// trip to memory where lists are short.
+template <int ECH, bool SEL, bool WON>
 __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
     const float *__restrict__ grad_out, const int32_t *__restrict__ argmax,
     const int32_t *__restrict__ in_off, const int32_t *__restrict__ in_src,
     const int32_t *__restrict__ sel, float *__restrict__ grad_feat, int N, int Nf, int L, int C, int tiles_per_cloud,
-    int64_t total_tiles)
+    int64_t total_tiles, int parts)
 {
     constexpr int CH = 4, U = 4, J = ECH / 64;
     static_assert(ECH % (64 * U) == 0, "a lane takes U entries of a chunk at a time");
@@ -1021,7 +1052,8 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
     // what the entry routes, per channel of the pass (rows private to a wave); entry i of point p sits at
     // column i + p, so that the points' stretches, which start about K apart, begin in different banks
     __shared__ float s_c[4 * CH][ECH + 64];
-    const int64_t tile = xcd_tile(total_tiles);
+    const PartTile pt = xcd_part_tile(total_tiles, parts);
+    const int64_t tile = pt.tile;
     if (tile < 0) return;
     const int64_t b = tile / tiles_per_cloud;
     const int lane = threadIdx.x & 63;
@@ -1050,7 +1082,7 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
     __syncthreads();
     const int E0 = s_off[0], E1 = s_off[64];
     const int my0 = s_off[lane], my1 = s_off[lane + 1];
-    for (int cg = blockIdx.y * 4 * CH; cg < C; cg += 4 * CH * gridDim.y) {
+    for (int cg = pt.part * 4 * CH; cg < C; cg += 4 * CH * pt.parts) {
         const int c0 = cg + w * CH;
         const int32_t *arow[CH];
         const float *grow[CH];
@@ -1088,28 +1120,39 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
 #pragma unroll
             for (int j0 = 0; j0 < J; j0 += U) {
                 if (j0 * 64 < nEc) {
-                    int l[U], t[U], a[CH][U];
+                    int l[U], t[U], m[U], a[CH][U];
                     float g[CH][U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int i = (j0 + u) * 64 + lane;
                         l[u] = s_l[i < nEc ? i : 0];
                         t[u] = i < nEc ? s_t[i] : 0;    // past the end: routes nothing
+                        m[u] = SEL ? s_m[t[u] & 63] : m0 + (t[u] & 63);
                     }
 #pragma unroll
                     for (int ch = 0; ch < CH; ++ch)
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
                             a[ch][u] = at_byte(arow[ch], 4u * (unsigned)l[u]);
-                            g[ch][u] = at_byte(grow[ch], 4u * (unsigned)l[u]);
+                            if constexpr (!WON) g[ch][u] = at_byte(grow[ch], 4u * (unsigned)l[u]);
                         }
+                    if constexpr (WON) {
+#pragma unroll
+                        for (int ch = 0; ch < CH; ++ch) {
+                            const auto row = __builtin_amdgcn_make_buffer_rsrc((void *)grow[ch], 0, (int)(4u * (unsigned)L), 0x00020000);
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {       // others ask for a place behind the row, which reads as zero
+                                const bool won = (t[u] & 64) && a[ch][u] == m[u];
+                                g[ch][u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(row, won ? (int)(4u * (unsigned)l[u]) : -4, 0, 0));
+                            }
+                        }
+                    }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int i = (j0 + u) * 64 + lane;
-                        const int m = SEL ? s_m[t[u] & 63] : m0 + (t[u] & 63);
 #pragma unroll
                         for (int ch = 0; ch < CH; ++ch)
-                            if (i < nEc) s_c[w * CH + ch][i + (t[u] & 63)] = ((t[u] & 64) && a[ch][u] == m) ? g[ch][u] : 0.f;
+                            if (i < nEc) s_c[w * CH + ch][i + (t[u] & 63)] = (WON || ((t[u] & 64) && a[ch][u] == m[u])) ? g[ch][u] : 0.f;
                     }
                 }
             }
@@ -1189,8 +1232,18 @@ hipError_t launch_pool_sub_bwd_gather(const float *grad_out, const int32_t *argm
     } else if (!bnc && L < (1 << 30)) {
         const int tpc = (N + 63) / 64;
         const int64_t tiles = (int64_t)B * tpc;
-        hipLaunchKernelGGL((pool_bwd_gather_bcn_kernel<512, false>), dim3(xcd_grid(tiles), channel_parts(tiles, C, 1024)), dim3(256), 0, s, grad_out,
-                           argmax, in_off, in_src, (const int32_t *)nullptr, grad_feat, N, N, L, C, tpc, tiles);
+        if (L == N) {
+            // us, K = 8, all channels a workgroup and every gradient | dealt over grid.y to fill the device | part by part, winners' gradients, Z-order: 2k
+            // points x 112 channels 64 | 11 | 11, 77k x 128 421 | 424 | 170, 1M x 128 2010 | 2000 | 1730; in the order drawn: 14k x 150 164 | 192 | 79, 77k
+            // x 128 2100 | 2130 | 528, 250k x 128 5510 | 5490 | 970
+            const int parts = all_parts(tiles, C);
+            hipLaunchKernelGGL((pool_bwd_gather_bcn_kernel<512, false, true>), dim3(xcd_grid(tiles * parts)), dim3(256), 0, s, grad_out, argmax, in_off,
+                               in_src, (const int32_t *)nullptr, grad_feat, N, N, L, C, tpc, tiles, parts);
+        } else
+            // lists of K / 4 entries for a kept quarter: their setting out, once a part, would be most of the work (400k points x 256, K = 4, in Z-order
+            // 329 us so, 422 part by part)
+            hipLaunchKernelGGL((pool_bwd_gather_bcn_kernel<512, false, false>), dim3(xcd_grid(tiles), channel_parts(tiles, C, 1024)), dim3(256), 0, s,
+                               grad_out, argmax, in_off, in_src, (const int32_t *)nullptr, grad_feat, N, N, L, C, tpc, tiles, 1);
     } else {
         const int64_t total = (int64_t)B * N * C;
         int64_t blocks = (total + 255) / 256;
@@ -1201,14 +1254,18 @@ hipError_t launch_pool_sub_bwd_gather(const float *grad_out, const int32_t *argm
     return hipGetLastError();
 }
 
-// Channel-major upsampling, backward: the sums of the kept points alone, over the larger layer's lists
+// Channel-major upsampling, backward: the sums of the kept points alone, over the larger layer's lists.  us, a quarter kept, K = 8, an element per
+// thread | these lists with channels dealt over grid.y and every gradient read | as here, Z-order: 26k points x 128, K = 12, 67 | 28 | 23, 33k x 13,
+// K = 32, 28 | 41 | 38, 1M x 128 2660 | 630 | 498; in the order drawn: 10k x 113 27 | 53 | 19, 33k x 13, K = 32, 33 | 54 | 41, 77k x 128 266 | 499 |
+// 199, 475k x 64, K = 9, 750 | 1425 | 594.
 hipError_t launch_upsample_bwd_bcn(const float *grad_out, const int32_t *argmax, const int32_t *sel, const int32_t *in_off,
                                    const int32_t *in_src, float *grad_small, int B, int Ns, int Nf, int C, hipStream_t s)
 {
     const int tpc = (Ns + 63) / 64;
     const int64_t tiles = (int64_t)B * tpc;
-    hipLaunchKernelGGL((pool_bwd_gather_bcn_kernel<512, true>), dim3(xcd_grid(tiles), channel_parts(tiles, C, 1024)), dim3(256), 0, s, grad_out, argmax,
-                       in_off, in_src, sel, grad_small, Ns, Nf, Nf, C, tpc, tiles);
+    const int parts = all_parts(tiles, C);
+    hipLaunchKernelGGL((pool_bwd_gather_bcn_kernel<512, true, true>), dim3(xcd_grid(tiles * parts)), dim3(256), 0, s, grad_out, argmax, in_off, in_src, sel,
+                       grad_small, Ns, Nf, Nf, C, tpc, tiles, parts);
     return hipGetLastError();
 }
 

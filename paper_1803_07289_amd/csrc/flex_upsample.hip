@@ -412,9 +412,11 @@ hipError_t launch_upsample_bwd(const float *grad_out, const int32_t *argmax, con
         const auto kernel = C % 4 == 0 ? upsample_bwd_bnc4_kernel<false> : upsample_bwd_bnc4_kernel<true>;
         hipLaunchKernelGGL(kernel, dim3(xcd_grid_up(tiles)), dim3(256), 0, s, grad_out, argmax, sel,
                            in_off, in_src, grad_small, BNs, Ns, Nf, C, PT, tiles);
-    } else if (!bnc && Nf < 1 << 30 && (int64_t)B * Ns * C >= 1 << 16) {
-        // below that an element per thread is all at once and has no lists to set out (us, it and here: 1.5k of 6k points x 16 channels
-        // 9.4 and 12.5, 1k x 33 9.5 and 12.3, 300 x 128 9.4 and 8.9, 5k x 64 17.7 and 12.4, 59k x 128, K = 16, 1530 and 266)
+    } else if (!bnc && Nf < 1 << 30 && (int64_t)B * Ns * C * C >= (int64_t)147456 * ((C + 15) / 16 * 16)) {
+        // Below that (outputs, with the channels of a workgroup that are missing taken off) an element per thread is all at once and
+        // has no lists to set out.  us, it and here, a quarter kept, K = 8, Z-order | as drawn: 4k points x 128 9.4 and 9.4 | 9.7 and 11.3, 20k x 32 11.0 and
+        // 10.0 | 12.1 and 12.2, 40k x 13 9.4 and 9.6 | 13.6 and 12.0, 80k x 3 7.8 and 11.9, 10k x 64 10.5 and 9.8 | 17.4 and 13.6; K = 32, 20k x 16 25
+        // and 38, 20k x 32 37.5 and 37.3 | 44.9 and 41.1
         return launch_upsample_bwd_bcn(grad_out, argmax, sel, in_off, in_src, grad_small, B, Ns, Nf, C, s);
     } else {
         hipLaunchKernelGGL(upsample_bwd_generic_kernel, dim3(capped_blocks((int64_t)B * Ns * C, 1 << 20)), dim3(256),

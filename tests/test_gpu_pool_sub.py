@@ -73,6 +73,29 @@ def test_channels_dealt_over_workgroups(C):
     test_flexpool_sub_matches_oracle(2, 130, 65, 9, C, fx.BCN)
 
 
+@pytest.mark.parametrize("Ns", [24576, 24577])               # part by part, and dealt over the grid's second dimension
+def test_channel_major_parts_of_many_centres(Ns):
+    test_flexpool_sub_matches_oracle(1, 24700, Ns, 3, 49, fx.BCN)
+
+
+@pytest.mark.parametrize("B,N,K,C", [(1, 63, 3, 1), (2, 130, 9, 15), (1, 64, 1, 16), (3, 65, 8, 17), (2, 700, 9, 130), (1, 2100, 32, 403)])
+def test_channel_major_pooling_part_by_part(B, N, K, C):
+    """A point on every list (entries in several rounds), points on none, ties, parts of fewer than 16 channels."""
+    say(f"pool channel-major B={B} N={N} K={K} C={C}")
+    rng = np.random.default_rng(N + C)
+    feat, g = (rng.integers(-3, 4, size=(B, C, N)).astype(np.float32) for _ in range(2))
+    nbr = rng.integers(0, N, size=(B, K, N)).astype(np.int32)
+    nbr[:, -1] = N // 2
+    nbr[nbr == N // 3] = N // 2
+    feat[:, ::2, N // 2] = 4
+    ro, ra = oracle.flexpool_fwd(feat, nbr)
+    out, arg = fx.flexpool_fwd(to_layout(feat, fx.BCN), dev(nbr), layout=fx.BCN)
+    gf = fx.flexpool_bwd(to_layout(g, fx.BCN), arg, layout=fx.BCN, in_edges=fx.flex_inedges_build(dev(nbr)))
+    torch.cuda.synchronize()
+    assert np.array_equal(from_layout(arg, fx.BCN), ra) and np.array_equal(from_layout(out, fx.BCN), ro)
+    assert np.array_equal(from_layout(gf, fx.BCN), oracle.flexpool_bwd(g, ra))          # sums of small whole numbers
+
+
 def test_flexpool_sub_equals_full_pooling_on_kept_rows():
     rng = np.random.default_rng(5)
     B, N, K, C, Ns = 2, 3000, 8, 64, 750

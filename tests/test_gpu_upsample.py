@@ -47,9 +47,11 @@ def test_rows_of_any_width(C):
 
 
 # channel-major: several workgroups to a tile's channels, entries in several rounds (a point that every centre lists), places of the
-# selection that name no point, more slots than the lists hold, the sizes on both sides of the backward kernels' line
+# selection that name no point, more slots than the lists hold, the sizes on both sides of the kernels' lines (forward 4096 points of 8
+# neighbours and 64 channels, backward 2304 kept points of 64)
 @pytest.mark.parametrize("B,Nf,Ns,K,C", [(2, 1040, 260, 9, 130), (1, 1040, 260, 64, 256), (1, 300, 75, 65, 17), (1, 4100, 1024, 8, 64), (1, 4100, 1023, 8, 64),
-                                         (3, 130, 65, 5, 400)])
+                                         (3, 130, 65, 5, 400), (2, 1040, 650, 9, 130), (1, 1040, 600, 64, 256), (3, 260, 130, 5, 400), (1, 16400, 16330, 3, 17),
+                                         (1, 4096, 1024, 8, 64), (1, 4095, 1024, 8, 64), (1, 9300, 2304, 8, 64), (1, 9300, 2303, 8, 64)])
 def test_layouts_agree_bit_for_bit(B, Nf, Ns, K, C):
     say(f"upsample layouts B={B} Nf={Nf} Ns={Ns} K={K} C={C}")
     rng = np.random.default_rng(Nf + K)
@@ -99,7 +101,8 @@ def test_flexupsample_room_scale():
     assert rel_err(from_layout(gs, fx.BNC), oracle.flexupsample_bwd(g, ra, sel)) <= 1e-5
 
 
-@pytest.mark.parametrize("Nf,Ns,K,C", [(45, 1, 7, 4), (33, 33, 17, 8), (150, 40, 100, 12), (64, 16, 9, 1028), (2100, 500, 2100, 4)])
+@pytest.mark.parametrize("Nf,Ns,K,C", [(45, 1, 7, 4), (33, 33, 17, 8), (150, 40, 100, 12), (64, 16, 9, 1028), (2100, 500, 2100, 4),
+                                       (2100, 500, 8, 33), (4200, 900, 5, 65), (8300, 2000, 8, 130)])     # 16, 8 and 4 points a workgroup
 def test_flexupsample_fwd_list_edges(Nf, Ns, K, C):
     """The forward pass sorts a workgroup's neighbours out first: lists with nothing but zero-filled neighbours and with none,
     K around the eight lanes a point has, fewer points per workgroup for long lists, rows wider than a workgroup."""
