@@ -384,12 +384,19 @@ hipError_t launch_upsample_fwd(const float *feat_small, const int32_t *inv, cons
     // 32 points a workgroup (eight lanes each) as far as their lists fit 16 KB
     int points = 32;
     while (points > 1 && (int64_t)points * K > 2048) points >>= 1;
-    const int64_t BN = (int64_t)B * Nf, tiles = (BN + points - 1) / points;
+    const int64_t BN = (int64_t)B * Nf;
+    // Fewer where a workgroup would go over its rows several times and the device is not full: us, 32 points and so, K = 8: 300 points x 113 10.2
+    // and 7.5 (an element per thread 7.9), 3k x 113 11.3 and 8.2 (10.0), 3k x 256 14.7 and 8.4, 10k x 150 13.4 and 11.4, 10k x 33 9.0 and 8.6.
+    while (bnc && points > 4 && (int64_t)points * C > 1024 && BN / points < 1024) points >>= 1;
+    const int64_t tiles = (BN + points - 1) / points;
     if (bnc && C >= 4 && K <= 8192) {          // one point's list of up to 64 KB
         const auto kernel = C % 4 == 0 ? upsample_fwd_bnc4_kernel<false> : upsample_fwd_bnc4_kernel<true>;
         hipLaunchKernelGGL(kernel, dim3(xcd_grid_up(tiles)), dim3(256), sizeof(int2) * points * K, s, feat_small,
                            inv, nbr, out, argmax, BN, Ns, Nf, K, C, points, tiles);
-    } else if (!bnc && K <= 64 && Ns < 1 << 30) {
+    } else if (!bnc && K <= 64 && Ns < 1 << 30 && (K > 10 || BN * C * K >= 1 << 21)) {
+        // Few outputs of few neighbours are sooner compared by a thread each than the neighbours sorted out: us, that and here, K = 8, 300 points x 64
+        // 7.9 and 9.1, 1k x 128 8.5 and 9.5, 2k x 128 9.9 and 9.9, 2k x 256 13.0 and 12.1; K = 6, 4k x 64 9.4 and 9.9; K = 4, 8k x 64 10.7 and 9.9;
+        // K = 16, 1k x 3 10.1 and 9.0, 1k x 64 10.2 and 10.0.
         const int tpc = (Nf + 63) / 64;
         const int64_t tiles64 = (int64_t)B * tpc;
         hipLaunchKernelGGL(upsample_fwd_bcn_kernel<4>, dim3(xcd_grid_up(tiles64), channel_parts(tiles64, C, 2048)), dim3(256),
