@@ -322,6 +322,7 @@ __device__ __forceinline__ int lds_count(int *counter, int key, bool on, int &al
     return old;
 }
 
+template <int UN>                             // edges a thread has under way
 __global__ __launch_bounds__(BUCKET_NT) void edge_count_kernel(const EdgeRuns p, int32_t *__restrict__ bucket_cnt,
                                                                int buckets)
 {
@@ -330,7 +331,6 @@ __global__ __launch_bounds__(BUCKET_NT) void edge_count_kernel(const EdgeRuns p,
     __syncthreads();
     const int64_t first = (int64_t)blockIdx.x * p.run;
     const int n = (int)min((int64_t)p.run, p.E - first);
-    constexpr int UN = 8;
     int alone = 0;
     EdgeWalk w(p, min(first + threadIdx.x, (int64_t)p.E - 1));
     for (int e0 = 0; e0 < n; e0 += BUCKET_NT * UN) {
@@ -804,11 +804,15 @@ hipError_t launch_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int 
         const size_t lds = sizeof(int) * (size_t)buckets;
         hipError_t e = launch_fill_zero(cnt, sizeof(int32_t) * (size_t)buckets, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(edge_count_kernel, g, blk, lds, s, p, cnt, buckets);
+        // (34k points of 4 neighbours to a quarter, a run of one edge a thread, eight asked for: 4.8 us, two 3.9)
+        hipLaunchKernelGGL(run <= 2 * BUCKET_NT ? edge_count_kernel<2> : edge_count_kernel<8>, g, blk, lds, s, p, cnt, buckets);
         hipLaunchKernelGGL(edge_scan_kernel, dim3(1), blk, 0, s, cnt, off, cur, buckets);
         if (buckets <= DEAL_BUCKETS_MAX && run >= DEAL_RUN_MIN) hipLaunchKernelGGL(edge_deal_kernel<true>, g, blk, lds, s, p, cur, st_src, st_tgt, buckets);
         else hipLaunchKernelGGL(edge_deal_kernel<false>, g, blk, lds, s, p, cur, st_src, st_tgt, buckets);
-        const auto sort = K <= 10 ? edge_sort_kernel<16> : K <= 16 ? edge_sort_kernel<24> : edge_sort_kernel<32>;
+        // by the mean list; us of the build with W = 8 and 16: a mean of one, 140k points 22.2 and 24.1, 1M 44.6 and 48.6 (K = 8 to a quarter); K = 4,
+        // all points, 30k 22.5 and 23.7; a mean of four from K = 8, half the points, 77k 25.1 and 24.6; K = 6, all points, 18k 25 and 21
+        const auto sort = E <= 3 * BN || K <= 4 ? edge_sort_kernel<8> : E <= 10 * BN ? edge_sort_kernel<16> : E <= 16 * BN ? edge_sort_kernel<24>
+                                                                                                                         : edge_sort_kernel<32>;
         hipLaunchKernelGGL(sort, dim3((unsigned)buckets), blk, 0, s, off, st_src, st_tgt, in_off, in_src, BN, (int)E, p.shift);
         return hipGetLastError();
     }

@@ -51,12 +51,12 @@ def test_hub_points_past_a_buckets_lds():
     check(nbr)
 
 
-# lists on both sides of what a thread (16, 24 or 32, by K), a wave (64) and a workgroup order in a bucket's LDS, half of them with
+# lists on both sides of what a thread (8, 16, 24 or 32, by K), a wave (64) and a workgroup order in a bucket's LDS, half of them with
 # every centre twice
-@pytest.mark.parametrize("K", [8, 10, 11, 16, 17])
+@pytest.mark.parametrize("K", [4, 8, 10, 11, 16, 17])
 def test_lists_of_every_length(K):
     say(f"in-edges, lists of every length, K={K}")
-    N, sizes = 20_000, [1, 2, 15, 16, 17, 23, 24, 25, 31, 32, 33, 63, 64, 65, 66, 127, 128, 129, 1000, 2049]
+    N, sizes = 20_000, [1, 2, 7, 8, 9, 15, 16, 17, 23, 24, 25, 31, 32, 33, 63, 64, 65, 66, 127, 128, 129, 1000, 2049]
     rng = np.random.default_rng(K)
     nbr = rng.integers(len(sizes), N, size=(1, K, N))
     for i, n in enumerate(sizes):
@@ -106,6 +106,14 @@ def test_kept_centres():
     nbr = rng.integers(0, 5000, size=(2, 8, 5000)).astype(np.int32)
     sel = np.sort(np.stack([rng.choice(5000, 1250, replace=False) for _ in range(2)])).astype(np.int32)
     check(nbr, sel)
+
+
+@pytest.mark.parametrize("Ns", [15_000, 15_001])             # both sides of three entries a list
+def test_kept_centres_of_several_buckets(Ns):
+    rng = np.random.default_rng(Ns)
+    nbr = rng.integers(0, 40_000, size=(1, 8, 40_000)).astype(np.int32)
+    nbr[0, 0, :40], nbr[0, 1, ::7] = 5, 6
+    check(nbr, rng.permutation(40_000)[None, :Ns].astype(np.int32))
 
 
 def check_large(nbr, sel=None):
