@@ -325,6 +325,14 @@ __global__ __launch_bounds__(256) void knn_sort_kernel(const int32_t *__restrict
     }
 }
 
+// Every operation rounded on its own.  (The pragma: __fmul_rn and __fadd_rn are plain operators to this compiler, which makes fused
+// multiply-adds of them, and one pair in some 10^6 whose distances differ in the last bit changed places.)
+__device__ __forceinline__ float knn_d2(float dx, float dy, float dz)
+{
+#pragma clang fp contract(off)
+    return (dx * dx + dy * dy) + dz * dz;
+}
+
 // (d2, id) as one number whose order is theirs: the bits of d2 (non-negative: they order like the value) above those
 // of id, read as a double -- positive, and finite since a float's exponent field fills only the upper bits of a
 // double's -- so that the sorted insertion is a minimum and a maximum per place.  (Double arithmetic keeps denormals
@@ -361,9 +369,7 @@ __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict
 #pragma unroll
         for (int k = 0; k < K; ++k) best[k] = knn_key(__builtin_inff(), 0x7fffffff);
         auto offer = [&](const float4 &q, bool on) {
-            const float dx = __fsub_rn(q.x, me.x), dy = __fsub_rn(q.y, me.y), dz = __fsub_rn(q.z, me.z);
-            const float d2 = __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
-            double x = knn_key(d2, __float_as_int(q.w));
+            double x = knn_key(knn_d2(q.x - me.x, q.y - me.y, q.z - me.z), __float_as_int(q.w));
             if (on && x < best[K - 1]) {
 #pragma unroll
                 for (int k = 0; k < K; ++k) {        // sorted insertion: the candidate bubbles down the list
@@ -480,8 +486,7 @@ struct GroupBest {
     }
     __device__ __forceinline__ void offer(float mx, float my, float mz, float x, float y, float z, int id)
     {
-        const float dx = __fsub_rn(x, mx), dy = __fsub_rn(y, my), dz = __fsub_rn(z, mz);
-        double c = knn_key(__fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz)), id);
+        double c = knn_key(knn_d2(x - mx, y - my, z - mz), id);
         if (c < best[K - 1]) {
 #pragma unroll
             for (int k = 0; k < K; ++k) {            // sorted insertion: the candidate bubbles down the list

@@ -63,6 +63,14 @@ def test_knn_on_both_sides_of_every_line(B, N, K):
     _check(pos, K)
 
 
+# all against all, 16, 8 and 4 lanes to a point, a thread each: so many lists that some distances differ in their last bit alone, and in
+# the other direction if a product and a sum are rounded together
+@pytest.mark.parametrize("B,N", [(12, 1400), (6, 5000), (9, 5461), (16, 6000), (24, 5500)])
+def test_knn_ranks_by_distances_rounded_step_by_step(B, N, K=32):
+    say(f"knn rounding B={B} N={N}")
+    _check(np.random.default_rng(N).random((B, 3, N)).astype(np.float32), K)
+
+
 def test_knn_degenerate_shapes_on_the_grid():
     rng = np.random.default_rng(2)
     N = 4500
