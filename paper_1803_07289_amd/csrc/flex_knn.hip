@@ -44,12 +44,12 @@ __device__ __forceinline__ float from_ordered_bits(unsigned u)
 }
 
 // bbox[b][0..2] = min, [3..5] = max, as order-preserving unsigned keys (min starts at ~0, max at 0); the buckets' counters
-// start at zero
+// start at zero, and so do the clouds' pairs, a float each behind the boxes
 __global__ __launch_bounds__(256) void knn_init_kernel(unsigned *__restrict__ bbox, int B, int32_t *__restrict__ cnt,
                                                        int64_t buckets)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < 6 * B) bbox[i] = (i % 6 < 3) ? 0xffffffffu : 0u;
+    if (i < 7 * B) bbox[i] = (i < 6 * B && i % 6 < 3) ? 0xffffffffu : 0u;
     for (int64_t c = i; c < buckets; c += (int64_t)gridDim.x * blockDim.x) cnt[c] = 0;
 }
 
@@ -263,9 +263,12 @@ __global__ __launch_bounds__(KNN_DEAL_NT) void knn_deal_kernel(const float *__re
 
 // rec = the points in cell order, off[b*cells_per_cloud + cell] = where a cell's begin, place[b*N + id] = a point's record, inside
 // the cloud.  Dynamic LDS: 2^shift counters.
+// pairs[b]: less than no number if the grid is one layer of cells (layers), else how many records lie in the row of three
+// cells around every record's own, added up (rows; a bucket's first and last cell without the neighbour outside)
 __global__ __launch_bounds__(256) void knn_sort_kernel(const int32_t *__restrict__ bucket_off, const float4 *__restrict__ st_rec,
                                                        const unsigned *__restrict__ bbox, float4 *__restrict__ rec,
-                                                       int32_t *__restrict__ off, int32_t *__restrict__ place, int N,
+                                                       int32_t *__restrict__ off, int32_t *__restrict__ place,
+                                                       float *__restrict__ pairs, bool layers, bool rows, int N,
                                                        int64_t cells_per_cloud, const KnnBuckets k)
 {
     extern __shared__ int s_at[];                // counts, then the next record of every cell
@@ -289,6 +292,15 @@ __global__ __launch_bounds__(256) void knn_sort_kernel(const int32_t *__restrict
     const int per = cells / 256, i0 = tid * per;
     int sum = 0;
     for (int i = 0; i < per; ++i) sum += s_at[i0 + i];
+    if (layers && blockIdx.x == 0 && tid == 0 && min(min(g.n[0], g.n[1]), g.n[2]) == 1) atomicAdd(&pairs[b], -__builtin_inff());
+    if (rows) {
+        float mine = 0.f;
+        for (int i = i0; i < i0 + per; ++i)
+            mine += (float)s_at[i] * (float)(s_at[i] + (i > 0 ? s_at[i - 1] : 0) + (i + 1 < cells ? s_at[i + 1] : 0));
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d, 64);
+        if (lane == 0 && mine > 0.f) atomicAdd(&pairs[b], mine);
+    }
     int x = sum;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -349,9 +361,9 @@ __device__ __forceinline__ double knn_key(float d2, int id) { return __hiloint2d
 // and not for 90.  Two records a step: what a step costs beside them, the row's end above all, is paid half as often.  Both
 // together: 168 -> 127 us there, 1M points in a cube (where the second shell takes most of the time) the whole call 412 -> 402.
 template <int K>
-__global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict__ rec, const int32_t *__restrict__ off,
-                                                        const unsigned *__restrict__ bbox, int32_t *__restrict__ lists,
-                                                        int N, int64_t cells_per_cloud)
+__device__ __forceinline__ void knn_search(const float4 *__restrict__ rec, const int32_t *__restrict__ off,
+                                           const unsigned *__restrict__ bbox, int32_t *__restrict__ lists, int N,
+                                           int64_t cells_per_cloud)
 {
     __shared__ int s_beg[9][256], s_end[9][256];
     const int b = blockIdx.y, tid = threadIdx.x;
@@ -455,6 +467,21 @@ __global__ __launch_bounds__(256) void knn_query_kernel(const float4 *__restrict
     }
 }
 
+// Waves a SIMD that the K best in registers leave room for; S: lanes to a point.  (Left to itself the compiler takes two registers more
+// at some K, and a wave less.)
+constexpr int knn_waves(int K, int S)
+{
+    return K <= 2 ? 7 : K <= 4 ? (S == 1 ? 7 : S == 16 && K == 4 ? 5 : 6) : K <= 6 ? 5 : K <= 8 ? (S <= 4 ? 5 : 4) : K <= 12 ? 4 : K <= 16 ? 3 : 2;
+}
+
+template <int K>
+__global__ __launch_bounds__(256, knn_waves(K, 1)) void knn_query_kernel(const float4 *__restrict__ rec, const int32_t *__restrict__ off,
+                                                        const unsigned *__restrict__ bbox, int32_t *__restrict__ lists,
+                                                        int N, int64_t cells_per_cloud)
+{
+    knn_search<K>(rec, off, bbox, lists, N, cells_per_cloud);
+}
+
 // ---- several lanes to a point ---------------------------------------------------------------------------
 // minimum over the S lanes (a power of two, at most 16) of the caller's group, in each of them
 template <int CTRL>
@@ -519,14 +546,21 @@ struct GroupBest {
 
 // The search above with S lanes to a point, for clouds whose points are too few to fill the device a thread each: the nine rows'
 // bounds are asked for by as many lanes, the records of all of them dealt out one by one, a shell's rows one by one.
+// Merging costs the same however few records a point has around it, and in a layer of cells there are hardly more than K (nine cells;
+// scanned surfaces in a box of cells have 4 K to 6 K, points that fill it 3 K).  A cloud with fewer pairs (knn_sort_kernel) than `few` is searched
+// a thread to a point all the same.
 template <int K, int S>
-__global__ __launch_bounds__(256) void knn_query_group_kernel(const float4 *__restrict__ rec, const int32_t *__restrict__ off,
-                                                              const unsigned *__restrict__ bbox, int32_t *__restrict__ lists,
-                                                              int N, int64_t cells_per_cloud)
+__global__ __launch_bounds__(256, knn_waves(K, S)) void knn_query_group_kernel(const float4 *__restrict__ rec, const int32_t *__restrict__ off,
+                                                              const unsigned *__restrict__ bbox, const float *__restrict__ pairs,
+                                                              float few, int32_t *__restrict__ lists, int N, int64_t cells_per_cloud)
 {
     constexpr int G = 256 / S;
     __shared__ int s_beg[9][G], s_end[9][G];
     const int b = blockIdx.y, sub = threadIdx.x % S, grp = threadIdx.x / S;
+    if (pairs[b] < few) {
+        if ((int)blockIdx.x * 256 < N) knn_search<K>(rec, off, bbox, lists, N, cells_per_cloud);
+        return;
+    }
     const KnnGrid g = knn_grid(bbox, b, cells_per_cloud);
     const int32_t *offb = off + b * cells_per_cloud;
     const float span = fmaxf(fmaxf(g.n[0], g.n[1]), (float)g.n[2]) * g.h;
@@ -680,7 +714,7 @@ static size_t knn_used_bytes(int B, int N, int K)
 {
     const int64_t cpc = knn_cell_cap(N, K), BN = (int64_t)B * N;
     return align256(sizeof(float4) * (size_t)BN) + align256(sizeof(int32_t) * (size_t)BN) + align256(sizeof(int32_t) * (size_t)(B * cpc + 1)) +
-           align256(sizeof(unsigned) * 6 * (size_t)B) + align256(sizeof(int32_t) * (size_t)(3 * (int64_t)B * knn_buckets(cpc).n + 1)) +
+           align256(sizeof(unsigned) * 7 * (size_t)B) + align256(sizeof(int32_t) * (size_t)(3 * (int64_t)B * knn_buckets(cpc).n + 1)) +
            std::max(align256(sizeof(int32_t) * (size_t)BN * K), align256(sizeof(float4) * (size_t)BN));
 }
 
@@ -701,14 +735,36 @@ size_t knn_ws_bytes(int B, int N, int K)
 static bool knn_all(int64_t B, int64_t N) { return N <= 4096 && B * N * N <= 25 << 20; }
 
 // Lanes to a point.  A thread's search is a chain of dependent reads that few points leave uncovered; merging costs the more the
-// more lanes.  us, the whole call, with 1, 4, 8 and 16 lanes: surfaces, K = 8, 30k points 126, 73, 58, 52; 65k 140, 82, 69, 68; 100k 171, 92,
-// 84, 87; 250k 139, 123, 132, 155; 1M 221, 321; K = 16, 8k 243, 127, 94, 70; a filled cube, K = 8, 5.5k 90, 50, 42, 36; 65k 88, 66, 71, 83;
-// 100k 94, 88, 100, 115; 300k 138, 176.  With K = 1 a list is one number: 50k 33, 35, 35, 38.
+// more lanes.  us, the whole call, with 1, 4, 8 and 16 lanes: a room, K = 8, 30k points 131, 77, 64, 56; 65k 139, 90, 76, 71; 90k 151, 109, 86,
+// 85; 130k 133, 100, 94, 104; 200k 134, 107, 116, 136; K = 16, 30k 194, 111, 85, 79; 130k 223, 159, 148, 169; box surfaces, K = 8, 30k 185, 105, 83, 73;
+// a filled cube, K = 8, 15k 81, 49, 43, 40; 65k 91, 69, 76, 88; 90k 112, 90, 99, 110; 130k 105, 104, 124, 147; 200k 112, 133.  With K = 1 a list is one
+// number: 50k 33, 35, 35, 38.
+// Clouds whose points have few others around them would lose from so many points on that they fill the device a thread each (layers, rows of
+// cells).  us, lanes and a thread: a sheet, K = 8, 47k points 58.6 and 58.0, 130k 86.9 and 72.3; K = 16, 30k 85 and 71, 65k 102 and 76; K = 32, 30k 179 and
+// 104; a cube, K = 16, 65k 115 and 110, 130k 166 and 146; K = 32, 47k 164 and 169, 65k 222 and 182.  Records in the row of three cells, of K: cubes 0.38
+// to 0.49, surfaces in boxes 0.6 and more, 0.9 at such sizes.
 static int knn_lanes(int64_t points, int K)
 {
     if (points <= 1 << 15) return 16;
     if (K < 4) return 1;
     return points <= 1 << 16 ? 8 : points <= 1 << 17 ? 4 : 1;
+}
+
+template <int K>
+static void launch_knn_query(const float4 *rec, const int32_t *off, const unsigned *bbox, int32_t *lists, int B, int N, int64_t cells_per_cloud,
+                             const float *pairs, float few, hipStream_t s)
+{
+    const int lanes = knn_lanes((int64_t)B * N, K);
+    const dim3 grid((unsigned)std::min<int64_t>(((int64_t)N * lanes + 255) / 256, 65535), B);
+    auto groups = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, rec, off, bbox, pairs, few, lists, N, cells_per_cloud);
+    };
+    if (lanes == 16) return groups(knn_query_group_kernel<K, 16>);
+    if constexpr (K >= 4) {
+        if (lanes == 8) return groups(knn_query_group_kernel<K, 8>);
+        if (lanes == 4) return groups(knn_query_group_kernel<K, 4>);
+    }
+    hipLaunchKernelGGL(knn_query_kernel<K>, grid, dim3(256), 0, s, rec, off, bbox, lists, N, cells_per_cloud);
 }
 
 #define FLEX_KNN_KS(CASE) \
@@ -733,12 +789,12 @@ hipError_t launch_knn(const float *pos, int32_t *nbr, int B, int N, int K, void 
     float4 *rec = (float4 *)at;       at += align256(sizeof(float4) * (size_t)B * N);
     int32_t *place = (int32_t *)at;   at += align256(sizeof(int32_t) * (size_t)B * N);
     int32_t *off = (int32_t *)at;     at += align256(sizeof(int32_t) * (size_t)(cells + 1));
-    unsigned *bbox = (unsigned *)at;  at += align256(sizeof(unsigned) * 6 * (size_t)B);
+    unsigned *bbox = (unsigned *)at;  at += align256(sizeof(unsigned) * 7 * (size_t)B);
     int32_t *cnt = (int32_t *)at, *cur = cnt + buckets, *boff = cur + buckets;
     at += align256(sizeof(int32_t) * (size_t)(3 * buckets + 1));
     int32_t *lists = (int32_t *)at;               // written when the staged points are done with
     float4 *st_rec = (float4 *)at;
-    const int64_t ib = cdiv64(buckets > 6 * (int64_t)B ? buckets : 6 * (int64_t)B, 256);
+    const int64_t ib = cdiv64(buckets > 7 * (int64_t)B ? buckets : 7 * (int64_t)B, 256);
     hipLaunchKernelGGL(knn_init_kernel, dim3((unsigned)(ib < 8192 ? ib : 8192)), dim3(256), 0, s, bbox, B, cnt, buckets);
     const int bb = (N + 4095) / 4096;                      // four points per thread
     hipLaunchKernelGGL(knn_bbox_kernel, dim3(bb < 256 ? bb : 256, B), dim3(1024), 0, s, pos, bbox, N);
@@ -756,27 +812,21 @@ hipError_t launch_knn(const float *pos, int32_t *nbr, int B, int N, int K, void 
     if (all <= 1 << 17) deal(std::integral_constant<int, 1>{});
     else if (all <= 1 << 19) deal(std::integral_constant<int, 2>{});
     else deal(std::integral_constant<int, 4>{});
-    hipLaunchKernelGGL(knn_sort_kernel, dim3(k.n, B), dim3(256), sizeof(int) << k.shift, s, boff, st_rec, bbox, rec, off, place, N,
+    const int64_t entries = (int64_t)B * N * K;
+    const bool lanes = knn_lanes((int64_t)B * N, K) > 1, layers = lanes && entries > 7 << 15 && (int64_t)B * N > 1 << 14, rows = lanes && entries > 3 << 19;
+    float *pairs = (float *)(bbox + 6 * (int64_t)B);
+    hipLaunchKernelGGL(knn_sort_kernel, dim3(k.n, B), dim3(256), sizeof(int) << k.shift, s, boff, st_rec, bbox, rec, off, place, pairs, layers, rows, N,
                        cpc, k);
-    int qb = (int)((N + 255) / 256);
-    if (qb > 65535) qb = 65535;
-    const int lanes = knn_lanes((int64_t)B * N, K);
-    const dim3 group_grid((unsigned)std::min<int64_t>(((int64_t)N * lanes + 255) / 256, 65535), B);
-#define FLEX_KNN_GROUP(KK, S) \
-    hipLaunchKernelGGL((knn_query_group_kernel<KK, S>), group_grid, dim3(256), 0, s, rec, off, bbox, lists, N, cpc)
+    const float few = rows ? 0.45f * (float)K * (float)N : -1.f;
 #define FLEX_KNN_CASE(KK) \
-    case KK: \
-        if (lanes == 16) FLEX_KNN_GROUP(KK, 16); \
-        else if (lanes == 8) FLEX_KNN_GROUP(KK, 8); \
-        else if (lanes == 4) FLEX_KNN_GROUP(KK, 4); \
-        else hipLaunchKernelGGL(knn_query_kernel<KK>, dim3(qb, B), dim3(256), 0, s, rec, off, bbox, lists, N, cpc); \
-        break;
+    case KK: launch_knn_query<KK>(rec, off, bbox, lists, B, N, cpc, pairs, few, s); break;
     switch (K) {
         FLEX_KNN_KS(FLEX_KNN_CASE)
     default: return hipErrorInvalidValue;
     }
 #undef FLEX_KNN_CASE
-#undef FLEX_KNN_GROUP
+    int qb = (int)((N + 255) / 256);
+    if (qb > 65535) qb = 65535;
     hipLaunchKernelGGL(knn_place_kernel, dim3(qb, B), dim3(256), 0, s, lists, place, nbr, N, K);
     return hipGetLastError();
 }

@@ -71,6 +71,18 @@ def test_knn_ranks_by_distances_rounded_step_by_step(B, N, K=32):
     _check(np.random.default_rng(N).random((B, 3, N)).astype(np.float32), K)
 
 
+# clouds searched a thread to a point although there are lanes to spare, and others of the same batch that are not: one layer of cells beyond
+# 229376 entries and 16384 points, filled boxes beyond 3 * 2^19 entries
+@pytest.mark.parametrize("B,N,K", [(2, 14_336, 8), (2, 14_337, 8), (4, 4097, 12), (4, 4097, 16), (3, 12_000, 8), (7, 9500, 4), (9, 5462, 32), (9, 5461, 32), (6, 11_000, 24)])
+def test_knn_of_clouds_with_few_records_around(B, N, K):
+    say(f"knn few records B={B} N={N} K={K}")
+    rng = np.random.default_rng(N + K)
+    pos = rng.random((B, 3, N)).astype(np.float32)
+    pos[1::3, 2] = 0.25                                                          # a plane
+    pos[2::3, 0] = (rng.random(pos[2::3, 0].shape) < 0.5) + 0.001 * pos[2::3, 0]       # two walls far apart
+    _check(pos, K)
+
+
 def test_knn_degenerate_shapes_on_the_grid():
     rng = np.random.default_rng(2)
     N = 4500
