@@ -279,15 +279,28 @@ __global__ __launch_bounds__(256) void knn_sort_kernel(const int32_t *__restrict
     for (int i = tid; i < cells; i += 256) s_at[i] = 0;
     const KnnGrid g = knn_grid(bbox, b, cells_per_cloud);
     auto cell = [&](const float4 &q) { return knn_linear_cell(g, q.x, q.y, q.z) & (cells - 1); };
+    // each(f): f of every point, the next ones already requested.  (A cloud whose box a few stray points stretch has most of its points in few
+    // buckets, and this is their time: a sheet of 1M points and 16 outside it by its own length, sixteen buckets of 65k, 229 us and 170; 4M of it, all
+    // in one, 3240 and 2170; a cube without 22.7 and 21.7.)
+    auto each = [&](auto &&f) {
+        float4 next[UN];
+        auto request = [&](int i0) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) next[u] = st_rec[beg + min(i0 + 256 * u, n - 1)];
+        };
+        if (tid < n) request(tid);
+        for (int i0 = tid; i0 < n; i0 += 256 * UN) {
+            float4 q[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) q[u] = next[u];
+            if (i0 + 256 * UN < n) request(i0 + 256 * UN);
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+                if (i0 + 256 * u < n) f(q[u]);
+        }
+    };
     __syncthreads();
-    for (int i0 = tid; i0 < n; i0 += 256 * UN) {
-        float4 q[UN];
-#pragma unroll
-        for (int u = 0; u < UN; ++u) q[u] = st_rec[beg + min(i0 + 256 * u, n - 1)];
-#pragma unroll
-        for (int u = 0; u < UN; ++u)
-            if (i0 + 256 * u < n) atomicAdd(&s_at[cell(q[u])], 1);
-    }
+    each([&](const float4 &q) { atomicAdd(&s_at[cell(q)], 1); });
     __syncthreads();
     const int per = cells / 256, i0 = tid * per;
     int sum = 0;
@@ -322,19 +335,12 @@ __global__ __launch_bounds__(256) void knn_sort_kernel(const int32_t *__restrict
     for (int i = tid; i < cells && c0 + i < cells_per_cloud; i += 256) my_off[i] = s_at[i];
     if (b == (int)gridDim.y - 1 && blockIdx.x == gridDim.x - 1 && tid == 0) off[gridDim.y * cells_per_cloud] = (b + 1) * N;
     __syncthreads();
-    for (int i0 = tid; i0 < n; i0 += 256 * UN) {
-        float4 q[UN];
-#pragma unroll
-        for (int u = 0; u < UN; ++u) q[u] = st_rec[beg + min(i0 + 256 * u, n - 1)];
-#pragma unroll
-        for (int u = 0; u < UN; ++u)
-            if (i0 + 256 * u < n) {
-                const int at = atomicAdd(&s_at[cell(q[u])], 1);
-                const int id = min((unsigned)__float_as_int(q[u].w), (unsigned)(N - 1));
-                rec[at] = make_float4(q[u].x, q[u].y, q[u].z, __int_as_float(id));
-                place[(int64_t)b * N + id] = at - b * N;
-            }
-    }
+    each([&](const float4 &q) {
+        const int at = atomicAdd(&s_at[cell(q)], 1);
+        const int id = min((unsigned)__float_as_int(q.w), (unsigned)(N - 1));
+        rec[at] = make_float4(q.x, q.y, q.z, __int_as_float(id));
+        place[(int64_t)b * N + id] = at - b * N;
+    });
 }
 
 // Every operation rounded on its own.  (The pragma: __fmul_rn and __fadd_rn are plain operators to this compiler, which makes fused

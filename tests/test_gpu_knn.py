@@ -112,6 +112,28 @@ def test_knn_of_clouds_dealt_into_buckets(B, N, K):
             assert np.array_equal(nbr[b, :, l], np.lexsort((np.arange(N), d2))[:K]), (b, l)
 
 
+# most points in a few cells of a box that others stretch: a bucket of as many points as a workgroup sorts alone (8208) and one more, several
+# such buckets that begin and end anywhere, a cloud without beside one with
+@pytest.mark.parametrize("sizes", [(8208,), (8209,), (8192, 8209), (20_000, 9000, 100, 8300)])
+@pytest.mark.parametrize("K", [8, 3])
+def test_knn_of_clouds_that_stray_points_stretch(sizes, K):
+    say(f"knn piles {sizes} K={K}")
+    rng = np.random.default_rng(sum(sizes) + K)
+    at = rng.permutation(27)[: len(sizes)]                                       # corners of a lattice, buckets apart
+    p = [rng.random((3, n)) * 0.02 + 10.0 * np.array([[c // 9], [c // 3 % 3], [c % 3]]) for n, c in zip(sizes, at)]
+    p.append(rng.random((3, 500)) * 25 + 1)
+    p = np.concatenate(p, axis=1).astype(np.float32)
+    p[:, 7], p[:, 8:12] = p[:, 5], p[:, 6:7]                                     # coincident points
+    pos = np.stack([p[:, rng.permutation(p.shape[1])], rng.random(p.shape).astype(np.float32)])
+    _check(pos, K)
+    for left in (0x7F, 0xFF):
+        ws = ExactWorkspace(fx.OP_KNN, *pos.shape[::2], K, 1, 1, fx.BCN)
+        ws.ws.fill_(left)
+        got = fx.flex_knn(dev(pos), K, workspace=ws.ws)
+        ws.check()
+        assert torch.equal(got, fx.flex_knn(dev(pos), K))
+
+
 # a lane group and a thread to a point
 @pytest.mark.parametrize("N", [9000, 140_000])
 @pytest.mark.parametrize("left", [0, 0x7F, 0xFF])
@@ -129,7 +151,7 @@ def test_knn_takes_nothing_from_what_the_workspace_held(N, left, K=8):
         assert np.array_equal(got.cpu().numpy(), oracle.knn(pos, K))
 
 
-@pytest.mark.parametrize("N", [600, 4500])
+@pytest.mark.parametrize("N", [600, 4500, 12_000])
 def test_knn_infinite_locations(N):
     """At infinity a point is as far as can be from the others and no distance from its like."""
     pos = np.random.default_rng(8).random((1, 3, N)).astype(np.float32)
