@@ -937,8 +937,8 @@ int flexconv_bwd(const float *feat, const float *pos, const int32_t *nbr, const 
     const float *rows = feat, *g_rows = grad_out;
     // The parameter gradients alone have nothing else to prepare unless tensors are copied: the packing would be a launch of its
     // own, which only a cloud in no order earns back.  K = 8, us without and with it: 32 -> 32, 4k points 8.7 and 10.8, 300k 59 and 63,
-    // 1M 173 and 180; 64 -> 64, 300k 96 and 100 (in no order 105 and 97).
-    const float *packed = grad_feat || p.copy_f || p.copy_g ? p.packed.in(ws, workspace_bytes) : nullptr;
+    // 1M 173 and 180; 64 -> 64, 300k 96 and 100 (in no order 105 and 97).  The tile kernels read the location tensor.
+    const float *packed = grad_feat || (!p.tile_params && (p.copy_f || p.copy_g)) ? p.packed.in(ws, workspace_bytes) : nullptr;
     const bool records = packed != nullptr && p.gather.route == FLEX_ROUTE_NARROW;       // made from the tensor as it is
     if (p.copy_g && (grad_theta || !records)) {
         prep.copy(grad_out, (float *)(ws + p.gT), B, N, Dout, p.c_out, bcn, 0);

@@ -129,3 +129,17 @@ def test_parameter_gradients_alone_pack_only_beside_copies():
         w.check()
         assert bool((w.ws[least:] != 0x5A).any()) == packs
         assert rel_err(gt.cpu().numpy(), oracle.flexconv_bwd(feat, pos, nbr, theta, bias, g)[1]) <= TOL
+
+
+@pytest.mark.parametrize("layout", [fx.BNC, fx.BCN], ids=["bnc", "bcn"])
+def test_parameter_gradients_on_tiles_pack_nothing(layout, B=2, N=700, K=8, Din=128, Dout=64):
+    """Their kernels read the location tensor, copies or not."""
+    pos, nbr, feat, theta, bias, g = random_problem(5, B, N, K, Din, Dout)
+    a = (to_layout(feat, layout), dev(pos), dev(nbr), dev(theta), dev(bias), to_layout(g, layout))
+    w = BestWorkspace(fx.OP_CONV_BWD, B, N, K, Din, Dout, layout)
+    least = fx.workspace_bytes(fx.OP_CONV_BWD, B, N, K, Din, Dout, layout)
+    w.ws[least:] = 0x5A
+    _, gt, gb = fx.flexconv_bwd(*a, layout=layout, in_edges=fx.flex_inedges_build(a[2]), need_feat=False, workspace=w.ws)
+    w.check()
+    assert bool((w.ws[least:] == 0x5A).all())
+    assert rel_err(gt.cpu().numpy(), oracle.flexconv_bwd(feat, pos, nbr, theta, bias, g)[1]) <= TOL
