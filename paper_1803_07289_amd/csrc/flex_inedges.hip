@@ -768,9 +768,14 @@ static int small_targets(int64_t B, int64_t N, int64_t Nc, int K)
     const int64_t edges = K * Nc, cus = device_cu_count();
     if (bucket_count(B * N, K) == 0 || edges > 3 << 13) return 0;
     const int64_t own = B * edges > 2048 * cus ? 4096 : 2048;
-    const int64_t targets = own / K < 1 ? 1 : own / K < BUCKET_TARGETS_MAX ? own / K : BUCKET_TARGETS_MAX;
+    auto clamped = [](int64_t x) { return x < 1 ? 1 : x < BUCKET_TARGETS_MAX ? x : BUCKET_TARGETS_MAX; };
+    int64_t targets = clamped(own / K);
+    // Lists over kept centres are short: where there is more than a workgroup a CU, as many edges are given more targets, and the five launches
+    // are overtaken earlier.  us, those, a workgroup to 2048 / K targets and this: 8 x 9.3k points, K = 9, to a quarter 19.9, 32.8 and 18.3; 30 x 1079, K = 32,
+    // 21.1, 32.0 and 18.3, to a half 24.5, 42 and those; 1000 x 100, K = 8, to a quarter 19.6, 25.3 and those.
+    if (B * cdiv64(N, targets) > cus) targets = clamped(own * N / edges);
     const int64_t groups = B * cdiv64(N, targets);
-    return groups <= 2048 && groups * edges <= cus << 15 ? (int)targets : 0;
+    return groups <= (Nc < N ? 768 : 2048) && groups * edges <= cus << (Nc < N ? 14 : 15) ? (int)targets : 0;
 }
 
 hipError_t launch_inedges_build(const int32_t *nbr, int B, int N, int K, int32_t *in_off,

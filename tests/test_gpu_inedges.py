@@ -116,6 +116,15 @@ def test_kept_centres_of_several_buckets(Ns):
     check(nbr, rng.permutation(40_000)[None, :Ns].astype(np.int32))
 
 
+# the one-launch build over kept centres: more than a workgroup a CU, and both sides of its lines (768 workgroups, 2^22 edges walked)
+@pytest.mark.parametrize("B,N,Ns,K", [(8, 9313, 2328, 9), (30, 1079, 269, 32), (30, 1079, 539, 32), (260, 40, 9, 5), (768, 50, 49, 3), (769, 50, 49, 3), (300, 300, 1, 2)])
+def test_kept_centres_of_many_small_clouds(B, N, Ns, K):
+    rng = np.random.default_rng(B + N)
+    nbr = rng.integers(0, N, size=(B, K, N)).astype(np.int32)
+    nbr[B // 2, 0] = N - 1
+    check(nbr, np.stack([rng.permutation(N)[:Ns] for _ in range(B)]).astype(np.int32))
+
+
 def check_large(nbr, sel=None):
     """The same on the device: the edges in (cloud, centre, slot) order, sorted by target without disturbing it."""
     B, K, N = nbr.shape
