@@ -313,8 +313,10 @@ int flex_inedges_build_sub(const int32_t *nbr, const int32_t *sel, int B, int N,
  * this is an exact search on a uniform grid).  nbr[b,k,l] = the point with the k-th smallest
  * squared distance to point l in cloud b, the point itself included (slot 0 unless an equal
  * point has a lower index), ordered by (d2, index): equal distances go to the LOWER INDEX.
- * d2 is evaluated in fp32 as ((dx*dx + dy*dy) + dz*dz), dx = pos[n] - pos[l], each operation
- * rounded separately; the result is the exact ranking under that d2.
+ * d2 is evaluated in fp32 as fma(dz, dz, fma(dx, dx, dy*dy)), dx = pos[n] - pos[l]; the result is
+ * the exact ranking under that d2.  (Under ((dx*dx + dy*dy) + dz*dz), each operation rounded
+ * separately, some two in 10^7 entries, of points whose distances agree to the last bit or so,
+ * would be others.)
  * Cost: every query scans the cells around it, so M points at one location (or closer together than the
  * cell edge, about the mean spacing) cost M*M distance evaluations; meant for clouds without such piles.
  * pos [B,3,N] finite; nbr int32 [B,K,N] overwritten.  K in 1..10, 12, 16, 24 or 32, K <= N;

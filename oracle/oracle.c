@@ -720,8 +720,9 @@ int oracle_idiss_sample(const float *phi, const uint32_t *u, int32_t *sel, int B
  * ordered by (d2 ascending, index ascending); equal d2 are broken by the LOWER INDEX.
  * d2 is evaluated in float, exactly as ((dx*dx + dy*dy) + dz*dz) with dx = pos[n] - pos[l]
  * and every operation rounded on its own (no fused multiply-add: build with
- * -ffp-contract=off), because the ranking is an integer-valued decision that both this
- * code and the library must take in the same precision.  nbr is int32 [B,K,N].
+ * -ffp-contract=off), because the ranking is an integer-valued decision.  The library takes
+ * it in the same precision, under fma(dz, dz, fma(dx, dx, dy*dy)): lists differ where
+ * distances agree to the last bit or so, in some two of 10^7 entries.  nbr is int32 [B,K,N].
  * ------------------------------------------------------------------------- */
 int oracle_knn(const float *pos, int32_t *nbr, int B, int N, int K)
 {

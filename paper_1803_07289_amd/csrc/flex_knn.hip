@@ -343,12 +343,11 @@ __global__ __launch_bounds__(256) void knn_sort_kernel(const int32_t *__restrict
     });
 }
 
-// Every operation rounded on its own.  (The pragma: __fmul_rn and __fadd_rn are plain operators to this compiler, which makes fused
-// multiply-adds of them, and one pair in some 10^6 whose distances differ in the last bit changed places.)
+// Two of the products are rounded with their sums: written out, so that every form of the search ranks by the same bits whatever a
+// compiler makes of operators.
 __device__ __forceinline__ float knn_d2(float dx, float dy, float dz)
 {
-#pragma clang fp contract(off)
-    return (dx * dx + dy * dy) + dz * dz;
+    return __builtin_fmaf(dz, dz, __builtin_fmaf(dx, dx, dy * dy));
 }
 
 // (d2, id) as one number whose order is theirs: the bits of d2 (non-negative: they order like the value) above those
