@@ -60,7 +60,7 @@ def test_hub_point_and_empty_lists():
 
 @pytest.mark.parametrize("B,N,K,Din,Dout", [
     (1, 1, 1, 128, 128), (1, 63, 7, 128, 256), (2, 65, 9, 256, 128), (3, 130, 16, 130, 70),
-    (1, 3001, 8, 1024, 128),     # six tiles per workgroup: the accumulators go into the running totals in between
+    (1, 3001, 8, 1024, 128),     # sixteen input blocks, three tiles per workgroup
 ])
 def test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout, layout=fx.BNC):
     say(f"tile parameter gradients: B={B} N={N} K={K} {Din}->{Dout} layout={layout}")
@@ -85,7 +85,7 @@ def test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout, layout=fx.BNC):
     (3, 700, 9, 640, 384),       # several clouds, a workgroup's tiles across them
 ])
 def test_parameter_gradients_in_blocks_of_128_channels(B, N, K, Din, Dout):
-    """Clouds of enough tiles for the wider blocks (wide_grad_plan)."""
+    """Clouds of enough tiles for the wider blocks (tile_grad_plan)."""
     test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout)
 
 
@@ -163,9 +163,40 @@ def test_parameter_gradients_of_narrow_layers_on_tiles(B, N, K, Din, Dout):
     test_parameter_gradients_of_wide_layers(B, N, K, Din, Dout)
 
 
-@pytest.mark.parametrize("N", [16 * 64 + 1, 64 * 64, 8129])     # 17 and 64 partials a block of 64 channels, 128 and one tile twice
-def test_partials_of_every_reduction(N):
-    test_parameter_gradients_of_wide_layers(1, N, 8, 128, 128)
+# (chunks of workgroups a block are the smaller of its tiles and its share of the 256 CUs)
+@pytest.mark.parametrize("partials,N,Din,Dout", [
+    (16, 16 * 64, 128, 128), (17, 16 * 64 + 1, 128, 128), (64, 64 * 64, 128, 128), (64, 8129, 128, 128),
+    (128, 24_513, 128, 128),                               # blocks of 128 channels
+    (127, 127 * 64, 64, 128), (128, 20_000, 64, 128),      # in fp32
+    (128, 128 * 64, 50, 50), (129, 128 * 64 + 1, 50, 50), (256, 256 * 64 + 1, 50, 50),
+])
+def test_partials_of_every_reduction(partials, N, Din, Dout):
+    """Up to 16 partials a block, up to 128 and more: a kernel each."""
+    say(f"{partials} partials")
+    test_parameter_gradients_of_wide_layers(1, N, 8, Din, Dout)
+
+
+@pytest.mark.parametrize("N,Din,Dout", [
+    (85 * 64 * 129 + 1, 129, 16),     # three blocks of 64 channels, 129 and 130 tiles a workgroup
+    (128 * 64 * 129 + 1, 65, 16),     # two, in fp32
+    (128 * 64 * 129 + 1, 65, 65),     # two of 128 channels
+])
+def test_parameter_gradients_of_more_tiles_than_a_chain_of_sums(N, Din, Dout):
+    """A workgroup's totals are written after 64 tiles, added to after 128 and once more at the end."""
+    say(f"tile parameter gradients, long chains: N={N} {Din}->{Dout}")
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    rand = lambda *shape: torch.rand(shape, generator=gen, device="cuda")
+    pos, feat, g = rand(1, 3, N), rand(1, N, Din) - 0.5, rand(1, N, Dout) - 0.5
+    near = torch.randint(-40, 41, (N,), generator=gen, device="cuda") + torch.arange(N, device="cuda")
+    nbr = near.clamp(0, N - 1).to(torch.int32).reshape(1, 1, N)
+    theta, bias = torch.zeros(3, Din, Dout, device="cuda"), torch.zeros(Din, Dout, device="cuda")
+    _, gt, gb = fx.flexconv_bwd(feat, pos, nbr, theta, bias, g, layout=fx.BNC, need_feat=False)
+    ids, up = nbr[0, 0].long(), g[0].double()
+    rows = feat[0].double()[ids]
+    assert rel_err(gb.cpu().numpy(), (rows.t() @ up).cpu().numpy()) <= TOL
+    for d in range(3):
+        ref = (rows * (pos[0, d].double()[ids] - pos[0, d].double())[:, None]).t() @ up
+        assert rel_err(gt[d].cpu().numpy(), ref.cpu().numpy()) <= TOL
 
 
 @pytest.mark.parametrize("Din,Dout", [(64, 13), (64, 9), (128, 128), (70, 90), (64, 64)])
