@@ -120,9 +120,10 @@ __device__ __forceinline__ double reduce_segment(const float *__restrict__ parti
 // four elements reads them all.  512 x 512 channels, four partials per block: 9 us (61 in the form above, most of whose
 // threads would have nothing to read).
 constexpr int REDUCE_FEW = 16;
-// Up to here 16 partials at a time, workgroups of 256 threads: most of 1024 would have nothing to read.  Parameter gradients, us, 64
-// partials at a time and 16: 256 -> 256, 4k points (32 partials) 43.3 and 32.5, 2k (32) 39.3 and 28.5; 128 -> 128, 4k (63) 22.2 and
-// 20.0, 12k (64) 28.8 and 27.0, 30k (128) 41.5 and 40.9, 60k (128) 60.8 and 60.9.
+// Up to here 16 partials at a time, workgroups of 256 threads: most of 1024 would have nothing to read.  Parameter gradients, us (replayed
+// from a graph), 64 partials at a time and 16: 32 -> 32, 1k points (32 partials) 7.97 and 7.71, 2k (64) 8.51 and 8.02, 4k (128) 9.13 and
+// 9.07; 64 -> 64, 2k (64) 11.15 and 10.85, 4k (128) 13.27 and 13.20; 9 -> 64, 4k 8.57 and 8.55; 64 -> 128, 3k (47) 18.0 and 17.1, 20k (128)
+// 33.8 and 33.5; 128 -> 128, 4k (64) 22.95 and 20.74, 24k (128) 37.4 and 37.1; 256 -> 256, 4k (16 blocks of 16 to 32) 43.3 and 32.5.
 constexpr int REDUCE_SOME = 128;
 __global__ __launch_bounds__(256) void reduce_partials_few_kernel(const float *__restrict__ partials, const ReduceArgs p,
                                                                   float *__restrict__ grad_theta,
