@@ -525,7 +525,7 @@ __device__ __forceinline__ void sort_short(int *p, int d)
 // Lists of up to W edges are sorted by a thread each, up to 64 by a wave, longer ones by the whole workgroup.  What bounded it was LDS:
 // a rank for every edge, by reading all of its list, is some 13 reads an edge at K = 8 with 64 lanes in as many places (the longest list of
 // a wave's counts), and the arrays for it left one workgroup to a CU; a list in registers is read and written once, target and slot share
-// a register, and two workgroups fit.  us of the build, ranks and so: 1M points, K = 8, 135 and 104 (Z-order 121 and 91), 100k, K = 16, 64
+// a register, and two workgroups fit (in 64 registers a thread: one is spilled, six with W = 32).  us of the build, ranks and so: 1M points, K = 8, 135 and 104 (Z-order 121 and 91), 100k, K = 16, 64
 // and 52, 500k, K = 16, 167 and 116, K = 12 110 and 76, 400k, K = 10, 84 and 61, 200k, K = 32, 199 and 156.  With W = 32 at K = 16 the
 // 100k were 66.
 template <int W>

@@ -157,10 +157,6 @@ struct StepWalk {
 // Lane's channels of a row in input block ib: past the row's end the last four again, put right after the sums.
 __device__ __forceinline__ int tile_lane_channel(const TileArgs &a, int ib) { return min(ib * 64 + 4 * ((int)threadIdx.x & 15), a.w_in - 4); }
 
-// What a gathering wave does: the sums of its eight points (from `first` of every tile) over input blocks ib0 .. ib0 + n_in - 1,
-// acc[pass][channel][component]; park(acc, ib, point) takes them when a (tile, input block) is complete, HALVES: park(acc[pass], pass)
-// those of the first four points and of the second four as each is.
-// Eight rows are in flight at all times.
 // Four channels (X: numbers, or sums of several components) that were read `shift` places early, back in their own places: what lies
 // past the row's end becomes zero.
 template <class X>
@@ -177,6 +173,11 @@ __device__ __forceinline__ void put_channels_right(X &&c, int shift)
     }
 }
 
+// What a gathering wave does: the sums of its eight points (from `first` of every tile) over input blocks ib0 .. ib0 + n_in - 1,
+// acc[pass][channel][component]; park(acc, ib, point) takes them when a (tile, input block) is complete, HALVES: park(acc[pass], pass)
+// those of the first four points and of the second four as each is.
+// Eight rows are in flight at all times.
+//
 // How a slot's row is weighed with its (dx, dy, dz, 1).  MX: by outer products on the matrix cores (outer_slot): an entry is
 // then needed once per wave, in the layout lane = 16 * point + 4 * slot + component, and its row's offset, the fourth
 // component, reaches the address by a DPP add.  Else by fused multiply-adds, every lane reading its point's entry from LDS,
