@@ -487,7 +487,7 @@ static bool padded_shape(int Din, int Dout, int *DIp, int *DOp)
 // Do the parameter gradients run on the 64-point tile kernels, at the tensors' own widths?  (k_in, k_out): the listed widths.
 // - Where a side is wider than 64 channels, always: 64 and 128 channels ran a workgroup's points in one chain of sums, other widths on
 //   zero-padded copies.  us, K = 8, those and tiles: 64 -> 128, 3k points 23.9 and 17.2, 20k 47 and 33, 300k 378 and 236; 128 -> 64, 300 points
-//   14.0 and 14.2, 3k 25.2 and 17.2, 300k 489 and 233; 100 -> 50, 3k 30.3 and 17.3, 300k 556 and 221; 3 -> 100, 300k 439 and 246; 160 -> 160,
+//   14.0 and 14.2, 3k 25.2 and 17.2, 300k 489 and 233; 100 -> 50, 3k 30.3 and 17.3, 300k 556 and 221; 3 -> 100, 300k 439 and 171; 160 -> 160,
 //   3k 42 and 22, 300k 1124 and 650.
 // - Below that the wave-specialised kernels take fewer points at a time.  Point-major tensors that they need copies of: at 64 x 64 channels
 //   from 8k points on (all gradients, copies and tiles: 50 -> 50, 3k 30.8 and 31.1, 20k 45.8 and 44.7, 300k 210 and 165; 33 -> 64, 3k 28.3

@@ -581,8 +581,10 @@ void tile_conv_kernel(const TileArgs a)
 // and 6.8e-8.  A tile's points are summed eight at a time and those sums in pairs: 2-norm error 64 -> 128 at 64, 4k, 30k and 200k points
 // 0.9e-7, 0.9e-7, 1.0e-7, 1.3e-7 (chains over a workgroup's points: 1.2e-7, 1.2e-7, 2.0e-7, 5.0e-7).  The fp32 op holds the vector ALU
 // with the matrix cores (8192 clocks a tile), so that gathering and contracting add up: 300k points 236 us, 128 -> 64 233.
+// SOME: contracting waves whose channels all lie past the rows' ends have no sums (the reduction drops their part of the partial) and
+// leave the vector ALU to the others; the launch says from where on.
 // ---------------------------------------------------------------------------
-template <bool F32>
+template <bool F32, bool SOME>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, int n_ho, float *__restrict__ partials)
 {
@@ -660,6 +662,8 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
         }
     };
 
+    const bool idle = SOME && __builtin_amdgcn_readfirstlane(IC * hi + 16 * wm >= a.w_in || OC * ho + 16 * wn >= a.w_out);
+
     TileWalk tw(sc, a.tpc);
     v4f gv[2];                             // upstream gradient of a tile: two four-float chunks per thread
     const int g_col = OC * ho + 4 * (ctid & 15), g_at = min(g_col, a.w_out - 4);      // past the row's end the last four again
@@ -697,6 +701,7 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
         if (k % FLUSH == 0 && k > 0) flush(k > FLUSH);
         __syncthreads();                   // the tile is complete
         if constexpr (F32) {
+            if (idle) continue;
             // Sixteen points of a row block at a time, as two chains of eight; what they leave is added, in pairs over the tile, while
             // the next ones run.
             constexpr int SETS = T / 16;
@@ -773,6 +778,7 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
         }
     }
 
+    if (idle) return;                      // (their part of the partial is read and dropped)
     flush(tiles > FLUSH);                  // a workgroup without tiles still writes its (zero) partial
 }
 
@@ -786,8 +792,8 @@ void tile_grad_theta_kernel(const TileArgs a, const float *__restrict__ g_rows, 
 // and 759 with the contracting waves' priority raised; blocks of 64 channels in halves lose, 1005 -> 1050.)
 // Sums and their rounding are those of the kernel above, and the chains half as long: 2-norm error 128 -> 128 at 30k points 1.2e-7 ->
 // 1.1e-7, at 200k 2.0e-7 -> 1.6e-7, at 1M 2.27e-7 -> 2.25e-7.
-// What bounds it: the matrix cores 56 percent of the time, the vector ALU as much, LDS 27 (counters at 128 -> 128, 1M points); the
-// contraction alone would take 520 us of the 759, the gathering alone 415.  us, 64 channels a block -> 128: 128 -> 128, 1M points
+// What bounds it: no unit alone; at 128 -> 128, 1M points, the matrix cores are busy 51 percent of the time, the vector ALU 74 (four clocks an
+// instruction, matrix ops among them), no bank conflicts; the contraction alone would take 520 us of the 759, the gathering alone 415.  us, 64 channels a block -> 128: 128 -> 128, 1M points
 // 960 -> 759; 256 -> 256, 250k 918 -> 760; 512 -> 512, 109k 1600 -> 1240; K = 16: 1290 -> 940, 1246 -> 905, 2130 -> 1540.
 // ---------------------------------------------------------------------------
 

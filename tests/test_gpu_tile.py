@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import paper_1803_07289_amd as fx
-from gpu_util import TOL, dev, to_layout, from_layout, say
+from gpu_util import TOL, ExactWorkspace, dev, to_layout, from_layout, say
 from helpers import rel_err
 from test_gpu_parity import random_problem
 
@@ -124,6 +124,24 @@ def test_parameter_gradients_of_one_point_are_products_rounded_once(Din, Dout, N
     assert np.array_equal(gb, f[:, None] * up[None])
     for d in range(3):
         assert np.array_equal(gt[d], ((pos[0, d, n] - pos[0, d, at]) * f)[:, None] * up[None])
+
+
+# sides that end in every part of 16 channels of a block: contracting waves without a channel write nothing
+@pytest.mark.parametrize("Din,Dout", [(3, 100), (16, 65), (17, 80), (48, 81), (49, 96), (64, 97), (65, 16), (80, 17), (81, 33), (112, 64), (128, 1)])
+@pytest.mark.parametrize("N", [130, 9000])
+def test_fp32_parameter_gradients_take_nothing_from_what_the_workspace_held(Din, Dout, N, K=5):
+    say(f"tile parameter gradients in a used workspace, N={N} {Din}->{Dout}")
+    pos, nbr, feat, theta, bias, g = random_problem(15, 1, N, K, Din, Dout)
+    a = (to_layout(feat, fx.BNC), dev(pos), dev(nbr), dev(theta), dev(bias), to_layout(g, fx.BNC))
+    ws = ExactWorkspace(fx.OP_CONV_BWD_BUILD, 1, N, K, Din, Dout, fx.BNC)
+    ws.ws.fill_(0xFF)
+    _, gt, gb = fx.flexconv_bwd(*a, layout=fx.BNC, need_feat=False, workspace=ws.ws)
+    ws.check()
+    p, f, up = (x[0].astype(np.float64) for x in (pos, feat, g))
+    rows = f.T[nbr[0]]
+    assert rel_err(gb.cpu().numpy(), rows.sum(axis=0).T @ up.T) <= TOL
+    for d in range(3):
+        assert rel_err(gt[d].cpu().numpy(), ((p[d][nbr[0]] - p[d])[:, :, None] * rows).sum(axis=0).T @ up.T) <= TOL
 
 
 @pytest.mark.parametrize("Din,Dout", FP32_WIDTHS)
