@@ -473,10 +473,10 @@ __device__ __forceinline__ void knn_search(const float4 *__restrict__ rec, const
 }
 
 // Waves a SIMD that the K best in registers leave room for; S: lanes to a point.  (Left to itself the compiler takes two registers more
-// at some K, and a wave less.)
+// at some K, and a wave less.  One thread and K = 9: the same four waves either way, and 158k points of a room take 190 us bound to four, 182 not.)
 constexpr int knn_waves(int K, int S)
 {
-    return K <= 2 ? 7 : K <= 4 ? (S == 1 ? 7 : S == 16 && K == 4 ? 5 : 6) : K <= 6 ? 5 : K <= 8 ? (S <= 4 ? 5 : 4) : K <= 12 ? 4 : K <= 16 ? 3 : 2;
+    return K <= 2 ? 7 : K <= 4 ? (S == 1 ? 7 : S == 16 && K == 4 ? 5 : 6) : K <= 6 ? 5 : K <= 8 ? (S <= 4 ? 5 : 4) : K == 9 && S == 1 ? 1 : K <= 12 ? 4 : K <= 16 ? 3 : 2;
 }
 
 template <int K>
