@@ -50,11 +50,29 @@ __device__ __forceinline__ PartTile xcd_part_tile(int64_t total_tiles, int parts
     const int part = (int)((unsigned)at / (unsigned)total_tiles);       // (a grid has fewer than 2^24 workgroups of 256 threads)
     return PartTile{part + (int)blockIdx.y, parts * (int)gridDim.y, at - part * total_tiles};
 }
-// every 16 channels a part of their own, as far as the grid reaches
-static inline int all_parts(int64_t tiles, int C)
+// A part's channels in chunks of CH, one to a wave at a time.  The chunks are dealt evenly: with 16 channels to every part but the last, the
+// XCDs that take the last one's tiles would be done early (C = 37: two parts of 16 and one of 5).
+struct PartChunks { int first, end; };
+__device__ __forceinline__ PartChunks part_chunks(const PartTile &pt, int chunks)
 {
-    const int64_t most = (C + 15) / 16, reach = ((1 << 24) - 8) / (tiles > 0 ? tiles : 1);
+    const int each = chunks / pt.parts, more = chunks - each * pt.parts;
+    const int first = pt.part * each + min(pt.part, more);
+    return PartChunks{first, first + each + (pt.part < more ? 1 : 0)};
+}
+// every 4 * waves channels a part of their own, as far as the grid reaches
+static inline int all_parts(int64_t tiles, int C, int waves = 4)
+{
+    const int64_t most = (C + 4 * waves - 1) / (4 * waves), reach = ((1 << 24) - 8) / (tiles > 0 ? tiles : 1);
     return (int)std::max<int64_t>(1, std::min(most, reach));
+}
+// Waves a workgroup with which parts leave hardly a wave without a chunk (whose place no other workgroup gets before this one's waves are
+// all done), 0: none
+static inline int part_waves(int C)
+{
+    const int chunks = (C + 3) / 4;
+    for (const int w : {4, 3})
+        if (((chunks + w - 1) / w * w - chunks) * 16 <= chunks) return w;
+    return 0;
 }
 
 // Point-major, C >= 4: one thread per (point, 4 channels); a block owns PT consecutive points.
@@ -136,7 +154,7 @@ __device__ __forceinline__ int row_bcast(int x)
 }
 
 // Channel-major ([B,C,N]) forward.  A block owns 64 consecutive centres of one cloud: lane = centre, so
-// the ids, the outputs and the winner table move as whole 256-byte rows, and the four waves split the
+// the ids, the outputs and the winner table move as whole 256-byte rows, and the waves split the
 // channels in chunks of CH.  A thread requests CH x 8 values (4 bytes each, from CH channel rows) before
 // it compares; the ids of the first eight slots are read once for all channels.
 // sel == nullptr: every point is a centre (L = N); else the centres are sel[b, 0..L).
@@ -164,7 +182,8 @@ __global__ __launch_bounds__(256) void pool_fwd_bcn_kernel(const float *__restri
     int n0[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) n0[u] = nb[(int64_t)min(u, K - 1) * N];      // past K: the last slot again
-    for (int c0 = (pt.part * 4 + w) * CH; c0 < C; c0 += 4 * CH * pt.parts) {
+    const PartChunks mine = part_chunks(pt, (C + CH - 1) / CH);
+    for (int c0 = (mine.first + w) * CH; c0 < mine.end * CH; c0 += (int)(blockDim.x >> 6) * CH) {
         const float *row[CH];
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch) row[ch] = feat + (b * C + min(c0 + ch, C - 1)) * N;
@@ -252,9 +271,12 @@ hipError_t launch_pool_fwd(const float *feat, const int32_t *nbr, float *out, in
         // us, all channels a workgroup | dealt over grid.y to fill the device | part by part, K = 8, Z-order: 2k points x 112 channels 11.7 | 4.2 | 4.2,
         // 26k x 128, K = 12, 51 | 40 | 37, 77k x 128 108 | 109 | 86, 1M x 128 777 | 783 | 765; in the order drawn: 2k x 112 15 | 4.8 | 4.7, 63k x 113, K = 6,
         // 215 | 247 | 178, 77k x 128 503 | 501 | 336, 250k x 128 1438 | 1428 | 594
-        const int parts = all_parts(tiles, C);
-        hipLaunchKernelGGL(pool_fwd_bcn_kernel<4>, dim3(xcd_grid(tiles * parts)), dim3(256), 0, s, feat, nbr,
-                           (const int32_t *)nullptr, out, argmax, N, N, K, C, tpc, tiles, parts);
+        // Widths whose parts would have idle waves keep their channels together: part by part and so, 8 neighbours, Z-order 200k x 17 28.6 and 24.4, x 50
+        // 66 and 57, 5.9k x 37 8.5 and 7.1; in the order drawn 235 and 247, 810 and 836, 13.9 and 11.2.  With three waves 200k x 33 40.1 and 40.9, in the
+        // order drawn 419 and 519.
+        const int waves = part_waves(C), parts = waves ? all_parts(tiles, C, waves) : 1;
+        hipLaunchKernelGGL(pool_fwd_bcn_kernel<4>, dim3(xcd_grid(tiles * parts), waves ? 1 : channel_parts(tiles, C, 2048)), dim3(waves ? 64 * waves : 256),
+                           0, s, feat, nbr, (const int32_t *)nullptr, out, argmax, N, N, K, C, tpc, tiles, parts);
     } else {
         const int64_t total = (int64_t)B * N * C;
         int64_t blocks = (total + 255) / 256;
@@ -1082,8 +1104,10 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
     __syncthreads();
     const int E0 = s_off[0], E1 = s_off[64];
     const int my0 = s_off[lane], my1 = s_off[lane + 1];
-    for (int cg = pt.part * 4 * CH; cg < C; cg += 4 * CH * pt.parts) {
+    const PartChunks mine = part_chunks(pt, (C + CH - 1) / CH);
+    for (int cg = mine.first * CH; cg < mine.end * CH; cg += 4 * CH) {
         const int c0 = cg + w * CH;
+        const bool busy = c0 < mine.end * CH;
         const int32_t *arow[CH];
         const float *grow[CH];
 #pragma unroll
@@ -1119,7 +1143,7 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
             __syncthreads();
 #pragma unroll
             for (int j0 = 0; j0 < J; j0 += U) {
-                if (j0 * 64 < nEc) {
+                if (busy && j0 * 64 < nEc) {
                     int l[U], t[U], m[U], a[CH][U];
                     float g[CH][U];
 #pragma unroll
@@ -1157,6 +1181,7 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
                 }
             }
             // rows w*CH.. of s_c are written and read by this wave only, whose LDS operations keep their order
+            if (busy)
 #pragma unroll 1
             for (int i = lo; i < hi; ++i)
 #pragma unroll
@@ -1164,7 +1189,7 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
         }
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch)
-            if (lane < np && c0 + ch < C)
+            if (busy && lane < np && c0 + ch < C)
                 __builtin_nontemporal_store(acc[ch], &grad_feat[(b * C + c0 + ch) * N + m0 + lane]);
     }
 }
