@@ -52,12 +52,15 @@ __device__ __forceinline__ PartTile xcd_part_tile(int64_t total_tiles, int parts
 }
 // A part's channels in chunks of CH, one to a wave at a time.  The chunks are dealt evenly: with 16 channels to every part but the last, the
 // XCDs that take the last one's tiles would be done early (C = 37: two parts of 16 and one of 5).
-struct PartChunks { int first, end; };
+// Dealt over grid.y: a wave's chunk after the other in turn.
+struct PartChunks { int first, end, step; };
 __device__ __forceinline__ PartChunks part_chunks(const PartTile &pt, int chunks)
 {
+    const int waves = (int)(blockDim.x >> 6);
+    if (gridDim.y > 1) return PartChunks{pt.part * waves, chunks, pt.parts * waves};
     const int each = chunks / pt.parts, more = chunks - each * pt.parts;
     const int first = pt.part * each + min(pt.part, more);
-    return PartChunks{first, first + each + (pt.part < more ? 1 : 0)};
+    return PartChunks{first, first + each + (pt.part < more ? 1 : 0), waves};
 }
 // every 4 * waves channels a part of their own, as far as the grid reaches
 static inline int all_parts(int64_t tiles, int C, int waves = 4)
@@ -183,7 +186,7 @@ __global__ __launch_bounds__(256) void pool_fwd_bcn_kernel(const float *__restri
 #pragma unroll
     for (int u = 0; u < U; ++u) n0[u] = nb[(int64_t)min(u, K - 1) * N];      // past K: the last slot again
     const PartChunks mine = part_chunks(pt, (C + CH - 1) / CH);
-    for (int c0 = (mine.first + w) * CH; c0 < mine.end * CH; c0 += (int)(blockDim.x >> 6) * CH) {
+    for (int c0 = (mine.first + w) * CH; c0 < mine.end * CH; c0 += mine.step * CH) {
         const float *row[CH];
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch) row[ch] = feat + (b * C + min(c0 + ch, C - 1)) * N;
@@ -1105,7 +1108,7 @@ __global__ __launch_bounds__(256) void pool_bwd_gather_bcn_kernel(
     const int E0 = s_off[0], E1 = s_off[64];
     const int my0 = s_off[lane], my1 = s_off[lane + 1];
     const PartChunks mine = part_chunks(pt, (C + CH - 1) / CH);
-    for (int cg = mine.first * CH; cg < mine.end * CH; cg += 4 * CH) {
+    for (int cg = mine.first * CH; cg < mine.end * CH; cg += mine.step * CH) {
         const int c0 = cg + w * CH;
         const bool busy = c0 < mine.end * CH;
         const int32_t *arow[CH];
